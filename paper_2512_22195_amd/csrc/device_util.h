@@ -33,6 +33,33 @@ __device__ __forceinline__ uint2 ldg8(const void* p) {
     return make_uint2(r.x, r.y);
 }
 
+// ---- global memory straight into LDS ------------------------------------------------------------
+// One instruction moves 16 bytes per lane from sbase + voff (voff: per-lane byte offset) to LDS
+// bytes lds + 16 * lane (lds: byte address, the same in every lane).  No register holds the data,
+// so what is in flight is bounded by LDS alone, and the copy counts like a load: in order, on
+// vmcnt.  The compiler does not see these copies: dma_wait<N>() - all but the wave's N youngest
+// copies have landed - and a barrier stand between a copy and the reads of its bytes by any wave,
+// and a barrier between those reads and the next copy onto the same bytes.
+__device__ __forceinline__ void dma16(const void* sbase, uint32_t voff, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :: "s"(lds), "v"(voff), "s"(sbase) : "memory", "m0");
+}
+// The same with 4 bytes per lane (LDS bytes lds + 4 * lane).
+__device__ __forceinline__ void dma4(const void* sbase, uint32_t voff, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
+                 :: "s"(lds), "v"(voff), "s"(sbase) : "memory", "m0");
+}
+template <int N>
+__device__ __forceinline__ void dma_wait() {
+    static_assert(N >= 0 && N <= 63, "vmcnt has six bits");
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
+}
+// Byte address of an LDS object, as dma16 takes it (the object counts as written from here on).
+__device__ __forceinline__ uint32_t lds_address(void* p) {
+    typedef __attribute__((address_space(3))) char* lptr;
+    return (uint32_t)(uintptr_t)(lptr)p;
+}
+
 // Agent-scope relaxed accesses: coherent across the chip's L2 slices without cache flushes.
 __device__ __forceinline__ void st_agent2(float* p, float x, float y) {
     const uint64_t v = (uint64_t)__float_as_uint(x) | ((uint64_t)__float_as_uint(y) << 32);
@@ -41,6 +68,22 @@ __device__ __forceinline__ void st_agent2(float* p, float x, float y) {
 __device__ __forceinline__ float2 ld_agent2(const float* p) {
     const uint64_t r = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return make_float2(__uint_as_float((uint32_t)r), __uint_as_float((uint32_t)(r >> 32)));
+}
+
+// The same for 16 bytes.  The loads are not waited for: ld_agent_wait stands between a batch of
+// them and the first use of their registers.
+typedef float f32x4v __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void st_agent4(float* p, f32x4v v) {
+    asm volatile("global_store_dwordx4 %0, %1, off sc1" :: "v"(p), "v"(v) : "memory");
+}
+__device__ __forceinline__ void ld_agent4(f32x4v& v, const float* p) {
+    asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(v) : "v"(p) : "memory");
+}
+template <int N>
+__device__ __forceinline__ void ld_agent_wait(f32x4v (&v)[N]) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < N; ++i) asm volatile("" : "+v"(v[i]));
 }
 
 // One workgroup's arrival at a counter: every thread has waited for its own agent-scope stores,

@@ -219,9 +219,6 @@ __global__ __launch_bounds__(kWavesPerBlock * KS * 64) void materialize_gemv_ker
     }
 }
 
-constexpr int kGemmMinRows = 64;
-constexpr int kSkinnyMinRows = 32;
-
 bool gemv_supported(const MaterializeArgs& a, int dtype) {
     return dtype == MATKV_BF16 && ((a.Hd % 4096) == 0 || (a.Hd % 3072) == 0);
 }
@@ -270,22 +267,17 @@ hipError_t launch_rows(const MaterializeArgs& a, int total_rows, hipStream_t s) 
 hipError_t launch_materialize(const MaterializeArgs& a, int dtype, hipStream_t s) {
     const int total_rows = a.n_tokens;
     if (total_rows <= 0) return hipSuccess;
-    // a decode step of a batch: the GEMV form reads the weights once per 4 rows; from 16 rows on
-    // the matrix cores take over where the skinny form that stages rows through LDS exists (hidden
-    // a multiple of 1024; 16 rows at hidden 4096 / 8192: 8.0 / 14.8 us against 9.7 / 20.7, 31 rows
-    // 8.0 / 13.5 against 16.1 / 33.6), from 32 rows on elsewhere (skinny forms, then the tiled GEMM)
     // up to 16 rows (a decode step): the staged form cut into 256 workgroups where it is ahead of the
     // GEMV form (per layer, every layer's weights from HBM: 4 rows at hidden 8192 10.9 -> 9.0 us,
     // 16 rows at hidden 4096 10.4 -> 7.9 us; one row at hidden 4096 5.8 us against 6.1: GEMV kept)
     if ((total_rows >= 8 || a.Hd >= 8192) && materialize_fewrows_supported(a, dtype, total_rows))
         return launch_materialize_fewrows(a, total_rows, s);
-    const int skinny_min = (a.Hd % 1024) == 0 ? 16 : kSkinnyMinRows;
-    if (gemv_supported(a, dtype) && total_rows < kGemmMinRows &&
-        !(total_rows >= skinny_min && materialize_mfma_supported(a, dtype, total_rows) && (a.Hd % 512) == 0))
+    // the GEMV form reads the weights once per 4 rows: the matrix cores take over from 16 rows on (16
+    // rows at hidden 4096 / 8192: 8.0 / 14.8 us against 9.7 / 20.7, 31 rows 8.0 / 13.5 against 16.1 / 33.6)
+    if (gemv_supported(a, dtype) && (total_rows < 16 || !materialize_mfma_supported(a, dtype, total_rows)))
         return launch_gemv(a, total_rows, s);
     if (materialize_mfma_supported(a, dtype, total_rows)) return launch_materialize_mfma(a, total_rows, s);
     if (dtype == MATKV_F32) return launch_rows<float>(a, total_rows, s);
-    if (gemv_supported(a, dtype)) return launch_gemv(a, total_rows, s);
     return launch_rows<uint16_t>(a, total_rows, s);
 }
 

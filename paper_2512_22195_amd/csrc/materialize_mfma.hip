@@ -4,9 +4,8 @@
 // Both operands are contiguous along the contraction (hidden) axis, which is what the
 // matrix-core operand layout wants: a lane's 8 consecutive bf16 of one row.
 //
-// Three forms by row count: the tiled GEMM (128 x 128 tiles, below), and two skinny forms for a
-// few hundred rows at most (a question, a decode step of a large batch), whose eight waves split
-// the hidden axis.  In all of them the two features of a rotary pair sit in the same lane, so the
+// Three forms by row count: the tiled GEMM (below), a skinny form for up to 128 rows (a question) and
+// one for a handful (a decode step of a batch), whose eight waves split the hidden axis.  In all of them the two features of a rotary pair sit in the same lane, so the
 // rotation is lane-local on the fp32 accumulators, and values are rounded to bf16 once, on store.
 #include <type_traits>
 
@@ -72,321 +71,277 @@ __device__ __forceinline__ void rope_cs(const RopeEntry& e, float p, float& c, f
     s = __builtin_amdgcn_sinf(fr);
 }
 
-// ---- tiled GEMM: 128 x 128 tiles, the hidden axis split over SK workgroups ---------------------
-// A workgroup owns 128 tokens x one head of K or of V (128 features: both halves of every rotary
-// pair); 64 hidden columns per step through double-buffered LDS tiles fed from four rotating
-// register stages (loads carry no branch - past the end they repeat the last step - and the
-// loop has one exit, so the compiler counts the loads in flight instead of draining them).
-// LDS rows are 160 bytes: the 16-byte operand reads of 16 rows measured 4.5 cycles per
-// instruction with them, 8.6 with 144.
-// The launch is bound by what the L2s hand to the compute units, every workgroup reading its
-// token rows and its weight rows over the whole hidden axis: 64 x 128 tiles (the earlier form)
-// moved 393 MB for a 1000-token chunk at hidden 4096 against 25 MB of distinct operands, these
-// tiles a third less.  Where 128 x 128 tiles alone would leave half of the chip idle (up to 1024
-// rows with 8 KV heads), two workgroups share a tile, each over half of the hidden axis: both
-// leave their fp32 partial in the workspace (agent-scope stores), arrive at the tile's counter,
-// and the one that arrives second adds the other's partial to its own and runs the epilogue.
-// Measured, us per launch at hidden 4096 / 8192 (8 KV heads), against the 64 x 128 forms this
-// replaced (eight waves up to 1000 rows, four waves beyond): 512 rows 30.6 / - (33.1 / -),
-// 1000 rows 34.0 / 57.9 (35.9 / 67.6), 1206 rows 46.9 / 88.7 (56.7 / 103.4), 2048 rows
-// 50.2 / 96.0 (62.8 / 111.4), 8192 rows 173 / 315 (185 / 327).
-// The work is split between waves.  In a first form every wave did everything - requested the
-// next operands, moved a tile into LDS, read operands back, multiplied - and the barrier kept
-// all eight in the same phase, so a step lasted as long as its phases added up.  Now waves 4-7
-// only move data (global -> registers -> LDS, four steps of loads in flight) and waves 0-3, one
-// per SIMD, only read operands and multiply (2 x 2 waves, 64 tokens x the 16-feature blocks
-// {2wn, 2wn+1, 2wn+4, 2wn+5} each), so the load path and the LDS writes of step i + 1 run beside
-// the matrix work of step i (1206 rows at hidden 4096 / 8192: 48.9 / 90.0 -> 45.8 / 80.0 us, 2048
-// rows 52.1 / 95.4 -> 48.5 / 86.0; 1000 rows and 8192 rows unchanged).
-template <int SK>
-__global__ __launch_bounds__(512, 2) void materialize_mfma128_kernel(MaterializeArgs a, int total_rows) {
-    constexpr int BM = 128, BKS = BK, STR = BKS + 16;
-    constexpr int A_ELEMS = BM * STR, B_ELEMS = D * STR;
-    __shared__ __attribute__((aligned(16))) uint16_t tiles[2 * (A_ELEMS + B_ELEMS)];
-    RowDest* const sm_dest = reinterpret_cast<RowDest*>(tiles);
-    int* const sm_last = reinterpret_cast<int*>(sm_dest + BM);
+// ---- tiled GEMM ----------------------------------------------------------------------------------
+// A workgroup of eight waves owns 32 MI token rows x one head of K or of V (128 features: both halves
+// of every rotary pair), over the whole hidden axis or (SK = 2) over half of it.  What bounds it is
+// the path from L2 into a compute unit: a read of L2-resident memory peaks at 110 GB/s per compute
+// unit with the chip full (46 bytes a cycle, whether the bytes go to registers or to LDS), and a step
+// of 64 hidden columns brings 16 KB of weights whatever the tile's height.  So a launch takes as long
+// as one workgroup's operands take to arrive, and the choices follow from that:
+//  - operands go from global memory straight into LDS (dma16): no registers, no LDS write
+//    instructions, as many steps in flight as LDS holds (six of 24 KB at MI = 2, three of 48 KB at
+//    MI = 8), one barrier per step.  The form this replaced moved operands through registers with
+//    four of its eight waves and reached 17 bytes a cycle.
+//  - LDS rows are unpadded 128 bytes (the copy writes 1 KB runs); the eight 16-byte pieces of row r
+//    are permuted by (r >> 1) & 7 instead - the copy picks its global addresses accordingly - which
+//    spreads an operand read of sixteen rows over all banks.
+//  - half a step is multiplied while the operands of the next half are on their way from LDS.
+//  - finished tiles leave through LDS as whole 256-byte rows.
+// Two workgroups that share a tile (SK = 2) leave their fp32 partials in the workspace (agent-scope
+// stores), arrive at the tile's counter, and the second to arrive adds the other's and finishes.
+// Measured, us per launch with every layer's weights from HBM, 8 KV heads, before -> now:
+//   hidden 4096:  256 rows 21.9 -> 17.3, 512 rows 32.3 -> 21.4, 1000 rows 34.5 -> 28.5, 1206 rows
+//                 45.6 -> 33.5, 2048 rows 48.5 -> 42.3, 3501 rows 83 -> 62, 8192 rows 168 -> 133
+//   hidden 8192:  512 rows 62.6 -> 36.3, 1000 rows 53 -> 48, 2048 rows 83 -> 72, 4096 rows 156 -> 121
+// Tried and left out: starting every workgroup at another hidden column (no channel of the L2s is
+// favoured by the power-of-two row strides: no change), an extra wave that touches the weight rows
+// some steps ahead (-12 % at 512 rows of hidden 8192, +20 % at 64 rows, nothing at 1000).
+template <int MI> struct TileShape {
+    static constexpr int BM = 32 * MI;                              // token rows of a workgroup
+    static constexpr int ROWS = BM + D;                             // LDS rows of a step: tokens, then weight rows
+    static constexpr int STEP_BYTES = ROWS * BK * 2;
+    static constexpr int NBUF = 158 * 1024 / STEP_BYTES;            // steps that fit in LDS
+};
+
+// WN: waves along the features; the other 8 / WN split the rows.  Few waves along the features read
+// fewer LDS bytes per product from MI = 8 on (68 -> 64 us at 3501 rows), where LDS becomes the limit.
+template <int MI, int WN, int SK>
+__global__ __launch_bounds__(512) void materialize_tile_kernel(MaterializeArgs a, int total_rows, int row_tiles) {
+    typedef TileShape<MI> S;
+    constexpr int WM = 8 / WN, XB = 2 * MI / WM, PB = 4 / WN;       // waves along the rows; row blocks and pair blocks of a wave
+    constexpr int BM = S::BM, NBUF = S::NBUF, OSTR = D + 8;         // OSTR: bf16 per LDS row of the finished tile
+    static_assert(BM * OSTR * 2 + BM * (int)sizeof(RowDest) <= NBUF * S::STEP_BYTES, "epilogue fits over the dead buffers");
+    __shared__ __attribute__((aligned(16))) char smem[NBUF * S::STEP_BYTES];
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int c16 = lane & 15, g4 = lane >> 4;
-    const int kv = blockIdx.x / a.Hkv, head = blockIdx.x % a.Hkv;
-    const int row0 = blockIdx.y * BM;
-    const int part = blockIdx.z;
-    const int nk = a.Hd / (BKS * SK);                   // steps of this workgroup
-    const size_t kbase = (size_t)part * nk * BKS;
-    auto a_tile = [&](int buf) { return tiles + buf * (A_ELEMS + B_ELEMS); };
-    auto b_tile = [&](int buf) { return tiles + buf * (A_ELEMS + B_ELEMS) + A_ELEMS; };
-
-    const int wm = (wave >> 1) & 1, wn = wave & 1;      // of the multiplying waves
-    f32x4 acc[4][4];            // [token block 4 wm + mi][feature block 2wn, 2wn+1, 2wn+4, 2wn+5]
-    // where the tile's rows go and their rotary positions: looked up once per row, now
+    // Workgroup -> (half of the hidden axis, column tile, row tile).  Workgroups go to the eight XCDs in
+    // turn; an XCD's L2 should see few distinct operands: with SK = 2 an XCD holds one half of the hidden
+    // axis and every fourth column tile, with SK = 1 every fourth column tile and every second row tile.
+    const int nct = 2 * a.Hkv;
+    int part = 0, ct, rt;
+    if (SK == 2) {
+        part = blockIdx.x & 1;
+        ct = (blockIdx.x >> 1) % nct; rt = (blockIdx.x >> 1) / nct;
+    } else if (nct % 4 == 0) {                                      // (the grid has an even number of row tiles)
+        const int x = blockIdx.x & 7, q = blockIdx.x >> 3;
+        ct = (x & 3) + 4 * (q % (nct / 4)); rt = 2 * (q / (nct / 4)) + (x >> 2);
+        if (rt >= row_tiles) return;
+    } else {
+        ct = blockIdx.x % nct; rt = blockIdx.x / nct;
+    }
+    const int kv = ct / a.Hkv, head = ct % a.Hkv;
+    const int row0 = rt * BM;
+    const int nk = a.Hd / (BK * SK);
     const RowDest my_dest = resolve_row(a, row0 + min(tid, BM - 1));
 
-    if (wave >= 4) {
-        // ---- moving waves: thread t of 256 moves 16 bytes of rows t/8 + 32i, columns 8*(t%8) ----
-        const int lt = tid - 256;
-        const int ld_row = lt >> 3, ld_col = (lt & 7) * 8;
-        const uint16_t* X = reinterpret_cast<const uint16_t*>(a.hidden) + kbase;
-        const uint16_t* W = reinterpret_cast<const uint16_t*>(kv == 0 ? a.w_k : a.w_v) + (size_t)head * D * a.Hd + kbase;
-        const uint16_t* xg[4];
-        const uint16_t* wg[4];
+    // Copies of a step: 8 rows x 128 bytes per instruction; token rows are instructions 0 .. 4 MI - 1,
+    // wave w takes w, w + 8, ...; of the 16 weight instructions every wave takes two.  LDS row r holds
+    // its eight 16-byte pieces permuted: piece g sits at place g ^ ((r >> 1) & 7).
+    constexpr int XI = 4 * MI, XW = (XI + 7) / 8;
+    const int n_x = (XI - wave + 7) / 8;                            // token copies of this wave per step (XW or XW - 1)
+    const int lrow = lane >> 3, place = lane & 7;
+    const size_t row_bytes = (size_t)a.Hd * 2;
+    const char* X = reinterpret_cast<const char*>(a.hidden) + (size_t)row0 * row_bytes + (size_t)part * nk * (BK * 2);
+    const char* W = reinterpret_cast<const char*>(kv == 0 ? a.w_k : a.w_v) + (size_t)head * D * row_bytes + (size_t)part * nk * (BK * 2);
+    uint32_t xoff[XW], woff[2];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int r = min(row0 + ld_row + 32 * i, total_rows - 1);   // rows past the end repeat the last
-            xg[i] = X + (size_t)r * a.Hd + ld_col;
-            wg[i] = W + (size_t)(ld_row + 32 * i) * a.Hd + ld_col;
-        }
-        constexpr int NS = 4;
-        struct Stage { uint4 x[4], w[4]; };
-        Stage st[NS];
-        auto load_global = [&](Stage& g, int ks) {
-            const int k0 = min(ks, nk - 1) * BKS;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) { g.x[i] = ldg16(xg[i] + k0); g.w[i] = ldg16(wg[i] + k0); }
-        };
-        auto store_lds = [&](int buf, const Stage& g) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                *reinterpret_cast<uint4*>(a_tile(buf) + (ld_row + 32 * i) * STR + ld_col) = g.x[i];
-                *reinterpret_cast<uint4*>(b_tile(buf) + (ld_row + 32 * i) * STR + ld_col) = g.w[i];
-            }
-        };
-#pragma unroll
-        for (int i = 0; i < NS - 1; ++i) load_global(st[i], i);
-        store_lds(0, st[0]);
-        lds_barrier();
-        int ks = 0;
-        auto step = [&](auto stage_tag) {
-            constexpr int S = decltype(stage_tag)::value;
-            load_global(st[(S + NS - 1) % NS], ks + NS - 1);
-            store_lds((ks + 1) & 1, st[(S + 1) % NS]);
-            lds_barrier();
-            ++ks;
-        };
-        do {
-            step(std::integral_constant<int, 0>{});
-            step(std::integral_constant<int, 1>{});
-            step(std::integral_constant<int, 2>{});
-            step(std::integral_constant<int, 3>{});
-        } while (ks < nk);
-    } else {
-        // ---- multiplying waves ----
-#pragma unroll
-        for (int mi = 0; mi < 4; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < 4; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
-        auto compute = [&](int buf) {
-            const uint16_t* At = a_tile(buf) + (64 * wm + c16) * STR + 8 * g4;
-            const uint16_t* Bt = b_tile(buf) + c16 * STR + 8 * g4;
-#pragma unroll
-            for (int k2 = 0; k2 < BKS / 32; ++k2) {
-                bf16x8 av[4], bv[4];
-#pragma unroll
-                for (int mi = 0; mi < 4; ++mi) av[mi] = *reinterpret_cast<const bf16x8*>(At + 16 * mi * STR + 32 * k2);
-#pragma unroll
-                for (int ni = 0; ni < 4; ++ni) {
-                    const int tn = 2 * wn + (ni & 1) + 4 * (ni >> 1);
-                    bv[ni] = *reinterpret_cast<const bf16x8*>(Bt + 16 * tn * STR + 32 * k2);
-                }
-#pragma unroll
-                for (int mi = 0; mi < 4; ++mi)
-#pragma unroll
-                    for (int ni = 0; ni < 4; ++ni)
-                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[mi], bv[ni], acc[mi][ni], 0, 0, 0);
-            }
-        };
-        lds_barrier();                                  // tile 0 is in place
-        const int n_bar = (nk + 3) / 4 * 4;             // the moving waves run whole rounds of four steps
-        for (int ks = 0; ks < n_bar; ++ks) {
-            if (ks < nk) compute(ks & 1);
-            lds_barrier();
-        }
+    for (int i = 0; i < XW; ++i) {
+        const int r = (wave + 8 * i) * 8 + lrow;
+        xoff[i] = (uint32_t)(min(r, total_rows - 1 - row0) * row_bytes) + 16 * (place ^ ((r >> 1) & 7));
     }
-    if (tid < BM) sm_dest[tid] = my_dest;               // (the loop's last barrier is behind every read of the tiles)
-    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int r = (wave + 8 * i) * 8 + lrow;
+        woff[i] = (uint32_t)(r * row_bytes) + 16 * (place ^ ((r >> 1) & 7));
+    }
+    const uint32_t lds0 = dev::lds_address(smem);
+    auto copy_step = [&](int ks, int buf) {
+        const uint32_t base = lds0 + buf * S::STEP_BYTES + wave * 1024;
+        const size_t k = (size_t)ks * (BK * 2);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) dev::dma16(W + k, woff[i], base + BM * BK * 2 + i * 8192);
+#pragma unroll
+        for (int i = 0; i < XW; ++i) if (XI % 8 == 0 || i < n_x) dev::dma16(X + k, xoff[i], base + i * 8192);
+    };
 
-    if constexpr (SK > 1) {
-        static_assert(SK == 2, "two workgroups per tile");
-        const int tile = blockIdx.y * gridDim.x + blockIdx.x;
-        if (wave < 4) {
-            float* mine = a.ws_partials + ((size_t)(tile * SK + part) * 4 + wave) * (32 * 128) + lane * 2;
+    const int wm = wave / WN, wn = wave % WN;
+    f32x4 acc[XB][2 * PB];                                          // [row block][low pair blocks, then their partners]
 #pragma unroll
-            for (int mi = 0; mi < 4; ++mi)
+    for (int mi = 0; mi < XB; ++mi)
 #pragma unroll
-                for (int ni = 0; ni < 4; ++ni) {
-                    dev::st_agent2(mine + ((mi * 4 + ni) * 2 + 0) * 128, acc[mi][ni][0], acc[mi][ni][1]);
-                    dev::st_agent2(mine + ((mi * 4 + ni) * 2 + 1) * 128, acc[mi][ni][2], acc[mi][ni][3]);
-                }
+        for (int p = 0; p < 2 * PB; ++p) acc[mi][p] = f32x4{0.f, 0.f, 0.f, 0.f};
+    struct Frags { bf16x8 b[2 * PB], x[XB]; };                      // operands of half a step: 32 hidden columns
+    const int sw = (c16 >> 1) & 7;                                  // (the rows a lane reads differ by multiples of 16)
+    const char* const At = smem + (16 * XB * wm + c16) * 128;
+    const char* const Bt = smem + (BM + 16 * PB * wn + c16) * 128;
+    auto read = [&](Frags& f, int buf, int k2) {
+        const int off = buf * S::STEP_BYTES + 16 * ((4 * k2 + g4) ^ sw);
+#pragma unroll
+        for (int p = 0; p < PB; ++p) {
+            f.b[p] = *reinterpret_cast<const bf16x8*>(Bt + p * 2048 + off);
+            f.b[PB + p] = *reinterpret_cast<const bf16x8*>(Bt + 64 * 128 + p * 2048 + off);
         }
+#pragma unroll
+        for (int mi = 0; mi < XB; ++mi) f.x[mi] = *reinterpret_cast<const bf16x8*>(At + mi * 2048 + off);
+    };
+    auto multiply = [&](const Frags& f) {
+#pragma unroll
+        for (int mi = 0; mi < XB; ++mi)
+#pragma unroll
+            for (int p = 0; p < 2 * PB; ++p)
+                acc[mi][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.x[mi], f.b[p], acc[mi][p], 0, 0, 0);
+    };
+
+    // all but the youngest `steps` steps of this wave's copies have landed
+    auto wait_steps = [&](auto steps_tag) {
+        constexpr int K = decltype(steps_tag)::value;
+        if (XI % 8 == 0 || n_x == XW) dev::dma_wait<K * (2 + XW)>();
+        else                          dev::dma_wait<K * (1 + XW)>();
+    };
+    // Half a step is multiplied while the operands of the next half are on their way from LDS.  Behind
+    // the barrier every wave has its operands of step ks in registers, so step ks + NBUF is copied over it.
+    const int ahead = min(NBUF, nk);
+    for (int i = 0; i < ahead; ++i) copy_step(i, i);
+    if (ahead == NBUF) wait_steps(std::integral_constant<int, NBUF - 1>{}); else dev::dma_wait<0>();
+    lds_barrier();
+    Frags f0, f1;
+    read(f0, 0, 0);
+    int buf = 0, ks = 0;
+    for (; ks < nk - NBUF; ++ks) {
+        read(f1, buf, 1);
+        multiply(f0);
+        wait_steps(std::integral_constant<int, NBUF - 2>{});
+        lds_barrier();
+        const int nbuf = buf + 1 == NBUF ? 0 : buf + 1;
+        read(f0, nbuf, 0);
+        copy_step(ks + NBUF, buf);
+        multiply(f1);
+        buf = nbuf;
+    }
+    for (; ks < nk; ++ks) {                                         // nothing more to ask for
+        read(f1, buf, 1);
+        multiply(f0);
+        dev::dma_wait<0>();
+        lds_barrier();
+        buf = buf + 1 == NBUF ? 0 : buf + 1;
+        read(f0, buf, 0);                                           // (past the end: not used)
+        multiply(f1);
+    }
+    __syncthreads();                                                // the buffers are dead
+
+    if constexpr (SK == 2) {
+        const int tile = rt * nct + ct;
+        int* const sm_last = reinterpret_cast<int*>(smem);
+        float* mine = a.ws_partials + ((size_t)(tile * SK + part) * 8 + wave) * (BM * 16) + lane * 4;
+#pragma unroll
+        for (int mi = 0; mi < XB; ++mi)
+#pragma unroll
+            for (int p = 0; p < 2 * PB; ++p) dev::st_agent4(mine + (mi * 2 * PB + p) * 256, acc[mi][p]);
         int32_t* counter = a.ws_counters + (size_t)tile * kDecodeCounterStride;
         if (!dev::arrive_at(counter, SK, sm_last)) return;
         dev::reset_counter_at(counter);
-        if (wave < 4) {
-            const float* theirs = a.ws_partials + ((size_t)(tile * SK + (part ^ 1)) * 4 + wave) * (32 * 128) + lane * 2;
+        const float* theirs = a.ws_partials + ((size_t)(tile * SK + (part ^ 1)) * 8 + wave) * (BM * 16) + lane * 4;
+        f32x4 o[XB * 2 * PB];
 #pragma unroll
-            for (int mi = 0; mi < 4; ++mi) {
-                float2 o[8];
+        for (int i = 0; i < XB * 2 * PB; ++i) dev::ld_agent4(o[i], theirs + i * 256);
+        dev::ld_agent_wait(o);
 #pragma unroll
-                for (int r = 0; r < 8; ++r) o[r] = dev::ld_agent2(theirs + (mi * 8 + r) * 128);
+        for (int mi = 0; mi < XB; ++mi)
 #pragma unroll
-                for (int ni = 0; ni < 4; ++ni) {
-                    acc[mi][ni][0] += o[2 * ni].x; acc[mi][ni][1] += o[2 * ni].y;
-                    acc[mi][ni][2] += o[2 * ni + 1].x; acc[mi][ni][3] += o[2 * ni + 1].y;
-                }
-            }
-        }
+            for (int p = 0; p < 2 * PB; ++p) acc[mi][p] += o[mi * 2 * PB + p];
+        __syncthreads();
     }
-    if (wave >= 4) return;
 
-    // epilogue: lane holds tokens 64 wm + 16 mi + 4 g4 + i, features 16 tn + c16
-    uint16_t* out = reinterpret_cast<uint16_t*>(kv == 0 ? a.k_out : a.v_out) + (size_t)head * a.token_stride * D;
+    // epilogue: lane holds tokens 16 (XB wm + mi) + 4 g4 + i, features 16 (PB wn + p) + c16 and 64 further
+    uint16_t* const ot = reinterpret_cast<uint16_t*>(smem);
+    RowDest* const sm_dest = reinterpret_cast<RowDest*>(smem + BM * OSTR * 2);
+    if (tid < BM) sm_dest[tid] = my_dest;
+    __syncthreads();
 #pragma unroll
-    for (int mi = 0; mi < 4; ++mi)
+    for (int p = 0; p < PB; ++p) {
+        const int j = 16 * (PB * wn + p) + c16;
+        const RopeEntry re = a.rope[j];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const RowDest d = sm_dest[64 * wm + 16 * mi + 4 * g4 + i];
-            if (!d.valid) continue;
+        for (int mi = 0; mi < XB; ++mi)
 #pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                const int j = 16 * (2 * wn + p) + c16;           // rotary pair index, features j and j + 64
-                float lo = acc[mi][p][i], hi = acc[mi][p + 2][i];
+            for (int i = 0; i < 4; ++i) {
+                const int r = 16 * (XB * wm + mi) + 4 * g4 + i;
+                float lo = acc[mi][p][i], hi = acc[mi][PB + p][i];
                 if (kv == 0) {
                     float c, s;
-                    rope_cs(a.rope[j], d.pos, c, s);
+                    rope_cs(re, sm_dest[r].pos, c, s);
                     const float k0 = lo * c - hi * s;
                     const float k1 = lo * s + hi * c;
                     lo = k0; hi = k1;
                 }
-                out[d.elem_off + j] = f32_to_bf16_rne(lo);
-                out[d.elem_off + j + 64] = f32_to_bf16_rne(hi);
+                ot[r * OSTR + j] = f32_to_bf16_rne(lo);
+                ot[r * OSTR + j + 64] = f32_to_bf16_rne(hi);
             }
-        }
-}
-
-// ---- skinny form: 16 .. 255 token rows (a question, a decode step of a large batch) ----------
-// (The form for hidden sizes that are a multiple of 512 but not of 1024; multiples of 1024 take
-// the staged form below.)
-// Too few rows for the tiled GEMM to fill the chip (64 rows make 16 tiles).  Here a workgroup owns
-// up to 64 rows x 16 rotary pairs (features 16g .. 16g+15 and their partners 64 further) of one
-// head of K or of V, and its eight waves split the HIDDEN axis: each wave multiplies its slice
-// with operands loaded straight from global memory in matrix-core layout (tokens as A rows,
-// weight rows as B columns; 16 bytes per lane, no LDS staging: the weights are read once, the
-// few token rows come from the caches), the eight partial tiles meet in LDS, and the rotation
-// and the single rounding to bf16 follow.  Grid: 64 x row tiles workgroups of 8 waves.
-template <int MI>
-__global__ __launch_bounds__(512) void materialize_skinny_kernel(MaterializeArgs a, int total_rows) {
-    constexpr int NWV = 8, CH = 2;                      // waves; matrix-core steps per staged chunk (fixed by the lane layout below)
-    constexpr int TM = 16 * MI;
-    __shared__ float red[NWV][TM][33];
-
-    const int tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int c16 = lane & 15, g4 = lane >> 4;
-    const int pg = blockIdx.x & 3, head = (blockIdx.x >> 2) % a.Hkv, kv = (blockIdx.x >> 2) / a.Hkv;
-    const int row0 = blockIdx.y * TM;
-    const int kslice = a.Hd / NWV;                      // a multiple of 32 * CH (checked by the launcher)
-    const int n_chunks = kslice / (32 * CH);
-
-    // Columns: a chunk is 64 columns per wave; lane (c16, g4) takes the 16 consecutive columns
-    // 16 g4 .. 16 g4 + 15 of its row as two adjacent 16-byte loads, the first for one matrix-core
-    // step and the second for the next (the contraction order is free as long as tokens and
-    // weights agree), so that the four lanes of a row consume one whole 128-byte line at once
-    // instead of half of it now and half a step later.  The eight waves take adjacent 64-column
-    // pieces: together they read 1 KB of every row per chunk.
-    const uint16_t* W = reinterpret_cast<const uint16_t*>(kv == 0 ? a.w_k : a.w_v) +
-                        ((size_t)head * D + 16 * pg + c16) * a.Hd + 64 * wave + 16 * g4;
-    const uint16_t* Whi = W + (size_t)(D / 2) * a.Hd;
-    const uint16_t* X = reinterpret_cast<const uint16_t*>(a.hidden) + 64 * wave + 16 * g4;
-    const uint16_t* xr[MI];
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi) xr[mi] = X + (size_t)min(row0 + 16 * mi + c16, total_rows - 1) * a.Hd;
-
-    // a thread's output column in the epilogue is fixed (16 pg + tid % 16): its rotary entry is
-    // requested now, not after the reduction
-    const RopeEntry rope_e = a.rope[16 * pg + (tid & 15)];
-
-    struct Chunk { uint4 x[MI][CH], wl[CH], wh[CH]; };
-    auto load = [&](Chunk& c, int ci) {
-        const int off = min(ci, n_chunks - 1) * (32 * CH * NWV);
-#pragma unroll
-        for (int s = 0; s < CH; ++s) {
-            c.wl[s] = ldg16(W + off + 8 * s);
-            c.wh[s] = ldg16(Whi + off + 8 * s);
-#pragma unroll
-            for (int mi = 0; mi < MI; ++mi) c.x[mi][s] = ldg16(xr[mi] + off + 8 * s);
-        }
-    };
-    f32x4 acc[MI][2];
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi) { acc[mi][0] = f32x4{0.f, 0.f, 0.f, 0.f}; acc[mi][1] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-    auto mma = [&](const Chunk& c) {
-#pragma unroll
-        for (int s = 0; s < CH; ++s)
-#pragma unroll
-            for (int mi = 0; mi < MI; ++mi) {
-                const bf16x8 xa = __builtin_bit_cast(bf16x8, c.x[mi][s]);
-                acc[mi][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, __builtin_bit_cast(bf16x8, c.wl[s]), acc[mi][0], 0, 0, 0);
-                acc[mi][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, __builtin_bit_cast(bf16x8, c.wh[s]), acc[mi][1], 0, 0, 0);
-            }
-    };
-    // NCH chunks in flight; loads carry no branch (past the end they repeat the last chunk) and
-    // the loop has one exit, so the compiler counts the loads in flight exactly
-    {
-        constexpr int NCH = MI == 1 ? 4 : 2;
-        Chunk c[NCH];
-#pragma unroll
-        for (int i = 0; i < NCH; ++i) load(c[i], i);
-        int ci = 0;
-        do {
-#pragma unroll
-            for (int i = 0; i < NCH; ++i) {
-                if (ci + i < n_chunks) mma(c[i]);
-                load(c[i], ci + i + NCH);
-            }
-            ci += NCH;
-        } while (ci < n_chunks);
     }
-
-    // lane holds tokens 16mi + 4*g4 + i, feature c16 of the low (h = 0) or high (h = 1) half
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) red[wave][16 * mi + 4 * g4 + i][16 * h + c16] = acc[mi][h][i];
     __syncthreads();
-
+    // whole rows out: sixteen lanes write one row of 256 bytes
     uint16_t* out = reinterpret_cast<uint16_t*>(kv == 0 ? a.k_out : a.v_out) + (size_t)head * a.token_stride * D;
-    for (int idx = tid; idx < TM * 16; idx += NWV * 64) {
-        const int t = idx >> 4, p = idx & 15;
-        float lo = 0.f, hi = 0.f;
 #pragma unroll
-        for (int w = 0; w < NWV; ++w) { lo += red[w][t][p]; hi += red[w][t][16 + p]; }
-        const RowDest d = resolve_row(a, row0 + t);
-        if (!d.valid) continue;
-        const int j = 16 * pg + p;
-        if (kv == 0) {
-            float c, s;
-            rope_cs(rope_e, d.pos, c, s);
-            const float k0 = lo * c - hi * s;
-            const float k1 = lo * s + hi * c;
-            lo = k0; hi = k1;
-        }
-        out[d.elem_off + j] = f32_to_bf16_rne(lo);
-        out[d.elem_off + j + 64] = f32_to_bf16_rne(hi);
+    for (int i = 0; i < MI; ++i) {
+        const int r = 32 * i + (tid >> 4), c = 8 * (tid & 15);
+        const RowDest d = sm_dest[r];
+        if (d.valid) *reinterpret_cast<uint4*>(out + d.elem_off + c) = *reinterpret_cast<const uint4*>(ot + r * OSTR + c);
     }
 }
 
+template <int MI, int WN, int SK>
+hipError_t launch_tile(const MaterializeArgs& a, int total_rows, hipStream_t s) {
+    const int row_tiles = (total_rows + 32 * MI - 1) / (32 * MI), nct = 2 * a.Hkv;
+    const int grid_tiles = SK == 1 && nct % 4 == 0 ? (row_tiles + 1) / 2 * 2 : row_tiles;
+    hipLaunchKernelGGL((materialize_tile_kernel<MI, WN, SK>), dim3(nct * grid_tiles * SK), dim3(512), 0, s, a, total_rows, row_tiles);
+    return hipGetLastError();
+}
 
-// ---- skinny form with coalesced loads ---------------------------------------------------------
-// The kernel above loads operands straight into matrix-core layout: consecutive lanes then sit on
-// sixteen different rows, every lane's 16 bytes is a request of its own to the vector cache, and
-// the launch is bound by that request rate (64 rows, hidden 4096: 98 MB in 17 us).  Here a wave
-// loads its slice of the hidden axis row-wise instead - sixteen consecutive lanes take 256
-// consecutive bytes of one row - parks the rows in a private LDS region (272-byte rows: sixteen
+// Tile height.  One workgroup fills a compute unit's LDS, a launch is as long as its slowest
+// compute unit, and a workgroup's time grows slower than its height (hidden 4096, us: two workgroups
+// per tile of 32 / 64 / 96 / 128 rows 17 / 21 / 24 / 28, one per tile of 96 / 128 / 192 / 256 rows
+// 33 / 38 / 47 / 57): so the smallest height that gives no compute unit two workgroups, hidden axis
+// halved while that holds; beyond one full round the height with the smallest rounds x (4 + MI), which
+// is what those times follow (6000 rows: 192-row tiles 103 us, 128 rows 119, 256 rows 117).
+hipError_t launch_tiled(const MaterializeArgs& a, int total_rows, hipStream_t s) {
+    const int nct = 2 * a.Hkv;
+    auto groups = [&](int mi) { return nct * ((total_rows + 32 * mi - 1) / (32 * mi)); };
+    auto halved = [&](int mi) {
+        const int64_t tiles = groups(mi);
+        return (a.Hd % (2 * BK)) == 0 && tiles * 2 <= 256 && a.ws_partials && tiles * 2 * (32 * mi) * D <= a.ws_partial_floats &&
+               tiles * kDecodeCounterStride <= a.ws_n_counters;
+    };
+    if (halved(1)) return launch_tile<1, 4, 2>(a, total_rows, s);
+    if (halved(2)) return launch_tile<2, 4, 2>(a, total_rows, s);
+    if (halved(3)) return launch_tile<3, 4, 2>(a, total_rows, s);
+    if (halved(4)) return launch_tile<4, 4, 2>(a, total_rows, s);
+    int best = 3;
+    long best_cost = -1;
+    for (int mi : {3, 4, 6, 8}) {
+        const long cost = (long)((groups(mi) + 255) / 256) * (4 + mi);
+        if (best_cost < 0 || cost < best_cost) { best = mi; best_cost = cost; }
+    }
+    switch (best) {
+        case 3: return launch_tile<3, 4, 1>(a, total_rows, s);
+        case 4: return launch_tile<4, 4, 1>(a, total_rows, s);
+        case 6: return launch_tile<6, 4, 1>(a, total_rows, s);
+        default: return launch_tile<8, 2, 1>(a, total_rows, s);
+    }
+}
+
+// ---- skinny form: up to 128 token rows, hidden a multiple of 1024 ------------------------------
+// Too few rows for the tiled GEMM to fill the chip.  Here a workgroup owns 16 or 32 rows x 16 rotary
+// pairs (features 16g .. 16g+15 and their partners 64 further) of one head of K or of V, and its eight
+// waves split the HIDDEN axis.  Loading operands straight into matrix-core layout was bound by the
+// vector cache's request rate - consecutive lanes sit on sixteen different rows, every lane's 16 bytes
+// is a request of its own (64 rows, hidden 4096: 98 MB in 17 us) - so a wave loads its slice of the
+// hidden axis row-wise: sixteen consecutive lanes take 256 consecutive bytes of one row; it parks the rows in a private LDS region (272-byte rows: sixteen
 // lanes write one whole row, sixteen lanes read 16 bytes of sixteen different rows, both without a
 // bank conflict) and reads them back in operand layout.  The region belongs to one wave: no
-// workgroup barrier in the loop.  Same tile, same split of the hidden axis, same epilogue.
+// workgroup barrier in the loop.  The eight partial tiles meet in LDS, and the rotation and the single
+// rounding to bf16 follow.
 template <int MI, int NB>
 __global__ __launch_bounds__(512) void materialize_skinny_staged_kernel(MaterializeArgs a, int total_rows) {
     constexpr int NWV = 8, SC = 128;                    // waves; hidden columns per wave and round
@@ -635,49 +590,25 @@ bool materialize_mfma_supported(const MaterializeArgs& a, int dtype, int total_r
     return dtype == MATKV_BF16 && a.D == 128 && (a.Hd % BK) == 0 && total_rows >= 16;
 }
 
-// Skinny forms: measured ahead of the tiled GEMM below a few hundred rows, where the GEMM's grid
-// leaves most compute units idle.  The staged form (hidden a multiple of 1024), us per launch at
-// hidden 4096 / 8192 against the form with direct operand loads: 64 rows 8.1 / 13.8 (17.2 / -),
-// 128 rows 10.6 / 17.4, 255 rows 18.8 / 30.1 (33.9 / 61.6); against the tiled GEMM: 384 rows
-// 27.1 / 44.6 (about 30 / 58), 512 rows 35.3 / 57.3 (30.6 / 58), 768 rows 50.6 / 80.2 (about 33 / 58).
-constexpr int kSkinnyMaxRows = 256;
-constexpr int kStagedMaxRows = 448;
+// The staged skinny form (hidden a multiple of 1024) is ahead of the tiled GEMM up to 128 rows: us per
+// launch at hidden 4096 / 8192, weights from HBM: 64 rows 10.4 / 15.7 against 15.4 / 26, 128 rows
+// 12.6 / 19.6 against 17.0 / 29.6, 160 rows 20.5 / 31.8 against 17.0 / 29.4.
+constexpr int kStagedMaxRows = 128;
 
 hipError_t launch_materialize_mfma(const MaterializeArgs& a, int total_rows, hipStream_t s) {
-    const bool staged = (a.Hd % 1024) == 0;
-    if ((a.Hd % 512) == 0 && (total_rows < kSkinnyMaxRows || (staged && (total_rows <= kStagedMaxRows || (total_rows <= 512 && a.Hd >= 8192))))) {
-        const dim3 block(512);
-        const int gx = 2 * a.Hkv * 4;
-        if (staged) {
-            // rows staged through LDS: 16-row tiles up to 64 rows (64 x 4 workgroups fill the chip),
-            // 32-row tiles beyond (half the workgroups, the weights re-read half as often)
-            const int rounds = a.Hd / 1024;             // per wave: an eighth of the hidden axis, 128 columns a round
-            const bool mi2 = total_rows > 64;
-            const dim3 grid(gx, mi2 ? (total_rows + 31) / 32 : (total_rows + 15) / 16);
-            if (rounds % 2 == 0) {
-                if (mi2) hipLaunchKernelGGL((materialize_skinny_staged_kernel<2, 2>), grid, block, 0, s, a, total_rows);
-                else     hipLaunchKernelGGL((materialize_skinny_staged_kernel<1, 2>), grid, block, 0, s, a, total_rows);
-            } else {
-                if (mi2) hipLaunchKernelGGL((materialize_skinny_staged_kernel<2, 1>), grid, block, 0, s, a, total_rows);
-                else     hipLaunchKernelGGL((materialize_skinny_staged_kernel<1, 1>), grid, block, 0, s, a, total_rows);
-            }
-            return hipGetLastError();
-        }
-        // 16-row tiles keep every compute unit busy from 64 rows on (64 x 4 workgroups) and leave
-        // registers for four chunks of loads in flight; from 512 workgroups on, 32-row tiles halve
-        // the re-reading of the weights
-        if (total_rows <= 128) hipLaunchKernelGGL(materialize_skinny_kernel<1>, dim3(gx, (total_rows + 15) / 16), block, 0, s, a, total_rows);
-        else                   hipLaunchKernelGGL(materialize_skinny_kernel<2>, dim3(gx, (total_rows + 31) / 32), block, 0, s, a, total_rows);
-        return hipGetLastError();
+    if ((a.Hd % 1024) != 0 || total_rows > kStagedMaxRows) return launch_tiled(a, total_rows, s);
+    // rows staged through LDS: 16-row tiles up to 64 rows (64 x 4 workgroups fill the chip),
+    // 32-row tiles beyond (half the workgroups, the weights re-read half as often)
+    const int rounds = a.Hd / 1024;             // per wave: an eighth of the hidden axis, 128 columns a round
+    const bool mi2 = total_rows > 64;
+    const dim3 grid(2 * a.Hkv * 4, mi2 ? (total_rows + 31) / 32 : (total_rows + 15) / 16), block(512);
+    if (rounds % 2 == 0) {
+        if (mi2) hipLaunchKernelGGL((materialize_skinny_staged_kernel<2, 2>), grid, block, 0, s, a, total_rows);
+        else     hipLaunchKernelGGL((materialize_skinny_staged_kernel<1, 2>), grid, block, 0, s, a, total_rows);
+    } else {
+        if (mi2) hipLaunchKernelGGL((materialize_skinny_staged_kernel<2, 1>), grid, block, 0, s, a, total_rows);
+        else     hipLaunchKernelGGL((materialize_skinny_staged_kernel<1, 1>), grid, block, 0, s, a, total_rows);
     }
-    // two workgroups per tile while that fills the chip at most once (and the workspace has room)
-    const int tiles = 2 * a.Hkv * ((total_rows + 127) / 128);
-    const bool room = a.ws_partials && (int64_t)tiles * 2 * 128 * 128 <= a.ws_partial_floats &&
-                      (int64_t)tiles * kDecodeCounterStride <= a.ws_n_counters;
-    if (tiles * 2 <= 256 && (a.Hd % (2 * BK)) == 0 && room)
-        hipLaunchKernelGGL(materialize_mfma128_kernel<2>, dim3(2 * a.Hkv, (total_rows + 127) / 128, 2), dim3(512), 0, s, a, total_rows);
-    else
-        hipLaunchKernelGGL(materialize_mfma128_kernel<1>, dim3(2 * a.Hkv, (total_rows + 127) / 128, 1), dim3(512), 0, s, a, total_rows);
     return hipGetLastError();
 }
 

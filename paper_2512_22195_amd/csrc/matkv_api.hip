@@ -1540,6 +1540,7 @@ matkv_status matkv_decode_step(matkv_ctx* c, int32_t layer, const void* hidden, 
     m.pos0 = 0; m.token_stride = c->cfg.max_tail_tokens;
     m.rows_per_instance = 1; m.batch = th->batch; m.n_tokens = th->batch;
     m.Hkv = c->cfg.n_kv_heads; m.D = c->cfg.head_dim; m.Hd = c->cfg.hidden;
+    materialize_scratch(c, m);
     if (decode_step_supported(a, m, c->cfg.dtype)) {
         HIP_TRY(c, launch_decode_step(a, m, c->cfg.dtype, c->compute));
         return MATKV_OK;

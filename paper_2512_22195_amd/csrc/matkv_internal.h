@@ -132,7 +132,7 @@ inline WorkspaceLayout workspace_layout(const matkv_config& c) {
     // back at zero when its launch ends)
     W.n_counters = (size_t)c.max_batch * c.n_kv_heads * (size_t)std::max(max_q_rows(c), kDecodeCounterStride);
     // (bf16, head_dim 128: the projection GEMM may split the hidden axis over two workgroups per
-    // 128 x 128 tile, up to kSplitTiles tiles: a counter line and two fp32 partial tiles each)
+    // tile of up to 128 x 128, up to kSplitTiles tiles: a counter line and two fp32 partial tiles each)
     const bool gemm_split = c.dtype == MATKV_BF16 && c.head_dim == 128;
     if (gemm_split) W.n_counters = std::max(W.n_counters, (size_t)kSplitTiles * kDecodeCounterStride);
     o += ((W.n_counters * sizeof(int32_t)) + 255) & ~(size_t)255;

@@ -207,6 +207,36 @@ def test_materialize_hidden_sizes_bf16(hidden, T):
         ctx.close()
 
 
+@pytest.mark.parametrize("hidden,T,Hkv", [
+    (64, 33, 2), (128, 200, 2), (192, 300, 2), (320, 129, 8), (512, 256, 8), (512, 257, 8), (512, 513, 8), (512, 769, 8), (512, 1025, 8),
+    (512, 1537, 8), (512, 2049, 8), (512, 3073, 8), (512, 4160, 8), (1024, 129, 8), (384, 700, 1), (448, 450, 3)])
+def test_materialize_tile_heights(hidden, T, Hkv):
+    """Tiled projection: every tile height of both forms (two workgroups per tile: 32, 64, 96, 128
+    rows; one: 96, 128, 192, 256) just past the row count where the one before ends, hidden axes of one
+    step, of fewer steps than are in flight, and of an odd number of steps, and column tile counts that
+    are no multiple of four."""
+    case = Case("bf16-tiles", n_layers=1, Hq=Hkv, Hkv=Hkv, D=128, hidden=hidden, dtype="bf16",
+                chunk_lens={0: 8}, retrieved=[[0]], q_lens=[1], steps=0, rope_base=500000.0, scale=1.0 / 4.0)
+    from workload import normal, to_f64
+    import oracle
+    ctx = chain.make_context(case)
+    try:
+        with torch.cuda.stream(ctx.compute_stream):
+            w = normal(("tiles", hidden, Hkv, "w"), (2, Hkv * 128, hidden), 0.25, torch.bfloat16).cuda()
+            x = normal(("tiles", hidden, "x", T), (T, hidden), 0.25, torch.bfloat16).cuda()
+            k = torch.zeros((Hkv, T + 3, 128), dtype=torch.bfloat16, device="cuda")
+            v = torch.zeros_like(k)
+            for _ in range(2):          # (the second run finds the arrival counters at zero again)
+                ctx.materialize(x, w[0], w[1], T, 50, k, v, T + 3)
+            ctx.compute_stream.synchronize()
+        assert not k[:, T:].any() and not v[:, T:].any()        # rows past the last are not written
+        K, V = oracle.materialize(to_f64(x), to_f64(w[0]), to_f64(w[1]), Hkv, 128, 50.0, 500000.0)
+        chain.compare_materialized(case, k[:, :T].cpu(), K, f"K, hidden {hidden}, {T} rows")
+        chain.compare_materialized(case, v[:, :T].cpu(), V, f"V, hidden {hidden}, {T} rows")
+    finally:
+        ctx.close()
+
+
 def test_bf16_chain_batch17_decode_rows_on_matrix_cores():
     """Seventeen instances: the decode-token projection has 17 rows (skinny form, ragged second
     16-row block), the question projection 17 ragged groups of rows."""
