@@ -52,64 +52,120 @@ struct StepArgs {
     const void* w_v;
     const RopeEntry* rope;
     int32_t Hd, batch;
+    int32_t n_units;            // workgroups of a KV head that walk the cache; those beyond only project
 };
 
-// Last arrival of a fused decode step at instance b, KV head kvh: folds the units' partials and
-// the newest token into the G output rows.  Wave w owns row w (query head kvh*G + w), lane l
-// the dims 2l, 2l+1.  The newest token's K/V row is read back from the tail cache, where the
-// projection waves left it with agent-scope stores; its loads and the partials' loads are all
-// issued before anything is consumed (one memory round trip), its score is a 64-lane dot
-// product, and it enters as one more contribution of weight 1.  No barrier: waves past G leave.
-template <int G, int NT>
-__device__ __forceinline__ void merge_decode_step(const KernelArgs& a, const InstanceInfo& inst, int b, int kvh) {
-    typedef uint16_t T;
-    constexpr int PSTRIDE = kPartialStride(D);
-    constexpr int UPC = 32;                             // units per pass: the default partition (up to 32 units) folds in one
-    const int w0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    for (int w = w0; w < G; w += NT / 64) {             // more rows than waves: a wave takes several in turn
-    const int head = kvh * G + w, d = 2 * lane;
-
-    const size_t toff = (((size_t)b * a.Hkv + kvh) * (size_t)a.max_tail + (size_t)(inst.tail_len - 1)) * D + d;
-    const uint32_t kw = __hip_atomic_load(reinterpret_cast<const uint32_t*>(reinterpret_cast<const T*>(a.tail_k) + toff),
-                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint32_t vw = __hip_atomic_load(reinterpret_cast<const uint32_t*>(reinterpret_cast<const T*>(a.tail_v) + toff),
-                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint32_t qw = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const T*>(a.q) + ((size_t)b * a.Hq + head) * D + d);
-
-    const int n_units = inst.n_dunits;
-    const float* src = a.partials + ((size_t)inst.dunit0 * a.rows * a.Hq + head) * PSTRIDE;
-    const size_t ustride = (size_t)a.rows * a.Hq * PSTRIDE;
-    float M = kNegBig, L = 0.f, ox = 0.f, oy = 0.f;
-    for (int u0 = 0; u0 < n_units; u0 += UPC) {
-        float2 av[UPC], ml[UPC];
+// Folding the partials of a decode launch.  A wave takes RB output rows (an instance's newest token, one
+// query head) at a time, lane l the dims 2l, 2l+1.  Per pass of UPC units lane k fetches the (maximum, sum)
+// of unit k of every row, and all loads of the pass are requested before anything is consumed: one memory
+// round trip for UPC units of RB rows.  The wave agrees on the maximum, every lane has the weight of its
+// unit, and the weights reach the accumulators through lane reads.  (Until every lane fetched every unit's
+// pair itself, a pass had twice the loads, and a weight's exponential was taken in all lanes.)
+// src[i]: partial of row i's first unit; n[i]: its units (0: row not taken); ustride: floats between units.
+template <int RB, int UPC>
+__device__ __forceinline__ void fold_partials(const float* const (&src)[RB], const int (&n)[RB], size_t ustride, int lane,
+                                              float (&M)[RB], float (&L)[RB], float (&ox)[RB], float (&oy)[RB]) {
+    static_assert(UPC <= 64, "a lane per unit");
+    int nmax = 0;
 #pragma unroll
-        for (int k = 0; k < UPC; ++k) {
-            const size_t uo = (size_t)min(u0 + k, n_units - 1) * ustride;
-            ml[k] = ld_agent2(src + uo + D);
-            av[k] = ld_agent2(src + uo + d);
+    for (int i = 0; i < RB; ++i) {
+        nmax = max(nmax, n[i]);
+        M[i] = kNegBig; L[i] = 0.f; ox[i] = 0.f; oy[i] = 0.f;
+    }
+    for (int u0 = 0; u0 < nmax; u0 += UPC) {
+        float2 av[RB][UPC], ml[RB];
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+            const int top = max(n[i], 1) - 1;           // (past a row's units: its last one again)
+            ml[i] = ld_agent2(src[i] + (size_t)min(u0 + lane, top) * ustride + D);
+#pragma unroll
+            for (int k = 0; k < UPC; ++k) av[i][k] = ld_agent2(src[i] + (size_t)min(u0 + k, top) * ustride + 2 * lane);
         }
-        float mn = M;
 #pragma unroll
-        for (int k = 0; k < UPC; ++k) mn = fmaxf(mn, (u0 + k < n_units) ? ml[k].x : kNegBig);
-        const float cold = fast_exp2(M - mn);
-        L *= cold; ox *= cold; oy *= cold;
-        M = mn;
+        for (int i = 0; i < RB; ++i) {
+            const bool own = lane < UPC && u0 + lane < n[i];
+            const float mn = fmaxf(M[i], gemv::wave_max(own ? ml[i].x : kNegBig, lane));
+            const float w = own ? fast_exp2(ml[i].x - mn) : 0.f;
+            const float cold = fast_exp2(M[i] - mn);
+            L[i] = fmaf(L[i], cold, gemv::wave_sum(w * ml[i].y, lane));
+            ox[i] *= cold; oy[i] *= cold;
+            M[i] = mn;
 #pragma unroll
-        for (int k = 0; k < UPC; ++k) {
-            const float c = (u0 + k < n_units) ? fast_exp2(ml[k].x - mn) : 0.f;
-            L = fmaf(ml[k].y, c, L);
-            ox = fmaf(av[k].x, c, ox);
-            oy = fmaf(av[k].y, c, oy);
+            for (int k = 0; k < UPC; ++k) {
+                const float c = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), k));
+                ox[i] = fmaf(av[i][k].x, c, ox[i]);
+                oy[i] = fmaf(av[i][k].y, c, oy[i]);
+            }
         }
     }
-    const float sx = gemv::wave_sum(gemv::dot2(qw, kw, 0.f), lane) * a.scale_log2e;
-    const float mn = fmaxf(M, sx);
-    const float cold = fast_exp2(M - mn), cx = fast_exp2(sx - mn);
-    L = fmaf(L, cold, cx);
-    ox = fmaf(ox, cold, __uint_as_float(vw << 16) * cx);
-    oy = fmaf(oy, cold, __uint_as_float(vw & 0xffff0000u) * cx);
-    const float inv = 1.0f / L;
-    store_out2(a.out, a.out_f32, ((size_t)b * a.Hq + head) * D + d, ox * inv, oy * inv);
+}
+
+// Last arrival at (instance, KV head) of a plain decode launch: NWV waves fold the G rows.
+template <int G, int NWV, int UPC>
+__device__ __forceinline__ void merge_decode(const KernelArgs& a, const Unit& unit, int kvh, int wave, int lane) {
+    constexpr int PSTRIDE = kPartialStride(D), RB = (G + NWV - 1) / NWV;
+    const float* src[RB];
+    int n[RB];
+    float M[RB], L[RB], ox[RB], oy[RB];
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+        const int g = wave + NWV * i;
+        n[i] = g < G ? unit.n_units_inst : 0;
+        src[i] = a.partials + ((size_t)unit.unit0_inst * a.Hq + kvh * G + min(g, G - 1)) * PSTRIDE;
+    }
+    fold_partials<RB, UPC>(src, n, (size_t)a.Hq * PSTRIDE, lane, M, L, ox, oy);
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+        if (n[i] == 0) continue;
+        const float inv = 1.0f / L[i];
+        store_out2(a.out, a.out_f32, ((size_t)unit.inst * a.Hq + kvh * G + wave + NWV * i) * D + 2 * lane, ox[i] * inv, oy[i] * inv);
+    }
+}
+
+// Last arrivals of a fused decode step at KV head kvh: folds, for every instance at whose counter the
+// workgroup arrived last, the units' partials and the newest token into the G output rows - all such
+// instances at once.  The newest token's K/V row is read back from the tail cache, where the projection
+// waves left it with agent-scope stores; its score is a 64-lane dot product, and it enters as one more
+// contribution of weight 1.
+template <int G, int NWV, int RB, int UPC>
+__device__ __forceinline__ void merge_decode_step(const KernelArgs& a, const InstanceInfo* __restrict__ insts, int batch,
+                                                  const int* lastv, int kvh, int wave, int lane) {
+    typedef uint16_t T;
+    constexpr int PSTRIDE = kPartialStride(D);
+    const int rows = batch * G, d = 2 * lane;
+    for (int r0 = wave; r0 < rows; r0 += NWV * RB) {
+        const float* src[RB];
+        int n[RB];
+        uint32_t kw[RB], vw[RB], qw[RB];
+        size_t oidx[RB];
+        float M[RB], L[RB], ox[RB], oy[RB];
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+            const int r = min(r0 + NWV * i, rows - 1), b = r / G, head = kvh * G + r % G;
+            const InstanceInfo inst = insts[b];
+            n[i] = r0 + NWV * i < rows && lastv[b] ? inst.n_dunits : 0;
+            src[i] = a.partials + ((size_t)inst.dunit0 * a.Hq + head) * PSTRIDE;
+            const size_t toff = (((size_t)b * a.Hkv + kvh) * (size_t)a.max_tail + (size_t)max(inst.tail_len - 1, 0)) * D + d;
+            kw[i] = __hip_atomic_load(reinterpret_cast<const uint32_t*>(reinterpret_cast<const T*>(a.tail_k) + toff),
+                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            vw[i] = __hip_atomic_load(reinterpret_cast<const uint32_t*>(reinterpret_cast<const T*>(a.tail_v) + toff),
+                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            oidx[i] = ((size_t)b * a.Hq + head) * D + d;
+            qw[i] = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const T*>(a.q) + oidx[i]);
+        }
+        fold_partials<RB, UPC>(src, n, (size_t)a.Hq * PSTRIDE, lane, M, L, ox, oy);
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+            if (n[i] == 0) continue;
+            const float sx = gemv::wave_sum(gemv::dot2(qw[i], kw[i], 0.f), lane) * a.scale_log2e;
+            const float mn = fmaxf(M[i], sx);
+            const float cold = fast_exp2(M[i] - mn), cx = fast_exp2(sx - mn);
+            const float l = fmaf(L[i], cold, cx);
+            const float x = fmaf(ox[i], cold, __uint_as_float(vw[i] << 16) * cx);
+            const float y = fmaf(oy[i], cold, __uint_as_float(vw[i] & 0xffff0000u) * cx);
+            const float inv = 1.0f / l;
+            store_out2(a.out, a.out_f32, oidx[i], x * inv, y * inv);
+        }
     }
 }
 
@@ -151,64 +207,31 @@ __device__ __forceinline__ void projection_tasks(const KernelArgs& a, const Step
 constexpr int kFusedMaxBatch = 4;
 
 // Shared decode units: fold, for every user of this unit at whose counter the workgroup arrived
-// last, that instance's partial slots into its G output rows - all such users at once.  A thread
-// owns pairs of output elements; a wave's 64 pairs are one (user, head) row, so the number of
-// slots is uniform within a wave.  users[u] = {instance, this unit's slot, first slot, slots}.
-template <int G, int NT>
-__device__ __forceinline__ void merge_shared(const KernelArgs& a, const int4* users, const int* lastv, int n_users, int kvh) {
-    typedef uint16_t T;
-    constexpr int PSTRIDE = kPartialStride(D), CB = 4, UPC = 8;
-    const int total = n_users * G * (D / 2);
-    const size_t ustride = (size_t)a.Hq * PSTRIDE;                     // decode: one row per slot
-    for (int c0 = threadIdx.x; c0 < total; c0 += NT * CB) {
-        float M[CB], L[CB], ox[CB], oy[CB];
-        const float* src[CB];
-        int n[CB], inst[CB], head[CB], dd[CB];
-        int nmax = 0;
+// last (the first n_live entries of live), that instance's partial slots into its G output rows - all such users at once.
+// users[u] = {instance, this unit's slot, first slot, slots}.
+template <int G, int NWV, int RB, int UPC>
+__device__ __forceinline__ void merge_shared(const KernelArgs& a, const int4* users, const int* live, int n_live, int kvh, int wave, int lane) {
+    constexpr int PSTRIDE = kPartialStride(D);
+    const int rows = n_live * G;
+    for (int r0 = wave; r0 < rows; r0 += NWV * RB) {
+        const float* src[RB];
+        int n[RB];
+        size_t oidx[RB];
+        float M[RB], L[RB], ox[RB], oy[RB];
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) {
-            const int col = min(c0 + cb * NT, total - 1);
-            const int row = col / (D / 2), u = row / G;
-            const int4 us = users[u];
-            const bool live = c0 + cb * NT < total && lastv[u];
-            inst[cb] = us.x; head[cb] = kvh * G + row % G; dd[cb] = (col % (D / 2)) * 2;
-            n[cb] = live ? us.w : 0;
-            nmax = max(nmax, n[cb]);
-            src[cb] = a.partials + ((size_t)us.z * a.Hq + head[cb]) * PSTRIDE;
-            M[cb] = kNegBig; L[cb] = 0.f; ox[cb] = 0.f; oy[cb] = 0.f;
+        for (int i = 0; i < RB; ++i) {
+            const int r = min(r0 + NWV * i, rows - 1), head = kvh * G + r % G;
+            const int4 us = users[live[r / G]];
+            n[i] = r0 + NWV * i < rows ? __builtin_amdgcn_readfirstlane(us.w) : 0;
+            src[i] = a.partials + ((size_t)us.z * a.Hq + head) * PSTRIDE;           // decode: one row per slot
+            oidx[i] = ((size_t)us.x * a.Hq + head) * D + 2 * lane;
         }
-        for (int u0 = 0; u0 < nmax; u0 += UPC) {
-            float2 av[CB][UPC], ml[CB][UPC];
+        fold_partials<RB, UPC>(src, n, (size_t)a.Hq * PSTRIDE, lane, M, L, ox, oy);
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-                for (int k = 0; k < UPC; ++k) {
-                    const size_t uo = (size_t)min(u0 + k, max(n[cb], 1) - 1) * ustride;
-                    ml[cb][k] = ld_agent2(src[cb] + uo + D);
-                    av[cb][k] = ld_agent2(src[cb] + uo + dd[cb]);
-                }
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb) {
-                float mn = M[cb];
-#pragma unroll
-                for (int k = 0; k < UPC; ++k) mn = fmaxf(mn, (u0 + k < n[cb]) ? ml[cb][k].x : kNegBig);
-                const float cold = fast_exp2(M[cb] - mn);
-                L[cb] *= cold; ox[cb] *= cold; oy[cb] *= cold;
-                M[cb] = mn;
-#pragma unroll
-                for (int k = 0; k < UPC; ++k) {
-                    const float c = (u0 + k < n[cb]) ? fast_exp2(ml[cb][k].x - mn) : 0.f;
-                    L[cb] = fmaf(ml[cb][k].y, c, L[cb]);
-                    ox[cb] = fmaf(av[cb][k].x, c, ox[cb]);
-                    oy[cb] = fmaf(av[cb][k].y, c, oy[cb]);
-                }
-            }
-        }
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) {
-            if (n[cb] == 0) continue;
-            const float inv = 1.0f / L[cb];
-            store_out2(a.out, a.out_f32, ((size_t)inst[cb] * a.Hq + head[cb]) * D + dd[cb], ox[cb] * inv, oy[cb] * inv);
+        for (int i = 0; i < RB; ++i) {
+            if (n[i] == 0) continue;
+            const float inv = 1.0f / L[i];
+            store_out2(a.out, a.out_f32, oidx[i], ox[i] * inv, oy[i] * inv);
         }
     }
 }
@@ -246,7 +269,9 @@ __global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && 
     const int m0 = tile * ROWS;
 
     const SUnit* const su = reinterpret_cast<const SUnit*>(units) + blockIdx.x;     // SH only
-    const Unit unit = SH ? su->u : units[blockIdx.x];
+    // fused step: workgroups beyond the units of the cache have projection waves only
+    const bool walks = FR == 0 || (int)blockIdx.x < f.n_units;
+    const Unit unit = SH ? table_record(&su->u) : table_record(units + (FR > 0 ? min((int)blockIdx.x, f.n_units - 1) : (int)blockIdx.x));
 
     int n_m, q_row0, tail_len = 0, tail_visible;
     if (SH) {
@@ -290,9 +315,13 @@ __global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && 
         sm_users[tid] = make_int4(inst, su->users[tid].slot, insts[inst].sslot0, insts[inst].n_sslots);
     }
 
-    if (FR > 0 && wave >= NW) {
-        if constexpr (FR > 0)
-            projection_tasks<FR>(a, f, insts, kvh, (int)blockIdx.x * NW + (wave - NW), (int)gridDim.x * NW, lane);
+    if (FR > 0 && (wave >= NW || !walks)) {
+        if constexpr (FR > 0) {
+            // the waves of the projection-only workgroups come first: they have nothing else to do
+            const int extra = ((int)gridDim.x - f.n_units) * 2 * NW;
+            const int id = walks ? extra + (int)blockIdx.x * NW + (wave - NW) : ((int)blockIdx.x - f.n_units) * 2 * NW + wave;
+            projection_tasks<FR>(a, f, insts, kvh, id, extra + f.n_units * NW, lane);
+        }
     } else {
     // Q in operand layout: lane (c16, g4) holds, for sub-tile j and chunk c of the head
     // dimension, the 8 dims dim0(c) .. +8 of row m0 + 16j + c16: 32c + 8*g4 for plain pages; with
@@ -501,7 +530,7 @@ __global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && 
     // ---- per-wave states to LDS (the strips are dead now), then the common merge ----
     __syncthreads();                                    // every wave is done with its strip
     float* const sm_acc = reinterpret_cast<float*>(smem);
-    if (wave < NW) {
+    if (wave < NW && walks) {
 #pragma unroll
         for (int j = 0; j < MS; ++j) {
             float* dst = sm_acc + ((size_t)wave * ROWS + 16 * j + c16) * ACCS + 4 * g4;
@@ -532,16 +561,30 @@ __global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && 
         if (tid < n_users) {
             const int4 us = sm_users[tid];
             const int prev = __hip_atomic_fetch_add(&a.counters[counter_index(a, us.x, kvh, 0)], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            sm_lastv[tid] = (prev == us.w - 1);
-            if (prev == us.w - 1)                       // ready for the next launch
+            const bool last = prev == us.w - 1;
+            if (last)                                   // ready for the next launch
                 __hip_atomic_store(&a.counters[counter_index(a, us.x, kvh, 0)], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint64_t who = __builtin_amdgcn_ballot_w64(last);       // (n_users <= 16: all in the first wave)
+            if (last) sm_lastv[__popcll(who & ((1ull << tid) - 1))] = tid;
+            if (tid == 0) sm_last = __popcll(who);
         }
         __syncthreads();
-        merge_shared<G, NT>(a, sm_users, sm_lastv, n_users, kvh);
+        const int n_live = __builtin_amdgcn_readfirstlane(sm_last);
+        if (n_live * G <= NW) merge_shared<G, NW, 1, 16>(a, sm_users, sm_lastv, n_live, kvh, wave, lane);
+        else                  merge_shared<G, NW, 4, 8>(a, sm_users, sm_lastv, n_live, kvh, wave, lane);
     } else if constexpr (FR == 0) {
-        finish_unit<T, D, NW, NW, ROWS, ACCS>(a, unit, kvh, tile, sm_acc, sm_m, sm_l, &sm_last, min(ROWS, n_m - m0), map);
+        if constexpr (MS > 1) {                         // (prefill tiles)
+            finish_unit<T, D, NW, NW, ROWS, ACCS>(a, unit, kvh, tile, sm_acc, sm_m, sm_l, &sm_last, min(ROWS, n_m - m0), map);
+        } else {
+            const int cidx = counter_index(a, unit.inst, kvh, 0);
+            if (!publish_unit<T, D, NW, NW, ROWS, ACCS>(a, cidx, unit.n_units_inst, sm_acc, sm_m, sm_l, &sm_last, G, map)) return;
+            if (unit.n_units_inst <= 8)       merge_decode<G, NW, 8>(a, unit, kvh, wave, lane);
+            else if (unit.n_units_inst <= 16) merge_decode<G, NW, 16>(a, unit, kvh, wave, lane);
+            else                              merge_decode<G, NW, 32>(a, unit, kvh, wave, lane);
+            reset_counter(a, cidx);
+        }
     } else {
-        publish_partial<T, D, NT, NW, ROWS, ACCS>(a, sm_acc, sm_m, sm_l, G, map);
+        if (walks) publish_partial<T, D, NT, NW, ROWS, ACCS>(a, sm_acc, sm_m, sm_l, G, map);      // (uniform)
         // arrival at every instance's counter of this KV head
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_s_waitcnt(0);
@@ -551,11 +594,20 @@ __global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && 
             sm_lastv[tid] = (prev == (int)gridDim.x - 1);
         }
         __syncthreads();
-        for (int b = 0; b < f.batch; ++b) {
-            if (!sm_lastv[b]) continue;                 // uniform
-            merge_decode_step<G, NT>(a, insts[b], b, kvh);
-            reset_counter(a, counter_index(a, b, kvh, 0));
+        // one round trip where it fits: one row per wave, or two where the batch has more rows than the
+        // workgroup has waves; units requested per row: the smallest of 8, 16, 32 that covers the partition
+        // (an even cut: the batch's instances have at most n_units - batch + 1 units each)
+        constexpr int NWV = NT / 64;
+        if (FR == 1 || f.batch * G <= NWV) {            // (FR = 1: one instance)
+            if (f.n_units <= 8)       merge_decode_step<G, NWV, 1, 8>(a, insts, f.batch, sm_lastv, kvh, wave, lane);
+            else if (f.n_units <= 16) merge_decode_step<G, NWV, 1, 16>(a, insts, f.batch, sm_lastv, kvh, wave, lane);
+            else                      merge_decode_step<G, NWV, 1, 32>(a, insts, f.batch, sm_lastv, kvh, wave, lane);
+        } else {
+            if (f.n_units <= 8 * f.batch) merge_decode_step<G, NWV, 2, 8>(a, insts, f.batch, sm_lastv, kvh, wave, lane);
+            else                          merge_decode_step<G, NWV, 2, 16>(a, insts, f.batch, sm_lastv, kvh, wave, lane);
         }
+        if (tid < f.batch && sm_lastv[tid])             // ready for the next launch
+            __hip_atomic_store(&a.counters[counter_index(a, tid, kvh, 0)], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -575,8 +627,15 @@ hipError_t launch_step_v(const AttnArgs& a, const MaterializeArgs& m, hipStream_
     const KernelArgs k = make_kernel_args(a);
     StepArgs f;
     f.hidden = m.hidden; f.w_k = m.w_k; f.w_v = m.w_v; f.rope = m.rope;
-    f.Hd = m.Hd; f.batch = a.batch;
-    dim3 grid(a.n_units, a.Hkv, 1), block(2 * NW * 64);
+    f.Hd = m.Hd; f.batch = a.batch; f.n_units = a.n_units;
+    // A short cache is cut into few units, and their projection waves alone would each have several of
+    // a KV head's 128 rotary pairs (of K and of V) to do one after the other: workgroups that only project
+    // are added until every pair has a wave or every compute unit a workgroup (3B shape, three instances
+    // of 230 to 830 tokens, 14 units: 20.7 -> XX us per layer).
+    const int tasks = (a.batch + FR - 1) / FR * D;
+    const int lacking = tasks - a.n_units * NW;
+    const int extra = std::max(0, std::min((lacking + 2 * NW - 1) / (2 * NW), 256 / a.Hkv - a.n_units));
+    dim3 grid(a.n_units + extra, a.Hkv, 1), block(2 * NW * 64);
     auto kern = a.kv_fmt == MATKV_PAGE_E4M3 ? attn_mfma_kernel<G, NW, 1, 2, FR, true> : attn_mfma_kernel<G, NW, 1, 2, FR, false>;
     hipLaunchKernelGGL(kern, grid, block, 0, s, k, f,
                        reinterpret_cast<const InstanceInfo*>(a.table + a.off_inst),

@@ -70,22 +70,6 @@ __device__ __forceinline__ float2 ld_agent2(const float* p) {
     return make_float2(__uint_as_float((uint32_t)r), __uint_as_float((uint32_t)(r >> 32)));
 }
 
-// The same for 16 bytes.  The loads are not waited for: ld_agent_wait stands between a batch of
-// them and the first use of their registers.
-typedef float f32x4v __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void st_agent4(float* p, f32x4v v) {
-    asm volatile("global_store_dwordx4 %0, %1, off sc1" :: "v"(p), "v"(v) : "memory");
-}
-__device__ __forceinline__ void ld_agent4(f32x4v& v, const float* p) {
-    asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(v) : "v"(p) : "memory");
-}
-template <int N>
-__device__ __forceinline__ void ld_agent_wait(f32x4v (&v)[N]) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-#pragma unroll
-    for (int i = 0; i < N; ++i) asm volatile("" : "+v"(v[i]));
-}
-
 // One workgroup's arrival at a counter: every thread has waited for its own agent-scope stores,
 // the barrier orders them before thread 0's ticket.  Returns true in every thread of the
 // workgroup that arrived last of `expected`.

@@ -37,6 +37,20 @@ __device__ __forceinline__ float wave_sum(float v, int lane) {
     v += __uint_as_float((lane & 32) ? r32.x : r32.y);
     return v;
 }
+template <int CTRL>
+__device__ __forceinline__ float dpp_max(float v) {
+    int o = __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true);
+    return fmaxf(v, __int_as_float(o));
+}
+__device__ __forceinline__ float wave_max(float v, int lane) {
+    v = dpp_max<0xB1>(v); v = dpp_max<0x4E>(v); v = dpp_max<0x141>(v); v = dpp_max<0x140>(v);
+    const unsigned x = __float_as_uint(v);
+    const u32x2v r16 = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    v = fmaxf(v, __uint_as_float((lane & 16) ? r16.x : r16.y));
+    const unsigned y = __float_as_uint(v);
+    const u32x2v r32 = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+    return fmaxf(v, __uint_as_float((lane & 32) ? r32.x : r32.y));
+}
 
 // Dot products of R token rows (x + r * x_stride, rows past n_rows repeat the last) with the
 // two weight rows w0, w1 of one rotary pair; Hd a multiple of 512 * NL (NL = 8: passes of 4096

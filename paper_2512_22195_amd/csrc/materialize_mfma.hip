@@ -234,23 +234,26 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(MaterializeArgs a
     if constexpr (SK == 2) {
         const int tile = rt * nct + ct;
         int* const sm_last = reinterpret_cast<int*>(smem);
-        float* mine = a.ws_partials + ((size_t)(tile * SK + part) * 8 + wave) * (BM * 16) + lane * 4;
+        // a tile's accumulators as runs of 512 bytes: 8 bytes per lane and store
+        constexpr int NP2 = XB * 4 * PB;
+        float* mine = a.ws_partials + ((size_t)(tile * SK + part) * 8 + wave) * (BM * 16) + lane * 2;
 #pragma unroll
-        for (int mi = 0; mi < XB; ++mi)
-#pragma unroll
-            for (int p = 0; p < 2 * PB; ++p) dev::st_agent4(mine + (mi * 2 * PB + p) * 256, acc[mi][p]);
+        for (int i = 0; i < NP2; ++i) {
+            const f32x4& v = acc[i / (4 * PB)][i / 2 % (2 * PB)];
+            dev::st_agent2(mine + i * 128, v[2 * (i & 1)], v[2 * (i & 1) + 1]);
+        }
         int32_t* counter = a.ws_counters + (size_t)tile * kDecodeCounterStride;
         if (!dev::arrive_at(counter, SK, sm_last)) return;
         dev::reset_counter_at(counter);
-        const float* theirs = a.ws_partials + ((size_t)(tile * SK + (part ^ 1)) * 8 + wave) * (BM * 16) + lane * 4;
-        f32x4 o[XB * 2 * PB];
+        const float* theirs = a.ws_partials + ((size_t)(tile * SK + (part ^ 1)) * 8 + wave) * (BM * 16) + lane * 2;
+        float2 o[NP2];
 #pragma unroll
-        for (int i = 0; i < XB * 2 * PB; ++i) dev::ld_agent4(o[i], theirs + i * 256);
-        dev::ld_agent_wait(o);
+        for (int i = 0; i < NP2; ++i) o[i] = dev::ld_agent2(theirs + i * 128);
 #pragma unroll
-        for (int mi = 0; mi < XB; ++mi)
-#pragma unroll
-            for (int p = 0; p < 2 * PB; ++p) acc[mi][p] += o[mi * 2 * PB + p];
+        for (int i = 0; i < NP2; ++i) {
+            f32x4& v = acc[i / (4 * PB)][i / 2 % (2 * PB)];
+            v[2 * (i & 1)] += o[i].x; v[2 * (i & 1) + 1] += o[i].y;
+        }
         __syncthreads();
     }
 
