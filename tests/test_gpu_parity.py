@@ -100,6 +100,19 @@ def test_fused_decode_step_degenerate_caches():
     _chain_parity(case, fused=True)
 
 
+@pytest.mark.parametrize("batch,Hq,hidden,tokens", [
+    (1, 2, 4096, 5), (1, 6, 3072, 260), (2, 8, 3072, 140), (3, 6, 3072, 300), (4, 8, 4096, 90), (4, 4, 4096, 1100),
+    (1, 8, 4096, 1200), (1, 4, 3072, 4300), (2, 8, 4096, 2500)])
+def test_fused_decode_step_short_caches(batch, Hq, hidden, tokens):
+    """Fused step with workgroups that only project (caches of few units: none, some and all of the
+    pairs on them), and the fold over up to 8, 16, 32 and more units with one and with two rows per wave;
+    instances of uneven length, so that an instance has fewer units than a pass requests."""
+    case = Case(f"fused-short-{batch}-{Hq}-{tokens}", n_layers=1, Hq=Hq, Hkv=2, D=128, hidden=hidden, dtype="bf16",
+                chunk_lens={b: max(1, tokens - 37 * b) for b in range(batch)}, retrieved=[[b] for b in range(batch)],
+                q_lens=[3 + 2 * b for b in range(batch)], steps=3, rope_base=500000.0, scale=1.0 / 8.0, q_scale=1.0)
+    _chain_parity(case, fused=True, use_graph=batch % 2 == 0)
+
+
 def test_decode_step_rejects_bad_arguments():
     from paper_2512_22195_amd import binding as mk
     case = Case("step-args", n_layers=1, Hq=8, Hkv=2, D=128, hidden=4096, dtype="bf16",
