@@ -73,6 +73,14 @@ __device__ __forceinline__ void store_out2(void* out, bool f32, size_t idx, floa
     else *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(out) + idx) = (uint32_t)f32_to_bf16_rne(x) | ((uint32_t)f32_to_bf16_rne(y) << 16);
 }
 
+// Four output elements: 8 bytes of bf16 (the hardware conversion rounds as f32_to_bf16_rne does), or 16 of float.
+__device__ __forceinline__ void store_out4(void* out, bool f32, size_t idx, float4 v) {
+    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    if (f32) { *reinterpret_cast<float4*>(reinterpret_cast<float*>(out) + idx) = v; return; }
+    const bf16x4 b = {(__bf16)v.x, (__bf16)v.y, (__bf16)v.z, (__bf16)v.w};
+    *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(out) + idx) = __builtin_bit_cast(uint2, b);
+}
+
 // Arrival counter of (instance, KV head, row z).  Decode launches keep every counter on a
 // 128-byte line of its own: agent-scope atomics on one line are served one after the other, and
 // a launch's workgroups arrive within a microsecond or two of each other.

@@ -2,23 +2,41 @@
 // time": row i of the question attends to every chunk key and to question keys j <= i).
 //
 // The M dimension is the flattened (question row, query head of one KV head) index.  A
-// workgroup owns a tile of NW*16*MS such rows (NW = 4 or 8 waves) and one work unit of the cache;
-// its waves split the ROWS (16*MS each) and walk the unit's tokens TOGETHER, 64 at a time: each
-// K/V block is fetched from HBM once per workgroup with coalesced 16-byte loads into double-buffered LDS
-// tiles and shared by all waves -
-//   S^T = K Q^T     A = K rows from the LDS tile (padded rows, conflict-free 16-byte reads),
-//                   B = Q held in registers
-//   softmax         online, per lane on its own column; the four 16-lane groups agree on the
-//                   running maximum through register swaps
+// workgroup of eight waves owns a tile of 256 or 128 such rows and one work unit of the cache; a wave
+// owns 32 rows and walks the unit's tokens in blocks:
+//   S^T = K Q^T     32x32x16; A = K rows from LDS, B = Q held in registers
+//   softmax         online, per lane on its own column; the two half waves agree on the running
+//                   maximum through a register swap
 //   O^T += V^T P^T  A = V through the transposing LDS read, B = P rounded to bf16
-// The next block's loads are in flight (in registers) while the current one is computed out of
-// LDS; eight waves share a compute unit (two four-wave workgroups, or one of eight).
-// A wave owns its rows outright, so nothing is merged between waves.  An instance whose cache
-// is one unit gets its output rows straight from the registers; otherwise every unit leaves an
+// 256-row tiles: all waves walk the same 64-token blocks.  128-row tiles: waves 0 to 3 and 4 to 7 own
+// the same rows and take every second 32-token block; their states are folded in LDS at the end.
+//
+// What bounds it.  A step of 64 tokens needs of a SIMD 2 x 32 matrix instructions and 2 x 8 small ones (2200 cycles), of its
+// vector ALU about as much, and of the compute unit's LDS 2 x 8 x 16 KB at 128 bytes a cycle (2050
+// cycles) - so a step takes as long as these fail to overlap, and at full overlap the chip's power
+// limit is near (the clock falls to 1.9 GHz; a large library GEMM reaches 1385 TFLOP/s here).  Hence:
+//  - K and V go from global memory straight into LDS (dma16), into unpadded rows whose 16-byte pieces
+//    are permuted so that operand reads and transposing reads meet no bank conflict; four blocks of a
+//    group are in LDS, two of them landed or in use.
+//  - the two waves of a SIMD run half a step apart (see "the walk"): one multiplies, reads LDS and
+//    requests copies while the other computes its softmax.
+//  - 32x32x16 rather than 16x16x32: one row per lane halves the work per row, and the other wave's
+//    vector instructions lose less (32 multiply-adds and exponentials beside it 464 -> 580 cycles,
+//    beside 16x16x32 816).
+// The form this replaced (16x16x32, operands through registers, all waves in step, 64-token double
+// buffer) took 4900 cycles a step where this takes 3700.  Measured, us per layer with the fold, before
+// -> now: four 70B users of 20 000 tokens 361 -> 338 (990 TFLOP/s), sixteen 8B users of 5 000 175 -> 155, one
+// of 10 000 32 -> 28.6; chunks: 1000 tokens 8B 29 -> 25, 70B 43 -> 36, 3501 tokens 8B 132 -> 114, 4000
+// tokens 70B 295 -> 269.  Tried: every LDS read of the softmax phase spread between its exponentials,
+// copies between the matrix instructions, the vector phase at higher priority: within 2 %.
+//
+// An instance whose cache is one unit gets its output rows directly; otherwise every unit leaves an
 // unnormalised partial (accumulator, running maximum, sum) per row and a second, chip-wide
 // launch folds the units of each row together (the last-arrival merge of the decode kernels
 // would leave that work to a handful of compute units here: the partials of a question are
 // megabytes, not kilobytes).
+#include <type_traits>
+
 #include "attn_common.h"
 
 namespace matkv {
@@ -28,350 +46,469 @@ using namespace attn;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int D = 128;
-// Row strides of the LDS tiles, measured on the chip with the three access patterns used here
-// (16-byte operand reads of 16 rows, transposing 8-byte reads, 16-byte staging writes of whole
-// rows; cycles per instruction with eight waves): K 272 bytes 8.8, 288 bytes 5.4; V 288 bytes
-// 6.7, 304 bytes 6.2.
-constexpr int KSTR = D + 16;        // bf16 per LDS row of the K tile
-constexpr int VSTR = D + 24;        // bf16 per LDS row of the V tile
+constexpr int NW = 8;                 // waves of a workgroup
+constexpr int WR = 32;                // rows of a wave
+constexpr int kPageT0 = -(1 << 30);   // "position" of a page block: every row sees all of it
 constexpr float kLazyLog2 = 8.0f;     // slack of the running reference exponent, in powers of two
 
-__device__ __forceinline__ s16x4 lds_read_tr(const uint16_t* p) {
+__device__ __forceinline__ s16x4 lds_read_tr(const char* p) {
     typedef s16x4 __attribute__((address_space(3))) * lptr;
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lptr)(uintptr_t)p);
 }
 
-// TB = token rows per step (a multiple of 32).  64 against 32 halves the per-step costs that do
-// not depend on the number of tokens (walking the items, addresses, barrier, reference update)
-// and measured 5-12 % ahead.
-// F8: the pages hold E4M3 codes with per-head power-of-two scales (the tail stays bf16).  Codes
-// are widened to bf16 on their way into the LDS tiles (exact).  The K scale multiplies a block's
-// maximum and its exponent factor instead of its scores; the V scale goes into the weights as
-// they are rounded to bf16 (exact: a power of two) and is taken out of the row sums by summing
-// with 1/scale instead of 1 - so the per-element work is the same as for plain pages.
-template <int G, int MS, int TB, bool F8, int NW>
+// One 64- or 32-token block as the multiplying side sees it (wave-uniform).
+struct BlockDesc {
+    int n;              // token rows (0: none left)
+    int t0;             // tail row of the block's first token; kPageT0 for a page
+    int go;             // some group of the workgroup has a block in this step
+    float sk, sv;       // scales of a compressed page's codes
+};
+
+template <int RW, int TB, bool F8>
 __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
         KernelArgs a, const InstanceInfo* __restrict__ insts, const Item* __restrict__ items,
         const Unit* __restrict__ units) {
-    constexpr int WR = 16 * MS;                         // rows per wave
-    constexpr int RT = NW * WR;                         // rows per workgroup
-    constexpr int NH = TB / 32;                         // 32-token halves of a step
+    constexpr int TS = NW / RW;                         // token groups
+    constexpr int RT = RW * WR;                         // rows per workgroup
+    constexpr int NH = TB / 32;                         // 32-token parts of a block
+    constexpr int TILE = TB * D * 2;                    // bytes of a K or a V tile
+    constexpr int NBUF = 128 * 1024 / (TS * 2 * TILE);  // blocks of a group that LDS holds
+    constexpr int NI = TB / (4 * RW);                   // copies of four rows per wave, of K and of V
     typedef uint16_t T;
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rw = wave % RW, tg = wave / RW;           // row wave, token group
     const int lane = tid & 63;
-    const int c16 = lane & 15, g4 = lane >> 4;
+    const int c32 = lane & 31, g2 = lane >> 5;
+    const int G = a.Hq / a.Hkv;                         // 1, 2, 3, 4 or 8
+    auto div_g = [&](int m) { return G == 3 ? (int)__umulhi((unsigned)m, 0x55555556u) : m >> (31 - __builtin_clz(G)); };
     // a chunk's own attention: tile t walks (t + 1) * RT / G keys, so the longest go first
     const int kvh = blockIdx.y, tile = a.prefill == 2 ? gridDim.z - 1 - blockIdx.z : blockIdx.z;
     const int m0 = tile * RT;
 
-    const Unit unit = units[blockIdx.x];
-    const InstanceInfo inst = insts[unit.inst];
+    const Unit unit = table_record(units + blockIdx.x);
+    const InstanceInfo inst = table_record(insts + unit.inst);
     const int n_m = inst.q_len * G;
     if (m0 >= n_m) return;                              // whole workgroup leaves together
-    const int r_last = (min(m0 + RT, n_m) - 1) / G;
-    const bool wave_live = m0 + WR * wave < n_m;        // this wave has at least one real row
-    const int vis_min = (m0 + WR * wave) / G + 1;       // tail rows every row of this wave may see
+    const int r_last = div_g(min(m0 + RT, n_m) - 1);
+    const int wm0 = m0 + WR * rw;
+    const bool wave_live = wm0 < n_m;                   // this wave has at least one real row
+    const int vis_min = div_g(wm0) + 1;                    // tail rows every row of this wave may see
+    const int vis_max = div_g(max(min(wm0 + WR, n_m) - 1, 0)) + 1;
 
-    // Q in operand layout; padding rows repeat the last real row
-    bf16x8 bq[MS][4];
-    int vis[MS];                                        // tail rows this lane's row may see
-#pragma unroll
-    for (int j = 0; j < MS; ++j) {
-        const int m = min(m0 + WR * wave + 16 * j + c16, n_m - 1);
-        const int r = m / G, g = m % G;
-        const T* qp = reinterpret_cast<const T*>(a.q) + ((size_t)(inst.cu_q + r) * a.Hq + (size_t)kvh * G + g) * D + 8 * g4;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) bq[j][c] = __builtin_bit_cast(bf16x8, ldg16(qp + 32 * c));
-        vis[j] = r + 1;
-    }
-
-    f32x4 ot[MS][8], ol[MS];          // O^T accumulators; row sums (every element of a lane the same)
-    float mrow[MS];                   // reference score of the lane's row, unscaled
-#pragma unroll
-    for (int j = 0; j < MS; ++j) {
-        mrow[j] = kNegBig;
-        ol[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < 8; ++s) ot[j][s] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-
-    constexpr int TILE_ELEMS = TB * KSTR + TB * VSTR;               // one K tile + one V tile
-    __shared__ __attribute__((aligned(16))) uint16_t tiles[2 * TILE_ELEMS];
-
-    // The unit's item list sits in LDS: fetching an item from global memory inside the loop
-    // would put a memory wait there that also drains the block loads in flight.
-    __shared__ __attribute__((aligned(16))) Item sm_items[kMaxPrefillItemsPerUnit];
-    __shared__ float sm_scale[F8 ? kMaxPrefillItemsPerUnit : 1][2];    // K and V scale of every item
-    for (int i = tid; i < unit.n_items * 2; i += NW * 64)
-        reinterpret_cast<uint4*>(sm_items)[i] = reinterpret_cast<const uint4*>(items + unit.item0)[i];
-    if (F8 && tid < unit.n_items) {
-        const Item it = items[unit.item0 + tid];
-        float sk = 1.f, sv = 1.f;
-        if (it.base) page_scales(it, a.layer, a.Hkv, kvh, sk, sv);
-        sm_scale[tid][0] = sk; sm_scale[tid][1] = sv;
-    }
-    __syncthreads();
-
-    // Every wave walks the same blocks: the unit's items end to end (the tail clipped to the
-    // rows this tile may see), TB token rows at a time, never across two items.
-    struct {
-        Item item;
-        int item_i, rows, left;         // current item, its visible rows, rows of it not yet handed out
-    } wk;
-    const int tail_visible = r_last + 1;
-    auto rows_of = [&](const Item& it) { return it.base ? it.ntok : min(min(it.ntok, tail_visible), a.max_tail); };
-    wk.item = unit.first; wk.item_i = 0; wk.rows = rows_of(wk.item); wk.left = wk.rows;
-    // Past the unit's end the previous block comes back marked invalid: still safe to load,
-    // so that the loop below can issue its loads unconditionally.
-    BlockRef<T> last_block;
-    last_block.valid = false; last_block.is_tail = false; last_block.k = nullptr; last_block.v = nullptr;
-    last_block.t0 = 0; last_block.tok_end = 0; last_block.sk = 1.f; last_block.sv = 1.f;
-    auto next_block = [&]() {
-        BlockRef<T> r = last_block;
-        r.valid = false;
-        while (wk.left <= 0) {
-            if (++wk.item_i >= unit.n_items) return r;
-            wk.item = sm_items[wk.item_i];
-            wk.rows = rows_of(wk.item);
-            wk.left = wk.rows;
-        }
-        r.sk = 1.f; r.sv = 1.f;
-        if (wk.item.base) {
-            const size_t head_elems = (size_t)wk.item.page_tokens * D;
-            if (F8) {
-                const uint8_t* codes = reinterpret_cast<const uint8_t*>(wk.item.base);
-                r.k = reinterpret_cast<const T*>(codes + ((size_t)(a.layer * 2 + 0) * a.Hkv + kvh) * head_elems);
-                r.v = reinterpret_cast<const T*>(codes + ((size_t)(a.layer * 2 + 1) * a.Hkv + kvh) * head_elems);
-                r.sk = sm_scale[wk.item_i][0]; r.sv = sm_scale[wk.item_i][1];
-            } else {
-                const T* blob = reinterpret_cast<const T*>(wk.item.base);
-                r.k = blob + ((size_t)(a.layer * 2 + 0) * a.Hkv + kvh) * head_elems;
-                r.v = blob + ((size_t)(a.layer * 2 + 1) * a.Hkv + kvh) * head_elems;
-            }
+    // NBUF blocks of K and V per token group; the finished rows once those are dead
+    __shared__ __attribute__((aligned(1024))) char smem[TS * NBUF * 2 * TILE];
+    static_assert(NW * WR * D * 4 <= TS * NBUF * 2 * TILE, "finished rows fit over the dead tiles");
+    __shared__ float sm_m[NW * WR], sm_l[NW * WR];
+    // Every group walks the same blocks - the unit's items end to end (the tail clipped to the rows
+    // this tile may see), TB token rows at a time, never across two items - and takes every TS-th.
+    // All of it is wave-uniform.
+    struct { const char* k; const char* v; int tok0, rows, left, item_i; bool tail; } wk;
+    const int tail_visible = min(r_last + 1, a.max_tail);
+    // rows of the item not yet handed out: from tok0 + rows - left on, K and V of the next one at k and v
+    auto set_item = [&](uint64_t base, int page_tokens, int tok0, int ntok) {
+        wk.tail = base == 0;
+        wk.tok0 = tok0;
+        wk.rows = wk.left = base ? ntok : min(ntok, tail_visible);
+        if (base) {
+            const size_t row = F8 ? D : 2 * D, head = (size_t)page_tokens * row;
+            wk.k = reinterpret_cast<const char*>(base) + ((size_t)a.layer * 2 * a.Hkv + kvh) * head + (size_t)tok0 * row;
+            wk.v = wk.k + (size_t)a.Hkv * head;
         } else {
-            const size_t off = ((size_t)unit.inst * a.Hkv + kvh) * (size_t)a.max_tail * D;
-            r.k = reinterpret_cast<const T*>(a.tail_k) + off;
-            r.v = reinterpret_cast<const T*>(a.tail_v) + off;
-            r.is_tail = true;
+            const size_t off = (((size_t)unit.inst * a.Hkv + kvh) * (size_t)a.max_tail + tok0) * (2 * D);
+            wk.k = reinterpret_cast<const char*>(a.tail_k) + off;
+            wk.v = reinterpret_cast<const char*>(a.tail_v) + off;
         }
-        if (wk.item.base) r.is_tail = false;
-        const int n = min(TB, wk.left);
-        r.t0 = wk.item.tok0 + (wk.rows - wk.left);
-        r.tok_end = r.t0 + n;
-        r.valid = true;
-        wk.left -= n;
-        last_block = r;
-        return r;
     };
-
-    // cooperative staging: thread t moves rows t/16 + RPP*i, columns 8*(t%16), of K and of V
-    constexpr int RPP = NW * 4;                         // rows the workgroup moves per pass
-    const int st_row = tid >> 4, st_col = (tid & 15) * 8;
-    constexpr int SR = TB / RPP;
-    struct Stage { uint4 k[SR], v[SR]; };
-    auto load_global = [&](const BlockRef<T>& r, Stage& g) {
-        if (F8 && !r.is_tail) {      // the same number of loads, half as wide (see the loop below)
-#pragma unroll
-            for (int i = 0; i < SR; ++i) {
-                const size_t off = (size_t)min(r.t0 + st_row + RPP * i, r.tok_end - 1) * D + st_col;
-                const uint2 kw = ldg8(reinterpret_cast<const uint8_t*>(r.k) + off);
-                const uint2 vw = ldg8(reinterpret_cast<const uint8_t*>(r.v) + off);
-                g.k[i] = make_uint4(kw.x, kw.y, 0u, 0u);
-                g.v[i] = make_uint4(vw.x, vw.y, 0u, 0u);
-            }
+    // The next item's record is fetched (scalar loads) when its predecessor is taken up, so that taking
+    // it up waits for nothing.
+    struct { Item it; float sk, sv; } ahead;
+    float sk = 1.f, sv = 1.f;                           // scales of the current item
+    auto fetch_item = [&](int i) {
+        ahead.it = table_record(items + unit.item0 + min(i, unit.n_items - 1));
+        ahead.sk = 1.f; ahead.sv = 1.f;
+        if (F8 && ahead.it.base) page_scales(ahead.it, a.layer, a.Hkv, kvh, ahead.sk, ahead.sv);
+    };
+    wk.item_i = 0;
+    set_item(unit.first.base, unit.first.page_tokens, unit.first.tok0, unit.first.ntok);
+    if (F8 && unit.first.base) page_scales(unit.first, a.layer, a.Hkv, kvh, sk, sv);
+    fetch_item(1);
+    // where a block's rows lie: K and V of its first row, row stride 2 D bytes (codes: D bytes).
+    // Past the unit's end the last block comes back (or, for a group that never had one, the unit's
+    // first row), with n = 0 in its descriptor: still safe to copy, so that copies are unconditional.
+    struct Source { const char* k; const char* v; int n; bool codes; };
+    Source src;
+    src.k = wk.k; src.v = wk.v; src.n = 1; src.codes = F8 && !wk.tail;
+    auto next_step = [&](BlockDesc& d) {
+        if (!F8 && wk.left >= TS * TB) {                // the common case, in a few scalar instructions
+            const int skip = tg * TB;
+            d.n = TB; d.go = 1; d.sk = 1.f; d.sv = 1.f;
+            d.t0 = wk.tail ? wk.tok0 + wk.rows - wk.left + skip : kPageT0;
+            src.k = wk.k + skip * (2 * D); src.v = wk.v + skip * (2 * D); src.n = TB;
+            wk.left -= TS * TB;
+            wk.k += TS * TB * 2 * D; wk.v += TS * TB * 2 * D;
             return;
         }
+        d.n = 0; d.t0 = kPageT0; d.go = 0; d.sk = 1.f; d.sv = 1.f;
 #pragma unroll
-        for (int i = 0; i < SR; ++i) {
-            const size_t off = (size_t)min(r.t0 + st_row + RPP * i, r.tok_end - 1) * D + st_col;
-            g.k[i] = ldg16(r.k + off);
-            g.v[i] = ldg16(r.v + off);
-        }
-    };
-    auto store_lds = [&](int buf, const Stage& g, bool codes) {
-        uint16_t* kt = tiles + buf * TILE_ELEMS;
-        uint16_t* vt = kt + TB * KSTR;
-#pragma unroll
-        for (int i = 0; i < SR; ++i) {
-            uint4 kw = g.k[i], vw = g.v[i];
-            if (F8 && codes) {
-                kw = e4m3x8_to_bf16x8(make_uint2(kw.x, kw.y));
-                vw = e4m3x8_to_bf16x8(make_uint2(vw.x, vw.y));
+        for (int g = 0; g < TS; ++g) {
+            while (wk.left <= 0) {
+                if (wk.item_i + 1 >= unit.n_items) return;
+                ++wk.item_i;
+                set_item(ahead.it.base, ahead.it.page_tokens, ahead.it.tok0, ahead.it.ntok);
+                sk = ahead.sk; sv = ahead.sv;
+                fetch_item(wk.item_i + 1);
             }
-            *reinterpret_cast<uint4*>(kt + (st_row + RPP * i) * KSTR + st_col) = kw;
-            *reinterpret_cast<uint4*>(vt + (st_row + RPP * i) * VSTR + st_col) = vw;
+            const int n = min(TB, wk.left);
+            if (g == 0) d.go = 1;
+            if (g == tg) {
+                src.k = wk.k; src.v = wk.v; src.n = n; src.codes = F8 && !wk.tail;
+                d.n = n;
+                d.t0 = wk.tail ? wk.tok0 + wk.rows - wk.left : kPageT0;
+                d.sk = sk; d.sv = sv;
+            }
+            wk.left -= n;
+            const int bytes = n * (F8 && !wk.tail ? D : 2 * D);
+            wk.k += bytes; wk.v += bytes;
         }
     };
+
+    // A tile's rows are 256 bytes, sixteen 16-byte pieces.  Piece p of K row r sits at place
+    // p ^ (r & 15), of V row r at p ^ 4 (r & 3); rows past the block's end repeat its last one.
+    char* const group_lds = smem + tg * (NBUF * 2 * TILE);
+    const uint32_t lds0 = dev::lds_address(smem) + tg * (NBUF * 2 * TILE);
+    const int lrow = lane >> 4, place = lane & 15;
+    auto copy = [&](const Source& s, int buf) {
+        const uint32_t base = lds0 + buf * 2 * TILE + rw * 1024;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int r = 4 * (rw + RW * i) + lrow;
+            const uint32_t row = (uint32_t)min(r, s.n - 1) * (2 * D);
+            dev::dma16(s.k, row + 16 * (place ^ (r & 15)), base + i * RW * 1024);
+            dev::dma16(s.v, row + 16 * (place ^ (4 * (r & 3))), base + TILE + i * RW * 1024);
+        }
+    };
+    // Compressed pages: codes go through registers (one step ahead of the copy they replace) and are
+    // widened to bf16 on their way into the tile.  A lane moves 16 codes of a row: two pieces.
+    constexpr int NC = TB * D / (RW * 64 * 16);         // 16-byte loads per lane, of K and of V
+    struct Codes { uint4 k[NC], v[NC]; } codes;
+    const int ct = rw * 64 + lane;
+    auto load_codes = [&](Codes& codes, const Source& s) {
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            const int r = (ct >> 3) + RW * 8 * i;
+            const uint32_t off = (uint32_t)min(r, s.n - 1) * D + 16 * (ct & 7);
+            codes.k[i] = ldg16(s.k + off);
+            codes.v[i] = ldg16(s.v + off);
+        }
+    };
+    auto store_codes = [&](const Codes& codes, int buf) {
+        char* const kt = group_lds + buf * 2 * TILE;
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            const int r = (ct >> 3) + RW * 8 * i, p = 2 * (ct & 7);
+            char* const row = kt + r * (2 * D);
+            *reinterpret_cast<uint4*>(row + 16 * (p ^ (r & 15))) = e4m3x8_to_bf16x8(make_uint2(codes.k[i].x, codes.k[i].y));
+            *reinterpret_cast<uint4*>(row + 16 * ((p + 1) ^ (r & 15))) = e4m3x8_to_bf16x8(make_uint2(codes.k[i].z, codes.k[i].w));
+            *reinterpret_cast<uint4*>(row + TILE + 16 * (p ^ (4 * (r & 3)))) = e4m3x8_to_bf16x8(make_uint2(codes.v[i].x, codes.v[i].y));
+            *reinterpret_cast<uint4*>(row + TILE + 16 * ((p + 1) ^ (4 * (r & 3)))) = e4m3x8_to_bf16x8(make_uint2(codes.v[i].z, codes.v[i].w));
+        }
+    };
+
+    f32x16 ot[4];                     // O^T: dims 32 t + 8 (i / 4) + 4 g2 + i % 4 of the lane's row
+    f32x4 ol = f32x4{0.f, 0.f, 0.f, 0.f};   // sum of this lane's weights (every element the same; [0] is kept right)
+    float mrow = kNegBig;             // reference score of the lane's row, unscaled
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) ot[t][i] = 0.f;
 
     // Scores stay unscaled until the exponent: 2^((s - m) c) is one multiply-add and one
-    // exponential per element, with m the row's reference score (unscaled too).  The row sums
-    // come from the matrix cores as well - P times a block of ones - which sums the weights
-    // exactly as the output uses them (rounded to bf16) and spares the vector ALU the adds.
+    // exponential per element, with m the row's reference score (unscaled too).
     const float sc = a.scale_log2e;
     const float lazy_raw = kLazyLog2 / sc;
-    bf16x8 ones;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) ones[i] = (__bf16)1.0f;
 
-    // masked: the block is ragged, or lies in the tail and reaches past what the wave's first
-    // row may see (per-row causal limit); otherwise all TB rows are visible to every question
-    // row of the wave and no element needs a test.
-    auto compute = [&](const BlockRef<T>& r, int buf) {
-        const bool masked = r.tok_end - r.t0 != TB || (r.is_tail && r.tok_end > vis_min);
-        const uint16_t* kt = tiles + buf * TILE_ELEMS;
-        const uint16_t* vt = kt + TB * KSTR;
-        // compressed page: scores carry the factor 1 / sk until the exponent, weights the factor
-        // sv from the exponent on (nsv = log2 sv goes into the exponent's offset)
-        const float scb = F8 ? sc * r.sk : sc;
-        const float nsv = F8 ? __builtin_amdgcn_frexp_expf(r.sv) - 1.0f : 0.f;
-        bf16x8 ones_b = ones;
+    const int koff = c32 * 256 + 16 * (g2 ^ (c32 & 15));
+    const int e16 = lane & 15;
+    const int voff = TILE + (4 * g2 + (e16 >> 2)) * 256 + 64 * (e16 >> 2) + 32 * ((lane >> 4) & 1) + 8 * (e16 & 3);
+    // (the addresses of a step are formed from one register each time: kept over the loop they would
+    // cost the twelve registers that there are not)
+    auto read_k = [&](bf16x8 (&f)[8], int buf, int h) {
+        int o = koff + (tg * NBUF + buf) * 2 * TILE;
+        asm volatile("" : "+v"(o));
+#pragma unroll
+        for (int c = 0; c < 8; ++c) f[c] = *reinterpret_cast<const bf16x8*>(smem + (o ^ (32 * c)) + h * 8192);
+    };
+    auto read_v = [&](bf16x8 (&f)[2][4], int buf, int h, int t) {       // dims 32 t ..
+        int o = voff + (tg * NBUF + buf) * 2 * TILE;
+        asm volatile("" : "+v"(o));
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const char* p = smem + (o ^ (64 * t)) + (32 * h + 16 * u) * 256;
+            const s16x4 lo = lds_read_tr(p), hi = lds_read_tr(p + 8 * 256);
+            f[u][t] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+        }
+    };
+
+    // ---- the walk ----
+    // A step of a wave has a matrix phase X(i) - P V of block i - 1, then the scores of block i, all
+    // LDS reads and the copy of block i + 2 - and a vector phase Y(i) - softmax of block i - with a
+    // barrier behind each.  Waves 4 to 7, which share their SIMDs with waves 0 to 3, run one phase
+    // behind: while one wave of a SIMD multiplies, the other is in its vector phase.  Block i is read
+    // in X(i), Y(i) and X(i + 1) and, by the late waves, one phase on; X(i + 2), which copies block
+    // i + 4 over it, comes behind the barrier that ends the late waves' X(i + 1).  X(i) ends when
+    // block i + 1 has landed: the early waves read it from X(i + 1) on, one barrier after the late
+    // waves have passed that wait.
+    static_assert(NBUF == 4, "in use: two blocks; landed or in flight: two");
+    const bool late = wave >= NW / 2;
+    BlockDesc q[3];                   // descriptors of blocks i, i + 1, i + 2
+    Source next_src;                  // where block i + 2 lies
+    next_step(q[0]);
+    Codes first;
+    const bool codes0 = src.codes;
+    if (F8 && codes0) load_codes(first, src); else copy(src, 0);
+    // Q comes through LDS as well - over the tiles of blocks 2 and 3, which nothing else needs yet - so
+    // that whole rows are fetched and the first two blocks can be on their way at the same time; padding
+    // rows repeat the last real row.  Placed like K rows, and read like them: B operand, lane's row c32.
+    char* const q_lds = smem + (RW == NW ? 2 * 2 * TILE : TS * NBUF * 2 * TILE - RT * 2 * D);
+    static_assert(RT * 2 * D <= 2 * 2 * TILE, "Q fits over two blocks of a group");
+    {
+        const T* qb = reinterpret_cast<const T*>(a.q) + ((size_t)inst.cu_q * a.Hq + (size_t)kvh * G) * D;
+        const uint32_t q0 = dev::lds_address(q_lds) + wave * 1024;
+#pragma unroll
+        for (int i = 0; i < RT / (4 * NW); ++i) {
+            const int row = 4 * (wave + NW * i) + lrow, m = min(m0 + row, n_m - 1);
+            const int r = div_g(m), g = m - r * G;
+            dev::dma16(qb, (uint32_t)((r * a.Hq + g) * (2 * D)) + 16 * (place ^ (row & 15)), q0 + i * NW * 1024);
+        }
+    }
+    next_step(q[1]);
+    const bool codes1 = src.codes;
+    if (F8 && codes1) load_codes(codes, src); else copy(src, 1);
+    next_step(q[2]);
+    next_src = src;
+    if (F8) {                                   // (compressed pages: the codes of block i + 2 wait in registers)
+        if (codes0) store_codes(first, 0);
+        if (codes1) store_codes(codes, 1);
+        dev::dma_wait<0>();
+        if (src.codes) load_codes(codes, src);
+    } else {
+        dev::dma_wait<2 * NI>();                // Q and block 0 are there
+    }
+    lds_barrier();
+    bf16x8 bq[8];                     // dims 16 c + 8 g2 ..
+    const int vis = div_g(min(wm0 + c32, n_m - 1)) + 1;    // tail rows this lane's row may see
+#pragma unroll
+    for (int c = 0; c < 8; ++c) bq[c] = *reinterpret_cast<const bf16x8*>(q_lds + rw * (WR * 2 * D) + (koff ^ (32 * c)));
+    lds_barrier();                              // X(0) copies over it
+    bf16x8 av[NH][2][4], pb[NH][2];   // V operands (the first 32 tokens' read ahead in Y), weights
+    auto barrier_plain = [&]() {      // every LDS read before it is consumed before the next one
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // The row sums come from the matrix cores as well: they add the weights exactly as the output uses
+    // them (rounded to bf16).  A column of the 4x4x4 instruction's sixteen blocks is a lane's own four
+    // values, so with ones as A each lane gets the sum of its own weights (and a row that is not a number
+    // reaches no other): 8 cycles for four weights per lane.  (As dot products of the vector ALU they took
+    // eight times as long while the other wave of the SIMD multiplies: 16 of them 1154 cycles against 130.)
+    float ones_v = 1.0f;              // (compressed page: 1 / sv, so that the factor sv of the weights cancels)
+    auto multiply_pv = [&](int h) {
+        const short one = __builtin_bit_cast(short, (__bf16)(F8 ? ones_v : 1.0f));
+        const s16x4 ones = {one, one, one, one};
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const s16x8 w = __builtin_bit_cast(s16x8, pb[h][u]);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                ot[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[h][u][t], pb[h][u], ot[t], 0, 0, 0);
+                if (t == 1) ol = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, __builtin_shufflevector(w, w, 0, 1, 2, 3), ol, 0, 0, 0);
+                if (t == 3) ol = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, __builtin_shufflevector(w, w, 4, 5, 6, 7), ol, 0, 0, 0);
+            }
+        }
+    };
+    f32x16 st[NH];                    // S^T: tokens 32 h + 8 (i / 4) + 4 g2 + i % 4
+    auto multiply_qk = [&](const bf16x8 (&ak)[8], int h) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) st[h][i] = 0.f;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) st[h] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak[c], bq[c], st[h], 0, 0, 0);
+    };
+    auto spread = [&](auto reads) {   // eight matrix instructions, `reads` LDS reads behind each
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, decltype(reads)::value, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    if (late) barrier_plain();
+    int buf = 0;
+    bool prev_live = false;
+    bool copied = false;              // compressed pages: a block of the tail is on its way
+    while (q[0].go) {
+        const BlockDesc d = q[0];
+        const bool live = wave_live && d.n > 0 && d.t0 < vis_max;
+        // X (its wave goes first: a matrix instruction needs the issue port once in 32 cycles)
+        __builtin_amdgcn_s_setprio(1);
+        bf16x8 ak[NH][8];
+        if (prev_live) {
+            if constexpr (NH == 2) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) read_v(av[1], (buf + 3) & 3, 1, t);
+                multiply_pv(0);
+                spread(std::integral_constant<int, 2>{});
+            }
+            read_k(ak[0], buf, 0);
+            multiply_pv(NH - 1);
+            spread(std::integral_constant<int, 1>{});
+        } else if (live) {
+            read_k(ak[0], buf, 0);
+        }
+        if (!F8) copy(next_src, (buf + 2) & 3);
+        if (live) {
+            if constexpr (NH == 2) {
+                read_k(ak[1], buf, 1);
+                multiply_qk(ak[0], 0);
+                spread(std::integral_constant<int, 1>{});
+            }
+            multiply_qk(ak[NH - 1], NH - 1);
+        }
+        if (!F8) dev::dma_wait<2 * NI>();
+        else if (copied) { dev::dma_wait<0>(); copied = false; }
+        barrier_plain();
+        // Y
+        __builtin_amdgcn_s_setprio(0);
         if (F8) {
-            const __bf16 iv = (__bf16)(1.0f / r.sv);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) ones_b[i] = iv;
+            if (next_src.codes) { store_codes(codes, (buf + 2) & 3); }
+            else { copy(next_src, (buf + 2) & 3); copied = true; }
         }
-        // S^T in 16-token quarters q: lane holds tokens t0 + 16q + 4*g4 + i of its row
-        f32x4 st[MS][2 * NH];
+        q[0] = q[1]; q[1] = q[2];
+        next_step(q[2]);
+        next_src = src;
+        if (F8 && src.codes) load_codes(codes, src);
+        if (live) {
+            // masked: the block is ragged, or lies in the tail and reaches past what the wave's first
+            // row may see (per-row causal limit); otherwise all rows see all of it
+            if (d.n != TB || d.t0 + d.n > vis_min) {        // wave-uniform
+                const int limit = min(d.n, vis - d.t0) - 4 * g2;
 #pragma unroll
-        for (int h = 0; h < NH; ++h) {
-            bf16x8 ak[2][4];
+                for (int h = 0; h < NH; ++h)
 #pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    ak[hh][c] = *reinterpret_cast<const bf16x8*>(kt + (32 * h + 16 * hh + c16) * KSTR + 32 * c + 8 * g4);
-#pragma unroll
-            for (int j = 0; j < MS; ++j) {
-                st[j][2 * h] = f32x4{0.f, 0.f, 0.f, 0.f};
-                st[j][2 * h + 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    for (int i = 0; i < 16; ++i) st[h][i] = 32 * h + 8 * (i / 4) + i % 4 < limit ? st[h][i] : kNegBig;
             }
-            // dim chunk outermost: 2 * MS independent accumulation chains are interleaved, so no
-            // matrix instruction waits for the result of the one just before it
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-#pragma unroll
-                for (int j = 0; j < MS; ++j) {
-                    st[j][2 * h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ak[0][c], bq[j][c], st[j][2 * h], 0, 0, 0);
-                    st[j][2 * h + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ak[1][c], bq[j][c], st[j][2 * h + 1], 0, 0, 0);
-                }
-        }
-        bf16x8 pb[MS][NH];
-#pragma unroll
-        for (int j = 0; j < MS; ++j) {
-            float sv[8 * NH];
-#pragma unroll
-            for (int q = 0; q < 2 * NH; ++q)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) sv[4 * q + i] = st[j][q][i];
-            if (masked) {           // wave-uniform
-                const int limit = r.is_tail ? min(r.tok_end, vis[j]) : r.tok_end;
-                const int tb = r.t0 + 4 * g4;
-#pragma unroll
-                for (int q = 0; q < 2 * NH; ++q)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) sv[4 * q + i] = tb + 16 * q + i < limit ? sv[4 * q + i] : kNegBig;
-            }
-            float mx = sv[0];
-#pragma unroll
-            for (int i = 1; i < 8 * NH; ++i) mx = fmaxf(mx, sv[i]);
-            mx = fmaxf(mx, lane_xor(mx, 16, lane));
-            mx = fmaxf(mx, lane_xor(mx, 32, lane));
-            if (F8) mx = mx > 0.5f * kNegBig ? mx * r.sk : kNegBig;     // into the units of the reference
-            // The reference score of a row moves only when the block's maximum exceeds it by
-            // more than kLazyLog2 powers of two: weights stay below 2^kLazyLog2, and the
-            // accumulators are rescaled on few blocks instead of on most.
-            const float mn = mx > mrow[j] + lazy_raw ? mx : mrow[j];
-            const float alpha = fast_exp2((mrow[j] - mn) * sc);
-            mrow[j] = mn;
-            // a row that has seen no key yet keeps the floor as its reference; its masked
-            // scores must still come out as weight 0, not 2^0
-            const float nmc = mn > 0.5f * kNegBig ? -mn * sc : 0.f;
+            float mx = st[0][0];
 #pragma unroll
             for (int h = 0; h < NH; ++h)
 #pragma unroll
-                for (int i = 0; i < 8; ++i) pb[j][h][i] = (__bf16)fast_exp2(fmaf(sv[8 * h + i], scb, nmc + nsv));
+                for (int i = 0; i < 16; ++i) mx = fmaxf(mx, st[h][i]);
+            mx = fmaxf(mx, lane_xor(mx, 32, lane));
+            // compressed page: scores carry the factor 1 / sk until the exponent, weights the factor
+            // sv from the exponent on (nsv = log2 sv goes into the exponent's offset)
+            if (F8) mx = mx > 0.5f * kNegBig ? mx * d.sk : kNegBig;     // into the units of the reference
+            const float scb = F8 ? sc * d.sk : sc;
+            const float nsv = F8 ? __builtin_amdgcn_frexp_expf(d.sv) - 1.0f : 0.f;
+            // The reference score of a row moves only when the block's maximum exceeds it by
+            // more than kLazyLog2 powers of two: weights stay below 2^kLazyLog2, and the
+            // accumulators are rescaled on few blocks instead of on most.
+            const float mn = mx > mrow + lazy_raw ? mx : mrow;
+            const float alpha = fast_exp2((mrow - mn) * sc);
+            mrow = mn;
+            // a row that has seen no key yet keeps the floor as its reference; its masked
+            // scores must still come out as weight 0, not 2^0
+            const float nmc = (mn > 0.5f * kNegBig ? -mn * sc : 0.f) + nsv;
             if (__builtin_amdgcn_ballot_w64(alpha != 1.0f)) {   // wave-uniform: some row's reference moved
-                ol[j][0] *= alpha;
+                ol[0] *= alpha;
 #pragma unroll
-                for (int s = 0; s < 8; ++s) {
-                    ot[j][s][0] *= alpha; ot[j][s][1] *= alpha; ot[j][s][2] *= alpha; ot[j][s][3] *= alpha;
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) ot[t][i] *= alpha;
+            }
+            if (F8) ones_v = 1.0f / d.sv;
+            // (the V operand of the first 32 tokens is read for X(i + 1) on the way, a few reads per group
+            // of exponentials: issued together they would hold up the wave)
+#pragma unroll
+            for (int h = 0; h < NH; ++h)
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) pb[h][u][i] = (__bf16)fast_exp2(fmaf(st[h][8 * u + i], scb, nmc));
                 }
-            }
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int h = 0; h < NH; ++h) ol[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones_b, pb[j][h], ol[j], 0, 0, 0);
-        }
-        // lane (c16, g4) names 4 dims (4*(c16%4) ..) of token 4*g4 + c16/4 (+16 for the second
-        // quarter) of a half and receives dim 16s + c16 of tokens 4*g4 .. 4*g4+3: the k order of P
+            for (int t = 0; t < 4; ++t) read_v(av[0], buf, 0, t);
+        } else {
+            // not used again: without this the old values would take registers through the whole step
 #pragma unroll
-        for (int h = 0; h < NH; ++h) {
-            const uint16_t* vp = vt + (32 * h + 4 * g4 + (c16 >> 2)) * VSTR + 4 * (c16 & 3);
+            for (int i = 0; i < NH * 2; ++i) {
+                asm volatile("" : "=v"(pb[i / 2][i % 2]));
 #pragma unroll
-            for (int s = 0; s < 8; ++s) {
-                const s16x4 lo = lds_read_tr(vp + 16 * s);
-                const s16x4 hi = lds_read_tr(vp + 16 * VSTR + 16 * s);
-                const bf16x8 av = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-#pragma unroll
-                for (int j = 0; j < MS; ++j)
-                    ot[j][s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, pb[j][h], ot[j][s], 0, 0, 0);
+                for (int t = 0; t < 4; ++t) asm volatile("" : "=v"(av[i / 2][i % 2][t]));
             }
         }
-    };
-
-    // Loads and LDS stores are unconditional (a block past the end repeats the last one) and the
-    // loops have one exit at the bottom: a load under a branch, or a break half way, would leave
-    // the compiler no exact count of the loads in flight, and it would then wait for all of them.
-    // Every load before the loop (Q above all) is waited for once, ahead of it: otherwise each
-    // first use of Q inside the loop is guarded with a wait that, loads completing in order, would
-    // also drain the block just requested.
-    BlockRef<T> r0 = next_block();
-    if (r0.valid) {
-        // one register stage: the next block's loads are in flight while this one is computed,
-        // then move into the other LDS tile
-        Stage g;
-        load_global(r0, g);
-        store_lds(0, g, !r0.is_tail);
-        __builtin_amdgcn_s_waitcnt(0x0F70);             // vmcnt(0) only
-        lds_barrier();
-        int buf = 0;
-        do {
-            const BlockRef<T> r1 = next_block();
-            load_global(r1, g);
-            if (wave_live) compute(r0, buf);
-            store_lds(buf ^ 1, g, !r1.is_tail);
-            lds_barrier();
-            r0 = r1;
-            buf ^= 1;
-        } while (r0.valid);
+        prev_live = live;
+        buf = (buf + 1) & 3;
+        if (F8) lds_barrier();      // (the widened codes are written)
+        else barrier_plain();
     }
-    if (!wave_live) return;
+    if (!late) barrier_plain();
+    if (prev_live) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) if constexpr (NH == 2) read_v(av[1], (buf + 3) & 3, 1, t);
+#pragma unroll
+        for (int h = 0; h < NH; ++h) multiply_pv(h);
+    }
+    dev::dma_wait<0>();                                  // (copies past the end)
+    __syncthreads();
 
-    // ---- a wave owns its rows: results leave straight from the registers ----
-    // lane (c16, g4) holds, for row 16j + c16 of the wave, dims 16s + 4*g4 + {0..3}
+    // ---- finished rows leave through LDS as whole rows; token groups are folded on the way ----
+    // wave w's 32 rows of 512 bytes, piece p (4 dims) of row r at place p ^ r
+    if (wave_live) {
+        char* const mine = smem + wave * (WR * D * 4) + c32 * (D * 4);
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                *reinterpret_cast<float4*>(mine + 16 * ((8 * t + 2 * j + g2) ^ c32)) =
+                    make_float4(ot[t][4 * j], ot[t][4 * j + 1], ot[t][4 * j + 2], ot[t][4 * j + 3]);
+        const float l = ol[0] + lane_xor(ol[0], 32, lane);
+        if (g2 == 0) { sm_m[wave * WR + c32] = mrow * sc; sm_l[wave * WR + c32] = l; }
+    }
+    __syncthreads();
     const bool single = unit.n_units_inst == 1;
+    const int rows_here = min(RT, n_m - m0);
+    for (int row = tid >> 5; row < rows_here; row += NW * 2) {
+        const int w0 = row / WR, rr = row % WR;
+        float M = sm_m[row];
 #pragma unroll
-    for (int j = 0; j < MS; ++j) {
-        const int m = m0 + WR * wave + 16 * j + c16;
-        if (m >= n_m) continue;
-        const int r = m / G, head = kvh * G + m % G;
+        for (int g = 1; g < TS; ++g) M = fmaxf(M, sm_m[g * RT + row]);
+        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+        float L = 0.f;
+#pragma unroll
+        for (int g = 0; g < TS; ++g) {
+            const float4 v = *reinterpret_cast<const float4*>(smem + ((g * RW + w0) * WR + rr) * (D * 4) + 16 * (c32 ^ rr));
+            const float w = TS == 1 ? 1.f : fast_exp2(sm_m[g * RT + row] - M);
+            L = fmaf(w, sm_l[g * RT + row], L);
+            acc.x = fmaf(w, v.x, acc.x); acc.y = fmaf(w, v.y, acc.y);
+            acc.z = fmaf(w, v.z, acc.z); acc.w = fmaf(w, v.w, acc.w);
+        }
+        const int m = m0 + row, r = div_g(m), head = kvh * G + m - r * G;
         if (single) {
-            const float inv = 1.0f / ol[j][0];
-            const size_t oidx = ((size_t)(inst.cu_q + r) * a.Hq + head) * D + 4 * g4;
-#pragma unroll
-            for (int s = 0; s < 8; ++s) {
-                store_out2(a.out, a.out_f32, oidx + 16 * s, ot[j][s][0] * inv, ot[j][s][1] * inv);
-                store_out2(a.out, a.out_f32, oidx + 16 * s + 2, ot[j][s][2] * inv, ot[j][s][3] * inv);
-            }
+            const float inv = 1.0f / L;
+            store_out4(a.out, a.out_f32, ((size_t)(inst.cu_q + r) * a.Hq + head) * D + 4 * c32,
+                       make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv));
         } else {
             float* prow = a.partials + (((size_t)blockIdx.x * a.rows + r) * a.Hq + head) * kPartialStride(D);
-#pragma unroll
-            for (int s = 0; s < 8; ++s)
-                *reinterpret_cast<float4*>(prow + 16 * s + 4 * g4) = make_float4(ot[j][s][0], ot[j][s][1], ot[j][s][2], ot[j][s][3]);
-            if (g4 == 0) *reinterpret_cast<float2*>(prow + D) = make_float2(mrow[j] * sc, ol[j][0]);
+            *reinterpret_cast<float4*>(prow + 4 * c32) = acc;
+            if (c32 == 0) *reinterpret_cast<float2*>(prow + D) = make_float2(M, L);
         }
     }
 }
@@ -434,16 +571,15 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(
     if (n_units == 0) return;
     const float inv = 1.0f / L;
     const size_t oidx = ((size_t)q_row * a.Hq + head) * D + 4 * hl;
-    store_out2(a.out, a.out_f32, oidx, acc.x * inv, acc.y * inv);
-    store_out2(a.out, a.out_f32, oidx + 2, acc.z * inv, acc.w * inv);
+    store_out4(a.out, a.out_f32, oidx, make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv));
 }
 
-template <int G, int MS, int TB, bool F8, int NW = 4>
+template <int RW, int TB, bool F8>
 hipError_t launch_v(const AttnArgs& a, hipStream_t s) {
     const KernelArgs k = make_kernel_args(a);
-    const int tiles = (a.rows * G + NW * 16 * MS - 1) / (NW * 16 * MS);
+    const int tiles = (a.rows * (a.Hq / a.Hkv) + RW * WR - 1) / (RW * WR);
     dim3 grid(a.n_units, a.Hkv, tiles), block(NW * 64);
-    hipLaunchKernelGGL((attn_prefill_kernel<G, MS, TB, F8, NW>), grid, block, 0, s, k,
+    hipLaunchKernelGGL((attn_prefill_kernel<RW, TB, F8>), grid, block, 0, s, k,
                        reinterpret_cast<const InstanceInfo*>(a.table + a.off_inst),
                        reinterpret_cast<const Item*>(a.table + a.off_items),
                        reinterpret_cast<const Unit*>(a.table + a.off_units));
@@ -459,30 +595,9 @@ hipError_t launch_v(const AttnArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int G>
-hipError_t launch_g(const AttnArgs& a, hipStream_t s) {
-    const long rg = (long)a.rows * G;                   // (row, head) rows of the longest question
-    if (a.prefill == 2) {
-        // A chunk's own attention has one workgroup per (row tile, KV head) and the last tile walks
-        // the whole chunk: until 128-row tiles give every compute unit two workgroups, 64-row
-        // tiles do (1024 tokens, 8 KV heads: 31 us against 36 us; 4096 tokens: 269 against 210).
-        // (from 512 eight-wave workgroups on, 256-row tiles are a little ahead: 4096 tokens 188 against 196 us)
-        if (((rg + 255) / 256) * a.Hkv >= 512) return launch_v<G, 2, 64, false, 8>(a, s);
-        if (rg <= 64 || ((rg + 127) / 128) * a.Hkv < 512) return launch_v<G, 1, 64, false>(a, s);
-        return launch_v<G, 2, 64, false>(a, s);
-    }
-    // Up to 64 rows: one 16-row block per wave.  Up to 128: two.  Beyond: eight waves share the
-    // K/V tiles of a 256-row workgroup, which halves the reads of the cache per question row
-    // (config 3: 202 -> 187 us per layer, config 4: 418 -> 376 us; config 2, exactly 256 rows:
-    // 33.2 -> 32.3 us).
-    if (a.kv_fmt == MATKV_PAGE_E4M3) {
-        if (rg <= 64) return launch_v<G, 1, 64, true>(a, s);
-        if (rg <= 128) return launch_v<G, 2, 64, true>(a, s);
-        return launch_v<G, 2, 64, true, 8>(a, s);
-    }
-    if (rg <= 64) return launch_v<G, 1, 64, false>(a, s);
-    if (rg <= 128) return launch_v<G, 2, 64, false>(a, s);
-    return launch_v<G, 2, 64, false, 8>(a, s);
+template <bool F8>
+hipError_t launch_f(const AttnArgs& a, hipStream_t s) {
+    return a.tile_rows <= 128 ? launch_v<4, 32, F8>(a, s) : launch_v<8, 64, F8>(a, s);
 }
 
 }  // namespace
@@ -496,14 +611,7 @@ bool attn_prefill_supported(const AttnArgs& a, int dtype) {
 hipError_t launch_attn_prefill(const AttnArgs& a, int dtype, hipStream_t s) {
     if (a.n_units <= 0) return hipSuccess;
     if (!attn_prefill_supported(a, dtype)) return hipErrorInvalidValue;
-    switch (a.Hq / a.Hkv) {
-        case 1: return launch_g<1>(a, s);
-        case 2: return launch_g<2>(a, s);
-        case 3: return launch_g<3>(a, s);
-        case 4: return launch_g<4>(a, s);
-        case 8: return launch_g<8>(a, s);
-    }
-    return hipErrorInvalidValue;
+    return a.kv_fmt == MATKV_PAGE_E4M3 ? launch_f<true>(a, s) : launch_f<false>(a, s);
 }
 
 }  // namespace matkv

@@ -54,6 +54,7 @@ struct TableHost {
     int batch = 0, n_items = 0, n_dunits = 0, n_punits = 0, total_q = 0, max_q = 0;
     int max_punits_inst = 0;  // most prefill units of any one instance
     int max_punit_items = 0;  // most items of any one prefill unit
+    int prefill_tile_rows = 0;   // rows of a prefill workgroup's tile: 128 or 256
     int kv_fmt = 0;           // matkv_page_format of its pages
     int n_sunits = 0;         // units of the shared decode partition; 0 = the batch shares no page
     uint64_t sig_decode = 0, sig_prefill = 0;   // of what a recorded decode / prefill launch bakes in
@@ -245,33 +246,35 @@ int choose_decode_units(const matkv_config& c, int batch, long inst_tokens) {
 }
 
 // Units one instance's cache is cut into for the question prefill.  The matrix-core kernel runs
-// one workgroup per (unit, KV head, row tile); every extra unit costs a partial per question row
-// and a share of the fold launch.  Four-wave workgroups (128-row tiles, questions of up to 128
-// (row, head) rows): as many units as it takes to give every compute unit a workgroup (none
-// shorter than 256 tokens), and twice that - two resident workgroups per compute unit overlap
-// each other's matrix and vector phases - only while a unit keeps at least 4096 tokens to
-// amortise its partial over.  Eight-wave workgroups (256-row tiles): see below.
-// The other kernels launch a workgroup per question row and want few units.
+// one workgroup per (unit, KV head, row tile), one workgroup per compute unit (its LDS); every extra
+// unit costs a partial per question row and a share of the fold launch.  So: as many units as
+// leave every workgroup a compute unit of its own and no more - one workgroup too many and the launch
+// takes twice as long - none shorter than 256 tokens (128-row tiles, whose workgroups walk two blocks
+// of 32 tokens side by side: 128).  The other kernels launch a workgroup per question row and want few units.
 int choose_prefill_units(const matkv_config& cfg, long tiles_in_batch, long tile_rows, long tokens) {
     const int g = cfg.n_q_heads / cfg.n_kv_heads;
     const bool mfma = cfg.dtype == MATKV_BF16 && cfg.head_dim == 128 && group_size_built(g);
-    long pu;
-    if (mfma && tile_rows > 128) {
-        // eight-wave workgroups fill a compute unit alone: about 256 of them, and rather a few
-        // compute units idle than one more cut (config 3, 216 workgroups uncut: 187 us against
-        // 218 us in two units; config 4, 128 uncut: 376 us in two units against 414 us in four)
+    long pu = tokens / 1024;
+    if (mfma) {
         const long wgs_per_unit = std::max<long>(1, tiles_in_batch * cfg.n_kv_heads);
-        pu = (256 + wgs_per_unit / 2) / wgs_per_unit;
-        pu = std::max<long>(1, std::min<long>(pu, tokens / 256));
-    } else if (mfma) {
-        const long wgs_per_unit = std::max<long>(1, tiles_in_batch * cfg.n_kv_heads);
-        pu = (256 + wgs_per_unit - 1) / wgs_per_unit;
-        pu = std::max<long>(1, std::min<long>(pu, tokens / 256));
-        if (wgs_per_unit * pu < 512 && tokens / (2 * pu) >= 4096) pu *= 2;
-    } else {
-        pu = tokens / 1024;
+        pu = std::min<long>(256 / wgs_per_unit, tokens / (tile_rows > 128 ? 256 : 128));
     }
     return (int)std::max<long>(1, std::min<long>(pu, kMaxPrefillUnitsPerInstance));
+}
+
+// Rows of a prefill workgroup's tile.  A 256-row tile takes 1.8 us per 64 tokens, a 128-row tile 1.0 (it
+// feeds half as many matrix instructions with the same K and V, and walks two halves of its tokens side
+// by side), and an instance cut into units leaves its partials, which cost about 1.5 us of every
+// 128 rows.  The cheaper estimate wins; measured, 128 against 256 rows, us per layer at the 8B shape: one
+// 64-row question over 10 000 tokens 28.5 against 33.2, four of them 77.1 against 75.4, one of 100 rows over
+// 3000 tokens 24.5 against 28.4; 70B shape, one of 128 rows over 10 000 tokens 69.4 against 65.8.
+int choose_prefill_tile(const matkv_config& cfg, long tiles128, long tiles256, long most_tokens) {
+    auto cost = [&](long tiles, long rows) {
+        const long units = choose_prefill_units(cfg, tiles, rows, most_tokens);
+        const long rounds = (tiles * cfg.n_kv_heads * units + 255) / 256;
+        return (double)rounds * (((most_tokens + units - 1) / units + 63) / 64 * (rows > 128 ? 1.8 : 1.0) + (units > 1 ? 1.5 * rows / 128 : 0.0));
+    };
+    return cost(tiles128, 128) <= cost(tiles256, 256) ? 128 : 256;
 }
 
 // Cuts one instance's cache (its pages in order, then its tail) into n_units runs of nearly
@@ -1234,13 +1237,21 @@ matkv_status matkv_assemble(matkv_ctx* c, const matkv_page* pages, const int32_t
     int n_items = 0, n_dunits = 0, n_punits = 0, cu = 0, max_q = 0;
     TableHost th;
     th.min_tail_len = cfg.max_tail_tokens;
-    // row tiles of (question row, query head of one KV head) over the batch: the matrix-core prefill
-    // kernel takes 256-row workgroups once the longest question has more than 128 such rows
-    long prefill_tiles = 0, max_rg = 0;
-    for (int b = 0; b < batch; ++b) max_rg = std::max<long>(max_rg, (long)q_len[b] * (cfg.n_q_heads / cfg.n_kv_heads));
-    const long tile_rows = max_rg > 128 ? 256 : 128;
-    for (int b = 0; b < batch; ++b)
-        prefill_tiles += ((long)q_len[b] * (cfg.n_q_heads / cfg.n_kv_heads) + tile_rows - 1) / tile_rows;
+    // row tiles of (question row, query head of one KV head) over the batch
+    long prefill_tiles = 0, most_tokens = 0;
+    auto count_tiles = [&](long tile_rows) {
+        long n = 0;
+        for (int b = 0; b < batch; ++b) n += ((long)q_len[b] * (cfg.n_q_heads / cfg.n_kv_heads) + tile_rows - 1) / tile_rows;
+        return n;
+    };
+    for (int b = 0; b < batch; ++b) {
+        long t = q_len[b];
+        for (int p = 0; p < n_pages[b]; ++p) t += pages[(size_t)b * cfg.max_pages + p].n_tokens;
+        most_tokens = std::max(most_tokens, t);
+    }
+    th.prefill_tile_rows = choose_prefill_tile(cfg, count_tiles(128), count_tiles(256), most_tokens);
+    const long tile_rows = th.prefill_tile_rows;
+    prefill_tiles = count_tiles(tile_rows);
     for (int b = 0; b < batch; ++b) {
         InstanceInfo& in = insts[b];
         memset(&in, 0, sizeof(in));
@@ -1471,6 +1482,7 @@ static matkv_status attn_args(matkv_ctx* c, const char* name, int prefill, int32
     a.max_units_inst = prefill ? th->max_punits_inst : 0;
     a.batch = th->batch; a.total_q = th->total_q; a.kv_fmt = th->kv_fmt;
     a.max_unit_items = prefill ? th->max_punit_items : 0;
+    a.tile_rows = th->prefill_tile_rows;
     a.scale_log2e = c->scale_log2e;
     a.out_f32 = c->cfg.dtype == MATKV_BF16 && c->cfg.out_f32;
     a.off_inst = c->tl.off_inst; a.off_items = c->tl.off_items;
@@ -1578,6 +1590,11 @@ matkv_status matkv_chunk_attn(matkv_ctx* c, int32_t layer, const void* q, const 
     a.max_tail = n_tokens;
     a.prefill = 2; a.rows = n_tokens; a.n_units = 1; a.max_units_inst = 1;
     a.batch = 1; a.total_q = n_tokens; a.max_unit_items = 1;
+    // 256-row tiles once they give more workgroups than there are compute units, 128-row tiles (half the
+    // longest walk) until then: 8B shape, 1000 tokens (128 workgroups of 256 rows) 35 against 25 us, 70B, 1000
+    // (256) 38.7 against 36; 8B, 3501 tokens (440) 114 against 137
+    const long chunk_rows = (long)n_tokens * (cfg.n_q_heads / cfg.n_kv_heads);
+    a.tile_rows = (chunk_rows + 255) / 256 * cfg.n_kv_heads <= 256 ? 128 : 256;
     a.scale_log2e = c->scale_log2e;
     a.out_f32 = cfg.dtype == MATKV_BF16 && cfg.out_f32;
     const bool tiles = attn_prefill_supported(a, cfg.dtype);

@@ -389,6 +389,23 @@ def test_prefill_mixed_unit_counts_compressed_and_question_of_one_page(compresse
     _attention_parity(case)
 
 
+@pytest.mark.parametrize("compressed", [False, True])
+@pytest.mark.parametrize("name,Hq,Hkv,batch,q_len", [
+    ("rows128", 8, 2, 3, 40),        # 128-row tiles, two groups that take every second 32-token block
+    ("rows256", 32, 8, 10, 128),     # enough workgroups for 256-row tiles of 64-token blocks
+])
+def test_prefill_tile_forms_over_block_edges(name, Hq, Hkv, batch, q_len, compressed):
+    """Both tile forms of the row-parallel prefill kernel: pages one token short of, equal to and one
+    beyond a block, steps that cross several pages, a cache of a single token (a token group without any
+    block), and questions that leave a tile full, with one row, and with waves that have none."""
+    lens = {0: 31, 1: 32, 2: 33, 3: 63, 4: 64, 5: 65, 6: 1, 7: 5, 8: 129}
+    retrieved = [[0, 1, 2, 3, 4, 5, 6, 7, 8]] + [[8, 5, 7]] * (batch - 2) + [[6]]
+    q_lens = [q_len] * (batch - 2) + [q_len // 2 + 1, 1]
+    case = Case(f"prefill-{name}", n_layers=1, Hq=Hq, Hkv=Hkv, D=128, hidden=64, dtype="bf16", chunk_lens=lens, retrieved=retrieved,
+                q_lens=q_lens, steps=1, scale=0.5, compressed=compressed)
+    _attention_parity(case, instances=[0, batch - 2, batch - 1])
+
+
 def test_attention_no_pages_and_full_tail():
     """Degenerate caches: an instance that retrieved nothing (plain causal attention over its
     own tokens) and a tail filled to its capacity."""
