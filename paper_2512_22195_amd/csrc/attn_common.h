@@ -66,6 +66,7 @@ struct KernelArgs {
     int32_t cstride;             // ints between two arrival counters
     int32_t out_f32;             // bf16 path: outputs leave as float, unrounded
     float scale_log2e;
+    uint32_t g_mul;              // 2^29 / (Hq / Hkv), rounded up
 };
 
 __device__ __forceinline__ void store_out2(void* out, bool f32, size_t idx, float x, float y) {
@@ -96,6 +97,8 @@ inline KernelArgs make_kernel_args(const AttnArgs& a) {
     k.prefill = a.prefill; k.scale_log2e = a.scale_log2e;
     k.cstride = a.prefill ? 1 : kDecodeCounterStride;
     k.out_f32 = a.out_f32;
+    const uint32_t g = (uint32_t)(a.Hq / a.Hkv);
+    k.g_mul = ((1u << 29) + g - 1) / g;
     return k;
 }
 

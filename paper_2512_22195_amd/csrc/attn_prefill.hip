@@ -9,15 +9,15 @@
 //                   maximum through a register swap
 //   O^T += V^T P^T  A = V through the transposing LDS read, B = P rounded to bf16
 // 256-row tiles: all waves walk the same 64-token blocks.  128-row tiles: waves 0 to 3 and 4 to 7 own
-// the same rows and take every second 32-token block; their states are folded in LDS at the end.
+// the same rows and take every second block; their states are folded in LDS at the end.
 //
 // What bounds it.  A step of 64 tokens needs of a SIMD 2 x 32 matrix instructions and 2 x 8 small ones (2200 cycles), of its
 // vector ALU about as much, and of the compute unit's LDS 2 x 8 x 16 KB at 128 bytes a cycle (2050
 // cycles) - so a step takes as long as these fail to overlap, and at full overlap the chip's power
 // limit is near (the clock falls to 1.9 GHz; a large library GEMM reaches 1385 TFLOP/s here).  Hence:
 //  - K and V go from global memory straight into LDS (dma16), into unpadded rows whose 16-byte pieces
-//    are permuted so that operand reads and transposing reads meet no bank conflict; four blocks of a
-//    group are in LDS, two of them landed or in use.
+//    are permuted so that operand reads and transposing reads meet no bank conflict; up to two blocks
+//    are on their way while another is in use.
 //  - the two waves of a SIMD run half a step apart (see "the walk"): one multiplies, reads LDS and
 //    requests copies while the other computes its softmax.
 //  - 32x32x16 rather than 16x16x32: one row per lane halves the work per row, and the other wave's
@@ -26,9 +26,11 @@
 // The form this replaced (16x16x32, operands through registers, all waves in step, 64-token double
 // buffer) took 4900 cycles a step where this takes 3700.  Measured, us per layer with the fold, before
 // -> now: four 70B users of 20 000 tokens 361 -> 338 (990 TFLOP/s), sixteen 8B users of 5 000 175 -> 155, one
-// of 10 000 32 -> 28.6; chunks: 1000 tokens 8B 29 -> 25, 70B 43 -> 36, 3501 tokens 8B 132 -> 114, 4000
-// tokens 70B 295 -> 269.  Tried: every LDS read of the softmax phase spread between its exponentials,
-// copies between the matrix instructions, the vector phase at higher priority: within 2 %.
+// of 10 000 32 -> 28.8, of compressed pages 34 -> 30.5; chunks: 1000 tokens 8B 29 -> 24.3, 70B 43 -> 33, 3501
+// tokens 8B 132 -> 113, 4000 tokens 70B 295 -> 268.  Tried: every LDS read of the softmax phase spread
+// between its exponentials, copies between the matrix instructions, the vector phase at higher
+// priority: within 2 %; 128-row tiles over 32-token blocks, four of K and V each: 2.6 us per 128 tokens
+// against 2.2.
 //
 // An instance whose cache is one unit gets its output rows directly; otherwise every unit leaves an
 // unnormalised partial (accumulator, running maximum, sum) per row and a second, chip-wide
@@ -53,6 +55,7 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 constexpr int D = 128;
 constexpr int NW = 8;                 // waves of a workgroup
 constexpr int WR = 32;                // rows of a wave
+constexpr int TB = 64;                // tokens of a block
 constexpr int kPageT0 = -(1 << 30);   // "position" of a page block: every row sees all of it
 constexpr float kLazyLog2 = 8.0f;     // slack of the running reference exponent, in powers of two
 
@@ -61,7 +64,7 @@ __device__ __forceinline__ s16x4 lds_read_tr(const char* p) {
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lptr)(uintptr_t)p);
 }
 
-// One 64- or 32-token block as the multiplying side sees it (wave-uniform).
+// One block as the multiplying side sees it (wave-uniform).
 struct BlockDesc {
     int n;              // token rows (0: none left)
     int t0;             // tail row of the block's first token; kPageT0 for a page
@@ -69,15 +72,14 @@ struct BlockDesc {
     float sk, sv;       // scales of a compressed page's codes
 };
 
-template <int RW, int TB, bool F8>
+template <int RW, bool F8>
 __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
         KernelArgs a, const InstanceInfo* __restrict__ insts, const Item* __restrict__ items,
         const Unit* __restrict__ units) {
     constexpr int TS = NW / RW;                         // token groups
     constexpr int RT = RW * WR;                         // rows per workgroup
-    constexpr int NH = TB / 32;                         // 32-token parts of a block
     constexpr int TILE = TB * D * 2;                    // bytes of a K or a V tile
-    constexpr int NBUF = 128 * 1024 / (TS * 2 * TILE);  // blocks of a group that LDS holds
+    constexpr int GROUP = TS == 1 ? 8 * TILE : 5 * TILE;    // LDS of a token group (see "the walk")
     constexpr int NI = TB / (4 * RW);                   // copies of four rows per wave, of K and of V
     typedef uint16_t T;
 
@@ -87,13 +89,22 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     const int lane = tid & 63;
     const int c32 = lane & 31, g2 = lane >> 5;
     const int G = a.Hq / a.Hkv;                         // 1, 2, 3, 4 or 8
-    auto div_g = [&](int m) { return G == 3 ? (int)__umulhi((unsigned)m, 0x55555556u) : m >> (31 - __builtin_clz(G)); };
+    auto div_g = [&](int m) { return (int)__umulhi((unsigned)m << 3, a.g_mul); };     // m / G, m < 2^28
     // a chunk's own attention: tile t walks (t + 1) * RT / G keys, so the longest go first
     const int kvh = blockIdx.y, tile = a.prefill == 2 ? gridDim.z - 1 - blockIdx.z : blockIdx.z;
     const int m0 = tile * RT;
 
-    const Unit unit = table_record(units + blockIdx.x);
-    const InstanceInfo inst = table_record(insts + unit.inst);
+    Unit unit;
+    InstanceInfo inst;
+    if (a.prefill == 2) {                               // the chunk: one instance without pages, its tail the one item
+        unit = Unit{};
+        unit.n_items = 1; unit.n_units_inst = 1; unit.has_tail = 1; unit.first.ntok = a.rows;
+        inst = InstanceInfo{};
+        inst.q_len = a.rows;
+    } else {
+        unit = table_record(units + blockIdx.x);
+        inst = table_record(insts + unit.inst);
+    }
     const int n_m = inst.q_len * G;
     if (m0 >= n_m) return;                              // whole workgroup leaves together
     const int r_last = div_g(min(m0 + RT, n_m) - 1);
@@ -102,10 +113,12 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     const int vis_min = div_g(wm0) + 1;                    // tail rows every row of this wave may see
     const int vis_max = div_g(max(min(wm0 + WR, n_m) - 1, 0)) + 1;
 
-    // NBUF blocks of K and V per token group; the finished rows once those are dead
-    __shared__ __attribute__((aligned(1024))) char smem[TS * NBUF * 2 * TILE];
-    static_assert(NW * WR * D * 4 <= TS * NBUF * 2 * TILE, "finished rows fit over the dead tiles");
-    __shared__ float sm_m[NW * WR], sm_l[NW * WR];
+    // K and V tiles of the token groups; the finished rows and their (maximum, sum) once those are dead
+    __shared__ __attribute__((aligned(1024))) char smem[TS * GROUP + (TS == 1 ? 2 * NW * WR * 4 : 0)];
+    static_assert(NW * WR * (D + 2) * 4 <= sizeof(smem), "finished rows fit");
+    float* const sm_m = reinterpret_cast<float*>(smem + NW * WR * D * 4);
+    float* const sm_l = sm_m + NW * WR;
+
     // Every group walks the same blocks - the unit's items end to end (the tail clipped to the rows
     // this tile may see), TB token rows at a time, never across two items - and takes every TS-th.
     // All of it is wave-uniform.
@@ -139,9 +152,9 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     set_item(unit.first.base, unit.first.page_tokens, unit.first.tok0, unit.first.ntok);
     if (F8 && unit.first.base) page_scales(unit.first, a.layer, a.Hkv, kvh, sk, sv);
     fetch_item(1);
-    // where a block's rows lie: K and V of its first row, row stride 2 D bytes (codes: D bytes).
-    // Past the unit's end the last block comes back (or, for a group that never had one, the unit's
-    // first row), with n = 0 in its descriptor: still safe to copy, so that copies are unconditional.
+    // where a block's rows lie: K and V of its first row, row stride 2 D bytes (codes: D bytes).  Past the
+    // unit's end: one token group copies its last block again (a branch around the copies there cost 3 %),
+    // two groups (n = 0) copy nothing.
     struct Source { const char* k; const char* v; int n; bool codes; };
     Source src;
     src.k = wk.k; src.v = wk.v; src.n = 1; src.codes = F8 && !wk.tail;
@@ -156,6 +169,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
             return;
         }
         d.n = 0; d.t0 = kPageT0; d.go = 0; d.sk = 1.f; d.sv = 1.f;
+        if (TS == 2) { src.n = 0; src.codes = false; }
 #pragma unroll
         for (int g = 0; g < TS; ++g) {
             while (wk.left <= 0) {
@@ -181,17 +195,26 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
 
     // A tile's rows are 256 bytes, sixteen 16-byte pieces.  Piece p of K row r sits at place
     // p ^ (r & 15), of V row r at p ^ 4 (r & 3); rows past the block's end repeat its last one.
-    char* const group_lds = smem + tg * (NBUF * 2 * TILE);
-    const uint32_t lds0 = dev::lds_address(smem) + tg * (NBUF * 2 * TILE);
+    char* const group_lds = smem + tg * GROUP;
+    const uint32_t lds0 = dev::lds_address(smem) + tg * GROUP;
+    // Tiles of block i + d.  One group: four blocks of K and V.  Two groups: two tiles of K, three of V.
+    int i4 = 0, i3 = 0;                                 // i mod 4, i mod 3
+    auto k_at = [&](int d) { return TS == 1 ? ((i4 + d) & 3) * 2 * TILE : ((i4 + d) & 1) * TILE; };
+    auto v_at = [&](int d) {
+        if (TS == 1) return ((i4 + d) & 3) * 2 * TILE + TILE;
+        const int j = i3 + d;
+        return (2 + (j < 0 ? j + 3 : j >= 3 ? j - 3 : j)) * TILE;
+    };
     const int lrow = lane >> 4, place = lane & 15;
-    auto copy = [&](const Source& s, int buf) {
-        const uint32_t base = lds0 + buf * 2 * TILE + rw * 1024;
+    auto copy = [&](const Source& s, int d) {
+        if (TS == 2 && s.n <= 0) return;                // (wave-uniform)
+        const uint32_t kb = lds0 + k_at(d) + rw * 1024, vb = lds0 + v_at(d) + rw * 1024;
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             const int r = 4 * (rw + RW * i) + lrow;
             const uint32_t row = (uint32_t)min(r, s.n - 1) * (2 * D);
-            dev::dma16(s.k, row + 16 * (place ^ (r & 15)), base + i * RW * 1024);
-            dev::dma16(s.v, row + 16 * (place ^ (4 * (r & 3))), base + TILE + i * RW * 1024);
+            dev::dma16(s.k, row + 16 * (place ^ (r & 15)), kb + i * RW * 1024);
+            dev::dma16(s.v, row + 16 * (place ^ (4 * (r & 3))), vb + i * RW * 1024);
         }
     };
     // Compressed pages: codes go through registers (one step ahead of the copy they replace) and are
@@ -208,16 +231,18 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
             codes.v[i] = ldg16(s.v + off);
         }
     };
-    auto store_codes = [&](const Codes& codes, int buf) {
-        char* const kt = group_lds + buf * 2 * TILE;
+    auto store_codes = [&](const Codes& codes, int d) {
+        char* const kt = group_lds + k_at(d);
+        char* const vt = group_lds + v_at(d);
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
             const int r = (ct >> 3) + RW * 8 * i, p = 2 * (ct & 7);
-            char* const row = kt + r * (2 * D);
-            *reinterpret_cast<uint4*>(row + 16 * (p ^ (r & 15))) = e4m3x8_to_bf16x8(make_uint2(codes.k[i].x, codes.k[i].y));
-            *reinterpret_cast<uint4*>(row + 16 * ((p + 1) ^ (r & 15))) = e4m3x8_to_bf16x8(make_uint2(codes.k[i].z, codes.k[i].w));
-            *reinterpret_cast<uint4*>(row + TILE + 16 * (p ^ (4 * (r & 3)))) = e4m3x8_to_bf16x8(make_uint2(codes.v[i].x, codes.v[i].y));
-            *reinterpret_cast<uint4*>(row + TILE + 16 * ((p + 1) ^ (4 * (r & 3)))) = e4m3x8_to_bf16x8(make_uint2(codes.v[i].z, codes.v[i].w));
+            char* const krow = kt + r * (2 * D);
+            char* const vrow = vt + r * (2 * D);
+            *reinterpret_cast<uint4*>(krow + 16 * (p ^ (r & 15))) = e4m3x8_to_bf16x8(make_uint2(codes.k[i].x, codes.k[i].y));
+            *reinterpret_cast<uint4*>(krow + 16 * ((p + 1) ^ (r & 15))) = e4m3x8_to_bf16x8(make_uint2(codes.k[i].z, codes.k[i].w));
+            *reinterpret_cast<uint4*>(vrow + 16 * (p ^ (4 * (r & 3)))) = e4m3x8_to_bf16x8(make_uint2(codes.v[i].x, codes.v[i].y));
+            *reinterpret_cast<uint4*>(vrow + 16 * ((p + 1) ^ (4 * (r & 3)))) = e4m3x8_to_bf16x8(make_uint2(codes.v[i].z, codes.v[i].w));
         }
     };
 
@@ -236,17 +261,17 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
 
     const int koff = c32 * 256 + 16 * (g2 ^ (c32 & 15));
     const int e16 = lane & 15;
-    const int voff = TILE + (4 * g2 + (e16 >> 2)) * 256 + 64 * (e16 >> 2) + 32 * ((lane >> 4) & 1) + 8 * (e16 & 3);
+    const int voff = (4 * g2 + (e16 >> 2)) * 256 + 64 * (e16 >> 2) + 32 * ((lane >> 4) & 1) + 8 * (e16 & 3);
     // (the addresses of a step are formed from one register each time: kept over the loop they would
     // cost the twelve registers that there are not)
-    auto read_k = [&](bf16x8 (&f)[8], int buf, int h) {
-        int o = koff + (tg * NBUF + buf) * 2 * TILE;
+    auto read_k = [&](bf16x8 (&f)[8], int h) {                          // of block i
+        int o = koff + tg * GROUP + k_at(0);
         asm volatile("" : "+v"(o));
 #pragma unroll
         for (int c = 0; c < 8; ++c) f[c] = *reinterpret_cast<const bf16x8*>(smem + (o ^ (32 * c)) + h * 8192);
     };
-    auto read_v = [&](bf16x8 (&f)[2][4], int buf, int h, int t) {       // dims 32 t ..
-        int o = voff + (tg * NBUF + buf) * 2 * TILE;
+    auto read_v = [&](bf16x8 (&f)[2][4], int d, int h, int t) {         // of block i + d, dims 32 t ..
+        int o = voff + tg * GROUP + v_at(d);
         asm volatile("" : "+v"(o));
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
@@ -257,39 +282,46 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     };
 
     // ---- the walk ----
-    // A step of a wave has a matrix phase X(i) - P V of block i - 1, then the scores of block i, all
-    // LDS reads and the copy of block i + 2 - and a vector phase Y(i) - softmax of block i - with a
-    // barrier behind each.  Waves 4 to 7, which share their SIMDs with waves 0 to 3, run one phase
-    // behind: while one wave of a SIMD multiplies, the other is in its vector phase.  Block i is read
-    // in X(i), Y(i) and X(i + 1) and, by the late waves, one phase on; X(i + 2), which copies block
-    // i + 4 over it, comes behind the barrier that ends the late waves' X(i + 1).  X(i) ends when
-    // block i + 1 has landed: the early waves read it from X(i + 1) on, one barrier after the late
-    // waves have passed that wait.
-    static_assert(NBUF == 4, "in use: two blocks; landed or in flight: two");
+    // A step of a wave has a matrix phase X(i) - P V of block i - 1, then the scores of block i, and all
+    // LDS reads - and a vector phase Y(i) - softmax of block i - with a barrier behind each.  Waves 4 to
+    // 7, which share their SIMDs with waves 0 to 3, run one phase behind: while one wave of a SIMD
+    // multiplies, the other is in its vector phase.
+    // One token group (256 rows): K of block i is read in X(i), V in Y(i) and X(i + 1), by the late waves
+    // one phase on.  X(i) copies block i + 2 over block i - 2, behind the barrier that ends the late
+    // waves' X(i - 1), and ends when block i + 1 has landed: the early waves read it from X(i + 1) on,
+    // one barrier after the late waves have passed that wait.
+    // Two groups (128 rows): the late waves are the second group, with tiles of its own, so nothing is
+    // read in another phase than its owner's.  K of block i is dead behind X(i), V behind X(i + 1): two
+    // tiles of K and three of V do (all of LDS), Y(i) copies block i + 2 and ends when block i + 1 has landed.
     const bool late = wave >= NW / 2;
+    // every copy but the youngest block's has landed (ahead: that block's rows, 0 = it was not copied)
+    auto landed = [&](int ahead) { if (TS == 1 || ahead > 0) dev::dma_wait<2 * NI>(); else dev::dma_wait<0>(); };
     BlockDesc q[3];                   // descriptors of blocks i, i + 1, i + 2
     Source next_src;                  // where block i + 2 lies
     next_step(q[0]);
     Codes first;
     const bool codes0 = src.codes;
     if (F8 && codes0) load_codes(first, src); else copy(src, 0);
-    // Q comes through LDS as well - over the tiles of blocks 2 and 3, which nothing else needs yet - so
+    // Q comes through LDS as well - over tiles that nothing else needs yet - so
     // that whole rows are fetched and the first two blocks can be on their way at the same time; padding
     // rows repeat the last real row.  Placed like K rows, and read like them: B operand, lane's row c32.
-    char* const q_lds = smem + (RW == NW ? 2 * 2 * TILE : TS * NBUF * 2 * TILE - RT * 2 * D);
-    static_assert(RT * 2 * D <= 2 * 2 * TILE, "Q fits over two blocks of a group");
+    // (Two groups: rows 0 to 63 in the third V tile of the first, the rest in that of the second.)
+    const auto q_row = [&](int row) { return TS == 1 ? 4 * TILE + row * (2 * D) : (row >> 6) * GROUP + 4 * TILE + (row & 63) * (2 * D); };
+    static_assert(RT * 2 * D <= (TS == 1 ? 4 : TS) * TILE, "Q fits");
     {
         const T* qb = reinterpret_cast<const T*>(a.q) + ((size_t)inst.cu_q * a.Hq + (size_t)kvh * G) * D;
-        const uint32_t q0 = dev::lds_address(q_lds) + wave * 1024;
+        const uint32_t q0 = dev::lds_address(smem);
 #pragma unroll
         for (int i = 0; i < RT / (4 * NW); ++i) {
             const int row = 4 * (wave + NW * i) + lrow, m = min(m0 + row, n_m - 1);
+            if (m0 + (4 * (wave + NW * i) & ~(WR - 1)) >= n_m) continue;        // rows of a wave that has none
             const int r = div_g(m), g = m - r * G;
-            dev::dma16(qb, (uint32_t)((r * a.Hq + g) * (2 * D)) + 16 * (place ^ (row & 15)), q0 + i * NW * 1024);
+            dev::dma16(qb, (uint32_t)((r * a.Hq + g) * (2 * D)) + 16 * (place ^ (row & 15)), q0 + q_row(4 * (wave + NW * i)));
         }
     }
     next_step(q[1]);
     const bool codes1 = src.codes;
+    const int n1 = src.n;
     if (F8 && codes1) load_codes(codes, src); else copy(src, 1);
     next_step(q[2]);
     next_src = src;
@@ -299,15 +331,15 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
         dev::dma_wait<0>();
         if (src.codes) load_codes(codes, src);
     } else {
-        dev::dma_wait<2 * NI>();                // Q and block 0 are there
+        landed(n1);                       // Q and block 0 are there
     }
     lds_barrier();
     bf16x8 bq[8];                     // dims 16 c + 8 g2 ..
     const int vis = div_g(min(wm0 + c32, n_m - 1)) + 1;    // tail rows this lane's row may see
 #pragma unroll
-    for (int c = 0; c < 8; ++c) bq[c] = *reinterpret_cast<const bf16x8*>(q_lds + rw * (WR * 2 * D) + (koff ^ (32 * c)));
+    for (int c = 0; c < 8; ++c) bq[c] = *reinterpret_cast<const bf16x8*>(smem + q_row(WR * rw) + (koff ^ (32 * c)));
     lds_barrier();                              // X(0) copies over it
-    bf16x8 av[NH][2][4], pb[NH][2];   // V operands (the first 32 tokens' read ahead in Y), weights
+    bf16x8 av[2][2][4], pb[2][2];   // V operands (the first 32 tokens' read ahead in Y), weights
     auto barrier_plain = [&]() {      // every LDS read before it is consumed before the next one
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("" ::: "memory");
@@ -335,7 +367,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
             }
         }
     };
-    f32x16 st[NH];                    // S^T: tokens 32 h + 8 (i / 4) + 4 g2 + i % 4
+    f32x16 st[2];                    // S^T: tokens 32 h + 8 (i / 4) + 4 g2 + i % 4
     auto multiply_qk = [&](const bf16x8 (&ak)[8], int h) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) st[h][i] = 0.f;
@@ -351,7 +383,6 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
         __builtin_amdgcn_sched_barrier(0);
     };
     if (late) barrier_plain();
-    int buf = 0;
     bool prev_live = false;
     bool copied = false;              // compressed pages: a block of the tail is on its way
     while (q[0].go) {
@@ -359,38 +390,33 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
         const bool live = wave_live && d.n > 0 && d.t0 < vis_max;
         // X (its wave goes first: a matrix instruction needs the issue port once in 32 cycles)
         __builtin_amdgcn_s_setprio(1);
-        bf16x8 ak[NH][8];
+        bf16x8 ak[2][8];
         if (prev_live) {
-            if constexpr (NH == 2) {
 #pragma unroll
-                for (int t = 0; t < 4; ++t) read_v(av[1], (buf + 3) & 3, 1, t);
-                multiply_pv(0);
-                spread(std::integral_constant<int, 2>{});
-            }
-            read_k(ak[0], buf, 0);
-            multiply_pv(NH - 1);
+            for (int t = 0; t < 4; ++t) read_v(av[1], -1, 1, t);
+            multiply_pv(0);
+            spread(std::integral_constant<int, 2>{});
+            read_k(ak[0], 0);
+            multiply_pv(1);
             spread(std::integral_constant<int, 1>{});
         } else if (live) {
-            read_k(ak[0], buf, 0);
+            read_k(ak[0], 0);
         }
-        if (!F8) copy(next_src, (buf + 2) & 3);
+        if (!F8 && TS == 1) copy(next_src, 2);
         if (live) {
-            if constexpr (NH == 2) {
-                read_k(ak[1], buf, 1);
-                multiply_qk(ak[0], 0);
-                spread(std::integral_constant<int, 1>{});
-            }
-            multiply_qk(ak[NH - 1], NH - 1);
+            read_k(ak[1], 1);
+            multiply_qk(ak[0], 0);
+            spread(std::integral_constant<int, 1>{});
+            multiply_qk(ak[1], 1);
         }
-        if (!F8) dev::dma_wait<2 * NI>();
-        else if (copied) { dev::dma_wait<0>(); copied = false; }
+        if (!F8 && TS == 1) landed(next_src.n);
+        if (F8 && copied) { dev::dma_wait<0>(); copied = false; }
         barrier_plain();
         // Y
         __builtin_amdgcn_s_setprio(0);
-        if (F8) {
-            if (next_src.codes) { store_codes(codes, (buf + 2) & 3); }
-            else { copy(next_src, (buf + 2) & 3); copied = true; }
-        }
+        if (F8 && next_src.codes) store_codes(codes, 2);
+        else if (F8 || TS == 2) { copy(next_src, 2); copied = F8; }
+        const int ahead_n = next_src.n;
         q[0] = q[1]; q[1] = q[2];
         next_step(q[2]);
         next_src = src;
@@ -401,13 +427,13 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
             if (d.n != TB || d.t0 + d.n > vis_min) {        // wave-uniform
                 const int limit = min(d.n, vis - d.t0) - 4 * g2;
 #pragma unroll
-                for (int h = 0; h < NH; ++h)
+                for (int h = 0; h < 2; ++h)
 #pragma unroll
                     for (int i = 0; i < 16; ++i) st[h][i] = 32 * h + 8 * (i / 4) + i % 4 < limit ? st[h][i] : kNegBig;
             }
             float mx = st[0][0];
 #pragma unroll
-            for (int h = 0; h < NH; ++h)
+            for (int h = 0; h < 2; ++h)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) mx = fmaxf(mx, st[h][i]);
             mx = fmaxf(mx, lane_xor(mx, 32, lane));
@@ -433,40 +459,41 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
                     for (int i = 0; i < 16; ++i) ot[t][i] *= alpha;
             }
             if (F8) ones_v = 1.0f / d.sv;
-            // (the V operand of the first 32 tokens is read for X(i + 1) on the way, a few reads per group
-            // of exponentials: issued together they would hold up the wave)
 #pragma unroll
-            for (int h = 0; h < NH; ++h)
+            for (int h = 0; h < 2; ++h)
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
 #pragma unroll
                     for (int i = 0; i < 8; ++i) pb[h][u][i] = (__bf16)fast_exp2(fmaf(st[h][8 * u + i], scb, nmc));
                 }
+            // the V operand of the first 32 tokens, for X(i + 1)
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int t = 0; t < 4; ++t) read_v(av[0], buf, 0, t);
+            for (int t = 0; t < 4; ++t) read_v(av[0], 0, 0, t);
         } else {
             // not used again: without this the old values would take registers through the whole step
 #pragma unroll
-            for (int i = 0; i < NH * 2; ++i) {
+            for (int i = 0; i < 4; ++i) {
                 asm volatile("" : "=v"(pb[i / 2][i % 2]));
 #pragma unroll
                 for (int t = 0; t < 4; ++t) asm volatile("" : "=v"(av[i / 2][i % 2][t]));
             }
         }
         prev_live = live;
-        buf = (buf + 1) & 3;
+        i4 = (i4 + 1) & 3;
+        i3 = i3 == 2 ? 0 : i3 + 1;
+        if (!F8 && TS == 2) landed(ahead_n);
         if (F8) lds_barrier();      // (the widened codes are written)
         else barrier_plain();
     }
     if (!late) barrier_plain();
     if (prev_live) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) if constexpr (NH == 2) read_v(av[1], (buf + 3) & 3, 1, t);
+        for (int t = 0; t < 4; ++t) read_v(av[1], -1, 1, t);
 #pragma unroll
-        for (int h = 0; h < NH; ++h) multiply_pv(h);
+        for (int h = 0; h < 2; ++h) multiply_pv(h);
     }
-    dev::dma_wait<0>();                                  // (copies past the end)
+    if (TS == 1) dev::dma_wait<0>();                     // (copies past the end)
     __syncthreads();
 
     // ---- finished rows leave through LDS as whole rows; token groups are folded on the way ----
@@ -485,30 +512,41 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     __syncthreads();
     const bool single = unit.n_units_inst == 1;
     const int rows_here = min(RT, n_m - m0);
-    for (int row = tid >> 5; row < rows_here; row += NW * 2) {
-        const int w0 = row / WR, rr = row % WR;
-        float M = sm_m[row];
+    // half a wave takes a row; two rows at a time, so that their reads overlap
+    constexpr int RB = 2;
+    for (int row0 = tid >> 5; row0 < rows_here; row0 += NW * 2 * RB) {
+        float M[RB], L[RB];
+        float4 acc[RB];
 #pragma unroll
-        for (int g = 1; g < TS; ++g) M = fmaxf(M, sm_m[g * RT + row]);
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        float L = 0.f;
-#pragma unroll
-        for (int g = 0; g < TS; ++g) {
-            const float4 v = *reinterpret_cast<const float4*>(smem + ((g * RW + w0) * WR + rr) * (D * 4) + 16 * (c32 ^ rr));
-            const float w = TS == 1 ? 1.f : fast_exp2(sm_m[g * RT + row] - M);
-            L = fmaf(w, sm_l[g * RT + row], L);
-            acc.x = fmaf(w, v.x, acc.x); acc.y = fmaf(w, v.y, acc.y);
-            acc.z = fmaf(w, v.z, acc.z); acc.w = fmaf(w, v.w, acc.w);
+        for (int j = 0; j < RB; ++j) {
+            const int row = min(row0 + NW * 2 * j, rows_here - 1), w0 = row / WR, rr = row % WR;
+            M[j] = sm_m[row];
+            L[j] = sm_l[row];
+            acc[j] = *reinterpret_cast<const float4*>(smem + row * (D * 4) + 16 * (c32 ^ rr));
+            if (TS == 2) {
+                const float m1 = sm_m[RT + row], l1 = sm_l[RT + row];
+                const float4 v = *reinterpret_cast<const float4*>(smem + ((RW + w0) * WR + rr) * (D * 4) + 16 * (c32 ^ rr));
+                const float mm = fmaxf(M[j], m1), f0 = fast_exp2(M[j] - mm), f1 = fast_exp2(m1 - mm);
+                M[j] = mm;
+                L[j] = fmaf(f1, l1, L[j] * f0);
+                acc[j].x = fmaf(f1, v.x, acc[j].x * f0); acc[j].y = fmaf(f1, v.y, acc[j].y * f0);
+                acc[j].z = fmaf(f1, v.z, acc[j].z * f0); acc[j].w = fmaf(f1, v.w, acc[j].w * f0);
+            }
         }
-        const int m = m0 + row, r = div_g(m), head = kvh * G + m - r * G;
-        if (single) {
-            const float inv = 1.0f / L;
-            store_out4(a.out, a.out_f32, ((size_t)(inst.cu_q + r) * a.Hq + head) * D + 4 * c32,
-                       make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv));
-        } else {
-            float* prow = a.partials + (((size_t)blockIdx.x * a.rows + r) * a.Hq + head) * kPartialStride(D);
-            *reinterpret_cast<float4*>(prow + 4 * c32) = acc;
-            if (c32 == 0) *reinterpret_cast<float2*>(prow + D) = make_float2(M, L);
+#pragma unroll
+        for (int j = 0; j < RB; ++j) {
+            const int row = row0 + NW * 2 * j;
+            if (row >= rows_here) break;
+            const int m = m0 + row, r = div_g(m), head = kvh * G + m - r * G;
+            if (single) {
+                const float inv = 1.0f / L[j];
+                store_out4(a.out, a.out_f32, ((size_t)(inst.cu_q + r) * a.Hq + head) * D + 4 * c32,
+                           make_float4(acc[j].x * inv, acc[j].y * inv, acc[j].z * inv, acc[j].w * inv));
+            } else {
+                float* prow = a.partials + (((size_t)blockIdx.x * a.rows + r) * a.Hq + head) * kPartialStride(D);
+                *reinterpret_cast<float4*>(prow + 4 * c32) = acc[j];
+                if (c32 == 0) *reinterpret_cast<float2*>(prow + D) = make_float2(M[j], L[j]);
+            }
         }
     }
 }
@@ -574,12 +612,12 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(
     store_out4(a.out, a.out_f32, oidx, make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv));
 }
 
-template <int RW, int TB, bool F8>
+template <int RW, bool F8>
 hipError_t launch_v(const AttnArgs& a, hipStream_t s) {
     const KernelArgs k = make_kernel_args(a);
     const int tiles = (a.rows * (a.Hq / a.Hkv) + RW * WR - 1) / (RW * WR);
     dim3 grid(a.n_units, a.Hkv, tiles), block(NW * 64);
-    hipLaunchKernelGGL((attn_prefill_kernel<RW, TB, F8>), grid, block, 0, s, k,
+    hipLaunchKernelGGL((attn_prefill_kernel<RW, F8>), grid, block, 0, s, k,
                        reinterpret_cast<const InstanceInfo*>(a.table + a.off_inst),
                        reinterpret_cast<const Item*>(a.table + a.off_items),
                        reinterpret_cast<const Unit*>(a.table + a.off_units));
@@ -597,7 +635,7 @@ hipError_t launch_v(const AttnArgs& a, hipStream_t s) {
 
 template <bool F8>
 hipError_t launch_f(const AttnArgs& a, hipStream_t s) {
-    return a.tile_rows <= 128 ? launch_v<4, 32, F8>(a, s) : launch_v<8, 64, F8>(a, s);
+    return a.tile_rows <= 128 ? launch_v<4, F8>(a, s) : launch_v<8, F8>(a, s);
 }
 
 }  // namespace

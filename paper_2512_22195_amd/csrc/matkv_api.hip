@@ -249,8 +249,8 @@ int choose_decode_units(const matkv_config& c, int batch, long inst_tokens) {
 // one workgroup per (unit, KV head, row tile), one workgroup per compute unit (its LDS); every extra
 // unit costs a partial per question row and a share of the fold launch.  So: as many units as
 // leave every workgroup a compute unit of its own and no more - one workgroup too many and the launch
-// takes twice as long - none shorter than 256 tokens (128-row tiles, whose workgroups walk two blocks
-// of 32 tokens side by side: 128).  The other kernels launch a workgroup per question row and want few units.
+// takes twice as long - none shorter than 256 tokens (128-row tiles, whose workgroups take a
+// step of 128 tokens: 128).  The other kernels launch a workgroup per question row and want few units.
 int choose_prefill_units(const matkv_config& cfg, long tiles_in_batch, long tile_rows, long tokens) {
     const int g = cfg.n_q_heads / cfg.n_kv_heads;
     const bool mfma = cfg.dtype == MATKV_BF16 && cfg.head_dim == 128 && group_size_built(g);
@@ -262,17 +262,18 @@ int choose_prefill_units(const matkv_config& cfg, long tiles_in_batch, long tile
     return (int)std::max<long>(1, std::min<long>(pu, kMaxPrefillUnitsPerInstance));
 }
 
-// Rows of a prefill workgroup's tile.  A 256-row tile takes 1.8 us per 64 tokens, a 128-row tile 1.0 (it
-// feeds half as many matrix instructions with the same K and V, and walks two halves of its tokens side
-// by side), and an instance cut into units leaves its partials, which cost about 1.5 us of every
-// 128 rows.  The cheaper estimate wins; measured, 128 against 256 rows, us per layer at the 8B shape: one
-// 64-row question over 10 000 tokens 28.5 against 33.2, four of them 77.1 against 75.4, one of 100 rows over
-// 3000 tokens 24.5 against 28.4; 70B shape, one of 128 rows over 10 000 tokens 69.4 against 65.8.
+// Rows of a prefill workgroup's tile.  A step takes about 1.9 us for 64 tokens of a 256-row tile, 2.2 for 128
+// of a 128-row tile (two groups of waves with 64 each), and an instance cut into units leaves its
+// partials, which cost about 3 us of every 128 rows.  The cheaper estimate wins; measured, 128 against 256
+// rows, us per layer at the 8B shape: one 64-row question over 10 000 tokens 28.9 against 33.2, two of them 46.8
+// against 49.3, four 76.5 against 73, one of 100 rows over 3000 tokens 23.3 against 28.4; 70B shape, one of
+// 128 rows over 10 000 tokens 68 against 66, four over 20 000 374 against 345.
 int choose_prefill_tile(const matkv_config& cfg, long tiles128, long tiles256, long most_tokens) {
     auto cost = [&](long tiles, long rows) {
-        const long units = choose_prefill_units(cfg, tiles, rows, most_tokens);
+        const long units = choose_prefill_units(cfg, tiles, rows, most_tokens), step = rows > 128 ? 64 : 128;
         const long rounds = (tiles * cfg.n_kv_heads * units + 255) / 256;
-        return (double)rounds * (((most_tokens + units - 1) / units + 63) / 64 * (rows > 128 ? 1.8 : 1.0) + (units > 1 ? 1.5 * rows / 128 : 0.0));
+        const double steps = (double)(((most_tokens + units - 1) / units + step - 1) / step);
+        return (double)rounds * (steps * (rows > 128 ? 1.9 : 2.2) + (units > 1 ? 3.0 * rows / 128 : 0.0));
     };
     return cost(tiles128, 128) <= cost(tiles256, 256) ? 128 : 256;
 }
@@ -1591,8 +1592,8 @@ matkv_status matkv_chunk_attn(matkv_ctx* c, int32_t layer, const void* q, const 
     a.prefill = 2; a.rows = n_tokens; a.n_units = 1; a.max_units_inst = 1;
     a.batch = 1; a.total_q = n_tokens; a.max_unit_items = 1;
     // 256-row tiles once they give more workgroups than there are compute units, 128-row tiles (half the
-    // longest walk) until then: 8B shape, 1000 tokens (128 workgroups of 256 rows) 35 against 25 us, 70B, 1000
-    // (256) 38.7 against 36; 8B, 3501 tokens (440) 114 against 137
+    // longest walk) until then: 8B shape, 1000 tokens (128 workgroups of 256 rows) 35 against 24 us, 70B, 1000
+    // (256) 38.7 against 33; 8B, 3501 tokens (440) 113 against 137
     const long chunk_rows = (long)n_tokens * (cfg.n_q_heads / cfg.n_kv_heads);
     a.tile_rows = (chunk_rows + 255) / 256 * cfg.n_kv_heads <= 256 ? 128 : 256;
     a.scale_log2e = c->scale_log2e;
@@ -1606,10 +1607,11 @@ matkv_status matkv_chunk_attn(matkv_ctx* c, int32_t layer, const void* q, const 
             return fail(c, MATKV_ENOMEM, "chunk_attn: the workspace of this configuration holds the partial results of %zu rows, the chunk has %d",
                         std::min(c->wl.partial_floats / ((size_t)cfg.n_q_heads * (cfg.head_dim + 4)), c->wl.n_counters / cfg.n_kv_heads), n_tokens);
     }
-    // the one-instance table depends on the chunk's length alone: written again only when that
+    // (the tile kernel knows the one instance from its arguments.)  The one-instance table of the other
+    // kernel depends on the chunk's length alone: written again only when that
     // changes (a launch of its own costs 4-5 us per layer), always inside a capture (a replay
     // must not depend on what ran before it), and after any replay
-    if (c->capturing || c->chunk_table_tokens != n_tokens) {
+    if (!tiles && (c->capturing || c->chunk_table_tokens != n_tokens)) {
         HIP_TRY(c, launch_chunk_table(c->workspace + c->wl.off_chunk, n_tokens, c->compute));
         c->chunk_table_tokens = c->capturing ? -1 : n_tokens;
     }

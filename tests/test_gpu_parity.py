@@ -391,7 +391,7 @@ def test_prefill_mixed_unit_counts_compressed_and_question_of_one_page(compresse
 
 @pytest.mark.parametrize("compressed", [False, True])
 @pytest.mark.parametrize("name,Hq,Hkv,batch,q_len", [
-    ("rows128", 8, 2, 3, 40),        # 128-row tiles, two groups that take every second 32-token block
+    ("rows128", 8, 2, 3, 40),        # 128-row tiles, two groups that take every second block
     ("rows256", 32, 8, 10, 128),     # enough workgroups for 256-row tiles of 64-token blocks
 ])
 def test_prefill_tile_forms_over_block_edges(name, Hq, Hkv, batch, q_len, compressed):
