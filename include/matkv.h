@@ -338,7 +338,7 @@ matkv_status matkv_decode_step(matkv_ctx* ctx, int32_t layer, const void* hidden
  * src 16-byte aligned, bytes a multiple of 16. */
 matkv_status matkv_probe_read(matkv_ctx* ctx, const void* src, size_t bytes);
 
-/* ---- command capture: replay a fixed sequence of the calls above without host cost ------ */
+/* ---- command capture: replay a fixed sequence of the calls above at little host cost ---- */
 
 /* Between begin and end, calls to materialize_tail / advance / prefill_attn / decode_attn /
  * decode_step are recorded from the compute stream instead of executed.  Captured work reads tail

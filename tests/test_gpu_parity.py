@@ -452,6 +452,59 @@ def test_graph_replay_matches_eager():
     chain.compare_attention(case, g_pre, g_dec, pre, dec)
 
 
+@pytest.mark.parametrize("repeats,copy", [(1, False), (31, False), (32, False), (2, True)])
+def test_graph_replay_of_short_and_long_recordings(repeats, copy):
+    """Replays of a recording of one kernel more than an even number (3, 63: issued as kernels; 65: as a
+    graph) and of one that also holds a copy (a graph): each equals the eager calls, with eager work and
+    syncs in between."""
+    case = Case("graph-len", n_layers=1, Hq=8, Hkv=2, D=128, hidden=4096, dtype="bf16",
+                chunk_lens={0: 200}, retrieved=[[0]], q_lens=[3], steps=8)
+    ctx = chain.make_context(case)
+    try:
+        with torch.cuda.stream(ctx.compute_stream):
+            gen = torch.Generator(device="cuda").manual_seed(5)
+
+            def normal(*shape):
+                return torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+
+            slot, table = normal(2 * 2 * 200 * 128).view(torch.uint8), ctx.new_table()
+            start = torch.zeros_like(ctx.new_tail())
+            start[..., :3, :] = normal(*start[..., :3, :].shape)
+            x, w, q = normal(repeats, 1, 4096), normal(2, 256, 4096) / 64, normal(repeats, 1, 8, 128)
+
+            def step(tail, out, last):
+                ctx.advance(table, 1)
+                for i in range(repeats):
+                    ctx.materialize_tail(x[i], w[0], w[1], table, 1, tail[0, 0], tail[0, 1])
+                    ctx.decode_attn(0, q[i], table, tail[0, 0], tail[0, 1], out[i])
+                if copy:
+                    last.copy_(out[-1])
+
+            runs = []
+            for recorded in (False, True):
+                tail, out, seen = start.clone(), torch.zeros_like(q), []
+                last = torch.zeros_like(q[-1])
+                ctx.assemble([[(slot, 200)]], [3], table)
+                if recorded:
+                    ctx.graph_begin()
+                    step(tail, out, last)
+                    g = ctx.graph_end()
+                for _ in range(4):
+                    if recorded:
+                        ctx.graph_launch(g)
+                    else:
+                        step(tail, out, last)
+                    ctx.compute_stream.synchronize()
+                    seen += [out.clone(), last.clone()]
+                    out.zero_()
+                runs.append(seen + [tail])
+            for i, (a, b) in enumerate(zip(*runs)):
+                assert torch.equal(a, b), f"result {i}"
+            assert runs[0][0].any()
+    finally:
+        ctx.close()
+
+
 # ------------------------------------------------------------------ full-size, sampled ------
 def test_config2_full_size_sampled():
     """Llama-3-8B layer shape, 10 chunks x 1000 tokens, all 32 layers resident, the launch
