@@ -309,14 +309,15 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     const auto q_row = [&](int row) { return TS == 1 ? 4 * TILE + row * (2 * D) : (row >> 6) * GROUP + 4 * TILE + (row & 63) * (2 * D); };
     static_assert(RT * 2 * D <= (TS == 1 ? 4 : TS) * TILE, "Q fits");
     {
-        const T* qb = reinterpret_cast<const T*>(a.q) + ((size_t)inst.cu_q * a.Hq + (size_t)kvh * G) * D;
+        const int r0 = div_g(m0);               // (offsets from the tile's first row: they are 32 bits)
+        const T* qb = reinterpret_cast<const T*>(a.q) + ((size_t)(inst.cu_q + r0) * a.Hq + (size_t)kvh * G) * D;
         const uint32_t q0 = dev::lds_address(smem);
 #pragma unroll
         for (int i = 0; i < RT / (4 * NW); ++i) {
             const int row = 4 * (wave + NW * i) + lrow, m = min(m0 + row, n_m - 1);
             if (m0 + (4 * (wave + NW * i) & ~(WR - 1)) >= n_m) continue;        // rows of a wave that has none
             const int r = div_g(m), g = m - r * G;
-            dev::dma16(qb, (uint32_t)((r * a.Hq + g) * (2 * D)) + 16 * (place ^ (row & 15)), q0 + q_row(4 * (wave + NW * i)));
+            dev::dma16(qb, (uint32_t)(((r - r0) * a.Hq + g) * (2 * D)) + 16 * (place ^ (row & 15)), q0 + q_row(4 * (wave + NW * i)));
         }
     }
     next_step(q[1]);

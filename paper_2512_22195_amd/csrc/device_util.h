@@ -44,11 +44,6 @@ __device__ __forceinline__ void dma16(const void* sbase, uint32_t voff, uint32_t
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :: "s"(lds), "v"(voff), "s"(sbase) : "memory", "m0");
 }
-// The same with 4 bytes per lane (LDS bytes lds + 4 * lane).
-__device__ __forceinline__ void dma4(const void* sbase, uint32_t voff, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
-                 :: "s"(lds), "v"(voff), "s"(sbase) : "memory", "m0");
-}
 template <int N>
 __device__ __forceinline__ void dma_wait() {
     static_assert(N >= 0 && N <= 63, "vmcnt has six bits");
