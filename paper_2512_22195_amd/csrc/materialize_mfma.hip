@@ -38,20 +38,29 @@ __device__ __forceinline__ RowDest resolve_row(const MaterializeArgs& a, int r) 
     }
     const InstanceInfo* insts = reinterpret_cast<const InstanceInfo*>(a.table + a.off_inst);
     int b = -1, j = 0;
+    int64_t base = 0;
     if (a.rows_per_instance > 0) {
         if (r < a.batch * a.rows_per_instance) {
             b = r / a.rows_per_instance;
             j = insts[b].tail_len - a.rows_per_instance + (r % a.rows_per_instance);
+            base = insts[b].pos_base;
         }
     } else {
+        // every lane walks all instances through the constant address space (no kernel of the launch
+        // writes the table): scalar loads, several of them in flight, which do not wait for copies on their way
+        // (as a walk of dependent loads ahead of the first copy it cost 1.3 us of a launch's 38 at 16 instances)
+        typedef const __attribute__((address_space(4))) InstanceInfo* cptr;
+        const cptr t = (cptr)(uintptr_t)insts;
+#pragma unroll 4
         for (int i = 0; i < a.batch; ++i) {
-            const int c0 = insts[i].cu_q;
-            if (r >= c0 && r < c0 + insts[i].q_len) { b = i; j = r - c0; break; }
+            const int c0 = t[i].cu_q, n = t[i].q_len;
+            const int64_t p = t[i].pos_base;
+            if (r >= c0 && r < c0 + n) { b = i; j = r - c0; base = p; }
         }
     }
     if (b < 0 || j < 0 || j >= a.token_stride) return d;
     d.valid = true;
-    d.pos = (float)(insts[b].pos_base + j);
+    d.pos = (float)(base + j);
     d.elem_off = ((size_t)b * a.Hkv * a.token_stride + (size_t)j) * D;
     return d;
 }
@@ -134,7 +143,6 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(MaterializeArgs a
     const int kv = ct / a.Hkv, head = ct % a.Hkv;
     const int row0 = rt * BM;
     const int nk = a.Hd / (BK * SK);
-    const RowDest my_dest = resolve_row(a, row0 + min(tid, BM - 1));
 
     // Copies of a step: 8 rows x 128 bytes per instruction; token rows are instructions 0 .. 4 MI - 1,
     // wave w takes w, w + 8, ...; of the 16 weight instructions every wave takes two.  LDS row r holds
@@ -204,6 +212,7 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(MaterializeArgs a
     // the barrier every wave has its operands of step ks in registers, so step ks + NBUF is copied over it.
     const int ahead = min(NBUF, nk);
     for (int i = 0; i < ahead; ++i) copy_step(i, i);
+    const RowDest my_dest = resolve_row(a, row0 + min(tid, BM - 1));      // (while they are on their way)
     if (ahead == NBUF) wait_steps(std::integral_constant<int, NBUF - 1>{}); else dev::dma_wait<0>();
     lds_barrier();
     Frags f0, f1;
