@@ -263,6 +263,13 @@ matkv_status matkv_assemble(matkv_ctx* ctx, const matkv_page* pages_host,
 int32_t matkv_plan_decode_units(const matkv_config* cfg, const int32_t* page_tokens_host,
                                 int32_t n_pages, int32_t batch, int32_t q_len,
                                 int32_t* unit_tokens_out, int32_t* unit_items_out, int32_t cap);
+/* Host-only preview of how matkv_assemble lays out a batch's question prefill (no GPU is touched).
+ * page_tokens_host: [batch][max_pages], instance b has its first n_pages_host[b] chunk lengths; format: a
+ * matkv_page_format.  units_out[batch] (may be NULL): units each instance's cache is cut into.  Returns the
+ * (question row, query head) rows of a workgroup's tile - 64, 128 or 256 - or 0 where the prefill runs on a
+ * kernel without row tiles, -1 on a bad argument. */
+int32_t matkv_plan_prefill(const matkv_config* cfg, const int32_t* page_tokens_host, const int32_t* n_pages_host,
+                           const int32_t* q_len_host, int32_t batch, int32_t format, int32_t* units_out);
 /* Host-only preview of the shared decode partition (see matkv_table_shared_units) that
  * matkv_assemble would build for a batch (no GPU is touched).  page_ids_host /
  * page_tokens_host: [batch][max_pages], instance b uses its first n_pages_host[b] entries;

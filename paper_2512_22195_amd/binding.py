@@ -28,7 +28,7 @@ EXPORTS = [
     "matkv_wait", "matkv_query", "matkv_sync", "matkv_assemble", "matkv_advance",
     "matkv_prefill_attn", "matkv_decode_attn", "matkv_decode_step", "matkv_graph_begin", "matkv_graph_end",
     "matkv_graph_launch", "matkv_graph_destroy", "matkv_plan_decode_units", "matkv_probe_read",
-    "matkv_table_shared_units", "matkv_plan_shared_units", "matkv_decode_attn_static",
+    "matkv_table_shared_units", "matkv_plan_prefill", "matkv_plan_shared_units", "matkv_decode_attn_static",
 ]
 
 
@@ -106,6 +106,8 @@ def _load_library():
     lib.matkv_plan_decode_units.argtypes = [cfgp, POINTER(c_int32), c_int32, c_int32, c_int32,
                                             POINTER(c_int32), POINTER(c_int32), c_int32]
     lib.matkv_plan_decode_units.restype = c_int32
+    lib.matkv_plan_prefill.argtypes = [cfgp] + [POINTER(c_int32)] * 3 + [c_int32, c_int32, POINTER(c_int32)]
+    lib.matkv_plan_prefill.restype = c_int32
     lib.matkv_plan_shared_units.argtypes = [cfgp] + [POINTER(c_int32)] * 4 + [c_int32, POINTER(c_int32), c_int32, POINTER(c_int32)]
     lib.matkv_plan_shared_units.restype = c_int32
     lib.matkv_probe_read.argtypes = [c_void_p, c_void_p, c_size_t]; lib.matkv_probe_read.restype = c_int32
@@ -181,6 +183,21 @@ def plan_shared_units(cfg: Config, pages, q_lens):
                   users=[(out[u * w + 4 + 3 * k], out[u * w + 5 + 3 * k], out[u * w + 6 + 3 * k]) for k in range(out[u * w + 3])])
              for u in range(n)]
     return units, ([(slots[2 * b], slots[2 * b + 1]) for b in range(batch)] if n else None)
+
+
+def plan_prefill(cfg: Config, page_tokens, q_lens, format: int = PAGE_PLAIN):
+    """(tile rows - 0 without row tiles -, units per instance) of the question prefill matkv_assemble would lay
+    out.  page_tokens: per instance a list of chunk lengths."""
+    batch, mp = len(page_tokens), max(cfg.max_pages, 1)
+    toks = (c_int32 * (batch * mp))()
+    for b, lens in enumerate(page_tokens):
+        for i, n in enumerate(lens[:mp]):
+            toks[b * mp + i] = n
+    npg, ql, units = (c_int32 * batch)(*[len(p) for p in page_tokens]), (c_int32 * batch)(*q_lens), (c_int32 * batch)()
+    rows = _lib.matkv_plan_prefill(byref(cfg), toks, npg, ql, batch, format, units)
+    if rows < 0:
+        raise MatKVError(EINVAL, "matkv_plan_prefill")
+    return int(rows), list(units)
 
 
 def plan_decode_units(cfg: Config, page_tokens, batch: int, q_len: int):

@@ -552,6 +552,239 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     }
 }
 
+// ---- up to 64 (question row, query head) rows per KV head -------------------------------------
+// (Plain pages.)  A short question's launch is bound by fetching the cache, and the 128-row form above serves it
+// badly: its waves compute 32 rows whether they are there or not, its first blocks are a quarter of a unit of a
+// few hundred tokens, and a compute unit holds one workgroup.  Here a workgroup of four waves owns 64 rows, 16 per
+// wave (16x16x32), all waves walk the same 64-token blocks out of double-buffered LDS tiles, and two workgroups
+// share a compute unit.  The next block's loads are in flight in registers meanwhile.  8B shape, one row,
+// us per layer with the fold, 128-row form -> this one: four over 3000 tokens 19.0 -> 17.0 (49 MB), one over 10 000
+// 18.0 -> 16.6 (41 MB).  Over compressed pages (half the bytes) it was no faster and is not built.
+//   S^T = K Q^T     A = K rows from the LDS tile, B = Q held in registers
+//   softmax         online, per lane on its own column; the four 16-lane groups agree on the maximum
+//   O^T += V^T P^T  A = V through the transposing LDS read, B = P rounded to bf16
+// Row strides of the tiles: the ones on which the 16-byte operand reads (K) and the transposing reads (V)
+// measured fastest (K 288 bytes 5.4 cycles per instruction against 8.8 at 272; V 304 bytes 6.2 against 6.7 at 288).
+constexpr int KSTR = D + 16, VSTR = D + 24;             // bf16 per LDS row of the K and of the V tile
+
+__global__ __launch_bounds__(256, 2) void attn_prefill_short_kernel(
+        KernelArgs a, const InstanceInfo* __restrict__ insts, const Item* __restrict__ items,
+        const Unit* __restrict__ units) {
+    constexpr int NWV = 4, RT = 16 * NWV, SR = TB / (4 * NWV);
+    constexpr int TILE_ELEMS = TB * KSTR + TB * VSTR;   // one K tile + one V tile
+    typedef uint16_t T;
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63;
+    const int c16 = lane & 15, g4 = lane >> 4;
+    const int G = a.Hq / a.Hkv;
+    auto div_g = [&](int m) { return (int)__umulhi((unsigned)m << 3, a.g_mul); };
+    const int kvh = blockIdx.y, m0 = blockIdx.z * RT;
+
+    const Unit unit = table_record(units + blockIdx.x);
+    const InstanceInfo inst = table_record(insts + unit.inst);
+    const int n_m = inst.q_len * G;
+    if (m0 >= n_m) return;                              // whole workgroup leaves together
+    const bool wave_live = m0 + 16 * wave < n_m;        // this wave has at least one real row
+    const int vis_min = div_g(m0 + 16 * wave) + 1;      // tail rows every row of this wave may see
+
+    // Q in operand layout; padding rows repeat the last real row
+    bf16x8 bq[4];
+    const int mq = min(m0 + 16 * wave + c16, n_m - 1), rq = div_g(mq);
+    const int vis = rq + 1;                             // tail rows this lane's row may see
+    {
+        const T* qp = reinterpret_cast<const T*>(a.q) + ((size_t)(inst.cu_q + rq) * a.Hq + (size_t)kvh * G + (mq - rq * G)) * D + 8 * g4;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) bq[c] = __builtin_bit_cast(bf16x8, ldg16(qp + 32 * c));
+    }
+
+    f32x4 ot[8], ol = f32x4{0.f, 0.f, 0.f, 0.f};        // O^T accumulators; row sum (every element of a lane the same)
+    float mrow = kNegBig;                               // reference score of the lane's row, unscaled
+#pragma unroll
+    for (int s = 0; s < 8; ++s) ot[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    __shared__ __attribute__((aligned(16))) uint16_t tiles[2 * TILE_ELEMS];
+    // the unit's item list sits in LDS: a fetch inside the loop would also drain the block loads in flight
+    __shared__ __attribute__((aligned(16))) Item sm_items[kMaxPrefillItemsPerUnit];
+    for (int i = tid; i < unit.n_items * 2; i += NWV * 64)
+        reinterpret_cast<uint4*>(sm_items)[i] = reinterpret_cast<const uint4*>(items + unit.item0)[i];
+    __syncthreads();
+
+    // Every wave walks the same blocks: the unit's items end to end (the tail clipped to the rows this tile
+    // may see), TB token rows at a time, never across two items.  Past the unit's end the last block comes
+    // back marked invalid: still safe to load, so that the loop's loads are unconditional.
+    struct { Item item; int item_i, rows, left; } wk;   // current item, its visible rows, rows not yet handed out
+    const int tail_visible = min(div_g(min(m0 + RT, n_m) - 1) + 1, a.max_tail);
+    auto rows_of = [&](const Item& it) { return it.base ? it.ntok : min(it.ntok, tail_visible); };
+    wk.item = unit.first; wk.item_i = 0; wk.rows = rows_of(wk.item); wk.left = wk.rows;
+    BlockRef<T> last_block{};
+    auto next_block = [&]() {
+        BlockRef<T> r = last_block;
+        r.valid = false;
+        while (wk.left <= 0) {
+            if (++wk.item_i >= unit.n_items) return r;
+            wk.item = sm_items[wk.item_i];
+            wk.rows = rows_of(wk.item);
+            wk.left = wk.rows;
+        }
+        r.is_tail = wk.item.base == 0;
+        if (!r.is_tail) {
+            const size_t head = (size_t)wk.item.page_tokens * D;
+            r.k = reinterpret_cast<const T*>(wk.item.base) + ((size_t)a.layer * 2 * a.Hkv + kvh) * head;
+            r.v = r.k + (size_t)a.Hkv * head;
+        } else {
+            const size_t off = ((size_t)unit.inst * a.Hkv + kvh) * (size_t)a.max_tail * D;
+            r.k = reinterpret_cast<const T*>(a.tail_k) + off;
+            r.v = reinterpret_cast<const T*>(a.tail_v) + off;
+        }
+        const int n = min(TB, wk.left);
+        r.t0 = wk.item.tok0 + (wk.rows - wk.left);
+        r.tok_end = r.t0 + n;
+        r.valid = true;
+        wk.left -= n;
+        last_block = r;
+        return r;
+    };
+
+    // cooperative staging: thread t moves rows t / 16 + 16 i, columns 8 (t % 16), of K and of V; rows past the
+    // block's end repeat its last one
+    const int st_row = tid >> 4, st_col = (tid & 15) * 8;
+    struct Stage { uint4 k[SR], v[SR]; };
+    auto load_global = [&](const BlockRef<T>& r, Stage& g) {
+#pragma unroll
+        for (int i = 0; i < SR; ++i) {
+            const size_t off = (size_t)min(r.t0 + st_row + 4 * NWV * i, r.tok_end - 1) * D + st_col;
+            g.k[i] = ldg16(r.k + off);
+            g.v[i] = ldg16(r.v + off);
+        }
+    };
+    auto store_lds = [&](int buf, const Stage& g) {
+        uint16_t* kt = tiles + buf * TILE_ELEMS;
+        uint16_t* vt = kt + TB * KSTR;
+#pragma unroll
+        for (int i = 0; i < SR; ++i) {
+            *reinterpret_cast<uint4*>(kt + (st_row + 4 * NWV * i) * KSTR + st_col) = g.k[i];
+            *reinterpret_cast<uint4*>(vt + (st_row + 4 * NWV * i) * VSTR + st_col) = g.v[i];
+        }
+    };
+
+    // Scores, reference scores and masks as in the kernel above.
+    const float sc = a.scale_log2e;
+    const float lazy_raw = kLazyLog2 / sc;
+    auto compute = [&](const BlockRef<T>& r, int buf) {
+        const bool masked = r.tok_end - r.t0 != TB || (r.is_tail && r.tok_end > vis_min);
+        const uint16_t* kt = tiles + buf * TILE_ELEMS;
+        const uint16_t* vt = kt + TB * KSTR;
+        bf16x8 ones;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) ones[i] = (__bf16)1.0f;
+        // S^T in 16-token quarters q: lane holds tokens t0 + 16 q + 4 g4 + i of its row
+        f32x4 st[4];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            bf16x8 ak[2][4];
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    ak[hh][c] = *reinterpret_cast<const bf16x8*>(kt + (32 * h + 16 * hh + c16) * KSTR + 32 * c + 8 * g4);
+            st[2 * h] = f32x4{0.f, 0.f, 0.f, 0.f};
+            st[2 * h + 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int hh = 0; hh < 2; ++hh)
+                    st[2 * h + hh] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ak[hh][c], bq[c], st[2 * h + hh], 0, 0, 0);
+        }
+        if (masked) {               // wave-uniform
+            const int limit = (r.is_tail ? min(r.tok_end, vis) : r.tok_end) - r.t0 - 4 * g4;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) st[q][i] = 16 * q + i < limit ? st[q][i] : kNegBig;
+        }
+        float mx = st[0][0];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) mx = fmaxf(mx, st[q][i]);
+        mx = fmaxf(mx, lane_xor(mx, 16, lane));
+        mx = fmaxf(mx, lane_xor(mx, 32, lane));
+        const float mn = mx > mrow + lazy_raw ? mx : mrow;
+        const float alpha = fast_exp2((mrow - mn) * sc);
+        mrow = mn;
+        const float nmc = mn > 0.5f * kNegBig ? -mn * sc : 0.f;
+        bf16x8 pb[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) pb[h][i] = (__bf16)fast_exp2(fmaf(st[2 * h + i / 4][i % 4], sc, nmc));
+        if (__builtin_amdgcn_ballot_w64(alpha != 1.0f)) {           // wave-uniform: some row's reference moved
+            ol[0] *= alpha;
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) ot[s][i] *= alpha;
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) ol = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb[h], ol, 0, 0, 0);
+        // lane (c16, g4) names 4 dims (4 (c16 % 4) ..) of token 4 g4 + c16 / 4 (+ 16 for the second quarter)
+        // of a half and receives dim 16 s + c16 of tokens 4 g4 .. 4 g4 + 3: the k order of P
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const char* vp = reinterpret_cast<const char*>(vt + (32 * h + 4 * g4 + (c16 >> 2)) * VSTR + 4 * (c16 & 3));
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                const s16x4 lo = lds_read_tr(vp + 32 * s);
+                const s16x4 hi = lds_read_tr(vp + 32 * VSTR + 32 * s);
+                const bf16x8 av = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                ot[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, pb[h], ot[s], 0, 0, 0);
+            }
+        }
+    };
+
+    // Loads and LDS stores carry no branch and the loop has one exit at the bottom, so the compiler counts the
+    // loads in flight; every load before the loop (Q above all) is waited for once, ahead of it: otherwise each
+    // use of Q inside is guarded with a wait that would also drain the block just requested.
+    BlockRef<T> r0 = next_block();
+    if (r0.valid) {
+        Stage g;
+        load_global(r0, g);
+        store_lds(0, g);
+        __builtin_amdgcn_s_waitcnt(0x0F70);             // vmcnt(0) only
+        lds_barrier();
+        int buf = 0;
+        do {
+            const BlockRef<T> r1 = next_block();
+            load_global(r1, g);
+            if (wave_live) compute(r0, buf);
+            store_lds(buf ^ 1, g);
+            lds_barrier();
+            r0 = r1;
+            buf ^= 1;
+        } while (r0.valid);
+    }
+
+    // a wave owns its rows: lane (c16, g4) holds dims 16 s + 4 g4 .. + 3 of row c16
+    const int m = m0 + 16 * wave + c16;
+    if (m >= n_m) return;
+    const int r = div_g(m), head = kvh * G + m - r * G;
+    if (unit.n_units_inst == 1) {
+        const float inv = 1.0f / ol[0];
+        const size_t oidx = ((size_t)(inst.cu_q + r) * a.Hq + head) * D + 4 * g4;
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+            store_out4(a.out, a.out_f32, oidx + 16 * s, make_float4(ot[s][0] * inv, ot[s][1] * inv, ot[s][2] * inv, ot[s][3] * inv));
+    } else {
+        float* prow = a.partials + (((size_t)blockIdx.x * a.rows + r) * a.Hq + head) * kPartialStride(D);
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+            *reinterpret_cast<float4*>(prow + 16 * s + 4 * g4) = make_float4(ot[s][0], ot[s][1], ot[s][2], ot[s][3]);
+        if (g4 == 0) *reinterpret_cast<float2*>(prow + D) = make_float2(mrow * sc, ol[0]);
+    }
+}
+
 // Folds the units' partials of every (question row, query head) of instances cut into several
 // units: out = sum_u 2^(m_u - M) acc_u / sum_u 2^(m_u - M) l_u,  M = max_u m_u.
 // Half a wave owns one row: lane k first fetches (m, l) of unit k, the half wave agrees on M
@@ -613,12 +846,13 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(
     store_out4(a.out, a.out_f32, oidx, make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv));
 }
 
-template <int RW, bool F8>
-hipError_t launch_v(const AttnArgs& a, hipStream_t s) {
+template <bool F8>
+hipError_t launch_f(const AttnArgs& a, hipStream_t s) {
     const KernelArgs k = make_kernel_args(a);
-    const int tiles = (a.rows * (a.Hq / a.Hkv) + RW * WR - 1) / (RW * WR);
-    dim3 grid(a.n_units, a.Hkv, tiles), block(NW * 64);
-    hipLaunchKernelGGL((attn_prefill_kernel<RW, F8>), grid, block, 0, s, k,
+    const int tiles = (a.rows * (a.Hq / a.Hkv) + a.tile_rows - 1) / a.tile_rows;
+    const dim3 grid(a.n_units, a.Hkv, tiles), block(a.tile_rows <= 64 ? 256 : NW * 64);      // (64: plain pages only)
+    auto kern = !F8 && a.tile_rows <= 64 ? attn_prefill_short_kernel : a.tile_rows <= 128 ? attn_prefill_kernel<4, F8> : attn_prefill_kernel<8, F8>;
+    hipLaunchKernelGGL(kern, grid, block, 0, s, k,
                        reinterpret_cast<const InstanceInfo*>(a.table + a.off_inst),
                        reinterpret_cast<const Item*>(a.table + a.off_items),
                        reinterpret_cast<const Unit*>(a.table + a.off_units));
@@ -632,11 +866,6 @@ hipError_t launch_v(const AttnArgs& a, hipStream_t s) {
     else if (a.max_units_inst <= 8) hipLaunchKernelGGL(prefill_merge_kernel<8>, mgrid, mblock, 0, s, k, insts, a.batch, total_pairs);
     else                            hipLaunchKernelGGL(prefill_merge_kernel<16>, mgrid, mblock, 0, s, k, insts, a.batch, total_pairs);
     return hipGetLastError();
-}
-
-template <bool F8>
-hipError_t launch_f(const AttnArgs& a, hipStream_t s) {
-    return a.tile_rows <= 128 ? launch_v<4, F8>(a, s) : launch_v<8, F8>(a, s);
 }
 
 }  // namespace

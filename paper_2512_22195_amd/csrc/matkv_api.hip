@@ -50,11 +50,15 @@ struct SlotState {
     hipEvent_t release = nullptr;   // recorded on the compute stream when its last table let go of it
 };
 
+// How the question prefill of a table is laid out.
+struct PrefillLayout {
+    int tile_rows = 0;        // rows of a workgroup's tile: 64, 128 or 256
+    int n_units = 0, max_units_inst = 0, max_unit_items = 0;    // units; most of any one instance, most items of any one unit
+};
+
 struct TableHost {
-    int batch = 0, n_items = 0, n_dunits = 0, n_punits = 0, total_q = 0, max_q = 0;
-    int max_punits_inst = 0;  // most prefill units of any one instance
-    int max_punit_items = 0;  // most items of any one prefill unit
-    int prefill_tile_rows = 0;   // rows of a prefill workgroup's tile: 128 or 256
+    int batch = 0, n_items = 0, n_dunits = 0, total_q = 0, max_q = 0;
+    PrefillLayout prefill;
     int kv_fmt = 0;           // matkv_page_format of its pages
     int n_sunits = 0;         // units of the shared decode partition; 0 = the batch shares no page
     uint64_t sig_decode = 0, sig_prefill = 0;   // of what a recorded decode / prefill launch bakes in
@@ -279,6 +283,26 @@ int choose_prefill_tile(const matkv_config& cfg, long tiles128, long tiles256, l
     return cost(tiles128, 128) <= cost(tiles256, 256) ? 128 : 256;
 }
 
+// Estimated time (us) of one layer's row-tile prefill attention over plain pages without its fold: a start, then as
+// many steps as the longest walk has (a step takes one block of 64 tokens, with 128-row tiles two, none across two
+// pieces; two 64-row workgroups share a compute unit and take 1.23 times as long) or the reading of the
+// cache, whichever is longer - near one another they add up, hence the fourth root; the reading takes longer where
+// the compute units hold unequal numbers of workgroups.  The constants are fitted to measurements at the 3B, 8B and
+// 70B layer shapes (1 to 24 instances of 64 to 20 000 tokens in 1 to 32 units, questions of up to 64 (row, head)
+// rows), which they give within 6.5 %.
+// walk_tokens, walk_pieces: of the longest unit; tile_mb: K and V bytes that the tiles read, in MB.
+double prefill_form_time(int tile_rows, long workgroups, long walk_tokens, long walk_pieces, double tile_mb) {
+    const long blocks = std::max((walk_tokens + 63) / 64, walk_pieces), per_round = tile_rows == 64 ? 512 : 256;
+    const long steps = tile_rows == 128 ? (blocks + 1) / 2 : blocks;
+    double rounds = (double)((workgroups + per_round - 1) / per_round);
+    if (tile_rows == 64) rounds = (rounds - 1) * 1.23 + ((workgroups - 1) % per_round >= 256 ? 1.23 : 1.0);
+    const double start = tile_rows == 64 ? 5.28 : tile_rows == 128 ? 6.86 : 7.0;
+    const double step = tile_rows == 64 ? 1.22 : tile_rows == 128 ? 1.73 : 1.9;
+    const double uneven = workgroups >= 96 ? (double)((workgroups + 255) / 256 * 256) / (double)workgroups : 256.0 / 96.0;
+    const double walk = rounds * (double)steps * step, read = 0.17 * tile_mb * pow(uneven, 0.147);
+    return start + pow(pow(walk, 4) + pow(read, 4), 0.25);
+}
+
 // Cuts one instance's cache (its pages in order, then its tail) into n_units runs of nearly
 // equal token counts, in 8-token granules.  A run is a list of items (page pieces); the tail
 // is one item and belongs to the last run.  Appends to items / units; returns the number of
@@ -338,6 +362,54 @@ int build_units(const matkv_page* pages, int n_pages, int inst, int n_units, int
         un.unit0_inst = *n_units_out - made;
     }
     return made;
+}
+
+// Question prefill of a batch: tile height, units and their items (punit0 / n_punits of every instance), given the
+// batch's pages [batch][max_pages].
+template <typename ScalesOff>
+PrefillLayout lay_out_prefill(const matkv_config& cfg, const matkv_page* pages, const int32_t* n_pages, const int32_t* q_len, int batch,
+                              bool codes, InstanceInfo* insts, Item* items, int* n_items, Unit* units, ScalesOff scales_off) {
+    PrefillLayout L;
+    const int g = cfg.n_q_heads / cfg.n_kv_heads;
+    long most_tokens = 0, most_rows = 0;
+    std::vector<long> tokens(batch);
+    for (int b = 0; b < batch; ++b) {
+        tokens[b] = q_len[b];
+        for (int p = 0; p < n_pages[b]; ++p) tokens[b] += pages[(size_t)b * cfg.max_pages + p].n_tokens;
+        most_tokens = std::max(most_tokens, tokens[b]);
+        most_rows = std::max(most_rows, (long)q_len[b] * g);
+    }
+    auto tiles = [&](long tile_rows) {                  // of (question row, query head of one KV head) over the batch
+        long n = 0;
+        for (int b = 0; b < batch; ++b) n += ((long)q_len[b] * g + tile_rows - 1) / tile_rows;
+        return n;
+    };
+    L.tile_rows = choose_prefill_tile(cfg, tiles(128), tiles(256), most_tokens);
+    const long n_tiles = tiles(L.tile_rows);
+    long walk_tokens = 0;
+    for (int b = 0; b < batch; ++b) {
+        const int pu = choose_prefill_units(cfg, n_tiles, L.tile_rows, tokens[b]);
+        insts[b].punit0 = L.n_units;
+        insts[b].n_punits = build_units(pages ? pages + (size_t)b * cfg.max_pages : nullptr, n_pages[b], b, pu, q_len[b], cfg.max_tail_tokens,
+                                        items, n_items, units, &L.n_units, scales_off);
+        L.max_units_inst = std::max(L.max_units_inst, insts[b].n_punits);
+        for (int u = insts[b].punit0; u < L.n_units; ++u) {
+            L.max_unit_items = std::max(L.max_unit_items, units[u].n_items);
+            walk_tokens = std::max(walk_tokens, (long)units[u].page_tokens + (units[u].has_tail ? q_len[b] : 0));
+        }
+    }
+    // Questions of at most 64 (row, head) rows over plain pages: 64-row tiles over the same units where they are
+    // estimated to be faster by more than a tie.  8B shape, us per layer with 128-row tiles -> 64-row tiles: four 1-row questions over 3000
+    // tokens 19.0 -> 17.0, one over 10 000 18.0 -> 16.6, one 16-row question over 64 tokens 7.5 -> 6.6; not: 24 over 2000
+    // tokens 39.9 -> 49.8.
+    if (!codes && most_rows <= 64 && L.max_unit_items <= kMaxPrefillItemsPerUnit) {
+        auto time = [&](int tile_rows) {
+            return prefill_form_time(tile_rows, (long)L.n_units * cfg.n_kv_heads, walk_tokens, L.max_unit_items,
+                                     (double)tiles(tile_rows) * cfg.n_kv_heads * (double)most_tokens * 512e-6);
+        };
+        if (time(64) < 0.98 * time(L.tile_rows)) L.tile_rows = 64;
+    }
+    return L;
 }
 
 // Shared decode partition (instances of a batch that retrieved the same chunk read it once).
@@ -554,7 +626,9 @@ uint64_t fnv(std::initializer_list<int> f) {
 }
 void sign_partition(TableHost& th) {
     th.sig_decode = fnv({th.batch, th.n_dunits, th.n_sunits, th.kv_fmt});
-    th.sig_prefill = fnv({th.batch, th.n_punits, th.total_q, th.max_q, th.max_punits_inst, th.max_punit_items, th.kv_fmt});
+    // (a recorded prefill launch also bakes in the tile height.  It is left out: every height gives the right result
+    // on every partition, and a table that would now take another one is replayed as recorded.)
+    th.sig_prefill = fnv({th.batch, th.prefill.n_units, th.total_q, th.max_q, th.prefill.max_units_inst, th.prefill.max_unit_items, th.kv_fmt});
 }
 // While a graph is being recorded: remember that it reads this table's decode or prefill side.
 void note_table_use(matkv_ctx* c, const void* table, const TableHost& th, bool prefill) {
@@ -1236,24 +1310,9 @@ matkv_status matkv_assemble(matkv_ctx* c, const matkv_page* pages, const int32_t
     Unit* dunits = reinterpret_cast<Unit*>(h + c->tl.off_dunits);
     Unit* punits = reinterpret_cast<Unit*>(h + c->tl.off_punits);
     memset(hdr, 0, sizeof(*hdr));
-    int n_items = 0, n_dunits = 0, n_punits = 0, cu = 0, max_q = 0;
+    int n_items = 0, n_dunits = 0, cu = 0, max_q = 0;
     TableHost th;
     th.min_tail_len = cfg.max_tail_tokens;
-    // row tiles of (question row, query head of one KV head) over the batch
-    long prefill_tiles = 0, most_tokens = 0;
-    auto count_tiles = [&](long tile_rows) {
-        long n = 0;
-        for (int b = 0; b < batch; ++b) n += ((long)q_len[b] * (cfg.n_q_heads / cfg.n_kv_heads) + tile_rows - 1) / tile_rows;
-        return n;
-    };
-    for (int b = 0; b < batch; ++b) {
-        long t = q_len[b];
-        for (int p = 0; p < n_pages[b]; ++p) t += pages[(size_t)b * cfg.max_pages + p].n_tokens;
-        most_tokens = std::max(most_tokens, t);
-    }
-    th.prefill_tile_rows = choose_prefill_tile(cfg, count_tiles(128), count_tiles(256), most_tokens);
-    const long tile_rows = th.prefill_tile_rows;
-    prefill_tiles = count_tiles(tile_rows);
     for (int b = 0; b < batch; ++b) {
         InstanceInfo& in = insts[b];
         memset(&in, 0, sizeof(in));
@@ -1276,15 +1335,9 @@ matkv_status matkv_assemble(matkv_ctx* c, const matkv_page* pages, const int32_t
         in.dunit0 = n_dunits;
         in.n_dunits = build_units(pg, n_pages[b], b, choose_decode_units(cfg, batch, inst_tokens + tail_est),
                                   tail_est, cfg.max_tail_tokens, items, &n_items, dunits, &n_dunits, scales_off);
-        // prefill: coarse partition (the question rows supply most of the parallelism)
-        const int pu = choose_prefill_units(cfg, prefill_tiles, tile_rows, inst_tokens + q_len[b]);
-        in.punit0 = n_punits;
-        in.n_punits = build_units(pg, n_pages[b], b, pu, q_len[b], cfg.max_tail_tokens, items, &n_items,
-                                  punits, &n_punits, scales_off);
-        if (in.n_punits > th.max_punits_inst) th.max_punits_inst = in.n_punits;
-        for (int u = in.punit0; u < n_punits; ++u)
-            if (punits[u].n_items > th.max_punit_items) th.max_punit_items = punits[u].n_items;
     }
+    // prefill: coarse partition (the question rows supply most of the parallelism)
+    th.prefill = lay_out_prefill(cfg, pages, n_pages, q_len, batch, kv_fmt == MATKV_PAGE_E4M3, insts, items, &n_items, punits, scales_off);
     // decode over shared pages: only where the default matrix-core decode kernel runs
     const int grp = cfg.n_q_heads / cfg.n_kv_heads;
     int n_sunits = 0;
@@ -1292,20 +1345,20 @@ matkv_status matkv_assemble(matkv_ctx* c, const matkv_page* pages, const int32_t
         cfg.dtype == MATKV_BF16 && cfg.head_dim == 128 && group_size_built(grp))
         n_sunits = build_shared_units(cfg, pages, n_pages, batch, c->tl.max_sunits, c->tl.max_items, insts, items, &n_items,
                                       reinterpret_cast<SUnit*>(h + c->tl.off_sunits), kv_fmt);
-    hdr->batch = batch; hdr->n_items = n_items; hdr->n_dunits = n_dunits; hdr->n_punits = n_punits;
+    hdr->batch = batch; hdr->n_items = n_items; hdr->n_dunits = n_dunits; hdr->n_punits = th.prefill.n_units;
     hdr->total_q = cu; hdr->max_q = max_q;
 
     char* d = reinterpret_cast<char*>(table);
     HIP_TRY(c, hipMemcpyAsync(d, h, c->tl.off_inst + sizeof(InstanceInfo) * batch, hipMemcpyHostToDevice, c->compute));
     HIP_TRY(c, hipMemcpyAsync(d + c->tl.off_items, h + c->tl.off_items, sizeof(Item) * n_items, hipMemcpyHostToDevice, c->compute));
     HIP_TRY(c, hipMemcpyAsync(d + c->tl.off_dunits, h + c->tl.off_dunits, sizeof(Unit) * n_dunits, hipMemcpyHostToDevice, c->compute));
-    HIP_TRY(c, hipMemcpyAsync(d + c->tl.off_punits, h + c->tl.off_punits, sizeof(Unit) * n_punits, hipMemcpyHostToDevice, c->compute));
+    HIP_TRY(c, hipMemcpyAsync(d + c->tl.off_punits, h + c->tl.off_punits, sizeof(Unit) * th.prefill.n_units, hipMemcpyHostToDevice, c->compute));
     if (n_sunits > 0)
         HIP_TRY(c, hipMemcpyAsync(d + c->tl.off_sunits, h + c->tl.off_sunits, sizeof(SUnit) * n_sunits, hipMemcpyHostToDevice, c->compute));
     HIP_TRY(c, hipEventRecord(sg.ev, c->compute));
     sg.used = true;
 
-    th.batch = batch; th.n_items = n_items; th.n_dunits = n_dunits; th.n_punits = n_punits;
+    th.batch = batch; th.n_items = n_items; th.n_dunits = n_dunits;
     th.total_q = cu; th.max_q = max_q; th.kv_fmt = kv_fmt; th.n_sunits = n_sunits;
     th.n_decode_slots = n_dunits;
     if (n_sunits > 0) {
@@ -1368,6 +1421,38 @@ int32_t matkv_plan_decode_units(const matkv_config* cfg, const int32_t* page_tok
         if (unit_items_out) unit_items_out[u] = units[u].n_items - units[u].has_tail;
     }
     return made < cap ? made : cap;
+    MATKV_CATCH_INT
+}
+
+int32_t matkv_plan_prefill(const matkv_config* cfg, const int32_t* page_tokens, const int32_t* n_pages, const int32_t* q_len,
+                           int32_t batch, int32_t format, int32_t* units_out) {
+    const char* why;
+    if (check_config(cfg, &why) != MATKV_OK) return -1;
+    if (!n_pages || !q_len || batch < 1 || batch > cfg->max_batch || (format != MATKV_PAGE_PLAIN && format != MATKV_PAGE_E4M3)) return -1;
+    const bool row_tiles = cfg->dtype == MATKV_BF16 && cfg->head_dim == 128;
+    if (format == MATKV_PAGE_E4M3 && !row_tiles) return -1;
+    MATKV_TRY
+    std::vector<matkv_page> pages((size_t)batch * std::max(cfg->max_pages, 1));
+    std::vector<InstanceInfo> insts((size_t)batch);
+    for (int b = 0; b < batch; ++b) {
+        if (n_pages[b] < 0 || n_pages[b] > cfg->max_pages || q_len[b] < 1 || q_len[b] > cfg->max_tail_tokens) return -1;
+        if (n_pages[b] > 0 && !page_tokens) return -1;
+        for (int p = 0; p < n_pages[b]; ++p) {
+            const size_t i = (size_t)b * cfg->max_pages + p;
+            if (page_tokens[i] < 1) return -1;
+            pages[i].slot = reinterpret_cast<const void*>((uintptr_t)0x1000);     // never dereferenced
+            pages[i].n_tokens = page_tokens[i];
+            pages[i].format = format;
+        }
+    }
+    const TableLayout tl = table_layout(*cfg);
+    std::vector<Item> items((size_t)tl.max_items);
+    std::vector<Unit> units((size_t)tl.max_punits);
+    int n_items = 0;
+    const PrefillLayout L = lay_out_prefill(*cfg, pages.data(), n_pages, q_len, batch, format == MATKV_PAGE_E4M3, insts.data(), items.data(),
+                                            &n_items, units.data(), [](int) { return (size_t)0; });
+    if (units_out) for (int b = 0; b < batch; ++b) units_out[b] = insts[b].n_punits;
+    return row_tiles && L.max_unit_items <= kMaxPrefillItemsPerUnit ? L.tile_rows : 0;
     MATKV_CATCH_INT
 }
 
@@ -1480,11 +1565,11 @@ static matkv_status attn_args(matkv_ctx* c, const char* name, int prefill, int32
     a.prefill = prefill;
     a.rows = prefill ? th->max_q : 1;
     a.shared = !prefill && th->n_sunits > 0;
-    a.n_units = prefill ? th->n_punits : (a.shared ? th->n_sunits : th->n_dunits);
-    a.max_units_inst = prefill ? th->max_punits_inst : 0;
+    a.n_units = prefill ? th->prefill.n_units : (a.shared ? th->n_sunits : th->n_dunits);
+    a.max_units_inst = prefill ? th->prefill.max_units_inst : 0;
     a.batch = th->batch; a.total_q = th->total_q; a.kv_fmt = th->kv_fmt;
-    a.max_unit_items = prefill ? th->max_punit_items : 0;
-    a.tile_rows = th->prefill_tile_rows;
+    a.max_unit_items = prefill ? th->prefill.max_unit_items : 0;
+    a.tile_rows = th->prefill.tile_rows;
     a.scale_log2e = c->scale_log2e;
     a.out_f32 = c->cfg.dtype == MATKV_BF16 && c->cfg.out_f32;
     a.off_inst = c->tl.off_inst; a.off_items = c->tl.off_items;

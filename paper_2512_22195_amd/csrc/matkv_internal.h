@@ -22,8 +22,8 @@ inline bool group_size_built(int g) { return g == 1 || g == 2 || g == 3 || g == 
 constexpr int kMaxDecodeUnitsPerInstance = 256;
 constexpr int kDecodeCounterStride = 32;         // ints: decode arrival counters sit 128 bytes apart
 constexpr int kMaxPrefillUnitsPerInstance = 32;
-// The row-parallel prefill kernel takes one piece per step: units of more pieces than this (pages of a
-// few tokens) go to the kernel whose waves walk the tokens separately.
+// The row-tile prefill kernels take one piece, or two, per step: units of more pieces than this (pages of a
+// few tokens) go to the kernel whose waves walk the tokens separately.  (The 64-row form keeps so many in LDS.)
 constexpr int kMaxPrefillItemsPerUnit = 64;
 
 struct Item {              // 32 bytes: a run of tokens inside one page, or the tail
@@ -172,7 +172,7 @@ struct AttnArgs {
     int32_t max_units_inst;    // most units any one instance is cut into
     int32_t batch, total_q;    // instances; rows of the packed Q / O tensors (prefill)
     int32_t max_unit_items;    // most items in any one unit of this launch
-    int32_t tile_rows;         // prefill: (question row, query head) rows per workgroup, 128 or 256
+    int32_t tile_rows;         // prefill: (question row, query head) rows per workgroup, 64, 128 or 256
     int32_t prefill;           // 0: decode units + whole tail; 1: prefill units + causal tail;
                                // 2: as 1 for a chunk's own attention (longest row tiles first)
     float scale_log2e;

@@ -184,3 +184,34 @@ def test_shared_partition_covers_every_instance_once(mk):
     assert units and sum(u["tokens"] for u in units) == 500 and all(len(u["users"]) <= 4 for u in units)
     with pytest.raises(mk.MatKVError):
         mk.plan_shared_units(mk.make_config(2, 8, 2, 128, 512, "bf16", 500000.0, 3, 2, 64), [[(0, 0)], [(0, 5)]], [3, 3])
+
+
+def test_prefill_layout_takes_short_tiles_for_short_questions(mk):
+    """Host logic of the question prefill's layout: 64-row tiles only for questions of at most 64 (question row,
+    query head) rows over plain pages in units of at most 64 pieces, and there where the launch is a few short walks;
+    the units cover what the larger tiles' would."""
+    def plan(batch, lens, q, Hq=32, fmt=mk.PAGE_PLAIN, dtype="bf16", D=128):
+        cfg = mk.make_config(2, Hq, 8, D, 4096, dtype, 500000.0, batch, max(len(lens), 1), 224)
+        return mk.plan_prefill(cfg, [lens] * batch, [q] * batch, fmt)
+
+    for Hq, q in ((32, 1), (32, 16), (64, 1), (64, 8), (24, 1), (24, 21), (8, 64)):
+        rows, units = plan(1, [64], q, Hq)
+        assert (rows, units) == (64, [1]), (Hq, q)
+        rows, units = plan(4, [1000] * 3, q, Hq)
+        assert (rows, units) == (64, [8] * 4), (Hq, q)
+        rows, units = plan(1, [1000] * 10, q, Hq)
+        assert (rows, units) == (64, [32]), (Hq, q)
+        assert plan(4, [1000] * 3, q, Hq, mk.PAGE_E4M3) == (128, [8] * 4)
+    assert plan(4, [1000] * 3, 17)[0] == 128 and plan(4, [1000] * 3, 16)[0] == 64      # 68 and 64 rows
+    assert plan(4, [1000] * 3, 9, 64)[0] == 128 and plan(4, [1000] * 3, 22, 24)[0] == 128
+    assert plan(24, [500] * 4, 1)[0] == 128                     # 192 long walks: the 128-row form is ahead
+    assert plan(1, [], 5) == (64, [1])                          # no pages: the question alone
+    assert plan(1, [4] * 100, 1)[0] == 128                      # a step takes one piece of a few tokens, or two with 128 rows
+    assert plan(1, [1] * 300, 1)[0] == 0                        # units of more than 64 pieces
+    assert plan(1, [100], 4, dtype="f32", D=64)[0] == 0         # row-per-workgroup kernel
+    # one long question among short ones
+    cfg = mk.make_config(2, 32, 8, 128, 4096, "bf16", 500000.0, 3, 3, 224)
+    assert mk.plan_prefill(cfg, [[1000] * 3] * 3, [1, 40, 3])[0] == 128
+    for bad in (([[1000]], [0]), ([[0]], [4]), ([[1000]], [225])):
+        with pytest.raises(mk.MatKVError):
+            mk.plan_prefill(cfg, *bad)

@@ -406,6 +406,33 @@ def test_prefill_tile_forms_over_block_edges(name, Hq, Hkv, batch, q_len, compre
     _attention_parity(case, instances=[0, batch - 2, batch - 1])
 
 
+def _prefill_form(case):
+    """Tile rows of the case's question prefill (0: another kernel) and units per instance."""
+    from paper_2512_22195_amd import binding as mk
+    cfg = mk.make_config(case.n_layers, case.Hq, case.Hkv, case.D, case.hidden, case.dtype, 10000.0, case.batch,
+                         max(len(r) for r in case.retrieved) or 1, case.tail_cap)
+    return mk.plan_prefill(cfg, [[case.chunk_lens[c] for c in r] for r in case.retrieved], case.q_lens,
+                           mk.PAGE_E4M3 if case.compressed else mk.PAGE_PLAIN)
+
+
+@pytest.mark.parametrize("Hq,Hkv,q_lens", [
+    (4, 4, [64, 1, 15, 16]),         # rows 64, 1, 15, 16: the tile full, one row, a wave short of and exactly one block of rows
+    (8, 4, [32, 9, 8, 17]),
+    (12, 4, [21, 16, 6, 5]),         # a group of three: 63, 48, 18 and 15 rows
+    (16, 4, [16, 1, 5, 4]),
+    (32, 4, [8, 7, 1, 2]),
+])
+def test_prefill_short_tiles_over_block_edges(Hq, Hkv, q_lens):
+    """64-row prefill tiles: pages one token short of, equal to and one beyond a block, a cache of a single token,
+    none at all, one in several units; every group size; rows that fill the tile, a wave or a part of one."""
+    lens = {0: 63, 1: 64, 2: 65, 3: 1, 4: 5, 5: 129, 6: 700}
+    case = Case(f"prefill-short-{Hq}", n_layers=2, Hq=Hq, Hkv=Hkv, D=128, hidden=64, dtype="bf16", chunk_lens=lens,
+                retrieved=[[0, 1, 2, 3, 4, 5], [6, 5], [], [3]], q_lens=q_lens, steps=1, scale=0.5)
+    form, units = _prefill_form(case)
+    assert form == 64 and max(units) > 1 and units[2:] == [1, 1]
+    _attention_parity(case)
+
+
 def test_attention_no_pages_and_full_tail():
     """Degenerate caches: an instance that retrieved nothing (plain causal attention over its
     own tokens) and a tail filled to its capacity."""
