@@ -425,9 +425,9 @@ def _prefill_form(case):
 def test_prefill_short_tiles_over_block_edges(Hq, Hkv, q_lens):
     """64-row prefill tiles: pages one token short of, equal to and one beyond a block, a cache of a single token,
     none at all, one in several units; every group size; rows that fill the tile, a wave or a part of one."""
-    lens = {0: 63, 1: 64, 2: 65, 3: 1, 4: 5, 5: 129, 6: 700}
+    lens = {0: 63, 1: 64, 2: 65, 3: 1, 4: 5, 5: 190, 6: 700}
     case = Case(f"prefill-short-{Hq}", n_layers=2, Hq=Hq, Hkv=Hkv, D=128, hidden=64, dtype="bf16", chunk_lens=lens,
-                retrieved=[[0, 1, 2, 3, 4, 5], [6, 5], [], [3]], q_lens=q_lens, steps=1, scale=0.5)
+                retrieved=[[0, 1, 2, 5], [6, 4], [], [3]], q_lens=q_lens, steps=1, scale=0.5)
     form, units = _prefill_form(case)
     assert form == 64 and max(units) > 1 and units[2:] == [1, 1]
     _attention_parity(case)
