@@ -254,15 +254,18 @@ int choose_decode_units(const matkv_config& c, int batch, long inst_tokens) {
 // one workgroup per (unit, KV head, row tile), one workgroup per compute unit (its LDS); every extra
 // unit costs a partial per question row and a share of the fold launch.  So: as many units as
 // leave every workgroup a compute unit of its own and no more - one workgroup too many and the launch
-// takes twice as long - none shorter than 256 tokens (128-row tiles, whose workgroups take a
-// step of 128 tokens: 128).  The other kernels launch a workgroup per question row and want few units.
+// takes twice as long - none shorter than 256 tokens.  128-row tiles, whose workgroups take a
+// step of 128 tokens: 128, unless the batch alone nearly fills the chip (more than 85 workgroups uncut): then a cut in
+// two saves a step or two and costs the partials of many rows (8B shape, sixteen users of 300 tokens, us per layer
+// in two units -> uncut: questions of 32 rows 25.1 -> 15.9, of 16 rows 20.5 -> 14.2).  The other kernels launch a workgroup per question row and want few units.
 int choose_prefill_units(const matkv_config& cfg, long tiles_in_batch, long tile_rows, long tokens) {
     const int g = cfg.n_q_heads / cfg.n_kv_heads;
     const bool mfma = cfg.dtype == MATKV_BF16 && cfg.head_dim == 128 && group_size_built(g);
     long pu = tokens / 1024;
     if (mfma) {
         const long wgs_per_unit = std::max<long>(1, tiles_in_batch * cfg.n_kv_heads);
-        pu = std::min<long>(256 / wgs_per_unit, tokens / (tile_rows > 128 ? 256 : 128));
+        const long most = 256 / wgs_per_unit;
+        pu = std::min<long>(most, tokens / (tile_rows > 128 || most <= 2 ? 256 : 128));
     }
     return (int)std::max<long>(1, std::min<long>(pu, kMaxPrefillUnitsPerInstance));
 }

@@ -215,3 +215,18 @@ def test_prefill_layout_takes_short_tiles_for_short_questions(mk):
     for bad in (([[1000]], [0]), ([[0]], [4]), ([[1000]], [225])):
         with pytest.raises(mk.MatKVError):
             mk.plan_prefill(cfg, *bad)
+
+
+def test_prefill_layout_does_not_cut_short_caches_of_a_large_batch(mk):
+    """Host logic: a batch whose row tiles alone nearly fill the chip is cut only into units of 256 tokens and
+    more (a cut of a short cache costs more in partials than it saves); smaller batches into units of 128."""
+    def units(batch, lens, q, Hq=32):
+        cfg = mk.make_config(2, Hq, 8, 128, 4096, "bf16", 500000.0, batch, len(lens), 224)
+        return mk.plan_prefill(cfg, [lens] * batch, [q] * batch)[1]
+
+    for q in (1, 4, 16, 32):
+        assert units(16, [150, 150], q) == [1] * 16
+        assert units(12, [150, 150], q) == [1] * 12
+        assert units(16, [250, 250 + 32 - q], q) == [2] * 16    # two units of 256 and more
+        assert units(8, [150, 150], q) == [2] * 8
+    assert units(1, [150, 150], 32) == [2]

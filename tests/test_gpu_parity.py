@@ -433,6 +433,26 @@ def test_prefill_short_tiles_over_block_edges(Hq, Hkv, q_lens):
     _attention_parity(case)
 
 
+@pytest.mark.parametrize("q_len", [2, 32])
+def test_prefill_of_many_short_caches_uncut(q_len):
+    """Sixteen users with short caches: every cache one unit, outputs straight from the tiles (64 and 128 rows)."""
+    case = Case(f"prefill-many-{q_len}", n_layers=1, Hq=32, Hkv=8, D=128, hidden=64, dtype="bf16", chunk_lens={0: 150, 1: 130, 2: 60},
+                retrieved=[[0, 1], [2]] * 8, q_lens=[q_len, q_len // 2] * 8, steps=1, scale=0.5)
+    form, units = _prefill_form(case)
+    assert form == (64 if q_len * 4 <= 64 else 128) and units == [1] * 16
+    _attention_parity(case, instances=[0, 1, 7, 14, 15])
+
+
+@pytest.mark.parametrize("q_len", [2, 32])
+def test_prefill_of_many_short_caches_uncut(q_len):
+    """Sixteen users with short caches: every cache one unit, outputs straight from the tiles (64 and 128 rows)."""
+    case = Case(f"prefill-many-{q_len}", n_layers=1, Hq=32, Hkv=8, D=128, hidden=64, dtype="bf16", chunk_lens={0: 150, 1: 130, 2: 60},
+                retrieved=[[0, 1], [2]] * 8, q_lens=[q_len, q_len // 2] * 8, steps=1, scale=0.5)
+    form, units = _prefill_form(case)
+    assert form == (64 if q_len * 4 <= 64 else 128) and units == [1] * 16
+    _attention_parity(case, instances=[0, 1, 7, 14, 15])
+
+
 def test_attention_no_pages_and_full_tail():
     """Degenerate caches: an instance that retrieved nothing (plain causal attention over its
     own tokens) and a tail filled to its capacity."""
