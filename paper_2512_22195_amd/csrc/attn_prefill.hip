@@ -872,8 +872,7 @@ hipError_t launch_f(const AttnArgs& a, hipStream_t s) {
 
 bool attn_prefill_supported(const AttnArgs& a, int dtype) {
     const int g = a.Hq / a.Hkv;
-    return a.prefill && dtype == MATKV_BF16 && a.D == 128 && group_size_built(g) &&
-           a.max_unit_items <= kMaxPrefillItemsPerUnit;
+    return a.prefill && dtype == MATKV_BF16 && a.D == 128 && group_size_built(g) && a.row_tiles;
 }
 
 hipError_t launch_attn_prefill(const AttnArgs& a, int dtype, hipStream_t s) {

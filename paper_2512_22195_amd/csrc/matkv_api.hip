@@ -53,6 +53,7 @@ struct SlotState {
 // How the question prefill of a table is laid out.
 struct PrefillLayout {
     int tile_rows = 0;        // rows of a workgroup's tile: 64, 128 or 256
+    bool row_tiles = true;    // the prefill runs on the row-tile kernels (where the shape has them)
     int n_units = 0, max_units_inst = 0, max_unit_items = 0;    // units; most of any one instance, most items of any one unit
 };
 
@@ -412,6 +413,13 @@ PrefillLayout lay_out_prefill(const matkv_config& cfg, const matkv_page* pages, 
         };
         if (time(64) < 0.98 * time(L.tile_rows)) L.tile_rows = 64;
     }
+    // Units of more pieces than that (many pages, or short ones): the tile kernels take a piece, or two, a step however short it
+    // is, and the kernel whose waves walk the tokens separately is ahead of them only where their workgroups are few or
+    // mostly padding.  8B shape, us per layer on the tiles against the other kernel: twelve 64-row questions over 150
+    // pages of 40 tokens 184 against 425, over 100 of 4 tokens 154 against 170; one over 90 of 4 tokens (16 workgroups) 135
+    // against 55; 24 questions of 4 rows over 70 pages of 8 tokens 104 against 44.
+    const long workgroups = (long)L.n_units * cfg.n_kv_heads * ((most_rows + L.tile_rows - 1) / L.tile_rows);
+    L.row_tiles = L.max_unit_items <= kMaxPrefillItemsPerUnit || (most_rows > 64 && workgroups >= 96);
     return L;
 }
 
@@ -1455,7 +1463,7 @@ int32_t matkv_plan_prefill(const matkv_config* cfg, const int32_t* page_tokens, 
     const PrefillLayout L = lay_out_prefill(*cfg, pages.data(), n_pages, q_len, batch, format == MATKV_PAGE_E4M3, insts.data(), items.data(),
                                             &n_items, units.data(), [](int) { return (size_t)0; });
     if (units_out) for (int b = 0; b < batch; ++b) units_out[b] = insts[b].n_punits;
-    return row_tiles && L.max_unit_items <= kMaxPrefillItemsPerUnit ? L.tile_rows : 0;
+    return row_tiles && L.row_tiles ? L.tile_rows : 0;
     MATKV_CATCH_INT
 }
 
@@ -1571,7 +1579,7 @@ static matkv_status attn_args(matkv_ctx* c, const char* name, int prefill, int32
     a.n_units = prefill ? th->prefill.n_units : (a.shared ? th->n_sunits : th->n_dunits);
     a.max_units_inst = prefill ? th->prefill.max_units_inst : 0;
     a.batch = th->batch; a.total_q = th->total_q; a.kv_fmt = th->kv_fmt;
-    a.max_unit_items = prefill ? th->prefill.max_unit_items : 0;
+    a.row_tiles = th->prefill.row_tiles;
     a.tile_rows = th->prefill.tile_rows;
     a.scale_log2e = c->scale_log2e;
     a.out_f32 = c->cfg.dtype == MATKV_BF16 && c->cfg.out_f32;
@@ -1679,7 +1687,7 @@ matkv_status matkv_chunk_attn(matkv_ctx* c, int32_t layer, const void* q, const 
     a.Hq = cfg.n_q_heads; a.Hkv = cfg.n_kv_heads; a.D = cfg.head_dim;
     a.max_tail = n_tokens;
     a.prefill = 2; a.rows = n_tokens; a.n_units = 1; a.max_units_inst = 1;
-    a.batch = 1; a.total_q = n_tokens; a.max_unit_items = 1;
+    a.batch = 1; a.total_q = n_tokens; a.row_tiles = 1;
     // 256-row tiles once they give more workgroups than there are compute units, 128-row tiles (half the
     // longest walk) until then: 8B shape, 1000 tokens (128 workgroups of 256 rows) 35 against 24 us, 70B, 1000
     // (256) 38.7 against 33; 8B, 3501 tokens (440) 113 against 137

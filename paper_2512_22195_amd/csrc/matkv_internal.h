@@ -22,8 +22,8 @@ inline bool group_size_built(int g) { return g == 1 || g == 2 || g == 3 || g == 
 constexpr int kMaxDecodeUnitsPerInstance = 256;
 constexpr int kDecodeCounterStride = 32;         // ints: decode arrival counters sit 128 bytes apart
 constexpr int kMaxPrefillUnitsPerInstance = 32;
-// The row-tile prefill kernels take one piece, or two, per step: units of more pieces than this (pages of a
-// few tokens) go to the kernel whose waves walk the tokens separately.  (The 64-row form keeps so many in LDS.)
+// Items of a unit up to which the row-tile prefill kernels always run.  (The 64-row form keeps so many in LDS and
+// takes no more.)
 constexpr int kMaxPrefillItemsPerUnit = 64;
 
 struct Item {              // 32 bytes: a run of tokens inside one page, or the tail
@@ -171,7 +171,7 @@ struct AttnArgs {
     int32_t n_units;           // grid.x
     int32_t max_units_inst;    // most units any one instance is cut into
     int32_t batch, total_q;    // instances; rows of the packed Q / O tensors (prefill)
-    int32_t max_unit_items;    // most items in any one unit of this launch
+    int32_t row_tiles;         // prefill: on the row-tile kernels (where the shape has them)
     int32_t tile_rows;         // prefill: (question row, query head) rows per workgroup, 64, 128 or 256
     int32_t prefill;           // 0: decode units + whole tail; 1: prefill units + causal tail;
                                // 2: as 1 for a chunk's own attention (longest row tiles first)

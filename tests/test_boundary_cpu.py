@@ -230,3 +230,18 @@ def test_prefill_layout_does_not_cut_short_caches_of_a_large_batch(mk):
         assert units(16, [250, 250 + 32 - q], q) == [2] * 16    # two units of 256 and more
         assert units(8, [150, 150], q) == [2] * 8
     assert units(1, [150, 150], 32) == [2]
+
+
+def test_prefill_layout_over_many_pages(mk):
+    """Host logic: units of more than 64 pieces stay on the row-tile kernels where those have workgroups enough
+    and rows to fill them, and go to the other kernel otherwise."""
+    def form(batch, n, tokens, q, Hq=32, fmt=mk.PAGE_PLAIN):
+        cfg = mk.make_config(1, Hq, 8, 128, 4096, "bf16", 500000.0, batch, n, 224)
+        return mk.plan_prefill(cfg, [[tokens] * n] * batch, [q] * batch, fmt)[0]
+
+    for fmt in (mk.PAGE_PLAIN, mk.PAGE_E4M3):
+        assert form(12, 150, 40, 64, 32, fmt) in (128, 256)     # 75 or 150 pieces a unit, enough workgroups
+        assert form(3, 250, 64, 200, 24, fmt) in (128, 256)
+        assert form(1, 300, 1, 64, 32, fmt) == 0                # a few workgroups
+        assert form(24, 70, 8, 4, 32, fmt) == 0                 # tiles of mostly padding
+        assert form(24, 60, 8, 4, 32, fmt) != 0                 # up to 64 pieces: always tiles

@@ -453,6 +453,18 @@ def test_prefill_of_many_short_caches_uncut(q_len):
     _attention_parity(case, instances=[0, 1, 7, 14, 15])
 
 
+@pytest.mark.parametrize("compressed", [False, True])
+def test_prefill_units_of_many_pieces_on_tiles(compressed):
+    """Units of more than 64 pieces on the row-tile kernel, one with two and one without a ragged end; more pages than
+    a unit's item list once held."""
+    lens = {i: 9 + (7 * i) % 60 for i in range(150)}
+    case = Case("prefill-many-pieces", n_layers=1, Hq=32, Hkv=8, D=128, hidden=64, dtype="bf16", chunk_lens=lens,
+                retrieved=[list(range(150)), list(range(20, 150))] * 6, q_lens=[40, 33] * 6, steps=1, scale=0.5, compressed=compressed)
+    form, units = _prefill_form(case)
+    assert form in (128, 256) and max(units) <= 2              # 65 pieces a unit at the least
+    _attention_parity(case, instances=[0, 1, 11])
+
+
 def test_attention_no_pages_and_full_tail():
     """Degenerate caches: an instance that retrieved nothing (plain causal attention over its
     own tokens) and a tail filled to its capacity."""
