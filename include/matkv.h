@@ -263,6 +263,10 @@ matkv_status matkv_assemble(matkv_ctx* ctx, const matkv_page* pages_host,
 int32_t matkv_plan_decode_units(const matkv_config* cfg, const int32_t* page_tokens_host,
                                 int32_t n_pages, int32_t batch, int32_t q_len,
                                 int32_t* unit_tokens_out, int32_t* unit_items_out, int32_t cap);
+/* Host-only preview: the kernel that projects n_rows token rows (of a chunk, of a batch's questions or of its new
+ * tokens).  0: a row per workgroup, 1: matrix-vector products, 2: matrix cores for up to 16 rows, 3: matrix cores, the
+ * hidden axis split within a workgroup, 4: tiled matrix product; -1 on a bad argument. */
+int32_t matkv_plan_projection(const matkv_config* cfg, int32_t n_rows);
 /* Host-only preview of how matkv_assemble lays out a batch's question prefill (no GPU is touched).
  * page_tokens_host: [batch][max_pages], instance b has its first n_pages_host[b] chunk lengths; format: a
  * matkv_page_format.  units_out[batch] (may be NULL): units each instance's cache is cut into.  Returns the

@@ -219,10 +219,6 @@ __global__ __launch_bounds__(kWavesPerBlock * KS * 64) void materialize_gemv_ker
     }
 }
 
-bool gemv_supported(const MaterializeArgs& a, int dtype) {
-    return dtype == MATKV_BF16 && ((a.Hd % 4096) == 0 || (a.Hd % 3072) == 0);
-}
-
 template <int NL, int KS>
 hipError_t launch_gemv_nl(const MaterializeArgs& a, int total_rows, hipStream_t s) {
     const int n_tasks = 2 * a.Hkv * (a.D / 2);
@@ -264,21 +260,35 @@ hipError_t launch_rows(const MaterializeArgs& a, int total_rows, hipStream_t s) 
 
 }  // namespace
 
-hipError_t launch_materialize(const MaterializeArgs& a, int dtype, hipStream_t s) {
-    const int total_rows = a.n_tokens;
-    if (total_rows <= 0) return hipSuccess;
+ProjectionForm projection_form(int hidden, int Hkv, int D, int dtype, long rows) {
+    if (dtype != MATKV_BF16) return ProjectionForm::kRows;
     // up to 16 rows (a decode step): the staged form cut into 256 workgroups where it is ahead of the
     // GEMV form (per layer, every layer's weights from HBM: 4 rows at hidden 8192 10.9 -> 9.0 us,
     // 16 rows at hidden 4096 10.4 -> 7.9 us; one row at hidden 4096 5.8 us against 6.1: GEMV kept)
-    if ((total_rows >= 8 || a.Hd >= 8192) && materialize_fewrows_supported(a, dtype, total_rows))
-        return launch_materialize_fewrows(a, total_rows, s);
+    if ((rows >= 8 || hidden >= 8192) && rows <= 16 && D == 128 && hidden % 1024 == 0) return ProjectionForm::kFewRows;
     // the GEMV form reads the weights once per 4 rows: the matrix cores take over from 16 rows on (16
     // rows at hidden 4096 / 8192: 8.0 / 14.8 us against 9.7 / 20.7, 31 rows 8.0 / 13.5 against 16.1 / 33.6)
-    if (gemv_supported(a, dtype) && (total_rows < 16 || !materialize_mfma_supported(a, dtype, total_rows)))
-        return launch_gemv(a, total_rows, s);
-    if (materialize_mfma_supported(a, dtype, total_rows)) return launch_materialize_mfma(a, total_rows, s);
-    if (dtype == MATKV_F32) return launch_rows<float>(a, total_rows, s);
-    return launch_rows<uint16_t>(a, total_rows, s);
+    if (D != 128 || rows < 16) return hidden % 4096 == 0 || hidden % 3072 == 0 ? ProjectionForm::kGemv : ProjectionForm::kRows;
+    // The staged skinny form has eight workgroups per KV head and 32 rows.  While every one of them gets a
+    // compute unit of its own it is ahead of the tiles, one more and it is behind: hidden 4096, us staged against tiled,
+    // one KV head 448 rows 10.5 / 11.7, two 512 rows 10.9 / 12.4, four 256 rows 10.6 / 12.3 and 300 rows 17.6 / 12.4, eight
+    // 160 rows 18.1 / 12.1.  (One KV head: up to 512 rows; at 1024, 14.0 / 12.5.)  Up to 128 rows and eight KV heads or more it
+    // was taken before this line was drawn and still is.
+    if (hidden % 1024 == 0 && (rows <= 128 || (rows <= 512 && 8l * Hkv * ((rows + 31) / 32) <= 256))) return ProjectionForm::kStaged;
+    return ProjectionForm::kTiles;
+}
+
+hipError_t launch_materialize(const MaterializeArgs& a, int dtype, hipStream_t s) {
+    const int total_rows = a.n_tokens;
+    if (total_rows <= 0) return hipSuccess;
+    switch (projection_form(a.Hd, a.Hkv, a.D, dtype, total_rows)) {
+        case ProjectionForm::kFewRows: return launch_materialize_fewrows(a, total_rows, s);
+        case ProjectionForm::kGemv:    return launch_gemv(a, total_rows, s);
+        case ProjectionForm::kStaged:  return launch_materialize_staged(a, total_rows, s);
+        case ProjectionForm::kTiles:   return launch_materialize_tiles(a, total_rows, s);
+        case ProjectionForm::kRows:    break;
+    }
+    return dtype == MATKV_F32 ? launch_rows<float>(a, total_rows, s) : launch_rows<uint16_t>(a, total_rows, s);
 }
 
 // Plain streaming read (measurement aid): every workgroup sums one contiguous slice.

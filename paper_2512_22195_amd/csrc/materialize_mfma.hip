@@ -4,9 +4,10 @@
 // Both operands are contiguous along the contraction (hidden) axis, which is what the
 // matrix-core operand layout wants: a lane's 8 consecutive bf16 of one row.
 //
-// Three forms by row count: the tiled GEMM (below), a skinny form for up to 128 rows (a question) and
-// one for a handful (a decode step of a batch), whose eight waves split the hidden axis.  In all of them the two features of a rotary pair sit in the same lane, so the
-// rotation is lane-local on the fp32 accumulators, and values are rounded to bf16 once, on store.
+// Three forms by row count: the tiled GEMM (below), a skinny form for too few rows to fill the chip with tiles (a
+// question) and one for a handful (a decode step of a batch), whose eight waves split the hidden axis.  In all of
+// them the two features of a rotary pair sit in the same lane, so the rotation is lane-local on the fp32 accumulators,
+// and values are rounded to bf16 once, on store.
 #include <type_traits>
 
 #include "device_util.h"
@@ -343,7 +344,7 @@ hipError_t launch_tiled(const MaterializeArgs& a, int total_rows, hipStream_t s)
     }
 }
 
-// ---- skinny form: up to 128 token rows, hidden a multiple of 1024 ------------------------------
+// ---- skinny form: a few hundred token rows at most, hidden a multiple of 1024 ------------------
 // Too few rows for the tiled GEMM to fill the chip.  Here a workgroup owns 16 or 32 rows x 16 rotary
 // pairs (features 16g .. 16g+15 and their partners 64 further) of one head of K or of V, and its eight
 // waves split the HIDDEN axis.  Loading operands straight into matrix-core layout was bound by the
@@ -589,26 +590,15 @@ hipError_t launch_fewrows_t(const MaterializeArgs& a, int total_rows, hipStream_
 
 }  // namespace
 
-bool materialize_fewrows_supported(const MaterializeArgs& a, int dtype, int total_rows) {
-    return dtype == MATKV_BF16 && a.D == 128 && (a.Hd % 1024) == 0 && total_rows >= 1 && total_rows <= 16;
-}
 hipError_t launch_materialize_fewrows(const MaterializeArgs& a, int total_rows, hipStream_t s) {
     if (total_rows <= 4) return launch_fewrows_t<4>(a, total_rows, s);
     if (total_rows <= 8) return launch_fewrows_t<8>(a, total_rows, s);
     return launch_fewrows_t<16>(a, total_rows, s);
 }
 
-bool materialize_mfma_supported(const MaterializeArgs& a, int dtype, int total_rows) {
-    return dtype == MATKV_BF16 && a.D == 128 && (a.Hd % BK) == 0 && total_rows >= 16;
-}
+hipError_t launch_materialize_tiles(const MaterializeArgs& a, int total_rows, hipStream_t s) { return launch_tiled(a, total_rows, s); }
 
-// The staged skinny form (hidden a multiple of 1024) is ahead of the tiled GEMM up to 128 rows: us per
-// launch at hidden 4096 / 8192, weights from HBM: 64 rows 10.4 / 15.7 against 15.4 / 26, 128 rows
-// 12.6 / 19.6 against 17.0 / 29.6, 160 rows 20.5 / 31.8 against 17.0 / 29.4.
-constexpr int kStagedMaxRows = 128;
-
-hipError_t launch_materialize_mfma(const MaterializeArgs& a, int total_rows, hipStream_t s) {
-    if ((a.Hd % 1024) != 0 || total_rows > kStagedMaxRows) return launch_tiled(a, total_rows, s);
+hipError_t launch_materialize_staged(const MaterializeArgs& a, int total_rows, hipStream_t s) {
     // rows staged through LDS: 16-row tiles up to 64 rows (64 x 4 workgroups fill the chip),
     // 32-row tiles beyond (half the workgroups, the weights re-read half as often)
     const int rounds = a.Hd / 1024;             // per wave: an eighth of the hidden axis, 128 columns a round

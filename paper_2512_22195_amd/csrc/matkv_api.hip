@@ -1435,6 +1435,12 @@ int32_t matkv_plan_decode_units(const matkv_config* cfg, const int32_t* page_tok
     MATKV_CATCH_INT
 }
 
+int32_t matkv_plan_projection(const matkv_config* cfg, int32_t n_rows) {
+    const char* why;
+    if (check_config(cfg, &why) != MATKV_OK || n_rows < 1) return -1;
+    return (int32_t)projection_form(cfg->hidden, cfg->n_kv_heads, cfg->head_dim, cfg->dtype, n_rows);
+}
+
 int32_t matkv_plan_prefill(const matkv_config* cfg, const int32_t* page_tokens, const int32_t* n_pages, const int32_t* q_len,
                            int32_t batch, int32_t format, int32_t* units_out) {
     const char* why;

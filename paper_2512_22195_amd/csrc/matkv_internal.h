@@ -223,9 +223,11 @@ struct MaterializeArgs {
 };
 
 hipError_t launch_materialize(const MaterializeArgs& a, int dtype, hipStream_t s);
-bool materialize_mfma_supported(const MaterializeArgs& a, int dtype, int total_rows);
-hipError_t launch_materialize_mfma(const MaterializeArgs& a, int total_rows, hipStream_t s);
-bool materialize_fewrows_supported(const MaterializeArgs& a, int dtype, int total_rows);
+// Kernel that projects `rows` token rows (the values are what matkv_plan_projection returns).
+enum class ProjectionForm { kRows = 0, kGemv = 1, kFewRows = 2, kStaged = 3, kTiles = 4 };
+ProjectionForm projection_form(int hidden, int Hkv, int D, int dtype, long rows);
+hipError_t launch_materialize_tiles(const MaterializeArgs& a, int total_rows, hipStream_t s);
+hipError_t launch_materialize_staged(const MaterializeArgs& a, int total_rows, hipStream_t s);
 hipError_t launch_materialize_fewrows(const MaterializeArgs& a, int total_rows, hipStream_t s);
 bool decode_step_supported(const AttnArgs& a, const MaterializeArgs& m, int dtype);
 hipError_t launch_decode_step(const AttnArgs& a, const MaterializeArgs& m, int dtype, hipStream_t s);   // projection + attention

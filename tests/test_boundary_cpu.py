@@ -245,3 +245,23 @@ def test_prefill_layout_over_many_pages(mk):
         assert form(1, 300, 1, 64, 32, fmt) == 0                # a few workgroups
         assert form(24, 70, 8, 4, 32, fmt) == 0                 # tiles of mostly padding
         assert form(24, 60, 8, 4, 32, fmt) != 0                 # up to 64 pieces: always tiles
+
+
+def test_projection_forms(mk):
+    """Host logic: the split-axis form while its workgroups (eight per KV head and 32 rows) have a compute unit
+    each, tiles beyond; small row counts and other shapes on the forms for them."""
+    ROWS, GEMV, FEW, STAGED, TILES = range(5)
+
+    def form(rows, Hkv=8, hidden=4096, dtype="bf16", D=128):
+        return mk.plan_projection(mk.make_config(1, Hkv, Hkv, D, hidden, dtype, 10000.0, 1, 1, 64), rows)
+
+    for hidden in (1024, 3072, 4096, 8192):
+        for Hkv, last in ((1, 512), (2, 512), (4, 256), (6, 160), (8, 128), (16, 128)):
+            assert form(last, Hkv, hidden) == STAGED and form(17, Hkv, hidden) == STAGED
+            assert form(last + 1, Hkv, hidden) == TILES
+        assert form(4096, 8, hidden) == TILES and form(16, 8, hidden) == FEW
+    assert form(1) == GEMV and form(7) == GEMV and form(8) == FEW and form(1, hidden=8192) == FEW
+    assert form(15, hidden=4608) == ROWS and form(16, hidden=4608) == TILES and form(3, hidden=6144) == GEMV
+    assert form(100, dtype="f32", D=64, hidden=256) == ROWS and form(100, D=64, hidden=4096) == GEMV and form(100, D=64, hidden=512) == ROWS
+    with pytest.raises(mk.MatKVError):
+        form(0)

@@ -222,7 +222,9 @@ def test_materialize_hidden_sizes_bf16(hidden, T):
 
 @pytest.mark.parametrize("hidden,T,Hkv", [
     (64, 33, 2), (128, 200, 2), (192, 300, 2), (320, 129, 8), (512, 256, 8), (512, 257, 8), (512, 513, 8), (512, 769, 8), (512, 1025, 8),
-    (512, 1537, 8), (512, 2049, 8), (512, 3073, 8), (512, 4160, 8), (1024, 129, 8), (384, 700, 1), (448, 450, 3)])
+    (512, 1537, 8), (512, 2049, 8), (512, 3073, 8), (512, 4160, 8), (1024, 129, 8), (384, 700, 1), (448, 450, 3)] +
+    # narrow projections: the split-axis form up to 256 workgroups, tiles beyond
+    [(1024, 512, 1), (1024, 513, 1), (1024, 449, 2), (1024, 256, 4), (1024, 257, 4), (1024, 131, 6), (3072, 200, 4)])
 def test_materialize_tile_heights(hidden, T, Hkv):
     """Tiled projection: every tile height of both forms (two workgroups per tile: 32, 64, 96, 128
     rows; one: 96, 128, 192, 256) just past the row count where the one before ends, hidden axes of one
