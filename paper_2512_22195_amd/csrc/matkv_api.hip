@@ -258,15 +258,19 @@ int choose_decode_units(const matkv_config& c, int batch, long inst_tokens) {
 // takes twice as long - none shorter than 256 tokens.  128-row tiles, whose workgroups take a
 // step of 128 tokens: 128, unless the batch alone nearly fills the chip (more than 85 workgroups uncut): then a cut in
 // two saves a step or two and costs the partials of many rows (8B shape, sixteen users of 300 tokens, us per layer
-// in two units -> uncut: questions of 32 rows 25.1 -> 15.9, of 16 rows 20.5 -> 14.2).  The other kernels launch a workgroup per question row and want few units.
-int choose_prefill_units(const matkv_config& cfg, long tiles_in_batch, long tile_rows, long tokens) {
+// in two units -> uncut: questions of 32 rows 25.1 -> 15.9, of 16 rows 20.5 -> 14.2) - and unless short pages make the walk longer
+// than its tokens (a step takes two pieces at most: sixteen users over 120 pages of 4 tokens uncut 185, in two
+// units 105).  The other kernels launch a workgroup per question row and want few units.
+int choose_prefill_units(const matkv_config& cfg, long tiles_in_batch, long tile_rows, long tokens, long pieces) {
     const int g = cfg.n_q_heads / cfg.n_kv_heads;
     const bool mfma = cfg.dtype == MATKV_BF16 && cfg.head_dim == 128 && group_size_built(g);
     long pu = tokens / 1024;
     if (mfma) {
         const long wgs_per_unit = std::max<long>(1, tiles_in_batch * cfg.n_kv_heads);
         const long most = 256 / wgs_per_unit;
-        pu = std::min<long>(most, tokens / (tile_rows > 128 || most <= 2 ? 256 : 128));
+        pu = tokens / (tile_rows > 128 || most <= 2 ? 256 : 128);
+        if (tile_rows <= 128 && most <= 2) pu = std::max(pu, std::min(tokens / 128, pieces / 4));
+        pu = std::min(most, pu);
     }
     return (int)std::max<long>(1, std::min<long>(pu, kMaxPrefillUnitsPerInstance));
 }
@@ -277,9 +281,9 @@ int choose_prefill_units(const matkv_config& cfg, long tiles_in_batch, long tile
 // rows, us per layer at the 8B shape: one 64-row question over 10 000 tokens 28.9 against 33.2, two of them 46.8
 // against 49.3, four 76.5 against 73, one of 100 rows over 3000 tokens 23.3 against 28.4; 70B shape, one of
 // 128 rows over 10 000 tokens 68 against 66, four over 20 000 374 against 345.
-int choose_prefill_tile(const matkv_config& cfg, long tiles128, long tiles256, long most_tokens) {
+int choose_prefill_tile(const matkv_config& cfg, long tiles128, long tiles256, long most_tokens, long most_pieces) {
     auto cost = [&](long tiles, long rows) {
-        const long units = choose_prefill_units(cfg, tiles, rows, most_tokens), step = rows > 128 ? 64 : 128;
+        const long units = choose_prefill_units(cfg, tiles, rows, most_tokens, most_pieces), step = rows > 128 ? 64 : 128;
         const long rounds = (tiles * cfg.n_kv_heads * units + 255) / 256;
         const double steps = (double)(((most_tokens + units - 1) / units + step - 1) / step);
         return (double)rounds * (steps * (rows > 128 ? 1.9 : 2.2) + (units > 1 ? 3.0 * rows / 128 : 0.0));
@@ -375,24 +379,27 @@ PrefillLayout lay_out_prefill(const matkv_config& cfg, const matkv_page* pages, 
                               bool codes, InstanceInfo* insts, Item* items, int* n_items, Unit* units, ScalesOff scales_off) {
     PrefillLayout L;
     const int g = cfg.n_q_heads / cfg.n_kv_heads;
-    long most_tokens = 0, most_rows = 0;
+    long most_tokens = 0, most_rows = 0, most_pieces = 0;
     std::vector<long> tokens(batch);
     for (int b = 0; b < batch; ++b) {
         tokens[b] = q_len[b];
         for (int p = 0; p < n_pages[b]; ++p) tokens[b] += pages[(size_t)b * cfg.max_pages + p].n_tokens;
         most_tokens = std::max(most_tokens, tokens[b]);
+        most_pieces = std::max<long>(most_pieces, n_pages[b] + 1);
         most_rows = std::max(most_rows, (long)q_len[b] * g);
     }
+    // (short questions over many short pages are better off uncut, on the kernel for units of many pieces)
+    const bool cut_pieces = most_rows > 64;
     auto tiles = [&](long tile_rows) {                  // of (question row, query head of one KV head) over the batch
         long n = 0;
         for (int b = 0; b < batch; ++b) n += ((long)q_len[b] * g + tile_rows - 1) / tile_rows;
         return n;
     };
-    L.tile_rows = choose_prefill_tile(cfg, tiles(128), tiles(256), most_tokens);
+    L.tile_rows = choose_prefill_tile(cfg, tiles(128), tiles(256), most_tokens, cut_pieces ? most_pieces : 0);
     const long n_tiles = tiles(L.tile_rows);
     long walk_tokens = 0;
     for (int b = 0; b < batch; ++b) {
-        const int pu = choose_prefill_units(cfg, n_tiles, L.tile_rows, tokens[b]);
+        const int pu = choose_prefill_units(cfg, n_tiles, L.tile_rows, tokens[b], cut_pieces ? n_pages[b] + 1 : 0);
         insts[b].punit0 = L.n_units;
         insts[b].n_punits = build_units(pages ? pages + (size_t)b * cfg.max_pages : nullptr, n_pages[b], b, pu, q_len[b], cfg.max_tail_tokens,
                                         items, n_items, units, &L.n_units, scales_off);

@@ -230,6 +230,8 @@ def test_prefill_layout_does_not_cut_short_caches_of_a_large_batch(mk):
         assert units(16, [250, 250 + 32 - q], q) == [2] * 16    # two units of 256 and more
         assert units(8, [150, 150], q) == [2] * 8
     assert units(1, [150, 150], 32) == [2]
+    assert units(16, [4] * 120, 20) == [2] * 16                 # a walk of many short pieces is long all the same
+    assert units(16, [4] * 120, 16) == [1] * 16                 # (up to 64 rows another kernel takes it, uncut)
 
 
 def test_prefill_layout_over_many_pages(mk):
