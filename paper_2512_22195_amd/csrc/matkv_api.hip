@@ -297,7 +297,8 @@ int choose_prefill_tile(const matkv_config& cfg, long tiles128, long tiles256, l
 // cache, whichever is longer - near one another they add up, hence the fourth root; the reading takes longer where
 // the compute units hold unequal numbers of workgroups.  The constants are fitted to measurements at the 3B, 8B and
 // 70B layer shapes (1 to 24 instances of 64 to 20 000 tokens in 1 to 32 units, questions of up to 64 (row, head)
-// rows), which they give within 6.5 %.
+// rows), which they give within 6.5 %.  (A step of 128-row tiles over pieces that do not fill their blocks takes
+// longer, 2.6 to 3 us: it looks each of them up.)
 // walk_tokens, walk_pieces: of the longest unit; tile_mb: K and V bytes that the tiles read, in MB.
 double prefill_form_time(int tile_rows, long workgroups, long walk_tokens, long walk_pieces, double tile_mb) {
     const long blocks = std::max((walk_tokens + 63) / 64, walk_pieces), per_round = tile_rows == 64 ? 512 : 256;
@@ -305,7 +306,7 @@ double prefill_form_time(int tile_rows, long workgroups, long walk_tokens, long 
     double rounds = (double)((workgroups + per_round - 1) / per_round);
     if (tile_rows == 64) rounds = (rounds - 1) * 1.23 + ((workgroups - 1) % per_round >= 256 ? 1.23 : 1.0);
     const double start = tile_rows == 64 ? 5.28 : tile_rows == 128 ? 6.86 : 7.0;
-    const double step = tile_rows == 64 ? 1.22 : tile_rows == 128 ? 1.73 : 1.9;
+    const double step = tile_rows == 64 ? 1.22 : tile_rows == 128 ? (walk_pieces * 64 > walk_tokens + 63 ? 2.6 : 1.73) : 1.9;
     const double uneven = workgroups >= 96 ? (double)((workgroups + 255) / 256 * 256) / (double)workgroups : 256.0 / 96.0;
     const double walk = rounds * (double)steps * step, read = 0.17 * tile_mb * pow(uneven, 0.147);
     return start + pow(pow(walk, 4) + pow(read, 4), 0.25);
@@ -388,8 +389,8 @@ PrefillLayout lay_out_prefill(const matkv_config& cfg, const matkv_page* pages, 
         most_pieces = std::max<long>(most_pieces, n_pages[b] + 1);
         most_rows = std::max(most_rows, (long)q_len[b] * g);
     }
-    // (short questions over many short pages are better off uncut, on the kernel for units of many pieces)
-    const bool cut_pieces = most_rows > 64;
+    // (short questions over very many short pages are better off uncut, on the kernel for units of many pieces)
+    const bool cut_pieces = most_rows > 64 || most_pieces <= kMaxPrefillItemsPerUnit;
     auto tiles = [&](long tile_rows) {                  // of (question row, query head of one KV head) over the batch
         long n = 0;
         for (int b = 0; b < batch; ++b) n += ((long)q_len[b] * g + tile_rows - 1) / tile_rows;

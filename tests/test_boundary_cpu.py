@@ -206,7 +206,6 @@ def test_prefill_layout_takes_short_tiles_for_short_questions(mk):
     assert plan(4, [1000] * 3, 9, 64)[0] == 128 and plan(4, [1000] * 3, 22, 24)[0] == 128
     assert plan(24, [500] * 4, 1)[0] == 128                     # 192 long walks: the 128-row form is ahead
     assert plan(1, [], 5) == (64, [1])                          # no pages: the question alone
-    assert plan(1, [4] * 100, 1)[0] == 128                      # a step takes one piece of a few tokens, or two with 128 rows
     assert plan(1, [1] * 300, 1)[0] == 0                        # units of more than 64 pieces
     assert plan(1, [100], 4, dtype="f32", D=64)[0] == 0         # row-per-workgroup kernel
     # one long question among short ones
@@ -231,6 +230,7 @@ def test_prefill_layout_does_not_cut_short_caches_of_a_large_batch(mk):
         assert units(8, [150, 150], q) == [2] * 8
     assert units(1, [150, 150], 32) == [2]
     assert units(16, [4] * 120, 20) == [2] * 16                 # a walk of many short pieces is long all the same
+    assert units(16, [4] * 60, 16) == [2] * 16 and units(16, [16] * 30, 4) == [2] * 16
     assert units(16, [4] * 120, 16) == [1] * 16                 # (up to 64 rows another kernel takes it, uncut)
 
 
