@@ -364,6 +364,9 @@ matkv_status matkv_graph_begin(matkv_ctx* ctx);
 matkv_status matkv_graph_end(matkv_ctx* ctx, matkv_graph** out);
 matkv_status matkv_graph_launch(matkv_ctx* ctx, matkv_graph* g);
 matkv_status matkv_graph_destroy(matkv_ctx* ctx, matkv_graph* g);
+/* How a replay of the recording is issued: the number of kernel launches it is (a short chain of this library's own
+ * kernels), 0 if it is one graph launch, -1 on a null graph. */
+int32_t matkv_graph_kernel_launches(const matkv_graph* g);
 
 #ifdef __cplusplus
 }

@@ -27,7 +27,7 @@ EXPORTS = [
     "matkv_last_error", "matkv_materialize", "matkv_materialize_tail", "matkv_chunk_attn", "matkv_load", "matkv_load_file", "matkv_store_file",
     "matkv_wait", "matkv_query", "matkv_sync", "matkv_assemble", "matkv_advance",
     "matkv_prefill_attn", "matkv_decode_attn", "matkv_decode_step", "matkv_graph_begin", "matkv_graph_end",
-    "matkv_graph_launch", "matkv_graph_destroy", "matkv_plan_decode_units", "matkv_probe_read",
+    "matkv_graph_launch", "matkv_graph_destroy", "matkv_graph_kernel_launches", "matkv_plan_decode_units", "matkv_probe_read",
     "matkv_table_shared_units", "matkv_plan_projection", "matkv_plan_prefill",
     "matkv_plan_shared_units", "matkv_decode_attn_static",
 ]
@@ -117,6 +117,7 @@ def _load_library():
     lib.matkv_graph_end.argtypes = [c_void_p, POINTER(c_void_p)]; lib.matkv_graph_end.restype = c_int32
     lib.matkv_graph_launch.argtypes = [c_void_p, c_void_p]; lib.matkv_graph_launch.restype = c_int32
     lib.matkv_graph_destroy.argtypes = [c_void_p, c_void_p]; lib.matkv_graph_destroy.restype = c_int32
+    lib.matkv_graph_kernel_launches.argtypes = [c_void_p]; lib.matkv_graph_kernel_launches.restype = c_int32
     return lib
 
 
@@ -378,6 +379,10 @@ class Context:
 
     def graph_launch(self, g):
         self._check(_lib.matkv_graph_launch(self._h, g), "matkv_graph_launch")
+
+    def graph_kernel_launches(self, g) -> int:
+        """Kernel launches a replay is issued as; 0: one graph launch."""
+        return int(_lib.matkv_graph_kernel_launches(g))
 
     def graph_destroy(self, g):
         self._check(_lib.matkv_graph_destroy(self._h, g), "matkv_graph_destroy")

@@ -1,6 +1,7 @@
 // C-ABI of libmatkv: argument validation, host bookkeeping (tickets, slot states, cache
 // tables, captured graphs) and the enqueue of copies and kernels.  See include/matkv.h for
 // the contract of every entry point.
+#include <dlfcn.h>
 #include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
@@ -1744,31 +1745,38 @@ matkv_status matkv_probe_read(matkv_ctx* c, const void* src, size_t bytes) {
 // -------------------------------------------------------------------------------- graphs ----
 
 // A replay of a short recording is issued as its kernel launches instead of as a graph: between two
-// graph launches on one stream the device stands still for 8.3 us and the first kernel of the next graph
-// takes 4.5 instead of 0.7 us, between two kernels of a stream it waits for less than 0.1.  Per decode step, graph
-// -> launches: 8 layers over 10 000 tokens 146 -> 138.5 us, 8 layers of three short caches 102 -> 94, 4 layers of 16
-// users 251 -> 244.  A launch costs the host about 3 us (a graph of 9 kernels 18), and a kernel of these
-// recordings runs for 5 us at the least, so the host stays ahead of the device; from kChainMaxNodes
-// kernels on the saving is below 3 % of the replay and the graph's smaller host time is worth more.
-constexpr size_t kChainMaxNodes = 64;
+// graph launches on one stream the device stands still for about 8 us, between two kernels of a stream it waits for
+// less than 0.1 where the host is ahead.  A launch costs the host 2.7 us (a graph 15 and 0.5 a kernel), so the saving is
+// kept over any number of long kernels and eaten up by many short ones.  Us per replay, graph -> launches:
+//   projection and attention of bf16 models, hidden 3072 and more (8 us a kernel and up): one user of 64 tokens, 4 layers
+//   (5 kernels) 41.2 -> 33.4, 16 layers 135.3 -> 127.6, 60 layers 481.6 -> 473.5; sixteen of 1000, 31 layers (63) 816.6 -> 811.3
+//   fp32 and small hidden sizes (3 to 4 us a kernel): 4 layers (9) 44.9 -> 39.8, 8 layers (17) 79.6 -> 78.1, 16 layers (33)
+//   149.2 -> 153.9, 31 layers (63) 289 -> 298
+// so long kernels are launched up to kChainMaxNodes of them - the saving is 2 % of the replay there, 1.5 % of a step
+// through all layers of a 32-layer model, and an 80-layer one is a graph - and short ones up to kChainMaxShort.
+constexpr size_t kChainMaxNodes = 64, kChainMaxShort = 20;
 
-// The recording's kernel launches in order, if it is a single chain of at most kChainMaxNodes kernels that
-// are functions of this process's host code (a kernel loaded as a module has no such function); empty
-// otherwise.  The parameters belong to the graph's nodes and live as long as the graph.
-static std::vector<hipKernelNodeParams> kernel_chain(hipGraph_t graph) {
+// Whether a kernel is this library's own.  Launches of the caller's between them may carry attributes
+// (cooperative, priority) that a plain launch would drop, and may be short.
+static bool own_kernel(const void* func) {
+    Dl_info mine, other;
+    return dladdr(reinterpret_cast<const void*>(&matkv_graph_launch), &mine) && dladdr(func, &other) && mine.dli_fbase == other.dli_fbase;
+}
+
+// The recording's kernel launches in order, if it is a single chain of at most max_nodes kernels of this
+// library; empty otherwise.  The parameters belong to the graph's nodes and live as long as the graph.
+static std::vector<hipKernelNodeParams> kernel_chain(hipGraph_t graph, size_t max_nodes) {
     std::vector<hipKernelNodeParams> chain;
     size_t n = 0, roots = 0;
-    if (hipGraphGetNodes(graph, nullptr, &n) != hipSuccess || n == 0 || n > kChainMaxNodes) return {};
+    if (hipGraphGetNodes(graph, nullptr, &n) != hipSuccess || n == 0 || n > max_nodes) return {};
     if (hipGraphGetRootNodes(graph, nullptr, &roots) != hipSuccess || roots != 1) return {};
     hipGraphNode_t node = nullptr;
     if (hipGraphGetRootNodes(graph, &node, &roots) != hipSuccess) return {};
     while (true) {
         hipGraphNodeType type;
         hipKernelNodeParams p{};
-        hipFuncAttributes attr;
         if (hipGraphNodeGetType(node, &type) != hipSuccess || type != hipGraphNodeTypeKernel ||
-            hipGraphKernelNodeGetParams(node, &p) != hipSuccess || !p.func || !p.kernelParams || p.extra ||
-            hipFuncGetAttributes(&attr, p.func) != hipSuccess) {
+            hipGraphKernelNodeGetParams(node, &p) != hipSuccess || !p.func || !p.kernelParams || p.extra || !own_kernel(p.func)) {
             (void)hipGetLastError();                // (a query that failed is no error of the recording)
             return {};
         }
@@ -1809,7 +1817,8 @@ matkv_status matkv_graph_end(matkv_ctx* c, matkv_graph** out) {
         return hip_fail(c, e, "graph_end");
     }
     try {
-        g->chain = kernel_chain(g->graph);
+        const bool long_kernels = c->cfg.dtype == MATKV_BF16 && c->cfg.head_dim == 128 && c->cfg.hidden >= 3072;
+        g->chain = kernel_chain(g->graph, long_kernels ? kChainMaxNodes : kChainMaxShort);
         c->graphs.push_back(g);
     } catch (...) {
         (void)hipGraphExecDestroy(g->exec);
@@ -1858,6 +1867,8 @@ matkv_status matkv_graph_launch(matkv_ctx* c, matkv_graph* g) {
     HIP_TRY(c, hipGraphLaunch(g->exec, c->compute));
     return MATKV_OK;
 }
+
+int32_t matkv_graph_kernel_launches(const matkv_graph* g) { return g ? (int32_t)g->chain.size() : -1; }
 
 matkv_status matkv_graph_destroy(matkv_ctx* c, matkv_graph* g) {
     if (!c || !g) return MATKV_EINVAL;

@@ -513,12 +513,18 @@ def test_graph_replay_matches_eager():
     chain.compare_attention(case, g_pre, g_dec, pre, dec)
 
 
-@pytest.mark.parametrize("repeats,copy", [(1, False), (31, False), (32, False), (2, True)])
-def test_graph_replay_of_short_and_long_recordings(repeats, copy):
-    """Replays of a recording of one kernel more than an even number (3, 63: issued as kernels; 65: as a
-    graph) and of one that also holds a copy (a graph): each equals the eager calls, with eager work and
+@pytest.mark.parametrize("repeats,extra,hidden,launches", [
+    (1, None, 4096, 3), (31, None, 4096, 63), (32, None, 4096, 0),      # long kernels: up to 64 launches
+    (31, "advance", 4096, 64), (32, "advance", 4096, 0),                # (one kernel more)
+    (9, None, 1024, 19), (9, "advance", 1024, 20), (10, None, 1024, 0), # short kernels: up to 20
+    (2, "copy", 4096, 0),                                               # a copy of the caller's
+    (2, "kernel", 4096, 0),                                             # a kernel of the caller's
+])
+def test_graph_replay_of_short_and_long_recordings(repeats, extra, hidden, launches):
+    """Replays of recordings that are issued as kernel launches and of ones issued as a graph, at the limits
+    between them, and with work of the caller's in the recording: each equals the eager calls, with eager work and
     syncs in between."""
-    case = Case("graph-len", n_layers=1, Hq=8, Hkv=2, D=128, hidden=4096, dtype="bf16",
+    case = Case("graph-len", n_layers=1, Hq=8, Hkv=2, D=128, hidden=hidden, dtype="bf16",
                 chunk_lens={0: 200}, retrieved=[[0]], q_lens=[3], steps=8)
     ctx = chain.make_context(case)
     try:
@@ -531,15 +537,19 @@ def test_graph_replay_of_short_and_long_recordings(repeats, copy):
             slot, table = normal(2 * 2 * 200 * 128).view(torch.uint8), ctx.new_table()
             start = torch.zeros_like(ctx.new_tail())
             start[..., :3, :] = normal(*start[..., :3, :].shape)
-            x, w, q = normal(repeats, 1, 4096), normal(2, 256, 4096) / 64, normal(repeats, 1, 8, 128)
+            x, w, q = normal(repeats, 1, hidden), normal(2, 256, hidden) / 64, normal(repeats, 1, 8, 128)
 
             def step(tail, out, last):
                 ctx.advance(table, 1)
+                if extra == "advance":
+                    ctx.advance(table, 1)
                 for i in range(repeats):
                     ctx.materialize_tail(x[i], w[0], w[1], table, 1, tail[0, 0], tail[0, 1])
                     ctx.decode_attn(0, q[i], table, tail[0, 0], tail[0, 1], out[i])
-                if copy:
+                if extra == "copy":
                     last.copy_(out[-1])
+                if extra == "kernel":
+                    torch.mul(out[-1], 2.0, out=last)
 
             runs = []
             for recorded in (False, True):
@@ -550,7 +560,8 @@ def test_graph_replay_of_short_and_long_recordings(repeats, copy):
                     ctx.graph_begin()
                     step(tail, out, last)
                     g = ctx.graph_end()
-                for _ in range(4):
+                    assert ctx.graph_kernel_launches(g) == launches
+                for _ in range(4 if extra != "advance" else 2):
                     if recorded:
                         ctx.graph_launch(g)
                     else:
