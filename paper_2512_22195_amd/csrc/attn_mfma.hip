@@ -580,7 +580,7 @@ __global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && 
             if (!publish_unit<T, D, NW, NW, ROWS, ACCS>(a, cidx, unit.n_units_inst, sm_acc, sm_m, sm_l, &sm_last, G, map)) return;
             if (unit.n_units_inst <= 8)       merge_decode<G, NW, 8>(a, unit, kvh, wave, lane);
             else if (unit.n_units_inst <= 16) merge_decode<G, NW, 16>(a, unit, kvh, wave, lane);
-            else                              merge_decode<G, NW, 32>(a, unit, kvh, wave, lane);
+            else                              merge_decode<G, NW, (G + NW - 1) / NW <= 2 ? 32 : 16>(a, unit, kvh, wave, lane);   // (four rows x 32 units would not fit the registers)
             reset_counter(a, cidx);
         }
     } else {

@@ -325,6 +325,15 @@ def test_decode_kernel_variants(variant, Hq, Hkv):
     _attention_parity(case)
 
 
+@pytest.mark.parametrize("units", [8, 9, 16, 17, 32, 33])
+def test_decode_fold_of_four_rows_per_wave(units):
+    """Two waves and a group of eight: every wave folds four rows, in passes of 8 and 16 units (32 would not
+    fit the registers), at the edges of one and two passes."""
+    case = Case(f"attn-fold-{units}", n_layers=1, Hq=16, Hkv=2, D=128, hidden=64, dtype="bf16", chunk_lens={0: 400, 1: 260},
+                retrieved=[[0, 1], [0]], q_lens=[5, 3], steps=2, scale=1.0, decode_units=units, decode_variant=9022)
+    _attention_parity(case)
+
+
 def test_attention_baseline_distribution_auto_units():
     """The stated value distribution (N(0,1)/sqrt(128): near-uniform softmax) with the
     library's own choice of work units."""
