@@ -380,13 +380,14 @@ def test_prefill_group8_two_row_tiles():
 
 @pytest.mark.parametrize("compressed", [False, True])
 def test_prefill_many_small_pages_takes_the_other_kernel(compressed):
-    """More pages in one unit than the item list of the row-parallel prefill kernel holds
-    (64): the launch falls back to the token-parallel matrix-core kernel (plain and compressed
-    pages; every page has its own scales, and blocks never reach across two pages)."""
-    lens = {i: 3 + (i % 4) for i in range(90)}
+    """Units of more than 64 pieces and a question of few rows: the launch falls back to the token-parallel
+    matrix-core kernel (plain and compressed pages; every page has its own scales, and blocks never reach across
+    two pages)."""
+    lens = {i: 1 + (i % 2) for i in range(250)}
     case = Case("prefill-small-pages", n_layers=1, Hq=8, Hkv=2, D=128, hidden=64, dtype="bf16",
-                chunk_lens=lens, retrieved=[list(range(90))], q_lens=[9], steps=1, scale=0.5,
+                chunk_lens=lens, retrieved=[list(range(250))], q_lens=[9], steps=1, scale=0.5,
                 compressed=compressed)
+    assert _prefill_form(case)[0] == 0
     _attention_parity(case)
 
 
@@ -414,6 +415,7 @@ def test_prefill_tile_forms_over_block_edges(name, Hq, Hkv, batch, q_len, compre
     q_lens = [q_len] * (batch - 2) + [q_len // 2 + 1, 1]
     case = Case(f"prefill-{name}", n_layers=1, Hq=Hq, Hkv=Hkv, D=128, hidden=64, dtype="bf16", chunk_lens=lens, retrieved=retrieved,
                 q_lens=q_lens, steps=1, scale=0.5, compressed=compressed)
+    assert _prefill_form(case)[0] == int(name[4:])
     _attention_parity(case, instances=[0, batch - 2, batch - 1])
 
 
@@ -1118,11 +1120,13 @@ def test_chunk_prefill_attention(name, Hq, Hkv, D, dtype, lens, max_tail):
     print(f"{name}: worst abs err {worst:.3e}")
 
 
-def test_chunk_attention_table_follows_the_chunk_length_across_graph_replays():
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("bf16", 64), ("bf16", 128)])
+def test_chunk_attention_table_follows_the_chunk_length_across_graph_replays(dtype, D):
     """The one-instance table behind matkv_chunk_attn is rewritten only when the chunk length
     changes; a recorded chunk attention carries its own write, and a replay must not leave a
-    later eager call of another length with the replay's table."""
-    case = Case("chunk-graph", n_layers=1, Hq=8, Hkv=2, D=128, hidden=256, dtype="bf16",
+    later eager call of another length with the replay's table.  (fp32 and head_dim 64: the row kernel, which reads
+    the table; bf16 at head_dim 128: the tile kernel, which knows the chunk from its arguments.)"""
+    case = Case(f"chunk-graph-{dtype}-{D}", n_layers=1, Hq=8, Hkv=2, D=D, hidden=256, dtype=dtype, max_tail=152,
                 chunk_lens={0: 150, 1: 70}, retrieved=[[0]], q_lens=[1], steps=0, scale=1.0 / 4.0, q_scale=1.0)
     inp = chain.make_chain_inputs(case)
     q_chunk = chain.make_chunk_queries(case)
@@ -1188,6 +1192,11 @@ def test_chunk_attn_arguments_and_workspace_limit():
     (1000, 32, 8, None),                                       # config 2's chunk, every row
     (4096, 32, 8, [0, 1, 31, 32, 63, 64, 127, 128, 2047, 2048, 4000, 4095]),
     (1000, 64, 8, [0, 15, 16, 17, 500, 999]),                  # config 4's heads (group 8)
+    # 256-row tiles (more than 256 workgroups), ragged last tile and block: rows around the last tile's start, the last
+    # block's start and the end, for groups of 4, 8 and 3
+    (3501, 32, 8, [0, 63, 64, 1791, 3391, 3392, 3455, 3456, 3457, 3499, 3500]),
+    (1100, 64, 8, [0, 31, 32, 600, 1055, 1056, 1087, 1088, 1089, 1098, 1099]),
+    (2901, 24, 8, [0, 84, 85, 86, 1500, 2815, 2816, 2879, 2880, 2881, 2899, 2900]),
 ])
 def test_full_size_chunk_attention(L, Hq, Hkv, rows):
     """A chunk's own attention at the shapes bench.py times (Llama-3-8B / 70B heads, D 128):
