@@ -72,7 +72,45 @@ struct BlockDesc {
     float sk, sv;       // scales of a compressed page's codes
 };
 
-template <int RW, bool F8>
+// Inclusive sum over the lanes up to this one.
+__device__ __forceinline__ int wave_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);      // one, two, four, eight lanes to the right within 16
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);     // lane 15 of a row to the next, of the first and third
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);     // lane 31 to the upper half
+    return v;
+}
+
+// A launch has units x KV heads x the longest question's tiles workgroups, and a shorter question has no work for
+// the last of them.  Left where they fall, those idle ones lie between the others, and since workgroups go to the XCDs, and
+// there to the engines, in turn, some compute units are given two working ones while others have none (70B shape,
+// questions of 64, 50 and 21 rows over 12 900 tokens: 142 us per layer, 75 without them).  So the tiles beyond the first of every
+// unit are dealt to the workgroups behind the first ones without a gap, instance after instance.
+// k-th such tile -> instance, unit and tile; false: there is none.
+__device__ __forceinline__ bool find_further_tile(const InstanceInfo* __restrict__ insts, int batch, int k, int G, int rt, int& b, int& unit, int& tile) {
+    const int lane = threadIdx.x & 63;
+    for (int b0 = 0; b0 < batch; b0 += 64) {            // a lane per instance
+        const InstanceInfo* in = insts + min(b0 + lane, batch - 1);
+        const int further = (in->q_len * G - 1) / rt, unit0 = in->punit0;
+        const int n = b0 + lane < batch ? in->n_punits * further : 0, upto = wave_scan(n);
+        const uint64_t past = __builtin_amdgcn_ballot_w64(upto > k);
+        if (past) {
+            const int l = __builtin_ctzll(past), t = __builtin_amdgcn_readlane(further, l);
+            const int r = k - __builtin_amdgcn_readlane(upto - n, l);
+            b = b0 + l;
+            unit = r / t; tile = 1 + r - unit * t;
+            unit += __builtin_amdgcn_readlane(unit0, l);
+            return true;
+        }
+        k -= __builtin_amdgcn_readlane(upto, 63);
+    }
+    return false;
+}
+
+// DEAL: the tiles beyond the first are dealt out by find_further_tile.
+template <int RW, bool F8, bool DEAL>
 __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
         KernelArgs a, const InstanceInfo* __restrict__ insts, const Item* __restrict__ items,
         const Unit* __restrict__ units) {
@@ -91,8 +129,12 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     const int G = a.Hq / a.Hkv;                         // 1, 2, 3, 4 or 8
     auto div_g = [&](int m) { return (int)__umulhi((unsigned)m << 3, a.g_mul); };     // m / G, m < 2^28
     // a chunk's own attention: tile t walks (t + 1) * RT / G keys, so the longest go first
-    const int kvh = blockIdx.y, tile = a.prefill == 2 ? gridDim.z - 1 - blockIdx.z : blockIdx.z;
-    const int m0 = tile * RT;
+    int kvh = blockIdx.y, tile = a.prefill == 2 ? gridDim.z - 1 - blockIdx.z : blockIdx.z, unit_i = blockIdx.x, b = -1;
+    if (DEAL && blockIdx.z > 0) {
+        const int further = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * (blockIdx.z - 1)), k = further / a.Hkv;
+        if (!find_further_tile(insts, a.batch, k, G, RT, b, unit_i, tile)) return;
+        kvh = further - k * a.Hkv;
+    }
 
     Unit unit;
     InstanceInfo inst;
@@ -102,9 +144,10 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
         inst = InstanceInfo{};
         inst.q_len = a.rows;
     } else {
-        unit = table_record(units + blockIdx.x);
-        inst = table_record(insts + unit.inst);
+        unit = table_record(units + unit_i);
+        inst = table_record(insts + (DEAL && b >= 0 ? b : unit.inst));
     }
+    const int m0 = tile * RT;
     const int n_m = inst.q_len * G;
     if (m0 >= n_m) return;                              // whole workgroup leaves together
     const int r_last = div_g(min(m0 + RT, n_m) - 1);
@@ -544,7 +587,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
                 store_out4(a.out, a.out_f32, ((size_t)(inst.cu_q + r) * a.Hq + head) * D + 4 * c32,
                            make_float4(acc[j].x * inv, acc[j].y * inv, acc[j].z * inv, acc[j].w * inv));
             } else {
-                float* prow = a.partials + (((size_t)blockIdx.x * a.rows + r) * a.Hq + head) * kPartialStride(D);
+                float* prow = a.partials + (((size_t)unit_i * a.rows + r) * a.Hq + head) * kPartialStride(D);
                 *reinterpret_cast<float4*>(prow + 4 * c32) = acc[j];
                 if (c32 == 0) *reinterpret_cast<float2*>(prow + D) = make_float2(M[j], L[j]);
             }
@@ -851,7 +894,8 @@ hipError_t launch_f(const AttnArgs& a, hipStream_t s) {
     const KernelArgs k = make_kernel_args(a);
     const int tiles = (a.rows * (a.Hq / a.Hkv) + a.tile_rows - 1) / a.tile_rows;
     const dim3 grid(a.n_units, a.Hkv, tiles), block(a.tile_rows <= 64 ? 256 : NW * 64);      // (64: plain pages only)
-    auto kern = !F8 && a.tile_rows <= 64 ? attn_prefill_short_kernel : a.tile_rows <= 128 ? attn_prefill_kernel<4, F8> : attn_prefill_kernel<8, F8>;
+    auto kern = !F8 && a.tile_rows <= 64 ? attn_prefill_short_kernel : a.tile_rows <= 128 ? (a.deal_tiles ? attn_prefill_kernel<4, F8, true> : attn_prefill_kernel<4, F8, false>)
+                                     : (a.deal_tiles ? attn_prefill_kernel<8, F8, true> : attn_prefill_kernel<8, F8, false>);
     hipLaunchKernelGGL(kern, grid, block, 0, s, k,
                        reinterpret_cast<const InstanceInfo*>(a.table + a.off_inst),
                        reinterpret_cast<const Item*>(a.table + a.off_items),

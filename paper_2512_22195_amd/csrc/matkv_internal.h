@@ -173,6 +173,7 @@ struct AttnArgs {
     int32_t batch, total_q;    // instances; rows of the packed Q / O tensors (prefill)
     int32_t row_tiles;         // prefill: on the row-tile kernels (where the shape has them)
     int32_t tile_rows;         // prefill: (question row, query head) rows per workgroup, 64, 128 or 256
+    int32_t deal_tiles;        // prefill: workgroups without work are left to the end of the launch
     int32_t prefill;           // 0: decode units + whole tail; 1: prefill units + causal tail;
                                // 2: as 1 for a chunk's own attention (longest row tiles first)
     float scale_log2e;

@@ -446,6 +446,26 @@ def test_prefill_short_tiles_over_block_edges(Hq, Hkv, q_lens):
     _attention_parity(case)
 
 
+@pytest.mark.parametrize("compressed", [False, True], ids=["plain", "compressed"])
+@pytest.mark.parametrize("form,Hq,Hkv,retrieved,q_lens,instances", [
+    (128, 64, 8, [[0, 1], [2, 3], [4] * 11], [33, 17, 5], [0, 1, 2]),            # 3, 2 and 1 tiles, 5 units each: 240 workgroups, 360 with the idle
+    (128, 64, 8, [[0, 1], [4] * 11, [2, 3]], [5, 17, 33], [0, 1, 2]),            # the longest question last
+    (256, 64, 8, [[5, 5]] * 12, [85] * 4 + [60] * 4 + [40] * 4, [0, 3, 4, 11]),  # 224, 288 with the idle; one unit each
+    (128, 16, 8, [[6]] * 70, [100] + [20] * 67 + [65, 1], [0, 1, 63, 64, 68, 69]),   # more instances than a wave has lanes; several rounds
+], ids=["units", "longest-last", "tall", "many"])
+def test_prefill_questions_of_unequal_tiles(form, Hq, Hkv, retrieved, q_lens, instances, compressed):
+    """Row tiles beyond the first, dealt out without the idle ones of shorter questions: every tile of every
+    instance in every unit is computed, whatever the order of the lengths."""
+    lens = {0: 300, 1: 350, 2: 190, 3: 500, 4: 64, 5: 67, 6: 520}
+    case = Case("prefill-unequal", n_layers=1, Hq=Hq, Hkv=Hkv, D=128, hidden=64, dtype="bf16", chunk_lens=lens,
+                retrieved=retrieved, q_lens=q_lens, steps=1, scale=0.5, compressed=compressed)
+    got, units = _prefill_form(case)
+    tiles = [-(-q * (Hq // Hkv) // form) for q in q_lens]
+    live, every = sum(u * t for u, t in zip(units, tiles)) * Hkv, sum(units) * max(tiles) * Hkv
+    assert got == form and -(-every // 256) > -(-live // 256)
+    _attention_parity(case, instances=list(instances))
+
+
 @pytest.mark.parametrize("q_len", [2, 32])
 def test_prefill_of_many_short_caches_uncut(q_len):
     """Sixteen users with short caches: every cache one unit, outputs straight from the tiles (64 and 128 rows)."""
