@@ -596,13 +596,13 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
 }
 
 // ---- up to 64 (question row, query head) rows per KV head -------------------------------------
-// (Plain pages.)  A short question's launch is bound by fetching the cache, and the 128-row form above serves it
+// A short question's launch is bound by fetching the cache, and the 128-row form above serves it
 // badly: its waves compute 32 rows whether they are there or not, its first blocks are a quarter of a unit of a
 // few hundred tokens, and a compute unit holds one workgroup.  Here a workgroup of four waves owns 64 rows, 16 per
 // wave (16x16x32), all waves walk the same 64-token blocks out of double-buffered LDS tiles, and two workgroups
 // share a compute unit.  The next block's loads are in flight in registers meanwhile.  8B shape, one row,
 // us per layer with the fold, 128-row form -> this one: four over 3000 tokens 19.0 -> 17.0 (49 MB), one over 10 000
-// 18.0 -> 16.6 (41 MB).  Over compressed pages (half the bytes) it was no faster and is not built.
+// 18.0 -> 16.6 (41 MB); compressed pages: sixteen 70B users of 4 000 tokens 62.6 -> 55.8, twenty-three 8B users of 4 400 87 -> 73.
 //   S^T = K Q^T     A = K rows from the LDS tile, B = Q held in registers
 //   softmax         online, per lane on its own column; the four 16-lane groups agree on the maximum
 //   O^T += V^T P^T  A = V through the transposing LDS read, B = P rounded to bf16
@@ -610,6 +610,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
 // measured fastest (K 288 bytes 5.4 cycles per instruction against 8.8 at 272; V 304 bytes 6.2 against 6.7 at 288).
 constexpr int KSTR = D + 16, VSTR = D + 24;             // bf16 per LDS row of the K and of the V tile
 
+template <bool F8>
 __global__ __launch_bounds__(256, 2) void attn_prefill_short_kernel(
         KernelArgs a, const InstanceInfo* __restrict__ insts, const Item* __restrict__ items,
         const Unit* __restrict__ units) {
@@ -650,8 +651,15 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_short_kernel(
     __shared__ __attribute__((aligned(16))) uint16_t tiles[2 * TILE_ELEMS];
     // the unit's item list sits in LDS: a fetch inside the loop would also drain the block loads in flight
     __shared__ __attribute__((aligned(16))) Item sm_items[kMaxPrefillItemsPerUnit];
+    __shared__ float sm_scale[F8 ? kMaxPrefillItemsPerUnit : 1][2];      // K and V scale of every item
     for (int i = tid; i < unit.n_items * 2; i += NWV * 64)
         reinterpret_cast<uint4*>(sm_items)[i] = reinterpret_cast<const uint4*>(items + unit.item0)[i];
+    if (F8 && tid < unit.n_items) {
+        const Item it = items[unit.item0 + tid];
+        float sk = 1.f, sv = 1.f;
+        if (it.base) page_scales(it, a.layer, a.Hkv, kvh, sk, sv);
+        sm_scale[tid][0] = sk; sm_scale[tid][1] = sv;
+    }
     __syncthreads();
 
     // Every wave walks the same blocks: the unit's items end to end (the tail clipped to the rows this tile
@@ -673,13 +681,15 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_short_kernel(
         }
         r.is_tail = wk.item.base == 0;
         if (!r.is_tail) {
-            const size_t head = (size_t)wk.item.page_tokens * D;
+            const size_t head = (size_t)wk.item.page_tokens * (F8 ? D / 2 : D);     // in units of T
             r.k = reinterpret_cast<const T*>(wk.item.base) + ((size_t)a.layer * 2 * a.Hkv + kvh) * head;
             r.v = r.k + (size_t)a.Hkv * head;
+            if (F8) { r.sk = sm_scale[wk.item_i][0]; r.sv = sm_scale[wk.item_i][1]; }
         } else {
             const size_t off = ((size_t)unit.inst * a.Hkv + kvh) * (size_t)a.max_tail * D;
             r.k = reinterpret_cast<const T*>(a.tail_k) + off;
             r.v = reinterpret_cast<const T*>(a.tail_v) + off;
+            if (F8) { r.sk = 1.f; r.sv = 1.f; }
         }
         const int n = min(TB, wk.left);
         r.t0 = wk.item.tok0 + (wk.rows - wk.left);
@@ -695,6 +705,16 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_short_kernel(
     const int st_row = tid >> 4, st_col = (tid & 15) * 8;
     struct Stage { uint4 k[SR], v[SR]; };
     auto load_global = [&](const BlockRef<T>& r, Stage& g) {
+        if (F8 && !r.is_tail) {         // codes: the same number of loads, half as wide
+#pragma unroll
+            for (int i = 0; i < SR; ++i) {
+                const size_t off = (size_t)min(r.t0 + st_row + 4 * NWV * i, r.tok_end - 1) * D + st_col;
+                const uint2 kw = ldg8(reinterpret_cast<const uint8_t*>(r.k) + off), vw = ldg8(reinterpret_cast<const uint8_t*>(r.v) + off);
+                g.k[i] = make_uint4(kw.x, kw.y, 0u, 0u);
+                g.v[i] = make_uint4(vw.x, vw.y, 0u, 0u);
+            }
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < SR; ++i) {
             const size_t off = (size_t)min(r.t0 + st_row + 4 * NWV * i, r.tok_end - 1) * D + st_col;
@@ -702,17 +722,19 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_short_kernel(
             g.v[i] = ldg16(r.v + off);
         }
     };
-    auto store_lds = [&](int buf, const Stage& g) {
+    auto store_lds = [&](int buf, const Stage& g, bool codes) {
         uint16_t* kt = tiles + buf * TILE_ELEMS;
         uint16_t* vt = kt + TB * KSTR;
 #pragma unroll
         for (int i = 0; i < SR; ++i) {
-            *reinterpret_cast<uint4*>(kt + (st_row + 4 * NWV * i) * KSTR + st_col) = g.k[i];
-            *reinterpret_cast<uint4*>(vt + (st_row + 4 * NWV * i) * VSTR + st_col) = g.v[i];
+            *reinterpret_cast<uint4*>(kt + (st_row + 4 * NWV * i) * KSTR + st_col) =
+                F8 && codes ? e4m3x8_to_bf16x8(make_uint2(g.k[i].x, g.k[i].y)) : g.k[i];
+            *reinterpret_cast<uint4*>(vt + (st_row + 4 * NWV * i) * VSTR + st_col) =
+                F8 && codes ? e4m3x8_to_bf16x8(make_uint2(g.v[i].x, g.v[i].y)) : g.v[i];
         }
     };
 
-    // Scores, reference scores and masks as in the kernel above.
+    // Scores, reference scores, masks and the scales of compressed pages as in the kernel above.
     const float sc = a.scale_log2e;
     const float lazy_raw = kLazyLog2 / sc;
     auto compute = [&](const BlockRef<T>& r, int buf) {
@@ -721,7 +743,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_short_kernel(
         const uint16_t* vt = kt + TB * KSTR;
         bf16x8 ones;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) ones[i] = (__bf16)1.0f;
+        for (int i = 0; i < 8; ++i) ones[i] = (__bf16)(F8 ? 1.0f / r.sv : 1.0f);
         // S^T in 16-token quarters q: lane holds tokens t0 + 16 q + 4 g4 + i of its row
         f32x4 st[4];
 #pragma unroll
@@ -754,15 +776,17 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_short_kernel(
             for (int i = 0; i < 4; ++i) mx = fmaxf(mx, st[q][i]);
         mx = fmaxf(mx, lane_xor(mx, 16, lane));
         mx = fmaxf(mx, lane_xor(mx, 32, lane));
+        if (F8) mx = mx > 0.5f * kNegBig ? mx * r.sk : kNegBig;
+        const float scb = F8 ? sc * r.sk : sc;
         const float mn = mx > mrow + lazy_raw ? mx : mrow;
         const float alpha = fast_exp2((mrow - mn) * sc);
         mrow = mn;
-        const float nmc = mn > 0.5f * kNegBig ? -mn * sc : 0.f;
+        const float nmc = (mn > 0.5f * kNegBig ? -mn * sc : 0.f) + (F8 ? __builtin_amdgcn_frexp_expf(r.sv) - 1.0f : 0.f);
         bf16x8 pb[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) pb[h][i] = (__bf16)fast_exp2(fmaf(st[2 * h + i / 4][i % 4], sc, nmc));
+            for (int i = 0; i < 8; ++i) pb[h][i] = (__bf16)fast_exp2(fmaf(st[2 * h + i / 4][i % 4], scb, nmc));
         if (__builtin_amdgcn_ballot_w64(alpha != 1.0f)) {           // wave-uniform: some row's reference moved
             ol[0] *= alpha;
 #pragma unroll
@@ -794,7 +818,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_short_kernel(
     if (r0.valid) {
         Stage g;
         load_global(r0, g);
-        store_lds(0, g);
+        store_lds(0, g, !r0.is_tail);
         __builtin_amdgcn_s_waitcnt(0x0F70);             // vmcnt(0) only
         lds_barrier();
         int buf = 0;
@@ -802,7 +826,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_short_kernel(
             const BlockRef<T> r1 = next_block();
             load_global(r1, g);
             if (wave_live) compute(r0, buf);
-            store_lds(buf ^ 1, g);
+            store_lds(buf ^ 1, g, !r1.is_tail);
             lds_barrier();
             r0 = r1;
             buf ^= 1;
@@ -893,8 +917,8 @@ template <bool F8>
 hipError_t launch_f(const AttnArgs& a, hipStream_t s) {
     const KernelArgs k = make_kernel_args(a);
     const int tiles = (a.rows * (a.Hq / a.Hkv) + a.tile_rows - 1) / a.tile_rows;
-    const dim3 grid(a.n_units, a.Hkv, tiles), block(a.tile_rows <= 64 ? 256 : NW * 64);      // (64: plain pages only)
-    auto kern = !F8 && a.tile_rows <= 64 ? attn_prefill_short_kernel : a.tile_rows <= 128 ? (a.deal_tiles ? attn_prefill_kernel<4, F8, true> : attn_prefill_kernel<4, F8, false>)
+    const dim3 grid(a.n_units, a.Hkv, tiles), block(a.tile_rows <= 64 ? 256 : NW * 64);
+    auto kern = a.tile_rows <= 64 ? attn_prefill_short_kernel<F8> : a.tile_rows <= 128 ? (a.deal_tiles ? attn_prefill_kernel<4, F8, true> : attn_prefill_kernel<4, F8, false>)
                                      : (a.deal_tiles ? attn_prefill_kernel<8, F8, true> : attn_prefill_kernel<8, F8, false>);
     hipLaunchKernelGGL(kern, grid, block, 0, s, k,
                        reinterpret_cast<const InstanceInfo*>(a.table + a.off_inst),

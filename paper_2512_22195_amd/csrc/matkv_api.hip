@@ -293,24 +293,30 @@ int choose_prefill_tile(const matkv_config& cfg, long tiles128, long tiles256, l
     return cost(tiles128, 128) <= cost(tiles256, 256) ? 128 : 256;
 }
 
-// Estimated time (us) of one layer's row-tile prefill attention over plain pages without its fold: a start, then as
+// Estimated time (us) of one layer's row-tile prefill attention without its fold: a start, then as
 // many steps as the longest walk has (a step takes one block of 64 tokens, with 128-row tiles two, none across two
 // pieces; two 64-row workgroups share a compute unit and take 1.23 times as long) or the reading of the
 // cache, whichever is longer - near one another they add up, hence the fourth root; the reading takes longer where
 // the compute units hold unequal numbers of workgroups.  The constants are fitted to measurements at the 3B, 8B and
-// 70B layer shapes (1 to 24 instances of 64 to 20 000 tokens in 1 to 32 units, questions of up to 64 (row, head)
-// rows), which they give within 6.5 %.  (A step of 128-row tiles over pieces that do not fill their blocks takes
-// longer, 2.6 to 3 us: it looks each of them up.)
-// walk_tokens, walk_pieces: of the longest unit; tile_mb: K and V bytes that the tiles read, in MB.
-double prefill_form_time(int tile_rows, long workgroups, long walk_tokens, long walk_pieces, double tile_mb) {
+// 70B layer shapes (1 to 24 instances of 64 to 30 000 tokens in 1 to 32 units, questions of up to 64 (row, head)
+// rows), which they give within 6.5 % over plain pages and 10 % over compressed ones.  (A step of 128-row tiles over plain
+// pieces that do not fill their blocks takes longer, 2.6 to 3 us: it looks each of them up.)
+// walk_tokens, walk_pieces: of the longest unit (compressed pages: its blocks for its pieces); tile_mb: K and V bytes that the tiles read, in MB.
+double prefill_form_time(int tile_rows, bool codes, long workgroups, long walk_tokens, long walk_pieces, double tile_mb) {
     const long blocks = std::max((walk_tokens + 63) / 64, walk_pieces), per_round = tile_rows == 64 ? 512 : 256;
     const long steps = tile_rows == 128 ? (blocks + 1) / 2 : blocks;
     double rounds = (double)((workgroups + per_round - 1) / per_round);
     if (tile_rows == 64) rounds = (rounds - 1) * 1.23 + ((workgroups - 1) % per_round >= 256 ? 1.23 : 1.0);
-    const double start = tile_rows == 64 ? 5.28 : tile_rows == 128 ? 6.86 : 7.0;
-    const double step = tile_rows == 64 ? 1.22 : tile_rows == 128 ? (walk_pieces * 64 > walk_tokens + 63 ? 2.6 : 1.73) : 1.9;
+    double start = 7.0, step = 1.9, mb_time = 0.17;
+    if (tile_rows == 64) {
+        start = codes ? 5.8 : 5.28; step = codes ? 1.6 : 1.22;
+        if (codes) mb_time = 0.185;
+    } else if (tile_rows == 128) {
+        start = codes ? 5.8 : 6.86; step = codes ? 2.25 : walk_pieces * 64 > walk_tokens + 63 ? 2.6 : 1.73;
+        if (codes) mb_time = 0.32;
+    }
     const double uneven = workgroups >= 96 ? (double)((workgroups + 255) / 256 * 256) / (double)workgroups : 256.0 / 96.0;
-    const double walk = rounds * (double)steps * step, read = 0.17 * tile_mb * pow(uneven, 0.147);
+    const double walk = rounds * (double)steps * step, read = mb_time * tile_mb * pow(uneven, 0.147);
     return start + pow(pow(walk, 4) + pow(read, 4), 0.25);
 }
 
@@ -382,9 +388,10 @@ PrefillLayout lay_out_prefill(const matkv_config& cfg, const matkv_page* pages, 
                               bool codes, InstanceInfo* insts, Item* items, int* n_items, Unit* units, ScalesOff scales_off) {
     PrefillLayout L;
     const int g = cfg.n_q_heads / cfg.n_kv_heads;
-    long most_tokens = 0, most_rows = 0, most_pieces = 0;
+    long most_tokens = 0, most_rows = 0, most_pieces = 0, total_rows = 0;
     std::vector<long> tokens(batch);
     for (int b = 0; b < batch; ++b) {
+        total_rows += q_len[b];
         tokens[b] = q_len[b];
         for (int p = 0; p < n_pages[b]; ++p) tokens[b] += pages[(size_t)b * cfg.max_pages + p].n_tokens;
         most_tokens = std::max(most_tokens, tokens[b]);
@@ -400,28 +407,49 @@ PrefillLayout lay_out_prefill(const matkv_config& cfg, const matkv_page* pages, 
     };
     L.tile_rows = choose_prefill_tile(cfg, tiles(128), tiles(256), most_tokens, cut_pieces ? most_pieces : 0);
     const long n_tiles = tiles(L.tile_rows);
-    long walk_tokens = 0;
-    for (int b = 0; b < batch; ++b) {
-        const int pu = choose_prefill_units(cfg, n_tiles, L.tile_rows, tokens[b], cut_pieces ? n_pages[b] + 1 : 0);
-        insts[b].punit0 = L.n_units;
-        insts[b].n_punits = build_units(pages ? pages + (size_t)b * cfg.max_pages : nullptr, n_pages[b], b, pu, q_len[b], cfg.max_tail_tokens,
-                                        items, n_items, units, &L.n_units, scales_off);
-        L.max_units_inst = std::max(L.max_units_inst, insts[b].n_punits);
-        for (int u = insts[b].punit0; u < L.n_units; ++u) {
-            L.max_unit_items = std::max(L.max_unit_items, units[u].n_items);
-            walk_tokens = std::max(walk_tokens, (long)units[u].page_tokens + (units[u].has_tail ? q_len[b] : 0));
+    const int tall = L.tile_rows, items0 = *n_items;
+    long walk_tokens = 0, walk_blocks = 0;              // of the longest unit; blocks of 64 tokens, none across two items
+    auto cut = [&](auto units_of) {                     // units_of(b): units of instance b
+        *n_items = items0;
+        L.n_units = 0; L.max_units_inst = 0; L.max_unit_items = 0; walk_tokens = 0; walk_blocks = 0;
+        for (int b = 0; b < batch; ++b) {
+            insts[b].punit0 = L.n_units;
+            insts[b].n_punits = build_units(pages ? pages + (size_t)b * cfg.max_pages : nullptr, n_pages[b], b, units_of(b), q_len[b],
+                                            cfg.max_tail_tokens, items, n_items, units, &L.n_units, scales_off);
+            L.max_units_inst = std::max(L.max_units_inst, insts[b].n_punits);
+            for (int u = insts[b].punit0; u < L.n_units; ++u) {
+                L.max_unit_items = std::max(L.max_unit_items, units[u].n_items);
+                walk_tokens = std::max(walk_tokens, (long)units[u].page_tokens + (units[u].has_tail ? q_len[b] : 0));
+                long blocks = 0;
+                for (int i = units[u].item0; i < units[u].item0 + units[u].n_items; ++i)
+                    blocks += ((items[i].base ? items[i].ntok : std::min(items[i].ntok, q_len[b])) + 63) / 64;
+                walk_blocks = std::max(walk_blocks, blocks);
+            }
         }
-    }
-    // Questions of at most 64 (row, head) rows over plain pages: 64-row tiles over the same units where they are
-    // estimated to be faster by more than a tie.  8B shape, us per layer with 128-row tiles -> 64-row tiles: four 1-row questions over 3000
+    };
+    auto units_of = [&](int b) { return choose_prefill_units(cfg, n_tiles, tall, tokens[b], cut_pieces ? n_pages[b] + 1 : 0); };
+    cut(units_of);
+    // Questions of at most 64 (row, head) rows: 64-row tiles over the same units where they are estimated to be faster
+    // by more than a tie.  8B shape, us per layer with 128-row tiles -> 64-row tiles: four 1-row questions over 3000
     // tokens 19.0 -> 17.0, one over 10 000 18.0 -> 16.6, one 16-row question over 64 tokens 7.5 -> 6.6; not: 24 over 2000
     // tokens 39.9 -> 49.8.
-    if (!codes && most_rows <= 64 && L.max_unit_items <= kMaxPrefillItemsPerUnit) {
-        auto time = [&](int tile_rows) {
-            return prefill_form_time(tile_rows, (long)L.n_units * cfg.n_kv_heads, walk_tokens, L.max_unit_items,
-                                     (double)tiles(tile_rows) * cfg.n_kv_heads * (double)most_tokens * 512e-6);
+    if (cfg.dtype == MATKV_BF16 && cfg.head_dim == 128 && most_rows <= 64 && L.max_unit_items <= kMaxPrefillItemsPerUnit) {
+        const double mb = (double)batch * cfg.n_kv_heads * (double)most_tokens * (codes ? 256e-6 : 512e-6);
+        auto time = [&](int tile_rows) {                // (the fold included: units may differ)
+            const double fold = L.max_units_inst > 1 ? 2.2 + 3.2e-4 * (double)total_rows * cfg.n_q_heads * L.max_units_inst : 0.0;
+            return prefill_form_time(tile_rows, codes, (long)L.n_units * cfg.n_kv_heads, walk_tokens, codes ? walk_blocks : L.max_unit_items, mb) + fold;
         };
-        if (time(64) < 0.98 * time(L.tile_rows)) L.tile_rows = 64;
+        const double t128 = time(tall), t64 = time(64);
+        if (t64 < 0.98 * t128) L.tile_rows = 64;
+        // Two of them share a compute unit, so up to 512 of them are one round: more units, none below 96 tokens, where the
+        // estimate says so.  Compressed pages, us per layer with 128-row tiles -> 64-row tiles: twenty-three users of
+        // 4 400 tokens in 1 -> 2 units 87 -> 73 (8B), sixteen of 4 000 in 2 -> 4 62.6 -> 55.8 (70B).
+        const long most_units = std::min<long>(512 / std::max(1, batch * cfg.n_kv_heads), kMaxPrefillUnitsPerInstance);
+        if (std::min(most_units, most_tokens / 96) > L.max_units_inst) {
+            cut([&](int b) { return (int)std::max<long>(1, std::min(most_units, tokens[b] / 96)); });
+            if (L.max_unit_items <= kMaxPrefillItemsPerUnit && time(64) < 0.96 * (L.tile_rows == 64 ? t64 : t128)) L.tile_rows = 64;
+            else                                                                                             cut(units_of);
+        }
     }
     // A question of fewer tiles than the longest has no work for the last of them.  Those idle workgroups are moved to the
     // launch's end where they make one more round of 256: 70B shape, questions of 64, 50 and 21 rows over 12 900 tokens 140 -> 94 us

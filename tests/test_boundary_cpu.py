@@ -188,8 +188,8 @@ def test_shared_partition_covers_every_instance_once(mk):
 
 def test_prefill_layout_takes_short_tiles_for_short_questions(mk):
     """Host logic of the question prefill's layout: 64-row tiles only for questions of at most 64 (question row,
-    query head) rows over plain pages in units of at most 64 pieces, and there where the launch is a few short walks;
-    the units cover what the larger tiles' would."""
+    query head) rows in units of at most 64 pieces, and there where the launch is a few short walks or two workgroups
+    a compute unit shorten them."""
     def plan(batch, lens, q, Hq=32, fmt=mk.PAGE_PLAIN, dtype="bf16", D=128):
         cfg = mk.make_config(2, Hq, 8, D, 4096, dtype, 500000.0, batch, max(len(lens), 1), 224)
         return mk.plan_prefill(cfg, [lens] * batch, [q] * batch, fmt)
@@ -201,10 +201,12 @@ def test_prefill_layout_takes_short_tiles_for_short_questions(mk):
         assert (rows, units) == (64, [8] * 4), (Hq, q)
         rows, units = plan(1, [1000] * 10, q, Hq)
         assert (rows, units) == (64, [32]), (Hq, q)
-        assert plan(4, [1000] * 3, q, Hq, mk.PAGE_E4M3) == (128, [8] * 4)
     assert plan(4, [1000] * 3, 17)[0] == 128 and plan(4, [1000] * 3, 16)[0] == 64      # 68 and 64 rows
     assert plan(4, [1000] * 3, 9, 64)[0] == 128 and plan(4, [1000] * 3, 22, 24)[0] == 128
-    assert plan(24, [500] * 4, 1)[0] == 128                     # 192 long walks: the 128-row form is ahead
+    # many long walks of compressed pages: one unit each would leave compute units idle, two are one round of 64-row tiles
+    assert plan(23, [735] * 6, 4, 32, mk.PAGE_E4M3) == (64, [2] * 23)
+    assert plan(16, [270] * 15, 8, 64, mk.PAGE_E4M3) == (64, [4] * 16)
+    assert plan(1, [1000], 64, 32, mk.PAGE_E4M3)[0] > 64 and plan(4, [1000] * 3, 17, 32, mk.PAGE_E4M3)[0] > 64
     assert plan(1, [], 5) == (64, [1])                          # no pages: the question alone
     assert plan(1, [1] * 300, 1)[0] == 0                        # units of more than 64 pieces
     assert plan(1, [100], 4, dtype="f32", D=64)[0] == 0         # row-per-workgroup kernel
@@ -227,10 +229,10 @@ def test_prefill_layout_does_not_cut_short_caches_of_a_large_batch(mk):
         assert units(16, [150, 150], q) == [1] * 16
         assert units(12, [150, 150], q) == [1] * 12
         assert units(16, [250, 250 + 32 - q], q) == [2] * 16    # two units of 256 and more
-        assert units(8, [150, 150], q) == [2] * 8
+        assert units(8, [150, 150], q) == [2 if q > 4 else 3] * 8       # (64-row tiles, two a compute unit: down to 96)
     assert units(1, [150, 150], 32) == [2]
     assert units(16, [4] * 120, 20) == [2] * 16                 # a walk of many short pieces is long all the same
-    assert units(16, [4] * 60, 16) == [2] * 16 and units(16, [16] * 30, 4) == [2] * 16
+    assert units(16, [4] * 60, 16) == [2] * 16 and units(16, [16] * 30, 4) == [4] * 16
     assert units(16, [4] * 120, 16) == [1] * 16                 # (up to 64 rows another kernel takes it, uncut)
 
 

@@ -428,6 +428,7 @@ def _prefill_form(case):
                            mk.PAGE_E4M3 if case.compressed else mk.PAGE_PLAIN)
 
 
+@pytest.mark.parametrize("compressed", [False, True], ids=["plain", "compressed"])
 @pytest.mark.parametrize("Hq,Hkv,q_lens", [
     (4, 4, [64, 1, 15, 16]),         # rows 64, 1, 15, 16: the tile full, one row, a wave short of and exactly one block of rows
     (8, 4, [32, 9, 8, 17]),
@@ -435,15 +436,18 @@ def _prefill_form(case):
     (16, 4, [16, 1, 5, 4]),
     (32, 4, [8, 7, 1, 2]),
 ])
-def test_prefill_short_tiles_over_block_edges(Hq, Hkv, q_lens):
+def test_prefill_short_tiles_over_block_edges(Hq, Hkv, q_lens, compressed):
     """64-row prefill tiles: pages one token short of, equal to and one beyond a block, a cache of a single token,
-    none at all, one in several units; every group size; rows that fill the tile, a wave or a part of one."""
+    none at all, one in several units; every group size; rows that fill the tile, a wave or a part of one.
+    (Compressed pages take them in launches of many workgroups only: further users of one row each.)"""
     lens = {0: 63, 1: 64, 2: 65, 3: 1, 4: 5, 5: 190, 6: 700}
+    more = 36 if compressed else 0
     case = Case(f"prefill-short-{Hq}", n_layers=2, Hq=Hq, Hkv=Hkv, D=128, hidden=64, dtype="bf16", chunk_lens=lens,
-                retrieved=[[0, 1, 2, 5], [6, 4], [], [3]], q_lens=q_lens, steps=1, scale=0.5)
+                retrieved=[[0, 1, 2, 5], [6, 4], [], [3]] + [[6, 5]] * more, q_lens=q_lens + [1] * more, steps=1, scale=0.5,
+                compressed=compressed)
     form, units = _prefill_form(case)
-    assert form == 64 and max(units) > 1 and units[2:] == [1, 1]
-    _attention_parity(case)
+    assert form == 64 and max(units) > 1 and units[2:4] == [1, 1]
+    _attention_parity(case, instances=range(4))
 
 
 @pytest.mark.parametrize("compressed", [False, True], ids=["plain", "compressed"])
