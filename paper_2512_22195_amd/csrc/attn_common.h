@@ -62,7 +62,7 @@ struct KernelArgs {
     const void* tail_v;
     float* __restrict__ partials;
     int32_t* __restrict__ counters;
-    int32_t layer, Hq, Hkv, max_tail, rows, prefill, batch;
+    int32_t layer, Hq, Hkv, max_tail, rows, prefill;
     int32_t cstride;             // ints between two arrival counters
     int32_t out_f32;             // bf16 path: outputs leave as float, unrounded
     float scale_log2e;
@@ -94,8 +94,7 @@ inline KernelArgs make_kernel_args(const AttnArgs& a) {
     k.q = a.q; k.out = a.out; k.tail_k = a.tail_k; k.tail_v = a.tail_v;
     k.partials = a.partials; k.counters = a.counters;
     k.layer = a.layer; k.Hq = a.Hq; k.Hkv = a.Hkv; k.max_tail = a.max_tail; k.rows = a.rows;
-    k.prefill = a.prefill; k.batch = a.batch;
-    k.scale_log2e = a.scale_log2e;
+    k.prefill = a.prefill; k.scale_log2e = a.scale_log2e;
     k.cstride = a.prefill ? 1 : kDecodeCounterStride;
     k.out_f32 = a.out_f32;
     const uint32_t g = (uint32_t)(a.Hq / a.Hkv);

@@ -109,11 +109,13 @@ __device__ __forceinline__ bool find_further_tile(const InstanceInfo* __restrict
     return false;
 }
 
-// DEAL: the tiles beyond the first are dealt out by find_further_tile.
-template <int RW, bool F8, bool DEAL>
+// batch: given where the tiles beyond the first are dealt out by find_further_tile, and left out elsewhere: one
+// argument more moves the implicit ones into another line of the argument buffer, which costs every launch 0.3 us.
+template <int RW, bool F8, typename... Batch>
 __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
         KernelArgs a, const InstanceInfo* __restrict__ insts, const Item* __restrict__ items,
-        const Unit* __restrict__ units) {
+        const Unit* __restrict__ units, Batch... batch) {
+    constexpr bool DEAL = sizeof...(Batch) > 0;
     constexpr int TS = NW / RW;                         // token groups
     constexpr int RT = RW * WR;                         // rows per workgroup
     constexpr int TILE = TB * D * 2;                    // bytes of a K or a V tile
@@ -130,10 +132,12 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     auto div_g = [&](int m) { return (int)__umulhi((unsigned)m << 3, a.g_mul); };     // m / G, m < 2^28
     // a chunk's own attention: tile t walks (t + 1) * RT / G keys, so the longest go first
     int kvh = blockIdx.y, tile = a.prefill == 2 ? gridDim.z - 1 - blockIdx.z : blockIdx.z, unit_i = blockIdx.x, b = -1;
-    if (DEAL && blockIdx.z > 0) {
-        const int further = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * (blockIdx.z - 1)), k = further / a.Hkv;
-        if (!find_further_tile(insts, a.batch, k, G, RT, b, unit_i, tile)) return;
-        kvh = further - k * a.Hkv;
+    if constexpr (DEAL) {
+        if (blockIdx.z > 0) {
+            const int further = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * (blockIdx.z - 1)), k = further / a.Hkv;
+            if (!find_further_tile(insts, batch..., k, G, RT, b, unit_i, tile)) return;
+            kvh = further - k * a.Hkv;
+        }
     }
 
     Unit unit;
@@ -918,17 +922,20 @@ hipError_t launch_f(const AttnArgs& a, hipStream_t s) {
     const KernelArgs k = make_kernel_args(a);
     const int tiles = (a.rows * (a.Hq / a.Hkv) + a.tile_rows - 1) / a.tile_rows;
     const dim3 grid(a.n_units, a.Hkv, tiles), block(a.tile_rows <= 64 ? 256 : NW * 64);
-    auto kern = a.tile_rows <= 64 ? attn_prefill_short_kernel<F8> : a.tile_rows <= 128 ? (a.deal_tiles ? attn_prefill_kernel<4, F8, true> : attn_prefill_kernel<4, F8, false>)
-                                     : (a.deal_tiles ? attn_prefill_kernel<8, F8, true> : attn_prefill_kernel<8, F8, false>);
-    hipLaunchKernelGGL(kern, grid, block, 0, s, k,
-                       reinterpret_cast<const InstanceInfo*>(a.table + a.off_inst),
-                       reinterpret_cast<const Item*>(a.table + a.off_items),
-                       reinterpret_cast<const Unit*>(a.table + a.off_units));
+    const InstanceInfo* insts = reinterpret_cast<const InstanceInfo*>(a.table + a.off_inst);
+    const Item* items = reinterpret_cast<const Item*>(a.table + a.off_items);
+    const Unit* units = reinterpret_cast<const Unit*>(a.table + a.off_units);
+    if (a.tile_rows <= 64)       hipLaunchKernelGGL(attn_prefill_short_kernel<F8>, grid, block, 0, s, k, insts, items, units);
+    else if (a.deal_tiles) {
+        if (a.tile_rows <= 128)  hipLaunchKernelGGL((attn_prefill_kernel<4, F8, int>), grid, block, 0, s, k, insts, items, units, a.batch);
+        else                     hipLaunchKernelGGL((attn_prefill_kernel<8, F8, int>), grid, block, 0, s, k, insts, items, units, a.batch);
+    }
+    else if (a.tile_rows <= 128) hipLaunchKernelGGL((attn_prefill_kernel<4, F8>), grid, block, 0, s, k, insts, items, units);
+    else                         hipLaunchKernelGGL((attn_prefill_kernel<8, F8>), grid, block, 0, s, k, insts, items, units);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.max_units_inst <= 1) return e;
     const int total_pairs = a.total_q * a.Hq;
     const dim3 mgrid((total_pairs + 7) / 8), mblock(256);
-    const InstanceInfo* insts = reinterpret_cast<const InstanceInfo*>(a.table + a.off_inst);
     if (a.max_units_inst <= 2)      hipLaunchKernelGGL(prefill_merge_kernel<2>, mgrid, mblock, 0, s, k, insts, a.batch, total_pairs);
     else if (a.max_units_inst <= 4) hipLaunchKernelGGL(prefill_merge_kernel<4>, mgrid, mblock, 0, s, k, insts, a.batch, total_pairs);
     else if (a.max_units_inst <= 8) hipLaunchKernelGGL(prefill_merge_kernel<8>, mgrid, mblock, 0, s, k, insts, a.batch, total_pairs);
