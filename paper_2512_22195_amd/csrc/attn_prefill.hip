@@ -599,7 +599,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     }
 }
 
-// ---- up to 64 (question row, query head) rows per KV head -------------------------------------
+// ---- questions of up to 64 (question row, query head) rows per KV head, chunks of up to 512 tokens ----
 // A short question's launch is bound by fetching the cache, and the 128-row form above serves it
 // badly: its waves compute 32 rows whether they are there or not, its first blocks are a quarter of a unit of a
 // few hundred tokens, and a compute unit holds one workgroup.  Here a workgroup of four waves owns 64 rows, 16 per
@@ -607,6 +607,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
 // share a compute unit.  The next block's loads are in flight in registers meanwhile.  8B shape, one row,
 // us per layer with the fold, 128-row form -> this one: four over 3000 tokens 19.0 -> 17.0 (49 MB), one over 10 000
 // 18.0 -> 16.6 (41 MB); compressed pages: sixteen 70B users of 4 000 tokens 62.6 -> 55.8, twenty-three 8B users of 4 400 87 -> 73.
+// A short chunk's own attention walks few blocks, and the four waves start sooner than eight: 64 tokens 8.0 -> 4.9.
 //   S^T = K Q^T     A = K rows from the LDS tile, B = Q held in registers
 //   softmax         online, per lane on its own column; the four 16-lane groups agree on the maximum
 //   O^T += V^T P^T  A = V through the transposing LDS read, B = P rounded to bf16
@@ -628,10 +629,22 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_short_kernel(
     const int c16 = lane & 15, g4 = lane >> 4;
     const int G = a.Hq / a.Hkv;
     auto div_g = [&](int m) { return (int)__umulhi((unsigned)m << 3, a.g_mul); };
-    const int kvh = blockIdx.y, m0 = blockIdx.z * RT;
+    const int kvh = blockIdx.y;
 
-    const Unit unit = table_record(units + blockIdx.x);
-    const InstanceInfo inst = table_record(insts + unit.inst);
+    Unit unit;
+    InstanceInfo inst;
+    int tile = blockIdx.z;
+    if (a.prefill == 2) {                               // the chunk, as above; the longest tiles go first
+        unit = Unit{};
+        unit.n_items = 1; unit.n_units_inst = 1; unit.has_tail = 1; unit.first.ntok = a.rows;
+        inst = InstanceInfo{};
+        inst.q_len = a.rows;
+        tile = (a.rows * G - 1) / RT - tile;
+    } else {
+        unit = table_record(units + blockIdx.x);
+        inst = table_record(insts + unit.inst);
+    }
+    const int m0 = tile * RT;
     const int n_m = inst.q_len * G;
     if (m0 >= n_m) return;                              // whole workgroup leaves together
     const bool wave_live = m0 + 16 * wave < n_m;        // this wave has at least one real row
@@ -656,8 +669,9 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_short_kernel(
     // the unit's item list sits in LDS: a fetch inside the loop would also drain the block loads in flight
     __shared__ __attribute__((aligned(16))) Item sm_items[kMaxPrefillItemsPerUnit];
     __shared__ float sm_scale[F8 ? kMaxPrefillItemsPerUnit : 1][2];      // K and V scale of every item
-    for (int i = tid; i < unit.n_items * 2; i += NWV * 64)
-        reinterpret_cast<uint4*>(sm_items)[i] = reinterpret_cast<const uint4*>(items + unit.item0)[i];
+    if (a.prefill != 2)
+        for (int i = tid; i < unit.n_items * 2; i += NWV * 64)
+            reinterpret_cast<uint4*>(sm_items)[i] = reinterpret_cast<const uint4*>(items + unit.item0)[i];
     if (F8 && tid < unit.n_items) {
         const Item it = items[unit.item0 + tid];
         float sk = 1.f, sv = 1.f;

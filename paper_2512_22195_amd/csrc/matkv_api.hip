@@ -1744,11 +1744,15 @@ matkv_status matkv_chunk_attn(matkv_ctx* c, int32_t layer, const void* q, const 
     a.max_tail = n_tokens;
     a.prefill = 2; a.rows = n_tokens; a.n_units = 1; a.max_units_inst = 1;
     a.batch = 1; a.total_q = n_tokens; a.row_tiles = 1;
-    // 256-row tiles once they give more workgroups than there are compute units, 128-row tiles (half the
-    // longest walk) until then: 8B shape, 1000 tokens (128 workgroups of 256 rows) 35 against 24 us, 70B, 1000
-    // (256) 38.7 against 33; 8B, 3501 tokens (440) 113 against 137
+    // 64-row tiles for chunks of up to 512 tokens while all of their workgroups are on the chip at once (two share a
+    // compute unit): the longest walk is at most 8 blocks and a launch's start is shorter.  us, 128-row tiles -> 64-row: 64 tokens
+    // 8.0 -> 4.9 at every shape, 256 tokens 11.2 -> 8.9 (8B) and 11.8 -> 9.4 (70B), 512 tokens 15.5 -> 14.6 and 17.0 -> 16.1
+    // (70B, 512 workgroups; 16.9 in a second run); 600 tokens 16.7 -> 17.7 (8B).  Then 128-row tiles, and 256-row tiles (twice the longest walk) once
+    // they give more workgroups than there are compute units: 8B shape, 1000 tokens (128 workgroups of 256 rows) 35 against
+    // 24 us, 70B, 1000 (256) 38.7 against 33; 8B, 3501 tokens (440) 113 against 137
     const long chunk_rows = (long)n_tokens * (cfg.n_q_heads / cfg.n_kv_heads);
-    a.tile_rows = (chunk_rows + 255) / 256 * cfg.n_kv_heads <= 256 ? 128 : 256;
+    auto workgroups = [&](long rows) { return (chunk_rows + rows - 1) / rows * cfg.n_kv_heads; };
+    a.tile_rows = n_tokens <= 512 && workgroups(64) <= 512 ? 64 : workgroups(256) <= 256 ? 128 : 256;
     a.scale_log2e = c->scale_log2e;
     a.out_f32 = cfg.dtype == MATKV_BF16 && cfg.out_f32;
     const bool tiles = attn_prefill_supported(a, cfg.dtype);

@@ -1127,6 +1127,10 @@ def test_attention_refuses_a_table_whose_slot_is_being_reloaded():
     ("chunk-g1", 2, 2, 128, "bf16", [130], None),
     ("chunk-g2", 4, 2, 128, "bf16", [100, 129], None),
     ("chunk-g8", 8, 1, 128, "bf16", [77, 300], None),
+    # 64-row tiles up to 512 tokens (ragged rows of a wave, of a tile; full tiles), 128-row tiles from 513 on
+    ("chunk-g3", 6, 2, 128, "bf16", [5, 6, 85, 86, 511, 512, 513], None),
+    ("chunk-g8-tiles", 16, 2, 128, "bf16", [8, 9, 16, 505, 520, 700], None),
+    ("chunk-g1-tiles", 2, 2, 128, "bf16", [63, 64, 65, 512, 640], None),
     ("chunk-f32", 4, 2, 64, "f32", [50, 9], 56),                      # row-per-workgroup kernel
     ("chunk-bf16-d64", 4, 1, 64, "bf16", [40], 40),
 ])
