@@ -12,25 +12,22 @@
 // the same rows and take every second block; their states are folded in LDS at the end.
 //
 // What bounds it.  A step of 64 tokens needs of a SIMD 2 x 32 matrix instructions and 2 x 8 small ones (2200 cycles), of its
-// vector ALU about as much, and of the compute unit's LDS 2 x 8 x 16 KB at 128 bytes a cycle (2050
-// cycles) - so a step takes as long as these fail to overlap, and at full overlap the chip's power
-// limit is near (the clock falls to 1.9 GHz; a large library GEMM reaches 1385 TFLOP/s here).  Hence:
+// vector ALU about 1300 cycles (an exponential takes 8), and of the compute unit's LDS 2 x 8 x 16 KB at 256 bytes a cycle (1024
+// cycles) and the copies' 256.  On long walks the chip's power limit sets the pace: at 3290 cycles a step the clock is
+// 1.68 GHz (matrix instructions alone on such data would run at 1.7), and a large library GEMM reaches 1385 TFLOP/s here.  Hence:
 //  - K and V go from global memory straight into LDS (dma16), into unpadded rows whose 16-byte pieces
-//    are permuted so that operand reads and transposing reads meet no bank conflict; up to two blocks
+//    are permuted so that operand reads and transposing reads meet no bank conflict; up to three blocks
 //    are on their way while another is in use.
-//  - the two waves of a SIMD run half a step apart (see "the walk"): one multiplies, reads LDS and
-//    requests copies while the other computes its softmax.
-//  - 32x32x16 rather than 16x16x32: one row per lane halves the work per row, and the other wave's
-//    vector instructions lose less (32 multiply-adds and exponentials beside it 464 -> 580 cycles,
-//    beside 16x16x32 816).
-// The form this replaced (16x16x32, operands through registers, all waves in step, 64-token double
-// buffer) took 4900 cycles a step where this takes 3700.  Measured, us per layer with the fold, before
-// -> now: four 70B users of 20 000 tokens 361 -> 338 (990 TFLOP/s), sixteen 8B users of 5 000 175 -> 155, one
-// of 10 000 32 -> 28.8, of compressed pages 34 -> 30.5; chunks: 1000 tokens 8B 29 -> 24.3, 70B 43 -> 33, 3501
-// tokens 8B 132 -> 113, 4000 tokens 70B 295 -> 268.  Tried: every LDS read of the softmax phase spread
-// between its exponentials, copies between the matrix instructions, the vector phase at higher
-// priority: within 2 %; 128-row tiles over 32-token blocks, four of K and V each: 2.6 us per 128 tokens
-// against 2.2.
+//  - matrix and vector work of a wave alternate instruction by instruction (see "the walk").  The two waves of a SIMD half a step
+//    apart with a barrier behind each phase - one multiplies while the other is in its softmax - took 3550
+//    cycles a step: every phase had its own chain of dependent maxima, reads and scalar work with nothing beside it.
+//  - 32x32x16 rather than 16x16x32: one row per lane halves the work per row.
+// Measured, us per pass, that form -> this one: chunk passes of 1000 tokens (8B, 8 layers) 418 -> 404, (70B, 4 layers) 320 -> 314,
+// of 3501 674 -> 664; question passes (4 or 8 layers) of sixteen 8B users over 5000 tokens 705 -> 686, of four 70B users over
+// 20 000 1475 -> 1440 (a step 2.03 -> 1.95 us), of one over 10 000 316 -> 312.  Left out of a step of 1.95 us, for the measurement
+// only: every LDS read 1.94, the exponentials 1.90, the copies 1.80.  Tried: the weights formed beside the scores' matrix
+// instructions only 3870 cycles, all copies of a step at once 3900, the waves of a SIMD taking turns at the higher priority
+// 3360 against 3390, scalar work ahead of the first matrix instructions instead of between the periods 3390 against 3250.
 //
 // An instance whose cache is one unit gets its output rows directly; otherwise every unit leaves an
 // unnormalised partial (accumulator, running maximum, sum) per row and a second, chip-wide
@@ -66,9 +63,8 @@ __device__ __forceinline__ s16x4 lds_read_tr(const char* p) {
 
 // One block as the multiplying side sees it (wave-uniform).
 struct BlockDesc {
-    int n;              // token rows (0: none left)
-    int t0;             // tail row of the block's first token; kPageT0 for a page
-    int go;             // some group of the workgroup has a block in this step
+    int n;              // token rows; 0: none that a row of this wave may see, -1: no group of the workgroup has a block in this step
+    int t0;             // tail row of the block's first token; far below every row for a page
     float sk, sv;       // scales of a compressed page's codes
 };
 
@@ -169,13 +165,13 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     // Every group walks the same blocks - the unit's items end to end (the tail clipped to the rows
     // this tile may see), TB token rows at a time, never across two items - and takes every TS-th.
     // All of it is wave-uniform.
-    struct { const char* k; const char* v; int tok0, rows, left, item_i; bool tail; } wk;
+    struct { const char* k; const char* v; int left, t0, item_i, row_bytes; float sk, sv; } wk;
     const int tail_visible = min(r_last + 1, a.max_tail);
-    // rows of the item not yet handed out: from tok0 + rows - left on, K and V of the next one at k and v
+    // the item's next block: K and V at k and v, tail row t0 (a page: far below every row); rows left from there on
     auto set_item = [&](uint64_t base, int page_tokens, int tok0, int ntok) {
-        wk.tail = base == 0;
-        wk.tok0 = tok0;
-        wk.rows = wk.left = base ? ntok : min(ntok, tail_visible);
+        wk.left = base ? ntok : min(ntok, tail_visible);
+        wk.t0 = base ? kPageT0 : tok0;
+        wk.row_bytes = F8 && base ? D : 2 * D;
         if (base) {
             const size_t row = F8 ? D : 2 * D, head = (size_t)page_tokens * row;
             wk.k = reinterpret_cast<const char*>(base) + ((size_t)a.layer * 2 * a.Hkv + kvh) * head + (size_t)tok0 * row;
@@ -189,54 +185,44 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     // The next item's record is fetched (scalar loads) when its predecessor is taken up, so that taking
     // it up waits for nothing.
     struct { Item it; float sk, sv; } ahead;
-    float sk = 1.f, sv = 1.f;                           // scales of the current item
     auto fetch_item = [&](int i) {
         ahead.it = table_record(items + unit.item0 + min(i, unit.n_items - 1));
         ahead.sk = 1.f; ahead.sv = 1.f;
         if (F8 && ahead.it.base) page_scales(ahead.it, a.layer, a.Hkv, kvh, ahead.sk, ahead.sv);
     };
     wk.item_i = 0;
+    wk.sk = 1.f; wk.sv = 1.f;
     set_item(unit.first.base, unit.first.page_tokens, unit.first.tok0, unit.first.ntok);
-    if (F8 && unit.first.base) page_scales(unit.first, a.layer, a.Hkv, kvh, sk, sv);
+    if (F8 && unit.first.base) page_scales(unit.first, a.layer, a.Hkv, kvh, wk.sk, wk.sv);
     fetch_item(1);
     // where a block's rows lie: K and V of its first row, row stride 2 D bytes (codes: D bytes).  Past the
-    // unit's end: one token group copies its last block again (a branch around the copies there cost 3 %),
-    // two groups (n = 0) copy nothing.
+    // unit's end the last block's first row is copied instead (a branch around the copies there cost 3 %).
     struct Source { const char* k; const char* v; int n; bool codes; };
     Source src;
-    src.k = wk.k; src.v = wk.v; src.n = 1; src.codes = F8 && !wk.tail;
+    src.k = wk.k; src.v = wk.v; src.n = 1; src.codes = F8 && wk.row_bytes == D;
     auto next_step = [&](BlockDesc& d) {
-        if (!F8 && wk.left >= TS * TB) {                // the common case, in a few scalar instructions
-            const int skip = tg * TB;
-            d.n = TB; d.go = 1; d.sk = 1.f; d.sv = 1.f;
-            d.t0 = wk.tail ? wk.tok0 + wk.rows - wk.left + skip : kPageT0;
-            src.k = wk.k + skip * (2 * D); src.v = wk.v + skip * (2 * D); src.n = TB;
-            wk.left -= TS * TB;
-            wk.k += TS * TB * 2 * D; wk.v += TS * TB * 2 * D;
-            return;
-        }
-        d.n = 0; d.t0 = kPageT0; d.go = 0; d.sk = 1.f; d.sv = 1.f;
-        if (TS == 2) { src.n = 0; src.codes = false; }
+        d.n = -1; d.t0 = kPageT0; d.sk = 1.f; d.sv = 1.f;
+        src.n = 1;
 #pragma unroll
         for (int g = 0; g < TS; ++g) {
-            while (wk.left <= 0) {
-                if (wk.item_i + 1 >= unit.n_items) return;
+            while (wk.left <= 0 && wk.item_i + 1 < unit.n_items) {
                 ++wk.item_i;
                 set_item(ahead.it.base, ahead.it.page_tokens, ahead.it.tok0, ahead.it.ntok);
-                sk = ahead.sk; sv = ahead.sv;
+                if (F8) { wk.sk = ahead.sk; wk.sv = ahead.sv; }
                 fetch_item(wk.item_i + 1);
             }
             const int n = min(TB, wk.left);
-            if (g == 0) d.go = 1;
+            if (n <= 0) return;
+            if (g == 0) d.n = 0;
             if (g == tg) {
-                src.k = wk.k; src.v = wk.v; src.n = n; src.codes = F8 && !wk.tail;
-                d.n = n;
-                d.t0 = wk.tail ? wk.tok0 + wk.rows - wk.left : kPageT0;
-                d.sk = sk; d.sv = sv;
+                src.k = wk.k; src.v = wk.v; src.n = n; src.codes = F8 && wk.row_bytes == D;
+                d.n = wave_live && wk.t0 < vis_max ? n : 0;
+                d.t0 = wk.t0;
+                if (F8) { d.sk = wk.sk; d.sv = wk.sv; }
             }
             wk.left -= n;
-            const int bytes = n * (F8 && !wk.tail ? D : 2 * D);
-            wk.k += bytes; wk.v += bytes;
+            wk.t0 += n;
+            wk.k += n * wk.row_bytes; wk.v += n * wk.row_bytes;
         }
     };
 
@@ -250,46 +236,41 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     auto v_at = [&](int d) {
         if (TS == 1) return ((i4 + d) & 3) * 2 * TILE + TILE;
         const int j = i3 + d;
-        return (2 + (j < 0 ? j + 3 : j >= 3 ? j - 3 : j)) * TILE;
+        return (2 + (j >= 3 ? j - 3 : j)) * TILE;
     };
     const int lrow = lane >> 4, place = lane & 15;
-    auto copy = [&](const Source& s, int d) {
-        if (TS == 2 && s.n <= 0) return;                // (wave-uniform)
-        const uint32_t kb = lds0 + k_at(d) + rw * 1024, vb = lds0 + v_at(d) + rw * 1024;
+    auto copy_k1 = [&](const Source& s, int d, int i) {
+        const int r = 4 * (rw + RW * i) + lrow;
+        dev::dma16(s.k, (uint32_t)min(r, s.n - 1) * (2 * D) + 16 * (place ^ (r & 15)), lds0 + k_at(d) + rw * 1024 + i * RW * 1024);
+    };
+    auto copy_v1 = [&](const Source& s, int d, int i) {
+        const int r = 4 * (rw + RW * i) + lrow;
+        dev::dma16(s.v, (uint32_t)min(r, s.n - 1) * (2 * D) + 16 * (place ^ (4 * (r & 3))), lds0 + v_at(d) + rw * 1024 + i * RW * 1024);
+    };
+    auto copy_k = [&](const Source& s, int d) {
 #pragma unroll
-        for (int i = 0; i < NI; ++i) {
-            const int r = 4 * (rw + RW * i) + lrow;
-            const uint32_t row = (uint32_t)min(r, s.n - 1) * (2 * D);
-            dev::dma16(s.k, row + 16 * (place ^ (r & 15)), kb + i * RW * 1024);
-            dev::dma16(s.v, row + 16 * (place ^ (4 * (r & 3))), vb + i * RW * 1024);
-        }
+        for (int i = 0; i < NI; ++i) copy_k1(s, d, i);
+    };
+    auto copy_v = [&](const Source& s, int d) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) copy_v1(s, d, i);
     };
     // Compressed pages: codes go through registers (one step ahead of the copy they replace) and are
     // widened to bf16 on their way into the tile.  A lane moves 16 codes of a row: two pieces.
     constexpr int NC = TB * D / (RW * 64 * 16);         // 16-byte loads per lane, of K and of V
-    struct Codes { uint4 k[NC], v[NC]; } codes;
+    struct Codes { uint4 w[NC]; } kc, vc;
     const int ct = rw * 64 + lane;
-    auto load_codes = [&](Codes& codes, const Source& s) {
+    auto load_codes = [&](Codes& c, const char* from, int n) {
 #pragma unroll
-        for (int i = 0; i < NC; ++i) {
-            const int r = (ct >> 3) + RW * 8 * i;
-            const uint32_t off = (uint32_t)min(r, s.n - 1) * D + 16 * (ct & 7);
-            codes.k[i] = ldg16(s.k + off);
-            codes.v[i] = ldg16(s.v + off);
-        }
+        for (int i = 0; i < NC; ++i) c.w[i] = ldg16(from + (uint32_t)min((ct >> 3) + RW * 8 * i, n - 1) * D + 16 * (ct & 7));
     };
-    auto store_codes = [&](const Codes& codes, int d) {
-        char* const kt = group_lds + k_at(d);
-        char* const vt = group_lds + v_at(d);
+    auto store_codes = [&](const Codes& c, int at, bool v) {
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
-            const int r = (ct >> 3) + RW * 8 * i, p = 2 * (ct & 7);
-            char* const krow = kt + r * (2 * D);
-            char* const vrow = vt + r * (2 * D);
-            *reinterpret_cast<uint4*>(krow + 16 * (p ^ (r & 15))) = e4m3x8_to_bf16x8(make_uint2(codes.k[i].x, codes.k[i].y));
-            *reinterpret_cast<uint4*>(krow + 16 * ((p + 1) ^ (r & 15))) = e4m3x8_to_bf16x8(make_uint2(codes.k[i].z, codes.k[i].w));
-            *reinterpret_cast<uint4*>(vrow + 16 * (p ^ (4 * (r & 3)))) = e4m3x8_to_bf16x8(make_uint2(codes.v[i].x, codes.v[i].y));
-            *reinterpret_cast<uint4*>(vrow + 16 * ((p + 1) ^ (4 * (r & 3)))) = e4m3x8_to_bf16x8(make_uint2(codes.v[i].z, codes.v[i].w));
+            const int r = (ct >> 3) + RW * 8 * i, p = 2 * (ct & 7), turn = v ? 4 * (r & 3) : r & 15;
+            char* const row = group_lds + at + r * (2 * D);
+            *reinterpret_cast<uint4*>(row + 16 * (p ^ turn)) = e4m3x8_to_bf16x8(make_uint2(c.w[i].x, c.w[i].y));
+            *reinterpret_cast<uint4*>(row + 16 * ((p + 1) ^ turn)) = e4m3x8_to_bf16x8(make_uint2(c.w[i].z, c.w[i].w));
         }
     };
 
@@ -303,52 +284,26 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
 
     // Scores stay unscaled until the exponent: 2^((s - m) c) is one multiply-add and one
     // exponential per element, with m the row's reference score (unscaled too).
-    const float sc = a.scale_log2e;
-    const float lazy_raw = kLazyLog2 / sc;
-
     const int koff = c32 * 256 + 16 * (g2 ^ (c32 & 15));
     const int e16 = lane & 15;
     const int voff = (4 * g2 + (e16 >> 2)) * 256 + 64 * (e16 >> 2) + 32 * ((lane >> 4) & 1) + 8 * (e16 & 3);
-    // (the addresses of a step are formed from one register each time: kept over the loop they would
-    // cost the twelve registers that there are not)
-    auto read_k = [&](bf16x8 (&f)[8], int h) {                          // of block i
-        int o = koff + tg * GROUP + k_at(0);
-        asm volatile("" : "+v"(o));
-#pragma unroll
-        for (int c = 0; c < 8; ++c) f[c] = *reinterpret_cast<const bf16x8*>(smem + (o ^ (32 * c)) + h * 8192);
-    };
-    auto read_v = [&](bf16x8 (&f)[2][4], int d, int h, int t) {         // of block i + d, dims 32 t ..
-        int o = voff + tg * GROUP + v_at(d);
-        asm volatile("" : "+v"(o));
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const char* p = smem + (o ^ (64 * t)) + (32 * h + 16 * u) * 256;
-            const s16x4 lo = lds_read_tr(p), hi = lds_read_tr(p + 8 * 256);
-            f[u][t] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-        }
-    };
-
     // ---- the walk ----
-    // A step of a wave has a matrix phase X(i) - P V of block i - 1, then the scores of block i, and all
-    // LDS reads - and a vector phase Y(i) - softmax of block i - with a barrier behind each.  Waves 4 to
-    // 7, which share their SIMDs with waves 0 to 3, run one phase behind: while one wave of a SIMD
-    // multiplies, the other is in its vector phase.
-    // One token group (256 rows): K of block i is read in X(i), V in Y(i) and X(i + 1), by the late waves
-    // one phase on.  X(i) copies block i + 2 over block i - 2, behind the barrier that ends the late
-    // waves' X(i - 1), and ends when block i + 1 has landed: the early waves read it from X(i + 1) on,
-    // one barrier after the late waves have passed that wait.
-    // Two groups (128 rows): the late waves are the second group, with tiles of its own, so nothing is
-    // read in another phase than its owner's.  K of block i is dead behind X(i), V behind X(i + 1): two
-    // tiles of K and three of V do (all of LDS), Y(i) copies block i + 2 and ends when block i + 1 has landed.
-    const bool late = wave >= NW / 2;
-    // every copy but the youngest block's has landed (ahead: that block's rows, 0 = it was not copied)
-    auto landed = [&](int ahead) { if (TS == 1 || ahead > 0) dev::dma_wait<2 * NI>(); else dev::dma_wait<0>(); };
-    BlockDesc q[3];                   // descriptors of blocks i, i + 1, i + 2
-    Source next_src;                  // where block i + 2 lies
+    // A block is taken in halves of 32 tokens.  A period of a wave multiplies the scores of half t + 1 (eight matrix
+    // instructions), then the output of half t - 1 (eight more), and between these, evenly, forms the weights of half t and finds the
+    // maximum of half t + 1: the vector work of a SIMD's two waves then stands beside their matrix work throughout.
+    // Step i reads K of block i + 1 and V of block i and has one barrier.  One token group (256 rows): tiles of four
+    // blocks; step i copies block i + 3 over block i - 1, K first, and ends when K of block i + 2 has landed.  Two groups (128 rows; all of LDS): two
+    // tiles of K, three of V; step i copies block i + 2, K first, and ends when that K has landed.
+    constexpr bool RING4 = TS == 1 && !F8;
+    constexpr int AHEAD = RING4 ? 3 : 2;
+    BlockDesc q[AHEAD + 1];           // descriptors of blocks i .. i + AHEAD
     next_step(q[0]);
-    Codes first;
-    const bool codes0 = src.codes;
-    if (F8 && codes0) load_codes(first, src); else copy(src, 0);
+    if (F8 && src.codes) {
+        load_codes(kc, src.k, src.n); load_codes(vc, src.v, src.n);
+        store_codes(kc, k_at(0), false); store_codes(vc, v_at(0), true);
+    } else {
+        copy_k(src, 0); copy_v(src, 0);
+    }
     // Q comes through LDS as well - over tiles that nothing else needs yet - so
     // that whole rows are fetched and the first two blocks can be on their way at the same time; padding
     // rows repeat the last real row.  Placed like K rows, and read like them: B operand, lane's row c32.
@@ -368,26 +323,25 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
         }
     }
     next_step(q[1]);
-    const bool codes1 = src.codes;
-    const int n1 = src.n;
-    if (F8 && codes1) load_codes(codes, src); else copy(src, 1);
-    next_step(q[2]);
-    next_src = src;
-    if (F8) {                                   // (compressed pages: the codes of block i + 2 wait in registers)
-        if (codes0) store_codes(first, 0);
-        if (codes1) store_codes(codes, 1);
-        dev::dma_wait<0>();
-        if (src.codes) load_codes(codes, src);
+    if (F8 && src.codes) {
+        load_codes(kc, src.k, src.n); load_codes(vc, src.v, src.n);
+        store_codes(kc, k_at(1), false); store_codes(vc, v_at(1), true);
     } else {
-        landed(n1);                       // Q and block 0 are there
+        copy_k(src, 1); copy_v(src, 1);
     }
+    // Q and block 0 are there
+    if (F8) dev::dma_wait<0>(); else dev::dma_wait<2 * NI>();
+    next_step(q[2]);
     lds_barrier();
     bf16x8 bq[8];                     // dims 16 c + 8 g2 ..
     const int vis = div_g(min(wm0 + c32, n_m - 1)) + 1;    // tail rows this lane's row may see
 #pragma unroll
     for (int c = 0; c < 8; ++c) bq[c] = *reinterpret_cast<const bf16x8*>(smem + q_row(WR * rw) + (koff ^ (32 * c)));
-    lds_barrier();                              // X(0) copies over it
-    bf16x8 av[2][2][4], pb[2][2];   // V operands (the first 32 tokens' read ahead in Y), weights
+    lds_barrier();                              // block 2 comes over it
+    if (RING4) { copy_k(src, 2); copy_v(src, 2); next_step(q[AHEAD]); }
+    Source next_src = src;            // where block i + AHEAD lies (compressed pages: its codes wait in registers)
+    if (F8 && next_src.codes) { load_codes(kc, next_src.k, next_src.n); load_codes(vc, next_src.v, next_src.n); }
+
     auto barrier_plain = [&]() {      // every LDS read before it is consumed before the next one
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("" ::: "memory");
@@ -395,153 +349,230 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
     };
+    const float sc = a.scale_log2e;
+    const float lazy_raw = kLazyLog2 / sc;
+    // weight = 2^(score scb + nmc): scb the score scale (compressed page: with sk), nmc minus the reference score in its
+    // units (compressed page: plus log2 sv)
+    float scb = sc, nmc = 0.f, ones_v = 1.0f;       // (ones_v: 1 / sv, so that the factor sv of the weights cancels in their sum)
+    // Half h of block d's scores.  masked: the block is ragged, or lies in the tail and reaches past what the wave's first
+    // row may see (per-row causal limit); otherwise all rows see all of it
+    auto mask = [&](f32x16& st, const BlockDesc& d, int h) {
+        if (d.n != TB || d.t0 + d.n > vis_min) {            // wave-uniform
+            const int limit = min(d.n, vis - d.t0) - 4 * g2 - 32 * h;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) st[i] = 8 * (i / 4) + i % 4 < limit ? st[i] : kNegBig;
+        }
+    };
+    // The reference score of a row moves only when the maximum of a half exceeds it by
+    // more than kLazyLog2 powers of two: weights stay below 2^kLazyLog2, and the
+    // accumulators are rescaled on few blocks instead of on most - once the half before, whose weights are
+    // formed against the old reference, has been added to them.
+    float alpha = 1.f;
+    bool moved = false;               // (wave-uniform)
+    auto take_max = [&](float mx, const BlockDesc& d) {
+        mx = fmaxf(mx, lane_xor(mx, 32, lane));
+        if (F8) mx = mx > 0.5f * kNegBig ? mx * d.sk : kNegBig;     // into the units of the reference
+        const bool moves = mx > mrow + lazy_raw;
+        moved = __builtin_amdgcn_ballot_w64(moves) != 0;
+        if (moved) {
+            alpha = moves ? fast_exp2((mrow - mx) * sc) : 1.0f;
+            if (moves) mrow = mx;
+            // a row that has seen no key yet keeps the floor as its reference; its masked
+            // scores must still come out as weight 0, not 2^0
+            if (!F8) nmc = mrow > 0.5f * kNegBig ? -mrow * sc : 0.f;
+        }
+        if (F8) nmc = (mrow > 0.5f * kNegBig ? -mrow * sc : 0.f) + (__builtin_amdgcn_frexp_expf(d.sv) - 1.0f);
+    };
+    auto rescale = [&]() {
+        if (moved) {
+            ol[0] *= alpha;
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) ot[t][i] *= alpha;
+        }
+    };
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    auto pack2 = [&](float x, float y) { return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x, y}, bf16x2)); };
+    // (keeps what is computed here here, among instructions that the compiler would reorder)
+    auto pin = [](auto& x) { asm volatile("" : "+v"(x)); };
+    constexpr int PD = 4;             // LDS reads ahead of the matrix instructions
+    // operand addresses of a step: K of a block by 16 dims, V by 32
+    auto read_k1 = [&](int o) { return *reinterpret_cast<const bf16x8*>(smem + o); };
+    auto read_v1 = [&](int o) {                 // 16 tokens
+        const s16x4 lo = lds_read_tr(smem + o), hi = lds_read_tr(smem + o + 8 * 256);
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    const f32x16 zero = {};
     // The row sums come from the matrix cores as well: they add the weights exactly as the output uses
     // them (rounded to bf16).  A column of the 4x4x4 instruction's sixteen blocks is a lane's own four
     // values, so with ones as A each lane gets the sum of its own weights (and a row that is not a number
-    // reaches no other): 8 cycles for four weights per lane.  (As dot products of the vector ALU they took
-    // eight times as long while the other wave of the SIMD multiplies: 16 of them 1154 cycles against 130.)
-    float ones_v = 1.0f;              // (compressed page: 1 / sv, so that the factor sv of the weights cancels)
-    auto multiply_pv = [&](int h) {
+    // reaches no other).
+    auto row_sums = [&](const uint32_t (&pw)[8], float ones_v) {
         const short one = __builtin_bit_cast(short, (__bf16)(F8 ? ones_v : 1.0f));
         const s16x4 ones = {one, one, one, one};
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const s16x8 w = __builtin_bit_cast(s16x8, pb[h][u]);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                ot[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[h][u][t], pb[h][u], ot[t], 0, 0, 0);
-                if (t == 1) ol = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, __builtin_shufflevector(w, w, 0, 1, 2, 3), ol, 0, 0, 0);
-                if (t == 3) ol = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, __builtin_shufflevector(w, w, 4, 5, 6, 7), ol, 0, 0, 0);
-            }
-        }
+        for (int u = 0; u < 4; ++u)
+            ol = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, __builtin_bit_cast(s16x4, u32x2{pw[2 * u], pw[2 * u + 1]}), ol, 0, 0, 0);
     };
-    f32x16 st[2];                    // S^T: tokens 32 h + 8 (i / 4) + 4 g2 + i % 4
-    auto multiply_qk = [&](const bf16x8 (&ak)[8], int h) {
+
+    f32x16 s0, s1;                    // S^T of a block's halves: tokens 8 (i / 4) + 4 g2 + i % 4, + 32
+    uint32_t p0[8], p1[8];            // their weights, two to a register
+    auto weight_pair = [&](const uint32_t (&p)[8], int u) { return __builtin_bit_cast(bf16x8, u32x4{p[4 * u], p[4 * u + 1], p[4 * u + 2], p[4 * u + 3]}); };
+    // The matrix instructions find their first four operands in f, and those of the next eight are left there.
+    bf16x8 f[PD];
+    // st: scores at hand, sn: next scores (half h of block dn, K at ka), pt: weights at hand, pp: weights before (half h of V at va);
+    // K at kn comes next.  between(j): what else is to be done behind the j-th matrix instruction.
+    auto period = [&](const f32x16& st, f32x16& sn, uint32_t (&pt)[8], const uint32_t (&pp)[8], const int (&ka)[8], const int (&va)[4],
+                      const int (&kn)[8], int kn_off, const BlockDesc& dn, int h, float ones_pp, auto between) {
+        bf16x8 g[8 - PD];
+        float x = fmaf(st[0], scb, nmc), e[2];
+        auto vector_work = [&](int j) {     // one weight; those of the step before are packed
+            if (j > 0 && j % 2 == 0) { pt[j / 2 - 1] = pack2(e[0], e[1]); pin(pt[j / 2 - 1]); }
+            e[j & 1] = fast_exp2(x); pin(e[j & 1]);
+            if (j < 15) { x = fmaf(st[j + 1], scb, nmc); pin(x); }
+        };
+        auto v_operand = [&](int j) { return read_v1(va[j & 3] + 8192 * h + 4096 * (j >> 2)); };
 #pragma unroll
-        for (int i = 0; i < 16; ++i) st[h][i] = 0.f;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) st[h] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak[c], bq[c], st[h], 0, 0, 0);
-    };
-    auto spread = [&](auto reads) {   // eight matrix instructions, `reads` LDS reads behind each
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, decltype(reads)::value, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    if (late) barrier_plain();
-    bool prev_live = false;
-    bool copied = false;              // compressed pages: a block of the tail is on its way
-    while (q[0].go) {
-        const BlockDesc d = q[0];
-        const bool live = wave_live && d.n > 0 && d.t0 < vis_max;
-        // X (its wave goes first: a matrix instruction needs the issue port once in 32 cycles)
-        __builtin_amdgcn_s_setprio(1);
-        bf16x8 ak[2][8];
-        if (prev_live) {
-#pragma unroll
-            for (int t = 0; t < 4; ++t) read_v(av[1], -1, 1, t);
-            multiply_pv(0);
-            spread(std::integral_constant<int, 2>{});
-            read_k(ak[0], 0);
-            multiply_pv(1);
-            spread(std::integral_constant<int, 1>{});
-        } else if (live) {
-            read_k(ak[0], 0);
-        }
-        if (!F8 && TS == 1) copy(next_src, 2);
-        if (live) {
-            read_k(ak[1], 1);
-            multiply_qk(ak[0], 0);
-            spread(std::integral_constant<int, 1>{});
-            multiply_qk(ak[1], 1);
-        }
-        if (!F8 && TS == 1) landed(next_src.n);
-        if (F8 && copied) { dev::dma_wait<0>(); copied = false; }
-        barrier_plain();
-        // Y
-        __builtin_amdgcn_s_setprio(0);
-        if (F8 && next_src.codes) store_codes(codes, 2);
-        else if (F8 || TS == 2) { copy(next_src, 2); copied = F8; }
-        const int ahead_n = next_src.n;
-        q[0] = q[1]; q[1] = q[2];
-        next_step(q[2]);
-        next_src = src;
-        if (F8 && src.codes) load_codes(codes, src);
-        if (live) {
-            // masked: the block is ragged, or lies in the tail and reaches past what the wave's first
-            // row may see (per-row causal limit); otherwise all rows see all of it
-            if (d.n != TB || d.t0 + d.n > vis_min) {        // wave-uniform
-                const int limit = min(d.n, vis - d.t0) - 4 * g2;
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) st[h][i] = 32 * h + 8 * (i / 4) + i % 4 < limit ? st[h][i] : kNegBig;
-            }
-            float mx = st[0][0];
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) mx = fmaxf(mx, st[h][i]);
-            mx = fmaxf(mx, lane_xor(mx, 32, lane));
-            // compressed page: scores carry the factor 1 / sk until the exponent, weights the factor
-            // sv from the exponent on (nsv = log2 sv goes into the exponent's offset)
-            if (F8) mx = mx > 0.5f * kNegBig ? mx * d.sk : kNegBig;     // into the units of the reference
-            const float scb = F8 ? sc * d.sk : sc;
-            const float nsv = F8 ? __builtin_amdgcn_frexp_expf(d.sv) - 1.0f : 0.f;
-            // The reference score of a row moves only when the block's maximum exceeds it by
-            // more than kLazyLog2 powers of two: weights stay below 2^kLazyLog2, and the
-            // accumulators are rescaled on few blocks instead of on most.
-            const float mn = mx > mrow + lazy_raw ? mx : mrow;
-            const float alpha = fast_exp2((mrow - mn) * sc);
-            mrow = mn;
-            // a row that has seen no key yet keeps the floor as its reference; its masked
-            // scores must still come out as weight 0, not 2^0
-            const float nmc = (mn > 0.5f * kNegBig ? -mn * sc : 0.f) + nsv;
-            if (__builtin_amdgcn_ballot_w64(alpha != 1.0f)) {   // wave-uniform: some row's reference moved
-                ol[0] *= alpha;
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) ot[t][i] *= alpha;
-            }
-            if (F8) ones_v = 1.0f / d.sv;
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) pb[h][u][i] = (__bf16)fast_exp2(fmaf(st[h][8 * u + i], scb, nmc));
-                }
-            // the V operand of the first 32 tokens, for X(i + 1)
+        for (int j = 0; j < 8; ++j) {
+            sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(j < PD ? f[j] : g[j - PD], bq[j], j ? sn : zero, 0, 0, 0);
+            pin(sn);
+            if (j < 8 - PD) g[j] = read_k1(ka[j + PD] + 8192 * h); else f[j - (8 - PD)] = v_operand(j - (8 - PD));
+            between(j);
+            vector_work(j);
             __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) read_v(av[0], 0, 0, t);
-        } else {
-            // not used again: without this the old values would take registers through the whole step
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                asm volatile("" : "=v"(pb[i / 2][i % 2]));
-#pragma unroll
-                for (int t = 0; t < 4; ++t) asm volatile("" : "=v"(av[i / 2][i % 2][t]));
-            }
         }
-        prev_live = live;
+        mask(sn, dn, h);
+        __builtin_amdgcn_sched_barrier(0);
+        float mx = sn[0];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            ot[j & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(j < PD ? f[j] : g[j - PD], weight_pair(pp, j >> 2), ot[j & 3], 0, 0, 0);
+            pin(ot[j & 3]);
+            if (j < 8 - PD) g[j] = v_operand(j + PD); else f[j - (8 - PD)] = read_k1(kn[j - (8 - PD)] + kn_off);
+            between(8 + j);
+            mx = j ? fmaxf(fmaxf(mx, sn[2 * j]), sn[2 * j + 1]) : fmaxf(mx, sn[1]);
+            pin(mx);
+            vector_work(8 + j);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        pt[7] = pack2(e[0], e[1]);
+        row_sums(pp, ones_pp);
+        rescale();
+        return mx;
+    };
+    auto weights = [&](const f32x16& st, uint32_t (&p)[8]) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) p[j] = pack2(fast_exp2(fmaf(st[2 * j], scb, nmc)), fast_exp2(fmaf(st[2 * j + 1], scb, nmc)));
+    };
+    auto half_max = [&](const f32x16& st) {
+        float mx = st[0];
+#pragma unroll
+        for (int i = 1; i < 16; ++i) mx = fmaxf(mx, st[i]);
+        return mx;
+    };
+    const int kb = koff + tg * GROUP, vb = voff + tg * GROUP;
+    auto k_operands = [&](int (&ka)[8], int d) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) { ka[c] = (kb + k_at(d)) ^ (32 * c); pin(ka[c]); }
+    };
+    auto v_operands = [&](int (&va)[4]) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) { va[t] = (vb + v_at(0)) ^ (64 * t); pin(va[t]); }
+    };
+    if (q[0].n > 0) {
+        int ka[8];
+        k_operands(ka, 0);
+        auto scores = [&](f32x16& st, int h) {
+#pragma unroll
+            for (int c = 0; c < 8; ++c) { st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_k1(ka[c] + 8192 * h), bq[c], c ? st : zero, 0, 0, 0); pin(st); }
+            mask(st, q[0], h);
+        };
+        scores(s0, 0);
+        scores(s1, 1);
+        if (F8) { scb = sc * q[0].sk; ones_v = 1.0f / q[0].sv; }
+        take_max(half_max(s0), q[0]);           // (nothing summed yet)
+        weights(s0, p0);
+        take_max(half_max(s1), q[0]);
+    }
+    if (!F8) dev::dma_wait<RING4 ? NI : 0>();   // block 1 is there,
+    barrier_plain();                                // and K of block 0 read by every wave
+    // Step i: descriptors and sources move on by one block
+    bool copied = false;
+    Source now;
+    BlockDesc d, dn;
+    auto begin_step = [&]() {
+        d = q[0]; dn = q[1];
+        copied = false;
+        if (F8) {
+            if (next_src.codes) { store_codes(kc, k_at(2), false); store_codes(vc, v_at(2), true); }
+            else                { copy_k(next_src, 2); copy_v(next_src, 2); copied = true; }
+        }
+        now = next_src;
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k) q[k] = q[k + 1];
+        next_step(q[AHEAD]);
+        next_src = src;
+        if (F8 && next_src.codes) { load_codes(kc, next_src.k, next_src.n); load_codes(vc, next_src.v, next_src.n); }
+    };
+    auto end_step = [&]() {
         i4 = (i4 + 1) & 3;
         i3 = i3 == 2 ? 0 : i3 + 1;
-        if (!F8 && TS == 2) landed(ahead_n);
-        if (F8) lds_barrier();      // (the widened codes are written)
-        else barrier_plain();
-    }
-    if (!late) barrier_plain();
-    if (prev_live) {
+        if (F8) {
+            if (copied) dev::dma_wait<0>();
+            lds_barrier();                          // (the widened codes are written)
+        } else {
+            dev::dma_wait<NI>();
+            barrier_plain();
+        }
+    };
+    auto first_operands = [&]() {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) read_v(av[1], -1, 1, t);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) multiply_pv(h);
+        for (int c = 0; c < PD; ++c) f[c] = read_k1((kb + k_at(1)) ^ (32 * c));
+    };
+    first_operands();
+    while (q[0].n > 0 && q[1].n > 0) {
+        d = q[0]; dn = q[1];
+        int ka[8], kn[8], va[4];
+        k_operands(ka, 1);
+        v_operands(va);
+        // (the copies go among the matrix instructions: all at once they would hold up the waves)
+        now = next_src;
+        auto copies_k = [&](int j) { if (!F8 && j % (16 / NI) == 1) copy_k1(now, AHEAD, j / (16 / NI)); };
+        auto copies_v = [&](int j) { if (!F8 && j % (16 / NI) == 1) copy_v1(now, AHEAD, j / (16 / NI)); };
+        const float ones_now = ones_v;
+        float mx = period(s1, s0, p1, p0, ka, va, ka, 8192, dn, 0, ones_now, copies_k);
+        if (F8) { scb = sc * dn.sk; ones_v = 1.0f / dn.sv; }
+        take_max(mx, dn);
+        begin_step();
+        if (RING4) k_operands(kn, 2);               // (it has landed)
+        mx = period(s0, s1, p0, p1, ka, va, RING4 ? kn : ka, 0, dn, 1, ones_now, copies_v);
+        take_max(mx, dn);
+        end_step();
+        if (!RING4) first_operands();
     }
-    if (TS == 1) dev::dma_wait<0>();                     // (copies past the end)
+    if (q[0].n > 0) {                               // the wave's last block
+        begin_step();
+        if (!F8) { copy_k(now, AHEAD); copy_v(now, AHEAD); }
+        weights(s1, p1);
+        int va[4];
+        v_operands(va);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            ot[j & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_v1(va[j & 3] + 4096 * (j >> 2)), weight_pair(j < 8 ? p0 : p1, (j >> 2) & 1), ot[j & 3], 0, 0, 0);
+            pin(ot[j & 3]);
+            if (j == 7) { row_sums(p0, ones_v); rescale(); }
+        }
+        row_sums(p1, ones_v);
+        end_step();
+    }
+    while (q[0].n >= 0) {                           // blocks that other waves see
+        begin_step();
+        if (!F8) { copy_k(now, AHEAD); copy_v(now, AHEAD); }
+        end_step();
+    }
+    dev::dma_wait<0>();                                  // (copies past the end)
     __syncthreads();
 
     // ---- finished rows leave through LDS as whole rows; token groups are folded on the way ----
