@@ -18,6 +18,13 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
     return (uint16_t)(u >> 16);
 }
 
+// Two floats to two bf16, as f32_to_bf16_rne rounds them (the hardware conversion).
+__device__ __forceinline__ uint32_t pack_bf16(float x, float y) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x, y}, bf16x2));
+}
+
 // 16-byte load through the global address space (a pointer rebuilt from an integer would
 // otherwise be treated as generic and loaded with the slower flat instructions).
 __device__ __forceinline__ uint4 ldg16(const void* p) {
@@ -78,6 +85,18 @@ __device__ __forceinline__ bool arrive_at(int32_t* counter, int expected, int* s
     }
     __syncthreads();
     return *sm_last != 0;
+}
+// The same for a wave: its own agent-scope stores are acknowledged before its ticket is drawn.  True in the wave that
+// arrived last of `expected`, which also makes the counter ready for the next launch.
+__device__ __forceinline__ bool wave_arrives_last(int32_t* counter, int expected) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_s_waitcnt(0);
+    int prev = 0;
+    if ((threadIdx.x & 63) == 0) prev = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_amdgcn_readfirstlane(prev) != expected - 1) return false;
+    if ((threadIdx.x & 63) == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    return true;
 }
 // (by the workgroup that arrived last: ready for the next launch)
 __device__ __forceinline__ void reset_counter_at(int32_t* counter) {

@@ -68,18 +68,19 @@ __device__ __forceinline__ RowDest resolve_row(const MaterializeArgs& a, int r) 
 
 // cos / sin of pos * theta_j with the angle kept in turns: hi/lo split product, whole turns
 // dropped exactly, then the hardware sine / cosine (which take turns).
-__device__ __forceinline__ void rope_cs(const RopeEntry& e, float p, float& c, float& s) {
+__device__ __forceinline__ void rope_cs(float turns_hi, float turns_lo, float p, float& c, float& s) {
     // no contraction here: were p * turns_hi - rint(t) fused into one multiply-add, the product
     // would enter exactly and the rounding error of t, added back below, would count twice
     // (half an ulp of t: 1e-4 turns at position 20 000)
 #pragma clang fp contract(off)
-    const float t = p * e.turns_hi;
-    const float err = fmaf(p, e.turns_hi, -t);
+    const float t = p * turns_hi;
+    const float err = fmaf(p, turns_hi, -t);
     float fr = t - rintf(t);
-    fr += fmaf(p, e.turns_lo, err);
+    fr += fmaf(p, turns_lo, err);
     c = __builtin_amdgcn_cosf(fr);
     s = __builtin_amdgcn_sinf(fr);
 }
+__device__ __forceinline__ void rope_cs(const RopeEntry& e, float p, float& c, float& s) { rope_cs(e.turns_hi, e.turns_lo, p, c, s); }
 
 // ---- tiled GEMM ----------------------------------------------------------------------------------
 // A workgroup of eight waves owns 32 MI token rows x one head of K or of V (128 features: both halves
@@ -95,17 +96,24 @@ __device__ __forceinline__ void rope_cs(const RopeEntry& e, float p, float& c, f
 //  - LDS rows are unpadded 128 bytes (the copy writes 1 KB runs); the eight 16-byte pieces of row r
 //    are permuted by (r >> 1) & 7 instead - the copy picks its global addresses accordingly - which
 //    spreads an operand read of sixteen rows over all banks.
-//  - half a step is multiplied while the operands of the next half are on their way from LDS.
-//  - finished tiles leave through LDS as whole 256-byte rows.
-// Two workgroups that share a tile (SK = 2) leave their fp32 partials in the workspace (agent-scope
-// stores), arrive at the tile's counter, and the second to arrive adds the other's and finishes.
-// Measured, us per launch with every layer's weights from HBM, 8 KV heads, before -> now:
-//   hidden 4096:  256 rows 21.9 -> 17.3, 512 rows 32.3 -> 21.4, 1000 rows 34.5 -> 28.5, 1206 rows
-//                 45.6 -> 33.5, 2048 rows 48.5 -> 42.3, 3501 rows 83 -> 62, 8192 rows 168 -> 133
-//   hidden 8192:  512 rows 62.6 -> 36.3, 1000 rows 53 -> 48, 2048 rows 83 -> 72, 4096 rows 156 -> 121
+//  - half a step is multiplied while the operands of the next half are on their way from LDS and copies are
+//    requested, instruction by instruction: all waves' copies at once hold up their matrix instructions.
+//  - behind the loop every wave is on its own: results leave registers as 8 or 16 bytes of a row (its four or two
+//    waves along the features fill 256 bytes), rotated with entries fetched at the start.
+// Two workgroups that share a tile (SK = 2): each wave leaves its fp32 partial in the workspace (agent-scope
+// stores) and arrives at a counter of its own; of a pair the second to arrive adds the other's and finishes, so that the
+// two workgroups share that work too.
+// Measured, us per launch with every layer's weights from HBM, 8 KV heads, with copies, results through LDS and whole workgroups
+// arriving -> now:
+//   hidden 4096:  1000 rows 26.3 -> 24.0, 1206 rows 30.9 -> 29.2, 3501 rows 66.9 -> 60.6
+//   hidden 8192:  512 rows 36.3 -> 34.5, 1000 rows 49.7 -> 46.5, 1206 rows 62 -> 50, 2000 rows 73 -> 67
+// At 1000 rows of hidden 4096 a launch of 37 800 cycles waits 3800 for its first operands, takes 740 for each of 32 steps (44
+// bytes a cycle), then 1900 until its partials have left, 2700 to arrive, 3600 to fetch the other's and 1300 for the results (6500,
+// 3500 and 7400 for the last three before).  From the last-level cache 512 rows of hidden 8192 would take 24.7 us.
 // Tried and left out: starting every workgroup at another hidden column (no channel of the L2s is
 // favoured by the power-of-two row strides: no change), an extra wave that touches the weight rows
-// some steps ahead (-12 % at 512 rows of hidden 8192, +20 % at 64 rows, nothing at 1000).
+// some steps ahead (-12 % at 512 rows of hidden 8192, +20 % at 64 rows, nothing at 1000), workgroups that share an operand touching it
+// some steps ahead in turn (-10 % there, +8 to 13 % at 1000 rows and more).
 template <int MI> struct TileShape {
     static constexpr int BM = 32 * MI;                              // token rows of a workgroup
     static constexpr int ROWS = BM + D;                             // LDS rows of a step: tokens, then weight rows
@@ -114,14 +122,14 @@ template <int MI> struct TileShape {
 };
 
 // WN: waves along the features; the other 8 / WN split the rows.  Few waves along the features read
-// fewer LDS bytes per product from MI = 8 on (68 -> 64 us at 3501 rows), where LDS becomes the limit.
+// fewer LDS bytes per product from MI = 6 on, as many at MI = 4, and store 16 bytes of a row instead of 8.
 template <int MI, int WN, int SK>
 __global__ __launch_bounds__(512) void materialize_tile_kernel(MaterializeArgs a, int total_rows, int row_tiles) {
     typedef TileShape<MI> S;
     constexpr int WM = 8 / WN, XB = 2 * MI / WM, PB = 4 / WN;       // waves along the rows; row blocks and pair blocks of a wave
-    constexpr int BM = S::BM, NBUF = S::NBUF, OSTR = D + 8;         // OSTR: bf16 per LDS row of the finished tile
-    static_assert(BM * OSTR * 2 + BM * (int)sizeof(RowDest) <= NBUF * S::STEP_BYTES, "epilogue fits over the dead buffers");
+    constexpr int BM = S::BM, NBUF = S::NBUF;
     __shared__ __attribute__((aligned(16))) char smem[NBUF * S::STEP_BYTES];
+    __shared__ RowDest sm_dest[BM];
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -145,6 +153,12 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(MaterializeArgs a
     const int row0 = rt * BM;
     const int nk = a.Hd / (BK * SK);
 
+    // LDS row r of the weights -> feature.  Sixteen rows are one operand of a matrix instruction, whose results
+    // land in lanes by fours of these rows: the order makes a lane's results of its PB low (and of its PB high) operands features in a row.
+    auto feature = [](int r) {
+        const int b = (r & 63) >> 4, c = r & 15;
+        return (r & 64) + 16 * PB * (b / PB) + 4 * PB * (c >> 2) + 4 * (b % PB) + (c & 3);
+    };
     // Copies of a step: 8 rows x 128 bytes per instruction; token rows are instructions 0 .. 4 MI - 1,
     // wave w takes w, w + 8, ...; of the 16 weight instructions every wave takes two.  LDS row r holds
     // its eight 16-byte pieces permuted: piece g sits at place g ^ ((r >> 1) & 7).
@@ -163,16 +177,19 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(MaterializeArgs a
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int r = (wave + 8 * i) * 8 + lrow;
-        woff[i] = (uint32_t)(r * row_bytes) + 16 * (place ^ ((r >> 1) & 7));
+        woff[i] = (uint32_t)(feature(r) * row_bytes) + 16 * (place ^ ((r >> 1) & 7));
     }
     const uint32_t lds0 = dev::lds_address(smem);
-    auto copy_step = [&](int ks, int buf) {
+    constexpr int NC = 2 + XW;                                      // copies of a wave per step
+    auto copy_one = [&](int ks, int buf, int i) {
         const uint32_t base = lds0 + buf * S::STEP_BYTES + wave * 1024;
         const size_t k = (size_t)ks * (BK * 2);
+        if (i < 2)                                    dev::dma16(W + k, woff[i], base + BM * BK * 2 + i * 8192);
+        else if (XI % 8 == 0 || i - 2 < n_x)          dev::dma16(X + k, xoff[i - 2], base + (i - 2) * 8192);
+    };
+    auto copy_step = [&](int ks, int buf) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) dev::dma16(W + k, woff[i], base + BM * BK * 2 + i * 8192);
-#pragma unroll
-        for (int i = 0; i < XW; ++i) if (XI % 8 == 0 || i < n_x) dev::dma16(X + k, xoff[i], base + i * 8192);
+        for (int i = 0; i < NC; ++i) copy_one(ks, buf, i);
     };
 
     const int wm = wave / WN, wn = wave % WN;
@@ -185,22 +202,34 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(MaterializeArgs a
     const int sw = (c16 >> 1) & 7;                                  // (the rows a lane reads differ by multiples of 16)
     const char* const At = smem + (16 * XB * wm + c16) * 128;
     const char* const Bt = smem + (BM + 16 * PB * wn + c16) * 128;
-    auto read = [&](Frags& f, int buf, int k2) {
+    constexpr int NF = 2 * PB + XB, NM = XB * 2 * PB;               // operands and matrix instructions of half a step
+    auto read_one = [&](Frags& f, int buf, int k2, int i) {
         const int off = buf * S::STEP_BYTES + 16 * ((4 * k2 + g4) ^ sw);
-#pragma unroll
-        for (int p = 0; p < PB; ++p) {
-            f.b[p] = *reinterpret_cast<const bf16x8*>(Bt + p * 2048 + off);
-            f.b[PB + p] = *reinterpret_cast<const bf16x8*>(Bt + 64 * 128 + p * 2048 + off);
-        }
-#pragma unroll
-        for (int mi = 0; mi < XB; ++mi) f.x[mi] = *reinterpret_cast<const bf16x8*>(At + mi * 2048 + off);
+        if (i < 2 * PB) f.b[i] = *reinterpret_cast<const bf16x8*>(Bt + (i < PB ? i * 2048 : 64 * 128 + (i - PB) * 2048) + off);
+        else            f.x[i - 2 * PB] = *reinterpret_cast<const bf16x8*>(At + (i - 2 * PB) * 2048 + off);
     };
-    auto multiply = [&](const Frags& f) {
+    auto read = [&](Frags& f, int buf, int k2) {
 #pragma unroll
-        for (int mi = 0; mi < XB; ++mi)
+        for (int i = 0; i < NF; ++i) read_one(f, buf, k2, i);
+    };
+    // (keeps the instructions of a half step in the order written)
+    auto pin = [](auto& v) { asm volatile("" : "+v"(v)); };
+    // Half a step: f multiplied, the operands g of the next half read (block k2 of buffer rbuf) and copies c0 .. c1 of step ks into buffer
+    // cbuf requested, all in turn: copies of all waves at once would hold up their matrix instructions for as long as
+    // the address path takes them, 16 cycles each.
+    auto half_step = [&](const Frags& f, Frags& g, int rbuf, int k2, int ks, int cbuf, auto c0, auto c1) {
+        constexpr int C0 = decltype(c0)::value, CN = decltype(c1)::value - C0;
 #pragma unroll
-            for (int p = 0; p < 2 * PB; ++p)
-                acc[mi][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.x[mi], f.b[p], acc[mi][p], 0, 0, 0);
+        for (int m = 0; m < NM; ++m) {
+            f32x4& c = acc[m / (2 * PB)][m % (2 * PB)];
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.b[m % (2 * PB)], f.x[m / (2 * PB)], c, 0, 0, 0);
+            pin(c);
+#pragma unroll
+            for (int i = m * NF / NM; i < (m + 1) * NF / NM; ++i) read_one(g, rbuf, k2, i);
+#pragma unroll
+            for (int i = m * CN / NM; i < (m + 1) * CN / NM; ++i) copy_one(ks, cbuf, C0 + i);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     };
 
     // all but the youngest `steps` steps of this wave's copies have landed
@@ -213,94 +242,105 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(MaterializeArgs a
     // the barrier every wave has its operands of step ks in registers, so step ks + NBUF is copied over it.
     const int ahead = min(NBUF, nk);
     for (int i = 0; i < ahead; ++i) copy_step(i, i);
-    const RowDest my_dest = resolve_row(a, row0 + min(tid, BM - 1));      // (while they are on their way)
+    // (while they are on their way) where the rows go, and this lane's rotary entries
+    if (tid < BM) sm_dest[tid] = resolve_row(a, row0 + tid);
+    const int j0 = 16 * PB * wn + 4 * PB * g4;                      // first of the lane's features (and of their partners, 64 further)
+    float2 turns[4 * PB];
+    if (kv == 0) {
+#pragma unroll
+        for (int i = 0; i < 4 * PB; ++i) turns[i] = *reinterpret_cast<const float2*>(&a.rope[j0 + i].turns_hi);
+    }
     if (ahead == NBUF) wait_steps(std::integral_constant<int, NBUF - 1>{}); else dev::dma_wait<0>();
     lds_barrier();
     Frags f0, f1;
     read(f0, 0, 0);
     int buf = 0, ks = 0;
-    for (; ks < nk - NBUF; ++ks) {
-        read(f1, buf, 1);
-        multiply(f0);
-        wait_steps(std::integral_constant<int, NBUF - 2>{});
-        lds_barrier();
-        const int nbuf = buf + 1 == NBUF ? 0 : buf + 1;
-        read(f0, nbuf, 0);
-        copy_step(ks + NBUF, buf);
-        multiply(f1);
-        buf = nbuf;
+    typedef std::integral_constant<int, 0> C0;
+    typedef std::integral_constant<int, NC / 2> CH;
+    typedef std::integral_constant<int, NC> CN;
+    // (copies of step ks + NBUF: the first half behind step ks's barrier, the rest in the step after)
+    int last = 0;                                                   // buffer of the step before
+    if (nk > NBUF) {
+        half_step(f0, f1, 0, 1, 0, 0, C0{}, C0{});
+        for (;;) {
+            wait_steps(std::integral_constant<int, NBUF - 2>{});
+            lds_barrier();
+            const int nbuf = buf + 1 == NBUF ? 0 : buf + 1;
+            half_step(f1, f0, nbuf, 0, ks + NBUF, buf, C0{}, CH{});
+            last = buf; buf = nbuf;
+            ++ks;
+            half_step(f0, f1, buf, 1, ks + NBUF - 1, last, CH{}, CN{});
+            if (ks >= nk - NBUF) break;
+        }
+    } else {
+        half_step(f0, f1, 0, 1, 0, 0, C0{}, C0{});
     }
-    for (; ks < nk; ++ks) {                                         // nothing more to ask for
-        read(f1, buf, 1);
-        multiply(f0);
+    for (;; ++ks) {                                                 // nothing more to ask for
         dev::dma_wait<0>();
         lds_barrier();
         buf = buf + 1 == NBUF ? 0 : buf + 1;
-        read(f0, buf, 0);                                           // (past the end: not used)
-        multiply(f1);
+        half_step(f1, f0, buf, 0, 0, 0, C0{}, C0{});                // (past the end: not used)
+        if (ks == nk - 1) break;
+        half_step(f0, f1, buf, 1, 0, 0, C0{}, C0{});
     }
-    __syncthreads();                                                // the buffers are dead
-
+    // From here on a wave is on its own.
     if constexpr (SK == 2) {
+        // Both waves that hold a sum's halves leave theirs in the workspace (past the L2s, which are not coherent), and
+        // the one that arrives second, which finds the other's complete, goes on.
+        constexpr int NP = XB * 2 * PB;
         const int tile = rt * nct + ct;
-        int* const sm_last = reinterpret_cast<int*>(smem);
-        // a tile's accumulators as runs of 512 bytes: 8 bytes per lane and store
-        constexpr int NP2 = XB * 4 * PB;
-        float* mine = a.ws_partials + ((size_t)(tile * SK + part) * 8 + wave) * (BM * 16) + lane * 2;
+        float* const mine = a.ws_partials + ((size_t)(tile * SK + part) * 8 + wave) * (BM * 16) + lane * 2;
+        const float* const theirs = a.ws_partials + ((size_t)(tile * SK + (part ^ 1)) * 8 + wave) * (BM * 16) + lane * 2;
 #pragma unroll
-        for (int i = 0; i < NP2; ++i) {
+        for (int i = 0; i < 2 * NP; ++i) {          // (runs of 512 bytes: with each half of a lane's 16 bytes apart half as fast)
             const f32x4& v = acc[i / (4 * PB)][i / 2 % (2 * PB)];
             dev::st_agent2(mine + i * 128, v[2 * (i & 1)], v[2 * (i & 1) + 1]);
         }
-        int32_t* counter = a.ws_counters + (size_t)tile * kDecodeCounterStride;
-        if (!dev::arrive_at(counter, SK, sm_last)) return;
-        dev::reset_counter_at(counter);
-        const float* theirs = a.ws_partials + ((size_t)(tile * SK + (part ^ 1)) * 8 + wave) * (BM * 16) + lane * 2;
-        float2 o[NP2];
+        if (!dev::wave_arrives_last(a.ws_counters + (size_t)tile * kDecodeCounterStride + wave, SK)) return;
+        float2 o[2 * NP];
 #pragma unroll
-        for (int i = 0; i < NP2; ++i) o[i] = dev::ld_agent2(theirs + i * 128);
+        for (int i = 0; i < 2 * NP; ++i) o[i] = dev::ld_agent2(theirs + i * 128);
 #pragma unroll
-        for (int i = 0; i < NP2; ++i) {
+        for (int i = 0; i < 2 * NP; ++i) {
             f32x4& v = acc[i / (4 * PB)][i / 2 % (2 * PB)];
             v[2 * (i & 1)] += o[i].x; v[2 * (i & 1) + 1] += o[i].y;
         }
-        __syncthreads();
     }
 
-    // epilogue: lane holds tokens 16 (XB wm + mi) + 4 g4 + i, features 16 (PB wn + p) + c16 and 64 further
-    uint16_t* const ot = reinterpret_cast<uint16_t*>(smem);
-    RowDest* const sm_dest = reinterpret_cast<RowDest*>(smem + BM * OSTR * 2);
-    if (tid < BM) sm_dest[tid] = my_dest;
-    __syncthreads();
+    // lane: token 16 (XB wm + mi) + c16, features j0 .. j0 + 4 PB - 1 and 64 further, 4 PB in a row each
+    uint16_t* const out = reinterpret_cast<uint16_t*>(kv == 0 ? a.k_out : a.v_out) + (size_t)head * a.token_stride * D + j0;
 #pragma unroll
-    for (int p = 0; p < PB; ++p) {
-        const int j = 16 * (PB * wn + p) + c16;
-        const RopeEntry re = a.rope[j];
+    for (int mi = 0; mi < XB; ++mi) {
+        const RowDest d = sm_dest[16 * (XB * wm + mi) + c16];
+        uint32_t lo[2 * PB], hi[2 * PB];
 #pragma unroll
-        for (int mi = 0; mi < XB; ++mi)
+        for (int p = 0; p < PB; ++p)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int r = 16 * (XB * wm + mi) + 4 * g4 + i;
-                float lo = acc[mi][p][i], hi = acc[mi][PB + p][i];
-                if (kv == 0) {
-                    float c, s;
-                    rope_cs(re, sm_dest[r].pos, c, s);
-                    const float k0 = lo * c - hi * s;
-                    const float k1 = lo * s + hi * c;
-                    lo = k0; hi = k1;
+            for (int i = 0; i < 4; i += 2) {
+                float l[2], h[2];
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    l[k] = acc[mi][p][i + k]; h[k] = acc[mi][PB + p][i + k];
+                    if (kv == 0) {
+                        float c, s;
+                        rope_cs(turns[4 * p + i + k].x, turns[4 * p + i + k].y, d.pos, c, s);
+                        const float k0 = l[k] * c - h[k] * s;
+                        const float k1 = l[k] * s + h[k] * c;
+                        l[k] = k0; h[k] = k1;
+                    }
                 }
-                ot[r * OSTR + j] = f32_to_bf16_rne(lo);
-                ot[r * OSTR + j + 64] = f32_to_bf16_rne(hi);
+                lo[2 * p + i / 2] = dev::pack_bf16(l[0], l[1]);
+                hi[2 * p + i / 2] = dev::pack_bf16(h[0], h[1]);
             }
-    }
-    __syncthreads();
-    // whole rows out: sixteen lanes write one row of 256 bytes
-    uint16_t* out = reinterpret_cast<uint16_t*>(kv == 0 ? a.k_out : a.v_out) + (size_t)head * a.token_stride * D;
-#pragma unroll
-    for (int i = 0; i < MI; ++i) {
-        const int r = 32 * i + (tid >> 4), c = 8 * (tid & 15);
-        const RowDest d = sm_dest[r];
-        if (d.valid) *reinterpret_cast<uint4*>(out + d.elem_off + c) = *reinterpret_cast<const uint4*>(ot + r * OSTR + c);
+        if (!d.valid) continue;
+        uint16_t* const o = out + d.elem_off;
+        if constexpr (PB == 1) {
+            *reinterpret_cast<uint2*>(o) = make_uint2(lo[0], lo[1]);
+            *reinterpret_cast<uint2*>(o + 64) = make_uint2(hi[0], hi[1]);
+        } else {
+            *reinterpret_cast<uint4*>(o) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+            *reinterpret_cast<uint4*>(o + 64) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+        }
     }
 }
 
@@ -313,33 +353,38 @@ hipError_t launch_tile(const MaterializeArgs& a, int total_rows, hipStream_t s) 
 }
 
 // Tile height.  One workgroup fills a compute unit's LDS, a launch is as long as its slowest
-// compute unit, and a workgroup's time grows slower than its height (hidden 4096, us: two workgroups
-// per tile of 32 / 64 / 96 / 128 rows 17 / 21 / 24 / 28, one per tile of 96 / 128 / 192 / 256 rows
-// 33 / 38 / 47 / 57): so the smallest height that gives no compute unit two workgroups, hidden axis
-// halved while that holds; beyond one full round the height with the smallest rounds x (4 + MI), which
-// is what those times follow (6000 rows: 192-row tiles 103 us, 128 rows 119, 256 rows 117).
+// compute unit, and a workgroup's time grows slower than its height: so the smallest height that gives no compute unit two
+// workgroups, hidden axis halved while that holds.  Up to 128 rows two workgroups per tile are ahead at every width; taller
+// tiles leave the chip fewer bytes to fetch, but more partials to exchange, and pay from hidden 8192 on (us, one workgroup per tile
+// of fewer rows -> two per taller tile: hidden 8192 1206 rows 59.9 -> 50.3, 2000 rows 71.0 -> 66.7; hidden 4096 1206 rows 29.7 -> 30.3,
+// 2000 rows 39.0 -> 40.7).  Beyond one full round the height with the smallest rounds x (4 + MI), which
+// is what the times follow (hidden 4096, tiles of 128 / 160 / 192 / 256 rows: 2500 rows 72 / 47 / 49 / 56 us, 3501 rows 76 / 86 / 94 / 58).
 hipError_t launch_tiled(const MaterializeArgs& a, int total_rows, hipStream_t s) {
     const int nct = 2 * a.Hkv;
     auto groups = [&](int mi) { return nct * ((total_rows + 32 * mi - 1) / (32 * mi)); };
     auto halved = [&](int mi) {
         const int64_t tiles = groups(mi);
-        return (a.Hd % (2 * BK)) == 0 && tiles * 2 <= 256 && a.ws_partials && tiles * 2 * (32 * mi) * D <= a.ws_partial_floats &&
-               tiles * kDecodeCounterStride <= a.ws_n_counters;
+        return (a.Hd % (2 * BK)) == 0 && tiles * 2 <= 256 && (mi <= 4 || a.Hd >= 8192) && a.ws_partials &&
+               tiles * 2 * (32 * mi) * D <= a.ws_partial_floats && tiles * kDecodeCounterStride <= a.ws_n_counters;
     };
     if (halved(1)) return launch_tile<1, 4, 2>(a, total_rows, s);
     if (halved(2)) return launch_tile<2, 4, 2>(a, total_rows, s);
     if (halved(3)) return launch_tile<3, 4, 2>(a, total_rows, s);
-    if (halved(4)) return launch_tile<4, 4, 2>(a, total_rows, s);
+    if (halved(4)) return launch_tile<4, 2, 2>(a, total_rows, s);
+    if (halved(5)) return launch_tile<5, 4, 2>(a, total_rows, s);
+    if (halved(6)) return launch_tile<6, 2, 2>(a, total_rows, s);
+    if (halved(8)) return launch_tile<8, 2, 2>(a, total_rows, s);
     int best = 3;
     long best_cost = -1;
-    for (int mi : {3, 4, 6, 8}) {
+    for (int mi : {3, 4, 5, 6, 8}) {
         const long cost = (long)((groups(mi) + 255) / 256) * (4 + mi);
         if (best_cost < 0 || cost < best_cost) { best = mi; best_cost = cost; }
     }
     switch (best) {
         case 3: return launch_tile<3, 4, 1>(a, total_rows, s);
-        case 4: return launch_tile<4, 4, 1>(a, total_rows, s);
-        case 6: return launch_tile<6, 4, 1>(a, total_rows, s);
+        case 4: return launch_tile<4, 2, 1>(a, total_rows, s);
+        case 5: return launch_tile<5, 4, 1>(a, total_rows, s);
+        case 6: return launch_tile<6, 2, 1>(a, total_rows, s);
         default: return launch_tile<8, 2, 1>(a, total_rows, s);
     }
 }

@@ -252,6 +252,37 @@ def test_materialize_tile_heights(hidden, T, Hkv):
         ctx.close()
 
 
+@pytest.mark.parametrize("hidden,T", [(8192, 1025), (8192, 1281), (8192, 1537), (8192, 2048), (512, 2300)])
+def test_materialize_tall_tiles(hidden, T):
+    """Tiles of 160, 192 and 256 rows with two workgroups per tile (hidden 8192, just past the row count where the
+    height before ends, and the last that has them) and of 160 rows with one.  Rows at the tiles' edges and some
+    between, each against the oracle; the second run finds the arrival counters at zero again."""
+    Hkv, pos0 = 8, 50
+    case = Case("bf16-tall-tiles", n_layers=1, Hq=Hkv, Hkv=Hkv, D=128, hidden=hidden, dtype="bf16",
+                chunk_lens={0: 8}, retrieved=[[0]], q_lens=[1], steps=255, rope_base=500000.0, scale=1.0 / 4.0)
+    from workload import normal, to_f64
+    import oracle
+    ctx = chain.make_context(case)
+    try:
+        with torch.cuda.stream(ctx.compute_stream):
+            w = normal(("tall", hidden, "w"), (2, Hkv * 128, hidden), hidden ** -0.5, torch.bfloat16).cuda()
+            x = normal(("tall", hidden, "x", T), (T, hidden), 1.0, torch.bfloat16).cuda()
+            k = torch.zeros((Hkv, T + 3, 128), dtype=torch.bfloat16, device="cuda")
+            v = torch.zeros_like(k)
+            for _ in range(2):
+                ctx.materialize(x, w[0], w[1], T, pos0, k, v, T + 3)
+            ctx.compute_stream.synchronize()
+        assert not k[:, T:].any() and not v[:, T:].any()        # rows past the last are not written
+        wk, wv = to_f64(w[0]), to_f64(w[1])
+        edges = {r + e for h in (160, 192, 256) for r in range(0, T, h) for e in (-1, 0)} | set(range(7, T, 97)) | {T - 1}
+        for r in sorted(r for r in edges if 0 <= r < T):
+            K, V = oracle.materialize(to_f64(x[r:r + 1]), wk, wv, Hkv, 128, float(pos0 + r), 500000.0)
+            chain.compare_materialized(case, k[:, r:r + 1].cpu(), K, f"K, hidden {hidden}, {T} rows, row {r}")
+            chain.compare_materialized(case, v[:, r:r + 1].cpu(), V, f"V, hidden {hidden}, {T} rows, row {r}")
+    finally:
+        ctx.close()
+
+
 def test_bf16_chain_batch17_decode_rows_on_matrix_cores():
     """Seventeen instances: the decode-token projection has 17 rows (skinny form, ragged second
     16-row block), the question projection 17 ragged groups of rows."""
