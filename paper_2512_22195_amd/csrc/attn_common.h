@@ -344,13 +344,13 @@ __device__ __forceinline__ void reset_counter(const KernelArgs& a, int cidx) { d
 // unit's partial, written with agent-scope stores (coherent across the chip's L2 slices; no
 // L2 write-back or invalidate is involved), followed by the workgroup's arrival.  Returns true
 // in the workgroup that arrived last of `expected`: it then folds all partials (merge_dispatch)
-// and resets the counter.
-template <typename T, int D, int NT, int NS, int ROWS, int ACC_STRIDE, typename MapFn>
+// and resets the counter.  WAVE_STRIDE: floats between two waves' accumulators.
+template <typename T, int D, int NT, int NS, int ROWS, int ACC_STRIDE, int WAVE_STRIDE = ROWS * ACC_STRIDE, typename MapFn>
 __device__ __forceinline__ void publish_partial(const KernelArgs& a, const float* sm_acc, const float* sm_m,
                                                 const float* sm_l, int n_valid_rows, MapFn map) {
     constexpr int PSTRIDE = kPartialStride(D);
     const int tid = threadIdx.x;
-    __syncthreads();
+    lds_barrier();                                            // (global stores may still be on their way)
 
     const int cols_valid = n_valid_rows * (D / 2);            // valid rows are a prefix of the local rows
     for (int col = tid; col < cols_valid; col += NT) {
@@ -363,7 +363,7 @@ __device__ __forceinline__ void publish_partial(const KernelArgs& a, const float
 #pragma unroll
         for (int w = 0; w < NS; ++w) {
             const float c = fast_exp2(sm_m[w * ROWS + i] - mn);
-            const float* src = sm_acc + ((size_t)w * ROWS + i) * ACC_STRIDE + d;
+            const float* src = sm_acc + (size_t)w * WAVE_STRIDE + (size_t)i * ACC_STRIDE + d;
             ax = fmaf(src[0], c, ax);
             ay = fmaf(src[1], c, ay);
             lv = fmaf(sm_l[w * ROWS + i], c, lv);
@@ -375,20 +375,20 @@ __device__ __forceinline__ void publish_partial(const KernelArgs& a, const float
     }
 }
 
-template <typename T, int D, int NW, int NS, int ROWS, int ACC_STRIDE, typename MapFn>
+template <typename T, int D, int NW, int NS, int ROWS, int ACC_STRIDE, int WAVE_STRIDE = ROWS * ACC_STRIDE, typename MapFn>
 __device__ __forceinline__ bool publish_unit(const KernelArgs& a, int cidx, int expected,
                                              const float* sm_acc, const float* sm_m, const float* sm_l,
                                              int* sm_last, int n_valid_rows, MapFn map) {
-    publish_partial<T, D, NW * 64, NS, ROWS, ACC_STRIDE>(a, sm_acc, sm_m, sm_l, n_valid_rows, map);
+    publish_partial<T, D, NW * 64, NS, ROWS, ACC_STRIDE, WAVE_STRIDE>(a, sm_acc, sm_m, sm_l, n_valid_rows, map);
     return arrive(a, cidx, expected, sm_last);
 }
 
-template <typename T, int D, int NW, int NS, int ROWS, int ACC_STRIDE, typename MapFn>
+template <typename T, int D, int NW, int NS, int ROWS, int ACC_STRIDE, int WAVE_STRIDE = ROWS * ACC_STRIDE, typename MapFn>
 __device__ __forceinline__ void finish_unit(const KernelArgs& a, const Unit& unit, int kvh, int zidx,
                                             const float* sm_acc, const float* sm_m, const float* sm_l,
                                             int* sm_last, int n_valid_rows, MapFn map) {
     const int cidx = counter_index(a, unit.inst, kvh, zidx);
-    if (!publish_unit<T, D, NW, NS, ROWS, ACC_STRIDE>(a, cidx, unit.n_units_inst, sm_acc, sm_m, sm_l, sm_last, n_valid_rows, map))
+    if (!publish_unit<T, D, NW, NS, ROWS, ACC_STRIDE, WAVE_STRIDE>(a, cidx, unit.n_units_inst, sm_acc, sm_m, sm_l, sm_last, n_valid_rows, map))
         return;
     merge_dispatch<T, D, NW * 64>(a, unit.unit0_inst, unit.n_units_inst, n_valid_rows * (D / 2), map);
     reset_counter(a, cidx);

@@ -17,6 +17,8 @@
 //                   B = P rounded to bf16, already sitting in operand layout
 // Waves of a workgroup split the unit's tokens; workgroups split the cache; merging is the
 // same as in the plain-ALU kernel.
+#include <type_traits>
+
 #include "attn_common.h"
 #include "gemv_common.h"
 
@@ -55,32 +57,81 @@ struct StepArgs {
     int32_t n_units;            // workgroups of a KV head that walk the cache; those beyond only project
 };
 
+// The NS waves' states of a decode tile's rows (accumulators WS floats apart) to the workgroup's partials, with agent-scope
+// stores.  A wave takes RB rows at a time, lane l the dims 2l, 2l + 1: where a row goes is then the same for all lanes, and everything it
+// needs of LDS is read at once.  (By columns over all threads, as the fallback prefill does it, it took 1 us of a step.)
+template <int NWV, int NS, int ROWS, int WS, int RB, typename MapFn>
+__device__ __forceinline__ void publish_rows(const KernelArgs& a, const float* sm_acc, const float* sm_m, const float* sm_l, int n_rows,
+                                             MapFn map, int wave, int lane) {
+    lds_barrier();                                      // (global stores may still be on their way)
+    for (int i0 = wave; i0 < n_rows; i0 += NWV * RB) {
+        float m[RB][NS], l[RB][NS];
+        float2 v[RB][NS];
+        float* prow[RB];
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            const int i = min(i0 + NWV * r, n_rows - 1);
+#pragma unroll
+            for (int w = 0; w < NS; ++w) {
+                m[r][w] = sm_m[w * ROWS + i];
+                l[r][w] = sm_l[w * ROWS + i];
+                v[r][w] = *reinterpret_cast<const float2*>(sm_acc + w * WS + i * ACCS + 2 * lane);
+            }
+            const RowMap rm = map(i);
+            prow[r] = a.partials + ((size_t)(rm.unit_slot >= 0 ? rm.unit_slot : (int)blockIdx.x) * a.Hq + rm.head) * kPartialStride(D);
+        }
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            float mn = m[r][0];
+#pragma unroll
+            for (int w = 1; w < NS; ++w) mn = fmaxf(mn, m[r][w]);
+            float ax = 0.f, ay = 0.f, lv = 0.f;
+#pragma unroll
+            for (int w = 0; w < NS; ++w) {
+                const float c = fast_exp2(m[r][w] - mn);
+                ax = fmaf(v[r][w].x, c, ax);
+                ay = fmaf(v[r][w].y, c, ay);
+                lv = fmaf(l[r][w], c, lv);
+            }
+            if (RB > 1 && i0 + NWV * r >= n_rows) break;
+            st_agent2(prow[r] + 2 * lane, ax, ay);
+            if (lane == 0) st_agent2(prow[r] + D, mn, lv);
+        }
+    }
+}
+
 // Folding the partials of a decode launch.  A wave takes RB output rows (an instance's newest token, one
-// query head) at a time, lane l the dims 2l, 2l+1.  Per pass of UPC units lane k fetches the (maximum, sum)
-// of unit k of every row, and all loads of the pass are requested before anything is consumed: one memory
-// round trip for UPC units of RB rows.  The wave agrees on the maximum, every lane has the weight of its
-// unit, and the weights reach the accumulators through lane reads.  (Until every lane fetched every unit's
-// pair itself, a pass had twice the loads, and a weight's exponential was taken in all lanes.)
+// query head) at a time; its lower half takes the even units, its upper half the odd ones, lane l of a half the dims
+// 4l .. 4l + 3.  Per pass of UPC units lane k fetches the (maximum, sum) of unit k of every row, and all loads of the pass are
+// requested before anything is consumed: one memory round trip for UPC units of RB rows, in 16-byte loads (loads past the L2s
+// leave one after the other: 32 units of a row 1.6 us in 8-byte ones).  The wave agrees on the maximum, every lane has the
+// weight of its unit and hands it to the half that needs it.
 // src[i]: partial of row i's first unit; n[i]: its units (0: row not taken); ustride: floats between units.
-template <int RB, int UPC>
-__device__ __forceinline__ void fold_partials(const float* const (&src)[RB], const int (&n)[RB], size_t ustride, int lane,
-                                              float (&M)[RB], float (&L)[RB], float (&ox)[RB], float (&oy)[RB]) {
-    static_assert(UPC <= 64, "a lane per unit");
+// meanwhile(): done while the first pass's loads are on their way.
+template <int RB, int UPC, typename F>
+__device__ __forceinline__ void fold_partials(const float* const (&src)[RB], const int (&n)[RB], uint32_t ustride, int lane,
+                                              float (&M)[RB], float (&L)[RB], float4 (&o)[RB], F meanwhile) {
+    static_assert(UPC <= 64 && UPC % 2 == 0, "a lane per unit, two units a load");
+    const int half = lane >> 5, l32 = lane & 31;
     int nmax = 0;
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
         nmax = max(nmax, n[i]);
-        M[i] = kNegBig; L[i] = 0.f; ox[i] = 0.f; oy[i] = 0.f;
+        M[i] = kNegBig; L[i] = 0.f; o[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
     for (int u0 = 0; u0 < nmax; u0 += UPC) {
-        float2 av[RB][UPC], ml[RB];
+        float4 av[RB][UPC / 2];
+        float2 ml[RB];
+#pragma unroll
+        for (int i = 0; i < RB; ++i) ml[i] = ld_agent2(src[i] + (size_t)min(u0 + lane, max(n[i], 1) - 1) * ustride + D);
 #pragma unroll
         for (int i = 0; i < RB; ++i) {
-            const int top = max(n[i], 1) - 1;           // (past a row's units: its last one again)
-            ml[i] = ld_agent2(src[i] + (size_t)min(u0 + lane, top) * ustride + D);
+            const uint32_t top = (uint32_t)(max(n[i], 1) - 1) * ustride * 4;        // (past a row's units: its last one again)
+            uint32_t off = (uint32_t)(u0 + half) * ustride * 4;
 #pragma unroll
-            for (int k = 0; k < UPC; ++k) av[i][k] = ld_agent2(src[i] + (size_t)min(u0 + k, top) * ustride + 2 * lane);
+            for (int k = 0; k < UPC / 2; ++k, off += 8 * ustride) av[i][k] = dev::ld_agent4(src[i], min(off, top) + 16 * l32);
         }
+        if (u0 == 0) meanwhile();
 #pragma unroll
         for (int i = 0; i < RB; ++i) {
             const bool own = lane < UPC && u0 + lane < n[i];
@@ -88,16 +139,26 @@ __device__ __forceinline__ void fold_partials(const float* const (&src)[RB], con
             const float w = own ? fast_exp2(ml[i].x - mn) : 0.f;
             const float cold = fast_exp2(M[i] - mn);
             L[i] = fmaf(L[i], cold, gemv::wave_sum(w * ml[i].y, lane));
-            ox[i] *= cold; oy[i] *= cold;
+            o[i].x *= cold; o[i].y *= cold; o[i].z *= cold; o[i].w *= cold;
             M[i] = mn;
+            const int wi = __float_as_int(w);
 #pragma unroll
-            for (int k = 0; k < UPC; ++k) {
-                const float c = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), k));
-                ox[i] = fmaf(av[i][k].x, c, ox[i]);
-                oy[i] = fmaf(av[i][k].y, c, oy[i]);
+            for (int k = 0; k < UPC / 2; ++k) {
+                const float c = __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (2 * k + half), wi));
+                o[i].x = fmaf(av[i][k].x, c, o[i].x); o[i].y = fmaf(av[i][k].y, c, o[i].y);
+                o[i].z = fmaf(av[i][k].z, c, o[i].z); o[i].w = fmaf(av[i][k].w, c, o[i].w);
             }
         }
     }
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {                      // the halves' sums together, in either
+        o[i].x += lane_xor(o[i].x, 32, lane); o[i].y += lane_xor(o[i].y, 32, lane);
+        o[i].z += lane_xor(o[i].z, 32, lane); o[i].w += lane_xor(o[i].w, 32, lane);
+    }
+}
+// One row out, from the lower half of a wave.
+__device__ __forceinline__ void store_row(const KernelArgs& a, size_t row, int lane, const float4& o, float inv) {
+    if (lane < 32) store_out4(a.out, a.out_f32, row * D + 4 * lane, make_float4(o.x * inv, o.y * inv, o.z * inv, o.w * inv));
 }
 
 // Last arrival at (instance, KV head) of a plain decode launch: NWV waves fold the G rows.
@@ -106,19 +167,19 @@ __device__ __forceinline__ void merge_decode(const KernelArgs& a, const Unit& un
     constexpr int PSTRIDE = kPartialStride(D), RB = (G + NWV - 1) / NWV;
     const float* src[RB];
     int n[RB];
-    float M[RB], L[RB], ox[RB], oy[RB];
+    float M[RB], L[RB];
+    float4 o[RB];
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
         const int g = wave + NWV * i;
         n[i] = g < G ? unit.n_units_inst : 0;
         src[i] = a.partials + ((size_t)unit.unit0_inst * a.Hq + kvh * G + min(g, G - 1)) * PSTRIDE;
     }
-    fold_partials<RB, UPC>(src, n, (size_t)a.Hq * PSTRIDE, lane, M, L, ox, oy);
+    fold_partials<RB, UPC>(src, n, (uint32_t)a.Hq * PSTRIDE, lane, M, L, o, []() {});
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
         if (n[i] == 0) continue;
-        const float inv = 1.0f / L[i];
-        store_out2(a.out, a.out_f32, ((size_t)unit.inst * a.Hq + kvh * G + wave + NWV * i) * D + 2 * lane, ox[i] * inv, oy[i] * inv);
+        store_row(a, (size_t)unit.inst * a.Hq + kvh * G + wave + NWV * i, lane, o[i], 1.0f / L[i]);
     }
 }
 
@@ -126,46 +187,62 @@ __device__ __forceinline__ void merge_decode(const KernelArgs& a, const Unit& un
 // workgroup arrived last, the units' partials and the newest token into the G output rows - all such
 // instances at once.  The newest token's K/V row is read back from the tail cache, where the projection
 // waves left it with agent-scope stores; its score is a 64-lane dot product, and it enters as one more
-// contribution of weight 1.
+// contribution of weight 1.  What a wave's rows are is looked up before the workgroup arrives.
+template <int G, int NWV, int RB>
+struct StepRows {
+    const float* src[RB];
+    int n[RB], b[RB];
+    uint32_t qw[RB];
+    size_t toff[RB], row[RB];
+    __device__ __forceinline__ StepRows(const KernelArgs& a, const InstanceInfo* __restrict__ insts, int batch, int kvh, int wave, int lane) {
+        const int rows = batch * G;
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+            const int r = min(wave + NWV * i, rows - 1), head = kvh * G + r % G;
+            b[i] = r / G;
+            const InstanceInfo inst = insts[b[i]];
+            n[i] = wave + NWV * i < rows ? inst.n_dunits : 0;
+            src[i] = a.partials + ((size_t)inst.dunit0 * a.Hq + head) * kPartialStride(D);
+            toff[i] = (((size_t)b[i] * a.Hkv + kvh) * (size_t)a.max_tail + (size_t)max(inst.tail_len - 1, 0)) * D;
+            row[i] = (size_t)b[i] * a.Hq + head;
+            qw[i] = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint16_t*>(a.q) + row[i] * D + 2 * lane);
+        }
+    }
+};
 template <int G, int NWV, int RB, int UPC>
-__device__ __forceinline__ void merge_decode_step(const KernelArgs& a, const InstanceInfo* __restrict__ insts, int batch,
-                                                  const int* lastv, int kvh, int wave, int lane) {
+__device__ __forceinline__ void merge_decode_step(const KernelArgs& a, const StepRows<G, NWV, RB>& rows, const int* lastv, int lane) {
     typedef uint16_t T;
-    constexpr int PSTRIDE = kPartialStride(D);
-    const int rows = batch * G, d = 2 * lane;
-    for (int r0 = wave; r0 < rows; r0 += NWV * RB) {
-        const float* src[RB];
-        int n[RB];
-        uint32_t kw[RB], vw[RB], qw[RB];
-        size_t oidx[RB];
-        float M[RB], L[RB], ox[RB], oy[RB];
+    int n[RB], any = 0;
 #pragma unroll
-        for (int i = 0; i < RB; ++i) {
-            const int r = min(r0 + NWV * i, rows - 1), b = r / G, head = kvh * G + r % G;
-            const InstanceInfo inst = insts[b];
-            n[i] = r0 + NWV * i < rows && lastv[b] ? inst.n_dunits : 0;
-            src[i] = a.partials + ((size_t)inst.dunit0 * a.Hq + head) * PSTRIDE;
-            const size_t toff = (((size_t)b * a.Hkv + kvh) * (size_t)a.max_tail + (size_t)max(inst.tail_len - 1, 0)) * D + d;
-            kw[i] = __hip_atomic_load(reinterpret_cast<const uint32_t*>(reinterpret_cast<const T*>(a.tail_k) + toff),
-                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            vw[i] = __hip_atomic_load(reinterpret_cast<const uint32_t*>(reinterpret_cast<const T*>(a.tail_v) + toff),
-                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            oidx[i] = ((size_t)b * a.Hq + head) * D + d;
-            qw[i] = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const T*>(a.q) + oidx[i]);
-        }
-        fold_partials<RB, UPC>(src, n, (size_t)a.Hq * PSTRIDE, lane, M, L, ox, oy);
+    for (int i = 0; i < RB; ++i) { n[i] = __builtin_amdgcn_readfirstlane(lastv[rows.b[i]]) ? rows.n[i] : 0; any |= n[i]; }
+    if (any == 0) return;
+    uint32_t kw[RB];
+    uint64_t vw[RB];
+    float M[RB], L[RB], sx[RB];
+    float4 o[RB];
 #pragma unroll
-        for (int i = 0; i < RB; ++i) {
-            if (n[i] == 0) continue;
-            const float sx = gemv::wave_sum(gemv::dot2(qw[i], kw[i], 0.f), lane) * a.scale_log2e;
-            const float mn = fmaxf(M[i], sx);
-            const float cold = fast_exp2(M[i] - mn), cx = fast_exp2(sx - mn);
-            const float l = fmaf(L[i], cold, cx);
-            const float x = fmaf(ox[i], cold, __uint_as_float(vw[i] << 16) * cx);
-            const float y = fmaf(oy[i], cold, __uint_as_float(vw[i] & 0xffff0000u) * cx);
-            const float inv = 1.0f / l;
-            store_out2(a.out, a.out_f32, oidx[i], x * inv, y * inv);
-        }
+    for (int i = 0; i < RB; ++i) {
+        kw[i] = __hip_atomic_load(reinterpret_cast<const uint32_t*>(reinterpret_cast<const T*>(a.tail_k) + rows.toff[i] + 2 * lane),
+                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        vw[i] = __hip_atomic_load(reinterpret_cast<const uint64_t*>(reinterpret_cast<const T*>(a.tail_v) + rows.toff[i] + 4 * (lane & 31)),
+                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    fold_partials<RB, UPC>(rows.src, n, (uint32_t)a.Hq * kPartialStride(D), lane, M, L, o, [&]() {
+#pragma unroll
+        for (int i = 0; i < RB; ++i) sx[i] = gemv::wave_sum(gemv::dot2(rows.qw[i], kw[i], 0.f), lane) * a.scale_log2e;
+    });
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+        if (n[i] == 0) continue;
+        const float mn = fmaxf(M[i], sx[i]);
+        const float cold = fast_exp2(M[i] - mn), cx = fast_exp2(sx[i] - mn);
+        const float l = fmaf(L[i], cold, cx);
+        const uint32_t v01 = (uint32_t)vw[i], v23 = (uint32_t)(vw[i] >> 32);
+        o[i].x = fmaf(o[i].x, cold, __uint_as_float(v01 << 16) * cx);
+        o[i].y = fmaf(o[i].y, cold, __uint_as_float(v01 & 0xffff0000u) * cx);
+        o[i].z = fmaf(o[i].z, cold, __uint_as_float(v23 << 16) * cx);
+        o[i].w = fmaf(o[i].w, cold, __uint_as_float(v23 & 0xffff0000u) * cx);
+        store_row(a, rows.row[i], lane, o[i], 1.0f / l);
     }
 }
 
@@ -216,22 +293,22 @@ __device__ __forceinline__ void merge_shared(const KernelArgs& a, const int4* us
     for (int r0 = wave; r0 < rows; r0 += NWV * RB) {
         const float* src[RB];
         int n[RB];
-        size_t oidx[RB];
-        float M[RB], L[RB], ox[RB], oy[RB];
+        size_t row[RB];
+        float M[RB], L[RB];
+        float4 o[RB];
 #pragma unroll
         for (int i = 0; i < RB; ++i) {
             const int r = min(r0 + NWV * i, rows - 1), head = kvh * G + r % G;
             const int4 us = users[live[r / G]];
             n[i] = r0 + NWV * i < rows ? __builtin_amdgcn_readfirstlane(us.w) : 0;
-            src[i] = a.partials + ((size_t)us.z * a.Hq + head) * PSTRIDE;           // decode: one row per slot
-            oidx[i] = ((size_t)us.x * a.Hq + head) * D + 2 * lane;
+            src[i] = a.partials + ((size_t)__builtin_amdgcn_readfirstlane(us.z) * a.Hq + head) * PSTRIDE;           // decode: one row per slot
+            row[i] = (size_t)us.x * a.Hq + head;
         }
-        fold_partials<RB, UPC>(src, n, (size_t)a.Hq * PSTRIDE, lane, M, L, ox, oy);
+        fold_partials<RB, UPC>(src, n, (uint32_t)a.Hq * PSTRIDE, lane, M, L, o, []() {});
 #pragma unroll
         for (int i = 0; i < RB; ++i) {
             if (n[i] == 0) continue;
-            const float inv = 1.0f / L[i];
-            store_out2(a.out, a.out_f32, oidx[i], ox[i] * inv, oy[i] * inv);
+            store_row(a, row[i], lane, o[i], 1.0f / L[i]);
         }
     }
 }
@@ -302,10 +379,10 @@ __global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && 
         for (int s = 0; s < 8; ++s) ot[j][s] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 
-    // LDS: per-wave V strips during the walk, the merge buffer afterwards (same bytes).
-    constexpr int V_BYTES = NW * BLK * VSTR * 2;
-    constexpr int ACC_BYTES = NW * ROWS * ACCS * 4;
-    __shared__ __attribute__((aligned(16))) char smem[V_BYTES > ACC_BYTES ? V_BYTES : ACC_BYTES];
+    // LDS: per-wave V strips during the walk, the waves' finished states afterwards, each over its own wave's strip.
+    constexpr int V_BYTES = BLK * VSTR * 2, ACC_BYTES = ROWS * ACCS * 4;
+    constexpr int WAVE_BYTES = V_BYTES > ACC_BYTES ? V_BYTES : ACC_BYTES, WS = WAVE_BYTES / 4;
+    __shared__ __attribute__((aligned(16))) char smem[NW * WAVE_BYTES];
     __shared__ float sm_m[NW * ROWS], sm_l[NW * ROWS];
 
     // shared unit: its users with their slot ranges, for the publishing and folding at the end
@@ -350,7 +427,7 @@ __global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && 
         vis[j] = (a.prefill && !SH) ? r + 1 : tail_len;
     }
 
-    uint16_t* const vstrip = reinterpret_cast<uint16_t*>(smem) + (size_t)wave * BLK * VSTR;
+    uint16_t* const vstrip = reinterpret_cast<uint16_t*>(smem + wave * WAVE_BYTES);
 
     // One block's loads in registers.  Plain rows: lane (c16, g4) holds, per 16-token half, the
     // 8 dims of each of the 4 chunks of its token row, and 8 V rows' worth of 8 dims.  Code rows
@@ -527,13 +604,12 @@ __global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && 
     }
     }   // attention waves
 
-    // ---- per-wave states to LDS (the strips are dead now), then the common merge ----
-    __syncthreads();                                    // every wave is done with its strip
+    // ---- per-wave states to LDS (the wave's strip is dead now), then the common merge ----
     float* const sm_acc = reinterpret_cast<float*>(smem);
     if (wave < NW && walks) {
 #pragma unroll
         for (int j = 0; j < MS; ++j) {
-            float* dst = sm_acc + ((size_t)wave * ROWS + 16 * j + c16) * ACCS + 4 * g4;
+            float* dst = sm_acc + wave * WS + (16 * j + c16) * ACCS + 4 * g4;
 #pragma unroll
             for (int s = 0; s < 8; ++s)
                 *reinterpret_cast<float4*>(dst + 16 * s) = make_float4(ot[j][s][0], ot[j][s][1], ot[j][s][2], ot[j][s][3]);
@@ -548,11 +624,11 @@ __global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && 
         rm.slot_row = (prefill && !SH) ? r : 0;
         rm.head = kvh * G + g;
         rm.q_row = prefill ? q_row0 + r : q_row0;
-        if (SH) { const int4 us = sm_users[r]; rm.q_row = us.x; rm.unit_slot = us.y; }
+        if (SH) { const int4 us = sm_users[r]; rm.q_row = us.x; rm.unit_slot = __builtin_amdgcn_readfirstlane(us.y); }      // (a wave has one row)
         return rm;
     };
     if constexpr (SH) {
-        publish_partial<T, D, NT, NW, ROWS, ACCS>(a, sm_acc, sm_m, sm_l, n_m, map);
+        publish_rows<NW, NW, ROWS, WS, 2>(a, sm_acc, sm_m, sm_l, n_m, map, wave, lane);
         // arrival at the counter of every user of this unit
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_s_waitcnt(0);
@@ -574,37 +650,46 @@ __global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && 
         else                  merge_shared<G, NW, 4, 8>(a, sm_users, sm_lastv, n_live, kvh, wave, lane);
     } else if constexpr (FR == 0) {
         if constexpr (MS > 1) {                         // (prefill tiles)
-            finish_unit<T, D, NW, NW, ROWS, ACCS>(a, unit, kvh, tile, sm_acc, sm_m, sm_l, &sm_last, min(ROWS, n_m - m0), map);
+            finish_unit<T, D, NW, NW, ROWS, ACCS, WS>(a, unit, kvh, tile, sm_acc, sm_m, sm_l, &sm_last, min(ROWS, n_m - m0), map);
         } else {
             const int cidx = counter_index(a, unit.inst, kvh, 0);
-            if (!publish_unit<T, D, NW, NW, ROWS, ACCS>(a, cidx, unit.n_units_inst, sm_acc, sm_m, sm_l, &sm_last, G, map)) return;
+            publish_rows<NW, NW, ROWS, WS, (G + NW - 1) / NW>(a, sm_acc, sm_m, sm_l, G, map, wave, lane);
+            if (!arrive(a, cidx, unit.n_units_inst, &sm_last)) return;
             if (unit.n_units_inst <= 8)       merge_decode<G, NW, 8>(a, unit, kvh, wave, lane);
             else if (unit.n_units_inst <= 16) merge_decode<G, NW, 16>(a, unit, kvh, wave, lane);
             else                              merge_decode<G, NW, (G + NW - 1) / NW <= 2 ? 32 : 16>(a, unit, kvh, wave, lane);   // (four rows x 32 units would not fit the registers)
             reset_counter(a, cidx);
         }
     } else {
-        if (walks) publish_partial<T, D, NT, NW, ROWS, ACCS>(a, sm_acc, sm_m, sm_l, G, map);      // (uniform)
-        // arrival at every instance's counter of this KV head
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        if (tid < f.batch) {
-            const int prev = __hip_atomic_fetch_add(&a.counters[counter_index(a, tid, kvh, 0)], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            sm_lastv[tid] = (prev == (int)gridDim.x - 1);
-        }
-        __syncthreads();
+        if (walks) publish_rows<NT / 64, NW, ROWS, WS, (G + NT / 64 - 1) / (NT / 64)>(a, sm_acc, sm_m, sm_l, G, map, wave, lane);      // (uniform)
+        // arrival at every instance's counter of this KV head, then the fold, in
         // one round trip where it fits: one row per wave, or two where the batch has more rows than the
         // workgroup has waves; units requested per row: the smallest of 8, 16, 32 that covers the partition
         // (an even cut: the batch's instances have at most n_units - batch + 1 units each)
         constexpr int NWV = NT / 64;
+        auto arrive_and_fold = [&](auto rb, auto fold) {
+            const StepRows<G, NWV, decltype(rb)::value> rows(a, insts, f.batch, kvh, wave, lane);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            __builtin_amdgcn_s_waitcnt(0);
+            __syncthreads();
+            if (tid < f.batch) {
+                const int prev = __hip_atomic_fetch_add(&a.counters[counter_index(a, tid, kvh, 0)], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                sm_lastv[tid] = (prev == (int)gridDim.x - 1);
+            }
+            __syncthreads();
+            fold(rows);
+        };
         if (FR == 1 || f.batch * G <= NWV) {            // (FR = 1: one instance)
-            if (f.n_units <= 8)       merge_decode_step<G, NWV, 1, 8>(a, insts, f.batch, sm_lastv, kvh, wave, lane);
-            else if (f.n_units <= 16) merge_decode_step<G, NWV, 1, 16>(a, insts, f.batch, sm_lastv, kvh, wave, lane);
-            else                      merge_decode_step<G, NWV, 1, 32>(a, insts, f.batch, sm_lastv, kvh, wave, lane);
+            arrive_and_fold(std::integral_constant<int, 1>{}, [&](const auto& rows) {
+                if (f.n_units <= 8)       merge_decode_step<G, NWV, 1, 8>(a, rows, sm_lastv, lane);
+                else if (f.n_units <= 16) merge_decode_step<G, NWV, 1, 16>(a, rows, sm_lastv, lane);
+                else                      merge_decode_step<G, NWV, 1, 32>(a, rows, sm_lastv, lane);
+            });
         } else {
-            if (f.n_units <= 8 * f.batch) merge_decode_step<G, NWV, 2, 8>(a, insts, f.batch, sm_lastv, kvh, wave, lane);
-            else                          merge_decode_step<G, NWV, 2, 16>(a, insts, f.batch, sm_lastv, kvh, wave, lane);
+            arrive_and_fold(std::integral_constant<int, 2>{}, [&](const auto& rows) {
+                if (f.n_units <= 8 * f.batch) merge_decode_step<G, NWV, 2, 8>(a, rows, sm_lastv, lane);
+                else                          merge_decode_step<G, NWV, 2, 16>(a, rows, sm_lastv, lane);
+            });
         }
         if (tid < f.batch && sm_lastv[tid])             // ready for the next launch
             __hip_atomic_store(&a.counters[counter_index(a, tid, kvh, 0)], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

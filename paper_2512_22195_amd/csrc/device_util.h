@@ -71,6 +71,14 @@ __device__ __forceinline__ float2 ld_agent2(const float* p) {
     const uint64_t r = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return make_float2(__uint_as_float((uint32_t)r), __uint_as_float((uint32_t)(r >> 32)));
 }
+// 16 bytes the same way, `off` bytes behind a wave-uniform address (no such atomic load exists; the cache policy is that of the one above).
+__device__ __forceinline__ float4 ld_agent4(const float* base, uint32_t off) {
+    typedef float f32x4v __attribute__((ext_vector_type(4)));
+    constexpr int kSc1 = 16;
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, 0xffffffffu, 0x00027000);
+    const f32x4v v = __builtin_bit_cast(f32x4v, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kSc1));
+    return make_float4(v.x, v.y, v.z, v.w);
+}
 
 // One workgroup's arrival at a counter: every thread has waited for its own agent-scope stores,
 // the barrier orders them before thread 0's ticket.  Returns true in every thread of the
