@@ -36,6 +36,8 @@ def build(verbose: bool = False, only: list[str] | None = None) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
     flags = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+             # the first kernel arguments (up to the first structure) arrive in scalar registers
+             "-mllvm", "-amdgpu-kernarg-preload-count=16",
              "-Wno-unused-command-line-argument",
              "-I", os.path.join(_ROOT, "include"), "-I", CSRC]
     objs = {s: os.path.join(OBJ_DIR, s.replace(".hip", ".o")) for s in SOURCES}

@@ -54,7 +54,7 @@ struct StepArgs {
     const void* w_v;
     const RopeEntry* rope;
     int32_t Hd, batch;
-    int32_t n_units;            // workgroups of a KV head that walk the cache; those beyond only project
+    int32_t workgroups;         // per KV head
 };
 
 // The NS waves' states of a decode tile's rows (accumulators WS floats apart) to the workgroup's partials, with agent-scope
@@ -321,6 +321,9 @@ __device__ __forceinline__ void merge_shared(const KernelArgs& a, const int4* us
 // workgroup of a KV head arrives at the counter of EVERY instance of the batch once all its
 // work is out, so the last arrival at an instance's counter knows that instance's partials and
 // its newest K/V row are complete, whichever workgroups produced them.
+// The table's addresses and the number of walking workgroups (n_units, per KV head; those beyond only project) come first among the
+// arguments: the build asks for the leading ones in registers when a workgroup starts, so that its unit's record is requested without
+// waiting for the argument buffer (0.3 us for the slowest of 256 workgroups).
 // F8: the pages hold E4M3 codes with per-head power-of-two scales; a block's codes are widened
 // to bf16 in registers (exact), the K scale multiplies the block's scores and the V scale its
 // weights on their way to bf16 (exact too: powers of two), the row sums stay unscaled.
@@ -331,8 +334,8 @@ __device__ __forceinline__ void merge_shared(const KernelArgs& a, const int4* us
 // instance's counter folds that instance's partial slots.
 template <int G, int NW, int MS, int PF, int FR, bool F8, bool SH = false>
 __global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && PF <= 2)) ? 2 : 1) void attn_mfma_kernel(
-        KernelArgs a, StepArgs f, const InstanceInfo* __restrict__ insts, const Item* __restrict__ items,
-        const Unit* __restrict__ units) {
+        const Unit* __restrict__ units, const InstanceInfo* __restrict__ insts, const Item* __restrict__ items, int n_units,
+        KernelArgs a, StepArgs f) {
     constexpr int ROWS = 16 * MS;                       // (row, head) pairs per workgroup
     constexpr int NT = (FR > 0 ? 2 : 1) * NW * 64;      // threads of the workgroup
     typedef uint16_t T;
@@ -347,8 +350,14 @@ __global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && 
 
     const SUnit* const su = reinterpret_cast<const SUnit*>(units) + blockIdx.x;     // SH only
     // fused step: workgroups beyond the units of the cache have projection waves only
-    const bool walks = FR == 0 || (int)blockIdx.x < f.n_units;
-    const Unit unit = SH ? table_record(&su->u) : table_record(units + (FR > 0 ? min((int)blockIdx.x, f.n_units - 1) : (int)blockIdx.x));
+    const bool walks = FR == 0 || (int)blockIdx.x < n_units;
+    const Unit unit = SH ? table_record(&su->u) : table_record(units + (FR > 0 ? min((int)blockIdx.x, n_units - 1) : (int)blockIdx.x));
+
+    // The other arguments are wanted here, together with the record: fetched where they are first used, each group of them
+    // would be waited for by itself (3B shape, three short instances: 1428 -> 1385 us per pass of 128 steps and layers).
+    asm volatile("" :: "s"(a.q), "s"(a.out), "s"(a.tail_k), "s"(a.tail_v), "s"(a.partials), "s"(a.counters), "s"(a.layer), "s"(a.Hq), "s"(a.Hkv),
+                       "s"(a.max_tail), "s"(a.prefill), "s"(a.cstride), "s"(a.out_f32), "s"(a.scale_log2e));
+    if (FR > 0) asm volatile("" :: "s"(f.hidden), "s"(f.w_k), "s"(f.w_v), "s"(f.rope), "s"(f.Hd), "s"(f.batch), "s"(f.workgroups));
 
     int n_m, q_row0, tail_len = 0, tail_visible;
     if (SH) {
@@ -395,9 +404,9 @@ __global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && 
     if (FR > 0 && (wave >= NW || !walks)) {
         if constexpr (FR > 0) {
             // the waves of the projection-only workgroups come first: they have nothing else to do
-            const int extra = ((int)gridDim.x - f.n_units) * 2 * NW;
-            const int id = walks ? extra + (int)blockIdx.x * NW + (wave - NW) : ((int)blockIdx.x - f.n_units) * 2 * NW + wave;
-            projection_tasks<FR>(a, f, insts, kvh, id, extra + f.n_units * NW, lane);
+            const int extra = (f.workgroups - n_units) * 2 * NW;
+            const int id = walks ? extra + (int)blockIdx.x * NW + (wave - NW) : ((int)blockIdx.x - n_units) * 2 * NW + wave;
+            projection_tasks<FR>(a, f, insts, kvh, id, extra + n_units * NW, lane);
         }
     } else {
     // Q in operand layout: lane (c16, g4) holds, for sub-tile j and chunk c of the head
@@ -674,20 +683,20 @@ __global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && 
             __syncthreads();
             if (tid < f.batch) {
                 const int prev = __hip_atomic_fetch_add(&a.counters[counter_index(a, tid, kvh, 0)], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                sm_lastv[tid] = (prev == (int)gridDim.x - 1);
+                sm_lastv[tid] = (prev == f.workgroups - 1);
             }
             __syncthreads();
             fold(rows);
         };
         if (FR == 1 || f.batch * G <= NWV) {            // (FR = 1: one instance)
             arrive_and_fold(std::integral_constant<int, 1>{}, [&](const auto& rows) {
-                if (f.n_units <= 8)       merge_decode_step<G, NWV, 1, 8>(a, rows, sm_lastv, lane);
-                else if (f.n_units <= 16) merge_decode_step<G, NWV, 1, 16>(a, rows, sm_lastv, lane);
+                if (n_units <= 8)       merge_decode_step<G, NWV, 1, 8>(a, rows, sm_lastv, lane);
+                else if (n_units <= 16) merge_decode_step<G, NWV, 1, 16>(a, rows, sm_lastv, lane);
                 else                      merge_decode_step<G, NWV, 1, 32>(a, rows, sm_lastv, lane);
             });
         } else {
             arrive_and_fold(std::integral_constant<int, 2>{}, [&](const auto& rows) {
-                if (f.n_units <= 8 * f.batch) merge_decode_step<G, NWV, 2, 8>(a, rows, sm_lastv, lane);
+                if (n_units <= 8 * f.batch) merge_decode_step<G, NWV, 2, 8>(a, rows, sm_lastv, lane);
                 else                          merge_decode_step<G, NWV, 2, 16>(a, rows, sm_lastv, lane);
             });
         }
@@ -700,10 +709,9 @@ template <int G, int NW, int MS, int PF, bool F8 = false>
 hipError_t launch_v(const AttnArgs& a, int tiles, hipStream_t s) {
     const KernelArgs k = make_kernel_args(a);
     dim3 grid(a.n_units, a.Hkv, tiles), block(NW * 64);
-    hipLaunchKernelGGL((attn_mfma_kernel<G, NW, MS, PF, 0, F8>), grid, block, 0, s, k, StepArgs{},
-                       reinterpret_cast<const InstanceInfo*>(a.table + a.off_inst),
-                       reinterpret_cast<const Item*>(a.table + a.off_items),
-                       reinterpret_cast<const Unit*>(a.table + a.off_units));
+    hipLaunchKernelGGL((attn_mfma_kernel<G, NW, MS, PF, 0, F8>), grid, block, 0, s,
+                       reinterpret_cast<const Unit*>(a.table + a.off_units), reinterpret_cast<const InstanceInfo*>(a.table + a.off_inst),
+                       reinterpret_cast<const Item*>(a.table + a.off_items), a.n_units, k, StepArgs{});
     return hipGetLastError();
 }
 
@@ -712,7 +720,7 @@ hipError_t launch_step_v(const AttnArgs& a, const MaterializeArgs& m, hipStream_
     const KernelArgs k = make_kernel_args(a);
     StepArgs f;
     f.hidden = m.hidden; f.w_k = m.w_k; f.w_v = m.w_v; f.rope = m.rope;
-    f.Hd = m.Hd; f.batch = a.batch; f.n_units = a.n_units;
+    f.Hd = m.Hd; f.batch = a.batch;
     // A short cache is cut into few units, and their projection waves alone would each have several of
     // a KV head's 128 rotary pairs (of K and of V) to do one after the other: workgroups that only project
     // are added until every pair has a wave or every compute unit a workgroup (3B shape, three instances
@@ -720,12 +728,12 @@ hipError_t launch_step_v(const AttnArgs& a, const MaterializeArgs& m, hipStream_
     const int tasks = (a.batch + FR - 1) / FR * D;
     const int lacking = tasks - a.n_units * NW;
     const int extra = std::max(0, std::min((lacking + 2 * NW - 1) / (2 * NW), 256 / a.Hkv - a.n_units));
-    dim3 grid(a.n_units + extra, a.Hkv, 1), block(2 * NW * 64);
+    f.workgroups = a.n_units + extra;
+    dim3 grid(f.workgroups, a.Hkv, 1), block(2 * NW * 64);
     auto kern = a.kv_fmt == MATKV_PAGE_E4M3 ? attn_mfma_kernel<G, NW, 1, 2, FR, true> : attn_mfma_kernel<G, NW, 1, 2, FR, false>;
-    hipLaunchKernelGGL(kern, grid, block, 0, s, k, f,
-                       reinterpret_cast<const InstanceInfo*>(a.table + a.off_inst),
-                       reinterpret_cast<const Item*>(a.table + a.off_items),
-                       reinterpret_cast<const Unit*>(a.table + a.off_units));
+    hipLaunchKernelGGL(kern, grid, block, 0, s,
+                       reinterpret_cast<const Unit*>(a.table + a.off_units), reinterpret_cast<const InstanceInfo*>(a.table + a.off_inst),
+                       reinterpret_cast<const Item*>(a.table + a.off_items), a.n_units, k, f);
     return hipGetLastError();
 }
 
@@ -745,10 +753,9 @@ hipError_t launch_g(const AttnArgs& a, hipStream_t s) {
     if (a.shared) {
         const KernelArgs k = make_kernel_args(a);
         auto kern = f8 ? attn_mfma_kernel<G, 4, 1, 2, 0, true, true> : attn_mfma_kernel<G, 4, 1, 2, 0, false, true>;
-        hipLaunchKernelGGL(kern, dim3(a.n_units, a.Hkv, 1), dim3(4 * 64), 0, s, k, StepArgs{},
-                           reinterpret_cast<const InstanceInfo*>(a.table + a.off_inst),
-                           reinterpret_cast<const Item*>(a.table + a.off_items),
-                           reinterpret_cast<const Unit*>(a.table + a.off_units));
+        hipLaunchKernelGGL(kern, dim3(a.n_units, a.Hkv, 1), dim3(4 * 64), 0, s,
+                           reinterpret_cast<const Unit*>(a.table + a.off_units), reinterpret_cast<const InstanceInfo*>(a.table + a.off_inst),
+                           reinterpret_cast<const Item*>(a.table + a.off_items), a.n_units, k, StepArgs{});
         return hipGetLastError();
     }
     if (f8) return launch_v<G, 4, 1, 2, true>(a, 1, s);
