@@ -9,7 +9,7 @@
 //                   maximum through a register swap
 //   O^T += V^T P^T  A = V through the transposing LDS read, B = P rounded to bf16
 // 256-row tiles: all waves walk the same 64-token blocks.  128-row tiles: waves 0 to 3 and 4 to 7 own
-// the same rows and take every second block; their states are folded in LDS at the end.
+// the same rows and take every second block; at the end each finishes half of the dims for both.
 //
 // What bounds it.  A step of 64 tokens needs of a SIMD 2 x 32 matrix instructions and 2 x 8 small ones (2200 cycles), of its
 // vector ALU about 1300 cycles (an exponential takes 8), and of the compute unit's LDS 2 x 8 x 16 KB at 256 bytes a cycle (1024
@@ -22,12 +22,15 @@
 //    apart with a barrier behind each phase - one multiplies while the other is in its softmax - took 3550
 //    cycles a step: every phase had its own chain of dependent maxima, reads and scalar work with nothing beside it.
 //  - 32x32x16 rather than 16x16x32: one row per lane halves the work per row.
-// Measured, us per pass, that form -> this one: chunk passes of 1000 tokens (8B, 8 layers) 418 -> 404, (70B, 4 layers) 320 -> 314,
+//  - the fixed part of a workgroup, 10 us around a 1000-token chunk's longest walk of 13, is kept short: it starts when Q and K of its first
+//    block have landed and copies the rest beside the first scores, and token groups are folded in registers (3.2 -> 1.9 us).
+// Measured, us per pass, that form -> this one without the last point: chunk passes of 1000 tokens (8B, 8 layers) 418 -> 404, (70B, 4 layers) 320 -> 314,
 // of 3501 674 -> 664; question passes (4 or 8 layers) of sixteen 8B users over 5000 tokens 705 -> 686, of four 70B users over
 // 20 000 1475 -> 1440 (a step 2.03 -> 1.95 us), of one over 10 000 316 -> 312.  Left out of a step of 1.95 us, for the measurement
 // only: every LDS read 1.94, the exponentials 1.90, the copies 1.80.  Tried: the weights formed beside the scores' matrix
 // instructions only 3870 cycles, all copies of a step at once 3900, the waves of a SIMD taking turns at the higher priority
 // 3360 against 3390, scalar work ahead of the first matrix instructions instead of between the periods 3390 against 3250.
+// The last point: chunk passes 407 -> 385, 319 -> 301, 654 -> 637, question passes 687 -> 681, 1439 -> 1445, 318 -> 313.
 //
 // An instance whose cache is one unit gets its output rows directly; otherwise every unit leaves an
 // unnormalised partial (accumulator, running maximum, sum) per row and a second, chip-wide
@@ -158,9 +161,6 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
 
     // K and V tiles of the token groups; the finished rows and their (maximum, sum) once those are dead
     __shared__ __attribute__((aligned(1024))) char smem[TS * GROUP + (TS == 1 ? 2 * NW * WR * 4 : 0)];
-    static_assert(NW * WR * (D + 2) * 4 <= sizeof(smem), "finished rows fit");
-    float* const sm_m = reinterpret_cast<float*>(smem + NW * WR * D * 4);
-    float* const sm_l = sm_m + NW * WR;
 
     // Every group walks the same blocks - the unit's items end to end (the tail clipped to the rows
     // this tile may see), TB token rows at a time, never across two items - and takes every TS-th.
@@ -297,16 +297,13 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     constexpr bool RING4 = TS == 1 && !F8;
     constexpr int AHEAD = RING4 ? 3 : 2;
     BlockDesc q[AHEAD + 1];           // descriptors of blocks i .. i + AHEAD
+    Codes k0, v0, k1, v1;             // (compressed pages: of blocks 0 and 1)
     next_step(q[0]);
-    if (F8 && src.codes) {
-        load_codes(kc, src.k, src.n); load_codes(vc, src.v, src.n);
-        store_codes(kc, k_at(0), false); store_codes(vc, v_at(0), true);
-    } else {
-        copy_k(src, 0); copy_v(src, 0);
-    }
+    const Source src0 = src;
+    if (F8 && src0.codes) { load_codes(k0, src0.k, src0.n); load_codes(v0, src0.v, src0.n); }
+    else                  { copy_k(src0, 0); if (F8) copy_v(src0, 0); }
     // Q comes through LDS as well - over tiles that nothing else needs yet - so
-    // that whole rows are fetched and the first two blocks can be on their way at the same time; padding
-    // rows repeat the last real row.  Placed like K rows, and read like them: B operand, lane's row c32.
+    // that whole rows are fetched; padding rows repeat the last real row.  Placed like K rows, and read like them: B operand, lane's row c32.
     // (Two groups: rows 0 to 63 in the third V tile of the first, the rest in that of the second.)
     const auto q_row = [&](int row) { return TS == 1 ? 4 * TILE + row * (2 * D) : (row >> 6) * GROUP + 4 * TILE + (row & 63) * (2 * D); };
     static_assert(RT * 2 * D <= (TS == 1 ? 4 : TS) * TILE, "Q fits");
@@ -323,22 +320,22 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
         }
     }
     next_step(q[1]);
-    if (F8 && src.codes) {
-        load_codes(kc, src.k, src.n); load_codes(vc, src.v, src.n);
-        store_codes(kc, k_at(1), false); store_codes(vc, v_at(1), true);
-    } else {
-        copy_k(src, 1); copy_v(src, 1);
+    const Source src1 = src;
+    if (F8) {
+        if (src1.codes) { load_codes(k1, src1.k, src1.n); load_codes(v1, src1.v, src1.n); }
+        else            { copy_k(src1, 1); copy_v(src1, 1); }
+        if (src0.codes) { store_codes(k0, k_at(0), false); store_codes(v0, v_at(0), true); }
+        if (src1.codes) { store_codes(k1, k_at(1), false); store_codes(v1, v_at(1), true); }
     }
-    // Q and block 0 are there
-    if (F8) dev::dma_wait<0>(); else dev::dma_wait<2 * NI>();
     next_step(q[2]);
+    const Source src2 = src;
+    dev::dma_wait<0>();                         // Q and K of block 0 are there (compressed pages: both blocks)
     lds_barrier();
     bf16x8 bq[8];                     // dims 16 c + 8 g2 ..
     const int vis = div_g(min(wm0 + c32, n_m - 1)) + 1;    // tail rows this lane's row may see
 #pragma unroll
     for (int c = 0; c < 8; ++c) bq[c] = *reinterpret_cast<const bf16x8*>(smem + q_row(WR * rw) + (koff ^ (32 * c)));
-    lds_barrier();                              // block 2 comes over it
-    if (RING4) { copy_k(src, 2); copy_v(src, 2); next_step(q[AHEAD]); }
+    if (RING4) { lds_barrier(); next_step(q[AHEAD]); }       // (block 2 comes over Q)
     Source next_src = src;            // where block i + AHEAD lies (compressed pages: its codes wait in registers)
     if (F8 && next_src.codes) { load_codes(kc, next_src.k, next_src.n); load_codes(vc, next_src.v, next_src.n); }
 
@@ -481,22 +478,46 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
 #pragma unroll
         for (int t = 0; t < 4; ++t) { va[t] = (vb + v_at(0)) ^ (64 * t); pin(va[t]); }
     };
+    // Block 0's scores, first weights and maxima; what else step 0 finds in LDS is copied meanwhile, in the order in which it
+    // is needed (the copies ahead of them would hold up the waves for 1.5 us).
+    auto first_copies = [&](int i) {
+        if (F8) return;
+        if (i < NI)                      copy_v1(src0, 0, i);
+        else if (i < 2 * NI)             copy_k1(src1, 1, i - NI);
+        else if (i < 3 * NI)             copy_v1(src1, 1, i - 2 * NI);
+        else if (RING4 && i < 4 * NI)    copy_k1(src2, 2, i - 3 * NI);
+        else if (RING4 && i < 5 * NI)    copy_v1(src2, 2, i - 4 * NI);
+    };
+    static_assert((RING4 ? 5 : 3) * NI <= 16, "a copy behind every matrix instruction at most");
     if (q[0].n > 0) {
         int ka[8];
         k_operands(ka, 0);
-        auto scores = [&](f32x16& st, int h) {
-#pragma unroll
-            for (int c = 0; c < 8; ++c) { st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_k1(ka[c] + 8192 * h), bq[c], c ? st : zero, 0, 0, 0); pin(st); }
-            mask(st, q[0], h);
-        };
-        scores(s0, 0);
-        scores(s1, 1);
         if (F8) { scb = sc * q[0].sk; ones_v = 1.0f / q[0].sv; }
-        take_max(half_max(s0), q[0]);           // (nothing summed yet)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_k1(ka[c]), bq[c], c ? s0 : zero, 0, 0, 0);
+            pin(s0);
+            first_copies(c);
+        }
+        mask(s0, q[0], 0);
+        float mx = s0[0];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_k1(ka[c] + 8192), bq[c], c ? s1 : zero, 0, 0, 0);
+            pin(s1);
+            first_copies(8 + c);
+            mx = c ? fmaxf(fmaxf(mx, s0[2 * c]), s0[2 * c + 1]) : fmaxf(mx, s0[1]);
+            pin(mx);
+        }
+        take_max(mx, q[0]);                     // (nothing summed yet)
         weights(s0, p0);
+        mask(s1, q[0], 1);
         take_max(half_max(s1), q[0]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) first_copies(i);
     }
-    if (!F8) dev::dma_wait<RING4 ? NI : 0>();   // block 1 is there,
+    if (!F8) dev::dma_wait<NI>();                   // all but the youngest block's V is there,
     barrier_plain();                                // and K of block 0 read by every wave
     // Step i: descriptors and sources move on by one block
     bool copied = false;
@@ -554,17 +575,22 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     }
     if (q[0].n > 0) {                               // the wave's last block
         begin_step();
-        if (!F8) { copy_k(now, AHEAD); copy_v(now, AHEAD); }
-        weights(s1, p1);
         int va[4];
         v_operands(va);
+        bf16x8 g[16];
+#pragma unroll
+        for (int j = 0; j < PD; ++j) g[j] = read_v1(va[j]);
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
-            ot[j & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_v1(va[j & 3] + 4096 * (j >> 2)), weight_pair(j < 8 ? p0 : p1, (j >> 2) & 1), ot[j & 3], 0, 0, 0);
+            ot[j & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(g[j], weight_pair(j < 8 ? p0 : p1, (j >> 2) & 1), ot[j & 3], 0, 0, 0);
             pin(ot[j & 3]);
+            if (j + PD < 16) g[j + PD] = read_v1(va[j & 3] + 4096 * ((j + PD) >> 2));
+            if (j < 8) { p1[j] = pack2(fast_exp2(fmaf(s1[2 * j], scb, nmc)), fast_exp2(fmaf(s1[2 * j + 1], scb, nmc))); pin(p1[j]); }
+            __builtin_amdgcn_sched_barrier(0);
             if (j == 7) { row_sums(p0, ones_v); rescale(); }
         }
         row_sums(p1, ones_v);
+        if (!F8) { copy_k(now, AHEAD); copy_v(now, AHEAD); }
         end_step();
     }
     while (q[0].n >= 0) {                           // blocks that other waves see
@@ -575,56 +601,107 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     dev::dma_wait<0>();                                  // (copies past the end)
     __syncthreads();
 
-    // ---- finished rows leave through LDS as whole rows; token groups are folded on the way ----
-    // wave w's 32 rows of 512 bytes, piece p (4 dims) of row r at place p ^ r
-    if (wave_live) {
-        char* const mine = smem + wave * (WR * D * 4) + c32 * (D * 4);
+    // ---- out ----
+    // Of two waves with the same rows (two token groups) each finishes half of the dims: it hands the other half's accumulators, as
+    // they lie in its registers, to its partner.  Finished rows - normalised and rounded by the lane that holds them, or as partials -
+    // go through LDS, so that they leave as whole rows.  (Folded and divided row by row on their way out they took 3.2 us.)
+    constexpr int NT = 4 / TS;                           // 32-dim tiles that a wave finishes
+    constexpr int ROWS_AT = TS == 1 ? 0 : NW * 8192 + NW * 256, ML_AT = ROWS_AT + RT * D * 4;
+    static_assert(ML_AT + RT * 8 <= sizeof(smem), "rows fit beside what the waves exchange");
+    f32x16 o[NT];
+    float M = mrow * sc, L = ol[0] + lane_xor(ol[0], 32, lane);
+    if constexpr (TS == 1) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+        for (int t = 0; t < NT; ++t) o[t] = ot[t];
+    } else {
+        f32x16 other[NT];
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                *reinterpret_cast<float4*>(mine + 16 * ((8 * t + 2 * j + g2) ^ c32)) =
-                    make_float4(ot[t][4 * j], ot[t][4 * j + 1], ot[t][4 * j + 2], ot[t][4 * j + 3]);
-        const float l = ol[0] + lane_xor(ol[0], 32, lane);
-        if (g2 == 0) { sm_m[wave * WR + c32] = mrow * sc; sm_l[wave * WR + c32] = l; }
-    }
-    __syncthreads();
-    const bool single = unit.n_units_inst == 1;
-    const int rows_here = min(RT, n_m - m0);
-    // half a wave takes a row; two rows at a time, so that their reads overlap
-    constexpr int RB = 2;
-    for (int row0 = tid >> 5; row0 < rows_here; row0 += NW * 2 * RB) {
-        float M[RB], L[RB];
-        float4 acc[RB];
+        for (int t = 0; t < NT; ++t) { o[t] = tg == 0 ? ot[t] : ot[2 + t]; other[t] = tg == 0 ? ot[2 + t] : ot[t]; }
+        float2* const ml = reinterpret_cast<float2*>(smem + NW * 8192);
+        if (wave_live) {
 #pragma unroll
-        for (int j = 0; j < RB; ++j) {
-            const int row = min(row0 + NW * 2 * j, rows_here - 1), w0 = row / WR, rr = row % WR;
-            M[j] = sm_m[row];
-            L[j] = sm_l[row];
-            acc[j] = *reinterpret_cast<const float4*>(smem + row * (D * 4) + 16 * (c32 ^ rr));
-            if (TS == 2) {
-                const float m1 = sm_m[RT + row], l1 = sm_l[RT + row];
-                const float4 v = *reinterpret_cast<const float4*>(smem + ((RW + w0) * WR + rr) * (D * 4) + 16 * (c32 ^ rr));
-                const float mm = fmaxf(M[j], m1), f0 = fast_exp2(M[j] - mm), f1 = fast_exp2(m1 - mm);
-                M[j] = mm;
-                L[j] = fmaf(f1, l1, L[j] * f0);
-                acc[j].x = fmaf(f1, v.x, acc[j].x * f0); acc[j].y = fmaf(f1, v.y, acc[j].y * f0);
-                acc[j].z = fmaf(f1, v.z, acc[j].z * f0); acc[j].w = fmaf(f1, v.w, acc[j].w * f0);
+            for (int j = 0; j < 8; ++j)
+                *reinterpret_cast<f32x4*>(smem + wave * 8192 + (j * 64 + lane) * 16) =
+                    f32x4{other[j / 4][4 * (j & 3)], other[j / 4][4 * (j & 3) + 1], other[j / 4][4 * (j & 3) + 2], other[j / 4][4 * (j & 3) + 3]};
+            if (g2 == 0) ml[wave * WR + c32] = make_float2(M, L);
+        }
+        lds_barrier();
+        if (wave_live) {
+            const int partner = wave ^ (NW / 2);
+            const float2 mlp = ml[partner * WR + c32];
+            const float mm = fmaxf(M, mlp.x), f0 = fast_exp2(M - mm), f1 = fast_exp2(mlp.x - mm);
+            M = mm;
+            L = fmaf(f1, mlp.y, L * f0);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const f32x4 v = *reinterpret_cast<const f32x4*>(smem + partner * 8192 + (j * 64 + lane) * 16);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) o[j / 4][4 * (j & 3) + i] = fmaf(f1, v[i], o[j / 4][4 * (j & 3) + i] * f0);
             }
         }
+    }
+    const bool single = unit.n_units_inst == 1, bf16_out = single && !a.out_f32;
+    const int rows_here = min(RT, n_m - m0);
+    if (wave_live) {
+        const int row = WR * rw + c32;
+        if (single) {
+            const float inv = 1.0f / L;
 #pragma unroll
-        for (int j = 0; j < RB; ++j) {
-            const int row = row0 + NW * 2 * j;
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) o[t][i] *= inv;
+        } else if (g2 == 0 && tg == 0) {
+            *reinterpret_cast<float2*>(smem + ML_AT + row * 8) = make_float2(M, L);
+        }
+        // 16-byte piece p of row r at place p ^ r (bf16 rows of 16 pieces: whose halves change places in rows 16 to 31 of 32)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int tt = TS == 1 ? t : 2 * tg + t;
+                if (bf16_out)
+                    *reinterpret_cast<uint2*>(smem + ROWS_AT + row * (D * 2) + 16 * ((4 * tt + j) ^ (c32 & 15)) + 8 * (g2 ^ (c32 >> 4))) =
+                        make_uint2(pack2(o[t][4 * j], o[t][4 * j + 1]), pack2(o[t][4 * j + 2], o[t][4 * j + 3]));
+                else
+                    *reinterpret_cast<float4*>(smem + ROWS_AT + row * (D * 4) + 16 * ((8 * tt + 2 * j + g2) ^ c32)) =
+                        make_float4(o[t][4 * j], o[t][4 * j + 1], o[t][4 * j + 2], o[t][4 * j + 3]);
+            }
+    }
+    lds_barrier();
+    if (bf16_out) {                                      // sixteen lanes take a row
+        uint4 v[RT / 32];
+#pragma unroll
+        for (int i = 0; i < RT / 32; ++i) {
+            const int row = (tid >> 4) + 32 * i;
+            v[i] = *reinterpret_cast<const uint4*>(smem + ROWS_AT + row * (D * 2) + 16 * ((tid ^ row) & 15));
+        }
+#pragma unroll
+        for (int i = 0; i < RT / 32; ++i) {
+            const int row = (tid >> 4) + 32 * i, m = m0 + row, r = div_g(m), head = kvh * G + m - r * G;
             if (row >= rows_here) break;
-            const int m = m0 + row, r = div_g(m), head = kvh * G + m - r * G;
-            if (single) {
-                const float inv = 1.0f / L[j];
-                store_out4(a.out, a.out_f32, ((size_t)(inst.cu_q + r) * a.Hq + head) * D + 4 * c32,
-                           make_float4(acc[j].x * inv, acc[j].y * inv, acc[j].z * inv, acc[j].w * inv));
-            } else {
-                float* prow = a.partials + (((size_t)unit_i * a.rows + r) * a.Hq + head) * kPartialStride(D);
-                *reinterpret_cast<float4*>(prow + 4 * c32) = acc[j];
-                if (c32 == 0) *reinterpret_cast<float2*>(prow + D) = make_float2(M[j], L[j]);
+            *reinterpret_cast<uint4*>(reinterpret_cast<T*>(a.out) + ((size_t)(inst.cu_q + r) * a.Hq + head) * D + 8 * (tid & 15)) =
+                row & 16 ? make_uint4(v[i].z, v[i].w, v[i].x, v[i].y) : v[i];
+        }
+    } else {                                             // half a wave takes a row
+#pragma unroll
+        for (int i0 = 0; i0 < RT / 16; i0 += 4) {
+            float4 v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int row = (tid >> 5) + 16 * (i0 + i);
+                v[i] = *reinterpret_cast<const float4*>(smem + ROWS_AT + row * (D * 4) + 16 * ((tid ^ row) & 31));
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int row = (tid >> 5) + 16 * (i0 + i), m = m0 + row, r = div_g(m), head = kvh * G + m - r * G;
+                if (row >= rows_here) break;
+                if (single) {
+                    *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.out) + ((size_t)(inst.cu_q + r) * a.Hq + head) * D + 4 * c32) = v[i];
+                } else {
+                    float* const prow = a.partials + (((size_t)unit_i * a.rows + r) * a.Hq + head) * kPartialStride(D);
+                    *reinterpret_cast<float4*>(prow + 4 * c32) = v[i];
+                    if (c32 == 0) *reinterpret_cast<float2*>(prow + D) = *reinterpret_cast<const float2*>(smem + ML_AT + row * 8);
+                }
             }
         }
     }
