@@ -108,12 +108,13 @@ __device__ __forceinline__ bool find_further_tile(const InstanceInfo* __restrict
     return false;
 }
 
+// units .. chunk (a chunk's own attention) arrive in registers, so that the unit's record is asked for without waiting for the other arguments.
 // batch: given where the tiles beyond the first are dealt out by find_further_tile, and left out elsewhere: one
 // argument more moves the implicit ones into another line of the argument buffer, which costs every launch 0.3 us.
 template <int RW, bool F8, typename... Batch>
 __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
-        KernelArgs a, const InstanceInfo* __restrict__ insts, const Item* __restrict__ items,
-        const Unit* __restrict__ units, Batch... batch) {
+        const Unit* __restrict__ units, const InstanceInfo* __restrict__ insts, const Item* __restrict__ items, int chunk,
+        KernelArgs a, Batch... batch) {
     constexpr bool DEAL = sizeof...(Batch) > 0;
     constexpr int TS = NW / RW;                         // token groups
     constexpr int RT = RW * WR;                         // rows per workgroup
@@ -130,7 +131,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     const int G = a.Hq / a.Hkv;                         // 1, 2, 3, 4 or 8
     auto div_g = [&](int m) { return (int)__umulhi((unsigned)m << 3, a.g_mul); };     // m / G, m < 2^28
     // a chunk's own attention: tile t walks (t + 1) * RT / G keys, so the longest go first
-    int kvh = blockIdx.y, tile = a.prefill == 2 ? gridDim.z - 1 - blockIdx.z : blockIdx.z, unit_i = blockIdx.x, b = -1;
+    int kvh = blockIdx.y, tile = chunk ? gridDim.z - 1 - blockIdx.z : blockIdx.z, unit_i = blockIdx.x, b = -1;
     if constexpr (DEAL) {
         if (blockIdx.z > 0) {
             const int further = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * (blockIdx.z - 1)), k = further / a.Hkv;
@@ -141,7 +142,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
 
     Unit unit;
     InstanceInfo inst;
-    if (a.prefill == 2) {                               // the chunk: one instance without pages, its tail the one item
+    if (chunk) {                               // the chunk: one instance without pages, its tail the one item
         unit = Unit{};
         unit.n_items = 1; unit.n_units_inst = 1; unit.has_tail = 1; unit.first.ntok = a.rows;
         inst = InstanceInfo{};
@@ -725,8 +726,8 @@ constexpr int KSTR = D + 16, VSTR = D + 24;             // bf16 per LDS row of t
 
 template <bool F8>
 __global__ __launch_bounds__(256, 2) void attn_prefill_short_kernel(
-        KernelArgs a, const InstanceInfo* __restrict__ insts, const Item* __restrict__ items,
-        const Unit* __restrict__ units) {
+        const Unit* __restrict__ units, const InstanceInfo* __restrict__ insts, const Item* __restrict__ items, int chunk,
+        KernelArgs a) {
     constexpr int NWV = 4, RT = 16 * NWV, SR = TB / (4 * NWV);
     constexpr int TILE_ELEMS = TB * KSTR + TB * VSTR;   // one K tile + one V tile
     typedef uint16_t T;
@@ -742,7 +743,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_short_kernel(
     Unit unit;
     InstanceInfo inst;
     int tile = blockIdx.z;
-    if (a.prefill == 2) {                               // the chunk, as above; the longest tiles go first
+    if (chunk) {                               // the chunk, as above; the longest tiles go first
         unit = Unit{};
         unit.n_items = 1; unit.n_units_inst = 1; unit.has_tail = 1; unit.first.ntok = a.rows;
         inst = InstanceInfo{};
@@ -777,7 +778,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_short_kernel(
     // the unit's item list sits in LDS: a fetch inside the loop would also drain the block loads in flight
     __shared__ __attribute__((aligned(16))) Item sm_items[kMaxPrefillItemsPerUnit];
     __shared__ float sm_scale[F8 ? kMaxPrefillItemsPerUnit : 1][2];      // K and V scale of every item
-    if (a.prefill != 2)
+    if (!chunk)
         for (int i = tid; i < unit.n_items * 2; i += NWV * 64)
             reinterpret_cast<uint4*>(sm_items)[i] = reinterpret_cast<const uint4*>(items + unit.item0)[i];
     if (F8 && tid < unit.n_items) {
@@ -1047,13 +1048,14 @@ hipError_t launch_f(const AttnArgs& a, hipStream_t s) {
     const InstanceInfo* insts = reinterpret_cast<const InstanceInfo*>(a.table + a.off_inst);
     const Item* items = reinterpret_cast<const Item*>(a.table + a.off_items);
     const Unit* units = reinterpret_cast<const Unit*>(a.table + a.off_units);
-    if (a.tile_rows <= 64)       hipLaunchKernelGGL(attn_prefill_short_kernel<F8>, grid, block, 0, s, k, insts, items, units);
+    const int chunk = a.prefill == 2;
+    if (a.tile_rows <= 64)       hipLaunchKernelGGL(attn_prefill_short_kernel<F8>, grid, block, 0, s, units, insts, items, chunk, k);
     else if (a.deal_tiles) {
-        if (a.tile_rows <= 128)  hipLaunchKernelGGL((attn_prefill_kernel<4, F8, int>), grid, block, 0, s, k, insts, items, units, a.batch);
-        else                     hipLaunchKernelGGL((attn_prefill_kernel<8, F8, int>), grid, block, 0, s, k, insts, items, units, a.batch);
+        if (a.tile_rows <= 128)  hipLaunchKernelGGL((attn_prefill_kernel<4, F8, int>), grid, block, 0, s, units, insts, items, chunk, k, a.batch);
+        else                     hipLaunchKernelGGL((attn_prefill_kernel<8, F8, int>), grid, block, 0, s, units, insts, items, chunk, k, a.batch);
     }
-    else if (a.tile_rows <= 128) hipLaunchKernelGGL((attn_prefill_kernel<4, F8>), grid, block, 0, s, k, insts, items, units);
-    else                         hipLaunchKernelGGL((attn_prefill_kernel<8, F8>), grid, block, 0, s, k, insts, items, units);
+    else if (a.tile_rows <= 128) hipLaunchKernelGGL((attn_prefill_kernel<4, F8>), grid, block, 0, s, units, insts, items, chunk, k);
+    else                         hipLaunchKernelGGL((attn_prefill_kernel<8, F8>), grid, block, 0, s, units, insts, items, chunk, k);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.max_units_inst <= 1) return e;
     const int total_pairs = a.total_q * a.Hq;

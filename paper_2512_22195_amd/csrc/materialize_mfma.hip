@@ -114,6 +114,8 @@ __device__ __forceinline__ void rope_cs(const RopeEntry& e, float p, float& c, f
 // favoured by the power-of-two row strides: no change), an extra wave that touches the weight rows
 // some steps ahead (-12 % at 512 rows of hidden 8192, +20 % at 64 rows, nothing at 1000), workgroups that share an operand touching it
 // some steps ahead in turn (-10 % there, +8 to 13 % at 1000 rows and more).
+// (The operands' addresses and sizes come first among the arguments of these kernels: they arrive in registers, and the first operands are
+// asked for without waiting for the argument buffer.)
 template <int MI> struct TileShape {
     static constexpr int BM = 32 * MI;                              // token rows of a workgroup
     static constexpr int ROWS = BM + D;                             // LDS rows of a step: tokens, then weight rows
@@ -124,7 +126,8 @@ template <int MI> struct TileShape {
 // WN: waves along the features; the other 8 / WN split the rows.  Few waves along the features read
 // fewer LDS bytes per product from MI = 6 on, as many at MI = 4, and store 16 bytes of a row instead of 8.
 template <int MI, int WN, int SK>
-__global__ __launch_bounds__(512) void materialize_tile_kernel(MaterializeArgs a, int total_rows, int row_tiles) {
+__global__ __launch_bounds__(512) void materialize_tile_kernel(
+        const void* __restrict__ hidden, const void* __restrict__ w_k, const void* __restrict__ w_v, int Hd, int Hkv, int total_rows, int row_tiles, MaterializeArgs a) {
     typedef TileShape<MI> S;
     constexpr int WM = 8 / WN, XB = 2 * MI / WM, PB = 4 / WN;       // waves along the rows; row blocks and pair blocks of a wave
     constexpr int BM = S::BM, NBUF = S::NBUF;
@@ -137,7 +140,7 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(MaterializeArgs a
     // Workgroup -> (half of the hidden axis, column tile, row tile).  Workgroups go to the eight XCDs in
     // turn; an XCD's L2 should see few distinct operands: with SK = 2 an XCD holds one half of the hidden
     // axis and every fourth column tile, with SK = 1 every fourth column tile and every second row tile.
-    const int nct = 2 * a.Hkv;
+    const int nct = 2 * Hkv;
     int part = 0, ct, rt;
     if (SK == 2) {
         part = blockIdx.x & 1;
@@ -149,9 +152,9 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(MaterializeArgs a
     } else {
         ct = blockIdx.x % nct; rt = blockIdx.x / nct;
     }
-    const int kv = ct / a.Hkv, head = ct % a.Hkv;
+    const int kv = ct >= Hkv, head = ct - kv * Hkv;
     const int row0 = rt * BM;
-    const int nk = a.Hd / (BK * SK);
+    const int nk = Hd / (BK * SK);
 
     // LDS row r of the weights -> feature.  Sixteen rows are one operand of a matrix instruction, whose results
     // land in lanes by fours of these rows: the order makes a lane's results of its PB low (and of its PB high) operands features in a row.
@@ -165,9 +168,9 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(MaterializeArgs a
     constexpr int XI = 4 * MI, XW = (XI + 7) / 8;
     const int n_x = (XI - wave + 7) / 8;                            // token copies of this wave per step (XW or XW - 1)
     const int lrow = lane >> 3, place = lane & 7;
-    const size_t row_bytes = (size_t)a.Hd * 2;
-    const char* X = reinterpret_cast<const char*>(a.hidden) + (size_t)row0 * row_bytes + (size_t)part * nk * (BK * 2);
-    const char* W = reinterpret_cast<const char*>(kv == 0 ? a.w_k : a.w_v) + (size_t)head * D * row_bytes + (size_t)part * nk * (BK * 2);
+    const size_t row_bytes = (size_t)Hd * 2;
+    const char* X = reinterpret_cast<const char*>(hidden) + (size_t)row0 * row_bytes + (size_t)part * nk * (BK * 2);
+    const char* W = reinterpret_cast<const char*>(kv == 0 ? w_k : w_v) + (size_t)head * D * row_bytes + (size_t)part * nk * (BK * 2);
     uint32_t xoff[XW], woff[2];
 #pragma unroll
     for (int i = 0; i < XW; ++i) {
@@ -348,7 +351,8 @@ template <int MI, int WN, int SK>
 hipError_t launch_tile(const MaterializeArgs& a, int total_rows, hipStream_t s) {
     const int row_tiles = (total_rows + 32 * MI - 1) / (32 * MI), nct = 2 * a.Hkv;
     const int grid_tiles = SK == 1 && nct % 4 == 0 ? (row_tiles + 1) / 2 * 2 : row_tiles;
-    hipLaunchKernelGGL((materialize_tile_kernel<MI, WN, SK>), dim3(nct * grid_tiles * SK), dim3(512), 0, s, a, total_rows, row_tiles);
+    hipLaunchKernelGGL((materialize_tile_kernel<MI, WN, SK>), dim3(nct * grid_tiles * SK), dim3(512), 0, s,
+                       a.hidden, a.w_k, a.w_v, a.Hd, a.Hkv, total_rows, row_tiles, a);
     return hipGetLastError();
 }
 
@@ -401,7 +405,8 @@ hipError_t launch_tiled(const MaterializeArgs& a, int total_rows, hipStream_t s)
 // workgroup barrier in the loop.  The eight partial tiles meet in LDS, and the rotation and the single
 // rounding to bf16 follow.
 template <int MI, int NB>
-__global__ __launch_bounds__(512) void materialize_skinny_staged_kernel(MaterializeArgs a, int total_rows) {
+__global__ __launch_bounds__(512) void materialize_skinny_staged_kernel(
+        const void* __restrict__ hidden, const void* __restrict__ w_k, const void* __restrict__ w_v, int Hd, int Hkv, int total_rows, MaterializeArgs a) {
     constexpr int NWV = 8, SC = 128;                    // waves; hidden columns per wave and round
     constexpr int TM = 16 * MI;
     constexpr int NR = 32 + TM;                         // rows staged per round: 16 + 16 weight rows, TM token rows
@@ -413,9 +418,9 @@ __global__ __launch_bounds__(512) void materialize_skinny_staged_kernel(Material
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int c16 = lane & 15, g4 = lane >> 4;
-    const int pg = blockIdx.x & 3, head = (blockIdx.x >> 2) % a.Hkv, kv = (blockIdx.x >> 2) / a.Hkv;
+    const int pg = blockIdx.x & 3, kv = (int)(blockIdx.x >> 2) >= Hkv, head = (int)(blockIdx.x >> 2) - kv * Hkv;
     const int row0 = blockIdx.y * TM;
-    const int kslice = a.Hd / NWV;                      // a multiple of SC (checked by the launcher)
+    const int kslice = Hd / NWV;                      // a multiple of SC (checked by the launcher)
     const int n_rounds = kslice / SC;
 
     // the epilogue's row and rotary entry of this thread are fixed: asked for now, not after the sums
@@ -428,17 +433,17 @@ __global__ __launch_bounds__(512) void materialize_skinny_staged_kernel(Material
     // load i of a round: row 4 i + lane / 16 of the staged rows, 16 bytes at column 8 (lane % 16)
     const int lr = lane >> 4, lc = 8 * (lane & 15);
     const size_t col0 = (size_t)wave * kslice + lc;
-    const uint16_t* wbase = reinterpret_cast<const uint16_t*>(kv == 0 ? a.w_k : a.w_v) + ((size_t)head * D + 16 * pg + lr) * a.Hd + col0;
+    const uint16_t* wbase = reinterpret_cast<const uint16_t*>(kv == 0 ? w_k : w_v) + ((size_t)head * D + 16 * pg + lr) * Hd + col0;
     const uint16_t* xp[MI * 4];
 #pragma unroll
     for (int i = 0; i < MI * 4; ++i)
-        xp[i] = reinterpret_cast<const uint16_t*>(a.hidden) + (size_t)min(row0 + 4 * i + lr, total_rows - 1) * a.Hd + col0;
+        xp[i] = reinterpret_cast<const uint16_t*>(hidden) + (size_t)min(row0 + 4 * i + lr, total_rows - 1) * Hd + col0;
     auto load = [&](uint4 (&b)[NL], int r) {
         const int off = min(r, n_rounds - 1) * SC;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            b[i] = ldg16(wbase + (size_t)(4 * i) * a.Hd + off);
-            b[4 + i] = ldg16(wbase + (size_t)(D / 2 + 4 * i) * a.Hd + off);
+            b[i] = ldg16(wbase + (size_t)(4 * i) * Hd + off);
+            b[4 + i] = ldg16(wbase + (size_t)(D / 2 + 4 * i) * Hd + off);
         }
 #pragma unroll
         for (int i = 0; i < MI * 4; ++i) b[8 + i] = ldg16(xp[i] + off);
@@ -520,7 +525,8 @@ __global__ __launch_bounds__(512) void materialize_skinny_staged_kernel(Material
 // their results are dropped.  Eight waves split the hidden axis as above; only the TMR real token
 // rows are staged.
 template <int NP, int TMR, int NB>
-__global__ __launch_bounds__(512) void materialize_fewrows_kernel(MaterializeArgs a, int total_rows) {
+__global__ __launch_bounds__(512) void materialize_fewrows_kernel(
+        const void* __restrict__ hidden, const void* __restrict__ w_k, const void* __restrict__ w_v, int Hd, int Hkv, int total_rows, MaterializeArgs a) {
     constexpr int NWV = 8, SC = 128;                    // waves; hidden columns per wave and round
     constexpr int NR = 2 * NP + TMR;                    // rows staged per round
     static_assert(NP % 4 == 0 && TMR % 4 == 0 && 2 * NP <= 16 && TMR <= 16, "whole loads of four rows; one matrix tile");
@@ -533,9 +539,9 @@ __global__ __launch_bounds__(512) void materialize_fewrows_kernel(MaterializeArg
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int c16 = lane & 15, g4 = lane >> 4;
     constexpr int GPH = (D / 2) / NP;                   // pair groups per head
-    const int pg = blockIdx.x % GPH, head = (blockIdx.x / GPH) % a.Hkv, kv = (blockIdx.x / GPH) / a.Hkv;
+    const int pg = blockIdx.x % GPH, kv = (int)(blockIdx.x / GPH) >= Hkv, head = (int)(blockIdx.x / GPH) - kv * Hkv;
     const int row0 = blockIdx.y * TMR;
-    const int kslice = a.Hd / NWV;                      // a multiple of SC (checked by the launcher)
+    const int kslice = Hd / NWV;                      // a multiple of SC (checked by the launcher)
     const int n_rounds = kslice / SC;
 
     // the epilogue's row and rotary entry of this thread are fixed: asked for now, not after the sums
@@ -547,17 +553,17 @@ __global__ __launch_bounds__(512) void materialize_fewrows_kernel(MaterializeArg
     // load i of a round: staged row 4 i + lane / 16, 16 bytes at column 8 (lane % 16)
     const int lr = lane >> 4, lc = 8 * (lane & 15);
     const size_t col0 = (size_t)wave * kslice + lc;
-    const uint16_t* wbase = reinterpret_cast<const uint16_t*>(kv == 0 ? a.w_k : a.w_v) + ((size_t)head * D + NP * pg + lr) * a.Hd + col0;
+    const uint16_t* wbase = reinterpret_cast<const uint16_t*>(kv == 0 ? w_k : w_v) + ((size_t)head * D + NP * pg + lr) * Hd + col0;
     const uint16_t* xp[TMR / 4];
 #pragma unroll
     for (int i = 0; i < TMR / 4; ++i)
-        xp[i] = reinterpret_cast<const uint16_t*>(a.hidden) + (size_t)min(row0 + 4 * i + lr, total_rows - 1) * a.Hd + col0;
+        xp[i] = reinterpret_cast<const uint16_t*>(hidden) + (size_t)min(row0 + 4 * i + lr, total_rows - 1) * Hd + col0;
     auto load = [&](uint4 (&b)[NL], int r) {
         const int off = min(r, n_rounds - 1) * SC;
 #pragma unroll
         for (int i = 0; i < NP / 4; ++i) {
-            b[i] = ldg16(wbase + (size_t)(4 * i) * a.Hd + off);
-            b[NP / 4 + i] = ldg16(wbase + (size_t)(D / 2 + 4 * i) * a.Hd + off);
+            b[i] = ldg16(wbase + (size_t)(4 * i) * Hd + off);
+            b[NP / 4 + i] = ldg16(wbase + (size_t)(D / 2 + 4 * i) * Hd + off);
         }
 #pragma unroll
         for (int i = 0; i < TMR / 4; ++i) b[NP / 2 + i] = ldg16(xp[i] + off);
@@ -627,9 +633,9 @@ hipError_t launch_fewrows_t(const MaterializeArgs& a, int total_rows, hipStream_
     constexpr int NP = 4;
     const dim3 grid(2 * a.Hkv * (64 / NP), (total_rows + TMR - 1) / TMR), block(512);
     const int rounds = a.Hd / 1024;
-    if (rounds % 4 == 0) hipLaunchKernelGGL((materialize_fewrows_kernel<NP, TMR, 4>), grid, block, 0, s, a, total_rows);
-    else if (rounds % 2 == 0) hipLaunchKernelGGL((materialize_fewrows_kernel<NP, TMR, 2>), grid, block, 0, s, a, total_rows);
-    else hipLaunchKernelGGL((materialize_fewrows_kernel<NP, TMR, 1>), grid, block, 0, s, a, total_rows);
+    if (rounds % 4 == 0) hipLaunchKernelGGL((materialize_fewrows_kernel<NP, TMR, 4>), grid, block, 0, s, a.hidden, a.w_k, a.w_v, a.Hd, a.Hkv, total_rows, a);
+    else if (rounds % 2 == 0) hipLaunchKernelGGL((materialize_fewrows_kernel<NP, TMR, 2>), grid, block, 0, s, a.hidden, a.w_k, a.w_v, a.Hd, a.Hkv, total_rows, a);
+    else hipLaunchKernelGGL((materialize_fewrows_kernel<NP, TMR, 1>), grid, block, 0, s, a.hidden, a.w_k, a.w_v, a.Hd, a.Hkv, total_rows, a);
     return hipGetLastError();
 }
 
@@ -650,11 +656,11 @@ hipError_t launch_materialize_staged(const MaterializeArgs& a, int total_rows, h
     const bool mi2 = total_rows > 64;
     const dim3 grid(2 * a.Hkv * 4, mi2 ? (total_rows + 31) / 32 : (total_rows + 15) / 16), block(512);
     if (rounds % 2 == 0) {
-        if (mi2) hipLaunchKernelGGL((materialize_skinny_staged_kernel<2, 2>), grid, block, 0, s, a, total_rows);
-        else     hipLaunchKernelGGL((materialize_skinny_staged_kernel<1, 2>), grid, block, 0, s, a, total_rows);
+        if (mi2) hipLaunchKernelGGL((materialize_skinny_staged_kernel<2, 2>), grid, block, 0, s, a.hidden, a.w_k, a.w_v, a.Hd, a.Hkv, total_rows, a);
+        else     hipLaunchKernelGGL((materialize_skinny_staged_kernel<1, 2>), grid, block, 0, s, a.hidden, a.w_k, a.w_v, a.Hd, a.Hkv, total_rows, a);
     } else {
-        if (mi2) hipLaunchKernelGGL((materialize_skinny_staged_kernel<2, 1>), grid, block, 0, s, a, total_rows);
-        else     hipLaunchKernelGGL((materialize_skinny_staged_kernel<1, 1>), grid, block, 0, s, a, total_rows);
+        if (mi2) hipLaunchKernelGGL((materialize_skinny_staged_kernel<2, 1>), grid, block, 0, s, a.hidden, a.w_k, a.w_v, a.Hd, a.Hkv, total_rows, a);
+        else     hipLaunchKernelGGL((materialize_skinny_staged_kernel<1, 1>), grid, block, 0, s, a.hidden, a.w_k, a.w_v, a.Hd, a.Hkv, total_rows, a);
     }
     return hipGetLastError();
 }
