@@ -332,12 +332,13 @@ __device__ __forceinline__ void merge_shared(const KernelArgs& a, const int4* us
 // tile are (user, query head) pairs, the piece is streamed once for all of them, every user gets
 // its own partial, and the workgroup arrives at every user's counter: the last arrival at an
 // instance's counter folds that instance's partial slots.
-template <int G, int NW, int MS, int PF, int FR, bool F8, bool SH = false>
+// NT: the cache's rows are not left in the last-level cache (launch_g tells when).
+template <int G, int NW, int MS, int PF, int FR, bool F8, bool SH = false, bool NT = false>
 __global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && PF <= 2)) ? 2 : 1) void attn_mfma_kernel(
         const Unit* __restrict__ units, const InstanceInfo* __restrict__ insts, const Item* __restrict__ items, int n_units,
         KernelArgs a, StepArgs f) {
     constexpr int ROWS = 16 * MS;                       // (row, head) pairs per workgroup
-    constexpr int NT = (FR > 0 ? 2 : 1) * NW * 64;      // threads of the workgroup
+    constexpr int NTH = (FR > 0 ? 2 : 1) * NW * 64;     // threads of the workgroup
     typedef uint16_t T;
     static_assert(!SH || (FR == 0 && MS == 1), "shared units: decode tiles only");
     __shared__ int sm_last, sm_lastv[SH ? kMaxSharedUsers : (FR > 0 ? kFusedMaxBatch : 1)];
@@ -446,30 +447,32 @@ __global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && 
 
     // Rows past the block's end are clamped to its last row and masked in the softmax.
     auto issue_plain = [&](const BlockRef<T>& r, PlainBuf& b) {
+        const T* const kp = r.k + (size_t)r.t0 * D;
+        const T* const vp = r.v + (size_t)r.t0 * D;
+        const int n = r.tok_end - r.t0;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const T* kp = r.k + (size_t)min(r.t0 + 16 * h + c16, r.tok_end - 1) * D;
+            const uint32_t row = min(16 * h + c16, n - 1) * (2 * D);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) b.k[h][c] = ldg16(kp + dim0(c));
+            for (int c = 0; c < 4; ++c) b.k[h][c] = dev::ld16_at<NT>(kp, row + 2 * dim0(c));
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-            b.v[u] = ldg16(r.v + (size_t)min(r.t0 + 4 * u + g4, r.tok_end - 1) * D + 8 * c16);
+        for (int u = 0; u < 8; ++u) b.v[u] = dev::ld16_at<NT>(vp, min(4 * u + g4, n - 1) * (2 * D) + 16 * c16);
     };
     // K: the two 16-byte pieces of the lane's token row that hold its dims (chunks 0-1, 2-3);
     // V: lane l takes 16 dims (l % 8) of token row 8u + l / 8.
     auto issue_codes = [&](const BlockRef<T>& r, CodeBuf& b) {
-        const uint8_t* kc = reinterpret_cast<const uint8_t*>(r.k);
-        const uint8_t* vc = reinterpret_cast<const uint8_t*>(r.v);
+        const uint8_t* const kp = reinterpret_cast<const uint8_t*>(r.k) + (size_t)r.t0 * D;
+        const uint8_t* const vp = reinterpret_cast<const uint8_t*>(r.v) + (size_t)r.t0 * D;
+        const int n = r.tok_end - r.t0;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const uint8_t* kp = kc + (size_t)min(r.t0 + 16 * h + c16, r.tok_end - 1) * D + 16 * g4;
-            b.k[h][0] = ldg16(kp);
-            b.k[h][1] = ldg16(kp + 64);
+            const uint32_t row = min(16 * h + c16, n - 1) * D + 16 * g4;
+            b.k[h][0] = dev::ld16_at<NT>(kp, row);
+            b.k[h][1] = dev::ld16_at<NT>(kp, row + 64);
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            b.v[u] = ldg16(vc + (size_t)min(r.t0 + 8 * u + (lane >> 3), r.tok_end - 1) * D + 16 * (lane & 7));
+        for (int u = 0; u < 4; ++u) b.v[u] = dev::ld16_at<NT>(vp, min(8 * u + (lane >> 3), n - 1) * D + 16 * (lane & 7));
     };
 
     // Scores, online softmax and P V of one block whose K operands are in ak and whose V rows
@@ -670,12 +673,12 @@ __global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && 
             reset_counter(a, cidx);
         }
     } else {
-        if (walks) publish_rows<NT / 64, NW, ROWS, WS, (G + NT / 64 - 1) / (NT / 64)>(a, sm_acc, sm_m, sm_l, G, map, wave, lane);      // (uniform)
+        if (walks) publish_rows<NTH / 64, NW, ROWS, WS, (G + NTH / 64 - 1) / (NTH / 64)>(a, sm_acc, sm_m, sm_l, G, map, wave, lane);      // (uniform)
         // arrival at every instance's counter of this KV head, then the fold, in
         // one round trip where it fits: one row per wave, or two where the batch has more rows than the
         // workgroup has waves; units requested per row: the smallest of 8, 16, 32 that covers the partition
         // (an even cut: the batch's instances have at most n_units - batch + 1 units each)
-        constexpr int NWV = NT / 64;
+        constexpr int NWV = NTH / 64;
         auto arrive_and_fold = [&](auto rb, auto fold) {
             const StepRows<G, NWV, decltype(rb)::value> rows(a, insts, f.batch, kvh, wave, lane);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -705,11 +708,11 @@ __global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && 
     }
 }
 
-template <int G, int NW, int MS, int PF, bool F8 = false>
+template <int G, int NW, int MS, int PF, bool F8 = false, bool NT = false>
 hipError_t launch_v(const AttnArgs& a, int tiles, hipStream_t s) {
     const KernelArgs k = make_kernel_args(a);
     dim3 grid(a.n_units, a.Hkv, tiles), block(NW * 64);
-    hipLaunchKernelGGL((attn_mfma_kernel<G, NW, MS, PF, 0, F8>), grid, block, 0, s,
+    hipLaunchKernelGGL((attn_mfma_kernel<G, NW, MS, PF, 0, F8, false, NT>), grid, block, 0, s,
                        reinterpret_cast<const Unit*>(a.table + a.off_units), reinterpret_cast<const InstanceInfo*>(a.table + a.off_inst),
                        reinterpret_cast<const Item*>(a.table + a.off_items), a.n_units, k, StepArgs{});
     return hipGetLastError();
@@ -730,7 +733,9 @@ hipError_t launch_step_v(const AttnArgs& a, const MaterializeArgs& m, hipStream_
     const int extra = std::max(0, std::min((lacking + 2 * NW - 1) / (2 * NW), 256 / a.Hkv - a.n_units));
     f.workgroups = a.n_units + extra;
     dim3 grid(f.workgroups, a.Hkv, 1), block(2 * NW * 64);
-    auto kern = a.kv_fmt == MATKV_PAGE_E4M3 ? attn_mfma_kernel<G, NW, 1, 2, FR, true> : attn_mfma_kernel<G, NW, 1, 2, FR, false>;
+    const bool f8 = a.kv_fmt == MATKV_PAGE_E4M3;
+    auto kern = a.past_llc ? (f8 ? attn_mfma_kernel<G, NW, 1, 2, FR, true, false, true> : attn_mfma_kernel<G, NW, 1, 2, FR, false, false, true>)
+                           : (f8 ? attn_mfma_kernel<G, NW, 1, 2, FR, true> : attn_mfma_kernel<G, NW, 1, 2, FR, false>);
     hipLaunchKernelGGL(kern, grid, block, 0, s,
                        reinterpret_cast<const Unit*>(a.table + a.off_units), reinterpret_cast<const InstanceInfo*>(a.table + a.off_inst),
                        reinterpret_cast<const Item*>(a.table + a.off_items), a.n_units, k, f);
@@ -743,6 +748,13 @@ hipError_t launch_step_g(const AttnArgs& a, const MaterializeArgs& m, hipStream_
     return hipErrorInvalidValue;
 }
 
+// A step that reads more than the last-level cache holds (256 MB) finds nothing of the cache there in the next one, and leaving its
+// rows there costs a launch 5 to 10 %: then they pass it by (past_llc: distinct pages, tails and projection
+// weights of all layers).  Below that they are left there and found again.  us per pass of 8 steps, left there -> passing by,
+// by what a step reads: 8B shape, eight layers, one user 167 MB 594 -> 642, 233 MB 696 -> 712, 265 MB 757 -> 754, 298 MB 824 -> 792, 396 MB
+// 968 -> 907; four layers, four users 224 MB 539 -> 560, 277 MB 621 -> 622, 382 MB 814 -> 739; compressed 164 + 134 MB 869 -> 835.
+// Large caches: decode of sixteen 8B users over 5000 tokens 1925 -> 1762, of four 70B users over 20 000 2250 -> 2073, of
+// one 8B user over 10 000 1052 -> 990.  The weights stay on the ordinary path: what is left of the cache then holds them.
 template <int G>
 hipError_t launch_g(const AttnArgs& a, hipStream_t s) {
     const bool f8 = a.kv_fmt == MATKV_PAGE_E4M3;        // compressed pages: the default shapes only
@@ -752,13 +764,14 @@ hipError_t launch_g(const AttnArgs& a, hipStream_t s) {
     }
     if (a.shared) {
         const KernelArgs k = make_kernel_args(a);
-        auto kern = f8 ? attn_mfma_kernel<G, 4, 1, 2, 0, true, true> : attn_mfma_kernel<G, 4, 1, 2, 0, false, true>;
+        auto kern = a.past_llc ? (f8 ? attn_mfma_kernel<G, 4, 1, 2, 0, true, true, true> : attn_mfma_kernel<G, 4, 1, 2, 0, false, true, true>)
+                               : (f8 ? attn_mfma_kernel<G, 4, 1, 2, 0, true, true> : attn_mfma_kernel<G, 4, 1, 2, 0, false, true>);
         hipLaunchKernelGGL(kern, dim3(a.n_units, a.Hkv, 1), dim3(4 * 64), 0, s,
                            reinterpret_cast<const Unit*>(a.table + a.off_units), reinterpret_cast<const InstanceInfo*>(a.table + a.off_inst),
                            reinterpret_cast<const Item*>(a.table + a.off_items), a.n_units, k, StepArgs{});
         return hipGetLastError();
     }
-    if (f8) return launch_v<G, 4, 1, 2, true>(a, 1, s);
+    if (f8) return a.past_llc ? launch_v<G, 4, 1, 2, true, true>(a, 1, s) : launch_v<G, 4, 1, 2, true>(a, 1, s);
     // decode: variant 9000 + 10 * (blocks in flight) + waves
     switch (a.variant % 100) {
         case 24: return launch_v<G, 4, 1, 2>(a, 1, s);
@@ -769,7 +782,7 @@ hipError_t launch_g(const AttnArgs& a, hipStream_t s) {
     }
     // measured: four waves are ahead for every group size (config 4, G = 8: 62.7 us against
     // 65.1 us with eight)
-    return launch_v<G, 4, 1, 2>(a, 1, s);
+    return a.past_llc ? launch_v<G, 4, 1, 2, false, true>(a, 1, s) : launch_v<G, 4, 1, 2>(a, 1, s);
 }
 
 }  // namespace

@@ -68,6 +68,7 @@ struct TableHost {
     int max_tail_len = 0;     // largest tail_len of any instance (host mirror)
     int min_tail_len = 0;
     int n_decode_slots = 0;   // partial slots a decode launch writes (units, or (unit, user) pairs when shared)
+    bool past_llc = false;    // a decode step over all layers reads more than the last-level cache holds
     std::vector<const void*> slots;   // distinct slots its pages point into
 };
 
@@ -1428,11 +1429,16 @@ matkv_status matkv_assemble(matkv_ctx* c, const matkv_page* pages, const int32_t
     sign_partition(th);
     // Slot bookkeeping: the table's old contents are dead from here on in stream order, so the
     // slots only they pointed into may be overwritten once the work enqueued so far is done.
+    size_t page_tokens = 0;
     for (int b = 0; b < batch; ++b) {
         const matkv_page* pg = pages ? pages + (size_t)b * cfg.max_pages : nullptr;
         for (int p = 0; p < n_pages[b]; ++p)
-            if (std::find(th.slots.begin(), th.slots.end(), pg[p].slot) == th.slots.end()) th.slots.push_back(pg[p].slot);
+            if (std::find(th.slots.begin(), th.slots.end(), pg[p].slot) == th.slots.end()) { th.slots.push_back(pg[p].slot); page_tokens += pg[p].n_tokens; }
     }
+    // What a step reads of a layer: the distinct pages, the tails, the projection's weights.  All layers of it are read again by
+    // the next step, from the last-level cache if they fit there.
+    const size_t rows = 2 * (size_t)cfg.n_kv_heads * cfg.head_dim, esz = cfg.dtype == MATKV_BF16 ? 2 : 4;
+    th.past_llc = rows * (page_tokens * (kv_fmt == MATKV_PAGE_E4M3 ? 1 : esz) + ((size_t)cu + cfg.hidden) * esz) * cfg.n_layers > kLastLevelCacheBytes;
     auto old = c->tables.find(table);
     if (old != c->tables.end() && !old->second.slots.empty()) {
         hipEvent_t& ev = c->release_ev[c->release_next];
@@ -1631,6 +1637,7 @@ static matkv_status attn_args(matkv_ctx* c, const char* name, int prefill, int32
     a.prefill = prefill;
     a.rows = prefill ? th->max_q : 1;
     a.shared = !prefill && th->n_sunits > 0;
+    a.past_llc = !prefill && th->past_llc;
     a.n_units = prefill ? th->prefill.n_units : (a.shared ? th->n_sunits : th->n_dunits);
     a.max_units_inst = prefill ? th->prefill.max_units_inst : 0;
     a.batch = th->batch; a.total_q = th->total_q; a.kv_fmt = th->kv_fmt;

@@ -120,6 +120,9 @@ struct WorkspaceLayout {
     size_t n_counters, partial_floats;
 };
 
+// Last-level cache of the chip, which all XCDs share.
+constexpr size_t kLastLevelCacheBytes = (size_t)256 << 20;
+
 inline int max_q_rows(const matkv_config& c) { return c.max_tail_tokens; }
 constexpr int kSplitTiles = 128;    // half the compute units: two workgroups per tile
 
@@ -178,6 +181,7 @@ struct AttnArgs {
                                // 2: as 1 for a chunk's own attention (longest row tiles first)
     float scale_log2e;
     int32_t kv_fmt;            // matkv_page_format of every page of the table
+    int32_t past_llc;          // decode: a step over all layers reads more than the last-level cache holds
     int32_t shared;            // decode over the shared partition (units = SUnit records)
     int32_t out_f32;           // bf16 configurations: q / out of the attention calls: out is float
     int32_t variant;           // kernel shape: 0 = default; 9000 + waves = matrix-core kernel;

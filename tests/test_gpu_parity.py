@@ -579,6 +579,53 @@ def test_graph_replay_matches_eager():
     chain.compare_attention(case, g_pre, g_dec, pre, dec)
 
 
+@pytest.mark.parametrize("Hq,batch,shared,compressed", [(8, 1, False, False), (24, 3, False, True), (32, 4, False, False), (32, 2, True, False),
+                                                        (16, 5, True, True), (64, 2, False, False), (64, 3, False, True)])
+def test_decode_past_the_last_level_cache(Hq, batch, shared, compressed):
+    """A model whose steps read more than 256 MB (33 layers of 8B weights) takes the kernels that leave the cache's rows out of
+    the last-level cache; one layer of it does not.  Both do the same sums in the same order, so every output and tail
+    row is the same bit for bit, over ragged pages, one of a single token among them, fused and as two launches (64 heads, batch 5)."""
+    from paper_2512_22195_amd import binding as mk
+    Hkv, D, hidden, cap = 8, 128, 4096, 40
+    lens, q_len = [333, 1, 64, 97], [31 - b for b in range(batch)]
+    g = torch.Generator(device="cuda").manual_seed(5 + Hq)
+    draw = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    w, q, x = draw(2, Hkv * D, hidden) * hidden ** -0.5, draw(batch, Hq, D), draw(batch, hidden)
+    rows = {(b, i): draw(2, Hkv, n, D) for b in range(batch) for i, n in enumerate(lens)}
+    tails = draw(2, batch, Hkv, cap, D)
+    results = []
+    for n_layers in (1, 33):
+        cfg = mk.make_config(n_layers, Hq, Hkv, D, hidden, "bf16", 500000.0, max_batch=batch, max_pages=len(lens), max_tail_tokens=cap)
+        assert (n_layers * 2 * Hkv * D * hidden * 2 > 256 << 20) == (n_layers > 1)
+        ctx = mk.Context(cfg)
+        try:
+            with torch.cuda.stream(ctx.compute_stream):
+                ctx.compute_stream.wait_stream(torch.cuda.default_stream())
+                slots = {}
+                for (b, i), r in rows.items():
+                    blob = torch.zeros((n_layers, 2, Hkv, lens[i], D), dtype=torch.bfloat16, device="cuda")
+                    blob[0] = r
+                    slots[b, i] = blob.view(torch.uint8).view(-1)
+                    if compressed:
+                        slots[b, i] = torch.empty(mk.compressed_blob_bytes(cfg, lens[i]), dtype=torch.uint8, device="cuda")
+                        ctx.compress(blob, lens[i], slots[b, i])
+                fmt = mk.PAGE_E4M3 if compressed else mk.PAGE_PLAIN
+                table = ctx.new_table()
+                ctx.assemble([[(slots[0 if shared else b, i], n, fmt) for i, n in enumerate(lens)] for b in range(batch)], q_len, table)
+                assert (ctx.table_shared_units(table) > 0) == shared
+                tail, out = tails.clone(), torch.empty((3, batch, Hq, D), dtype=torch.bfloat16, device="cuda")
+                ctx.decode_attn(0, q, table, tail[0], tail[1], out[0])
+                for step in (1, 2):
+                    ctx.advance(table, 1)
+                    ctx.decode_step(0, x, w[0], w[1], q, table, tail[0], tail[1], out[step])
+                ctx.compute_stream.synchronize()
+            results.append((out, tail))
+        finally:
+            ctx.close()
+    assert torch.isfinite(results[0][0]).all()
+    assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
+
+
 @pytest.mark.parametrize("repeats,extra,hidden,launches", [
     (1, None, 4096, 3), (31, None, 4096, 63), (32, None, 4096, 0),      # long kernels: up to 64 launches
     (31, "advance", 4096, 64), (32, "advance", 4096, 0),                # (one kernel more)
