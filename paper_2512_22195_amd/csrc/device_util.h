@@ -80,6 +80,11 @@ __device__ __forceinline__ float4 ld_agent4(const float* base, uint32_t off) {
     return make_float4(v.x, v.y, v.z, v.w);
 }
 
+__device__ __forceinline__ void st_agent4(void* base, uint32_t off, const uint4& v) {
+    constexpr int kSc1 = 16;
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(base, 0, 0xffffffffu, 0x00027000);
+    __builtin_amdgcn_raw_buffer_store_b128(u32x4v{v.x, v.y, v.z, v.w}, r, off, 0, kSc1);
+}
 // 16 bytes `off` bytes behind a wave-uniform address.  NT: not kept in the last-level cache (memory that is not read again before
 // it would have been displaced there), and as a buffer load, which a large cache's walk is 0.5 % faster with; the ordinary
 // load is 2 to 3 % faster where a step is short (8B shape, one user of 1000 tokens 583 -> 569 us per pass).
