@@ -898,7 +898,8 @@ matkv_status matkv_compress(matkv_ctx* c, const void* blob, int32_t n_tokens, vo
     const char* b = static_cast<const char*>(out);
     if (a < b + matkv_compressed_blob_bytes(&c->cfg, n_tokens) && b < a + matkv_blob_bytes(&c->cfg, n_tokens))
         return fail(c, MATKV_EINVAL, "compress: output overlaps the blob");
-    HIP_TRY(c, launch_compress(blob, out, c->cfg.n_layers, c->cfg.n_kv_heads, n_tokens, c->cfg.head_dim, c->compute));
+    HIP_TRY(c, launch_compress(blob, out, c->cfg.n_layers, c->cfg.n_kv_heads, n_tokens, c->cfg.head_dim,
+                               reinterpret_cast<float*>(c->workspace + c->wl.off_partials), c->wl.partial_floats, c->compute));
     return MATKV_OK;
 }
 

@@ -239,7 +239,8 @@ hipError_t launch_decode_step(const AttnArgs& a, const MaterializeArgs& m, int d
 hipError_t launch_probe_read(const void* src, size_t bytes, unsigned* sink, hipStream_t s);
 hipError_t launch_advance(char* table, size_t off_inst, int batch, int n, int max_tail, hipStream_t s);
 hipError_t launch_chunk_table(char* table, int n_tokens, hipStream_t s);
-hipError_t launch_compress(const void* blob, void* out, int n_layers, int Hkv, int n_tokens, int D, hipStream_t s);
+// scratch: for the largest magnitudes of pieces of long heads; 2 Hkv floats at the least.
+hipError_t launch_compress(const void* blob, void* out, int n_layers, int Hkv, int n_tokens, int D, float* scratch, size_t scratch_floats, hipStream_t s);
 
 // Compressed blob: codes, then the scale table [layer][K|V][Hkv] (float), both padded to 16 bytes.
 inline size_t compressed_codes_bytes(const matkv_config& c, int n_tokens) {

@@ -1337,12 +1337,12 @@ def test_full_size_chunk_attention(L, Hq, Hkv, rows):
 
 
 # ------------------------------------------------------------------ compressed chunk blobs --
-@pytest.mark.parametrize("L", [77, 1000, 1024, 1100])
+@pytest.mark.parametrize("L", [77, 1000, 1024, 1025, 1100, 1280, 1281])
 def test_compress_is_bit_exact(L):
     """matkv_compress against the oracle: every code byte and every scale.  Heads of very
     different magnitudes, one head of zeros, one tiny head on the scale floor, values on exact
     ties of the 8-bit grid, a largest value just above a power-of-two boundary.  Chunks of up to
-    1024 tokens take the kernel that keeps a head in registers, longer ones the two-pass kernel."""
+    1024 tokens take the kernel that keeps a head in registers, longer ones the two launches over pieces of 256 tokens."""
     from paper_2512_22195_amd import binding as mk
     from workload import normal, to_f64
     import oracle
@@ -1377,6 +1377,34 @@ def test_compress_is_bit_exact(L):
     assert scales[1, 0, 2] == 1.0 and (codes[1, 0, 2] & 0x7F == 0).all()       # head of zeros
     assert scales[1, 1, 3] == 2.0 ** -60                                       # floor
     assert scales[1, 1, 0] == 2.0 ** -6
+
+
+@pytest.mark.parametrize("n_layers,L,D", [(3, 33001, 128), (5, 10243, 64)])
+def test_compress_of_many_pieces(n_layers, L, D):
+    """Long heads: several launches (layers in groups of at most 128 MB, here one by one and all at once), pieces with a ragged end, the
+    largest value in another piece of every head.  Codes and scales against the library cast of x / s, s by the rule, bit for bit."""
+    from paper_2512_22195_amd import binding as mk
+    Hkv = 8
+    ctx = mk.Context(mk.make_config(n_layers, Hkv, Hkv, D, 256, "bf16", 10000.0, max_batch=1, max_pages=1, max_tail_tokens=8))
+    try:
+        with torch.cuda.stream(ctx.compute_stream):
+            g = torch.Generator(device="cuda").manual_seed(L)
+            blob = torch.empty((n_layers, 2, Hkv, L, D), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+            heads = blob.view(-1, L, D)
+            for h in range(heads.shape[0]):
+                heads[h, (h * 257 * 5 + L - 1) % L, h % D] = 8.0 + h
+            out = torch.zeros(mk.compressed_blob_bytes(ctx.cfg, L), dtype=torch.uint8, device="cuda")
+            ctx.compress(blob, L, out)
+            amax = heads.float().abs().amax(dim=(1, 2))
+            s = torch.exp2(torch.ceil(torch.log2(amax / 448.0)))
+            ctx.compute_stream.synchronize()
+        n = blob.numel()
+        assert torch.equal(out[(n + 15) // 16 * 16:].view(torch.float32)[:heads.shape[0]], s)
+        for h in range(heads.shape[0]):
+            want = (heads[h].float() / s[h]).to(torch.float8_e4m3fn).view(torch.uint8).view(-1)
+            assert torch.equal(out[h * L * D:(h + 1) * L * D], want), f"head {h}"
+    finally:
+        ctx.close()
 
 
 @pytest.mark.parametrize("name,Hq,Hkv,use_graph", [("g4", 8, 2, False), ("g1", 2, 2, False), ("g8", 8, 1, True), ("g2", 4, 2, False)])
