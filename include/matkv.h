@@ -259,7 +259,9 @@ matkv_status matkv_assemble(matkv_ctx* ctx, const matkv_page* pages_host,
  * batch of `batch` instances like it (no GPU is touched): page_tokens_host[n_pages] are the
  * chunk lengths, q_len the question length.  Unit u streams unit_tokens_out[u] page tokens and
  * is made of unit_items_out[u] page pieces; the last unit also owns the tail.  Returns the
- * number of units (at most cap), or -1 on a bad argument.  Either output may be NULL. */
+ * number of units (at most cap), or -1 on a bad argument.  Either output may be NULL.  (Where these
+ * units would leave compute units idle or waiting, matkv_assemble has decode launches take runs of
+ * equal length across the batch's caches instead; results are the same.) */
 int32_t matkv_plan_decode_units(const matkv_config* cfg, const int32_t* page_tokens_host,
                                 int32_t n_pages, int32_t batch, int32_t q_len,
                                 int32_t* unit_tokens_out, int32_t* unit_items_out, int32_t cap);

@@ -354,6 +354,8 @@ __global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && 
     const bool walks = FR == 0 || (int)blockIdx.x < n_units;
     const Unit unit = SH ? table_record(&su->u) : table_record(units + (FR > 0 ? min((int)blockIdx.x, n_units - 1) : (int)blockIdx.x));
 
+    if (SH && su->n_users == 0) return;                 // (the even partition's last runs may be empty)
+
     // The other arguments are wanted here, together with the record: fetched where they are first used, each group of them
     // would be waited for by itself (3B shape, three short instances: 1428 -> 1385 us per pass of 128 steps and layers).
     asm volatile("" :: "s"(a.q), "s"(a.out), "s"(a.tail_k), "s"(a.tail_v), "s"(a.partials), "s"(a.counters), "s"(a.layer), "s"(a.Hq), "s"(a.Hkv),

@@ -64,6 +64,7 @@ struct TableHost {
     PrefillLayout prefill;
     int kv_fmt = 0;           // matkv_page_format of its pages
     int n_sunits = 0;         // units of the shared decode partition; 0 = the batch shares no page
+    bool even = false;        // decode launches take the even partition, whose units lie behind the others in the table
     uint64_t sig_decode = 0, sig_prefill = 0;   // of what a recorded decode / prefill launch bakes in
     int max_tail_len = 0;     // largest tail_len of any instance (host mirror)
     int min_tail_len = 0;
@@ -473,6 +474,112 @@ PrefillLayout lay_out_prefill(const matkv_config& cfg, const matkv_page* pages, 
     return L;
 }
 
+// Even decode partition: the batch's caches end to end (an instance's pages, then its tail), cut into runs of nearly equal length
+// without regard to where an instance ends, one workgroup per KV head each, in the records of the shared partition (below).  A run holds
+// one tail at the most, so two instances, and each (run, instance) pair has a partial slot.  Always 256 / KV heads runs, empty ones at
+// the end: a recorded step has that launch shape whatever the lengths.  By instance, a batch of 17 leaves half of the chip idle, and a
+// ragged one waits for its longest cache.
+// Returns whether launches take it.  Its kernel looks up whose rows are whose and costs 2 to 4 us more, as long as a workgroup takes for 150
+// tokens: so only where the longest workgroup has 400 tokens fewer than by instance, and there an eighth of the compute units would be idle or
+// it would be half as long again.  us per layer step, caches of 3600 tokens unless said, by instance -> even: 8B shape, 12 users 46.8 -> 44.0, ragged
+// (1080 to 3600) 40.4 -> 35.6, 17 users 75.0 -> 59.0, ragged 66.7 -> 44.6, 24 users 83.7 -> 75.5, ragged 66.6 -> 55.5; 70B shape, 17 users
+// 86.7 -> 64.7.  Beyond the line: 5 users 26.1 -> 28.4, 9 users 35.7 -> 36.3, 32 ragged 76.2 -> 75.2 (70B 81.7 -> 82.1), 24 users of 400
+// tokens 23.9 -> 25.5.
+constexpr long kEvenMinGranules = 16;           // 128 tokens
+bool build_even_units(const matkv_config& cfg, const matkv_page* pages, const int32_t* n_pages, int batch, InstanceInfo* insts, Item* items,
+                      int* n_items, int n_dunits, SUnit* sunits, int kv_fmt) {
+    const int n_units = 256 / cfg.n_kv_heads;
+    auto tail_gran = [&](int b) { return (long)(insts[b].q_len + (cfg.max_tail_tokens - insts[b].q_len) / 2 + 7) / 8; };
+    long total = 0, by_inst = 0;                    // by_inst: tokens of the longest unit by instance
+    for (int b = 0; b < batch; ++b) {
+        long inst = tail_gran(b);
+        for (int p = 0; p < n_pages[b]; ++p) inst += (pages[(size_t)b * cfg.max_pages + p].n_tokens + 7) / 8;
+        total += inst;
+        by_inst = std::max(by_inst, 8 * inst / std::max(insts[b].n_dunits, 1));
+    }
+    // runs of `per` granules of eight tokens; emit = false only counts them
+    auto cut = [&](long per, bool emit) {
+        int n = 0;                                              // runs opened
+        long room = 0;
+        bool has_tail = true;                                   // (of the open run: nothing fits any more)
+        SUnit* su = nullptr;
+        Item* it = items + *n_items;
+        for (int b = 0; b < batch; ++b) {
+            if (emit) insts[b].n_sslots = 0;
+            bool joined = false;                                // the open run has this instance among its users
+            auto open = [&]() {
+                if (emit) {
+                    su = sunits + n;
+                    memset(su, 0, sizeof(*su));
+                    su->u.item0 = (int)(it - items);
+                    su->u.idx_in_inst = n;
+                }
+                ++n;
+                room = per; has_tail = false; joined = false;
+            };
+            auto add = [&](const Item& piece) {
+                if (!joined) {
+                    su->users[su->n_users].inst = b;
+                    su->users[su->n_users++].slot = insts[b].n_sslots++;        // (of the instance; its first slot is added below)
+                    joined = true;
+                }
+                *it = piece;
+                it->umask = 1 << (su->n_users - 1);
+                ++it; ++su->u.n_items;
+            };
+            for (int p = 0; p < n_pages[b]; ++p) {
+                const matkv_page& pg = pages[(size_t)b * cfg.max_pages + p];
+                const long gran = (pg.n_tokens + 7) / 8;
+                for (long g = 0; g < gran;) {
+                    if (room <= 0) open();
+                    const long take = std::min(gran - g, room);
+                    if (emit) {
+                        Item piece;
+                        memset(&piece, 0, sizeof(piece));
+                        piece.base = reinterpret_cast<uint64_t>(pg.slot);
+                        piece.page_tokens = pg.n_tokens;
+                        piece.tok0 = (int)(g * 8);
+                        piece.ntok = (int)std::min<long>(pg.n_tokens, (g + take) * 8) - piece.tok0;
+                        piece.fmt = kv_fmt;
+                        piece.scales16 = kv_fmt == MATKV_PAGE_E4M3 ? (int32_t)(compressed_codes_bytes(cfg, pg.n_tokens) / 16) : 0;
+                        su->u.page_tokens += piece.ntok;
+                        add(piece);
+                    }
+                    g += take; room -= take;
+                }
+            }
+            if (room <= 0 || has_tail) open();                  // a tail is not cut
+            if (emit) {
+                Item piece;
+                memset(&piece, 0, sizeof(piece));
+                piece.page_tokens = cfg.max_tail_tokens; piece.ntok = cfg.max_tail_tokens;
+                su->u.has_tail = 1; su->u.inst = b;
+                add(piece);
+            }
+            has_tail = true;
+            room -= tail_gran(b);
+        }
+        if (emit) *n_items = (int)(it - items);
+        return n;
+    };
+    // the shortest runs of which there are no more than workgroups (one per instance is always few enough)
+    long per = std::max(kEvenMinGranules, (total + n_units - 1) / n_units);
+    while (cut(per, false) > n_units) per += std::max<long>(1, per / 32);
+    const int n = cut(per, true);
+    if (n < n_units) memset(static_cast<void*>(sunits + n), 0, sizeof(SUnit) * (n_units - n));
+    int slot0 = 0;
+    for (int b = 0; b < batch; ++b) { insts[b].sslot0 = slot0; slot0 += insts[b].n_sslots; }
+    for (int u = 0; u < n; ++u) {
+        Unit& un = sunits[u].u;
+        // the tail goes last (compressed pages: the kernel walks the code pages and then the plain tail)
+        for (int i = un.item0; i + 1 < un.item0 + un.n_items; ++i)
+            if (items[i].base == 0) std::rotate(items + i, items + i + 1, items + un.item0 + un.n_items);
+        un.first = items[un.item0];
+        for (int k = 0; k < sunits[u].n_users; ++k) sunits[u].users[k].slot += insts[sunits[u].users[k].inst].sslot0;
+    }
+    return by_inst - 8 * per > 400 && (8 * n_dunits <= 7 * n_units || 2 * by_inst > 3 * 8 * per);
+}
+
 // Shared decode partition (instances of a batch that retrieved the same chunk read it once).
 // The batch's DISTINCT pages and its tails form one stream of token rows - per instance its
 // private pages, then the shared pages it uses first, then its tail - which is cut into equal
@@ -677,6 +784,16 @@ int build_shared_units(const matkv_config& cfg, const matkv_page* pages, const i
 TableHost* find_table(matkv_ctx* c, const void* t) {
     auto it = c->tables.find(t);
     return it == c->tables.end() ? nullptr : &it->second;
+}
+
+// Whether a batch without shared pages gets the even partition (build_even_units) beside the one by instance: one whose step is not
+// the fused launch.  A step that was recorded over it replays over every table with the same batch and units by instance, and this says the
+// same of all of them.  Its units follow the others in their section (and are copied with them).
+bool even_partition(const matkv_config& cfg, int batch, int n_dunits) {
+    const int g = cfg.n_q_heads / cfg.n_kv_heads, n_units = 256 / cfg.n_kv_heads;
+    return cfg.decode_units == 0 && cfg.decode_variant == 0 && cfg.dtype == MATKV_BF16 && cfg.head_dim == 128 && group_size_built(g) &&
+           batch >= 2 && (batch > 4 || g > 4) && batch <= n_units &&
+           sizeof(Unit) * n_dunits + sizeof(SUnit) * n_units <= sizeof(Unit) * (size_t)table_layout(cfg).max_dunits;
 }
 
 // Launch shapes and kernel choices are fixed when a call is recorded; they follow from these.
@@ -1407,13 +1524,18 @@ matkv_status matkv_assemble(matkv_ctx* c, const matkv_page* pages, const int32_t
         cfg.dtype == MATKV_BF16 && cfg.head_dim == 128 && group_size_built(grp))
         n_sunits = build_shared_units(cfg, pages, n_pages, batch, c->tl.max_sunits, c->tl.max_items, insts, items, &n_items,
                                       reinterpret_cast<SUnit*>(h + c->tl.off_sunits), kv_fmt);
+    size_t dunit_bytes = sizeof(Unit) * n_dunits;
+    if (n_sunits == 0 && even_partition(cfg, batch, n_dunits)) {
+        th.even = build_even_units(cfg, pages, n_pages, batch, insts, items, &n_items, n_dunits, reinterpret_cast<SUnit*>(dunits + n_dunits), kv_fmt);
+        dunit_bytes += sizeof(SUnit) * (256 / cfg.n_kv_heads);
+    }
     hdr->batch = batch; hdr->n_items = n_items; hdr->n_dunits = n_dunits; hdr->n_punits = th.prefill.n_units;
     hdr->total_q = cu; hdr->max_q = max_q;
 
     char* d = reinterpret_cast<char*>(table);
     HIP_TRY(c, hipMemcpyAsync(d, h, c->tl.off_inst + sizeof(InstanceInfo) * batch, hipMemcpyHostToDevice, c->compute));
     HIP_TRY(c, hipMemcpyAsync(d + c->tl.off_items, h + c->tl.off_items, sizeof(Item) * n_items, hipMemcpyHostToDevice, c->compute));
-    HIP_TRY(c, hipMemcpyAsync(d + c->tl.off_dunits, h + c->tl.off_dunits, sizeof(Unit) * n_dunits, hipMemcpyHostToDevice, c->compute));
+    HIP_TRY(c, hipMemcpyAsync(d + c->tl.off_dunits, h + c->tl.off_dunits, dunit_bytes, hipMemcpyHostToDevice, c->compute));
     HIP_TRY(c, hipMemcpyAsync(d + c->tl.off_punits, h + c->tl.off_punits, sizeof(Unit) * th.prefill.n_units, hipMemcpyHostToDevice, c->compute));
     if (n_sunits > 0)
         HIP_TRY(c, hipMemcpyAsync(d + c->tl.off_sunits, h + c->tl.off_sunits, sizeof(SUnit) * n_sunits, hipMemcpyHostToDevice, c->compute));
@@ -1423,7 +1545,7 @@ matkv_status matkv_assemble(matkv_ctx* c, const matkv_page* pages, const int32_t
     th.batch = batch; th.n_items = n_items; th.n_dunits = n_dunits;
     th.total_q = cu; th.max_q = max_q; th.kv_fmt = kv_fmt; th.n_sunits = n_sunits;
     th.n_decode_slots = n_dunits;
-    if (n_sunits > 0) {
+    if (n_sunits > 0 || th.even) {
         th.n_decode_slots = 0;
         for (int b = 0; b < batch; ++b) th.n_decode_slots = std::max(th.n_decode_slots, insts[b].sslot0 + insts[b].n_sslots);
     }
@@ -1637,9 +1759,10 @@ static matkv_status attn_args(matkv_ctx* c, const char* name, int prefill, int32
     a.max_tail = c->cfg.max_tail_tokens;
     a.prefill = prefill;
     a.rows = prefill ? th->max_q : 1;
-    a.shared = !prefill && th->n_sunits > 0;
+    const bool even = !prefill && th->even;
+    a.shared = !prefill && (th->n_sunits > 0 || even);
     a.past_llc = !prefill && th->past_llc;
-    a.n_units = prefill ? th->prefill.n_units : (a.shared ? th->n_sunits : th->n_dunits);
+    a.n_units = prefill ? th->prefill.n_units : (even ? 256 / c->cfg.n_kv_heads : a.shared ? th->n_sunits : th->n_dunits);
     a.max_units_inst = prefill ? th->prefill.max_units_inst : 0;
     a.batch = th->batch; a.total_q = th->total_q; a.kv_fmt = th->kv_fmt;
     a.row_tiles = th->prefill.row_tiles;
@@ -1648,7 +1771,7 @@ static matkv_status attn_args(matkv_ctx* c, const char* name, int prefill, int32
     a.scale_log2e = c->scale_log2e;
     a.out_f32 = c->cfg.dtype == MATKV_BF16 && c->cfg.out_f32;
     a.off_inst = c->tl.off_inst; a.off_items = c->tl.off_items;
-    a.off_units = prefill ? c->tl.off_punits : (a.shared ? c->tl.off_sunits : c->tl.off_dunits);
+    a.off_units = prefill ? c->tl.off_punits : even ? c->tl.off_dunits + sizeof(Unit) * th->n_dunits : (a.shared ? c->tl.off_sunits : c->tl.off_dunits);
     *out_args = a;
     return MATKV_OK;
 }

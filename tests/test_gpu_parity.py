@@ -626,6 +626,97 @@ def test_decode_past_the_last_level_cache(Hq, batch, shared, compressed):
     assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
 
 
+def _decode_batch(Hq, caches, q_lens, compressed, decode_units, replays=(), max_pages=4):
+    """Decode outputs (float) of a batch whose instance b has pages of caches[b] tokens; with replays, those of a step recorded over
+    that table and replayed after each re-assembly with other caches.  Same seeds, same contents, whatever the partition."""
+    from paper_2512_22195_amd import binding as mk
+    Hkv, D, cap, batch = 8, 128, 24, len(caches)
+    ctx = mk.Context(mk.make_config(1, Hq, Hkv, D, 256, "bf16", 10000.0, max_batch=batch, max_pages=max_pages, max_tail_tokens=cap,
+                                    decode_units=decode_units, out_f32=1))
+    fmt = mk.PAGE_E4M3 if compressed else mk.PAGE_PLAIN
+    keep, outs = [], []
+    try:
+        with torch.cuda.stream(ctx.compute_stream):
+            g = torch.Generator(device="cuda").manual_seed(17)
+            draw = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+            q, tail, table = draw(batch, Hq, D), draw(2, batch, Hkv, cap, D), ctx.new_table()
+
+            def assemble(caches):
+                pages = []
+                for lens in caches:
+                    pages.append([])
+                    for n in lens:
+                        blob = draw(1, 2, Hkv, n, D)
+                        slot = torch.empty(mk.compressed_blob_bytes(ctx.cfg, n), dtype=torch.uint8, device="cuda") if compressed else blob.view(torch.uint8).view(-1)
+                        if compressed:
+                            ctx.compress(blob, n, slot)
+                        keep.append(slot)
+                        pages[-1].append((slot, n, fmt))
+                ctx.assemble(pages, q_lens, table)
+                assert ctx.table_shared_units(table) == 0
+            assemble(caches)
+            out = torch.zeros((batch, Hq, D), dtype=torch.float32, device="cuda")
+            if not replays:
+                for _ in range(2):                              # the second finds the arrival counters at zero again
+                    ctx.decode_attn(0, q, table, tail[0], tail[1], out)
+                outs.append(out.clone())
+            else:
+                ctx.graph_begin()
+                ctx.decode_attn(0, q, table, tail[0], tail[1], out)
+                graph = ctx.graph_end()
+                for c in replays:
+                    assemble(c)
+                    out.zero_()
+                    ctx.graph_launch(graph)
+                    outs.append(out.clone())
+            ctx.compute_stream.synchronize()
+            if replays:
+                ctx.graph_destroy(graph)
+        return outs
+    finally:
+        ctx.close()
+
+
+def _same_attention(a, b):
+    """Two partitions of the same caches: weights are rounded to bf16 against other references, 2^-9 of a value each, and sums are taken
+    in another order; the bar is that of one side against the oracle."""
+    rms = b.pow(2).mean(dim=(1, 2), keepdim=True).sqrt()
+    assert torch.isfinite(a).all() and ((a - b).abs() <= 2e-2 * rms).all(), ((a - b).abs() / rms).max()
+
+
+@pytest.mark.parametrize("compressed", [False, True], ids=["plain", "compressed"])
+@pytest.mark.parametrize("Hq,caches,units,even", [
+    (32, [[1000]] * 17, 1, True),                                       # an even batch that leaves compute units idle
+    (8, [[3000, 7]] + [[], [1], [8, 9], [64]] * 4, 1, True),            # one long cache, short ones, none at all
+    (16, [[700, 40]] * 30 + [[1999, 2001]], 1, True),                   # as many instances as there are runs, but one
+    (24, [[900, 33, 1], [2800, 801], [64], [1500]] * 3, 2, True),       # two units by instance, ragged
+    (64, [[8001], [100], [50]], 10, True),                              # two instances at most fit a tile of 64 heads
+    (64, [[500, 3000, 2999, 1502], [1, 2, 3, 4]], 16, True),
+    (32, [[600]] * 17, 1, False), (16, [[1000]] * 32, 1, False), (24, [[2000]] * 12, 2, False),
+])
+def test_decode_over_even_runs(Hq, caches, units, even, compressed):
+    """The even partition against the one by instance (decode_units fixed): the same attention.  Where the rule leaves it aside, outputs are
+    those of the partition by instance bit for bit."""
+    q_lens = [1 + (5 * b) % 23 for b in range(len(caches))]
+    got, = _decode_batch(Hq, caches, q_lens, compressed, 0)
+    want, = _decode_batch(Hq, caches, q_lens, compressed, units)
+    _same_attention(got, want)
+    assert torch.equal(got, want) != even
+
+
+def test_recorded_decode_replays_over_either_partition():
+    """A step recorded over a table with even runs replays over one that would be taken by instance, and the other way round, empty runs and
+    caches without pages among them, as recordings over tables with as many units by instance always have."""
+    q_lens = [3 + b for b in range(17)]
+    long, short = [[1000]] * 17, [[100], [200, 28], []] * 5 + [[5], [190]]
+    mixed = [[3000]] + [[20]] * 16
+    for first in (long, short):
+        got = _decode_batch(32, first, q_lens, False, 0, replays=[short, long, mixed, short])
+        want = _decode_batch(32, first, q_lens, False, 1, replays=[short, long, mixed, short])
+        for a, b in zip(got, want):
+            _same_attention(a, b)
+
+
 @pytest.mark.parametrize("repeats,extra,hidden,launches", [
     (1, None, 4096, 3), (31, None, 4096, 63), (32, None, 4096, 0),      # long kernels: up to 64 launches
     (31, "advance", 4096, 64), (32, "advance", 4096, 0),                # (one kernel more)
