@@ -197,13 +197,15 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     if (F8 && unit.first.base) page_scales(unit.first, a.layer, a.Hkv, kvh, wk.sk, wk.sv);
     fetch_item(1);
     // where a block's rows lie: K and V of its first row, row stride 2 D bytes (codes: D bytes).  Past the
-    // unit's end the last block's first row is copied instead (a branch around the copies there cost 3 %).
+    // unit's end the last block's first row is copied instead (a branch around the copies there cost 3 %); over compressed
+    // pages (n = 0) nothing is: two blocks fetched and widened for nothing are a large part of a walk of three steps.
     struct Source { const char* k; const char* v; int n; bool codes; };
     Source src;
     src.k = wk.k; src.v = wk.v; src.n = 1; src.codes = F8 && wk.row_bytes == D;
     auto next_step = [&](BlockDesc& d) {
         d.n = -1; d.t0 = kPageT0; d.sk = 1.f; d.sv = 1.f;
-        src.n = 1;
+        src.n = F8 ? 0 : 1;
+        if (F8) src.codes = false;
 #pragma unroll
         for (int g = 0; g < TS; ++g) {
             while (wk.left <= 0 && wk.item_i + 1 < unit.n_items) {
@@ -219,7 +221,10 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
                 src.k = wk.k; src.v = wk.v; src.n = n; src.codes = F8 && wk.row_bytes == D;
                 d.n = wave_live && wk.t0 < vis_max ? n : 0;
                 d.t0 = wk.t0;
-                if (F8) { d.sk = wk.sk; d.sv = wk.sv; }
+                if (F8) {
+                    d.sk = wk.sk; d.sv = wk.sv;
+                    if (TS == 2) asm volatile("" : "+v"(d.sk), "+v"(d.sv));      // (in vector registers: the scalar ones are all taken)
+                }
             }
             wk.left -= n;
             wk.t0 += n;
@@ -258,6 +263,11 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     };
     // Compressed pages: codes go through registers (one step ahead of the copy they replace) and are
     // widened to bf16 on their way into the tile.  A lane moves 16 codes of a row: two pieces.
+    // As with plain pages, the first scores wait for Q and K of the first block only, and V and the second block are widened beside
+    // them.  us per layer, one user, the form with a barrier behind each phase / both blocks waited for and two more
+    // widened past the end / now: 8B shape, 10 000 tokens and 4 rows 17.2 / 18.4 / 17.0, 64 rows 29.4 / 29.7 / 28.7, 1200 tokens and 32 rows 16.2 / 17.3 / 16.4,
+    // 333 tokens and 100 rows 16.0 / 16.8 / 16.0; 70B shape, 10 000 tokens and 4 rows 18.0 / 19.6 / 17.9.
+    // Tried: the codes of a step widened between its matrix instructions, K's half a step after they were asked for (+3 to 17 %).
     constexpr int NC = TB * D / (RW * 64 * 16);         // 16-byte loads per lane, of K and of V
     struct Codes { uint4 w[NC]; } kc, vc;
     const int ct = rw * 64 + lane;
@@ -265,14 +275,15 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
 #pragma unroll
         for (int i = 0; i < NC; ++i) c.w[i] = ldg16(from + (uint32_t)min((ct >> 3) + RW * 8 * i, n - 1) * D + 16 * (ct & 7));
     };
+    auto store_codes1 = [&](const Codes& c, int at, bool v, int i) {
+        const int r = (ct >> 3) + RW * 8 * i, p = 2 * (ct & 7), turn = v ? 4 * (r & 3) : r & 15;
+        char* const row = group_lds + at + r * (2 * D);
+        *reinterpret_cast<uint4*>(row + 16 * (p ^ turn)) = e4m3x8_to_bf16x8(make_uint2(c.w[i].x, c.w[i].y));
+        *reinterpret_cast<uint4*>(row + 16 * ((p + 1) ^ turn)) = e4m3x8_to_bf16x8(make_uint2(c.w[i].z, c.w[i].w));
+    };
     auto store_codes = [&](const Codes& c, int at, bool v) {
 #pragma unroll
-        for (int i = 0; i < NC; ++i) {
-            const int r = (ct >> 3) + RW * 8 * i, p = 2 * (ct & 7), turn = v ? 4 * (r & 3) : r & 15;
-            char* const row = group_lds + at + r * (2 * D);
-            *reinterpret_cast<uint4*>(row + 16 * (p ^ turn)) = e4m3x8_to_bf16x8(make_uint2(c.w[i].x, c.w[i].y));
-            *reinterpret_cast<uint4*>(row + 16 * ((p + 1) ^ turn)) = e4m3x8_to_bf16x8(make_uint2(c.w[i].z, c.w[i].w));
-        }
+        for (int i = 0; i < NC; ++i) store_codes1(c, at, v, i);
     };
 
     f32x16 ot[4];                     // O^T: dims 32 t + 8 (i / 4) + 4 g2 + i % 4 of the lane's row
@@ -301,8 +312,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     Codes k0, v0, k1, v1;             // (compressed pages: of blocks 0 and 1)
     next_step(q[0]);
     const Source src0 = src;
-    if (F8 && src0.codes) { load_codes(k0, src0.k, src0.n); load_codes(v0, src0.v, src0.n); }
-    else                  { copy_k(src0, 0); if (F8) copy_v(src0, 0); }
+    if (F8 && src0.codes)         load_codes(k0, src0.k, src0.n);
+    else if (!F8 || src0.n > 0)   copy_k(src0, 0);
     // Q comes through LDS as well - over tiles that nothing else needs yet - so
     // that whole rows are fetched; padding rows repeat the last real row.  Placed like K rows, and read like them: B operand, lane's row c32.
     // (Two groups: rows 0 to 63 in the third V tile of the first, the rest in that of the second.)
@@ -322,15 +333,24 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     }
     next_step(q[1]);
     const Source src1 = src;
-    if (F8) {
-        if (src1.codes) { load_codes(k1, src1.k, src1.n); load_codes(v1, src1.v, src1.n); }
-        else            { copy_k(src1, 1); copy_v(src1, 1); }
-        if (src0.codes) { store_codes(k0, k_at(0), false); store_codes(v0, v_at(0), true); }
-        if (src1.codes) { store_codes(k1, k_at(1), false); store_codes(v1, v_at(1), true); }
+    const bool both = F8 && TS == 2 && src0.codes && src1.codes;
+    if (both) {                                 // (one straight piece, so that K is waited for without the loads behind it; 256-row tiles got 1 to 2 % slower by it)
+        load_codes(v0, src0.v, src0.n);
+        load_codes(k1, src1.k, src1.n); load_codes(v1, src1.v, src1.n);
+        store_codes(k0, k_at(0), false);
+    } else if (F8) {
+        if (src0.codes)         { load_codes(v0, src0.v, src0.n); store_codes(k0, k_at(0), false); }
+        else if (src0.n > 0)    copy_v(src0, 0);
+#pragma unroll
+        for (int i = 0; i < NC; ++i)            // (K has arrived here too: otherwise all is waited for where the branches meet)
+            asm volatile("" :: "v"(k0.w[i].x), "v"(k0.w[i].y), "v"(k0.w[i].z), "v"(k0.w[i].w));
+        if (src1.codes)         { load_codes(k1, src1.k, src1.n); load_codes(v1, src1.v, src1.n); }
+        else if (src1.n > 0)    { copy_k(src1, 1); copy_v(src1, 1); }
     }
     next_step(q[2]);
     const Source src2 = src;
-    dev::dma_wait<0>();                         // Q and K of block 0 are there (compressed pages: both blocks)
+    // Q and K of block 0 are there (of compressed pages the 3 NC loads behind them may still be on their way)
+    if (both) dev::dma_wait<3 * NC>(); else dev::dma_wait<0>();
     lds_barrier();
     bf16x8 bq[8];                     // dims 16 c + 8 g2 ..
     const int vis = div_g(min(wm0 + c32, n_m - 1)) + 1;    // tail rows this lane's row may see
@@ -482,14 +502,21 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     // Block 0's scores, first weights and maxima; what else step 0 finds in LDS is copied meanwhile, in the order in which it
     // is needed (the copies ahead of them would hold up the waves for 1.5 us).
     auto first_copies = [&](int i) {
-        if (F8) return;
+        if (F8) {                                   // (codes: widened beside the second half's scores)
+            const int k = i - 8;
+            if (k < 0)                               return;
+            if (k < NC)                              { if (src0.codes) store_codes1(v0, v_at(0), true, k); }
+            else if (k < 2 * NC)                     { if (src1.codes) store_codes1(k1, k_at(1), false, k - NC); }
+            else if (k < 3 * NC)                     { if (src1.codes) store_codes1(v1, v_at(1), true, k - 2 * NC); }
+            return;
+        }
         if (i < NI)                      copy_v1(src0, 0, i);
         else if (i < 2 * NI)             copy_k1(src1, 1, i - NI);
         else if (i < 3 * NI)             copy_v1(src1, 1, i - 2 * NI);
         else if (RING4 && i < 4 * NI)    copy_k1(src2, 2, i - 3 * NI);
         else if (RING4 && i < 5 * NI)    copy_v1(src2, 2, i - 4 * NI);
     };
-    static_assert((RING4 ? 5 : 3) * NI <= 16, "a copy behind every matrix instruction at most");
+    static_assert((RING4 ? 5 : 3) * NI <= 16 && 3 * NC <= 8, "a copy behind every matrix instruction at most");
     if (q[0].n > 0) {
         int ka[8];
         k_operands(ka, 0);
@@ -520,8 +547,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
 #pragma unroll
         for (int i = 0; i < 16; ++i) first_copies(i);
     }
-    if (!F8) dev::dma_wait<NI>();                   // all but the youngest block's V is there,
-    barrier_plain();                                // and K of block 0 read by every wave
+    // all but the youngest block's V is there (compressed pages: and all that was widened), and K of block 0 read by every wave
+    if (F8) lds_barrier(); else { dev::dma_wait<NI>(); barrier_plain(); }
     // Step i: descriptors and sources move on by one block
     bool copied = false;
     Source now;
@@ -530,8 +557,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
         d = q[0]; dn = q[1];
         copied = false;
         if (F8) {
-            if (next_src.codes) { store_codes(kc, k_at(2), false); store_codes(vc, v_at(2), true); }
-            else                { copy_k(next_src, 2); copy_v(next_src, 2); copied = true; }
+            if (next_src.codes)         { store_codes(kc, k_at(2), false); store_codes(vc, v_at(2), true); }
+            else if (next_src.n > 0)    { copy_k(next_src, 2); copy_v(next_src, 2); copied = true; }
         }
         now = next_src;
 #pragma unroll

@@ -482,6 +482,20 @@ def test_prefill_short_tiles_over_block_edges(Hq, Hkv, q_lens, compressed):
 
 
 @pytest.mark.parametrize("compressed", [False, True], ids=["plain", "compressed"])
+@pytest.mark.parametrize("form,Hq,q_len", [(128, 32, 17), (128, 32, 130), (256, 64, 40), (256, 64, 130)])
+def test_prefill_walks_of_few_steps(form, Hq, q_len, compressed):
+    """Walks that end in or right behind the blocks a workgroup starts with (the first three of a token group): caches of one to seven
+    blocks in one unit each, without and with a ragged end, of the question alone, and whose first, second or third block is the
+    question's; one tile and several."""
+    tokens = [1, 63, 64, 65, 128, 129, 192, 193, 256, 257, 320, 385]
+    lens = {i: n for i, n in enumerate(tokens)}
+    case = Case(f"prefill-few-steps-{form}", n_layers=1, Hq=Hq, Hkv=8, D=128, hidden=64, dtype="bf16", chunk_lens=lens,
+                retrieved=[[i] for i in lens] + [[], [2, 2], [0, 2], [0] * 5], q_lens=[q_len] * 16, steps=1, scale=0.5, compressed=compressed)
+    assert _prefill_form(case) == (form, [1] * 16)
+    _attention_parity(case)
+
+
+@pytest.mark.parametrize("compressed", [False, True], ids=["plain", "compressed"])
 @pytest.mark.parametrize("form,Hq,Hkv,retrieved,q_lens,instances", [
     (128, 64, 8, [[0, 1], [2, 3], [4] * 11], [33, 17, 5], [0, 1, 2]),            # 3, 2 and 1 tiles, 5 units each: 240 workgroups, 360 with the idle
     (128, 64, 8, [[0, 1], [4] * 11, [2, 3]], [5, 17, 33], [0, 1, 2]),            # the longest question last
