@@ -265,6 +265,10 @@ matkv_status matkv_assemble(matkv_ctx* ctx, const matkv_page* pages_host,
 int32_t matkv_plan_decode_units(const matkv_config* cfg, const int32_t* page_tokens_host,
                                 int32_t n_pages, int32_t batch, int32_t q_len,
                                 int32_t* unit_tokens_out, int32_t* unit_items_out, int32_t cap);
+/* Host-only preview: whether decode launches over a batch whose distinct pages hold page_tokens tokens together, in `format`, and whose
+ * tails start with tail_rows rows read the cache past the last-level cache (1) or through it (0); -1 on a bad argument.  A matter
+ * of speed: results are the same bit for bit. */
+int32_t matkv_plan_decode_streams(const matkv_config* cfg, int64_t page_tokens, int32_t tail_rows, int32_t format);
 /* Host-only preview: the kernel that projects n_rows token rows (of a chunk, of a batch's questions or of its new
  * tokens).  0: a row per workgroup, 1: matrix-vector products, 2: matrix cores for up to 16 rows, 3: matrix cores, the
  * hidden axis split within a workgroup, 4: tiled matrix product; -1 on a bad argument. */

@@ -29,7 +29,7 @@ EXPORTS = [
     "matkv_prefill_attn", "matkv_decode_attn", "matkv_decode_step", "matkv_graph_begin", "matkv_graph_end",
     "matkv_graph_launch", "matkv_graph_destroy", "matkv_graph_kernel_launches", "matkv_plan_decode_units", "matkv_probe_read",
     "matkv_table_shared_units", "matkv_plan_projection", "matkv_plan_prefill",
-    "matkv_plan_shared_units", "matkv_decode_attn_static",
+    "matkv_plan_shared_units", "matkv_plan_decode_streams", "matkv_decode_attn_static",
 ]
 
 
@@ -107,6 +107,7 @@ def _load_library():
     lib.matkv_plan_decode_units.argtypes = [cfgp, POINTER(c_int32), c_int32, c_int32, c_int32,
                                             POINTER(c_int32), POINTER(c_int32), c_int32]
     lib.matkv_plan_decode_units.restype = c_int32
+    lib.matkv_plan_decode_streams.argtypes = [cfgp, c_int64, c_int32, c_int32]; lib.matkv_plan_decode_streams.restype = c_int32
     lib.matkv_plan_projection.argtypes = [cfgp, c_int32]; lib.matkv_plan_projection.restype = c_int32
     lib.matkv_plan_prefill.argtypes = [cfgp] + [POINTER(c_int32)] * 3 + [c_int32, c_int32, POINTER(c_int32)]
     lib.matkv_plan_prefill.restype = c_int32
@@ -186,6 +187,14 @@ def plan_shared_units(cfg: Config, pages, q_lens):
                   users=[(out[u * w + 4 + 3 * k], out[u * w + 5 + 3 * k], out[u * w + 6 + 3 * k]) for k in range(out[u * w + 3])])
              for u in range(n)]
     return units, ([(slots[2 * b], slots[2 * b + 1]) for b in range(batch)] if n else None)
+
+
+def plan_decode_streams(cfg: Config, page_tokens: int, tail_rows: int, format: int = PAGE_PLAIN) -> bool:
+    """Whether decode launches read the cache past the last-level cache (page_tokens: of the batch's distinct pages)."""
+    r = int(_lib.matkv_plan_decode_streams(byref(cfg), page_tokens, tail_rows, format))
+    if r < 0:
+        raise MatKVError(EINVAL, "matkv_plan_decode_streams")
+    return bool(r)
 
 
 def plan_projection(cfg: Config, n_rows: int) -> int:

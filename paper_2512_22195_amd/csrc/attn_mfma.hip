@@ -332,7 +332,7 @@ __device__ __forceinline__ void merge_shared(const KernelArgs& a, const int4* us
 // tile are (user, query head) pairs, the piece is streamed once for all of them, every user gets
 // its own partial, and the workgroup arrives at every user's counter: the last arrival at an
 // instance's counter folds that instance's partial slots.
-// NT: the cache's rows are not left in the last-level cache (launch_g tells when).
+// NT: the cache's rows are not left in the last-level cache.
 template <int G, int NW, int MS, int PF, int FR, bool F8, bool SH = false, bool NT = false>
 __global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && PF <= 2)) ? 2 : 1) void attn_mfma_kernel(
         const Unit* __restrict__ units, const InstanceInfo* __restrict__ insts, const Item* __restrict__ items, int n_units,
@@ -750,12 +750,8 @@ hipError_t launch_step_g(const AttnArgs& a, const MaterializeArgs& m, hipStream_
     return hipErrorInvalidValue;
 }
 
-// A step that reads more than the last-level cache holds (256 MB) finds nothing of the cache there in the next one, and leaving its
-// rows there costs a launch 5 to 10 %: then they pass it by (past_llc: distinct pages, tails and projection
-// weights of all layers).  Below that they are left there and found again.  us per pass of 8 steps, left there -> passing by,
-// by what a step reads: 8B shape, eight layers, one user 167 MB 594 -> 642, 233 MB 696 -> 712, 265 MB 757 -> 754, 298 MB 824 -> 792, 396 MB
-// 968 -> 907; four layers, four users 224 MB 539 -> 560, 277 MB 621 -> 622, 382 MB 814 -> 739; compressed 164 + 134 MB 869 -> 835.
-// Large caches: decode of sixteen 8B users over 5000 tokens 1925 -> 1762, of four 70B users over 20 000 2250 -> 2073, of
+// past_llc: the cache's rows are not left in the last-level cache (rows_pass_llc, where the table is assembled, says when).  us per pass of
+// 8 steps, left there -> not: decode of sixteen 8B users over 5000 tokens 1925 -> 1762, of four 70B users over 20 000 2250 -> 2073, of
 // one 8B user over 10 000 1052 -> 990.  The weights stay on the ordinary path: what is left of the cache then holds them.
 template <int G>
 hipError_t launch_g(const AttnArgs& a, hipStream_t s) {

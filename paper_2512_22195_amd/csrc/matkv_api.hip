@@ -69,7 +69,7 @@ struct TableHost {
     int max_tail_len = 0;     // largest tail_len of any instance (host mirror)
     int min_tail_len = 0;
     int n_decode_slots = 0;   // partial slots a decode launch writes (units, or (unit, user) pairs when shared)
-    bool past_llc = false;    // a decode step over all layers reads more than the last-level cache holds
+    bool past_llc = false;    // decode launches leave the cache's rows out of the last-level cache (rows_pass_llc)
     std::vector<const void*> slots;   // distinct slots its pages point into
 };
 
@@ -821,6 +821,28 @@ bool even_partition(const matkv_config& cfg, int batch, int n_dunits) {
     return cfg.decode_units == 0 && cfg.decode_variant == 0 && cfg.dtype == MATKV_BF16 && cfg.head_dim == 128 && group_size_built(g) &&
            batch >= 2 && (batch > 4 || g > 4) && batch <= n_units &&
            sizeof(Unit) * n_dunits + sizeof(SUnit) * n_units <= sizeof(Unit) * (size_t)table_layout(cfg).max_dunits;
+}
+
+// Whether decode launches leave the cache's rows (distinct pages and tails) out of the last-level cache.  A step reads the rows and the
+// projection's weights of all layers, and the next step reads them again.
+//  - All of it fits: it is found there again, rows are left there.  Past that by a sixteenth, weights fit: rows pass by and the weights stay.
+//    us per layer step, rows left there / passing by: 8B shape, 8 layers and 265 MB 11.0 / 11.3, 12 layers and 300 MB 10.3 / 10.0, 15 layers and
+//    313 MB 9.9 / 9.4; 70B, 7 layers and 264 MB 14.9 / 15.5, 292 MB 15.9 / 16.2, 349 MB 18.4 / 18.1; sixteen 8B users over 5000 tokens 70.0 / 63.0.
+//  - The weights alone exceed it, as they do in a whole model: nothing is found again either way.  Rows that pass by are asked for in loads that cost
+//    a short step up to 6 %, and rows that are left there hold up a long one.  8B, 32 layers, by the rows of a layer: 4 MB 10.1 / 10.7, 8 MB 10.8 / 11.2,
+//    16 MB 12.1 / 12.3 (four users 14.6 / 14.7), 33 MB 14.8 / 14.7 (eight users 24.0 / 23.4), 66 MB 21.0 / 20.3, 335 MB 70.0 / 65.5; 70B, 20 layers,
+//    16 MB 18.8 / 19.1, 33 MB 21.7 / 21.4, 66 MB 27.3 / 26.6; compressed, two users of 8B, 3B and 70B with 4 MB 12.0 / 12.2, 10.4 / 10.4, 16.7 / 16.8, three
+//    with 6 MB 12.7 / 12.6, 11.5 / 11.3, 17.1 / 17.1, four with 8 MB 13.5 / 13.5, 12.0 / 11.8, 17.8 / 17.8, one of 8B with 33 MB 16.0 / 15.7.  In between (17 layers,
+//    285 MB of weights) part of the weights is found: 8 MB 10.7 / 11.0, 16 MB 12.1 / 12.0 (four users 14.6 / 14.1), compressed 8 MB 10.9 / 10.5.  So the
+//    line is at 24 MB, or 7 MB of codes, where they exceed it by an eighth, and falls to nothing where they just fit.
+constexpr size_t kStreamedLayerBytes = (size_t)24 << 20, kStreamedCodeBytes = (size_t)7 << 20;
+bool rows_pass_llc(const matkv_config& cfg, size_t page_tokens, size_t tail_rows, int kv_fmt) {
+    const size_t row = 2 * (size_t)cfg.n_kv_heads * cfg.head_dim, esz = cfg.dtype == MATKV_BF16 ? 2 : 4, llc = kLastLevelCacheBytes;
+    const size_t layer = row * (page_tokens * (kv_fmt == MATKV_PAGE_E4M3 ? 1 : esz) + tail_rows * esz);
+    const size_t weights = row * cfg.hidden * esz * cfg.n_layers;
+    if (layer * cfg.n_layers + weights <= llc + llc / 16) return false;
+    const size_t over = weights > llc ? std::min(weights - llc, llc / 8) : 0;
+    return layer > (kv_fmt == MATKV_PAGE_E4M3 ? kStreamedCodeBytes : kStreamedLayerBytes) / (llc / 8 >> 10) * (over >> 10);
 }
 
 // Launch shapes and kernel choices are fixed when a call is recorded; they follow from these.
@@ -1587,10 +1609,7 @@ matkv_status matkv_assemble(matkv_ctx* c, const matkv_page* pages, const int32_t
         for (int p = 0; p < n_pages[b]; ++p)
             if (std::find(th.slots.begin(), th.slots.end(), pg[p].slot) == th.slots.end()) { th.slots.push_back(pg[p].slot); page_tokens += pg[p].n_tokens; }
     }
-    // What a step reads of a layer: the distinct pages, the tails, the projection's weights.  All layers of it are read again by
-    // the next step, from the last-level cache if they fit there.
-    const size_t rows = 2 * (size_t)cfg.n_kv_heads * cfg.head_dim, esz = cfg.dtype == MATKV_BF16 ? 2 : 4;
-    th.past_llc = rows * (page_tokens * (kv_fmt == MATKV_PAGE_E4M3 ? 1 : esz) + ((size_t)cu + cfg.hidden) * esz) * cfg.n_layers > kLastLevelCacheBytes;
+    th.past_llc = rows_pass_llc(cfg, page_tokens, (size_t)cu, kv_fmt);
     auto old = c->tables.find(table);
     if (old != c->tables.end() && !old->second.slots.empty()) {
         hipEvent_t& ev = c->release_ev[c->release_next];
@@ -1640,6 +1659,12 @@ int32_t matkv_plan_decode_units(const matkv_config* cfg, const int32_t* page_tok
     }
     return made < cap ? made : cap;
     MATKV_CATCH_INT
+}
+
+int32_t matkv_plan_decode_streams(const matkv_config* cfg, int64_t page_tokens, int32_t tail_rows, int32_t format) {
+    const char* why;
+    if (check_config(cfg, &why) != MATKV_OK || page_tokens < 0 || tail_rows < 0 || (format != MATKV_PAGE_PLAIN && format != MATKV_PAGE_E4M3)) return -1;
+    return rows_pass_llc(*cfg, (size_t)page_tokens, (size_t)tail_rows, format) ? 1 : 0;
 }
 
 int32_t matkv_plan_projection(const matkv_config* cfg, int32_t n_rows) {

@@ -114,6 +114,32 @@ def test_decode_partition_never_exceeds_the_compute_units(mk):
         assert sum(toks) == 10000
 
 
+def test_decode_streams_only_rows_that_displace_something(mk):
+    """Host logic: the cache's rows pass the last-level cache (256 MB) by where a step over all layers does not fit there and the weights do,
+    or where the rows of one layer are many; short contexts of a whole model, whose weights alone exceed it, take the ordinary loads."""
+    shapes = {"3b": (28, 24, 3072), "8b": (32, 32, 4096), "70b": (80, 64, 8192)}
+
+    def streams(model, tokens, batch=1, layers=None, fmt=mk.PAGE_PLAIN):
+        n, Hq, hidden = shapes[model]
+        cfg = mk.make_config(layers or n, Hq, 8, 128, hidden, "bf16", 500000.0, batch, 8, 64)
+        return mk.plan_decode_streams(cfg, batch * tokens, batch * 32, fmt)
+
+    for model in shapes:
+        for batch, tokens in ((1, 1), (1, 300), (3, 1000), (1, 4000), (16, 300)):
+            assert not streams(model, tokens, batch)
+        for batch, tokens in ((1, 1), (1, 3000), (3, 1000), (8, 100)):
+            assert not streams(model, tokens, batch, fmt=mk.PAGE_E4M3)
+        for batch, tokens in ((1, 8000), (8, 1000), (16, 5000)):
+            assert streams(model, tokens, batch) and streams(model, tokens // 2, batch, fmt=mk.PAGE_E4M3)
+    # slices of a model: all of it fits, the weights fit (16 layers of 8B: exactly), they nearly do
+    assert not streams("8b", 4000, layers=8) and streams("8b", 5000, layers=8) and streams("8b", 300, layers=16)
+    assert not streams("8b", 100, layers=16) and not streams("8b", 2000, layers=17) and streams("8b", 4000, layers=17)
+    cfg = mk.make_config(32, 32, 8, 128, 4096, "bf16", 500000.0, 1, 8, 64)
+    for bad in ((-1, 0), (0, -1), (0, 0, 7)):
+        with pytest.raises(mk.MatKVError):
+            mk.plan_decode_streams(cfg, *bad)
+
+
 def test_shared_partition_covers_every_instance_once(mk):
     """Host logic of the shared decode partition: built when the batch's distinct pages are at least
     a twentieth fewer tokens than all uses; every (instance, page token) is streamed by exactly one

@@ -596,7 +596,7 @@ def test_graph_replay_matches_eager():
 @pytest.mark.parametrize("Hq,batch,shared,compressed", [(8, 1, False, False), (24, 3, False, True), (32, 4, False, False), (32, 2, True, False),
                                                         (16, 5, True, True), (64, 2, False, False), (64, 3, False, True)])
 def test_decode_past_the_last_level_cache(Hq, batch, shared, compressed):
-    """A model whose steps read more than 256 MB (33 layers of 8B weights) takes the kernels that leave the cache's rows out of
+    """Sixteen layers of 8B weights (256 MB) and a short cache take the kernels that leave the cache's rows out of
     the last-level cache; one layer of it does not.  Both do the same sums in the same order, so every output and tail
     row is the same bit for bit, over ragged pages, one of a single token among them, fused and as two launches (64 heads, batch 5)."""
     from paper_2512_22195_amd import binding as mk
@@ -608,9 +608,10 @@ def test_decode_past_the_last_level_cache(Hq, batch, shared, compressed):
     rows = {(b, i): draw(2, Hkv, n, D) for b in range(batch) for i, n in enumerate(lens)}
     tails = draw(2, batch, Hkv, cap, D)
     results = []
-    for n_layers in (1, 33):
+    for n_layers in (1, 16):
         cfg = mk.make_config(n_layers, Hq, Hkv, D, hidden, "bf16", 500000.0, max_batch=batch, max_pages=len(lens), max_tail_tokens=cap)
-        assert (n_layers * 2 * Hkv * D * hidden * 2 > 256 << 20) == (n_layers > 1)
+        fmt, tokens = mk.PAGE_E4M3 if compressed else mk.PAGE_PLAIN, sum(lens) * (1 if shared else batch)
+        assert mk.plan_decode_streams(cfg, tokens, sum(q_len), fmt) == (n_layers > 1)
         ctx = mk.Context(cfg)
         try:
             with torch.cuda.stream(ctx.compute_stream):
@@ -623,7 +624,6 @@ def test_decode_past_the_last_level_cache(Hq, batch, shared, compressed):
                     if compressed:
                         slots[b, i] = torch.empty(mk.compressed_blob_bytes(cfg, lens[i]), dtype=torch.uint8, device="cuda")
                         ctx.compress(blob, lens[i], slots[b, i])
-                fmt = mk.PAGE_E4M3 if compressed else mk.PAGE_PLAIN
                 table = ctx.new_table()
                 ctx.assemble([[(slots[0 if shared else b, i], n, fmt) for i, n in enumerate(lens)] for b in range(batch)], q_len, table)
                 assert (ctx.table_shared_units(table) > 0) == shared
