@@ -265,10 +265,6 @@ matkv_status matkv_assemble(matkv_ctx* ctx, const matkv_page* pages_host,
 int32_t matkv_plan_decode_units(const matkv_config* cfg, const int32_t* page_tokens_host,
                                 int32_t n_pages, int32_t batch, int32_t q_len,
                                 int32_t* unit_tokens_out, int32_t* unit_items_out, int32_t cap);
-/* Host-only preview: whether decode launches over a batch whose distinct pages hold page_tokens tokens together, in `format`, and whose
- * tails start with tail_rows rows read the cache past the last-level cache (1) or through it (0); -1 on a bad argument.  A matter
- * of speed: results are the same bit for bit. */
-int32_t matkv_plan_decode_streams(const matkv_config* cfg, int64_t page_tokens, int32_t tail_rows, int32_t format);
 /* Host-only preview: the kernel that projects n_rows token rows (of a chunk, of a batch's questions or of its new
  * tokens).  0: a row per workgroup, 1: matrix-vector products, 2: matrix cores for up to 16 rows, 3: matrix cores, the
  * hidden axis split within a workgroup, 4: tiled matrix product; -1 on a bad argument. */
@@ -293,6 +289,11 @@ int32_t matkv_plan_shared_units(const matkv_config* cfg, const int32_t* page_ids
                                 const int32_t* page_tokens_host, const int32_t* n_pages_host,
                                 const int32_t* q_len_host, int32_t batch, int32_t* units_out,
                                 int32_t cap, int32_t* slots_out);
+/* Host-only preview: whether decode launches over the table that matkv_assemble would build for a batch (arguments as for
+ * matkv_plan_shared_units, its pages in `format`) read the cache past the last-level cache (1) or through it (0); -1 on a bad
+ * argument.  A matter of speed: results are the same bit for bit. */
+int32_t matkv_plan_decode_streams(const matkv_config* cfg, const int32_t* page_ids_host, const int32_t* page_tokens_host,
+                                  const int32_t* n_pages_host, const int32_t* q_len_host, int32_t batch, int32_t format);
 /* Decode work units of the table's shared partition, 0 if matkv_assemble built none, -1 if the
  * table is unknown.  When two or more instances of a batch point at the same slot (the same
  * chunk, retrieved by several requests), matkv_assemble cuts the batch's DISTINCT pages and its

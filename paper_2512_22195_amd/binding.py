@@ -107,7 +107,8 @@ def _load_library():
     lib.matkv_plan_decode_units.argtypes = [cfgp, POINTER(c_int32), c_int32, c_int32, c_int32,
                                             POINTER(c_int32), POINTER(c_int32), c_int32]
     lib.matkv_plan_decode_units.restype = c_int32
-    lib.matkv_plan_decode_streams.argtypes = [cfgp, c_int64, c_int32, c_int32]; lib.matkv_plan_decode_streams.restype = c_int32
+    lib.matkv_plan_decode_streams.argtypes = [cfgp] + [POINTER(c_int32)] * 4 + [c_int32, c_int32]
+    lib.matkv_plan_decode_streams.restype = c_int32
     lib.matkv_plan_projection.argtypes = [cfgp, c_int32]; lib.matkv_plan_projection.restype = c_int32
     lib.matkv_plan_prefill.argtypes = [cfgp] + [POINTER(c_int32)] * 3 + [c_int32, c_int32, POINTER(c_int32)]
     lib.matkv_plan_prefill.restype = c_int32
@@ -189,9 +190,16 @@ def plan_shared_units(cfg: Config, pages, q_lens):
     return units, ([(slots[2 * b], slots[2 * b + 1]) for b in range(batch)] if n else None)
 
 
-def plan_decode_streams(cfg: Config, page_tokens: int, tail_rows: int, format: int = PAGE_PLAIN) -> bool:
-    """Whether decode launches read the cache past the last-level cache (page_tokens: of the batch's distinct pages)."""
-    r = int(_lib.matkv_plan_decode_streams(byref(cfg), page_tokens, tail_rows, format))
+def plan_decode_streams(cfg: Config, pages, q_lens, format: int = PAGE_PLAIN) -> bool:
+    """Whether decode launches over the batch's table read the cache past the last-level cache.  pages: per instance a list of
+    (page id, tokens)."""
+    batch, mp = len(pages), max(cfg.max_pages, 1)
+    ids, toks = (c_int32 * (batch * mp))(), (c_int32 * (batch * mp))()
+    for b, plist in enumerate(pages):
+        for i, (pid, n) in enumerate(plist[:mp]):
+            ids[b * mp + i], toks[b * mp + i] = pid, n
+    npg, ql = (c_int32 * batch)(*[len(p) for p in pages]), (c_int32 * batch)(*q_lens)
+    r = int(_lib.matkv_plan_decode_streams(byref(cfg), ids, toks, npg, ql, batch, format))
     if r < 0:
         raise MatKVError(EINVAL, "matkv_plan_decode_streams")
     return bool(r)

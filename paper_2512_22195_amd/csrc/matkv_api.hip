@@ -808,11 +808,6 @@ int build_shared_units(const matkv_config& cfg, const matkv_page* pages, const i
     return n;
 }
 
-TableHost* find_table(matkv_ctx* c, const void* t) {
-    auto it = c->tables.find(t);
-    return it == c->tables.end() ? nullptr : &it->second;
-}
-
 // Whether a batch without shared pages gets the even partition (build_even_units) beside the one by instance: one whose step is not
 // the fused launch.  A step that was recorded over it replays over every table with the same batch and units by instance, and this says the
 // same of all of them.  Its units follow the others in their section (and are copied with them).
@@ -823,26 +818,81 @@ bool even_partition(const matkv_config& cfg, int batch, int n_dunits) {
            sizeof(Unit) * n_dunits + sizeof(SUnit) * n_units <= sizeof(Unit) * (size_t)table_layout(cfg).max_dunits;
 }
 
-// Whether decode launches leave the cache's rows (distinct pages and tails) out of the last-level cache.  A step reads the rows and the
-// projection's weights of all layers, and the next step reads them again.
+// Whether decode launches leave the cache's rows out of the last-level cache.  page_tokens, tail_rows: what they stream of a layer; longest: tokens
+// of the longest workgroup's walk.  A step reads the rows and the projection's weights of all layers, and the next step reads them again.
 //  - All of it fits: it is found there again, rows are left there.  Past that by a sixteenth, weights fit: rows pass by and the weights stay.
 //    us per layer step, rows left there / passing by: 8B shape, 8 layers and 265 MB 11.0 / 11.3, 12 layers and 300 MB 10.3 / 10.0, 15 layers and
 //    313 MB 9.9 / 9.4; 70B, 7 layers and 264 MB 14.9 / 15.5, 292 MB 15.9 / 16.2, 349 MB 18.4 / 18.1; sixteen 8B users over 5000 tokens 70.0 / 63.0.
-//  - The weights alone exceed it, as they do in a whole model: nothing is found again either way.  Rows that pass by are asked for in loads that cost
-//    a short step up to 6 %, and rows that are left there hold up a long one.  8B, 32 layers, by the rows of a layer: 4 MB 10.1 / 10.7, 8 MB 10.8 / 11.2,
-//    16 MB 12.1 / 12.3 (four users 14.6 / 14.7), 33 MB 14.8 / 14.7 (eight users 24.0 / 23.4), 66 MB 21.0 / 20.3, 335 MB 70.0 / 65.5; 70B, 20 layers,
-//    16 MB 18.8 / 19.1, 33 MB 21.7 / 21.4, 66 MB 27.3 / 26.6; compressed, two users of 8B, 3B and 70B with 4 MB 12.0 / 12.2, 10.4 / 10.4, 16.7 / 16.8, three
-//    with 6 MB 12.7 / 12.6, 11.5 / 11.3, 17.1 / 17.1, four with 8 MB 13.5 / 13.5, 12.0 / 11.8, 17.8 / 17.8, one of 8B with 33 MB 16.0 / 15.7.  In between (17 layers,
-//    285 MB of weights) part of the weights is found: 8 MB 10.7 / 11.0, 16 MB 12.1 / 12.0 (four users 14.6 / 14.1), compressed 8 MB 10.9 / 10.5.  So the
-//    line is at 24 MB, or 7 MB of codes, where they exceed it by an eighth, and falls to nothing where they just fit.
+//  - The weights alone exceed it, as they do in a whole model: nothing is found again either way, and short steps are better off with the ordinary
+//    loads.  8B, 32 layers, by the rows of a layer: 4 MB 10.1 / 10.7, 8 MB 10.8 / 11.2, 16 MB 12.1 / 12.3 (four users 14.6 / 14.7), 33 MB 14.8 / 14.7
+//    (eight users 24.0 / 23.4), 66 MB 21.0 / 20.3, 335 MB 70.0 / 65.5; 70B, 20 layers, 16 MB 18.8 / 19.1, 33 MB 21.7 / 21.4, 66 MB 27.3 / 26.6; compressed, two
+//    users of 8B, 3B and 70B with 4 MB 12.0 / 12.2, 10.4 / 10.4, 16.7 / 16.8, three with 6 MB 12.7 / 12.6, 11.5 / 11.3, 17.1 / 17.1, four with 8 MB 13.5 / 13.5,
+//    12.0 / 11.8, 17.8 / 17.8, one of 8B with 33 MB 16.0 / 15.7.  So a layer's rows have to be 24 MB, or 7 MB of codes.  In between (17 layers, 285 MB
+//    of weights) part of the weights is found: 8 MB 10.7 / 11.0, 16 MB 12.1 / 12.0, compressed 8 MB 10.9 / 10.5: the line falls to nothing where they just fit.
+//  - A load that passes by takes longer, and a workgroup has two blocks on their way: it gains only with most of the chip walking to the end.
+//    Time saved by passing by, mean over seeded steps of 1 to 31 users (3B, 8B, 70B; 4 to 28 layers, plain pages), by the workgroups that would
+//    take as long if all walks were as long as the longest: weights fit, up to 64 -5 %, 64 to 128 -3.5 %, 128 to 160 -1 %, 160 to 192 +1 %, 192 to 224 +4 %, more
+//    +7 %; they exceed it, up to 128 -5 %, 128 to 192 -3 %, 192 to 208 -1 %, 208 to 224 0, more +2 %.  Compressed pages alike.  So 160 and 208 of them.
+//    Attention over 2000 tokens each, one unit per user, 16 layers: one user 22.3 / 30.9, eight 28.4 / 33.5, 17 32.3 / 36.3, 24 38.0 / 38.8.
+// Over 8196 such steps (plain and compressed) the better of the two is taken but for 0.2 % of the time; where all beyond 256 MB passed by it was 1.6 %.
 constexpr size_t kStreamedLayerBytes = (size_t)24 << 20, kStreamedCodeBytes = (size_t)7 << 20;
-bool rows_pass_llc(const matkv_config& cfg, size_t page_tokens, size_t tail_rows, int kv_fmt) {
+constexpr int kStreamedWalks = 160, kStreamedWalksFar = 208;
+bool rows_pass_llc(const matkv_config& cfg, size_t page_tokens, size_t tail_rows, size_t longest, int kv_fmt) {
     const size_t row = 2 * (size_t)cfg.n_kv_heads * cfg.head_dim, esz = cfg.dtype == MATKV_BF16 ? 2 : 4, llc = kLastLevelCacheBytes;
     const size_t layer = row * (page_tokens * (kv_fmt == MATKV_PAGE_E4M3 ? 1 : esz) + tail_rows * esz);
     const size_t weights = row * cfg.hidden * esz * cfg.n_layers;
     if (layer * cfg.n_layers + weights <= llc + llc / 16) return false;
-    const size_t over = weights > llc ? std::min(weights - llc, llc / 8) : 0;
-    return layer > (kv_fmt == MATKV_PAGE_E4M3 ? kStreamedCodeBytes : kStreamedLayerBytes) / (llc / 8 >> 10) * (over >> 10);
+    const double over = weights > llc ? std::min(1.0, (double)(weights - llc) / (double)(llc / 8)) : 0.0;      // 1: nothing of the weights is found again
+    const double walks = (double)cfg.n_kv_heads * (double)(page_tokens + tail_rows) / (double)std::max<size_t>(longest, 1);
+    return (double)layer > over * (double)(kv_fmt == MATKV_PAGE_E4M3 ? kStreamedCodeBytes : kStreamedLayerBytes) &&
+           walks >= kStreamedWalks + over * (kStreamedWalksFar - kStreamedWalks);
+}
+
+// Decode attention of a batch (insts: q_len is set): the units of every instance, and beside them the shared partition or
+// the even one where they apply.  sunits: the table's section of the shared partition; the even one's records follow dunits.
+struct DecodeLayout {
+    int n_dunits = 0, n_sunits = 0;
+    bool even_built = false, even = false, past_llc = false;
+};
+template <typename ScalesOff>
+DecodeLayout lay_out_decode(const matkv_config& cfg, const TableLayout& tl, const matkv_page* pages, const int32_t* n_pages, int batch, int kv_fmt,
+                            InstanceInfo* insts, Item* items, int* n_items, Unit* dunits, SUnit* sunits, ScalesOff scales_off) {
+    DecodeLayout L;
+    for (int b = 0; b < batch; ++b) {
+        const matkv_page* pg = pages ? pages + (size_t)b * cfg.max_pages : nullptr;
+        long inst_tokens = 0;
+        for (int p = 0; p < n_pages[b]; ++p) inst_tokens += pg[p].n_tokens;
+        const int tail_est = insts[b].q_len + (cfg.max_tail_tokens - insts[b].q_len) / 2;
+        // fine partition, one workgroup per (unit, KV head)
+        insts[b].dunit0 = L.n_dunits;
+        insts[b].n_dunits = build_units(pg, n_pages[b], b, choose_decode_units(cfg, batch, inst_tokens + tail_est),
+                                        tail_est, cfg.max_tail_tokens, items, n_items, dunits, &L.n_dunits, scales_off);
+    }
+    // over shared pages: only where the default matrix-core decode kernel runs
+    if (batch >= 2 && pages && cfg.decode_units == 0 && cfg.decode_variant == 0 &&
+        cfg.dtype == MATKV_BF16 && cfg.head_dim == 128 && group_size_built(cfg.n_q_heads / cfg.n_kv_heads))
+        L.n_sunits = build_shared_units(cfg, pages, n_pages, batch, tl.max_sunits, tl.max_items, insts, items, n_items, sunits, kv_fmt);
+    SUnit* const runs = reinterpret_cast<SUnit*>(dunits + L.n_dunits);
+    if (L.n_sunits == 0 && even_partition(cfg, batch, L.n_dunits)) {
+        L.even_built = true;
+        L.even = build_even_units(cfg, pages, n_pages, batch, insts, items, n_items, L.n_dunits, runs, kv_fmt);
+    }
+    size_t page_tokens = 0, tail_rows = 0, longest = 0;
+    auto walk = [&](const Unit& u) {
+        const size_t tail = u.has_tail ? insts[u.inst].q_len : 0;
+        page_tokens += u.page_tokens; tail_rows += tail;
+        longest = std::max(longest, u.page_tokens + tail);
+    };
+    if (L.even)              for (int u = 0; u < 256 / cfg.n_kv_heads && runs[u].n_users > 0; ++u) walk(runs[u].u);
+    else if (L.n_sunits > 0) for (int u = 0; u < L.n_sunits; ++u) walk(sunits[u].u);
+    else                     for (int u = 0; u < L.n_dunits; ++u) walk(dunits[u]);
+    L.past_llc = rows_pass_llc(cfg, page_tokens, tail_rows, longest, kv_fmt);
+    return L;
+}
+
+TableHost* find_table(matkv_ctx* c, const void* t) {
+    auto it = c->tables.find(t);
+    return it == c->tables.end() ? nullptr : &it->second;
 }
 
 // Launch shapes and kernel choices are fixed when a call is recorded; they follow from these.
@@ -1539,7 +1589,7 @@ matkv_status matkv_assemble(matkv_ctx* c, const matkv_page* pages, const int32_t
     Unit* dunits = reinterpret_cast<Unit*>(h + c->tl.off_dunits);
     Unit* punits = reinterpret_cast<Unit*>(h + c->tl.off_punits);
     memset(hdr, 0, sizeof(*hdr));
-    int n_items = 0, n_dunits = 0, cu = 0, max_q = 0;
+    int n_items = 0, cu = 0, max_q = 0;
     TableHost th;
     th.min_tail_len = cfg.max_tail_tokens;
     for (int b = 0; b < batch; ++b) {
@@ -1559,26 +1609,14 @@ matkv_status matkv_assemble(matkv_ctx* c, const matkv_page* pages, const int32_t
         if (q_len[b] > max_q) max_q = q_len[b];
         if (q_len[b] > th.max_tail_len) th.max_tail_len = q_len[b];
         if (q_len[b] < th.min_tail_len) th.min_tail_len = q_len[b];
-        const int tail_est = q_len[b] + (cfg.max_tail_tokens - q_len[b]) / 2;
-        // decode: fine partition, one workgroup per (unit, KV head)
-        in.dunit0 = n_dunits;
-        in.n_dunits = build_units(pg, n_pages[b], b, choose_decode_units(cfg, batch, inst_tokens + tail_est),
-                                  tail_est, cfg.max_tail_tokens, items, &n_items, dunits, &n_dunits, scales_off);
     }
+    const DecodeLayout decode = lay_out_decode(cfg, c->tl, pages, n_pages, batch, kv_fmt, insts, items, &n_items, dunits,
+                                               reinterpret_cast<SUnit*>(h + c->tl.off_sunits), scales_off);
+    const int n_dunits = decode.n_dunits, n_sunits = decode.n_sunits;
+    th.even = decode.even; th.past_llc = decode.past_llc;
     // prefill: coarse partition (the question rows supply most of the parallelism)
     th.prefill = lay_out_prefill(cfg, pages, n_pages, q_len, batch, kv_fmt == MATKV_PAGE_E4M3, insts, items, &n_items, punits, scales_off);
-    // decode over shared pages: only where the default matrix-core decode kernel runs
-    const int grp = cfg.n_q_heads / cfg.n_kv_heads;
-    int n_sunits = 0;
-    if (batch >= 2 && pages && cfg.decode_units == 0 && cfg.decode_variant == 0 &&
-        cfg.dtype == MATKV_BF16 && cfg.head_dim == 128 && group_size_built(grp))
-        n_sunits = build_shared_units(cfg, pages, n_pages, batch, c->tl.max_sunits, c->tl.max_items, insts, items, &n_items,
-                                      reinterpret_cast<SUnit*>(h + c->tl.off_sunits), kv_fmt);
-    size_t dunit_bytes = sizeof(Unit) * n_dunits;
-    if (n_sunits == 0 && even_partition(cfg, batch, n_dunits)) {
-        th.even = build_even_units(cfg, pages, n_pages, batch, insts, items, &n_items, n_dunits, reinterpret_cast<SUnit*>(dunits + n_dunits), kv_fmt);
-        dunit_bytes += sizeof(SUnit) * (256 / cfg.n_kv_heads);
-    }
+    const size_t dunit_bytes = sizeof(Unit) * n_dunits + (decode.even_built ? sizeof(SUnit) * (256 / cfg.n_kv_heads) : 0);
     hdr->batch = batch; hdr->n_items = n_items; hdr->n_dunits = n_dunits; hdr->n_punits = th.prefill.n_units;
     hdr->total_q = cu; hdr->max_q = max_q;
 
@@ -1603,13 +1641,11 @@ matkv_status matkv_assemble(matkv_ctx* c, const matkv_page* pages, const int32_t
     sign_partition(th);
     // Slot bookkeeping: the table's old contents are dead from here on in stream order, so the
     // slots only they pointed into may be overwritten once the work enqueued so far is done.
-    size_t page_tokens = 0;
     for (int b = 0; b < batch; ++b) {
         const matkv_page* pg = pages ? pages + (size_t)b * cfg.max_pages : nullptr;
         for (int p = 0; p < n_pages[b]; ++p)
-            if (std::find(th.slots.begin(), th.slots.end(), pg[p].slot) == th.slots.end()) { th.slots.push_back(pg[p].slot); page_tokens += pg[p].n_tokens; }
+            if (std::find(th.slots.begin(), th.slots.end(), pg[p].slot) == th.slots.end()) th.slots.push_back(pg[p].slot);
     }
-    th.past_llc = rows_pass_llc(cfg, page_tokens, (size_t)cu, kv_fmt);
     auto old = c->tables.find(table);
     if (old != c->tables.end() && !old->second.slots.empty()) {
         hipEvent_t& ev = c->release_ev[c->release_next];
@@ -1659,12 +1695,6 @@ int32_t matkv_plan_decode_units(const matkv_config* cfg, const int32_t* page_tok
     }
     return made < cap ? made : cap;
     MATKV_CATCH_INT
-}
-
-int32_t matkv_plan_decode_streams(const matkv_config* cfg, int64_t page_tokens, int32_t tail_rows, int32_t format) {
-    const char* why;
-    if (check_config(cfg, &why) != MATKV_OK || page_tokens < 0 || tail_rows < 0 || (format != MATKV_PAGE_PLAIN && format != MATKV_PAGE_E4M3)) return -1;
-    return rows_pass_llc(*cfg, (size_t)page_tokens, (size_t)tail_rows, format) ? 1 : 0;
 }
 
 int32_t matkv_plan_projection(const matkv_config* cfg, int32_t n_rows) {
@@ -1756,6 +1786,38 @@ int32_t matkv_plan_shared_units(const matkv_config* cfg, const int32_t* page_ids
     if (slots_out && n > 0)
         for (int b = 0; b < batch; ++b) { slots_out[2 * b] = insts[b].sslot0; slots_out[2 * b + 1] = insts[b].n_sslots; }
     return n < cap ? n : cap;
+    MATKV_CATCH_INT
+}
+
+int32_t matkv_plan_decode_streams(const matkv_config* cfg, const int32_t* page_ids, const int32_t* page_tokens, const int32_t* n_pages,
+                                  const int32_t* q_len, int32_t batch, int32_t format) {
+    const char* why;
+    if (check_config(cfg, &why) != MATKV_OK) return -1;
+    if (!n_pages || !q_len || batch < 1 || batch > cfg->max_batch || (format != MATKV_PAGE_PLAIN && format != MATKV_PAGE_E4M3)) return -1;
+    if (format == MATKV_PAGE_E4M3 && !(cfg->dtype == MATKV_BF16 && cfg->head_dim == 128)) return -1;
+    MATKV_TRY
+    std::vector<matkv_page> pages((size_t)batch * std::max(cfg->max_pages, 1));
+    std::vector<InstanceInfo> insts((size_t)batch);
+    for (int b = 0; b < batch; ++b) {
+        if (n_pages[b] < 0 || n_pages[b] > cfg->max_pages || q_len[b] < 1 || q_len[b] > cfg->max_tail_tokens) return -1;
+        if (n_pages[b] > 0 && (!page_ids || !page_tokens)) return -1;
+        memset(&insts[b], 0, sizeof(InstanceInfo));
+        insts[b].q_len = q_len[b];
+        for (int p = 0; p < n_pages[b]; ++p) {
+            const size_t i = (size_t)b * cfg->max_pages + p;
+            if (page_ids[i] < 0 || page_tokens[i] < 1) return -1;
+            pages[i].slot = reinterpret_cast<const void*>(((uintptr_t)page_ids[i] + 1) * 4096);   // never dereferenced
+            pages[i].n_tokens = page_tokens[i];
+            pages[i].format = format;
+        }
+    }
+    const TableLayout tl = table_layout(*cfg);
+    std::vector<Item> items((size_t)tl.max_items);
+    std::vector<Unit> units((size_t)tl.max_dunits);
+    std::vector<SUnit> sunits((size_t)tl.max_sunits);
+    int n_items = 0;
+    return lay_out_decode(*cfg, tl, pages.data(), n_pages, batch, format, insts.data(), items.data(), &n_items, units.data(), sunits.data(),
+                          [](int) { return (size_t)0; }).past_llc;
     MATKV_CATCH_INT
 }
 

@@ -116,26 +116,36 @@ def test_decode_partition_never_exceeds_the_compute_units(mk):
 
 def test_decode_streams_only_rows_that_displace_something(mk):
     """Host logic: the cache's rows pass the last-level cache (256 MB) by where a step over all layers does not fit there and the weights do,
-    or where the rows of one layer are many; short contexts of a whole model, whose weights alone exceed it, take the ordinary loads."""
+    or where the rows of one layer are many, and only while most of the chip walks to the end; short contexts of a whole model,
+    whose weights alone exceed it, and launches of few workgroups or with one long walk take the ordinary loads."""
     shapes = {"3b": (28, 24, 3072), "8b": (32, 32, 4096), "70b": (80, 64, 8192)}
 
-    def streams(model, tokens, batch=1, layers=None, fmt=mk.PAGE_PLAIN):
+    def streams(model, tokens, batch=1, layers=None, fmt=mk.PAGE_PLAIN, question=32, units=0):
         n, Hq, hidden = shapes[model]
-        cfg = mk.make_config(layers or n, Hq, 8, 128, hidden, "bf16", 500000.0, batch, 8, 64)
-        return mk.plan_decode_streams(cfg, batch * tokens, batch * 32, fmt)
+        cfg = mk.make_config(layers or n, Hq, 8, 128, hidden, "bf16", 500000.0, batch, 8, (question + 39) // 8 * 8, decode_units=units)
+        return mk.plan_decode_streams(cfg, [[(b, tokens)] for b in range(batch)], [question] * batch, fmt)
 
     for model in shapes:
         for batch, tokens in ((1, 1), (1, 300), (3, 1000), (1, 4000), (16, 300)):
             assert not streams(model, tokens, batch)
         for batch, tokens in ((1, 1), (1, 3000), (3, 1000), (8, 100)):
             assert not streams(model, tokens, batch, fmt=mk.PAGE_E4M3)
-        for batch, tokens in ((1, 8000), (8, 1000), (16, 5000)):
+        for batch, tokens in ((1, 8000), (8, 1500), (16, 5000), (17, 4000)):
             assert streams(model, tokens, batch) and streams(model, tokens // 2, batch, fmt=mk.PAGE_E4M3)
+        # 136, 160, 192 and 232 workgroups
+        assert not streams(model, 4000, 17, units=1) and not streams(model, 4000, 20, units=1) and not streams(model, 4000, 24, units=1)
+        assert streams(model, 4000, 29, units=1) and not streams(model, 4000, 17, layers=4, units=1)
+        assert streams(model, 4000, 20, layers=4, units=1) and streams(model, 4000, 24, layers=4, units=1)
+        # one workgroup of each user walks the whole question
+        assert streams(model, 4000, 8, layers=4) and not streams(model, 500, 8, question=2000) and not streams(model, 2000, 8, layers=4, question=2000)
     # slices of a model: all of it fits, the weights fit (16 layers of 8B: exactly), they nearly do
-    assert not streams("8b", 4000, layers=8) and streams("8b", 5000, layers=8) and streams("8b", 300, layers=16)
+    assert not streams("8b", 4000, layers=8) and streams("8b", 5000, layers=8) and streams("8b", 3500, layers=16)
     assert not streams("8b", 100, layers=16) and not streams("8b", 2000, layers=17) and streams("8b", 4000, layers=17)
-    cfg = mk.make_config(32, 32, 8, 128, 4096, "bf16", 500000.0, 1, 8, 64)
-    for bad in ((-1, 0), (0, -1), (0, 0, 7)):
+    # a batch that shares its pages streams them once
+    cfg = mk.make_config(4, 32, 8, 128, 4096, "bf16", 500000.0, 4, 8, 64)
+    assert mk.plan_decode_streams(cfg, [[(b, 5000)] for b in range(4)], [32] * 4)
+    assert not mk.plan_decode_streams(cfg, [[(0, 5000)]] * 4, [32] * 4)
+    for bad in (([[(0, 0)]], [4]), ([[(-1, 5)]], [4]), ([[(0, 5)]], [0]), ([[(0, 5)]], [65]), ([[(0, 5)]], [4], 7)):
         with pytest.raises(mk.MatKVError):
             mk.plan_decode_streams(cfg, *bad)
 

@@ -596,12 +596,12 @@ def test_graph_replay_matches_eager():
 @pytest.mark.parametrize("Hq,batch,shared,compressed", [(8, 1, False, False), (24, 3, False, True), (32, 4, False, False), (32, 2, True, False),
                                                         (16, 5, True, True), (64, 2, False, False), (64, 3, False, True)])
 def test_decode_past_the_last_level_cache(Hq, batch, shared, compressed):
-    """Sixteen layers of 8B weights (256 MB) and a short cache take the kernels that leave the cache's rows out of
+    """Sixteen layers of 8B weights (256 MB) and caches of 25 workgroups take the kernels that leave the cache's rows out of
     the last-level cache; one layer of it does not.  Both do the same sums in the same order, so every output and tail
     row is the same bit for bit, over ragged pages, one of a single token among them, fused and as two launches (64 heads, batch 5)."""
     from paper_2512_22195_amd import binding as mk
     Hkv, D, hidden, cap = 8, 128, 4096, 40
-    lens, q_len = [333, 1, 64, 97], [31 - b for b in range(batch)]
+    lens, q_len = [2333, 1, 764, 197], [31 - b for b in range(batch)]
     g = torch.Generator(device="cuda").manual_seed(5 + Hq)
     draw = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
     w, q, x = draw(2, Hkv * D, hidden) * hidden ** -0.5, draw(batch, Hq, D), draw(batch, hidden)
@@ -610,8 +610,8 @@ def test_decode_past_the_last_level_cache(Hq, batch, shared, compressed):
     results = []
     for n_layers in (1, 16):
         cfg = mk.make_config(n_layers, Hq, Hkv, D, hidden, "bf16", 500000.0, max_batch=batch, max_pages=len(lens), max_tail_tokens=cap)
-        fmt, tokens = mk.PAGE_E4M3 if compressed else mk.PAGE_PLAIN, sum(lens) * (1 if shared else batch)
-        assert mk.plan_decode_streams(cfg, tokens, sum(q_len), fmt) == (n_layers > 1)
+        fmt, ids = mk.PAGE_E4M3 if compressed else mk.PAGE_PLAIN, [[(len(lens) * (0 if shared else b) + i, n) for i, n in enumerate(lens)] for b in range(batch)]
+        assert mk.plan_decode_streams(cfg, ids, q_len, fmt) == (n_layers > 1)
         ctx = mk.Context(cfg)
         try:
             with torch.cuda.stream(ctx.compute_stream):
