@@ -656,11 +656,16 @@ __global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && 
                 __hip_atomic_store(&a.counters[counter_index(a, us.x, kvh, 0)], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const uint64_t who = __builtin_amdgcn_ballot_w64(last);       // (n_users <= 16: all in the first wave)
             if (last) sm_lastv[__popcll(who & ((1ull << tid) - 1))] = tid;
-            if (tid == 0) sm_last = __popcll(who);
+            const bool many = __builtin_amdgcn_ballot_w64(last && us.w > 8) != 0;
+            if (tid == 0) sm_last = 2 * __popcll(who) + many;
         }
         __syncthreads();
-        const int n_live = __builtin_amdgcn_readfirstlane(sm_last);
+        // Which instances a workgroup is the last of is a matter of timing, the order of an instance's sums is not: 16 partials a pass where
+        // one of them has more than 8 (up to 8, passes of 8 and of 16 do the same sums).
+        const int n_live = __builtin_amdgcn_readfirstlane(sm_last) >> 1;
+        const bool many = __builtin_amdgcn_readfirstlane(sm_last) & 1;
         if (n_live * G <= NW) merge_shared<G, NW, 1, 16>(a, sm_users, sm_lastv, n_live, kvh, wave, lane);
+        else if (many)        merge_shared<G, NW, 2, 16>(a, sm_users, sm_lastv, n_live, kvh, wave, lane);
         else                  merge_shared<G, NW, 4, 8>(a, sm_users, sm_lastv, n_live, kvh, wave, lane);
     } else if constexpr (FR == 0) {
         if constexpr (MS > 1) {                         // (prefill tiles)

@@ -698,6 +698,30 @@ def _same_attention(a, b):
     assert torch.isfinite(a).all() and ((a - b).abs() <= 2e-2 * rms).all(), ((a - b).abs() / rms).max()
 
 
+@pytest.mark.parametrize("Hq,batch,tokens", [(16, 5, 3000), (32, 4, 4000), (8, 16, 2000)])
+def test_decode_over_shared_units_is_reproducible(Hq, batch, tokens):
+    """Decode over the shared partition with more than eight partials an instance: which instances a workgroup folds depends on
+    which of them it is the last of, their sums do not.  Forty launches, float outputs, bit for bit."""
+    from paper_2512_22195_amd import binding as mk
+    Hkv, D, cap = 8, 128, 24
+    ctx = mk.Context(mk.make_config(1, Hq, Hkv, D, 256, "bf16", 10000.0, max_batch=batch, max_pages=1, max_tail_tokens=cap, out_f32=1))
+    try:
+        with torch.cuda.stream(ctx.compute_stream):
+            gen = torch.Generator(device="cuda").manual_seed(3)
+            draw = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+            slot = draw(2 * Hkv * tokens * D).view(torch.uint8)
+            q, tail, table = draw(batch, Hq, D), draw(2, batch, Hkv, cap, D), ctx.new_table()
+            ctx.assemble([[(slot, tokens)]] * batch, [1 + b for b in range(batch)], table)
+            assert ctx.table_shared_units(table) > 8
+            outs = torch.zeros((40, batch, Hq, D), dtype=torch.float32, device="cuda")
+            for o in outs:
+                ctx.decode_attn(0, q, table, tail[0], tail[1], o)
+            ctx.compute_stream.synchronize()
+        assert torch.isfinite(outs).all() and (outs == outs[0]).all()
+    finally:
+        ctx.close()
+
+
 @pytest.mark.parametrize("compressed", [False, True], ids=["plain", "compressed"])
 @pytest.mark.parametrize("Hq,caches,units,even", [
     (32, [[1000]] * 17, 1, True),                                       # an even batch that leaves compute units idle
