@@ -260,11 +260,23 @@ matkv_status matkv_assemble(matkv_ctx* ctx, const matkv_page* pages_host,
  * chunk lengths, q_len the question length.  Unit u streams unit_tokens_out[u] page tokens and
  * is made of unit_items_out[u] page pieces; the last unit also owns the tail.  Returns the
  * number of units (at most cap), or -1 on a bad argument.  Either output may be NULL.  (Where these
- * units would leave compute units idle or waiting, matkv_assemble has decode launches take runs of
- * equal length across the batch's caches instead; results are the same.) */
+ * units would leave compute units idle or waiting, decode launches take the runs of
+ * matkv_plan_even_units instead.) */
 int32_t matkv_plan_decode_units(const matkv_config* cfg, const int32_t* page_tokens_host,
                                 int32_t n_pages, int32_t batch, int32_t q_len,
                                 int32_t* unit_tokens_out, int32_t* unit_items_out, int32_t cap);
+/* Host-only preview of the even decode partition that matkv_assemble builds beside the one by instance for a batch without
+ * shared pages whose decode step is not a single launch: the batch's caches end to end (an instance's pages, then its tail),
+ * cut into 256 / n_kv_heads runs of nearly equal length, one workgroup per KV head each (no GPU is touched).
+ * page_tokens_host: [batch][max_pages], instance b has its first n_pages_host[b] chunk lengths, in `format`.  Run u is written to
+ * units_out[u * 8 ..]: page tokens it streams, the instance whose tail it holds (-1: none), then two triples (instance, partial
+ * slot, page tokens of the run that are this instance's), -1 / -1 / 0 where unused; the last runs may be empty.  slots_out (may be
+ * NULL): [batch][2] = first partial slot and number of slots of each instance.  taken_out (may be NULL): whether decode launches take
+ * the runs; if not they take the units by instance.  Both give the same attention up to rounding (sums are taken in another
+ * order).  Returns the number of runs (at most cap), 0 if none are built, -1 on a bad argument. */
+int32_t matkv_plan_even_units(const matkv_config* cfg, const int32_t* page_tokens_host, const int32_t* n_pages_host,
+                              const int32_t* q_len_host, int32_t batch, int32_t format, int32_t* units_out, int32_t cap,
+                              int32_t* slots_out, int32_t* taken_out);
 /* Host-only preview: the kernel that projects n_rows token rows (of a chunk, of a batch's questions or of its new
  * tokens).  0: a row per workgroup, 1: matrix-vector products, 2: matrix cores for up to 16 rows, 3: matrix cores, the
  * hidden axis split within a workgroup, 4: tiled matrix product; -1 on a bad argument. */

@@ -29,7 +29,7 @@ EXPORTS = [
     "matkv_prefill_attn", "matkv_decode_attn", "matkv_decode_step", "matkv_graph_begin", "matkv_graph_end",
     "matkv_graph_launch", "matkv_graph_destroy", "matkv_graph_kernel_launches", "matkv_plan_decode_units", "matkv_probe_read",
     "matkv_table_shared_units", "matkv_plan_projection", "matkv_plan_prefill",
-    "matkv_plan_shared_units", "matkv_plan_decode_streams", "matkv_decode_attn_static",
+    "matkv_plan_shared_units", "matkv_plan_even_units", "matkv_plan_decode_streams", "matkv_decode_attn_static",
 ]
 
 
@@ -107,6 +107,8 @@ def _load_library():
     lib.matkv_plan_decode_units.argtypes = [cfgp, POINTER(c_int32), c_int32, c_int32, c_int32,
                                             POINTER(c_int32), POINTER(c_int32), c_int32]
     lib.matkv_plan_decode_units.restype = c_int32
+    lib.matkv_plan_even_units.argtypes = [cfgp] + [POINTER(c_int32)] * 3 + [c_int32, c_int32, POINTER(c_int32), c_int32, POINTER(c_int32), POINTER(c_int32)]
+    lib.matkv_plan_even_units.restype = c_int32
     lib.matkv_plan_decode_streams.argtypes = [cfgp] + [POINTER(c_int32)] * 4 + [c_int32, c_int32]
     lib.matkv_plan_decode_streams.restype = c_int32
     lib.matkv_plan_projection.argtypes = [cfgp, c_int32]; lib.matkv_plan_projection.restype = c_int32
@@ -188,6 +190,27 @@ def plan_shared_units(cfg: Config, pages, q_lens):
                   users=[(out[u * w + 4 + 3 * k], out[u * w + 5 + 3 * k], out[u * w + 6 + 3 * k]) for k in range(out[u * w + 3])])
              for u in range(n)]
     return units, ([(slots[2 * b], slots[2 * b + 1]) for b in range(batch)] if n else None)
+
+
+def plan_even_units(cfg: Config, page_tokens, q_lens, format: int = PAGE_PLAIN):
+    """Even decode partition matkv_assemble would build for a batch without shared pages.  page_tokens: per instance a list of chunk
+    lengths.  Returns (runs, slots, taken): runs = dicts {tokens, tail (the instance whose tail the run holds, or None), users:
+    [(instance, slot, page tokens)]}, slots = [(first, count)] per instance, taken = whether decode launches take them; ([], None, False)
+    if none are built."""
+    batch, mp = len(page_tokens), max(cfg.max_pages, 1)
+    toks = (c_int32 * (batch * mp))()
+    for b, lens in enumerate(page_tokens):
+        for i, n in enumerate(lens[:mp]):
+            toks[b * mp + i] = n
+    npg, ql = (c_int32 * batch)(*[len(p) for p in page_tokens]), (c_int32 * batch)(*q_lens)
+    cap, taken = 256, c_int32(0)
+    out, slots = (c_int32 * (cap * 8))(), (c_int32 * (2 * batch))()
+    n = _lib.matkv_plan_even_units(byref(cfg), toks, npg, ql, batch, format, out, cap, slots, byref(taken))
+    if n < 0:
+        raise MatKVError(EINVAL, "matkv_plan_even_units")
+    runs = [dict(tokens=out[u * 8], tail=out[u * 8 + 1] if out[u * 8 + 1] >= 0 else None,
+                 users=[tuple(out[u * 8 + 2 + 3 * k:u * 8 + 5 + 3 * k]) for k in range(2) if out[u * 8 + 2 + 3 * k] >= 0]) for u in range(n)]
+    return runs, ([(slots[2 * b], slots[2 * b + 1]) for b in range(batch)] if n else None), bool(taken.value)
 
 
 def plan_decode_streams(cfg: Config, pages, q_lens, format: int = PAGE_PLAIN) -> bool:

@@ -17,6 +17,7 @@
 #include <mutex>
 #include <exception>
 #include <new>
+#include <numeric>
 #include <thread>
 #include <unordered_map>
 #include <vector>
@@ -506,28 +507,34 @@ PrefillLayout lay_out_prefill(const matkv_config& cfg, const matkv_page* pages, 
 // one tail at the most, so two instances, and each (run, instance) pair has a partial slot.  Always 256 / KV heads runs, empty ones at
 // the end: a recorded step has that launch shape whatever the lengths.  By instance, a batch of 17 leaves half of the chip idle, and a
 // ragged one waits for its longest cache.
-// Returns whether launches take it.  Its kernel looks up whose rows are whose and costs 2 to 4 us more, as long as a workgroup takes for 150
-// tokens: so only where the longest workgroup has 400 tokens fewer than by instance, and there an eighth of the compute units would be idle or
-// it would be half as long again.  us per layer step, caches of 3600 tokens unless said, by instance -> even: 8B shape, 12 users 46.8 -> 44.0, ragged
-// (1080 to 3600) 40.4 -> 35.6, 17 users 75.0 -> 59.0, ragged 66.7 -> 44.6, 24 users 83.7 -> 75.5, ragged 66.6 -> 55.5; 70B shape, 17 users
-// 86.7 -> 64.7.  Beyond the line: 5 users 26.1 -> 28.4, 9 users 35.7 -> 36.3, 32 ragged 76.2 -> 75.2 (70B 81.7 -> 82.1), 24 users of 400
-// tokens 23.9 -> 25.5.
+// Items: at most one per run, page and tail, 256 / KV heads + pages + batch of them, for which the table has room behind the two
+// partitions by instance (units + pages + batch each) in the 128 per instance that are the shared partition's.
+// Returns whether launches take it.  Its kernel looks up whose rows are whose and costs 2 to 4 us more, so only where a run has 400 tokens fewer
+// (500 of compressed pages) than the longest unit by instance, as that is cut, its tail whole - and where the longest run, whose tail is not cut either, is
+// shorter than that unit.  us per layer step, by instance -> even: 8B shape, 17 users of 3600 tokens 56.3 -> 47.0, of 1000 19.0 -> 17.8, 24 of up to 2000 with 300-row
+// questions 36.2 -> 31.5; 70B shape, 17 of 3600 56.6 -> 48.7.  Beyond the line: 9 of 3600 28.8 -> 29.4, 24 of 400 23.9 -> 25.5; 70B, five with 982-row questions
+// over 3577 tokens 25.8 -> 33.7, seven with 1488 over 510 19.3 -> 25.6.  Mean gain over 5384 seeded steps (2 to 31 users of 100 to 8000 tokens, questions
+// of up to 1600 rows, even and ragged; 3B, 8B, 70B; 4 to 28 layers) by how many tokens fewer: 200 to 300 -1 %, 300 to 400 +2 %, 400 to 500 +3 %, 500 to
+// 1000 +8 %, more +17 %; compressed 300 to 400 -3 %, 400 to 500 -2 %, 500 to 700 +2 %, more +12 %.  The better of the two is taken but for 0.2 % of the
+// time; by the runs' nominal length and a unit's mean alone, as the line once was, it was 1.1 %, and of 1312 steps over runs 470 were slower for it.
 constexpr long kEvenMinGranules = 16;           // 128 tokens
 bool build_even_units(const matkv_config& cfg, const matkv_page* pages, const int32_t* n_pages, int batch, InstanceInfo* insts, Item* items,
-                      int* n_items, int n_dunits, SUnit* sunits, int kv_fmt) {
+                      int* n_items, const Unit* dunits, int n_dunits, SUnit* sunits, int kv_fmt) {
     const int n_units = 256 / cfg.n_kv_heads;
     auto tail_gran = [&](int b) { return (long)(insts[b].q_len + (cfg.max_tail_tokens - insts[b].q_len) / 2 + 7) / 8; };
     long total = 0, by_inst = 0;                    // by_inst: tokens of the longest unit by instance
     for (int b = 0; b < batch; ++b) {
-        long inst = tail_gran(b);
-        for (int p = 0; p < n_pages[b]; ++p) inst += (pages[(size_t)b * cfg.max_pages + p].n_tokens + 7) / 8;
-        total += inst;
-        by_inst = std::max(by_inst, 8 * inst / std::max(insts[b].n_dunits, 1));
+        total += tail_gran(b);
+        for (int p = 0; p < n_pages[b]; ++p) total += (pages[(size_t)b * cfg.max_pages + p].n_tokens + 7) / 8;
     }
-    // runs of `per` granules of eight tokens; emit = false only counts them
+    for (int u = 0; u < n_dunits; ++u)
+        by_inst = std::max(by_inst, dunits[u].page_tokens + (dunits[u].has_tail ? 8 * tail_gran(dunits[u].inst) : 0));
+    long longest = 0;                               // granules of the longest run of the last cut
+    // runs of `per` granules of eight tokens, and of what a tail in their last one has beyond that; emit = false only counts them
     auto cut = [&](long per, bool emit) {
         int n = 0;                                              // runs opened
         long room = 0;
+        longest = 0;
         bool has_tail = true;                                   // (of the open run: nothing fits any more)
         SUnit* su = nullptr;
         Item* it = items + *n_items;
@@ -573,6 +580,7 @@ bool build_even_units(const matkv_config& cfg, const matkv_page* pages, const in
                         add(piece);
                     }
                     g += take; room -= take;
+                    longest = std::max(longest, per - room);
                 }
             }
             if (room <= 0 || has_tail) open();                  // a tail is not cut
@@ -585,6 +593,7 @@ bool build_even_units(const matkv_config& cfg, const matkv_page* pages, const in
             }
             has_tail = true;
             room -= tail_gran(b);
+            longest = std::max(longest, per - room);
         }
         if (emit) *n_items = (int)(it - items);
         return n;
@@ -604,7 +613,7 @@ bool build_even_units(const matkv_config& cfg, const matkv_page* pages, const in
         un.first = items[un.item0];
         for (int k = 0; k < sunits[u].n_users; ++k) sunits[u].users[k].slot += insts[sunits[u].users[k].inst].sslot0;
     }
-    return by_inst - 8 * per > 400 && (8 * n_dunits <= 7 * n_units || 2 * by_inst > 3 * 8 * per);
+    return by_inst - 8 * per > (kv_fmt == MATKV_PAGE_E4M3 ? 500 : 400) && by_inst > 8 * longest;
 }
 
 // Shared decode partition (instances of a batch that retrieved the same chunk read it once).
@@ -875,7 +884,7 @@ DecodeLayout lay_out_decode(const matkv_config& cfg, const TableLayout& tl, cons
     SUnit* const runs = reinterpret_cast<SUnit*>(dunits + L.n_dunits);
     if (L.n_sunits == 0 && even_partition(cfg, batch, L.n_dunits)) {
         L.even_built = true;
-        L.even = build_even_units(cfg, pages, n_pages, batch, insts, items, n_items, L.n_dunits, runs, kv_fmt);
+        L.even = build_even_units(cfg, pages, n_pages, batch, insts, items, n_items, dunits, L.n_dunits, runs, kv_fmt);
     }
     size_t page_tokens = 0, tail_rows = 0, longest = 0;
     auto walk = [&](const Unit& u) {
@@ -1735,6 +1744,27 @@ int32_t matkv_plan_prefill(const matkv_config* cfg, const int32_t* page_tokens, 
     MATKV_CATCH_INT
 }
 
+// The pages and instances of a batch as a preview gets them; ids: equal ones mean the same slot.  False on a bad argument.
+static bool preview_batch(const matkv_config& cfg, const int32_t* ids, const int32_t* tokens, const int32_t* n_pages, const int32_t* q_len,
+                          int32_t batch, int32_t format, std::vector<matkv_page>& pages, std::vector<InstanceInfo>& insts) {
+    pages.resize((size_t)batch * std::max(cfg.max_pages, 1));
+    insts.resize((size_t)batch);
+    for (int b = 0; b < batch; ++b) {
+        if (n_pages[b] < 0 || n_pages[b] > cfg.max_pages || q_len[b] < 1 || q_len[b] > cfg.max_tail_tokens) return false;
+        if (n_pages[b] > 0 && (!ids || !tokens)) return false;
+        memset(&insts[b], 0, sizeof(InstanceInfo));
+        insts[b].q_len = q_len[b];
+        for (int p = 0; p < n_pages[b]; ++p) {
+            const size_t i = (size_t)b * cfg.max_pages + p;
+            if (ids[i] < 0 || tokens[i] < 1) return false;
+            pages[i].slot = reinterpret_cast<const void*>(((uintptr_t)ids[i] + 1) * 4096);   // never dereferenced
+            pages[i].n_tokens = tokens[i];
+            pages[i].format = format;
+        }
+    }
+    return true;
+}
+
 int32_t matkv_plan_shared_units(const matkv_config* cfg, const int32_t* page_ids, const int32_t* page_tokens,
                                 const int32_t* n_pages, const int32_t* q_len, int32_t batch,
                                 int32_t* units_out, int32_t cap, int32_t* slots_out) {
@@ -1743,21 +1773,9 @@ int32_t matkv_plan_shared_units(const matkv_config* cfg, const int32_t* page_ids
     if (!n_pages || !q_len || batch < 1 || batch > cfg->max_batch || cap < 0 || (cap > 0 && !units_out)) return -1;
     MATKV_TRY
     const int grp = cfg->n_q_heads / cfg->n_kv_heads;
-    std::vector<matkv_page> pages((size_t)batch * std::max(cfg->max_pages, 1));
-    std::vector<InstanceInfo> insts((size_t)batch);
-    for (int b = 0; b < batch; ++b) {
-        if (n_pages[b] < 0 || n_pages[b] > cfg->max_pages || q_len[b] < 1 || q_len[b] > cfg->max_tail_tokens) return -1;
-        if (n_pages[b] > 0 && (!page_ids || !page_tokens)) return -1;
-        memset(&insts[b], 0, sizeof(InstanceInfo));
-        insts[b].q_len = q_len[b];
-        for (int p = 0; p < n_pages[b]; ++p) {
-            const size_t i = (size_t)b * cfg->max_pages + p;
-            if (page_ids[i] < 0 || page_tokens[i] < 1) return -1;
-            pages[i].slot = reinterpret_cast<const void*>(((uintptr_t)page_ids[i] + 1) * 4096);   // never dereferenced
-            pages[i].n_tokens = page_tokens[i];
-            pages[i].format = MATKV_PAGE_PLAIN;
-        }
-    }
+    std::vector<matkv_page> pages;
+    std::vector<InstanceInfo> insts;
+    if (!preview_batch(*cfg, page_ids, page_tokens, n_pages, q_len, batch, MATKV_PAGE_PLAIN, pages, insts)) return -1;
     // the conditions of matkv_assemble
     if (batch < 2 || cfg->decode_units != 0 || cfg->decode_variant != 0 || cfg->dtype != MATKV_BF16 ||
         cfg->head_dim != 128 || !group_size_built(grp))
@@ -1796,21 +1814,9 @@ int32_t matkv_plan_decode_streams(const matkv_config* cfg, const int32_t* page_i
     if (!n_pages || !q_len || batch < 1 || batch > cfg->max_batch || (format != MATKV_PAGE_PLAIN && format != MATKV_PAGE_E4M3)) return -1;
     if (format == MATKV_PAGE_E4M3 && !(cfg->dtype == MATKV_BF16 && cfg->head_dim == 128)) return -1;
     MATKV_TRY
-    std::vector<matkv_page> pages((size_t)batch * std::max(cfg->max_pages, 1));
-    std::vector<InstanceInfo> insts((size_t)batch);
-    for (int b = 0; b < batch; ++b) {
-        if (n_pages[b] < 0 || n_pages[b] > cfg->max_pages || q_len[b] < 1 || q_len[b] > cfg->max_tail_tokens) return -1;
-        if (n_pages[b] > 0 && (!page_ids || !page_tokens)) return -1;
-        memset(&insts[b], 0, sizeof(InstanceInfo));
-        insts[b].q_len = q_len[b];
-        for (int p = 0; p < n_pages[b]; ++p) {
-            const size_t i = (size_t)b * cfg->max_pages + p;
-            if (page_ids[i] < 0 || page_tokens[i] < 1) return -1;
-            pages[i].slot = reinterpret_cast<const void*>(((uintptr_t)page_ids[i] + 1) * 4096);   // never dereferenced
-            pages[i].n_tokens = page_tokens[i];
-            pages[i].format = format;
-        }
-    }
+    std::vector<matkv_page> pages;
+    std::vector<InstanceInfo> insts;
+    if (!preview_batch(*cfg, page_ids, page_tokens, n_pages, q_len, batch, format, pages, insts)) return -1;
     const TableLayout tl = table_layout(*cfg);
     std::vector<Item> items((size_t)tl.max_items);
     std::vector<Unit> units((size_t)tl.max_dunits);
@@ -1818,6 +1824,48 @@ int32_t matkv_plan_decode_streams(const matkv_config* cfg, const int32_t* page_i
     int n_items = 0;
     return lay_out_decode(*cfg, tl, pages.data(), n_pages, batch, format, insts.data(), items.data(), &n_items, units.data(), sunits.data(),
                           [](int) { return (size_t)0; }).past_llc;
+    MATKV_CATCH_INT
+}
+
+int32_t matkv_plan_even_units(const matkv_config* cfg, const int32_t* page_tokens, const int32_t* n_pages, const int32_t* q_len, int32_t batch,
+                              int32_t format, int32_t* units_out, int32_t cap, int32_t* slots_out, int32_t* taken_out) {
+    const char* why;
+    if (check_config(cfg, &why) != MATKV_OK) return -1;
+    if (!n_pages || !q_len || batch < 1 || batch > cfg->max_batch || cap < 0 || (cap > 0 && !units_out)) return -1;
+    if ((format != MATKV_PAGE_PLAIN && format != MATKV_PAGE_E4M3) || (format == MATKV_PAGE_E4M3 && !(cfg->dtype == MATKV_BF16 && cfg->head_dim == 128))) return -1;
+    MATKV_TRY
+    std::vector<matkv_page> pages;
+    std::vector<InstanceInfo> insts;
+    std::vector<int32_t> ids((size_t)batch * std::max(cfg->max_pages, 1));
+    std::iota(ids.begin(), ids.end(), 0);
+    if (!preview_batch(*cfg, ids.data(), page_tokens, n_pages, q_len, batch, format, pages, insts)) return -1;
+    const TableLayout tl = table_layout(*cfg);
+    std::vector<Item> items((size_t)tl.max_items);
+    std::vector<Unit> units((size_t)tl.max_dunits);
+    std::vector<SUnit> sunits((size_t)tl.max_sunits);
+    int n_items = 0;
+    const DecodeLayout L = lay_out_decode(*cfg, tl, pages.data(), n_pages, batch, format, insts.data(), items.data(), &n_items, units.data(),
+                                          sunits.data(), [](int) { return (size_t)0; });
+    if (!L.even_built) return 0;
+    if (taken_out) *taken_out = L.even;
+    const int n = 256 / cfg->n_kv_heads;
+    for (int u = 0; u < n && u < cap; ++u) {
+        const SUnit& su = reinterpret_cast<const SUnit*>(units.data() + L.n_dunits)[u];
+        int32_t* o = units_out + (size_t)u * 8;
+        int32_t seen[2] = {0, 0};
+        for (int i = su.u.item0; i < su.u.item0 + su.u.n_items; ++i)
+            for (int k = 0; k < 2; ++k) if (items[i].base && (items[i].umask >> k & 1)) seen[k] += items[i].ntok;
+        o[0] = su.u.page_tokens;
+        o[1] = su.u.has_tail ? su.u.inst : -1;
+        for (int k = 0; k < 2; ++k) {
+            o[2 + 3 * k] = k < su.n_users ? su.users[k].inst : -1;
+            o[3 + 3 * k] = k < su.n_users ? su.users[k].slot : -1;
+            o[4 + 3 * k] = k < su.n_users ? seen[k] : 0;
+        }
+    }
+    if (slots_out)
+        for (int b = 0; b < batch; ++b) { slots_out[2 * b] = insts[b].sslot0; slots_out[2 * b + 1] = insts[b].n_sslots; }
+    return n < cap ? n : cap;
     MATKV_CATCH_INT
 }
 

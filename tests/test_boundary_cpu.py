@@ -114,6 +114,75 @@ def test_decode_partition_never_exceeds_the_compute_units(mk):
         assert sum(toks) == 10000
 
 
+def test_even_partition_covers_every_instance_once(mk):
+    """Host logic of the even decode partition: runs in number always 256 / KV heads; every page token of an instance streamed by exactly
+    one run that lists it; one tail per run and two users at most; an instance's tail in exactly one of its runs; its partial slots used
+    up by its runs' entries, the slots of all instances one behind the other; no run longer than the cut and a tail.  Instances without
+    pages, single tokens and tails longer than a run among them."""
+    rng = np.random.default_rng(11)
+    built = chosen = 0
+    for G, Hkv in ((4, 8), (8, 8), (3, 8), (8, 2), (1, 16)):
+        for trial in range(24):
+            batch = int(rng.integers(2, min(256 // Hkv, 40) + 1))
+            most = int(rng.choice([3, 200, 4000]))
+            pages = [[int(rng.integers(1, most + 1)) for _ in range(int(rng.integers(0, 5)))] for _ in range(batch)]
+            max_tail = int(rng.choice([16, 128, 2048]))
+            q_lens = [int(rng.integers(1, max_tail + 1)) for _ in range(batch)]
+            cfg = mk.make_config(2, G * Hkv, Hkv, 128, 4096, "bf16", 500000.0, batch, 4, max_tail)
+            runs, slots, taken = mk.plan_even_units(cfg, pages, q_lens)
+            if batch <= 4 and G <= 4:
+                assert runs == [] and not taken             # (one launch per step)
+                continue
+            built += 1
+            chosen += taken
+            assert len(runs) == 256 // Hkv
+            seen, used, tails = [0] * batch, [set() for _ in range(batch)], [0] * batch
+            tail_tokens = [(q + (max_tail - q) // 2 + 7) // 8 * 8 for q in q_lens]
+            total = sum(sum((n + 7) // 8 * 8 for n in p) for p in pages) + sum(tail_tokens)
+            for r in runs:
+                assert len(r["users"]) <= 2 and r["tokens"] == sum(n for _, _, n in r["users"])
+                assert len({b for b, _, _ in r["users"]}) == len(r["users"])
+                if r["tail"] is not None:
+                    assert r["tail"] in [b for b, _, _ in r["users"]]
+                    tails[r["tail"]] += 1
+                for b, slot, n in r["users"]:
+                    assert n > 0 or r["tail"] == b
+                    seen[b] += n
+                    assert slot not in used[b] and slots[b][0] <= slot < slots[b][0] + slots[b][1]
+                    used[b].add(slot)
+            assert seen == [sum(p) for p in pages] and tails == [1] * batch
+            assert [len(u) for u in used] == [c for _, c in slots]
+            assert [f for f, _ in slots] == [sum(c for _, c in slots[:b]) for b in range(batch)]
+            empty = [not r["users"] for r in runs]
+            assert empty == sorted(empty)                   # empty runs come last
+            assert max(r["tokens"] for r in runs) <= 8 * max(16, -(-total // 8 // len(runs)) * 2 + max(tail_tokens) // 8)
+    assert built > 100 and 10 < chosen < built
+    cfg = mk.make_config(2, 32, 8, 128, 4096, "bf16", 500000.0, 6, 2, 64, decode_units=3)
+    assert mk.plan_even_units(cfg, [[500]] * 6, [9] * 6) == ([], None, False)
+    for bad in (([[0]] * 6, [9] * 6), ([[5]] * 6, [65] * 6), ([[5]] * 7, [9] * 7)):
+        with pytest.raises(mk.MatKVError):
+            mk.plan_even_units(mk.make_config(2, 32, 8, 128, 4096, "bf16", 500000.0, 6, 2, 64), *bad)
+
+
+def test_even_partition_is_taken_where_its_longest_run_is_shorter(mk):
+    """Host logic: the choice between the two decode partitions.  Long tails, which are not cut, make runs as long as the units they
+    replace: then the units stay."""
+    def taken(caches, q_len, max_tail, Hq=32, fmt=mk.PAGE_PLAIN):
+        cfg = mk.make_config(2, Hq, 8, 128, 4096, "bf16", 500000.0, len(caches), 3, max_tail)
+        return mk.plan_even_units(cfg, caches, [q_len] * len(caches), fmt)[2]
+
+    for Hq in (32, 64):
+        assert taken([[3600]] * 17, 64, 256, Hq) and taken([[3600]] * 12, 64, 256, Hq) and taken([[900] * 3] * 20, 64, 256, Hq)
+        assert taken([[1080 + 90 * b] for b in range(17)], 64, 256, Hq)
+        assert not taken([[3600]] * 9, 64, 256, Hq) and not taken([[3600]] * 5, 64, 256, Hq) and not taken([[400]] * 24, 64, 256, Hq)
+        assert not taken([[3600]] * 16, 64, 256, Hq) and not taken([[3600]] * 32, 64, 256, Hq)
+        # longest run / longest unit: 2224 / 2224, 1120 / 1120, 1230 / 1230 tokens
+        assert not taken([[200]] * 17, 2000, 2048, Hq) and not taken([[500]] * 20, 600, 640, Hq) and not taken([[300]] * 18, 900, 960, Hq)
+        assert not taken([[510]] * 7, 1488, 1552, Hq) and not taken([[3577]] * 5, 982, 992, Hq)
+        # 448 tokens fewer
+        assert taken([[850]] * 17, 64, 256, Hq) and not taken([[850]] * 17, 64, 256, Hq, mk.PAGE_E4M3) and taken([[1200]] * 17, 64, 256, Hq, mk.PAGE_E4M3)
+
+
 def test_decode_streams_only_rows_that_displace_something(mk):
     """Host logic: the cache's rows pass the last-level cache (256 MB) by where a step over all layers does not fit there and the weights do,
     or where the rows of one layer are many, and only while most of the chip walks to the end; short contexts of a whole model,

@@ -691,6 +691,13 @@ def _decode_batch(Hq, caches, q_lens, compressed, decode_units, replays=(), max_
         ctx.close()
 
 
+def _takes_even_runs(Hq, caches, q_lens, compressed=False):
+    """What matkv_assemble decides for _decode_batch's table (decode_units = 0)."""
+    from paper_2512_22195_amd import binding as mk
+    cfg = mk.make_config(1, Hq, 8, 128, 256, "bf16", 10000.0, max_batch=len(caches), max_pages=4, max_tail_tokens=24, out_f32=1)
+    return mk.plan_even_units(cfg, caches, q_lens, mk.PAGE_E4M3 if compressed else mk.PAGE_PLAIN)[2]
+
+
 def _same_attention(a, b):
     """Two partitions of the same caches: weights are rounded to bf16 against other references, 2^-9 of a value each, and sums are taken
     in another order; the bar is that of one side against the oracle."""
@@ -698,9 +705,9 @@ def _same_attention(a, b):
     assert torch.isfinite(a).all() and ((a - b).abs() <= 2e-2 * rms).all(), ((a - b).abs() / rms).max()
 
 
-@pytest.mark.parametrize("Hq,batch,tokens", [(16, 5, 3000), (32, 4, 4000), (8, 16, 2000)])
-def test_decode_over_shared_units_is_reproducible(Hq, batch, tokens):
-    """Decode over the shared partition with more than eight partials an instance: which instances a workgroup folds depends on
+@pytest.mark.parametrize("Hq,batch,tokens,shared", [(16, 5, 3000, True), (32, 4, 4000, True), (8, 16, 2000, True), (64, 3, 4000, False), (24, 6, 3000, False)])
+def test_decode_over_shared_units_is_reproducible(Hq, batch, tokens, shared):
+    """Decode over the shared and the even partition with more than eight partials an instance: which instances a workgroup folds depends on
     which of them it is the last of, their sums do not.  Forty launches, float outputs, bit for bit."""
     from paper_2512_22195_amd import binding as mk
     Hkv, D, cap = 8, 128, 24
@@ -709,10 +716,16 @@ def test_decode_over_shared_units_is_reproducible(Hq, batch, tokens):
         with torch.cuda.stream(ctx.compute_stream):
             gen = torch.Generator(device="cuda").manual_seed(3)
             draw = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
-            slot = draw(2 * Hkv * tokens * D).view(torch.uint8)
+            # (not shared: the first cache long, so that the even partition is taken and it has the most slots)
+            lens = [tokens] * batch if shared else [2 * tokens] + [100] * (batch - 1)
+            slots = [draw(2 * Hkv * n * D).view(torch.uint8) for n in ([tokens] if shared else lens)]
             q, tail, table = draw(batch, Hq, D), draw(2, batch, Hkv, cap, D), ctx.new_table()
-            ctx.assemble([[(slot, tokens)]] * batch, [1 + b for b in range(batch)], table)
-            assert ctx.table_shared_units(table) > 8
+            ctx.assemble([[(slots[0 if shared else b], lens[b])] for b in range(batch)], [1 + b for b in range(batch)], table)
+            if shared:
+                assert ctx.table_shared_units(table) > 8
+            else:
+                runs, counts, taken = mk.plan_even_units(ctx.cfg, [[n] for n in lens], [1 + b for b in range(batch)])
+                assert taken and max(c for _, c in counts) > 8
             outs = torch.zeros((40, batch, Hq, D), dtype=torch.float32, device="cuda")
             for o in outs:
                 ctx.decode_attn(0, q, table, tail[0], tail[1], o)
@@ -724,18 +737,19 @@ def test_decode_over_shared_units_is_reproducible(Hq, batch, tokens):
 
 @pytest.mark.parametrize("compressed", [False, True], ids=["plain", "compressed"])
 @pytest.mark.parametrize("Hq,caches,units,even", [
-    (32, [[1000]] * 17, 1, True),                                       # an even batch that leaves compute units idle
+    (32, [[1200]] * 17, 1, True),                                       # an even batch that leaves compute units idle
     (8, [[3000, 7]] + [[], [1], [8, 9], [64]] * 4, 1, True),            # one long cache, short ones, none at all
     (16, [[700, 40]] * 30 + [[1999, 2001]], 1, True),                   # as many instances as there are runs, but one
     (24, [[900, 33, 1], [2800, 801], [64], [1500]] * 3, 2, True),       # two units by instance, ragged
     (64, [[8001], [100], [50]], 10, True),                              # two instances at most fit a tile of 64 heads
-    (64, [[500, 3000, 2999, 1502], [1, 2, 3, 4]], 16, True),
+    (64, [[500, 3000, 2999, 1502], [1, 2, 3, 4], [700]], 10, True),
     (32, [[600]] * 17, 1, False), (16, [[1000]] * 32, 1, False), (24, [[2000]] * 12, 2, False),
 ])
 def test_decode_over_even_runs(Hq, caches, units, even, compressed):
     """The even partition against the one by instance (decode_units fixed): the same attention.  Where the rule leaves it aside, outputs are
     those of the partition by instance bit for bit."""
     q_lens = [1 + (5 * b) % 23 for b in range(len(caches))]
+    assert _takes_even_runs(Hq, caches, q_lens, compressed) == even
     got, = _decode_batch(Hq, caches, q_lens, compressed, 0)
     want, = _decode_batch(Hq, caches, q_lens, compressed, units)
     _same_attention(got, want)
@@ -748,6 +762,7 @@ def test_recorded_decode_replays_over_either_partition():
     q_lens = [3 + b for b in range(17)]
     long, short = [[1000]] * 17, [[100], [200, 28], []] * 5 + [[5], [190]]
     mixed = [[3000]] + [[20]] * 16
+    assert [_takes_even_runs(32, c, q_lens) for c in (long, short, mixed)] == [True, False, True]
     for first in (long, short):
         got = _decode_batch(32, first, q_lens, False, 0, replays=[short, long, mixed, short])
         want = _decode_batch(32, first, q_lens, False, 1, replays=[short, long, mixed, short])
