@@ -375,7 +375,7 @@ hipError_t launch_tiled(const MaterializeArgs& a, int total_rows, hipStream_t s)
     auto groups = [&](int mi) { return nct * ((total_rows + 32 * mi - 1) / (32 * mi)); };
     auto halved = [&](int mi) {
         const int64_t tiles = groups(mi);
-        return (a.Hd % (2 * BK)) == 0 && tiles * 2 <= 256 && (mi <= 4 || a.Hd >= 8192) && a.ws_partials &&
+        return (a.Hd % (2 * BK)) == 0 && tiles * 2 <= 256 && (mi <= 4 || a.Hd >= kTallSplitHidden) && a.ws_partials &&
                tiles * 2 * (32 * mi) * D <= a.ws_partial_floats && tiles * kDecodeCounterStride <= a.ws_n_counters;
     };
     if (halved(1)) return launch_tile<1, 4, 2>(a, total_rows, s);

@@ -69,6 +69,9 @@ def test_workspace_and_table_sizes_are_positive_and_aligned(mk):
     # 128 x 128) however small the attention's own needs are
     small = mk.make_config(1, 8, 2, 128, 512, "bf16", 500000.0, 1, 1, 8)
     assert mk.workspace_bytes(small) >= 128 * 2 * 128 * 128 * 4
+    # hidden 8192: tiles of up to 256 rows are split as well, whatever the longest tail and the head count
+    for hq, max_tail in ((8, 8), (64, 16), (16, 64)):
+        assert mk.workspace_bytes(mk.make_config(1, hq, 8, 128, 8192, "bf16", 500000.0, 1, 1, max_tail)) >= 128 * 2 * 256 * 128 * 4
 
 
 def test_null_context_is_an_error_not_a_crash(mk):

@@ -259,10 +259,13 @@ def test_materialize_tall_tiles(hidden, T):
     between, each against the oracle; the second run finds the arrival counters at zero again."""
     Hkv, pos0 = 8, 50
     case = Case("bf16-tall-tiles", n_layers=1, Hq=Hkv, Hkv=Hkv, D=128, hidden=hidden, dtype="bf16",
-                chunk_lens={0: 8}, retrieved=[[0]], q_lens=[1], steps=255, rope_base=500000.0, scale=1.0 / 4.0)
+                chunk_lens={0: 8}, retrieved=[[0]], q_lens=[1], steps=1, rope_base=500000.0, scale=1.0 / 4.0)
+    from paper_2512_22195_amd import binding as mk
     from workload import normal, to_f64
     import oracle
     ctx = chain.make_context(case)
+    # the workspace has room for every tile's two halves (a tile of at most 256 rows, 128 of them)
+    assert hidden < 8192 or mk.workspace_bytes(ctx.cfg) >= 128 * 2 * 256 * 128 * 4
     try:
         with torch.cuda.stream(ctx.compute_stream):
             w = normal(("tall", hidden, "w"), (2, Hkv * 128, hidden), hidden ** -0.5, torch.bfloat16).cuda()
