@@ -528,14 +528,35 @@ def test_prefill_of_many_short_caches_uncut(q_len):
     _attention_parity(case, instances=[0, 1, 7, 14, 15])
 
 
-@pytest.mark.parametrize("q_len", [2, 32])
-def test_prefill_of_many_short_caches_uncut(q_len):
-    """Sixteen users with short caches: every cache one unit, outputs straight from the tiles (64 and 128 rows)."""
-    case = Case(f"prefill-many-{q_len}", n_layers=1, Hq=32, Hkv=8, D=128, hidden=64, dtype="bf16", chunk_lens={0: 150, 1: 130, 2: 60},
-                retrieved=[[0, 1], [2]] * 8, q_lens=[q_len, q_len // 2] * 8, steps=1, scale=0.5)
-    form, units = _prefill_form(case)
-    assert form == (64 if q_len * 4 <= 64 else 128) and units == [1] * 16
-    _attention_parity(case, instances=[0, 1, 7, 14, 15])
+@pytest.mark.parametrize("form,Hq,Hkv,retrieved,q_lens,compressed", [
+    (64, 16, 4, [[0, 1], [2, 3], [4], []], [16, 9, 5, 7], False),
+    (128, 64, 8, [[0, 1], [2, 3], [4] * 11], [33, 17, 9], False),        # two token groups, 5 units each
+    (128, 64, 8, [[0, 1], [2, 3], [4] * 11], [33, 17, 9], True),
+    (256, 64, 8, [[5, 5]] * 12, [85] * 4 + [60] * 4 + [40] * 4, False),    # one unit each
+    (256, 64, 8, [[5, 5]] * 12, [85] * 4 + [60] * 4 + [40] * 4, True),
+], ids=["short", "groups", "groups-compressed", "tall", "tall-compressed"])
+def test_prefill_rows_that_are_not_numbers_reach_no_other(form, Hq, Hkv, retrieved, q_lens, compressed):
+    """Queries with a NaN or an infinite component: their own output rows are NaN, every other one is bit for bit what it is
+    without them.  The tail's rows past the question are NaN in both runs and reach none."""
+    case = Case("prefill-nan", n_layers=1, Hq=Hq, Hkv=Hkv, D=128, hidden=64, dtype="bf16", chunk_lens={0: 300, 1: 350, 2: 190, 3: 500, 4: 64, 5: 67},
+                retrieved=retrieved, q_lens=q_lens, steps=0, scale=0.5, compressed=compressed)
+    got, units = _prefill_form(case)
+    assert got == form and (max(units) > 1) == (form < 256)
+    inp = chain.make_attention_inputs(case)
+    for b, n in enumerate(q_lens):
+        inp["tail"][:, :, b, :, n:] = float("nan")
+    clean = chain.run_gpu_attention(case, inp)[0]
+    pre, _ = chain.run_oracle_attention(case, inp, instances=[0, 2])
+    chain.compare_attention(case, clean, clean[:0], pre, {})
+    rows = [(0, 0, float("nan")), (3, 1, float("inf")), (3, Hq - 1, float("-inf")), (sum(q_lens) - 1, 2, float("nan"))]
+    for r, h, x in rows:
+        inp["q_pre"][0, r, h, (17 * h + 5) % 128] = x
+    got = chain.run_gpu_attention(case, inp)[0]
+    bad = torch.zeros(got.shape[:3], dtype=torch.bool)
+    for r, h, _ in rows:
+        bad[0, r, h] = True
+    assert torch.isnan(got[bad].float()).all()
+    assert torch.equal(got[~bad], clean[~bad])
 
 
 @pytest.mark.parametrize("compressed", [False, True])
@@ -1526,12 +1547,13 @@ def test_compress_is_bit_exact(L):
     assert scales[1, 1, 0] == 2.0 ** -6
 
 
-@pytest.mark.parametrize("n_layers,L,D", [(3, 33001, 128), (5, 10243, 64)])
-def test_compress_of_many_pieces(n_layers, L, D):
-    """Long heads: several launches (layers in groups of at most 128 MB, here one by one and all at once), pieces with a ragged end, the
-    largest value in another piece of every head.  Codes and scales against the library cast of x / s, s by the rule, bit for bit."""
+@pytest.mark.parametrize("n_layers,L,D,Hkv", [(3, 33001, 128, 8), (5, 10243, 64, 8), (5, 16001, 128, 8), (1, 4500003, 64, 1)])
+def test_compress_of_many_pieces(n_layers, L, D, Hkv):
+    """Long heads: several launches (layers in groups of at most 128 MB, here one by one, all at once, and two, two and one), pieces with
+    a ragged end, more of them than scratch has places for (8790 pieces of a head on 8704 workgroups: the last ones are a second round of
+    some of these), the largest value in another piece of every head.  Codes and scales against the library cast of x / s, s by the
+    rule, bit for bit."""
     from paper_2512_22195_amd import binding as mk
-    Hkv = 8
     ctx = mk.Context(mk.make_config(n_layers, Hkv, Hkv, D, 256, "bf16", 10000.0, max_batch=1, max_pages=1, max_tail_tokens=8))
     try:
         with torch.cuda.stream(ctx.compute_stream):
