@@ -51,10 +51,6 @@ __device__ __forceinline__ float lane_xor(float v, int off, int lane) {
     return __shfl_xor(v, off);
 }
 
-// One pair of output elements of a bf16 launch: rounded to bf16, or as they are when the
-// configuration asks for float outputs.
-__device__ __forceinline__ void store_out2(void* out, bool f32, size_t idx, float x, float y);
-
 struct KernelArgs {
     const void* __restrict__ q;
     void* __restrict__ out;
@@ -68,16 +64,11 @@ struct KernelArgs {
     float scale_log2e;
     uint32_t g_mul;              // 2^29 / (Hq / Hkv), rounded up
 };
-// What follows the block in a launch's argument buffer (table pointers, grid size) is read first thing by every
-// workgroup; four bytes more move some of it into another line, which costs a launch 0.25 to 0.3 us.
+// The table pointers come before the block in a matrix-core launch's argument buffer and the grid size behind it; every workgroup
+// reads both first thing.  Four bytes more move some of that into another line, which costs a launch 0.25 to 0.3 us.
 static_assert(sizeof(KernelArgs) <= 88, "argument block of the attention kernels");
 
-__device__ __forceinline__ void store_out2(void* out, bool f32, size_t idx, float x, float y) {
-    if (f32) *reinterpret_cast<float2*>(reinterpret_cast<float*>(out) + idx) = make_float2(x, y);
-    else *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(out) + idx) = (uint32_t)f32_to_bf16_rne(x) | ((uint32_t)f32_to_bf16_rne(y) << 16);
-}
-
-// Four output elements: 8 bytes of bf16 (the hardware conversion rounds as f32_to_bf16_rne does), or 16 of float.
+// Four output elements, float where the configuration asks for it: 8 bytes of bf16 (the hardware conversion rounds as f32_to_bf16_rne does), or 16 of float.
 __device__ __forceinline__ void store_out4(void* out, bool f32, size_t idx, float4 v) {
     typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
     if (f32) { *reinterpret_cast<float4*>(reinterpret_cast<float*>(out) + idx) = v; return; }

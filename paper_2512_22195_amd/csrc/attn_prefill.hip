@@ -303,9 +303,11 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     // A block is taken in halves of 32 tokens.  A period of a wave multiplies the scores of half t + 1 (eight matrix
     // instructions), then the output of half t - 1 (eight more), and between these, evenly, forms the weights of half t and finds the
     // maximum of half t + 1: the vector work of a SIMD's two waves then stands beside their matrix work throughout.
-    // Step i reads K of block i + 1 and V of block i and has one barrier.  One token group (256 rows): tiles of four
-    // blocks; step i copies block i + 3 over block i - 1, K first, and ends when K of block i + 2 has landed.  Two groups (128 rows; all of LDS): two
-    // tiles of K, three of V; step i copies block i + 2, K first, and ends when that K has landed.
+    // Step i reads K of block i + 1 and V of block i and has one barrier.  It copies block i + AHEAD, K first, and ends when that K has
+    // landed and all V before it: all but the youngest NI copies (compressed pages: all that was widened).  One token group
+    // (256 rows): tiles of four blocks.  Of plain pages AHEAD = 3 and the copy goes over block i - 1; since K of block i + 2 is there
+    // when step i begins, its first operands are read within step i.  Two groups (128 rows; all of LDS): two tiles of K, three of V.  These,
+    // and compressed pages: AHEAD = 2, and the first operands of K of block i + 2 are read behind step i's barrier.
     constexpr bool RING4 = TS == 1 && !F8;
     constexpr int AHEAD = RING4 ? 3 : 2;
     BlockDesc q[AHEAD + 1];           // descriptors of blocks i .. i + AHEAD

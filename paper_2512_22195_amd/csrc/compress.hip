@@ -40,7 +40,7 @@ __device__ __forceinline__ uint2 encode8(const uint4& v, float inv) {
 // a piece's codes.  A workgroup per head, which read it twice, left most of the chip idle and had one load per thread in flight:
 // four layers of the 8B shape 164 us of a 3501-token chunk's pass, 64 of a 2000-token one's, 37 of a 1030-token one's; now 22, 11 and
 // 7.  (Heads that fit the registers stay there: eight layers of 1000 tokens 14.6 us against 16.6 this way, 32 layers 45 against 58;
-// up to four layers the two are equal.)
+// up to four layers the two are equal.  These are blobs from HBM; one that the last-level cache still holds takes 10.3 and 32.1.)
 // A piece is 4096 vectors of eight values (64 KB); a workgroup takes every gridDim.x-th.
 constexpr int NTP = 512, NVP = 8;
 __device__ __forceinline__ void load_piece(const uint4* src, size_t first, size_t n_vec, uint4 (&v)[NVP]) {

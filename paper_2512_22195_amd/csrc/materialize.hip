@@ -270,10 +270,10 @@ ProjectionForm projection_form(int hidden, int Hkv, int D, int dtype, long rows)
     // rows at hidden 4096 / 8192: 8.0 / 14.8 us against 9.7 / 20.7, 31 rows 8.0 / 13.5 against 16.1 / 33.6)
     if (D != 128 || rows < 16) return hidden % 4096 == 0 || hidden % 3072 == 0 ? ProjectionForm::kGemv : ProjectionForm::kRows;
     // The staged skinny form has eight workgroups per KV head and 32 rows.  While every one of them gets a
-    // compute unit of its own it is ahead of the tiles, one more and it is behind: hidden 4096, us staged against tiled,
-    // one KV head 448 rows 10.5 / 11.7, two 512 rows 10.9 / 12.4, four 256 rows 10.6 / 12.3 and 300 rows 17.6 / 12.4, eight
-    // 160 rows 18.1 / 12.1.  (One KV head: up to 512 rows; at 1024, 14.0 / 12.5.)  Up to 128 rows and eight KV heads or more it
-    // was taken before this line was drawn and still is.
+    // compute unit of its own it is ahead of the tiles, one more and it is behind: us staged against tiled, eight KV heads at hidden 4096
+    // 64 rows 9.4 / 16.1, 128 11.9 / 16.0, 160 19.4 / 15.9, at 8192 64 15.4 / 28.0, 128 18.7 / 27.7, 160 30.3 / 27.6, at 3072
+    // 128 9.7 / 13.6, 160 15.5 / 13.7; four at 4096 256 11.5 / 15.2, 320 18.8 / 15.3; two 512 10.7 / 12.3; one 512 10.3 / 11.7, 1024 14.0 / 12.5.
+    // Up to 128 rows it is taken whatever the heads.
     if (hidden % 1024 == 0 && (rows <= 128 || (rows <= 512 && 8l * Hkv * ((rows + 31) / 32) <= 256))) return ProjectionForm::kStaged;
     return ProjectionForm::kTiles;
 }

@@ -307,12 +307,14 @@ int choose_prefill_units(const matkv_config& cfg, long tiles_in_batch, long tile
     return (int)std::max<long>(1, std::min<long>(pu, kMaxPrefillUnitsPerInstance));
 }
 
-// Rows of a prefill workgroup's tile.  A step takes about 1.9 us for 64 tokens of a 256-row tile, 2.2 for 128
-// of a 128-row tile (two groups of waves with 64 each), and an instance cut into units leaves its
-// partials, which cost about 3 us of every 128 rows.  The cheaper estimate wins; measured, 128 against 256
-// rows, us per layer at the 8B shape: one 64-row question over 10 000 tokens 28.9 against 33.2, two of them 46.8
-// against 49.3, four 76.5 against 73, one of 100 rows over 3000 tokens 23.3 against 28.4; 70B shape, one of
-// 128 rows over 10 000 tokens 68 against 66, four over 20 000 374 against 345.
+// Rows of a prefill workgroup's tile.  The cheaper estimate wins: 1.9 us a step of 64 tokens of a 256-row tile, 2.2 of 128
+// of a 128-row tile (two groups of waves with 64 each), and about 3 us of every 128 rows for the partials of an instance that
+// is cut.  Measured over plain pages, us per layer 128 against 256 rows.  128 taken: 8B shape, one 64-row question over 10 000 tokens
+// 27.0 against 31.8, two 38.2 against 41.5, one of 100 rows over 3000 21.1 against 25.2.  256 taken: 8B, sixteen of
+// 100 rows over 5000 188.8 against 158.4, 70B, sixteen of 64 rows over 5000 201.8 against 172.5, four of 128 over 20 000 335.7 against 330.0.
+// Where the two are near it takes 256 rows too early by now (a step of 128 takes 1.75 to 2.1 us): 8B, four of 64 rows over 10 000 61.6 against
+// 65.2, sixteen over 5000 102.5 against 113.6, 70B, one of 128 rows over 10 000 54.2 against 57.2; over compressed pages by less (8B 62.9
+// against 63.8, 105.1 against 111.7, 70B 58.8 against 60.1).
 int choose_prefill_tile(const matkv_config& cfg, long tiles128, long tiles256, long most_tokens, long most_pieces) {
     auto cost = [&](long tiles, long rows) {
         const long units = choose_prefill_units(cfg, tiles, rows, most_tokens, most_pieces), step = rows > 128 ? 64 : 128;
@@ -329,7 +331,9 @@ int choose_prefill_tile(const matkv_config& cfg, long tiles128, long tiles256, l
 // cache, whichever is longer - near one another they add up, hence the fourth root; the reading takes longer where
 // the compute units hold unequal numbers of workgroups.  The constants are fitted to measurements at the 3B, 8B and
 // 70B layer shapes (1 to 24 instances of 64 to 30 000 tokens in 1 to 32 units, questions of up to 64 (row, head)
-// rows), which they give within 6.5 % over plain pages and 10 % over compressed ones.  (A step of 128-row tiles over plain
+// rows).  They give the kernels as they are, fold included, within 12 % over plain pages (a launch of 64 tokens 17 %), and the 128-row
+// form over compressed ones up to 26 % too slow, where its reading bounds it: so 64-row tiles are taken for twenty-four questions of 4 rows
+// over 2000 compressed tokens, 41.9 us a layer against 39.8 (70B shape 45.9 against 40.0).  (A step of 128-row tiles over plain
 // pieces that do not fill their blocks takes longer, 2.6 to 3 us: it looks each of them up.)
 // walk_tokens, walk_pieces: of the longest unit (compressed pages: its blocks for its pieces); tile_mb: K and V bytes that the tiles read, in MB.
 double prefill_form_time(int tile_rows, bool codes, long workgroups, long walk_tokens, long walk_pieces, double tile_mb) {
@@ -2040,11 +2044,11 @@ matkv_status matkv_chunk_attn(matkv_ctx* c, int32_t layer, const void* q, const 
     a.prefill = 2; a.rows = n_tokens; a.n_units = 1; a.max_units_inst = 1;
     a.batch = 1; a.total_q = n_tokens; a.row_tiles = 1;
     // 64-row tiles for chunks of up to 512 tokens while all of their workgroups are on the chip at once (two share a
-    // compute unit): the longest walk is at most 8 blocks and a launch's start is shorter.  us, 128-row tiles -> 64-row: 64 tokens
-    // 8.0 -> 4.9 at every shape, 256 tokens 11.2 -> 8.9 (8B) and 11.8 -> 9.4 (70B), 512 tokens 15.5 -> 14.6 and 17.0 -> 16.1
-    // (70B, 512 workgroups; 16.9 in a second run); 600 tokens 16.7 -> 17.7 (8B).  Then 128-row tiles, and 256-row tiles (twice the longest walk) once
-    // they give more workgroups than there are compute units: 8B shape, 1000 tokens (128 workgroups of 256 rows) 35 against
-    // 24 us, 70B, 1000 (256) 38.7 against 33; 8B, 3501 tokens (440) 113 against 137
+    // compute unit): a launch's start is shorter.  Then 128-row tiles, and 256-row tiles (twice the longest walk) once
+    // they give more workgroups than there are compute units.  us with 64 / 128 / 256 rows: 8B shape, 256 tokens 8.8 / 9.2 / 11.7,
+    // 300 10.0 / 9.9, 512 14.2 / 12.0 / 17.1, 1000 26.4 / 18.5 / 27.5, 3501 166 / 110 / 100; 70B, 200 9.0 / 8.3, 256 9.1 / 9.1,
+    // 512 16.1 / 12.1, 1000 37.8 / 25.5 / 29.9, 1300 55.7 / 41.6 / 37.8, 3501 319 / 218 / 196; 3B, 256 8.8 / 9.0, 512 14.1 / 12.0,
+    // 1000 25.6 / 18.0 / 27.0, 3501 126 / 88 / 93.  (Between 300 and 512 tokens the 128-row form has come to be ahead of the one taken.)
     const long chunk_rows = (long)n_tokens * (cfg.n_q_heads / cfg.n_kv_heads);
     auto workgroups = [&](long rows) { return (chunk_rows + rows - 1) / rows * cfg.n_kv_heads; };
     a.tile_rows = n_tokens <= 512 && workgroups(64) <= 512 ? 64 : workgroups(256) <= 256 ? 128 : 256;
