@@ -302,7 +302,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     // ---- the walk ----
     // A block is taken in halves of 32 tokens.  A period of a wave multiplies the scores of half t + 1 (eight matrix
     // instructions), then the output of half t - 1 (eight more), and between these, evenly, forms the weights of half t and finds the
-    // maximum of half t + 1: the vector work of a SIMD's two waves then stands beside their matrix work throughout.
+    // maximum of half t + 1: the vector work of a SIMD's two waves then stands beside their matrix work.  (Counters, four
+    // 70B users over 20 000 tokens: matrix cores at work 60 % of the launch, 54 with a barrier behind each phase, the vector ALU beside them in 45 % of that.)
     // Step i reads K of block i + 1 and V of block i and has one barrier.  It copies block i + AHEAD, K first, and ends when that K has
     // landed and all V before it: all but the youngest NI copies (compressed pages: all that was widened).  One token group
     // (256 rows): tiles of four blocks.  Of plain pages AHEAD = 3 and the copy goes over block i - 1; since K of block i + 2 is there
