@@ -831,8 +831,8 @@ bool even_partition(const matkv_config& cfg, int batch, int n_dunits) {
            sizeof(Unit) * n_dunits + sizeof(SUnit) * n_units <= sizeof(Unit) * (size_t)table_layout(cfg).max_dunits;
 }
 
-// Whether decode launches leave the cache's rows out of the last-level cache.  page_tokens, tail_rows: what they stream of a layer; longest: tokens
-// of the longest workgroup's walk.  A step reads the rows and the projection's weights of all layers, and the next step reads them again.
+// Whether decode launches leave the cache's rows out of the last-level cache.  streamed, tail_rows: the page tokens and tail rows that they walk of a
+// layer, distinct: the page tokens among them that are not the same ones again; longest: tokens of the longest workgroup's walk.  A step reads the rows and the projection's weights of all layers, and the next step reads them again.
 //  - All of it fits: it is found there again, rows are left there.  Past that by a sixteenth, weights fit: rows pass by and the weights stay.
 //    us per layer step, rows left there / passing by: 8B shape, 8 layers and 265 MB 11.0 / 11.3, 12 layers and 300 MB 10.3 / 10.0, 15 layers and
 //    313 MB 9.9 / 9.4; 70B, 7 layers and 264 MB 14.9 / 15.5, 292 MB 15.9 / 16.2, 349 MB 18.4 / 18.1; sixteen 8B users over 5000 tokens 70.0 / 63.0.
@@ -847,16 +847,23 @@ bool even_partition(const matkv_config& cfg, int batch, int n_dunits) {
 //    take as long if all walks were as long as the longest: weights fit, up to 64 -5 %, 64 to 128 -3.5 %, 128 to 160 -1 %, 160 to 192 +1 %, 192 to 224 +4 %, more
 //    +7 %; they exceed it, up to 128 -5 %, 128 to 192 -3 %, 192 to 208 -1 %, 208 to 224 0, more +2 %.  Compressed pages alike.  So 160 and 208 of them.
 //    Attention over 2000 tokens each, one unit per user, 16 layers: one user 22.3 / 30.9, eight 28.4 / 33.5, 17 32.3 / 36.3, 24 38.0 / 38.8.
-// Over 8196 such steps (plain and compressed) the better of the two is taken but for 0.2 % of the time; where all beyond 256 MB passed by it was 1.6 %.
+//  - Pages that several units stream (more users than a tile has rows; units by instance over pages that are shared after all) are found again
+//    within the launch if they are left there.  Time saved by passing by, mean over seeded steps of 2 to 32 users of shared pages where the rest speaks for it, by
+//    tokens walked per distinct one: 1 +5 %, up to 1.06 +3 %, 1.125 +1 %, 1.2 0, 1.3 -1 %, 1.6 -3 %, 3 -6 %, more -10 %; compressed pages 1 +4 %, up to 1.125 +3 %,
+//    1.3 +2 %, 1.6 0, 3 -2 %, more -5 %.  So 9/8.  us per layer, left there / passing by, 4 layers: sixteen 70B users of the same 5000 tokens 20.8 / 26.4, of 5 in 20
+//    chunks 45.8 / 51.7, 24 of 5 in 60 74.1 / 80.1.  Over 18147 such steps the slower of the two is taken for 0.2 % of the time; with the tokens walked for
+//    the distinct ones it was 1.9 %.
+// Over 8196 steps without shared pages (plain and compressed) the better of the two is taken but for 0.2 % of the time; where all beyond 256 MB passed by it was 1.6 %.
 constexpr size_t kStreamedLayerBytes = (size_t)24 << 20, kStreamedCodeBytes = (size_t)7 << 20;
 constexpr int kStreamedWalks = 160, kStreamedWalksFar = 208;
-bool rows_pass_llc(const matkv_config& cfg, size_t page_tokens, size_t tail_rows, size_t longest, int kv_fmt) {
+bool rows_pass_llc(const matkv_config& cfg, size_t distinct, size_t streamed, size_t tail_rows, size_t longest, int kv_fmt) {
+    if (8 * streamed > 9 * distinct) return false;
     const size_t row = 2 * (size_t)cfg.n_kv_heads * cfg.head_dim, esz = cfg.dtype == MATKV_BF16 ? 2 : 4, llc = kLastLevelCacheBytes;
-    const size_t layer = row * (page_tokens * (kv_fmt == MATKV_PAGE_E4M3 ? 1 : esz) + tail_rows * esz);
+    const size_t layer = row * (distinct * (kv_fmt == MATKV_PAGE_E4M3 ? 1 : esz) + tail_rows * esz);
     const size_t weights = row * cfg.hidden * esz * cfg.n_layers;
     if (layer * cfg.n_layers + weights <= llc + llc / 16) return false;
     const double over = weights > llc ? std::min(1.0, (double)(weights - llc) / (double)(llc / 8)) : 0.0;      // 1: nothing of the weights is found again
-    const double walks = (double)cfg.n_kv_heads * (double)(page_tokens + tail_rows) / (double)std::max<size_t>(longest, 1);
+    const double walks = (double)cfg.n_kv_heads * (double)(streamed + tail_rows) / (double)std::max<size_t>(longest, 1);
     return (double)layer > over * (double)(kv_fmt == MATKV_PAGE_E4M3 ? kStreamedCodeBytes : kStreamedLayerBytes) &&
            walks >= kStreamedWalks + over * (kStreamedWalksFar - kStreamedWalks);
 }
@@ -890,16 +897,25 @@ DecodeLayout lay_out_decode(const matkv_config& cfg, const TableLayout& tl, cons
         L.even_built = true;
         L.even = build_even_units(cfg, pages, n_pages, batch, insts, items, n_items, dunits, L.n_dunits, runs, kv_fmt);
     }
-    size_t page_tokens = 0, tail_rows = 0, longest = 0;
+    size_t streamed = 0, tail_rows = 0, longest = 0;
     auto walk = [&](const Unit& u) {
         const size_t tail = u.has_tail ? insts[u.inst].q_len : 0;
-        page_tokens += u.page_tokens; tail_rows += tail;
+        streamed += u.page_tokens; tail_rows += tail;
         longest = std::max(longest, u.page_tokens + tail);
     };
     if (L.even)              for (int u = 0; u < 256 / cfg.n_kv_heads && runs[u].n_users > 0; ++u) walk(runs[u].u);
     else if (L.n_sunits > 0) for (int u = 0; u < L.n_sunits; ++u) walk(sunits[u].u);
     else                     for (int u = 0; u < L.n_dunits; ++u) walk(dunits[u]);
-    L.past_llc = rows_pass_llc(cfg, page_tokens, tail_rows, longest, kv_fmt);
+    if (rows_pass_llc(cfg, streamed, streamed, tail_rows, longest, kv_fmt)) {       // (with fewer distinct ones it is no other without this)
+        std::vector<std::pair<const void*, int>> seen;
+        for (int b = 0; pages && b < batch; ++b)
+            for (int p = 0; p < n_pages[b]; ++p) seen.emplace_back(pages[(size_t)b * cfg.max_pages + p].slot, pages[(size_t)b * cfg.max_pages + p].n_tokens);
+        std::sort(seen.begin(), seen.end());
+        size_t distinct = 0;
+        for (size_t i = 0; i < seen.size(); ++i)
+            if (i == 0 || seen[i].first != seen[i - 1].first) distinct += seen[i].second;
+        L.past_llc = rows_pass_llc(cfg, distinct, streamed, tail_rows, longest, kv_fmt);
+    }
     return L;
 }
 

@@ -217,6 +217,15 @@ def test_decode_streams_only_rows_that_displace_something(mk):
     cfg = mk.make_config(4, 32, 8, 128, 4096, "bf16", 500000.0, 4, 8, 64)
     assert mk.plan_decode_streams(cfg, [[(b, 5000)] for b in range(4)], [32] * 4)
     assert not mk.plan_decode_streams(cfg, [[(0, 5000)]] * 4, [32] * 4)
+    # pages with more users than a tile has rows are walked by several units, which find them in the cache: four users of a page are one unit's
+    # at four heads per KV head, and two units' at eight
+    for model, Hq in (("8b", 32), ("70b", 64)):
+        cfg = mk.make_config(4, Hq, 8, 128, 4096, "bf16", 500000.0, 16, 16, 64)
+        for fmt, n in ((mk.PAGE_PLAIN, 1500), (mk.PAGE_E4M3, 3000)):
+            quads = [[(16 * (b // 4) + i, n) for i in range(12)] for b in range(16)]
+            assert mk.plan_decode_streams(cfg, quads, [32] * 16, fmt) == (Hq == 32)
+            assert mk.plan_decode_streams(cfg, [[(16 * b + i, n) for i in range(3)] for b in range(16)], [32] * 16, fmt)
+    cfg = mk.make_config(4, 32, 8, 128, 4096, "bf16", 500000.0, 4, 8, 64)
     for bad in (([[(0, 0)]], [4]), ([[(-1, 5)]], [4]), ([[(0, 5)]], [0]), ([[(0, 5)]], [65]), ([[(0, 5)]], [4], 7)):
         with pytest.raises(mk.MatKVError):
             mk.plan_decode_streams(cfg, *bad)
