@@ -107,11 +107,10 @@ __device__ __forceinline__ void rope_cs(const RopeEntry& e, float p, float& c, f
 // arriving -> now:
 //   hidden 4096:  1000 rows 26.3 -> 24.0, 1206 rows 30.9 -> 29.2, 3501 rows 66.9 -> 60.6
 //   hidden 8192:  512 rows 36.3 -> 34.5, 1000 rows 49.7 -> 46.5, 1206 rows 62 -> 50, 2000 rows 73 -> 67
-// At 1000 rows of hidden 4096 a launch of 37 800 cycles waits 3800 for its first operands, takes 740 for each of 32 steps (44
+// (and since then by where on the hidden axis workgroups start, see `first`).  At 1000 rows of hidden 4096 a launch of 37 800 cycles waits 3800 for its first operands, takes 740 for each of 32 steps (44
 // bytes a cycle), then 1900 until its partials have left, 2700 to arrive, 3600 to fetch the other's and 1300 for the results (6500,
 // 3500 and 7400 for the last three before).  From the last-level cache 512 rows of hidden 8192 would take 24.7 us.
-// Tried and left out: starting every workgroup at another hidden column (no channel of the L2s is
-// favoured by the power-of-two row strides: no change), an extra wave that touches the weight rows
+// Tried and left out: an extra wave that touches the weight rows
 // some steps ahead (-12 % at 512 rows of hidden 8192, +20 % at 64 rows, nothing at 1000), workgroups that share an operand touching it
 // some steps ahead in turn (-10 % there, +8 to 13 % at 1000 rows and more).
 // (The operands' addresses and sizes come first among the arguments of these kernels: they arrive in registers, and the first operands are
@@ -155,6 +154,17 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(
     const int kv = ct >= Hkv, head = ct - kv * Hkv;
     const int row0 = rt * BM;
     const int nk = Hd / (BK * SK);
+    // The step of the hidden axis at which this workgroup starts; it goes round from there.  A compute unit has 64 KB on their way at the
+    // most, which come at 50 GB/s from HBM and at 108 out of an L2, and workgroups of an XCD that share weight rows and ask
+    // for them at the same step all wait for HBM.  A few steps apart, one of them does and the others find them in the L2 (further
+    // apart they have left it: 256 rows of hidden 8192 27.6 -> 25.6 with 4 steps, 33.5 with 6).  The other XCDs start at other quarters, so that not all ask the
+    // same channels.  us per launch, all at step 0 -> this (weights from HBM, 8 KV heads): hidden 3072 150 rows 13.5 -> 11.3, 3000 38.5 -> 35.6;
+    // 4096 150 15.7 -> 14.2, 512 19.7 -> 17.6, 1000 25.4 -> 23.8, 3501 56.0 -> 51.2; 8192 512 33.8 -> 30.4, 1000 43.6 -> 40.6, 3501 105 -> 97.
+    // Steps from one row tile to the next: 1, 2, 3 and 4 measured, 4096 300 rows (tiles of 64) 17.4, 16.9, 16.7, 16.3, 512 18.3, 18.4, 18.1, 18.7,
+    // 1000 (128) 23.8, 24.5, 25.1, 25.7; 8192 1000 42.2, 40.4, 40.7, 41.6.
+    const int xcd = blockIdx.x & 7;
+    const int first = (SK == 2 ? rt * (MI == 1 ? 4 : MI == 2 ? 3 : nk >= 40 ? 2 : 1) + (xcd >> 1) * (nk / 4)
+                               : (rt >> 1) + (xcd & 3) * nk / 4) % nk;
 
     // LDS row r of the weights -> feature.  Sixteen rows are one operand of a matrix instruction, whose results
     // land in lanes by fours of these rows: the order makes a lane's results of its PB low (and of its PB high) operands features in a row.
@@ -186,7 +196,8 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(
     constexpr int NC = 2 + XW;                                      // copies of a wave per step
     auto copy_one = [&](int ks, int buf, int i) {
         const uint32_t base = lds0 + buf * S::STEP_BYTES + wave * 1024;
-        const size_t k = (size_t)ks * (BK * 2);
+        const int at = ks + first;
+        const size_t k = (size_t)(at >= nk ? at - nk : at) * (BK * 2);
         if (i < 2)                                    dev::dma16(W + k, woff[i], base + BM * BK * 2 + i * 8192);
         else if (XI % 8 == 0 || i - 2 < n_x)          dev::dma16(X + k, xoff[i - 2], base + (i - 2) * 8192);
     };

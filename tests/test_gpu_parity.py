@@ -224,12 +224,14 @@ def test_materialize_hidden_sizes_bf16(hidden, T):
     (64, 33, 2), (128, 200, 2), (192, 300, 2), (320, 129, 8), (512, 256, 8), (512, 257, 8), (512, 513, 8), (512, 769, 8), (512, 1025, 8),
     (512, 1537, 8), (512, 2049, 8), (512, 3073, 8), (512, 4160, 8), (1024, 129, 8), (384, 700, 1), (448, 450, 3)] +
     # narrow projections: the split-axis form up to 256 workgroups, tiles beyond
-    [(1024, 512, 1), (1024, 513, 1), (1024, 449, 2), (1024, 256, 4), (1024, 257, 4), (1024, 131, 6), (3072, 200, 4)])
+    [(1024, 512, 1), (1024, 513, 1), (1024, 449, 2), (1024, 256, 4), (1024, 257, 4), (1024, 131, 6), (3072, 200, 4)] +
+    # workgroups that start behind the last round of copies and go round: two halves of 9, 7, 21, 11 and 40 steps, 19 steps by one
+    [(1152, 150, 8), (896, 300, 8), (2688, 520, 8), (1408, 1000, 8), (5120, 790, 8), (1216, 1000, 8), (1216, 500, 3)])
 def test_materialize_tile_heights(hidden, T, Hkv):
     """Tiled projection: every tile height of both forms (two workgroups per tile: 32, 64, 96, 128
     rows; one: 96, 128, 192, 256) just past the row count where the one before ends, hidden axes of one
-    step, of fewer steps than are in flight, and of an odd number of steps, and column tile counts that
-    are no multiple of four."""
+    step, of fewer steps than are in flight, and of an odd number of steps, column tile counts that
+    are no multiple of four, and starts along the hidden axis of every workgroup that shares an operand."""
     case = Case("bf16-tiles", n_layers=1, Hq=Hkv, Hkv=Hkv, D=128, hidden=hidden, dtype="bf16",
                 chunk_lens={0: 8}, retrieved=[[0]], q_lens=[1], steps=0, rope_base=500000.0, scale=1.0 / 4.0)
     from workload import normal, to_f64
