@@ -13,7 +13,7 @@
 //
 // What bounds it.  A step of 64 tokens needs of a SIMD 2 x 32 matrix instructions and 2 x 8 small ones (2200 cycles), of its
 // vector ALU about 1300 cycles (an exponential takes 8), and of the compute unit's LDS 2 x 8 x 16 KB at 256 bytes a cycle (1024
-// cycles) and the copies' 256.  On long walks the chip's power limit sets the pace: at 3290 cycles a step the clock is
+// cycles) and the copies' 256.  On long walks the chip's power limit sets the pace: at 3290 cycles a step (3170 by now) the clock is
 // 1.68 GHz (matrix instructions alone on such data would run at 1.7), and a large library GEMM reaches 1385 TFLOP/s here.  Hence:
 //  - K and V go from global memory straight into LDS (dma16), into unpadded rows whose 16-byte pieces
 //    are permuted so that operand reads and transposing reads meet no bank conflict; up to three blocks
@@ -30,6 +30,11 @@
 // only: every LDS read 1.94, the exponentials 1.90, the copies 1.80.  Tried: the weights formed beside the scores' matrix
 // instructions only 3870 cycles, all copies of a step at once 3900, the waves of a SIMD taking turns at the higher priority
 // 3360 against 3390, scalar work ahead of the first matrix instructions instead of between the periods 3390 against 3250.
+// Of a step's 3275 cycles between two periods' matrix instructions 180 went to the maxima, 190 to the row sums, 130 to the copies, 130 to
+// finding the next block and 60 to whether it is ragged (each left out in turn).  What is rare stands out of line, whether a block is ragged is
+// found with the block and the maxima take three instructions less: 3170, and 0.3 to 0.7 % per chunk and question pass, nothing where the power
+// limit sets the pace (70B, 20 000 tokens: 1.87 -> 1.76 GHz).  Tried: the maxima, the operands' addresses and the search for the next block among
+// the matrix instructions (3190 to 3230; 128-row tiles 3430 -> 3590), K copied a step earlier (no change), whole blocks on a path of their own (3270).
 // The last point: chunk passes 407 -> 385, 319 -> 301, 654 -> 637, question passes 687 -> 681, 1439 -> 1445, 318 -> 313.
 //
 // An instance whose cache is one unit gets its output rows directly; otherwise every unit leaves an
@@ -68,6 +73,7 @@ __device__ __forceinline__ s16x4 lds_read_tr(const char* p) {
 struct BlockDesc {
     int n;              // token rows; 0: none that a row of this wave may see, -1: no group of the workgroup has a block in this step
     int t0;             // tail row of the block's first token; far below every row for a page
+    bool ragged;        // fewer than a whole block, or past what the wave's first row may see
     float sk, sv;       // scales of a compressed page's codes
 };
 
@@ -203,12 +209,12 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     Source src;
     src.k = wk.k; src.v = wk.v; src.n = 1; src.codes = F8 && wk.row_bytes == D;
     auto next_step = [&](BlockDesc& d) {
-        d.n = -1; d.t0 = kPageT0; d.sk = 1.f; d.sv = 1.f;
+        d.n = -1; d.t0 = kPageT0; d.sk = 1.f; d.sv = 1.f; d.ragged = true;
         src.n = F8 ? 0 : 1;
         if (F8) src.codes = false;
 #pragma unroll
         for (int g = 0; g < TS; ++g) {
-            while (wk.left <= 0 && wk.item_i + 1 < unit.n_items) {
+            while (__builtin_expect(wk.left <= 0 && wk.item_i + 1 < unit.n_items, 0)) {
                 ++wk.item_i;
                 set_item(ahead.it.base, ahead.it.page_tokens, ahead.it.tok0, ahead.it.ntok);
                 if (F8) { wk.sk = ahead.sk; wk.sv = ahead.sv; }
@@ -221,6 +227,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
                 src.k = wk.k; src.v = wk.v; src.n = n; src.codes = F8 && wk.row_bytes == D;
                 d.n = wave_live && wk.t0 < vis_max ? n : 0;
                 d.t0 = wk.t0;
+                d.ragged = n != TB || d.t0 + n > vis_min;
                 if (F8) {
                     d.sk = wk.sk; d.sv = wk.sv;
                     if (TS == 2) asm volatile("" : "+v"(d.sk), "+v"(d.sv));      // (in vector registers: the scalar ones are all taken)
@@ -378,7 +385,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     // Half h of block d's scores.  masked: the block is ragged, or lies in the tail and reaches past what the wave's first
     // row may see (per-row causal limit); otherwise all rows see all of it
     auto mask = [&](f32x16& st, const BlockDesc& d, int h) {
-        if (d.n != TB || d.t0 + d.n > vis_min) {            // wave-uniform
+        if (__builtin_expect(d.ragged, 0)) {            // wave-uniform
             const int limit = min(d.n, vis - d.t0) - 4 * g2 - 32 * h;
 #pragma unroll
             for (int i = 0; i < 16; ++i) st[i] = 8 * (i / 4) + i % 4 < limit ? st[i] : kNegBig;
@@ -390,14 +397,17 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
     // formed against the old reference, has been added to them.
     float alpha = 1.f;
     bool moved = false;               // (wave-uniform)
+    auto max2 = [](float x, float y) { float m; asm("v_max_f32 %0, %1, %2" : "=v"(m) : "v"(x), "v"(y)); return m; };     // (fmaxf makes both quiet first)
+    float mlim = kNegBig + lazy_raw;  // scores above it move the reference
     auto take_max = [&](float mx, const BlockDesc& d) {
-        mx = fmaxf(mx, lane_xor(mx, 32, lane));
+        const u32x2 both = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false));
+        mx = max2(__uint_as_float(both.x), __uint_as_float(both.y));
         if (F8) mx = mx > 0.5f * kNegBig ? mx * d.sk : kNegBig;     // into the units of the reference
-        const bool moves = mx > mrow + lazy_raw;
+        const bool moves = mx > mlim;
         moved = __builtin_amdgcn_ballot_w64(moves) != 0;
-        if (moved) {
+        if (__builtin_expect(moved, 0)) {
             alpha = moves ? fast_exp2((mrow - mx) * sc) : 1.0f;
-            if (moves) mrow = mx;
+            if (moves) { mrow = mx; mlim = mx + lazy_raw; }
             // a row that has seen no key yet keeps the floor as its reference; its masked
             // scores must still come out as weight 0, not 2^0
             if (!F8) nmc = mrow > 0.5f * kNegBig ? -mrow * sc : 0.f;
@@ -405,7 +415,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(
         if (F8) nmc = (mrow > 0.5f * kNegBig ? -mrow * sc : 0.f) + (__builtin_amdgcn_frexp_expf(d.sv) - 1.0f);
     };
     auto rescale = [&]() {
-        if (moved) {
+        if (__builtin_expect(moved, 0)) {
             ol[0] *= alpha;
 #pragma unroll
             for (int t = 0; t < 4; ++t)
