@@ -2059,15 +2059,16 @@ matkv_status matkv_chunk_attn(matkv_ctx* c, int32_t layer, const void* q, const 
     a.max_tail = n_tokens;
     a.prefill = 2; a.rows = n_tokens; a.n_units = 1; a.max_units_inst = 1;
     a.batch = 1; a.total_q = n_tokens; a.row_tiles = 1;
-    // 64-row tiles for chunks of up to 512 tokens while all of their workgroups are on the chip at once (two share a
-    // compute unit): a launch's start is shorter.  Then 128-row tiles, and 256-row tiles (twice the longest walk) once
-    // they give more workgroups than there are compute units.  us with 64 / 128 / 256 rows: 8B shape, 256 tokens 8.8 / 9.2 / 11.7,
-    // 300 10.0 / 9.9, 512 14.2 / 12.0 / 17.1, 1000 26.4 / 18.5 / 27.5, 3501 166 / 110 / 100; 70B, 200 9.0 / 8.3, 256 9.1 / 9.1,
-    // 512 16.1 / 12.1, 1000 37.8 / 25.5 / 29.9, 1300 55.7 / 41.6 / 37.8, 3501 319 / 218 / 196; 3B, 256 8.8 / 9.0, 512 14.1 / 12.0,
-    // 1000 25.6 / 18.0 / 27.0, 3501 126 / 88 / 93.  (Between 300 and 512 tokens the 128-row form has come to be ahead of the one taken.)
+    // 64-row tiles for the shortest chunks while all of their workgroups are on the chip at once (two share a compute unit): a
+    // launch's start is shorter.  Then 128-row tiles, and 256-row tiles (twice the longest walk) once they give more workgroups than there are
+    // compute units - a good third more where the walks are long, beside which a workgroup's start is little.  us with 64 / 128 / 256 rows: 8B shape,
+    // 192 tokens 7.8 / 8.5, 256 9.0 / 9.2, 280 10.3 / 9.7, 512 14.6 / 12.2 / 17.2, 1000 27.4 / 19.3 / 28.9, 2100 70 / 51.0 / 56.3, 2600 100 / 72.1 / 74.1, 3000
+    // 127 / 89.2 / 87.9; 3B 256 9.1 / 9.1, 280 10.3 / 9.6, 512 14.3 / 12.1, 2800 92 / 63.8 / 73.9, 3501 129 / 92.4 / 96.2, 4000 167 / 114.2 / 114.8; 70B 192 8.1 / 8.5,
+    // 200 9.2 / 8.6, 256 9.5 / 9.2, 512 17.1 / 13.7, 1024 43.8 / 29.4 / 33.0, 1060 43.9 / 35.4 / 33.7, 1300 58 / 44.6 / 41.2; one to four KV heads as 8B.
     const long chunk_rows = (long)n_tokens * (cfg.n_q_heads / cfg.n_kv_heads);
     auto workgroups = [&](long rows) { return (chunk_rows + rows - 1) / rows * cfg.n_kv_heads; };
-    a.tile_rows = n_tokens <= 512 && workgroups(64) <= 512 ? 64 : workgroups(256) <= 256 ? 128 : 256;
+    const bool shortest = n_tokens <= 192 || (n_tokens <= 256 && chunk_rows <= 1024);
+    a.tile_rows = shortest && workgroups(64) <= 512 ? 64 : workgroups(256) <= (n_tokens >= 2000 ? 352 : 256) ? 128 : 256;
     a.scale_log2e = c->scale_log2e;
     a.out_f32 = cfg.dtype == MATKV_BF16 && cfg.out_f32;
     const bool tiles = attn_prefill_supported(a, cfg.dtype);

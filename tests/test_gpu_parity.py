@@ -1375,8 +1375,10 @@ def test_attention_refuses_a_table_whose_slot_is_being_reloaded():
     ("chunk-g1", 2, 2, 128, "bf16", [130], None),
     ("chunk-g2", 4, 2, 128, "bf16", [100, 129], None),
     ("chunk-g8", 8, 1, 128, "bf16", [77, 300], None),
-    # 64-row tiles up to 512 tokens (ragged rows of a wave, of a tile; full tiles), 128-row tiles from 513 on
+    # 64-row tiles up to 256 tokens, of groups of 8 to 192 (ragged rows of a wave, of a tile; full tiles), 128-row tiles beyond
     ("chunk-g3", 6, 2, 128, "bf16", [5, 6, 85, 86, 511, 512, 513], None),
+    ("chunk-g4-line", 8, 2, 128, "bf16", [255, 256, 257, 300], None),
+    ("chunk-g8-line", 16, 2, 128, "bf16", [191, 192, 193, 256], None),
     ("chunk-g8-tiles", 16, 2, 128, "bf16", [8, 9, 16, 505, 520, 700], None),
     ("chunk-g1-tiles", 2, 2, 128, "bf16", [63, 64, 65, 512, 640], None),
     ("chunk-f32", 4, 2, 64, "f32", [50, 9], 56),                      # row-per-workgroup kernel
@@ -1473,6 +1475,9 @@ def test_chunk_attn_arguments_and_workspace_limit():
     (3501, 32, 8, [0, 63, 64, 1791, 3391, 3392, 3455, 3456, 3457, 3499, 3500]),
     (1100, 64, 8, [0, 31, 32, 600, 1055, 1056, 1087, 1088, 1089, 1098, 1099]),
     (2901, 24, 8, [0, 84, 85, 86, 1500, 2815, 2816, 2879, 2880, 2881, 2899, 2900]),
+    # 128-row tiles in more than one round of workgroups, and the first length past them
+    (2816, 32, 8, [0, 31, 32, 63, 64, 127, 128, 1500, 2687, 2688, 2783, 2784, 2815]),
+    (2817, 32, 8, [0, 63, 64, 1500, 2751, 2752, 2815, 2816]),
 ])
 def test_full_size_chunk_attention(L, Hq, Hkv, rows):
     """A chunk's own attention at the shapes bench.py times (Llama-3-8B / 70B heads, D 128):
