@@ -13,11 +13,13 @@
 #include <algorithm>
 #include <atomic>
 #include <condition_variable>
+#include <functional>
 #include <list>
 #include <mutex>
 #include <exception>
 #include <new>
 #include <numeric>
+#include <queue>
 #include <thread>
 #include <unordered_map>
 #include <vector>
@@ -354,6 +356,62 @@ double prefill_form_time(int tile_rows, bool codes, long workgroups, long walk_t
     return start + pow(pow(walk, 4) + pow(read, 4), 0.25);
 }
 
+// Another form and cut of a question prefill than the two rules above choose, where an estimate has it ahead by more than a tie: 128- or
+// 256-row tiles, every cache in up to 32 units.  What the rules miss: a cut of a cache of a few hundred tokens costs more in partials and their
+// fold than it saves, several rounds of workgroups want another number of them, and the line between the heights moves with how the tiles fill.
+// A workgroup takes a start and its steps, a step of a 256-row tile with at most 128 rows less; the compute units of a KV head take them in launch
+// order; beside the walk the tiles' K and V are read (near one another they add up, hence the fourth root), and partials are written, read
+// and folded.  Constants fitted to 9700 timings of 2500 seeded tables (3B, 8B and 70B shape, 1 to 24 users of 32 to 50 000 tokens, 1- to 260-row questions), 7
+// to 9 % apart from them.  Taken where it has a launch ahead by 6 % and 1.5 us, for questions of more than 64 (row, head) rows over 640 tokens and
+// more.  Of 1200 other tables of those shapes 10 % are laid out another way, which takes 1/1.11 of the time over plain pages, 1/1.08 compressed, and
+// of 2000 tables with 1 to 16 KV heads and 1 to 8 query heads to each 8 %, 1/1.11 and 1/1.08; six of those 158 were slower by 3 to 8 %, all of 12 to 23 us, when
+// 6 % were enough.  us a layer: 8B shape, two users of 145 rows over 631 tokens 22.4 -> 16.3, compressed, eleven of up to 83 rows over 10 800 345 -> 286;
+// 70B, eleven of 22 rows over 762 26.0 -> 19.3; 3B, compressed, nineteen of up to 42 rows over 27 000 501 -> 410.
+// Shorter caches would gain more and stay with the rules: 8B shape, 32 rows, in units -> uncut, sixteen users of 500 tokens 28.4 -> 17.5, one of 300 13.4 -> 11.8.
+struct PrefillShape {           // of an instance
+    long rows, tokens, pieces;  // (question row, query head of one KV head) rows; cache and question; pages and tail
+};
+double prefill_tiles_time(const std::vector<PrefillShape>& shapes, int Hkv, bool codes, int tile_rows, int most_units, double worth) {
+    struct Constants { double start, workgroup, step, half_step, mb_once, mb_tile, mb_partial, fold; };
+    static const Constants kForms[2][2] = {{{3.2, 3.1, 1.55, 1.55, 0.08, 0.126, 0.46, 3.6}, {2.2, 3.6, 1.46, 1.06, 0.02, 0.20, 0.39, 4.5}},
+                                           {{3.0, 3.3, 2.0, 2.0, 0.10, 0.20, 0.40, 4.3}, {2.9, 2.7, 1.75, 1.30, 0.02, 0.32, 0.38, 4.9}}};
+    const Constants& k = kForms[codes][tile_rows > 128];
+    const int slots = std::max(1, std::min(256, 256 / Hkv));
+    const double row_mb = Hkv * (codes ? 256e-6 : 512e-6);
+    struct Job { double us; long n; int tile; };
+    std::vector<Job> jobs;
+    double total = 0, longest = 0, read = 0, partials = 0;
+    long n_jobs = 0;
+    bool cut = false;
+    for (const PrefillShape& s : shapes) {
+        const long u = std::max<long>(1, std::min<long>(most_units, s.tokens / 64)), tiles = (s.rows + tile_rows - 1) / tile_rows;
+        const double pieces = (double)s.pieces / u + 1.0 - 1.0 / u, blocks = std::max((double)s.tokens / u / 64 + 0.5 * pieces, pieces);
+        const double steps = ceil(tile_rows > 128 ? blocks : 0.5 * blocks);
+        for (long t = 0; t < tiles; ++t) {
+            const bool half = tile_rows > 128 && s.rows - t * tile_rows <= 128;
+            const double us = k.workgroup + steps * (half ? k.half_step : k.step);
+            jobs.push_back({us, u, (int)t});
+            total += us * u; longest = std::max(longest, us); n_jobs += u;
+        }
+        read += row_mb * s.tokens * (k.mb_once + k.mb_tile * tiles);
+        if (u > 1) { cut = true; partials += (double)s.rows * Hkv * u * 528e-6; }
+    }
+    const double other = k.start + (cut ? k.fold + partials * k.mb_partial : 0.0), read4 = pow(read, 4);
+    auto launch = [&](double walk) { return other + pow(pow(walk, 4) + read4, 0.25); };
+    const double least = launch(std::max(longest, total / slots));
+    if (n_jobs <= slots || least >= worth) return least;
+    std::stable_sort(jobs.begin(), jobs.end(), [](const Job& a, const Job& b) { return a.tile < b.tile; });
+    std::priority_queue<double, std::vector<double>, std::greater<double>> busy(std::greater<double>(), std::vector<double>(slots, 0.0));
+    double end = 0;
+    for (const Job& j : jobs)
+        for (long i = 0; i < j.n; ++i) {
+            const double t = busy.top() + j.us;
+            busy.pop(); busy.push(t);
+            end = std::max(end, t);
+        }
+    return launch(end);
+}
+
 // Cuts one instance's cache (its pages in order, then its tail) into n_units runs of nearly
 // equal token counts, in 8-token granules.  A run is a list of items (page pieces); the tail
 // is one item and belongs to the last run.  Appends to items / units; returns the number of
@@ -442,6 +500,27 @@ PrefillLayout lay_out_prefill(const matkv_config& cfg, const matkv_page* pages, 
     L.tile_rows = choose_prefill_tile(cfg, tiles(128), tiles(256), most_tokens, cut_pieces ? most_pieces : 0);
     const long n_tiles = tiles(L.tile_rows);
     const int tall = L.tile_rows, items0 = *n_items;
+    int other_units = 0;                                // of every cache at most, where the rules' form and cut are not taken
+    if (cfg.dtype == MATKV_BF16 && cfg.head_dim == 128 && group_size_built(g) && most_rows > 64 && most_tokens >= 640 && most_pieces <= kMaxPrefillItemsPerUnit && tiles(128) <= 330) {
+        std::vector<PrefillShape> shapes(batch);
+        int rule_units = 1;
+        for (int b = 0; b < batch; ++b) {
+            shapes[b] = {(long)q_len[b] * g, tokens[b], (long)n_pages[b] + 1};
+            rule_units = std::max(rule_units, choose_prefill_units(cfg, n_tiles, tall, tokens[b], n_pages[b] + 1));
+        }
+        const double by_rule = prefill_tiles_time(shapes, cfg.n_kv_heads, codes, tall, rule_units, 1e30);
+        double best = std::min(0.94 * by_rule, by_rule - 1.5);
+        for (int rows : {128, 256}) {
+            const long one_round = 256 / std::max<long>(1, tiles(rows) * cfg.n_kv_heads);
+            long before = 0;
+            for (long u : {1l, 2l, 3l, 4l, 5l, 6l, 8l, 10l, 12l, 16l, 20l, 24l, 32l, std::min<long>(one_round, kMaxPrefillUnitsPerInstance)}) {
+                if (u < 1 || (u > 1 && u > most_tokens / 64) || u == before || tiles(rows) * u > 330) continue;
+                before = u;
+                const double us = prefill_tiles_time(shapes, cfg.n_kv_heads, codes, rows, (int)u, best);
+                if (us < best) { best = us; L.tile_rows = rows; other_units = (int)u; }
+            }
+        }
+    }
     long walk_tokens = 0, walk_blocks = 0;              // of the longest unit; blocks of 64 tokens, none across two items
     auto cut = [&](auto units_of) {                     // units_of(b): units of instance b
         *n_items = items0;
@@ -461,7 +540,10 @@ PrefillLayout lay_out_prefill(const matkv_config& cfg, const matkv_page* pages, 
             }
         }
     };
-    auto units_of = [&](int b) { return choose_prefill_units(cfg, n_tiles, tall, tokens[b], cut_pieces ? n_pages[b] + 1 : 0); };
+    auto units_of = [&](int b) {
+        if (other_units) return (int)std::max<long>(1, std::min<long>(other_units, tokens[b] / 64));
+        return choose_prefill_units(cfg, n_tiles, tall, tokens[b], cut_pieces ? n_pages[b] + 1 : 0);
+    };
     cut(units_of);
     // Questions of at most 64 (row, head) rows: 64-row tiles over the same units where they are estimated to be faster
     // by more than a tie.  8B shape, us per layer with 128-row tiles -> 64-row tiles: four 1-row questions over 3000

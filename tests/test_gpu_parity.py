@@ -530,6 +530,26 @@ def test_prefill_of_many_short_caches_uncut(q_len):
     _attention_parity(case, instances=[0, 1, 7, 14, 15])
 
 
+@pytest.mark.parametrize("Hq,Hkv,batch,lens,q_len,compressed,plan", [
+    (32, 8, 6, [640], 33, False, (128, 1)),             # uncut, two tiles a user, the second of four rows
+    (32, 8, 2, [1500], 64, False, (128, 5)),
+    (12, 4, 3, [701], 100, True, (128, 4)),
+    (8, 2, 1, [350, 351], 17, True, (128, 10)),         # units of a block and a bit
+    (32, 8, 3, [700, 801], 100, False, (128, 2)),
+    (24, 8, 6, [1500], 64, False, (128, 1)),            # 128-row tiles in two rounds of workgroups
+    (64, 8, 17, [640], 100, True, (256, 1)),            # 256-row tiles in more
+    (16, 8, 17, [4000], 33, True, (128, 3)),            # units in two rounds
+    (8, 8, 17, [3000], 130, True, (256, 3)),
+])
+def test_prefill_layout_by_estimate(Hq, Hkv, batch, lens, q_len, compressed, plan):
+    """Questions of more than 64 (row, head) rows over caches of 640 tokens and more whose form and cut the estimate of the launch's
+    time decides, against the oracle: the first, the middle and the last user."""
+    case = Case("prefill-estimate", n_layers=1, Hq=Hq, Hkv=Hkv, D=128, hidden=64, dtype="bf16", chunk_lens=dict(enumerate(lens)),
+                retrieved=[list(range(len(lens)))] * batch, q_lens=[q_len] * batch, steps=1, scale=0.5, compressed=compressed)
+    assert _prefill_form(case) == (plan[0], [plan[1]] * batch)
+    _attention_parity(case, instances=sorted({0, batch // 2, batch - 1}))
+
+
 @pytest.mark.parametrize("form,Hq,Hkv,retrieved,q_lens,compressed", [
     (64, 16, 4, [[0, 1], [2, 3], [4], []], [16, 9, 5, 7], False),
     (128, 64, 8, [[0, 1], [2, 3], [4] * 11], [33, 17, 9], False),        # two token groups, 5 units each
