@@ -289,8 +289,19 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(
     } else {
         half_step(f0, f1, 0, 1, 0, 0, C0{}, C0{});
     }
-    for (;; ++ks) {                                                 // nothing more to ask for
-        dev::dma_wait<0>();
+    // Nothing more to ask for: the last steps are multiplied as they arrive.  (With all of them waited for at first half a microsecond of
+    // multiplying stood alone at the end.)
+    constexpr bool DRAWN = SK == 2 && MI >= 4;
+    int drawn = 0;
+    int32_t* const counter = a.ws_counters + (size_t)(rt * nct + ct) * kDecodeCounterStride + wave;
+    if (DRAWN && lane == 0) drawn = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // (see below)
+    auto wait_left = [&](auto self, int left, auto steps_tag) -> void {
+        constexpr int K = decltype(steps_tag)::value;
+        if (left >= K || K == 0) wait_steps(steps_tag);         // (what was drawn counts as one more copy: waited for a little early)
+        else if constexpr (K > 0) self(self, left, std::integral_constant<int, K - 1>{});
+    };
+    for (;; ++ks) {
+        wait_left(wait_left, nk - 2 - ks, std::integral_constant<int, NBUF - 2>{});
         lds_barrier();
         buf = buf + 1 == NBUF ? 0 : buf + 1;
         half_step(f1, f0, buf, 0, 0, 0, C0{}, C0{});                // (past the end: not used)
@@ -299,22 +310,44 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(
     }
     // From here on a wave is on its own.
     if constexpr (SK == 2) {
-        // Both waves that hold a sum's halves leave theirs in the workspace (past the L2s, which are not coherent), and
-        // the one that arrives second, which finds the other's complete, goes on.  16 bytes a lane (in 8-byte pieces before: chunk passes of 1000 tokens 397 -> 393 us,
-        // 311 -> 309 at hidden 8192).
+        // One of the two waves that hold a sum's halves leaves its half in the workspace, past the L2s, which are not coherent, 16 bytes a lane,
+        // and the other goes on with both.  Tiles of up to 96 rows: both leave theirs, and the one that arrives second goes on.  Taller ones: the one that
+        // drew first, some steps ago, leaves its half, raises the counter once more and is done; the other waits for that.  It waits
+        // for a wave that has started and waits for nobody, so the wait ends whatever else the chip does.  That spares it its own stores and a trip
+        // to the counter, and the memory half of the writes, for a trip more where both end at once: us per launch, both leave theirs -> one does, hidden
+        // 4096 150 rows (tiles of 32) 14.2 -> 15.6, 300 (64) 16.6 -> 17.2, 512 (64) 18.2 -> 18.6, 1000 (128) 24.2 -> 24.0; hidden 8192 1000 rows 40.6 -> 39.2, 1500 (192)
+        // 52.0 -> 50.0, 2048 (256) 64.2 -> 61.8.  (In 8-byte pieces chunk passes of 1000 tokens took 397 us for 393, 311 for 309 at hidden 8192.)
         constexpr int NP = XB * 2 * PB;
         const int tile = rt * nct + ct;
-        float* const mine = a.ws_partials + ((size_t)(tile * SK + part) * 8 + wave) * (BM * 16);
-        const float* const theirs = a.ws_partials + ((size_t)(tile * SK + (part ^ 1)) * 8 + wave) * (BM * 16);
+        float* const halves = a.ws_partials + (size_t)tile * SK * 8 * (BM * 16);
+        auto leave = [&](float* to) {
 #pragma unroll
-        for (int i = 0; i < NP; ++i) {
-            const f32x4& v = acc[i / (2 * PB)][i % (2 * PB)];
-            dev::st_agent4(mine, i * 1024 + lane * 16, __builtin_bit_cast(uint4, v));
+            for (int i = 0; i < NP; ++i) {
+                const f32x4& v = acc[i / (2 * PB)][i % (2 * PB)];
+                dev::st_agent4(to, i * 1024 + lane * 16, __builtin_bit_cast(uint4, v));
+            }
+        };
+        int from = part ^ 1;
+        if constexpr (DRAWN) {
+            from = 0;
+            if (__builtin_amdgcn_readfirstlane(drawn) == 0) {
+                leave(halves + (size_t)wave * (BM * 16));
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_s_waitcnt(0);                      // (acknowledged)
+                if (lane == 0) __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return;
+            }
+            while (__builtin_amdgcn_readfirstlane(__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) < 3) __builtin_amdgcn_s_sleep(1);
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        } else {
+            leave(halves + (size_t)(part * 8 + wave) * (BM * 16));
+            if (!dev::wave_arrives_last(counter, SK)) return;
         }
-        if (!dev::wave_arrives_last(a.ws_counters + (size_t)tile * kDecodeCounterStride + wave, SK)) return;
+        const float* const theirs = halves + (size_t)(from * 8 + wave) * (BM * 16);
         float4 o[NP];
 #pragma unroll
         for (int i = 0; i < NP; ++i) o[i] = dev::ld_agent4(theirs, i * 1024 + lane * 16);
+        if (DRAWN && lane == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);     // (ready for the next launch)
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
             f32x4& v = acc[i / (2 * PB)][i % (2 * PB)];
