@@ -410,16 +410,21 @@ hipError_t launch_tile(const MaterializeArgs& a, int total_rows, hipStream_t s) 
 // Tile height.  One workgroup fills a compute unit's LDS, a launch is as long as its slowest
 // compute unit, and a workgroup's time grows slower than its height: so the smallest height that gives no compute unit two
 // workgroups, hidden axis halved while that holds.  Up to 128 rows two workgroups per tile are ahead at every width; taller
-// tiles leave the chip fewer bytes to fetch, but more partials to exchange, and pay from hidden 8192 on (us, one workgroup per tile
-// of fewer rows -> two per taller tile: hidden 8192 1206 rows 59.9 -> 50.3, 2000 rows 71.0 -> 66.7; hidden 4096 1206 rows 29.7 -> 30.3,
-// 2000 rows 39.0 -> 40.7).  Beyond one full round the height with the smallest rounds x (4 + MI), which
-// is what the times follow (hidden 4096, tiles of 128 / 160 / 192 / 256 rows: 2500 rows 72 / 47 / 49 / 56 us, 3501 rows 76 / 86 / 94 / 58).
+// tiles leave the chip fewer bytes to fetch, but more partials to exchange, and pay from some hidden size on (us, one workgroup per tile
+// of fewer rows -> two per taller tile, before only one of the two left its half; 160 and 192 rows: hidden 2048 1050 rows 18.6 -> 19.5, 1500 18.7 -> 20.6, hidden 2560
+// 1206 23.4 -> 22.3, hidden 3072 1050 26.4 -> 23.1, hidden 4096 1050 32.4 -> 29.1, 1500 31.7 -> 30.3, hidden 5120 1206 41.6 -> 33.9, hidden 6144 1500 47.4 -> 41.3; since then
+// a chunk pass of 1050 tokens (8B, four layers) 207 -> 191, of 1300 219 -> 212; 256 rows: hidden 4096 1700
+// 31.7 -> 34.8, hidden 5120 1800 41.9 -> 44.4, 2048 48.0 -> 45.6, hidden 6144 2000 52.4 -> 52.0, hidden 8192 2000 71.0 -> 66.7 when it was drawn).  Behind the attention of a question pass, which
+// streams the cache over the partials, the taller split costs more than it gives below hidden 8192: passes of four layers, sixteen 8B users 657 -> 674, twelve 3B users of
+// 100 rows 421 -> 438 (one card of several: 419 -> 408); 70B, split against not, sixteen of 100 rows 1046 against 1088.  Beyond one full round the
+// height with the smallest rounds x (4 + MI), which is what the times follow (hidden 4096, tiles of 128 / 160 / 192 / 256 rows: 2500 rows 72 / 47 / 49 / 56 us, 3501
+// rows 76 / 86 / 94 / 58).
 hipError_t launch_tiled(const MaterializeArgs& a, int total_rows, hipStream_t s) {
     const int nct = 2 * a.Hkv;
     auto groups = [&](int mi) { return nct * ((total_rows + 32 * mi - 1) / (32 * mi)); };
     auto halved = [&](int mi) {
         const int64_t tiles = groups(mi);
-        return (a.Hd % (2 * BK)) == 0 && tiles * 2 <= 256 && (mi <= 4 || a.Hd >= kTallSplitHidden) && a.ws_partials &&
+        return (a.Hd % (2 * BK)) == 0 && tiles * 2 <= 256 && 32 * mi <= most_split_rows(a.Hd, a.table != nullptr) && a.ws_partials &&
                tiles * 2 * (32 * mi) * D <= a.ws_partial_floats && tiles * kDecodeCounterStride <= a.ws_n_counters;
     };
     if (halved(1)) return launch_tile<1, 4, 2>(a, total_rows, s);

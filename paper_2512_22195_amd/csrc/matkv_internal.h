@@ -125,7 +125,8 @@ constexpr size_t kLastLevelCacheBytes = (size_t)256 << 20;
 
 inline int max_q_rows(const matkv_config& c) { return c.max_tail_tokens; }
 constexpr int kSplitTiles = 128;    // half the compute units: two workgroups per tile
-constexpr int kTallSplitHidden = 8192;      // from here on tiles of more than 128 rows are split as well
+// Rows of the tallest projection tile that is split, of a chunk's rows or a question's (materialize_mfma.hip).
+inline int most_split_rows(int hidden, bool question) { return hidden >= 8192 ? 256 : hidden >= 2560 && !question ? 192 : 128; }
 
 inline WorkspaceLayout workspace_layout(const matkv_config& c) {
     WorkspaceLayout W;
@@ -138,8 +139,7 @@ inline WorkspaceLayout workspace_layout(const matkv_config& c) {
     // back at zero when its launch ends)
     W.n_counters = (size_t)c.max_batch * c.n_kv_heads * (size_t)std::max(max_q_rows(c), kDecodeCounterStride);
     // (bf16, head_dim 128: the projection GEMM may split the hidden axis over two workgroups per
-    // tile, up to kSplitTiles tiles of up to 128 x 128 - from hidden 8192 on, 256 x 128: a counter line and
-    // two fp32 partial tiles each)
+    // tile, up to kSplitTiles tiles of up to most_split_rows x 128: a counter line and two fp32 partial tiles each)
     const bool gemm_split = c.dtype == MATKV_BF16 && c.head_dim == 128;
     if (gemm_split) W.n_counters = std::max(W.n_counters, (size_t)kSplitTiles * kDecodeCounterStride);
     o += ((W.n_counters * sizeof(int32_t)) + 255) & ~(size_t)255;
@@ -148,7 +148,7 @@ inline WorkspaceLayout workspace_layout(const matkv_config& c) {
     size_t dec = (size_t)c.max_batch * kMaxDecodeUnitsPerInstance * stride;
     size_t pre = (size_t)c.max_batch * kMaxPrefillUnitsPerInstance * (size_t)max_q_rows(c) * stride;
     W.partial_floats = dec > pre ? dec : pre;
-    if (gemm_split) W.partial_floats = std::max(W.partial_floats, (size_t)kSplitTiles * 2 * (c.hidden >= kTallSplitHidden ? 256 : 128) * 128);
+    if (gemm_split) W.partial_floats = std::max(W.partial_floats, (size_t)kSplitTiles * 2 * most_split_rows(c.hidden, false) * 128);
     o += W.partial_floats * sizeof(float);
     W.bytes = (o + 255) & ~(size_t)255;
     return W;

@@ -254,10 +254,11 @@ def test_materialize_tile_heights(hidden, T, Hkv):
         ctx.close()
 
 
-@pytest.mark.parametrize("hidden,T", [(8192, 1025), (8192, 1281), (8192, 1537), (8192, 2048), (512, 2300)])
+@pytest.mark.parametrize("hidden,T", [(8192, 1025), (8192, 1281), (8192, 1537), (8192, 2048), (512, 2300),
+                                      (2560, 1025), (2560, 1536), (2560, 1537), (2496, 1200)])
 def test_materialize_tall_tiles(hidden, T):
     """Tiles of 160, 192 and 256 rows with two workgroups per tile (hidden 8192, just past the row count where the
-    height before ends, and the last that has them) and of 160 rows with one.  Rows at the tiles' edges and some
+    height before ends, and the last that has them; the first hidden size that has them of 160 and 192) and of 160 rows with one.  Rows at the tiles' edges and some
     between, each against the oracle; the second run finds the arrival counters at zero again."""
     Hkv, pos0 = 8, 50
     case = Case("bf16-tall-tiles", n_layers=1, Hq=Hkv, Hkv=Hkv, D=128, hidden=hidden, dtype="bf16",
