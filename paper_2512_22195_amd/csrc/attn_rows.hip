@@ -11,6 +11,7 @@
 // one launch; partials travel through agent-scope (cache-bypassing) accesses, which keeps
 // the chip's separate L2 slices coherent without flushing them.
 #include "attn_common.h"
+#include "gemv_common.h"
 
 namespace matkv {
 namespace {
@@ -129,10 +130,69 @@ template <int G, int U> struct PV<uint16_t, G, U> {
     }
 };
 
-template <typename T, int D, int G, int NW, int U>
+// What a fused fp32 decode step adds: the newest token's K and V (paper Section III-B steps 2-3).
+struct StepArgs {
+    const float* hidden;        // [batch][Hd]
+    const float* w_k;           // [Hkv * D][Hd]
+    const float* w_v;
+    const RopeEntry* rope;
+    int32_t Hd;                 // 0: attention alone
+};
+
+// K and V of instance b's newest token for KV head kvh, into row `row` of its tail: a workgroup takes the head's D / 2 rotary pairs of K and
+// of V, a wave PB of them at a time, whose weights are requested at once.  (fp32: the angle in double, as in the projection kernel.)
+template <int D, int NW>
+__device__ __forceinline__ void project_newest(const KernelArgs& a, const StepArgs& f, int b, int kvh, int row, double pos, int wave, int lane) {
+    constexpr int HALF = D / 2, MINE = D / NW, PB = 8;              // pairs of a wave, K's before V's
+    static_assert(MINE % PB == 0 && MINE <= 64 && HALF % PB == 0, "whole groups of pairs, a lane per pair");
+    const float* const x = f.hidden + (size_t)b * f.Hd;
+    float mine0 = 0.f, mine1 = 0.f;                                 // pair `lane` of this wave
+#pragma unroll
+    for (int p0 = 0; p0 < MINE; p0 += PB) {
+        const int first = wave * MINE + p0, kv = first / HALF, j0 = first % HALF;
+        const float* const w = (kv == 0 ? f.w_k : f.w_v) + ((size_t)kvh * D + j0) * f.Hd;
+        float s0[PB], s1[PB];
+#pragma unroll
+        for (int i = 0; i < PB; ++i) { s0[i] = 0.f; s1[i] = 0.f; }
+        for (int c = 4 * lane; c < f.Hd; c += 256) {
+            const float4 xv = *reinterpret_cast<const float4*>(x + c);
+            float4 lo[PB], hi[PB];
+#pragma unroll
+            for (int i = 0; i < PB; ++i) {
+                lo[i] = *reinterpret_cast<const float4*>(w + (size_t)i * f.Hd + c);
+                hi[i] = *reinterpret_cast<const float4*>(w + (size_t)(HALF + i) * f.Hd + c);
+            }
+#pragma unroll
+            for (int i = 0; i < PB; ++i) {
+                s0[i] = fmaf(lo[i].w, xv.w, fmaf(lo[i].z, xv.z, fmaf(lo[i].y, xv.y, fmaf(lo[i].x, xv.x, s0[i]))));
+                s1[i] = fmaf(hi[i].w, xv.w, fmaf(hi[i].z, xv.z, fmaf(hi[i].y, xv.y, fmaf(hi[i].x, xv.x, s1[i]))));
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < PB; ++i) {
+            const float t0 = gemv::wave_sum(s0[i], lane), t1 = gemv::wave_sum(s1[i], lane);
+            if (lane == p0 + i) { mine0 = t0; mine1 = t1; }
+        }
+    }
+    if (lane < MINE) {
+        const int pair = wave * MINE + lane, kv = pair / HALF, j = pair % HALF;
+        if (kv == 0) {
+            double sd, cd;
+            sincos(pos * f.rope[j].inv_freq, &sd, &cd);
+            const float c = (float)cd, s = (float)sd, k0 = mine0 * c - mine1 * s, k1 = mine0 * s + mine1 * c;
+            mine0 = k0; mine1 = k1;
+        }
+        float* const out = reinterpret_cast<float*>(const_cast<void*>(kv == 0 ? a.tail_k : a.tail_v)) + (((size_t)b * a.Hkv + kvh) * (size_t)a.max_tail + row) * D + j;
+        out[0] = mine0; out[HALF] = mine1;
+    }
+}
+
+// STEP: a decode step of fp32 in one launch.  The workgroup that holds an instance's tail is the only one that reads the newest row, so it
+// computes that row first and nobody waits for another workgroup.
+template <typename T, int D, int G, int NW, int U, bool STEP>
 __global__ __launch_bounds__(NW * 64) void attn_rows_kernel(
         KernelArgs a, const InstanceInfo* __restrict__ insts, const Item* __restrict__ items,
-        const Unit* __restrict__ units) {
+        const Unit* __restrict__ units, StepArgs f) {
     constexpr int EPL = ElemTraits<T>::kPerLoad;        // elements per 16-byte load
     constexpr int LPT = D / EPL;                        // lanes that share one token row
     constexpr int TPW = 64 / LPT;                       // token rows per wave-wide load
@@ -156,6 +216,13 @@ __global__ __launch_bounds__(NW * 64) void attn_rows_kernel(
     } else {
         q_row = unit.inst;
         if (unit.has_tail) tail_visible = insts[unit.inst].tail_len;
+        if constexpr (STEP) {
+            if (unit.has_tail) {                        // (the whole workgroup)
+                const int row = tail_visible - 1;
+                if (row >= 0 && row < a.max_tail) project_newest<D, NW>(a, f, unit.inst, kvh, row, (double)(insts[unit.inst].pos_base + row), wave, lane);
+                __syncthreads();                        // the row is there for all waves
+            }
+        }
     }
 
     // This lane's slice of the G query vectors.
@@ -278,14 +345,14 @@ __global__ __launch_bounds__(NW * 64) void attn_rows_kernel(
     finish_unit<T, D, NW, NW, G, D>(a, unit, kvh, row, &sm_acc[0][0][0], &sm_m[0][0], &sm_l[0][0], &sm_last, G, map);
 }
 
-template <typename T, int D, int G, int NW, int U>
-hipError_t launch_v(const AttnArgs& a, hipStream_t s) {
+template <typename T, int D, int G, int NW, int U, bool STEP = false>
+hipError_t launch_v(const AttnArgs& a, hipStream_t s, const StepArgs& f = StepArgs{}) {
     const KernelArgs k = make_kernel_args(a);
     dim3 grid(a.n_units, a.Hkv, a.rows), block(NW * 64);
-    hipLaunchKernelGGL((attn_rows_kernel<T, D, G, NW, U>), grid, block, 0, s, k,
+    hipLaunchKernelGGL((attn_rows_kernel<T, D, G, NW, U, STEP>), grid, block, 0, s, k,
                        reinterpret_cast<const InstanceInfo*>(a.table + a.off_inst),
                        reinterpret_cast<const Item*>(a.table + a.off_items),
-                       reinterpret_cast<const Unit*>(a.table + a.off_units));
+                       reinterpret_cast<const Unit*>(a.table + a.off_units), f);
     return hipGetLastError();
 }
 
@@ -311,7 +378,19 @@ hipError_t launch_t(const AttnArgs& a, hipStream_t s) {
 }
 
 template <typename T, int D>
-hipError_t launch_g(const AttnArgs& a, hipStream_t s) {
+hipError_t launch_g(const AttnArgs& a, hipStream_t s, const StepArgs& f = StepArgs{}) {
+    if constexpr (sizeof(T) == 4) {
+        if (f.Hd) {
+            switch (a.Hq / a.Hkv) {
+                case 1: return launch_v<T, D, 1, 4, 4, true>(a, s, f);
+                case 2: return launch_v<T, D, 2, 4, 4, true>(a, s, f);
+                case 3: return launch_v<T, D, 3, 4, 4, true>(a, s, f);
+                case 4: return launch_v<T, D, 4, 4, 4, true>(a, s, f);
+                case 8: return launch_v<T, D, 8, 4, 4, true>(a, s, f);
+            }
+            return hipErrorInvalidValue;
+        }
+    }
     switch (a.Hq / a.Hkv) {
         case 1: return launch_t<T, D, 1>(a, s);
         case 2: return launch_t<T, D, 2>(a, s);
@@ -334,6 +413,21 @@ hipError_t launch_attn_rows(const AttnArgs& a, int dtype, hipStream_t s) {
         if (a.D == 128) return launch_g<uint16_t, 128>(a, s);
     }
     return hipErrorInvalidValue;
+}
+
+// A decode step of fp32 in one launch, while the workgroups that hold the tails have read the projection's weights as soon as a launch of its own would
+// have: a head's 2 D rows of hidden 256 at head_dim 64, of 512 with eight instances.  us per layer step, two launches -> one, head_dim 64: 4 / 2 heads, hidden 256, one
+// user of 512 tokens 10.0 -> 9.4, four 12.5 -> 9.9; 8 / 8 heads, hidden 512, one 10.5 -> 11.4, eight 16.0 -> 13.4; hidden 1024, one 12.0 -> 15.5.  A host that launches step
+// after step is spared one launch in three.
+bool decode_step_rows_supported(const AttnArgs& a, const MaterializeArgs& m, int dtype) {
+    return dtype == MATKV_F32 && !a.prefill && !a.shared && (a.D == 64 || a.D == 128) && group_size_built(a.Hq / a.Hkv) && m.rows_per_instance == 1 &&
+           a.D * m.Hd <= (a.batch >= 8 ? 32768 : 16384);
+}
+
+hipError_t launch_decode_step_rows(const AttnArgs& a, const MaterializeArgs& m, int dtype, hipStream_t s) {
+    if (a.n_units <= 0 || !decode_step_rows_supported(a, m, dtype)) return hipErrorInvalidValue;
+    const StepArgs f{static_cast<const float*>(m.hidden), static_cast<const float*>(m.w_k), static_cast<const float*>(m.w_v), m.rope, m.Hd};
+    return a.D == 64 ? launch_g<float, 64>(a, s, f) : launch_g<float, 128>(a, s, f);
 }
 
 }  // namespace matkv

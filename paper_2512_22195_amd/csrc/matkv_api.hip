@@ -2108,7 +2108,11 @@ matkv_status matkv_decode_step(matkv_ctx* c, int32_t layer, const void* hidden, 
         HIP_TRY(c, launch_decode_step(a, m, c->cfg.dtype, c->compute));
         return MATKV_OK;
     }
-    // shapes the fused kernel does not cover: the two launches it stands for
+    if (decode_step_rows_supported(a, m, c->cfg.dtype)) {
+        HIP_TRY(c, launch_decode_step_rows(a, m, c->cfg.dtype, c->compute));
+        return MATKV_OK;
+    }
+    // shapes the fused kernels do not cover: the two launches they stand for
     const bool want_mfma = a.variant == 0 || a.variant >= 9000;
     if (a.kv_fmt != MATKV_PAGE_PLAIN && !(want_mfma && attn_mfma_supported(a, c->cfg.dtype)))
         return fail(c, MATKV_EUNSUPPORTED, "decode_step: compressed pages need the matrix-core kernels (decode_variant 0 or 90xx)");

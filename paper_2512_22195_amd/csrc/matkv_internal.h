@@ -236,6 +236,8 @@ ProjectionForm projection_form(int hidden, int Hkv, int D, int dtype, long rows)
 hipError_t launch_materialize_tiles(const MaterializeArgs& a, int total_rows, hipStream_t s);
 hipError_t launch_materialize_staged(const MaterializeArgs& a, int total_rows, hipStream_t s);
 hipError_t launch_materialize_fewrows(const MaterializeArgs& a, int total_rows, hipStream_t s);
+bool decode_step_rows_supported(const AttnArgs& a, const MaterializeArgs& m, int dtype);
+hipError_t launch_decode_step_rows(const AttnArgs& a, const MaterializeArgs& m, int dtype, hipStream_t s);   // fp32: both in one launch
 bool decode_step_supported(const AttnArgs& a, const MaterializeArgs& m, int dtype);
 hipError_t launch_decode_step(const AttnArgs& a, const MaterializeArgs& m, int dtype, hipStream_t s);   // projection + attention
 hipError_t launch_probe_read(const void* src, size_t bytes, unsigned* sink, hipStream_t s);

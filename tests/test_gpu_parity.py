@@ -154,6 +154,17 @@ def test_decode_step_other_shapes_run_two_launches():
     _chain_parity(case, fused=True)
 
 
+@pytest.mark.parametrize("use_graph", [False, True])
+@pytest.mark.parametrize("D,Hq,Hkv,hidden,batch", [(64, 4, 2, 256, 1), (64, 2, 2, 64, 3), (64, 6, 2, 192, 2), (64, 8, 1, 256, 9), (64, 4, 1, 512, 8),
+                                                   (128, 2, 1, 128, 2), (128, 4, 4, 64, 5), (64, 4, 2, 320, 1)])
+def test_fp32_decode_step_in_one_launch(D, Hq, Hkv, hidden, batch, use_graph):
+    """fp32 decode steps whose workgroups with the tails project the newest token themselves (hidden sizes below and past one pass of a wave, every
+    group size, several units and none but the tail) and, in the last case, just past that: two launches."""
+    case = Case("step-f32", n_layers=2, Hq=Hq, Hkv=Hkv, D=D, hidden=hidden, dtype="f32", chunk_lens={0: 70, 1: 300, 2: 1},
+                retrieved=[[[0, 1], [], [2]][b % 3] for b in range(batch)], q_lens=[1 + b % 5 for b in range(batch)], steps=3, scale=1.0 / 8.0, q_scale=1.0)
+    _chain_parity(case, fused=True, use_graph=use_graph)
+
+
 @pytest.mark.parametrize("T", [16, 37, 64, 150, 255, 300, 1000, 1100, 2100])
 def test_materialize_row_count_forms_bf16(T):
     """The bf16 projection picks its kernel by row count: skinny split-hidden form (16..255 rows;
