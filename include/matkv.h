@@ -258,7 +258,8 @@ matkv_status matkv_assemble(matkv_ctx* ctx, const matkv_page* pages_host,
 /* Host-only preview of the decode work partition matkv_assemble builds for one instance of a
  * batch of `batch` instances like it (no GPU is touched): page_tokens_host[n_pages] are the
  * chunk lengths, q_len the question length.  Unit u streams unit_tokens_out[u] page tokens and
- * is made of unit_items_out[u] page pieces; the last unit also owns the tail.  Returns the
+ * is made of unit_items_out[u] page pieces; the last unit also owns the tail.  (Over E4M3 pages the
+ * unit with the tail is given up to 128 page tokens fewer than shown.)  Returns the
  * number of units (at most cap), or -1 on a bad argument.  Either output may be NULL.  (Where these
  * units would leave compute units idle or waiting, decode launches take the runs of
  * matkv_plan_even_units instead.) */

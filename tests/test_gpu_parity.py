@@ -1632,6 +1632,14 @@ def test_attention_over_compressed_pages(name, Hq, Hkv, use_graph):
     chain.compare_attention(case, o_pre, o_dec, pre, dec)
 
 
+@pytest.mark.parametrize("lens,q_lens", [([1000], [5]), ([520, 521], [5]), ([129], [3]), ([700], [200]), ([2100], [40, 7, 100]), ([128], [90, 1])])
+def test_decode_over_compressed_pages_spares_the_tail_unit(lens, q_lens):
+    """Caches whose last decode unit holds the tail and fewer pages than the others, a few rows of one, or none of them."""
+    case = Case("decode-spared", n_layers=1, Hq=16, Hkv=4, D=128, hidden=64, dtype="bf16", chunk_lens=dict(enumerate(lens)),
+                retrieved=[list(range(len(lens)))] * len(q_lens), q_lens=q_lens, steps=2, scale=0.5, compressed=True)
+    _attention_parity(case)
+
+
 @pytest.mark.parametrize("batch,fused,files", [(1, True, False), (3, True, True), (6, False, False)])
 def test_chain_with_compressed_blobs(batch, fused, files, tmp_path):
     """materialize -> compress -> (file ->) load -> assemble -> prefill -> decode steps (one launch
