@@ -162,6 +162,8 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(
     // 4096 150 15.7 -> 14.2, 512 19.7 -> 17.6, 1000 25.4 -> 23.8, 3501 56.0 -> 51.2; 8192 512 33.8 -> 30.4, 1000 43.6 -> 40.6, 3501 105 -> 97.
     // Steps from one row tile to the next: 1, 2, 3 and 4 measured, 4096 300 rows (tiles of 64) 17.4, 16.9, 16.7, 16.3, 512 18.3, 18.4, 18.1, 18.7,
     // 1000 (128) 23.8, 24.5, 25.1, 25.7; 8192 1000 42.2, 40.4, 40.7, 41.6.
+    // Where the few layers of a small program stay in the last-level cache the wait is shorter and 4 a little too many: chunk passes of the 3B shape, 224
+    // tokens, all at step 0 / 1 / 2 / 4: four layers (50 MB) 79.3 / 78.6 / 79.9 / 80.7, eight (three such programs in turn) 183 / 177 / 174 / 170.
     const int xcd = blockIdx.x & 7;
     const int first = (SK == 2 ? rt * (MI == 1 ? 4 : MI == 2 ? 3 : nk >= 40 ? 2 : 1) + (xcd >> 1) * (nk / 4)
                                : (rt >> 1) + (xcd & 3) * nk / 4) % nk;
