@@ -72,6 +72,7 @@ struct TableHost {
     int max_tail_len = 0;     // largest tail_len of any instance (host mirror)
     int min_tail_len = 0;
     int n_decode_slots = 0;   // partial slots a decode launch writes (units, or (unit, user) pairs when shared)
+    bool step_by_instance = false;      // a fused decode step reads every instance's cache for itself, beside a shared partition
     bool past_llc = false;    // decode launches leave the cache's rows out of the last-level cache (rows_pass_llc)
     std::vector<const void*> slots;   // distinct slots its pages point into
 };
@@ -950,6 +951,32 @@ bool rows_pass_llc(const matkv_config& cfg, size_t distinct, size_t streamed, si
            walks >= kStreamedWalks + over * (kStreamedWalksFar - kStreamedWalks);
 }
 
+// Page tokens of a batch: every use of a page counted, and every slot once.
+std::pair<size_t, size_t> count_page_tokens(const matkv_config& cfg, const matkv_page* pages, const int32_t* n_pages, int batch) {
+    std::vector<std::pair<const void*, int>> seen;
+    for (int b = 0; pages && b < batch; ++b)
+        for (int p = 0; p < n_pages[b]; ++p) seen.emplace_back(pages[(size_t)b * cfg.max_pages + p].slot, pages[(size_t)b * cfg.max_pages + p].n_tokens);
+    std::sort(seen.begin(), seen.end());
+    size_t uses = 0, distinct = 0;
+    for (size_t i = 0; i < seen.size(); ++i) {
+        uses += seen[i].second;
+        if (i == 0 || seen[i].first != seen[i - 1].first) distinct += seen[i].second;
+    }
+    return {uses, distinct};
+}
+
+// Whether a decode step that can be the fused launch is it although the batch shares pages.  That launch reads every instance's cache for itself, but
+// hides the projection and spares the shared kernel's fold: 5 us for two instances, 6 for four, less the time of the bytes that are read twice.  us per layer step,
+// over the shared partition -> fused, by what a layer reads twice (8B shape): two users, 1 MB 15.8 -> 11.1, 20 18.4 -> 17.2, 41 21.4 -> 22.6, 49 22.3 -> 24.4;
+// three, 39 22.0 -> 18.1 in four layers, 65 23.5 -> 26.1; four, 39 24.6 -> 22.2, 61 22.9 -> 22.1, 74 23.5 -> 24.1.  3B: two, 41 20.8 -> 21.1, four, 61 21.3 -> 21.0.  Of
+// compressed pages (8B) two, 20 18.6 -> 13.3, 41 22.5 -> 23.0, four, 61 25.3 -> 23.8; (3B) four, 74 24.2 -> 25.2.  Long caches end it: with 5 to 25 % of the uses
+// shared, four users of 82 MB 1.04 to 1.24 times as fast, 131 MB in all 1.05, 164 1.00 to 1.06, 184 1.02, 246 0.985.
+bool step_by_instance(const matkv_config& cfg, const matkv_page* pages, const int32_t* n_pages, int batch, int kv_fmt) {
+    const auto [uses, distinct] = count_page_tokens(cfg, pages, n_pages, batch);
+    const size_t row = (size_t)2 * cfg.n_kv_heads * cfg.head_dim * (kv_fmt == MATKV_PAGE_E4M3 ? 1 : 2);
+    return (uses - distinct) * row <= (size_t)batch * 12000000 && uses * row <= 192000000;
+}
+
 // Decode attention of a batch (insts: q_len is set): the units of every instance, and beside them the shared partition or
 // the even one where they apply.  sunits: the table's section of the shared partition; the even one's records follow dunits.
 struct DecodeLayout {
@@ -994,14 +1021,7 @@ DecodeLayout lay_out_decode(const matkv_config& cfg, const TableLayout& tl, cons
     else if (L.n_sunits > 0) for (int u = 0; u < L.n_sunits; ++u) walk(sunits[u].u);
     else                     for (int u = 0; u < L.n_dunits; ++u) walk(dunits[u]);
     if (rows_pass_llc(cfg, streamed, streamed, tail_rows, longest, kv_fmt)) {       // (with fewer distinct ones it is no other without this)
-        std::vector<std::pair<const void*, int>> seen;
-        for (int b = 0; pages && b < batch; ++b)
-            for (int p = 0; p < n_pages[b]; ++p) seen.emplace_back(pages[(size_t)b * cfg.max_pages + p].slot, pages[(size_t)b * cfg.max_pages + p].n_tokens);
-        std::sort(seen.begin(), seen.end());
-        size_t distinct = 0;
-        for (size_t i = 0; i < seen.size(); ++i)
-            if (i == 0 || seen[i].first != seen[i - 1].first) distinct += seen[i].second;
-        L.past_llc = rows_pass_llc(cfg, distinct, streamed, tail_rows, longest, kv_fmt);
+        L.past_llc = rows_pass_llc(cfg, count_page_tokens(cfg, pages, n_pages, batch).second, streamed, tail_rows, longest, kv_fmt);
     }
     return L;
 }
@@ -1730,6 +1750,7 @@ matkv_status matkv_assemble(matkv_ctx* c, const matkv_page* pages, const int32_t
                                                reinterpret_cast<SUnit*>(h + c->tl.off_sunits), scales_off);
     const int n_dunits = decode.n_dunits, n_sunits = decode.n_sunits;
     th.even = decode.even; th.past_llc = decode.past_llc;
+    th.step_by_instance = n_sunits > 0 && step_by_instance(cfg, pages, n_pages, batch, kv_fmt);
     // prefill: coarse partition (the question rows supply most of the parallelism)
     th.prefill = lay_out_prefill(cfg, pages, n_pages, q_len, batch, kv_fmt == MATKV_PAGE_E4M3, insts, items, &n_items, punits, scales_off);
     const size_t dunit_bytes = sizeof(Unit) * n_dunits + (decode.even_built ? sizeof(SUnit) * (256 / cfg.n_kv_heads) : 0);
@@ -2109,8 +2130,13 @@ matkv_status matkv_decode_step(matkv_ctx* c, int32_t layer, const void* hidden, 
     m.rows_per_instance = 1; m.batch = th->batch; m.n_tokens = th->batch;
     m.Hkv = c->cfg.n_kv_heads; m.D = c->cfg.head_dim; m.Hd = c->cfg.hidden;
     materialize_scratch(c, m);
-    if (decode_step_supported(a, m, c->cfg.dtype)) {
-        HIP_TRY(c, launch_decode_step(a, m, c->cfg.dtype, c->compute));
+    AttnArgs step = a;
+    if (th->step_by_instance) {         // (every table has these units)
+        step.shared = 0;
+        step.n_units = th->n_dunits; step.off_units = c->tl.off_dunits;
+    }
+    if (decode_step_supported(step, m, c->cfg.dtype)) {
+        HIP_TRY(c, launch_decode_step(step, m, c->cfg.dtype, c->compute));
         return MATKV_OK;
     }
     if (decode_step_rows_supported(a, m, c->cfg.dtype)) {

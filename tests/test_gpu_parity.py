@@ -698,6 +698,57 @@ def test_decode_past_the_last_level_cache(Hq, batch, shared, compressed):
     assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
 
 
+@pytest.mark.parametrize("Hq,batch,shared,own,compressed,launches", [
+    (32, 2, 700, 1, False, 1), (24, 4, 333, 40, True, 1), (32, 2, 5859, 3, False, 1), (32, 2, 5860, 3, False, 2),     # (24 MB are 5859 tokens)
+    (32, 4, 3906, 1, False, 1), (32, 4, 3907, 1, False, 2), (24, 2, 11719, 1, True, 2), (32, 5, 500, 30, False, 2), (64, 2, 500, 30, False, 2)])
+def test_decode_step_over_few_shared_pages(Hq, batch, shared, own, compressed, launches):
+    """A batch of which every user has one page in common and one of their own: the step is the fused launch up to 12 MB an instance
+    that are read twice, and two launches beyond, for more than four instances and for eight heads to a KV head.  Either meets the
+    two calls it stands for, replayed as well: each output is within the attention bar of the exact one, so two are within twice that."""
+    from paper_2512_22195_amd import binding as mk
+    Hkv, D, cap = 8, 128, 24
+    hidden = 3072 if Hq == 24 else 4096
+    ctx = mk.Context(mk.make_config(1, Hq, Hkv, D, hidden, "bf16", 10000.0, max_batch=batch, max_pages=2, max_tail_tokens=cap))
+    try:
+        with torch.cuda.stream(ctx.compute_stream):
+            g = torch.Generator(device="cuda").manual_seed(31 + Hq)
+            draw = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+
+            def page(n):
+                v = draw(1, 2, Hkv, n, D)
+                if not compressed:
+                    return v.view(torch.uint8).view(-1), n, mk.PAGE_PLAIN
+                packed = torch.empty(mk.compressed_blob_bytes(ctx.cfg, n), dtype=torch.uint8, device="cuda")
+                ctx.compress(v, n, packed)
+                return packed, n, mk.PAGE_E4M3
+            hot = page(shared)
+            pages = [[hot, page(own)] if b % 2 else [page(own), hot] for b in range(batch)]
+            w, q, x, tail, table = draw(2, Hkv * D, hidden) * hidden ** -0.5, draw(batch, Hq, D), draw(batch, hidden), draw(2, batch, Hkv, cap, D), ctx.new_table()
+            q_len = [5 + b for b in range(batch)]
+            want, got = torch.empty((2, batch, Hq, D), dtype=torch.bfloat16, device="cuda")
+            two, one = tail.clone(), tail.clone()
+            ctx.assemble(pages, q_len, table)
+            assert ctx.table_shared_units(table) > 0
+            ctx.advance(table, 1)
+            ctx.materialize_tail(x, w[0], w[1], table, 1, two[0], two[1])
+            ctx.decode_attn(0, q, table, two[0], two[1], want)
+            ctx.graph_begin()
+            ctx.decode_step(0, x, w[0], w[1], q, table, one[0], one[1], got)
+            step = ctx.graph_end()
+            assert ctx.graph_kernel_launches(step) == launches
+            for _ in range(3):
+                got.fill_(7.0)
+                one.copy_(tail)
+                ctx.graph_launch(step)
+                ctx.compute_stream.synchronize()
+                for a, b in ((got, want), (one, two)):
+                    a, b = a.float(), b.float()
+                    assert ((a - b).abs() <= 2 * (2e-2 * b.square().mean().sqrt() + 2.0 ** -8 * b.abs())).all()
+            ctx.graph_destroy(step)
+    finally:
+        ctx.close()
+
+
 def _decode_batch(Hq, caches, q_lens, compressed, decode_units, replays=(), max_pages=4):
     """Decode outputs (float) of a batch whose instance b has pages of caches[b] tokens; with replays, those of a step recorded over
     that table and replayed after each re-assembly with other caches.  Same seeds, same contents, whatever the partition."""
@@ -1841,8 +1892,7 @@ def test_group_of_three_fp32():
 @pytest.mark.parametrize("use_graph", [False, True])
 def test_decode_step_over_shared_pages(use_graph):
     """matkv_decode_step on a batch whose instances share their chunks: the table carries the
-    shared partition, so the step runs as projection + shared decode attention (two launches),
-    eagerly and recorded in a graph."""
+    shared partition, and the step, eagerly and recorded in a graph, is right beside it."""
     case = Case(f"shared-step-{int(use_graph)}", n_layers=2, Hq=8, Hkv=2, D=128, hidden=4096, dtype="bf16",
                 chunk_lens={0: 400, 1: 90}, retrieved=[[0, 1], [0], [1, 0], [0]], q_lens=[4, 9, 1, 17],
                 steps=3, rope_base=500000.0, scale=1.0 / 8.0, q_scale=1.0)
