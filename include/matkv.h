@@ -258,14 +258,16 @@ matkv_status matkv_assemble(matkv_ctx* ctx, const matkv_page* pages_host,
 /* Host-only preview of the decode work partition matkv_assemble builds for one instance of a
  * batch of `batch` instances like it (no GPU is touched): page_tokens_host[n_pages] are the
  * chunk lengths, q_len the question length.  Unit u streams unit_tokens_out[u] page tokens and
- * is made of unit_items_out[u] page pieces; the last unit also owns the tail.  (Over E4M3 pages the
- * unit with the tail is given up to 128 page tokens fewer than shown.)  Returns the
+ * is made of unit_items_out[u] page pieces; the last unit also owns the tail.  Returns the
  * number of units (at most cap), or -1 on a bad argument.  Either output may be NULL.  (Where these
  * units would leave compute units idle or waiting, decode launches take the runs of
- * matkv_plan_even_units instead.) */
+ * matkv_plan_even_units instead.)  Plain pages; matkv_plan_decode_units_of takes the pages' format (over
+ * E4M3 pages the unit with the tail gets up to 128 page tokens fewer, while units have 128 tokens). */
 int32_t matkv_plan_decode_units(const matkv_config* cfg, const int32_t* page_tokens_host,
                                 int32_t n_pages, int32_t batch, int32_t q_len,
                                 int32_t* unit_tokens_out, int32_t* unit_items_out, int32_t cap);
+int32_t matkv_plan_decode_units_of(const matkv_config* cfg, const int32_t* page_tokens_host, int32_t n_pages, int32_t batch, int32_t q_len,
+                                   int32_t format, int32_t* unit_tokens_out, int32_t* unit_items_out, int32_t cap);
 /* Host-only preview of the even decode partition that matkv_assemble builds beside the one by instance for a batch without
  * shared pages whose decode step is not a single launch: the batch's caches end to end (an instance's pages, then its tail),
  * cut into 256 / n_kv_heads runs of nearly equal length, one workgroup per KV head each (no GPU is touched).

@@ -27,7 +27,7 @@ EXPORTS = [
     "matkv_last_error", "matkv_materialize", "matkv_materialize_tail", "matkv_chunk_attn", "matkv_load", "matkv_load_file", "matkv_store_file",
     "matkv_wait", "matkv_query", "matkv_sync", "matkv_assemble", "matkv_advance",
     "matkv_prefill_attn", "matkv_decode_attn", "matkv_decode_step", "matkv_graph_begin", "matkv_graph_end",
-    "matkv_graph_launch", "matkv_graph_destroy", "matkv_graph_kernel_launches", "matkv_plan_decode_units", "matkv_probe_read",
+    "matkv_graph_launch", "matkv_graph_destroy", "matkv_graph_kernel_launches", "matkv_plan_decode_units", "matkv_plan_decode_units_of", "matkv_probe_read",
     "matkv_table_shared_units", "matkv_plan_projection", "matkv_plan_prefill",
     "matkv_plan_shared_units", "matkv_plan_even_units", "matkv_plan_decode_streams", "matkv_decode_attn_static",
 ]
@@ -107,6 +107,8 @@ def _load_library():
     lib.matkv_plan_decode_units.argtypes = [cfgp, POINTER(c_int32), c_int32, c_int32, c_int32,
                                             POINTER(c_int32), POINTER(c_int32), c_int32]
     lib.matkv_plan_decode_units.restype = c_int32
+    lib.matkv_plan_decode_units_of.argtypes = [cfgp, POINTER(c_int32)] + [c_int32] * 4 + [POINTER(c_int32), POINTER(c_int32), c_int32]
+    lib.matkv_plan_decode_units_of.restype = c_int32
     lib.matkv_plan_even_units.argtypes = [cfgp] + [POINTER(c_int32)] * 3 + [c_int32, c_int32, POINTER(c_int32), c_int32, POINTER(c_int32), POINTER(c_int32)]
     lib.matkv_plan_even_units.restype = c_int32
     lib.matkv_plan_decode_streams.argtypes = [cfgp] + [POINTER(c_int32)] * 4 + [c_int32, c_int32]
@@ -251,15 +253,15 @@ def plan_prefill(cfg: Config, page_tokens, q_lens, format: int = PAGE_PLAIN):
     return int(rows), list(units)
 
 
-def plan_decode_units(cfg: Config, page_tokens, batch: int, q_len: int):
-    """(tokens, page pieces) of each decode unit matkv_assemble would build for one instance."""
+def plan_decode_units(cfg: Config, page_tokens, batch: int, q_len: int, format: int = PAGE_PLAIN):
+    """(tokens, page pieces) of each decode unit matkv_assemble would build for one instance over pages in `format`."""
     n = len(page_tokens)
     pt = (c_int32 * max(n, 1))(*page_tokens)
     cap = 512
     toks, its = (c_int32 * cap)(), (c_int32 * cap)()
-    made = _lib.matkv_plan_decode_units(byref(cfg), pt, n, batch, q_len, toks, its, cap)
+    made = _lib.matkv_plan_decode_units_of(byref(cfg), pt, n, batch, q_len, format, toks, its, cap)
     if made < 0:
-        raise MatKVError(EINVAL, "matkv_plan_decode_units")
+        raise MatKVError(EINVAL, "matkv_plan_decode_units_of")
     return list(toks[:made]), list(its[:made])
 
 

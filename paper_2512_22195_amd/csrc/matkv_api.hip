@@ -977,6 +977,20 @@ bool step_by_instance(const matkv_config& cfg, const matkv_page* pages, const in
     return (uses - distinct) * row <= (size_t)batch * 12000000 && uses * row <= 192000000;
 }
 
+// How an instance's cache is cut into decode units, one workgroup per (unit, KV head).  Over compressed pages a unit walks its codes first and asks for
+// the tail behind them, a round trip of its own, and the launch ends with it (8B shape, one user of 10 000 tokens: 8.4 us against 7.5 of the others): the
+// unit that has the tail gets 128 tokens fewer, unless the tail fills it anyway.  us per pass, eight steps of eight layers, one 8B user of 10 000 compressed
+// tokens 820 -> 818, 5000 737 -> 708, 2000 655 -> 629, 700 571 -> 554, two of 5000 866 -> 854, four of 3000 1000 -> 925, one 3B user of 20 000 994 -> 953; of
+// 750 with a 200-row question, whatever the tail fills, 298 -> 325.  (256 fewer: in the mean the same.  Plain pages, 32 or 64 fewer: 0.98 to 1.02.)
+// Not where units are shorter than that, as they can be where the configuration fixes their number: several would come to lie behind the pages' end and
+// fall away, and a step recorded over one table would not fit the next.
+struct DecodeCut { int units, tail_tokens; };       // units; tokens that the tail counts for
+DecodeCut decode_cut(const matkv_config& cfg, int batch, long page_tokens, int q_len, int kv_fmt) {
+    const int tail = q_len + (cfg.max_tail_tokens - q_len) / 2, units = choose_decode_units(cfg, batch, page_tokens + tail);
+    const bool spares = kv_fmt == MATKV_PAGE_E4M3 && (long)std::max(tail + 1, 128) * units <= page_tokens + tail;
+    return {units, tail + (spares ? 128 : 0)};
+}
+
 // Decode attention of a batch (insts: q_len is set): the units of every instance, and beside them the shared partition or
 // the even one where they apply.  sunits: the table's section of the shared partition; the even one's records follow dunits.
 struct DecodeLayout {
@@ -991,16 +1005,9 @@ DecodeLayout lay_out_decode(const matkv_config& cfg, const TableLayout& tl, cons
         const matkv_page* pg = pages ? pages + (size_t)b * cfg.max_pages : nullptr;
         long inst_tokens = 0;
         for (int p = 0; p < n_pages[b]; ++p) inst_tokens += pg[p].n_tokens;
-        const int tail_est = insts[b].q_len + (cfg.max_tail_tokens - insts[b].q_len) / 2;
-        // Fine partition, one workgroup per (unit, KV head).  Over compressed pages a unit walks its codes first and asks for the tail behind them, a
-        // round trip of its own, and the launch ends with it (8B shape, one user of 10 000 tokens: 8.4 us against 7.5 of the others): the
-        // unit that has the tail gets 128 tokens fewer, unless the tail fills it anyway.  us per pass, eight steps of eight layers, one 8B user of 10 000 compressed
-        // tokens 820 -> 818, 5000 737 -> 708, 2000 655 -> 629, 700 571 -> 554, two of 5000 866 -> 854, four of 3000 1000 -> 925, one 3B user of 20 000 994 -> 953; of
-        // 750 with a 200-row question, whatever the tail fills, 298 -> 325.  (256 fewer: in the mean the same.  Plain pages, 32 or 64 fewer: 0.98 to 1.02.)
-        const int units = choose_decode_units(cfg, batch, inst_tokens + tail_est);
-        const int spared = kv_fmt == MATKV_PAGE_E4M3 && (long)tail_est * units < inst_tokens + tail_est ? 128 : 0;
+        const DecodeCut c = decode_cut(cfg, batch, inst_tokens, insts[b].q_len, kv_fmt);
         insts[b].dunit0 = L.n_dunits;
-        insts[b].n_dunits = build_units(pg, n_pages[b], b, units, tail_est + spared, cfg.max_tail_tokens, items, n_items, dunits, &L.n_dunits, scales_off);
+        insts[b].n_dunits = build_units(pg, n_pages[b], b, c.units, c.tail_tokens, cfg.max_tail_tokens, items, n_items, dunits, &L.n_dunits, scales_off);
     }
     // over shared pages: only where the default matrix-core decode kernel runs
     if (batch >= 2 && pages && cfg.decode_units == 0 && cfg.decode_variant == 0 &&
@@ -1801,30 +1808,29 @@ matkv_status matkv_assemble(matkv_ctx* c, const matkv_page* pages, const int32_t
     MATKV_CATCH(c, "assemble")
 }
 
-int32_t matkv_plan_decode_units(const matkv_config* cfg, const int32_t* page_tokens, int32_t n_pages,
-                                int32_t batch, int32_t q_len, int32_t* unit_tokens_out,
-                                int32_t* unit_items_out, int32_t cap) {
+int32_t matkv_plan_decode_units_of(const matkv_config* cfg, const int32_t* page_tokens, int32_t n_pages, int32_t batch, int32_t q_len,
+                                   int32_t format, int32_t* unit_tokens_out, int32_t* unit_items_out, int32_t cap) {
     const char* why;
     if (check_config(cfg, &why) != MATKV_OK) return -1;
     MATKV_TRY
     if (n_pages < 0 || n_pages > cfg->max_pages || (n_pages > 0 && !page_tokens) || batch < 1 ||
         batch > cfg->max_batch || q_len < 1 || q_len > cfg->max_tail_tokens || cap < 0)
         return -1;
+    if ((format != MATKV_PAGE_PLAIN && format != MATKV_PAGE_E4M3) || (format == MATKV_PAGE_E4M3 && !(cfg->dtype == MATKV_BF16 && cfg->head_dim == 128))) return -1;
     std::vector<matkv_page> pages((size_t)(n_pages > 0 ? n_pages : 1));
     long inst_tokens = 0;
     for (int p = 0; p < n_pages; ++p) {
         if (page_tokens[p] < 1) return -1;
         pages[p].slot = reinterpret_cast<const void*>((uintptr_t)0x1000);   // never dereferenced
         pages[p].n_tokens = page_tokens[p];
-        pages[p].format = MATKV_PAGE_PLAIN;
+        pages[p].format = format;
         inst_tokens += page_tokens[p];
     }
-    const int tail_est = q_len + (cfg->max_tail_tokens - q_len) / 2;
+    const DecodeCut c = decode_cut(*cfg, batch, inst_tokens, q_len, format);
     std::vector<Item> items((size_t)kMaxDecodeUnitsPerInstance + n_pages + 2);
     std::vector<Unit> units((size_t)kMaxDecodeUnitsPerInstance);
     int n_items = 0, n_units = 0;
-    const int made = build_units(pages.data(), n_pages, 0, choose_decode_units(*cfg, batch, inst_tokens + tail_est),
-                                 tail_est, cfg->max_tail_tokens, items.data(), &n_items, units.data(), &n_units,
+    const int made = build_units(pages.data(), n_pages, 0, c.units, c.tail_tokens, cfg->max_tail_tokens, items.data(), &n_items, units.data(), &n_units,
                                  [](int) { return (size_t)0; });
     for (int u = 0; u < made && u < cap; ++u) {
         if (unit_tokens_out) unit_tokens_out[u] = units[u].page_tokens;
@@ -1832,6 +1838,11 @@ int32_t matkv_plan_decode_units(const matkv_config* cfg, const int32_t* page_tok
     }
     return made < cap ? made : cap;
     MATKV_CATCH_INT
+}
+
+int32_t matkv_plan_decode_units(const matkv_config* cfg, const int32_t* page_tokens, int32_t n_pages, int32_t batch, int32_t q_len,
+                                int32_t* unit_tokens_out, int32_t* unit_items_out, int32_t cap) {
+    return matkv_plan_decode_units_of(cfg, page_tokens, n_pages, batch, q_len, MATKV_PAGE_PLAIN, unit_tokens_out, unit_items_out, cap);
 }
 
 int32_t matkv_plan_projection(const matkv_config* cfg, int32_t n_rows) {

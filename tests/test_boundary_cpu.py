@@ -107,6 +107,38 @@ def test_decode_partition_covers_every_token_once_and_is_balanced(mk):
         mk.plan_decode_units(cfg, [0, 5], batch=1, q_len=10)
 
 
+def test_decode_partition_over_compressed_pages(mk):
+    """Host logic: over compressed pages the unit with the tail has up to 128 page tokens fewer than over plain ones, the others share them
+    evenly, and there are as many units, also where the configuration fixes a number of them that leaves each a few tokens."""
+    rng = np.random.default_rng(5)
+    spared = short = 0
+    for trial in range(400):
+        units = int(rng.choice([0, 0, 1, 2, 3, 7, 16, 64]))
+        max_tail = int(rng.choice([8, 24, 128, 512]))
+        lens = [int(n) for n in rng.integers(1, int(rng.choice([30, 300, 2000])) + 1, size=int(rng.integers(0, 7)))]
+        batch, q = int(rng.integers(1, 5)), int(rng.integers(1, max_tail + 1))
+        cfg = mk.make_config(2, 32, 8, 128, 4096, "bf16", 500000.0, 4, 6, max_tail, decode_units=units)
+        plain, _ = mk.plan_decode_units(cfg, lens, batch, q)
+        codes, _ = mk.plan_decode_units(cfg, lens, batch, q, mk.PAGE_E4M3)
+        assert len(codes) == len(plain) and sum(codes) == sum(plain) == sum(lens)
+        tail = q + (max_tail - q) // 2
+        if len(plain) == 1 or tail * len(plain) >= sum(lens) + tail or sum(lens) + tail < 128 * len(plain):
+            assert codes == plain
+            short += len(plain) > 1
+        else:
+            ragged = 8 + 7 * len(lens)                     # (granules of eight tokens, a page's last one may hold one)
+            assert -ragged <= plain[-1] - codes[-1] <= 128 + ragged and codes[-1] <= codes[0] + ragged
+            assert max(codes[:-2] + codes[:1]) - min(codes[:-2] + codes[:1]) <= ragged
+            spared += 1
+    assert spared > 50 and short > 30
+    cfg = mk.make_config(2, 16, 4, 128, 4096, "bf16", 500000.0, 1, 1, 8, decode_units=16)
+    assert len(mk.plan_decode_units(cfg, [200], 1, 4, mk.PAGE_E4M3)[0]) == 16
+    with pytest.raises(mk.MatKVError):
+        mk.plan_decode_units(cfg, [200], 1, 4, 2)
+    with pytest.raises(mk.MatKVError):
+        mk.plan_decode_units(mk.make_config(2, 4, 2, 64, 256, "f32", 10000.0, 1, 1, 8), [200], 1, 4, mk.PAGE_E4M3)
+
+
 def test_decode_partition_never_exceeds_the_compute_units(mk):
     """Workgroups of a decode launch = units x KV heads over the batch: at most 256, so that no
     compute unit holds two (batch 3 x 8 KV heads: 10 units each, not 11)."""

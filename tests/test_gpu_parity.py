@@ -879,6 +879,15 @@ def test_recorded_decode_replays_over_either_partition():
             _same_attention(a, b)
 
 
+def test_recorded_decode_of_fixed_units_replays_over_short_compressed_pages():
+    """A step recorded with a fixed number of units over compressed pages replays over caches that leave each of them a few tokens."""
+    caches = [[[400]], [[200]], [[90, 31]], [[3000]], [[200]]]
+    got = _decode_batch(32, caches[0], [5], True, 16, replays=caches)
+    want = _decode_batch(32, caches[0], [5], True, 1, replays=caches)
+    for a, b in zip(got, want):
+        _same_attention(a, b)
+
+
 @pytest.mark.parametrize("repeats,extra,hidden,launches", [
     (1, None, 4096, 3), (31, None, 4096, 63), (32, None, 4096, 0),      # long kernels: up to 64 launches
     (31, "advance", 4096, 64), (32, "advance", 4096, 0),                # (one kernel more)
