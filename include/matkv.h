@@ -309,6 +309,9 @@ int32_t matkv_plan_shared_units(const matkv_config* cfg, const int32_t* page_ids
  * argument.  A matter of speed: results are the same bit for bit. */
 int32_t matkv_plan_decode_streams(const matkv_config* cfg, const int32_t* page_ids_host, const int32_t* page_tokens_host,
                                   const int32_t* n_pages_host, const int32_t* q_len_host, int32_t batch, int32_t format);
+/* The same for matkv_decode_step, whose launch over a batch that shares few pages reads every instance's cache for itself. */
+int32_t matkv_plan_step_streams(const matkv_config* cfg, const int32_t* page_ids_host, const int32_t* page_tokens_host,
+                                const int32_t* n_pages_host, const int32_t* q_len_host, int32_t batch, int32_t format);
 /* Decode work units of the table's shared partition, 0 if matkv_assemble built none, -1 if the
  * table is unknown.  When two or more instances of a batch point at the same slot (the same
  * chunk, retrieved by several requests), matkv_assemble cuts the batch's DISTINCT pages and its

@@ -29,7 +29,7 @@ EXPORTS = [
     "matkv_prefill_attn", "matkv_decode_attn", "matkv_decode_step", "matkv_graph_begin", "matkv_graph_end",
     "matkv_graph_launch", "matkv_graph_destroy", "matkv_graph_kernel_launches", "matkv_plan_decode_units", "matkv_plan_decode_units_of", "matkv_probe_read",
     "matkv_table_shared_units", "matkv_plan_projection", "matkv_plan_prefill",
-    "matkv_plan_shared_units", "matkv_plan_even_units", "matkv_plan_decode_streams", "matkv_decode_attn_static",
+    "matkv_plan_shared_units", "matkv_plan_even_units", "matkv_plan_decode_streams", "matkv_plan_step_streams", "matkv_decode_attn_static",
 ]
 
 
@@ -111,8 +111,9 @@ def _load_library():
     lib.matkv_plan_decode_units_of.restype = c_int32
     lib.matkv_plan_even_units.argtypes = [cfgp] + [POINTER(c_int32)] * 3 + [c_int32, c_int32, POINTER(c_int32), c_int32, POINTER(c_int32), POINTER(c_int32)]
     lib.matkv_plan_even_units.restype = c_int32
-    lib.matkv_plan_decode_streams.argtypes = [cfgp] + [POINTER(c_int32)] * 4 + [c_int32, c_int32]
-    lib.matkv_plan_decode_streams.restype = c_int32
+    for fn in (lib.matkv_plan_decode_streams, lib.matkv_plan_step_streams):
+        fn.argtypes = [cfgp] + [POINTER(c_int32)] * 4 + [c_int32, c_int32]
+        fn.restype = c_int32
     lib.matkv_plan_projection.argtypes = [cfgp, c_int32]; lib.matkv_plan_projection.restype = c_int32
     lib.matkv_plan_prefill.argtypes = [cfgp] + [POINTER(c_int32)] * 3 + [c_int32, c_int32, POINTER(c_int32)]
     lib.matkv_plan_prefill.restype = c_int32
@@ -215,19 +216,28 @@ def plan_even_units(cfg: Config, page_tokens, q_lens, format: int = PAGE_PLAIN):
     return runs, ([(slots[2 * b], slots[2 * b + 1]) for b in range(batch)] if n else None), bool(taken.value)
 
 
-def plan_decode_streams(cfg: Config, pages, q_lens, format: int = PAGE_PLAIN) -> bool:
-    """Whether decode launches over the batch's table read the cache past the last-level cache.  pages: per instance a list of
-    (page id, tokens)."""
+def _plan_streams(fn, name, cfg, pages, q_lens, format) -> bool:
     batch, mp = len(pages), max(cfg.max_pages, 1)
     ids, toks = (c_int32 * (batch * mp))(), (c_int32 * (batch * mp))()
     for b, plist in enumerate(pages):
         for i, (pid, n) in enumerate(plist[:mp]):
             ids[b * mp + i], toks[b * mp + i] = pid, n
     npg, ql = (c_int32 * batch)(*[len(p) for p in pages]), (c_int32 * batch)(*q_lens)
-    r = int(_lib.matkv_plan_decode_streams(byref(cfg), ids, toks, npg, ql, batch, format))
+    r = int(fn(byref(cfg), ids, toks, npg, ql, batch, format))
     if r < 0:
-        raise MatKVError(EINVAL, "matkv_plan_decode_streams")
+        raise MatKVError(EINVAL, name)
     return bool(r)
+
+
+def plan_decode_streams(cfg: Config, pages, q_lens, format: int = PAGE_PLAIN) -> bool:
+    """Whether decode launches over the batch's table read the cache past the last-level cache.  pages: per instance a list of
+    (page id, tokens)."""
+    return _plan_streams(_lib.matkv_plan_decode_streams, "matkv_plan_decode_streams", cfg, pages, q_lens, format)
+
+
+def plan_step_streams(cfg: Config, pages, q_lens, format: int = PAGE_PLAIN) -> bool:
+    """The same for matkv_decode_step."""
+    return _plan_streams(_lib.matkv_plan_step_streams, "matkv_plan_step_streams", cfg, pages, q_lens, format)
 
 
 def plan_projection(cfg: Config, n_rows: int) -> int:

@@ -290,8 +290,6 @@ __device__ __forceinline__ void projection_tasks(const KernelArgs& a, const Step
     }
 }
 
-constexpr int kFusedMaxBatch = 4;
-
 // Shared decode units: fold, for every user of this unit at whose counter the workgroup arrived
 // last (the first n_live entries of live), that instance's partial slots into its G output rows - all such users at once.
 // users[u] = {instance, this unit's slot, first slot, slots}.
@@ -828,9 +826,7 @@ bool decode_step_supported(const AttnArgs& a, const MaterializeArgs& m, int dtyp
     // batches) lose outright: the decode kernel wants exactly one attention workgroup per
     // compute unit - a second resident workgroup of any kind on a compute unit stretches the
     // launch by a third (batch 16: 57 us with 256 workgroups, 83 us with 264).
-    return attn_mfma_supported(a, dtype) && !a.prefill && !a.shared && a.variant == 0 &&
-           ((m.Hd % 4096) == 0 || (m.Hd % 3072) == 0) &&
-           a.batch >= 1 && a.batch <= kFusedMaxBatch && a.Hq / a.Hkv <= 4;
+    return !a.prefill && !a.shared && a.variant == 0 && fused_step_shape(dtype, a.D, a.Hq / a.Hkv, m.Hd, a.batch);
 }
 
 hipError_t launch_decode_step(const AttnArgs& a, const MaterializeArgs& m, int dtype, hipStream_t s) {

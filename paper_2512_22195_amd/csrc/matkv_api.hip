@@ -21,6 +21,7 @@
 #include <numeric>
 #include <queue>
 #include <thread>
+#include <tuple>
 #include <unordered_map>
 #include <vector>
 
@@ -73,7 +74,7 @@ struct TableHost {
     int min_tail_len = 0;
     int n_decode_slots = 0;   // partial slots a decode launch writes (units, or (unit, user) pairs when shared)
     bool step_by_instance = false;      // a fused decode step reads every instance's cache for itself, beside a shared partition
-    bool past_llc = false;    // decode launches leave the cache's rows out of the last-level cache (rows_pass_llc)
+    bool past_llc = false, step_past_llc = false;   // decode launches, fused steps leave the cache's rows out of the last-level cache (rows_pass_llc)
     std::vector<const void*> slots;   // distinct slots its pages point into
 };
 
@@ -936,14 +937,19 @@ bool even_partition(const matkv_config& cfg, int batch, int n_dunits) {
 //    1.3 +2 %, 1.6 0, 3 -2 %, more -5 %.  So 9/8.  us per layer, left there / passing by, 4 layers: sixteen 70B users of the same 5000 tokens 20.8 / 26.4, of 5 in 20
 //    chunks 45.8 / 51.7, 24 of 5 in 60 74.1 / 80.1.  Over 18147 such steps the slower of the two is taken for 0.2 % of the time; with the tokens walked for
 //    the distinct ones it was 1.9 %.
+//    A fused step over shared pages (four users at most, each walks all of its own) is worth that only where the weights exceed the cache; where they fit, keeping
+//    them there is worth more.  us per layer step, passing by / left there: 8B, 32 layers, two users, 5000 tokens in common and 1000 of their own 16.5 / 15.2, 4000
+//    19.7 / 19.1, four with 3500 and 3000 24.3 / 22.4, compressed, two with 9000 and 4000 17.5 / 16.9; 3B, three with 3500 and 8000 33.8 / 29.5; of 17 seeded
+//    batches 1.045 times as fast in the mean, 0.995 at least.  Weights that fit: 8B, 14 layers, two with 770 and 2000 compressed 11.0 / 12.7, 8 layers, two with
+//    1200 and 2000 12.8 / 13.0, four with 3500 and 3000 23.5 / 22.5; of 53 batches 0.991 in the mean, 0.87 at least.
 // Over 8196 steps without shared pages (plain and compressed) the better of the two is taken but for 0.2 % of the time; where all beyond 256 MB passed by it was 1.6 %.
 constexpr size_t kStreamedLayerBytes = (size_t)24 << 20, kStreamedCodeBytes = (size_t)7 << 20;
 constexpr int kStreamedWalks = 160, kStreamedWalksFar = 208;
-bool rows_pass_llc(const matkv_config& cfg, size_t distinct, size_t streamed, size_t tail_rows, size_t longest, int kv_fmt) {
-    if (8 * streamed > 9 * distinct) return false;
+bool rows_pass_llc(const matkv_config& cfg, size_t distinct, size_t streamed, size_t tail_rows, size_t longest, int kv_fmt, bool fused_step = false) {
     const size_t row = 2 * (size_t)cfg.n_kv_heads * cfg.head_dim, esz = cfg.dtype == MATKV_BF16 ? 2 : 4, llc = kLastLevelCacheBytes;
     const size_t layer = row * (distinct * (kv_fmt == MATKV_PAGE_E4M3 ? 1 : esz) + tail_rows * esz);
     const size_t weights = row * cfg.hidden * esz * cfg.n_layers;
+    if (8 * streamed > 9 * distinct && (!fused_step || weights > llc)) return false;
     if (layer * cfg.n_layers + weights <= llc + llc / 16) return false;
     const double over = weights > llc ? std::min(1.0, (double)(weights - llc) / (double)(llc / 8)) : 0.0;      // 1: nothing of the weights is found again
     const double walks = (double)cfg.n_kv_heads * (double)(streamed + tail_rows) / (double)std::max<size_t>(longest, 1);
@@ -971,8 +977,7 @@ std::pair<size_t, size_t> count_page_tokens(const matkv_config& cfg, const matkv
 // three, 39 22.0 -> 18.1 in four layers, 65 23.5 -> 26.1; four, 39 24.6 -> 22.2, 61 22.9 -> 22.1, 74 23.5 -> 24.1.  3B: two, 41 20.8 -> 21.1, four, 61 21.3 -> 21.0.  Of
 // compressed pages (8B) two, 20 18.6 -> 13.3, 41 22.5 -> 23.0, four, 61 25.3 -> 23.8; (3B) four, 74 24.2 -> 25.2.  Long caches end it: with 5 to 25 % of the uses
 // shared, four users of 82 MB 1.04 to 1.24 times as fast, 131 MB in all 1.05, 164 1.00 to 1.06, 184 1.02, 246 0.985.
-bool step_by_instance(const matkv_config& cfg, const matkv_page* pages, const int32_t* n_pages, int batch, int kv_fmt) {
-    const auto [uses, distinct] = count_page_tokens(cfg, pages, n_pages, batch);
+bool step_by_instance(const matkv_config& cfg, size_t uses, size_t distinct, int batch, int kv_fmt) {
     const size_t row = (size_t)2 * cfg.n_kv_heads * cfg.head_dim * (kv_fmt == MATKV_PAGE_E4M3 ? 1 : 2);
     return (uses - distinct) * row <= (size_t)batch * 12000000 && uses * row <= 192000000;
 }
@@ -996,6 +1001,7 @@ DecodeCut decode_cut(const matkv_config& cfg, int batch, long page_tokens, int q
 struct DecodeLayout {
     int n_dunits = 0, n_sunits = 0;
     bool even_built = false, even = false, past_llc = false;
+    bool step_by_instance = false, step_past_llc = false;       // of a decode step in one launch
 };
 template <typename ScalesOff>
 DecodeLayout lay_out_decode(const matkv_config& cfg, const TableLayout& tl, const matkv_page* pages, const int32_t* n_pages, int batch, int kv_fmt,
@@ -1018,17 +1024,32 @@ DecodeLayout lay_out_decode(const matkv_config& cfg, const TableLayout& tl, cons
         L.even_built = true;
         L.even = build_even_units(cfg, pages, n_pages, batch, insts, items, n_items, dunits, L.n_dunits, runs, kv_fmt);
     }
-    size_t streamed = 0, tail_rows = 0, longest = 0;
-    auto walk = [&](const Unit& u) {
-        const size_t tail = u.has_tail ? insts[u.inst].q_len : 0;
-        streamed += u.page_tokens; tail_rows += tail;
-        longest = std::max(longest, u.page_tokens + tail);
+    size_t uses = 0, distinct = 0;                  // page tokens, counted when they are first asked for
+    auto count = [&]() { if (uses == 0) std::tie(uses, distinct) = count_page_tokens(cfg, pages, n_pages, batch); };
+    auto past_llc = [&](auto unit, int n_units, bool fused_step) {      // of a launch over n_units units, unit(u) one of them
+        size_t streamed = 0, tail_rows = 0, longest = 0;
+        for (int u = 0; u < n_units; ++u) {
+            const Unit& un = unit(u);
+            const size_t tail = un.has_tail ? insts[un.inst].q_len : 0;
+            streamed += un.page_tokens; tail_rows += tail;
+            longest = std::max(longest, un.page_tokens + tail);
+        }
+        if (!rows_pass_llc(cfg, streamed, streamed, tail_rows, longest, kv_fmt)) return false;      // (with fewer distinct ones it is no other)
+        count();
+        return rows_pass_llc(cfg, distinct, streamed, tail_rows, longest, kv_fmt, fused_step);
     };
-    if (L.even)              for (int u = 0; u < 256 / cfg.n_kv_heads && runs[u].n_users > 0; ++u) walk(runs[u].u);
-    else if (L.n_sunits > 0) for (int u = 0; u < L.n_sunits; ++u) walk(sunits[u].u);
-    else                     for (int u = 0; u < L.n_dunits; ++u) walk(dunits[u]);
-    if (rows_pass_llc(cfg, streamed, streamed, tail_rows, longest, kv_fmt)) {       // (with fewer distinct ones it is no other without this)
-        L.past_llc = rows_pass_llc(cfg, count_page_tokens(cfg, pages, n_pages, batch).second, streamed, tail_rows, longest, kv_fmt);
+    auto by_instance = [&](int u) -> const Unit& { return dunits[u]; };
+    int n_runs = 0;
+    while (L.even && n_runs < 256 / cfg.n_kv_heads && runs[n_runs].n_users > 0) ++n_runs;
+    if (L.even)              L.past_llc = past_llc([&](int u) -> const Unit& { return runs[u].u; }, n_runs, false);
+    else if (L.n_sunits > 0) L.past_llc = past_llc([&](int u) -> const Unit& { return sunits[u].u; }, L.n_sunits, false);
+    else                     L.past_llc = past_llc(by_instance, L.n_dunits, false);
+    L.step_past_llc = L.past_llc;
+    // (a fused step over the units by instance walks a shared page once for each of its users: its own answer)
+    if (L.n_sunits > 0 && fused_step_shape(cfg.dtype, cfg.head_dim, cfg.n_q_heads / cfg.n_kv_heads, cfg.hidden, batch)) {
+        count();
+        L.step_by_instance = step_by_instance(cfg, uses, distinct, batch, kv_fmt);
+        if (L.step_by_instance) L.step_past_llc = past_llc(by_instance, L.n_dunits, true);
     }
     return L;
 }
@@ -1757,7 +1778,7 @@ matkv_status matkv_assemble(matkv_ctx* c, const matkv_page* pages, const int32_t
                                                reinterpret_cast<SUnit*>(h + c->tl.off_sunits), scales_off);
     const int n_dunits = decode.n_dunits, n_sunits = decode.n_sunits;
     th.even = decode.even; th.past_llc = decode.past_llc;
-    th.step_by_instance = n_sunits > 0 && step_by_instance(cfg, pages, n_pages, batch, kv_fmt);
+    th.step_by_instance = decode.step_by_instance; th.step_past_llc = decode.step_past_llc;
     // prefill: coarse partition (the question rows supply most of the parallelism)
     th.prefill = lay_out_prefill(cfg, pages, n_pages, q_len, batch, kv_fmt == MATKV_PAGE_E4M3, insts, items, &n_items, punits, scales_off);
     const size_t dunit_bytes = sizeof(Unit) * n_dunits + (decode.even_built ? sizeof(SUnit) * (256 / cfg.n_kv_heads) : 0);
@@ -1946,8 +1967,8 @@ int32_t matkv_plan_shared_units(const matkv_config* cfg, const int32_t* page_ids
     MATKV_CATCH_INT
 }
 
-int32_t matkv_plan_decode_streams(const matkv_config* cfg, const int32_t* page_ids, const int32_t* page_tokens, const int32_t* n_pages,
-                                  const int32_t* q_len, int32_t batch, int32_t format) {
+static int32_t plan_streams(const matkv_config* cfg, const int32_t* page_ids, const int32_t* page_tokens, const int32_t* n_pages,
+                            const int32_t* q_len, int32_t batch, int32_t format, bool step) {
     const char* why;
     if (check_config(cfg, &why) != MATKV_OK) return -1;
     if (!n_pages || !q_len || batch < 1 || batch > cfg->max_batch || (format != MATKV_PAGE_PLAIN && format != MATKV_PAGE_E4M3)) return -1;
@@ -1961,9 +1982,20 @@ int32_t matkv_plan_decode_streams(const matkv_config* cfg, const int32_t* page_i
     std::vector<Unit> units((size_t)tl.max_dunits);
     std::vector<SUnit> sunits((size_t)tl.max_sunits);
     int n_items = 0;
-    return lay_out_decode(*cfg, tl, pages.data(), n_pages, batch, format, insts.data(), items.data(), &n_items, units.data(), sunits.data(),
-                          [](int) { return (size_t)0; }).past_llc;
+    const DecodeLayout L = lay_out_decode(*cfg, tl, pages.data(), n_pages, batch, format, insts.data(), items.data(), &n_items, units.data(),
+                                          sunits.data(), [](int) { return (size_t)0; });
+    return step ? L.step_past_llc : L.past_llc;
     MATKV_CATCH_INT
+}
+
+int32_t matkv_plan_decode_streams(const matkv_config* cfg, const int32_t* page_ids, const int32_t* page_tokens, const int32_t* n_pages,
+                                  const int32_t* q_len, int32_t batch, int32_t format) {
+    return plan_streams(cfg, page_ids, page_tokens, n_pages, q_len, batch, format, false);
+}
+
+int32_t matkv_plan_step_streams(const matkv_config* cfg, const int32_t* page_ids, const int32_t* page_tokens, const int32_t* n_pages,
+                                const int32_t* q_len, int32_t batch, int32_t format) {
+    return plan_streams(cfg, page_ids, page_tokens, n_pages, q_len, batch, format, true);
 }
 
 int32_t matkv_plan_even_units(const matkv_config* cfg, const int32_t* page_tokens, const int32_t* n_pages, const int32_t* q_len, int32_t batch,
@@ -2143,7 +2175,7 @@ matkv_status matkv_decode_step(matkv_ctx* c, int32_t layer, const void* hidden, 
     materialize_scratch(c, m);
     AttnArgs step = a;
     if (th->step_by_instance) {         // (every table has these units)
-        step.shared = 0;
+        step.shared = 0; step.past_llc = th->step_past_llc;
         step.n_units = th->n_dunits; step.off_units = c->tl.off_dunits;
     }
     if (decode_step_supported(step, m, c->cfg.dtype)) {

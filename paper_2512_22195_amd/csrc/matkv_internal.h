@@ -238,6 +238,11 @@ hipError_t launch_materialize_staged(const MaterializeArgs& a, int total_rows, h
 hipError_t launch_materialize_fewrows(const MaterializeArgs& a, int total_rows, hipStream_t s);
 bool decode_step_rows_supported(const AttnArgs& a, const MaterializeArgs& m, int dtype);
 hipError_t launch_decode_step_rows(const AttnArgs& a, const MaterializeArgs& m, int dtype, hipStream_t s);   // fp32: both in one launch
+// Configurations and batches whose decode step can be the fused launch (the reasons stand at decode_step_supported).
+constexpr int kFusedMaxBatch = 4;
+inline bool fused_step_shape(int dtype, int D, int group, int hidden, int batch) {
+    return dtype == MATKV_BF16 && D == 128 && group_size_built(group) && group <= 4 && (hidden % 4096 == 0 || hidden % 3072 == 0) && batch >= 1 && batch <= kFusedMaxBatch;
+}
 bool decode_step_supported(const AttnArgs& a, const MaterializeArgs& m, int dtype);
 hipError_t launch_decode_step(const AttnArgs& a, const MaterializeArgs& m, int dtype, hipStream_t s);   // projection + attention
 hipError_t launch_probe_read(const void* src, size_t bytes, unsigned* sink, hipStream_t s);

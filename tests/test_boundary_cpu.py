@@ -263,6 +263,32 @@ def test_decode_streams_only_rows_that_displace_something(mk):
             mk.plan_decode_streams(cfg, *bad)
 
 
+def test_fused_step_over_shared_pages_decides_for_its_own_walk(mk):
+    """Host logic: a fused decode step beside a shared partition walks a shared page once for each of its users.  Where that is more than 9/8 of the
+    distinct tokens and the weights alone exceed the last-level cache its rows stay there, whatever launches over the shared units
+    do; where it is fewer, where the weights fit (8 and 16 layers), and where the step is not that launch, both say the same."""
+    def plans(common, own, batch=2, layers=32, Hq=32, fmt=mk.PAGE_PLAIN):
+        cfg = mk.make_config(layers, Hq, 8, 128, {24: 3072, 32: 4096, 64: 8192}[Hq], "bf16", 500000.0, batch, 2, 64)
+        ids = [[(0, common), (1 + b, own)] for b in range(batch)]
+        assert mk.plan_shared_units(cfg, ids, [32] * batch)[0]
+        return mk.plan_decode_streams(cfg, ids, [32] * batch, fmt), mk.plan_step_streams(cfg, ids, [32] * batch, fmt)
+
+    for layers in (18, 32):
+        for own in (2500, 4000):                                    # 1.4 to 1.5 tokens walked per distinct one
+            assert plans(5000, own, layers=layers) == (True, False)
+        assert plans(3500, 3000, 4, layers) == (True, False) and plans(9000, 4000, layers=layers, fmt=mk.PAGE_E4M3) == (True, False)
+        assert plans(700, 6000, layers=layers) == (True, True)      # 1.06
+        assert plans(700, 6000, 6, layers) == (True, True)          # two launches: five users and more, eight heads to a KV head, many shared pages
+        assert plans(5000, 4000, layers=layers, Hq=64) == (True, True) and plans(6000, 4000, layers=layers) == (True, True)
+    for layers in (8, 16):
+        assert plans(5000, 4000, layers=layers) == (True, True) and plans(3500, 3000, 4, layers) == (True, True)
+    assert plans(5000, 4000, layers=2) == (False, False)
+    cfg = mk.make_config(4, 32, 8, 128, 4096, "bf16", 500000.0, 4, 8, 64)
+    assert mk.plan_step_streams(cfg, [[(b, 5000)] for b in range(4)], [32] * 4)     # no shared pages
+    with pytest.raises(mk.MatKVError):
+        mk.plan_step_streams(cfg, [[(0, 5)]], [65])
+
+
 def test_shared_partition_covers_every_instance_once(mk):
     """Host logic of the shared decode partition: built when the batch's distinct pages are at least
     a twentieth fewer tokens than all uses; every (instance, page token) is streamed by exactly one
