@@ -11,6 +11,7 @@
 #include <unistd.h>
 
 #include <algorithm>
+#include <climits>
 #include <atomic>
 #include <condition_variable>
 #include <functional>
@@ -373,46 +374,92 @@ double prefill_form_time(int tile_rows, bool codes, long workgroups, long walk_t
 struct PrefillShape {           // of an instance
     long rows, tokens, pieces;  // (question row, query head of one KV head) rows; cache and question; pages and tail
 };
-double prefill_tiles_time(const std::vector<PrefillShape>& shapes, int Hkv, bool codes, int tile_rows, int most_units, double worth) {
-    struct Constants { double start, workgroup, step, half_step, mb_once, mb_tile, mb_partial, fold; };
-    static const Constants kForms[2][2] = {{{3.2, 3.1, 1.55, 1.55, 0.08, 0.126, 0.46, 3.6}, {2.2, 3.6, 1.46, 1.06, 0.02, 0.20, 0.39, 4.5}},
-                                           {{3.0, 3.3, 2.0, 2.0, 0.10, 0.20, 0.40, 4.3}, {2.9, 2.7, 1.75, 1.30, 0.02, 0.32, 0.38, 4.9}}};
-    const Constants& k = kForms[codes][tile_rows > 128];
-    const int slots = std::max(1, std::min(256, 256 / Hkv));
-    const double row_mb = Hkv * (codes ? 256e-6 : 512e-6);
-    struct Job { double us; long n; int tile; };
-    std::vector<Job> jobs;
-    double total = 0, longest = 0, read = 0, partials = 0;
-    long n_jobs = 0;
-    bool cut = false;
-    for (const PrefillShape& s : shapes) {
-        const long u = std::max<long>(1, std::min<long>(most_units, s.tokens / 64)), tiles = (s.rows + tile_rows - 1) / tile_rows;
-        const double pieces = (double)s.pieces / u + 1.0 - 1.0 / u, blocks = std::max((double)s.tokens / u / 64 + 0.5 * pieces, pieces);
-        const double steps = ceil(tile_rows > 128 ? blocks : 0.5 * blocks);
-        for (long t = 0; t < tiles; ++t) {
-            const bool half = tile_rows > 128 && s.rows - t * tile_rows <= 128;
-            const double us = k.workgroup + steps * (half ? k.half_step : k.step);
-            jobs.push_back({us, u, (int)t});
-            total += us * u; longest = std::max(longest, us); n_jobs += u;
+class PrefillTiles {
+public:
+    PrefillTiles(const std::vector<PrefillShape>& shapes, int Hkv, bool codes, int tile_rows)
+        : shapes_(shapes), tile_rows_(tile_rows), Hkv_(Hkv), slots_(std::max(1, std::min(256, 256 / Hkv))) {
+        static const Constants kForms[2][2] = {{{3.2, 3.1, 1.55, 1.55, 0.08, 0.126, 0.46, 3.6}, {2.2, 3.6, 1.46, 1.06, 0.02, 0.20, 0.39, 4.5}},
+                                               {{3.0, 3.3, 2.0, 2.0, 0.10, 0.20, 0.40, 4.3}, {2.9, 2.7, 1.75, 1.30, 0.02, 0.32, 0.38, 4.9}}};
+        k_ = kForms[codes][tile_rows > 128];
+        const double row_mb = Hkv * (codes ? 256e-6 : 512e-6);
+        double read = 0, whole = 0;
+        for (const PrefillShape& s : shapes) {
+            const Tiles t = tiles(s);
+            read += row_mb * s.tokens * (k_.mb_once + k_.mb_tile * (t.full + t.half));
+            whole += (t.full * k_.step + t.half * k_.half_step) * s.tokens * (tile_rows > 128 ? 1.0 / 64 : 1.0 / 128);
+            n_tiles_ += t.full + t.half;
+            rows_ += s.rows;
+            least_tokens_ = std::min(least_tokens_, s.tokens);
         }
-        read += row_mb * s.tokens * (k.mb_once + k.mb_tile * tiles);
-        if (u > 1) { cut = true; partials += (double)s.rows * Hkv * u * 528e-6; }
+        read4_ = read * read * read * read;
+        walk_ = (whole + k_.workgroup * n_tiles_) / slots_;
     }
-    const double other = k.start + (cut ? k.fold + partials * k.mb_partial : 0.0), read4 = pow(read, 4);
-    auto launch = [&](double walk) { return other + pow(pow(walk, 4) + read4, 0.25); };
-    const double least = launch(std::max(longest, total / slots));
-    if (n_jobs <= slots || least >= worth) return least;
-    std::stable_sort(jobs.begin(), jobs.end(), [](const Job& a, const Job& b) { return a.tile < b.tile; });
-    std::priority_queue<double, std::vector<double>, std::greater<double>> busy(std::greater<double>(), std::vector<double>(slots, 0.0));
-    double end = 0;
-    for (const Job& j : jobs)
-        for (long i = 0; i < j.n; ++i) {
-            const double t = busy.top() + j.us;
-            busy.pop(); busy.push(t);
-            end = std::max(end, t);
+    // Every cache in up to `units` units: no launch takes less than floor(), which grows with them, nor less than what bounds() finds with a look at
+    // every instance, nor more than its second; time() deals the workgroups out.
+    double floor(int units) const {
+        const long u = std::min<long>(units, least_tokens_ / 64);           // of every instance at least
+        return launch(walk_, k_.start + (u > 1 ? k_.fold + partials_us((double)rows_ * u) : 0.0));
+    }
+    std::pair<double, double> bounds(int units) {
+        total_ = 0; longest_ = 0; n_jobs_ = 0;
+        double partials = 0, shortest = 1e30;
+        bool cut = false;
+        for (const PrefillShape& s : shapes_) {
+            const Job j = job(s, units);
+            const Tiles t = tiles(s);
+            shortest = std::min(shortest, t.half ? j.half_us : j.us);
+            total_ += (t.full * j.us + t.half * j.half_us) * j.n;
+            longest_ = std::max(longest_, t.full ? j.us : j.half_us);
+            n_jobs_ += (t.full + t.half) * j.n;
+            if (j.n > 1) { cut = true; partials += (double)s.rows * j.n; }
         }
-    return launch(end);
-}
+        other_ = k_.start + (cut ? k_.fold + partials_us(partials) : 0.0);
+        const double mean = total_ / slots_, rounds = (double)((n_jobs_ + slots_ - 1) / slots_);
+        return {launch(std::max({longest_, mean, rounds * shortest}), other_), n_jobs_ <= slots_ ? launch(longest_, other_) : launch(mean + longest_, other_)};
+    }
+    double time(int units) {
+        const double least_us = bounds(units).first;
+        if (n_jobs_ <= slots_) return least_us;
+        std::priority_queue<double, std::vector<double>, std::greater<double>> busy(std::greater<double>(), std::vector<double>(slots_, 0.0));
+        double end = 0;
+        for (long dealt = 0, tile = 0; dealt < n_tiles_; ++tile)            // launch order: the first tiles of all, then the second
+            for (const PrefillShape& s : shapes_) {
+                const Tiles t = tiles(s);
+                if (tile >= t.full + t.half) continue;
+                const Job j = job(s, units);
+                for (long i = 0; i < j.n; ++i) {
+                    const double us = busy.top() + (tile < t.full ? j.us : j.half_us);
+                    busy.pop(); busy.push(us);
+                    end = std::max(end, us);
+                }
+                ++dealt;
+            }
+        return launch(end, other_);
+    }
+private:
+    struct Constants { double start, workgroup, step, half_step, mb_once, mb_tile, mb_partial, fold; };
+    struct Tiles { long full, half; };          // of an instance; half: its last tile of 256, with at most 128 rows
+    struct Job { double us, half_us; long n; }; // workgroups of an instance's tile, and how long each takes
+    Tiles tiles(const PrefillShape& s) const {
+        const long n = (s.rows + tile_rows_ - 1) / tile_rows_, half = tile_rows_ > 128 && s.rows - (n - 1) * tile_rows_ <= 128;
+        return {n - half, half};
+    }
+    Job job(const PrefillShape& s, int units) const {
+        const long u = std::max<long>(1, std::min<long>(units, s.tokens / 64));
+        const double pieces = (double)s.pieces / u + 1.0 - 1.0 / u, blocks = std::max((double)s.tokens / u / 64 + 0.5 * pieces, pieces);
+        const double steps = ceil(tile_rows_ > 128 ? blocks : 0.5 * blocks);
+        return {k_.workgroup + steps * k_.step, k_.workgroup + steps * k_.half_step, u};
+    }
+    double partials_us(double rows) const { return rows * Hkv_ * 528e-6 * k_.mb_partial; }
+    // (walk and reading near one another add up)
+    double launch(double walk, double other) const { return other + sqrt(sqrt(walk * walk * walk * walk + read4_)); }
+
+    const std::vector<PrefillShape>& shapes_;
+    const int tile_rows_, Hkv_, slots_;
+    Constants k_;
+    long n_tiles_ = 0, rows_ = 0, least_tokens_ = LONG_MAX, n_jobs_ = 0;
+    double read4_ = 0, walk_ = 0, total_ = 0, longest_ = 0, other_ = 0;
+};
 
 // Cuts one instance's cache (its pages in order, then its tail) into n_units runs of nearly
 // equal token counts, in 8-token granules.  A run is a list of items (page pieces); the tail
@@ -510,16 +557,24 @@ PrefillLayout lay_out_prefill(const matkv_config& cfg, const matkv_page* pages, 
             shapes[b] = {(long)q_len[b] * g, tokens[b], (long)n_pages[b] + 1};
             rule_units = std::max(rule_units, choose_prefill_units(cfg, n_tiles, tall, tokens[b], n_pages[b] + 1));
         }
-        const double by_rule = prefill_tiles_time(shapes, cfg.n_kv_heads, codes, tall, rule_units, 1e30);
-        double best = std::min(0.94 * by_rule, by_rule - 1.5);
-        for (int rows : {128, 256}) {
-            const long one_round = 256 / std::max<long>(1, tiles(rows) * cfg.n_kv_heads);
-            long before = 0;
-            for (long u : {1l, 2l, 3l, 4l, 5l, 6l, 8l, 10l, 12l, 16l, 20l, 24l, 32l, std::min<long>(one_round, kMaxPrefillUnitsPerInstance)}) {
-                if (u < 1 || (u > 1 && u > most_tokens / 64) || u == before || tiles(rows) * u > 330) continue;
-                before = u;
-                const double us = prefill_tiles_time(shapes, cfg.n_kv_heads, codes, rows, (int)u, best);
-                if (us < best) { best = us; L.tile_rows = rows; other_units = (int)u; }
+        PrefillTiles forms[2] = {{shapes, cfg.n_kv_heads, codes, 128}, {shapes, cfg.n_kv_heads, codes, 256}};
+        // The rules' own launch is dealt out only where another form's floor is below what it can take at most, and another one only where its bounds are
+        // below the best.  Host us of a layout, without the estimate / every candidate dealt out / this: one 8B user of 10 000 tokens 2.1 / 5.1 / 2.9, sixteen of
+        // 5000 9.5 / 16.5 / 10.5, four over 17 chunks 4.1 / 10.0 / 4.7, four 70B users of 20 000 4.0 / 9.5 / 4.5 (the same layouts for 60 000 seeded tables).
+        auto worth = [](double us) { return std::min(0.94 * us, us - 1.5); };       // another form has to stay below this
+        PrefillTiles& by_rule = forms[tall > 128];
+        if (std::min(forms[0].floor(1), forms[1].floor(1)) < worth(by_rule.bounds(rule_units).second)) {
+            double best = worth(by_rule.time(rule_units));
+            for (int f = 0; f < 2; ++f) {
+                const long tiles_in_batch = tiles(f ? 256 : 128), one_round = 256 / std::max<long>(1, tiles_in_batch * cfg.n_kv_heads);
+                long before = 0;
+                for (long u : {1l, 2l, 3l, 4l, 5l, 6l, 8l, 10l, 12l, 16l, 20l, 24l, 32l, std::min<long>(one_round, kMaxPrefillUnitsPerInstance)}) {
+                    if (u < 1 || (u > 1 && u > most_tokens / 64) || u == before || tiles_in_batch * u > 330) continue;
+                    before = u;
+                    if (forms[f].floor((int)u) >= best || forms[f].bounds((int)u).first >= best) continue;
+                    const double us = forms[f].time((int)u);
+                    if (us < best) { best = us; L.tile_rows = f ? 256 : 128; other_units = (int)u; }
+                }
             }
         }
     }

@@ -393,6 +393,30 @@ def test_prefill_layout_takes_short_tiles_for_short_questions(mk):
             mk.plan_prefill(cfg, *bad)
 
 
+def test_prefill_layout_estimate_costs_little(mk):
+    """Host time: the estimate of the launch's time (from 640 tokens on) adds less than half of what a layout takes without it (with every
+    candidate dealt out it doubled it).  Best of many calls, the two lengths in turn."""
+    import ctypes
+    import time
+    i32, B, n = ctypes.c_int32, 4, 3
+    cfg = mk.make_config(2, 32, 8, 128, 4096, "bf16", 500000.0, B, n, 256)
+
+    def call(tokens):
+        lens = [(tokens - 70) // n] * (n - 1)
+        args = (i32 * (B * n))(*((lens + [tokens - 70 - sum(lens)]) * B)), (i32 * B)(*[n] * B), (i32 * B)(*[70] * B), B, 0, None
+        t0 = time.perf_counter()
+        for _ in range(50):
+            assert mk.lib().matkv_plan_prefill(ctypes.byref(cfg), *args) > 0
+        return time.perf_counter() - t0
+
+    for attempt in range(3):                                # (another process may be at work)
+        times = [(call(639), call(640)) for _ in range(100)]
+        without, with_estimate = (min(t) for t in zip(*times))
+        if with_estimate < 1.5 * without:
+            return
+    raise AssertionError(f"{with_estimate / without:.2f} times")
+
+
 def test_prefill_layout_does_not_cut_short_caches_of_a_large_batch(mk):
     """Host logic: a batch whose row tiles alone nearly fill the chip is cut only into units of 256 tokens and
     more (a cut of a short cache costs more in partials than it saves); smaller batches into units of 128."""
