@@ -293,7 +293,7 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(
     }
     // Nothing more to ask for: the last steps are multiplied as they arrive.  (With all of them waited for at first half a microsecond of
     // multiplying stood alone at the end.)
-    constexpr bool DRAWN = SK == 2 && MI >= 4;
+    constexpr bool DRAWN = SK == 2 && split_partials(MI) == 1;
     int drawn = 0;
     int32_t* const counter = a.ws_counters + (size_t)(rt * nct + ct) * kDecodeCounterStride + wave;
     if (DRAWN && lane == 0) drawn = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // (see below)
@@ -321,7 +321,7 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(
         // 52.0 -> 50.0, 2048 (256) 64.2 -> 61.8.  (In 8-byte pieces chunk passes of 1000 tokens took 397 us for 393, 311 for 309 at hidden 8192.)
         constexpr int NP = XB * 2 * PB;
         const int tile = rt * nct + ct;
-        float* const halves = a.ws_partials + (size_t)tile * SK * 8 * (BM * 16);
+        float* const halves = a.ws_partials + (size_t)tile * split_partials(MI) * 8 * (BM * 16);
         auto leave = [&](float* to) {
 #pragma unroll
             for (int i = 0; i < NP; ++i) {
@@ -427,7 +427,7 @@ hipError_t launch_tiled(const MaterializeArgs& a, int total_rows, hipStream_t s)
     auto halved = [&](int mi) {
         const int64_t tiles = groups(mi);
         return (a.Hd % (2 * BK)) == 0 && tiles * 2 <= 256 && 32 * mi <= most_split_rows(a.Hd, a.table != nullptr) && a.ws_partials &&
-               tiles * 2 * (32 * mi) * D <= a.ws_partial_floats && tiles * kDecodeCounterStride <= a.ws_n_counters;
+               tiles * split_partials(mi) * (32 * mi) * D <= a.ws_partial_floats && tiles * kDecodeCounterStride <= a.ws_n_counters;
     };
     if (halved(1)) return launch_tile<1, 4, 2>(a, total_rows, s);
     if (halved(2)) return launch_tile<2, 4, 2>(a, total_rows, s);

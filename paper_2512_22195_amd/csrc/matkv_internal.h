@@ -127,6 +127,8 @@ inline int max_q_rows(const matkv_config& c) { return c.max_tail_tokens; }
 constexpr int kSplitTiles = 128;    // half the compute units: two workgroups per tile
 // Rows of the tallest projection tile that is split, of a chunk's rows or a question's (materialize_mfma.hip).
 inline int most_split_rows(int hidden, bool question) { return hidden >= 8192 ? 256 : hidden >= 2560 && !question ? 192 : 128; }
+// Partial tiles that the two workgroups of a split tile leave: both theirs up to 96 rows, one of them from 128 rows on (mi: rows / 32).
+constexpr int split_partials(int mi) { return mi >= 4 ? 1 : 2; }
 
 inline WorkspaceLayout workspace_layout(const matkv_config& c) {
     WorkspaceLayout W;
@@ -138,8 +140,8 @@ inline WorkspaceLayout workspace_layout(const matkv_config& c) {
     // on a 128-byte line of its own (the two kinds of launch never overlap, and every counter is
     // back at zero when its launch ends)
     W.n_counters = (size_t)c.max_batch * c.n_kv_heads * (size_t)std::max(max_q_rows(c), kDecodeCounterStride);
-    // (bf16, head_dim 128: the projection GEMM may split the hidden axis over two workgroups per
-    // tile, up to kSplitTiles tiles of up to most_split_rows x 128: a counter line and two fp32 partial tiles each)
+    // (bf16, head_dim 128: the projection GEMM may split the hidden axis over two workgroups per tile, up to kSplitTiles tiles: a counter line each and
+    // what they leave, two fp32 tiles of up to 96 x 128 or one of up to most_split_rows x 128.  Rounded up to two of 128 rows, from hidden 8192 on of 256)
     const bool gemm_split = c.dtype == MATKV_BF16 && c.head_dim == 128;
     if (gemm_split) W.n_counters = std::max(W.n_counters, (size_t)kSplitTiles * kDecodeCounterStride);
     o += ((W.n_counters * sizeof(int32_t)) + 255) & ~(size_t)255;
@@ -148,7 +150,7 @@ inline WorkspaceLayout workspace_layout(const matkv_config& c) {
     size_t dec = (size_t)c.max_batch * kMaxDecodeUnitsPerInstance * stride;
     size_t pre = (size_t)c.max_batch * kMaxPrefillUnitsPerInstance * (size_t)max_q_rows(c) * stride;
     W.partial_floats = dec > pre ? dec : pre;
-    if (gemm_split) W.partial_floats = std::max(W.partial_floats, (size_t)kSplitTiles * 2 * most_split_rows(c.hidden, false) * 128);
+    if (gemm_split) W.partial_floats = std::max(W.partial_floats, (size_t)kSplitTiles * 2 * (c.hidden >= 8192 ? 256 : 128) * 128);
     o += W.partial_floats * sizeof(float);
     W.bytes = (o + 255) & ~(size_t)255;
     return W;

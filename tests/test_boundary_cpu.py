@@ -74,6 +74,14 @@ def test_workspace_and_table_sizes_are_positive_and_aligned(mk):
         assert mk.workspace_bytes(mk.make_config(1, hq, 8, 128, 8192, "bf16", 500000.0, 1, 1, max_tail)) >= 128 * 2 * 256 * 128 * 4
 
 
+def test_workspace_holds_no_more_than_the_split_tiles_leave(mk):
+    """Tiles of 128 rows and more leave one partial each, lower ones two: up to hidden 8192, whose configurations split tiles of up to 192 rows, two
+    of 128 rows hold either.  (Beside the partials: a page and a counter line of each tile.)"""
+    for hidden in (512, 2048, 2560, 3072, 4096, 7168):
+        small = mk.workspace_bytes(mk.make_config(1, 8, 2, 128, hidden, "bf16", 500000.0, 1, 1, 8))
+        assert 128 * 192 * 128 * 4 <= small <= 128 * 2 * 128 * 128 * 4 + 8192 + 128 * 128
+
+
 def test_null_context_is_an_error_not_a_crash(mk):
     assert mk.lib().matkv_destroy(None) == mk.EINVAL
     assert mk.lib().matkv_advance(None, None, 1) == mk.EINVAL
