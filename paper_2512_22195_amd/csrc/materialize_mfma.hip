@@ -100,15 +100,15 @@ __device__ __forceinline__ void rope_cs(const RopeEntry& e, float p, float& c, f
 //    requested, instruction by instruction: all waves' copies at once hold up their matrix instructions.
 //  - behind the loop every wave is on its own: results leave registers as 8 or 16 bytes of a row (its four or two
 //    waves along the features fill 256 bytes), rotated with entries fetched at the start.
-// Two workgroups that share a tile (SK = 2): each wave leaves its fp32 partial in the workspace (agent-scope
-// stores) and arrives at a counter of its own; of a pair the second to arrive adds the other's and finishes, so that the
-// two workgroups share that work too.
-// Measured, us per launch with every layer's weights from HBM, 8 KV heads, with copies, results through LDS and whole workgroups
-// arriving -> now:
+// Two workgroups that share a tile (SK = 2) each hold half of every sum, wave by wave.  Up to 96 rows each wave leaves its fp32 partial in the
+// workspace (agent-scope stores) and arrives at a counter of its own, and of a pair the second to arrive adds the other's and finishes; from 128 rows on one of the
+// pair leaves its half and the other waits for it (below).  Either way the two workgroups share that work too.
+// Measured, us per launch with every layer's weights from HBM, 8 KV heads, when results went through LDS and whole workgroups arrived -> wave by wave, before
+// skewed starts (`first`) and draws:
 //   hidden 4096:  1000 rows 26.3 -> 24.0, 1206 rows 30.9 -> 29.2, 3501 rows 66.9 -> 60.6
 //   hidden 8192:  512 rows 36.3 -> 34.5, 1000 rows 49.7 -> 46.5, 1206 rows 62 -> 50, 2000 rows 73 -> 67
-// (and since then by where on the hidden axis workgroups start, see `first`).  At 1000 rows of hidden 4096 a launch of 37 800 cycles waits 3800 for its first operands, takes 740 for each of 32 steps (44
-// bytes a cycle), then 1900 until its partials have left, 2700 to arrive, 3600 to fetch the other's and 1300 for the results (6500,
+// At 1000 rows of hidden 4096 that launch took 37 800 cycles: 3800 for its first operands, 740 for each of 32 steps (44
+// bytes a cycle), then 1900 until its partials had left, 2700 to arrive, 3600 to fetch the other's and 1300 for the results (6500,
 // 3500 and 7400 for the last three before).  From the last-level cache 512 rows of hidden 8192 would take 24.7 us.
 // Tried and left out: an extra wave that touches the weight rows
 // some steps ahead (-12 % at 512 rows of hidden 8192, +20 % at 64 rows, nothing at 1000), workgroups that share an operand touching it
@@ -296,7 +296,14 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(
     constexpr bool DRAWN = SK == 2 && split_partials(MI) == 1;
     int drawn = 0;
     int32_t* const counter = a.ws_counters + (size_t)(rt * nct + ct) * kDecodeCounterStride + wave;
-    if (DRAWN && lane == 0) drawn = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // (see below)
+    if (DRAWN) {                                                    // (see below)
+        // On an address that all lanes share the compiler makes of it a sum over the wave, whose result it asks for at once: the last steps' copies and the
+        // trip would be waited for before any of them is multiplied.  us per launch, so -> as it is: hidden 4096 1000 rows 24.0 -> 23.9, hidden 3072 1300 24.2 -> 23.8,
+        // hidden 8192 1000 40.5 -> 39.9, 1500 50.9 -> 50.1, 2048 63.0 -> 62.7.
+        uint32_t at = 0;
+        asm volatile("" : "+v"(at));
+        if (lane == 0) drawn = __hip_atomic_fetch_add(counter + at, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     auto wait_left = [&](auto self, int left, auto steps_tag) -> void {
         constexpr int K = decltype(steps_tag)::value;
         if (left >= K || K == 0) wait_steps(steps_tag);         // (what was drawn counts as one more copy: waited for a little early)
@@ -317,8 +324,8 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(
         // drew first, some steps ago, leaves its half, raises the counter once more and is done; the other waits for that.  It waits
         // for a wave that has started and waits for nobody, so the wait ends whatever else the chip does.  That spares it its own stores and a trip
         // to the counter, and the memory half of the writes, for a trip more where both end at once: us per launch, both leave theirs -> one does, hidden
-        // 4096 150 rows (tiles of 32) 14.2 -> 15.6, 300 (64) 16.6 -> 17.2, 512 (64) 18.2 -> 18.6, 1000 (128) 24.2 -> 24.0; hidden 8192 1000 rows 40.6 -> 39.2, 1500 (192)
-        // 52.0 -> 50.0, 2048 (256) 64.2 -> 61.8.  (In 8-byte pieces chunk passes of 1000 tokens took 397 us for 393, 311 for 309 at hidden 8192.)
+        // 4096 150 rows (tiles of 32) 14.2 -> 15.0, 300 (64) 15.9 -> 16.4, 512 (64) 17.9 -> 18.2, 700 (96) 21.6 -> 21.6, 1000 (128) 24.2 -> 23.9; hidden 3072 150 rows 11.7 ->
+        // 12.4, 700 (96) 18.3 -> 18.2; hidden 8192 700 (96) 34.3 -> 34.6, 1000 rows 40.6 -> 39.2, 1500 (192) 52.0 -> 50.0, 2048 (256) 64.2 -> 61.8 (the last four with the draw waited for).  (In 8-byte pieces chunk passes of 1000 tokens took 397 us for 393, 311 for 309 at hidden 8192.)
         constexpr int NP = XB * 2 * PB;
         const int tile = rt * nct + ct;
         float* const halves = a.ws_partials + (size_t)tile * split_partials(MI) * 8 * (BM * 16);
