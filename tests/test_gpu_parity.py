@@ -154,6 +154,35 @@ def test_decode_step_other_shapes_run_two_launches():
     _chain_parity(case, fused=True)
 
 
+def _step_launches(case):
+    """Kernel launches of one decode step of one layer over the case's table (recorded, not run)."""
+    from paper_2512_22195_amd import binding as mk
+    ctx = chain.make_context(case)
+    try:
+        with torch.cuda.stream(ctx.compute_stream):
+            zeros = lambda *shape: torch.zeros(shape, dtype=ctx.torch_dtype, device="cuda")
+            slots = {c: torch.zeros(mk.blob_bytes(ctx.cfg, n), dtype=torch.uint8, device="cuda") for c, n in case.chunk_lens.items()}
+            table, tail = ctx.new_table(), ctx.new_tail()
+            w, x, q = zeros(2, case.Hkv * case.D, case.hidden), zeros(case.batch, case.hidden), zeros(case.batch, case.Hq, case.D)
+            ctx.assemble(chain.pages_of(case, slots), case.q_lens, table)
+            ctx.graph_begin()
+            ctx.decode_step(0, x, w[0], w[1], q, table, tail[0, 0], tail[0, 1], torch.empty_like(q))
+            graph = ctx.graph_end()
+            return ctx.graph_kernel_launches(graph)
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("D,Hq,Hkv,hidden,batch,launches", [
+    (64, 4, 2, 256, 1, 1), (64, 2, 2, 64, 3, 1), (64, 6, 2, 192, 2, 1), (64, 8, 1, 256, 9, 1), (64, 4, 1, 512, 8, 1), (128, 2, 1, 128, 2, 1), (128, 4, 4, 64, 5, 1),
+    (64, 4, 2, 320, 1, 2), (64, 4, 1, 512, 7, 2), (128, 4, 1, 192, 7, 2), (128, 4, 1, 256, 8, 1), (128, 4, 1, 320, 8, 2)])
+def test_fp32_decode_step_launches(D, Hq, Hkv, hidden, batch, launches):
+    """Which fp32 decode steps are one launch: head_dim * hidden up to 16384, 32768 from eight instances on."""
+    case = Case("step-f32-launches", n_layers=1, Hq=Hq, Hkv=Hkv, D=D, hidden=hidden, dtype="f32", chunk_lens={0: 70, 1: 300},
+                retrieved=[[[0, 1], [], [1]][b % 3] for b in range(batch)], q_lens=[1 + b % 5 for b in range(batch)], steps=1)
+    assert _step_launches(case) == launches
+
+
 @pytest.mark.parametrize("use_graph", [False, True])
 @pytest.mark.parametrize("D,Hq,Hkv,hidden,batch", [(64, 4, 2, 256, 1), (64, 2, 2, 64, 3), (64, 6, 2, 192, 2), (64, 8, 1, 256, 9), (64, 4, 1, 512, 8),
                                                    (128, 2, 1, 128, 2), (128, 4, 4, 64, 5), (64, 4, 2, 320, 1)])
@@ -1906,6 +1935,62 @@ def test_decode_step_over_shared_pages(use_graph):
                 chunk_lens={0: 400, 1: 90}, retrieved=[[0, 1], [0], [1, 0], [0]], q_lens=[4, 9, 1, 17],
                 steps=3, rope_base=500000.0, scale=1.0 / 8.0, q_scale=1.0)
     _chain_parity(case, fused=True, use_graph=use_graph)
+
+
+@pytest.mark.parametrize("use_graph", [False, True])
+@pytest.mark.parametrize("Hq,hidden,retrieved", [(8, 4096, [[0, 1], [0], [1, 0], [0], [1]]),      # five instances
+                                                 (8, 1024, [[0, 1], [0], [1, 0]]), (16, 4096, [[0], [0, 1]])])     # hidden, eight heads to a KV head
+def test_decode_step_over_shared_units_in_two_launches(Hq, hidden, retrieved, use_graph):
+    """Decode steps over shared pages that are not the fused launch: projection, then attention over the shared units."""
+    batch = len(retrieved)
+    case = Case(f"shared-step-two-{Hq}-{hidden}", n_layers=2, Hq=Hq, Hkv=2, D=128, hidden=hidden, dtype="bf16", chunk_lens={0: 400, 1: 90},
+                retrieved=retrieved, q_lens=[4, 9, 1, 17, 6][:batch], steps=3, rope_base=500000.0, scale=1.0 / 8.0, q_scale=1.0)
+    assert _step_launches(case) == 2
+    _chain_parity(case, fused=True, use_graph=use_graph)
+
+
+@pytest.mark.parametrize("first", ["few", "many"])
+def test_recorded_step_replays_over_few_and_many_shared_pages(first):
+    """A decode step recorded over a table with few shared pages (the fused launch) replays over one with many (two launches by itself), and the
+    other way round: either equals the two calls it stands for, each within the attention bar of the exact result, so twice that apart."""
+    from paper_2512_22195_amd import binding as mk
+    Hq, Hkv, D, hidden, cap, q_len = 32, 8, 128, 4096, 24, [5, 6]
+    sizes = {"few": (700, 3000), "many": (6000, 400)}           # tokens in common, tokens of one's own; 32 units either way
+    ctx = mk.Context(mk.make_config(1, Hq, Hkv, D, hidden, "bf16", 10000.0, max_batch=2, max_pages=2, max_tail_tokens=cap))
+    try:
+        with torch.cuda.stream(ctx.compute_stream):
+            g = torch.Generator(device="cuda").manual_seed(23)
+            draw = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+            page = lambda n: (draw(1, 2, Hkv, n, D).view(torch.uint8).view(-1), n)
+            pages = {}
+            for name, (common, own) in sizes.items():
+                hot = page(common)
+                pages[name] = [[hot, page(own)], [page(own), hot]]
+            w, q, x, tail, table = draw(2, Hkv * D, hidden) * hidden ** -0.5, draw(2, Hq, D), draw(2, hidden), draw(2, 2, Hkv, cap, D), ctx.new_table()
+            got, want, one, two = torch.empty_like(q), torch.empty_like(q), tail.clone(), tail.clone()
+            ctx.assemble(pages[first], q_len, table)
+            ctx.graph_begin()
+            ctx.advance(table, 1)
+            ctx.decode_step(0, x, w[0], w[1], q, table, one[0], one[1], got)
+            step = ctx.graph_end()
+            assert ctx.graph_kernel_launches(step) == {"few": 2, "many": 3}[first]
+            for name in ("few", "many", "many", "few", "few"):
+                ctx.assemble(pages[name], q_len, table)
+                ctx.advance(table, 1)
+                two.copy_(tail)
+                ctx.materialize_tail(x, w[0], w[1], table, 1, two[0], two[1])
+                ctx.decode_attn(0, q, table, two[0], two[1], want)
+                ctx.assemble(pages[name], q_len, table)
+                one.copy_(tail)
+                got.fill_(7.0)
+                ctx.graph_launch(step)
+                ctx.compute_stream.synchronize()
+                for a, b in ((got, want), (one, two)):
+                    a, b = a.float(), b.float()
+                    assert ((a - b).abs() <= 2 * (2e-2 * b.square().mean().sqrt() + 2.0 ** -8 * b.abs())).all(), name
+            ctx.graph_destroy(step)
+    finally:
+        ctx.close()
 
 
 # ------------------------------------------------------------- seeded random small chains ---
