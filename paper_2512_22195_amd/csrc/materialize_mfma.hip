@@ -164,9 +164,14 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(
     // 1000 (128) 23.8, 24.5, 25.1, 25.7; 8192 1000 42.2, 40.4, 40.7, 41.6.
     // Where the few layers of a small program stay in the last-level cache the wait is shorter and 4 a little too many: chunk passes of the 3B shape, 224
     // tokens, all at step 0 / 1 / 2 / 4: four layers (50 MB) 79.3 / 78.6 / 79.9 / 80.7, eight (three such programs in turn) 183 / 177 / 174 / 170.
+    // Distances are counted in the row tiles that share weight rows on an XCD: all of them where the column tiles are a multiple of four, else every second (SK = 1: every
+    // second, every fourth).  Counted in all of them an odd number of KV heads lay 4 to 8 steps apart: hidden 8192, 3 KV heads, all at step 0 / counted in all / this, 512
+    // rows 22.4 / 32.6 / 19.8, 1300 27.7 / 47.5 / 26.2, 4000 51.5 / 71.7 / 50.0; 5, 300 22.8 / 32.6 / 21.6, 724 27.9 / 41.8 / 26.7; 7, 224 23.5 / 30.3 / 23.1, 1050 37.1 / 40.9 / 38.1 (the
+    // worst); hidden 4096, 5, 724 16.9 / 19.1 / 16.1.  Quarters by column tile instead of by XCD are the same for multiples of four and else 2 to 3 % behind in the mean.
     const int xcd = blockIdx.x & 7;
-    const int first = (SK == 2 ? rt * (MI == 1 ? 4 : MI == 2 ? 3 : nk >= 40 ? 2 : 1) + (xcd >> 1) * (nk / 4)
-                               : (rt >> 1) + (xcd & 3) * nk / 4) % nk;
+    const int neighbour = SK == 2 ? (nct % 4 == 0 ? rt : rt >> 1) : (nct % 4 == 0 ? rt >> 1 : rt >> 2);
+    const int first = (SK == 2 ? neighbour * (MI == 1 ? 4 : MI == 2 ? 3 : nk >= 40 ? 2 : 1) + (xcd >> 1) * (nk / 4)
+                               : neighbour + (xcd & 3) * nk / 4) % nk;
 
     // LDS row r of the weights -> feature.  Sixteen rows are one operand of a matrix instruction, whose results
     // land in lanes by fours of these rows: the order makes a lane's results of its PB low (and of its PB high) operands features in a row.
