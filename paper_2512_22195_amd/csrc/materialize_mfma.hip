@@ -296,8 +296,9 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(
     } else {
         half_step(f0, f1, 0, 1, 0, 0, C0{}, C0{});
     }
-    // Nothing more to ask for: the last steps are multiplied as they arrive.  (With all of them waited for at first half a microsecond of
-    // multiplying stood alone at the end.)
+    // Nothing more to ask for.  Where halves are drawn for, the last steps are multiplied as they arrive; elsewhere all of them are waited for at first, in shorter code.  us
+    // per launch, all waited for -> as they arrive (median of three runs, 8 KV heads): drawn, hidden 4096 1300 rows 27.96 -> 27.80, 1500 29.41 -> 29.20, hidden 8192 1500 49.8 -> 49.5,
+    // 2048 61.6 -> 61.4 (1050 42.6 -> 43.0); not drawn, hidden 512 150 rows 5.8 -> 6.1, hidden 3072 150 11.5 -> 11.9, hidden 4096 224 13.5 -> 13.8, 3501 (one workgroup per tile) 54.0 -> 54.1.
     constexpr bool DRAWN = SK == 2 && split_partials(MI) == 1;
     int drawn = 0;
     int32_t* const counter = a.ws_counters + (size_t)(rt * nct + ct) * kDecodeCounterStride + wave;
@@ -315,7 +316,8 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(
         else if constexpr (K > 0) self(self, left, std::integral_constant<int, K - 1>{});
     };
     for (;; ++ks) {
-        wait_left(wait_left, nk - 2 - ks, std::integral_constant<int, NBUF - 2>{});
+        if constexpr (DRAWN) wait_left(wait_left, nk - 2 - ks, std::integral_constant<int, NBUF - 2>{});
+        else                 dev::dma_wait<0>();
         lds_barrier();
         buf = buf + 1 == NBUF ? 0 : buf + 1;
         half_step(f1, f0, buf, 0, 0, 0, C0{}, C0{});                // (past the end: not used)
