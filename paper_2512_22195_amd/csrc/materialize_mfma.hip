@@ -101,8 +101,8 @@ __device__ __forceinline__ void rope_cs(const RopeEntry& e, float p, float& c, f
 //  - behind the loop every wave is on its own: results leave registers as 8 or 16 bytes of a row (its four or two
 //    waves along the features fill 256 bytes), rotated with entries fetched at the start.
 // Two workgroups that share a tile (SK = 2) each hold half of every sum, wave by wave.  Up to 96 rows each wave leaves its fp32 partial in the
-// workspace (agent-scope stores) and arrives at a counter of its own, and of a pair the second to arrive adds the other's and finishes; from 128 rows on one of the
-// pair leaves its half and the other waits for it (below).  Either way the two workgroups share that work too.
+// workspace (agent-scope stores) and arrives at a counter of its own, and of a pair the second to arrive adds the other's and finishes; from 128 rows on (and hidden above 512) one of
+// the pair leaves its half and the other waits for it (below).  Either way the two workgroups share that work too.
 // Measured, us per launch with every layer's weights from HBM, 8 KV heads, when results went through LDS and whole workgroups arrived -> wave by wave, before
 // skewed starts (`first`) and draws:
 //   hidden 4096:  1000 rows 26.3 -> 24.0, 1206 rows 30.9 -> 29.2, 3501 rows 66.9 -> 60.6
@@ -124,7 +124,7 @@ template <int MI> struct TileShape {
 
 // WN: waves along the features; the other 8 / WN split the rows.  Few waves along the features read
 // fewer LDS bytes per product from MI = 6 on, as many at MI = 4, and store 16 bytes of a row instead of 8.
-template <int MI, int WN, int SK>
+template <int MI, int WN, int SK, bool DRAWN>
 __global__ __launch_bounds__(512) void materialize_tile_kernel(
         const void* __restrict__ hidden, const void* __restrict__ w_k, const void* __restrict__ w_v, int Hd, int Hkv, int total_rows, int row_tiles, MaterializeArgs a) {
     typedef TileShape<MI> S;
@@ -299,7 +299,6 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(
     // Nothing more to ask for.  Where halves are drawn for, the last steps are multiplied as they arrive; elsewhere all of them are waited for at first, in shorter code.  us
     // per launch, all waited for -> as they arrive (median of three runs, 8 KV heads): drawn, hidden 4096 1300 rows 27.96 -> 27.80, 1500 29.41 -> 29.20, hidden 8192 1500 49.8 -> 49.5,
     // 2048 61.6 -> 61.4 (1050 42.6 -> 43.0); not drawn, hidden 512 150 rows 5.8 -> 6.1, hidden 3072 150 11.5 -> 11.9, hidden 4096 224 13.5 -> 13.8, 3501 (one workgroup per tile) 54.0 -> 54.1.
-    constexpr bool DRAWN = SK == 2 && split_partials(MI) == 1;
     int drawn = 0;
     int32_t* const counter = a.ws_counters + (size_t)(rt * nct + ct) * kDecodeCounterStride + wave;
     if (DRAWN) {                                                    // (see below)
@@ -332,10 +331,11 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(
         // for a wave that has started and waits for nobody, so the wait ends whatever else the chip does.  That spares it its own stores and a trip
         // to the counter, and the memory half of the writes, for a trip more where both end at once: us per launch, both leave theirs -> one does, hidden
         // 4096 150 rows (tiles of 32) 14.2 -> 15.0, 300 (64) 15.9 -> 16.4, 512 (64) 17.9 -> 18.2, 700 (96) 21.6 -> 21.6, 1000 (128) 24.2 -> 23.9; hidden 3072 150 rows 11.7 ->
-        // 12.4, 700 (96) 18.3 -> 18.2; hidden 8192 700 (96) 34.3 -> 34.6, 1000 rows 40.6 -> 39.2, 1500 (192) 52.0 -> 50.0, 2048 (256) 64.2 -> 61.8 (the last four with the draw waited for).  (In 8-byte pieces chunk passes of 1000 tokens took 397 us for 393, 311 for 309 at hidden 8192.)
+        // 12.4, 700 (96) 18.3 -> 18.2; hidden 8192 700 (96) 34.3 -> 34.6, 1000 rows 40.6 -> 39.2, 1500 (192) 52.0 -> 50.0, 2048 (256) 64.2 -> 61.8 (the last three with the draw waited for);
+        // hidden 768 900 rows (128) 12.2 -> 11.2, 1024 12.6 -> 11.7, 2048 15.4 -> 15.2, 3072 18.9 -> 18.6; hidden 512, where a wave draws at its end, 11.1 -> 11.6: not there.  (In 8-byte pieces chunk passes of 1000 tokens took 397 us for 393, 311 for 309 at hidden 8192.)
         constexpr int NP = XB * 2 * PB;
         const int tile = rt * nct + ct;
-        float* const halves = a.ws_partials + (size_t)tile * split_partials(MI) * 8 * (BM * 16);
+        float* const halves = a.ws_partials + (size_t)tile * (DRAWN ? 1 : 2) * 8 * (BM * 16);
         auto leave = [&](float* to) {
 #pragma unroll
             for (int i = 0; i < NP; ++i) {
@@ -414,11 +414,11 @@ __global__ __launch_bounds__(512) void materialize_tile_kernel(
     }
 }
 
-template <int MI, int WN, int SK>
+template <int MI, int WN, int SK, bool DRAWN = SK == 2 && split_drawn(MI, 4096)>
 hipError_t launch_tile(const MaterializeArgs& a, int total_rows, hipStream_t s) {
     const int row_tiles = (total_rows + 32 * MI - 1) / (32 * MI), nct = 2 * a.Hkv;
     const int grid_tiles = SK == 1 && nct % 4 == 0 ? (row_tiles + 1) / 2 * 2 : row_tiles;
-    hipLaunchKernelGGL((materialize_tile_kernel<MI, WN, SK>), dim3(nct * grid_tiles * SK), dim3(512), 0, s,
+    hipLaunchKernelGGL((materialize_tile_kernel<MI, WN, SK, DRAWN>), dim3(nct * grid_tiles * SK), dim3(512), 0, s,
                        a.hidden, a.w_k, a.w_v, a.Hd, a.Hkv, total_rows, row_tiles, a);
     return hipGetLastError();
 }
@@ -441,12 +441,12 @@ hipError_t launch_tiled(const MaterializeArgs& a, int total_rows, hipStream_t s)
     auto halved = [&](int mi) {
         const int64_t tiles = groups(mi);
         return (a.Hd % (2 * BK)) == 0 && tiles * 2 <= 256 && 32 * mi <= most_split_rows(a.Hd, a.table != nullptr) && a.ws_partials &&
-               tiles * split_partials(mi) * (32 * mi) * D <= a.ws_partial_floats && tiles * kDecodeCounterStride <= a.ws_n_counters;
+               tiles * split_partials(mi, a.Hd) * (32 * mi) * D <= a.ws_partial_floats && tiles * kDecodeCounterStride <= a.ws_n_counters;
     };
     if (halved(1)) return launch_tile<1, 4, 2>(a, total_rows, s);
     if (halved(2)) return launch_tile<2, 4, 2>(a, total_rows, s);
     if (halved(3)) return launch_tile<3, 4, 2>(a, total_rows, s);
-    if (halved(4)) return launch_tile<4, 2, 2>(a, total_rows, s);
+    if (halved(4)) return split_drawn(4, a.Hd) ? launch_tile<4, 2, 2>(a, total_rows, s) : launch_tile<4, 2, 2, false>(a, total_rows, s);
     if (halved(5)) return launch_tile<5, 4, 2>(a, total_rows, s);
     if (halved(6)) return launch_tile<6, 2, 2>(a, total_rows, s);
     if (halved(8)) return launch_tile<8, 2, 2>(a, total_rows, s);

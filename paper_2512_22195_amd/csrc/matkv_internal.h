@@ -127,8 +127,10 @@ inline int max_q_rows(const matkv_config& c) { return c.max_tail_tokens; }
 constexpr int kSplitTiles = 128;    // half the compute units: two workgroups per tile
 // Rows of the tallest projection tile that is split, of a chunk's rows or a question's (materialize_mfma.hip).
 inline int most_split_rows(int hidden, bool question) { return hidden >= 8192 ? 256 : hidden >= 2560 && !question ? 192 : 128; }
-// Partial tiles that the two workgroups of a split tile leave: both theirs up to 96 rows, one of them from 128 rows on (mi: rows / 32).
-constexpr int split_partials(int mi) { return mi >= 4 ? 1 : 2; }
+// Whether one of the two workgroups of a split tile leaves its half (which one is drawn) or both leave theirs: tiles of 128 rows and more (mi: rows / 32), unless all
+// steps of half the axis are in flight at once, as they are up to hidden 512 (materialize_mfma.hip).  The partial tiles that are left follow from it.
+constexpr bool split_drawn(int mi, int hidden) { return mi >= 4 && hidden > 512; }
+constexpr int split_partials(int mi, int hidden) { return split_drawn(mi, hidden) ? 1 : 2; }
 
 inline WorkspaceLayout workspace_layout(const matkv_config& c) {
     WorkspaceLayout W;

@@ -268,7 +268,9 @@ def test_materialize_hidden_sizes_bf16(hidden, T):
     # workgroups that start behind the last round of copies and go round: two halves of 9, 7, 21, 11 and 40 steps, 19 steps by one
     [(1152, 150, 8), (896, 300, 8), (2688, 520, 8), (1408, 1000, 8), (5120, 790, 8), (1216, 1000, 8), (1216, 500, 3)] +
     # row tiles that share weight rows on an XCD counted in every second and every fourth: an odd number of KV heads
-    [(1152, 1300, 3), (896, 724, 5), (2688, 230, 7), (1408, 1500, 5), (1216, 2100, 3), (1024, 2900, 7)])
+    [(1152, 1300, 3), (896, 724, 5), (2688, 230, 7), (1408, 1500, 5), (1216, 2100, 3), (1024, 2900, 7)] +
+    # split tiles of 128 rows around the hidden size from which halves are drawn for
+    [(384, 900, 8), (512, 1024, 8), (640, 1000, 8), (512, 2000, 4)])
 def test_materialize_tile_heights(hidden, T, Hkv):
     """Tiled projection: every tile height of both forms (two workgroups per tile: 32, 64, 96, 128
     rows; one: 96, 128, 192, 256) just past the row count where the one before ends, hidden axes of one
