@@ -262,7 +262,7 @@ matkv_status matkv_assemble(matkv_ctx* ctx, const matkv_page* pages_host,
  * number of units (at most cap), or -1 on a bad argument.  Either output may be NULL.  (Where these
  * units would leave compute units idle or waiting, decode launches take the runs of
  * matkv_plan_even_units instead.)  Plain pages; matkv_plan_decode_units_of takes the pages' format (over
- * E4M3 pages the unit with the tail gets up to 128 page tokens fewer, while units have 128 tokens). */
+ * E4M3 pages the unit with the tail gets up to 128 page tokens fewer, while units have 192 tokens, or 128 of one page). */
 int32_t matkv_plan_decode_units(const matkv_config* cfg, const int32_t* page_tokens_host,
                                 int32_t n_pages, int32_t batch, int32_t q_len,
                                 int32_t* unit_tokens_out, int32_t* unit_items_out, int32_t cap);

@@ -1039,15 +1039,18 @@ bool step_by_instance(const matkv_config& cfg, size_t uses, size_t distinct, int
 
 // How an instance's cache is cut into decode units, one workgroup per (unit, KV head).  Over compressed pages a unit walks its codes first and asks for
 // the tail behind them, a round trip of its own, and the launch ends with it (8B shape, one user of 10 000 tokens: 8.4 us against 7.5 of the others): the
-// unit that has the tail gets 128 tokens fewer, unless the tail fills it anyway.  us per pass, eight steps of eight layers, one 8B user of 10 000 compressed
-// tokens 820 -> 818, 5000 737 -> 708, 2000 655 -> 629, 700 571 -> 554, two of 5000 866 -> 854, four of 3000 1000 -> 925, one 3B user of 20 000 994 -> 953; of
-// 750 with a 200-row question, whatever the tail fills, 298 -> 325.  (256 fewer: in the mean the same.  Plain pages, 32 or 64 fewer: 0.98 to 1.02.)
-// Not where units are shorter than that, as they can be where the configuration fixes their number: several would come to lie behind the pages' end and
+// unit that has the tail gets 128 tokens fewer, unless the tail fills it anyway (of 750 with a 200-row question, whatever the tail fills, 298 -> 325 us a pass).
+// Units below 192 tokens over several pages stay even: a longer unit is a wave that starts or goes on behind one more page boundary, whose record it has
+// to look up.  us per layer step, even -> spared: one 8B user of 3 x 214 tokens 8.3 -> 9.1, of 6 x 65 8.9 -> 9.5, one 3B user of 8 x 88 8.4 -> 9.1 (left even); of 1 x
+// 436 8.8 -> 8.1, one 3B user of 1 x 532 9.1 -> 8.0, two 8B users of 10 x 522 14.1 -> 13.0, one of 40 x 371 15.1 -> 14.3, four of 21 x 80 12.8 -> 13.1 (the worst); one of 4 x 1295, left even, would gain (11.3 -> 10.4).  Of 209
+// seeded steps (3B, 8B, 70B; 1 to 10 users of 130 to 15 000 tokens) the 136 that spare take 1/1.038 of the time in the mean; the 73 left even would have been between 0.916 and
+// 1.15 times as fast.  (256 fewer: in the mean the same.  Plain pages, 32 or 64 fewer: 0.98 to 1.02.)
+// Nor where units are below 128 tokens, as they can be where the configuration fixes their number: several would come to lie behind the pages' end and
 // fall away, and a step recorded over one table would not fit the next.
 struct DecodeCut { int units, tail_tokens; };       // units; tokens that the tail counts for
-DecodeCut decode_cut(const matkv_config& cfg, int batch, long page_tokens, int q_len, int kv_fmt) {
+DecodeCut decode_cut(const matkv_config& cfg, int batch, long page_tokens, int n_pages, int q_len, int kv_fmt) {
     const int tail = q_len + (cfg.max_tail_tokens - q_len) / 2, units = choose_decode_units(cfg, batch, page_tokens + tail);
-    const bool spares = kv_fmt == MATKV_PAGE_E4M3 && (long)std::max(tail + 1, 128) * units <= page_tokens + tail;
+    const bool spares = kv_fmt == MATKV_PAGE_E4M3 && (long)std::max(tail + 1, n_pages > 1 ? 192 : 128) * units <= page_tokens + tail;
     return {units, tail + (spares ? 128 : 0)};
 }
 
@@ -1066,7 +1069,7 @@ DecodeLayout lay_out_decode(const matkv_config& cfg, const TableLayout& tl, cons
         const matkv_page* pg = pages ? pages + (size_t)b * cfg.max_pages : nullptr;
         long inst_tokens = 0;
         for (int p = 0; p < n_pages[b]; ++p) inst_tokens += pg[p].n_tokens;
-        const DecodeCut c = decode_cut(cfg, batch, inst_tokens, insts[b].q_len, kv_fmt);
+        const DecodeCut c = decode_cut(cfg, batch, inst_tokens, n_pages[b], insts[b].q_len, kv_fmt);
         insts[b].dunit0 = L.n_dunits;
         insts[b].n_dunits = build_units(pg, n_pages[b], b, c.units, c.tail_tokens, cfg.max_tail_tokens, items, n_items, dunits, &L.n_dunits, scales_off);
     }
@@ -1902,7 +1905,7 @@ int32_t matkv_plan_decode_units_of(const matkv_config* cfg, const int32_t* page_
         pages[p].format = format;
         inst_tokens += page_tokens[p];
     }
-    const DecodeCut c = decode_cut(*cfg, batch, inst_tokens, q_len, format);
+    const DecodeCut c = decode_cut(*cfg, batch, inst_tokens, n_pages, q_len, format);
     std::vector<Item> items((size_t)kMaxDecodeUnitsPerInstance + n_pages + 2);
     std::vector<Unit> units((size_t)kMaxDecodeUnitsPerInstance);
     int n_items = 0, n_units = 0;

@@ -117,7 +117,8 @@ def test_decode_partition_covers_every_token_once_and_is_balanced(mk):
 
 def test_decode_partition_over_compressed_pages(mk):
     """Host logic: over compressed pages the unit with the tail has up to 128 page tokens fewer than over plain ones, the others share them
-    evenly, and there are as many units, also where the configuration fixes a number of them that leaves each a few tokens."""
+    evenly, and there are as many units, also where the configuration fixes a number of them that leaves each a few tokens.  Units of
+    several pages have to have 192 tokens for that, of one page 128."""
     rng = np.random.default_rng(5)
     spared = short = 0
     for trial in range(400):
@@ -130,7 +131,7 @@ def test_decode_partition_over_compressed_pages(mk):
         codes, _ = mk.plan_decode_units(cfg, lens, batch, q, mk.PAGE_E4M3)
         assert len(codes) == len(plain) and sum(codes) == sum(plain) == sum(lens)
         tail = q + (max_tail - q) // 2
-        if len(plain) == 1 or tail * len(plain) >= sum(lens) + tail or sum(lens) + tail < 128 * len(plain):
+        if len(plain) == 1 or tail * len(plain) >= sum(lens) + tail or sum(lens) + tail < (192 if len(lens) > 1 else 128) * len(plain):
             assert codes == plain
             short += len(plain) > 1
         else:
@@ -141,6 +142,9 @@ def test_decode_partition_over_compressed_pages(mk):
     assert spared > 50 and short > 30
     cfg = mk.make_config(2, 16, 4, 128, 4096, "bf16", 500000.0, 1, 1, 8, decode_units=16)
     assert len(mk.plan_decode_units(cfg, [200], 1, 4, mk.PAGE_E4M3)[0]) == 16
+    for lens, spares in (([214] * 3, False), ([642], True), ([88] * 8, False), ([1295] * 4, False), ([1295] * 5, True)):
+        cfg = mk.make_config(2, 32, 8, 128, 4096, "bf16", 500000.0, 1, 8, 72)
+        assert (mk.plan_decode_units(cfg, lens, 1, 64, mk.PAGE_E4M3) != mk.plan_decode_units(cfg, lens, 1, 64)) == spares
     with pytest.raises(mk.MatKVError):
         mk.plan_decode_units(cfg, [200], 1, 4, 2)
     with pytest.raises(mk.MatKVError):
