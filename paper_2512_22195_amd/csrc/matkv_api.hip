@@ -2282,10 +2282,12 @@ matkv_status matkv_chunk_attn(matkv_ctx* c, int32_t layer, const void* q, const 
     // compute units - a good third more where the walks are long, beside which a workgroup's start is little.  us with 64 / 128 / 256 rows: 8B shape,
     // 192 tokens 7.8 / 8.5, 256 9.0 / 9.2, 280 10.3 / 9.7, 512 14.6 / 12.2 / 17.2, 1000 27.4 / 19.3 / 28.9, 2100 70 / 51.0 / 56.3, 2600 100 / 72.1 / 74.1, 3000
     // 127 / 89.2 / 87.9; 3B 256 9.1 / 9.1, 280 10.3 / 9.6, 512 14.3 / 12.1, 2800 92 / 63.8 / 73.9, 3501 129 / 92.4 / 96.2, 4000 167 / 114.2 / 114.8; 70B 192 8.1 / 8.5,
-    // 200 9.2 / 8.6, 256 9.5 / 9.2, 512 17.1 / 13.7, 1024 43.8 / 29.4 / 33.0, 1060 43.9 / 35.4 / 33.7, 1300 58 / 44.6 / 41.2; one to four KV heads as 8B.
+    // 200 9.2 / 8.6, 256 9.5 / 9.2, 512 17.1 / 13.7, 1024 43.8 / 29.4 / 33.0, 1060 43.9 / 35.4 / 33.7, 1300 58 / 44.6 / 41.2.
+    // The first line, from 193 tokens on, by the 64-row workgroups, time of 64 over 128 rows at 224 / 257 / 288 tokens: 1 to 16 KV heads of 1 query head 0.89 / 0.97 / 0.98, of 4, 1 to 8 heads
+    // 0.97 / 0.97 / 1.02, 16 heads (224 workgroups) 1.01 / 1.09 / 1.14; of 8, 1 to 4 heads 0.975 / 0.97 / 1.025, 8 heads (224) 1.01 / 1.09 / 1.135.
     const long chunk_rows = (long)n_tokens * (cfg.n_q_heads / cfg.n_kv_heads);
     auto workgroups = [&](long rows) { return (chunk_rows + rows - 1) / rows * cfg.n_kv_heads; };
-    const bool shortest = n_tokens <= 192 || (n_tokens <= 256 && chunk_rows <= 1024);
+    const bool shortest = n_tokens <= 192 || (n_tokens <= 272 && workgroups(64) <= 192);
     a.tile_rows = shortest && workgroups(64) <= 512 ? 64 : workgroups(256) <= (n_tokens >= 2000 ? 352 : 256) ? 128 : 256;
     a.scale_log2e = c->scale_log2e;
     a.out_f32 = cfg.dtype == MATKV_BF16 && cfg.out_f32;

@@ -1500,10 +1500,12 @@ def test_attention_refuses_a_table_whose_slot_is_being_reloaded():
     ("chunk-g1", 2, 2, 128, "bf16", [130], None),
     ("chunk-g2", 4, 2, 128, "bf16", [100, 129], None),
     ("chunk-g8", 8, 1, 128, "bf16", [77, 300], None),
-    # 64-row tiles up to 256 tokens, of groups of 8 to 192 (ragged rows of a wave, of a tile; full tiles), 128-row tiles beyond
+    # 64-row tiles up to 192 tokens, up to 272 while they are 192 workgroups (ragged rows of a wave, of a tile; full tiles), 128-row tiles beyond
     ("chunk-g3", 6, 2, 128, "bf16", [5, 6, 85, 86, 511, 512, 513], None),
     ("chunk-g4-line", 8, 2, 128, "bf16", [255, 256, 257, 300], None),
     ("chunk-g8-line", 16, 2, 128, "bf16", [191, 192, 193, 256], None),
+    ("chunk-line-heads", 64, 8, 128, "bf16", [192, 193, 256], None),     # 200 workgroups at 193 tokens
+    ("chunk-line-few", 8, 1, 128, "bf16", [193, 271, 272, 273], None),
     ("chunk-g8-tiles", 16, 2, 128, "bf16", [8, 9, 16, 505, 520, 700], None),
     ("chunk-g1-tiles", 2, 2, 128, "bf16", [63, 64, 65, 512, 640], None),
     ("chunk-f32", 4, 2, 64, "f32", [50, 9], 56),                      # row-per-workgroup kernel
