@@ -359,10 +359,12 @@ matkv_status matkv_decode_attn_static(matkv_ctx* ctx, int32_t layer, const void*
  * to all page tokens and tail rows 0..tail_len[b]-1, the row just written included.
  * hidden: device [batch][hidden]; w_k, w_v: [Hkv*D][hidden]; q/out: [batch][Hq][D].
  * Call matkv_advance first, as before matkv_materialize_tail.  On bf16, head_dim 128, hidden a
- * multiple of 4096 and the default decode kernel the projection's weight reads overlap the
- * cache reads inside one kernel, also where the batch shares few pages (up to 12 MB a layer and instance would be read
- * twice, of caches up to 192 MB a layer): that kernel reads every instance's cache for itself; on fp32 with head_dim * hidden up to 16384 (32768 from eight instances on)
- * the workgroup that holds an instance's tail projects its row first; other configurations run the two launches above.
+ * multiple of 4096 or 3072, up to four instances, up to four query heads per KV head and the default
+ * decode kernel the projection's weight reads overlap the cache reads inside one kernel, which reads every
+ * instance's cache for itself: also where the batch shares pages, as long as at most 12 MB a layer
+ * and instance are read twice, of caches up to 192 MB a layer and of nearly even length.  On fp32 with
+ * head_dim * hidden up to 16384 (32768 from eight instances on) the workgroup that holds an instance's
+ * tail projects its row first.  Other configurations run the two launches above.
  * MATKV_EINVAL if some tail is empty. */
 matkv_status matkv_decode_step(matkv_ctx* ctx, int32_t layer, const void* hidden, const void* w_k,
                                const void* w_v, const void* q, const void* table, void* tail_k,

@@ -1032,7 +1032,11 @@ std::pair<size_t, size_t> count_page_tokens(const matkv_config& cfg, const matkv
 // three, 39 22.0 -> 18.1 in four layers, 65 23.5 -> 26.1; four, 39 24.6 -> 22.2, 61 22.9 -> 22.1, 74 23.5 -> 24.1.  3B: two, 41 20.8 -> 21.1, four, 61 21.3 -> 21.0.  Of
 // compressed pages (8B) two, 20 18.6 -> 13.3, 41 22.5 -> 23.0, four, 61 25.3 -> 23.8; (3B) four, 74 24.2 -> 25.2.  Long caches end it: with 5 to 25 % of the uses
 // shared, four users of 82 MB 1.04 to 1.24 times as fast, 131 MB in all 1.05, 164 1.00 to 1.06, 184 1.02, 246 0.985.
-bool step_by_instance(const matkv_config& cfg, size_t uses, size_t distinct, int batch, int kv_fmt) {
+// A ragged batch ends it too, since the launch waits for the longest unit by instance, and shared units are even.  605 seeded steps of two to four users within those lines,
+// by how many tokens longer it is (of codes half as many): up to 100 1.45 times as fast in the mean and 1.10 at least, 100 to 200 1.19, 200 to 300 1.10, 300 to 400 1.06, more
+// 1.005 and 0.951 at least (8B, four users of up to 12 000 tokens with 1895 in common 34.0 -> 35.8).
+bool step_by_instance(const matkv_config& cfg, size_t uses, size_t distinct, int batch, int kv_fmt, long longest, long longest_shared) {
+    if (longest - longest_shared > (kv_fmt == MATKV_PAGE_E4M3 ? 800 : 400)) return false;
     const size_t row = (size_t)2 * cfg.n_kv_heads * cfg.head_dim * (kv_fmt == MATKV_PAGE_E4M3 ? 1 : 2);
     return (uses - distinct) * row <= (size_t)batch * 12000000 && uses * row <= 192000000;
 }
@@ -1106,7 +1110,10 @@ DecodeLayout lay_out_decode(const matkv_config& cfg, const TableLayout& tl, cons
     // (a fused step over the units by instance walks a shared page once for each of its users: its own answer)
     if (L.n_sunits > 0 && fused_step_shape(cfg.dtype, cfg.head_dim, cfg.n_q_heads / cfg.n_kv_heads, cfg.hidden, batch)) {
         count();
-        L.step_by_instance = step_by_instance(cfg, uses, distinct, batch, kv_fmt);
+        long longest = 0, longest_shared = 0;
+        for (int u = 0; u < L.n_dunits; ++u) longest = std::max<long>(longest, dunits[u].page_tokens);
+        for (int u = 0; u < L.n_sunits; ++u) longest_shared = std::max<long>(longest_shared, sunits[u].u.page_tokens);
+        L.step_by_instance = step_by_instance(cfg, uses, distinct, batch, kv_fmt, longest, longest_shared);
         if (L.step_by_instance) L.step_past_llc = past_llc(by_instance, L.n_dunits, true);
     }
     return L;

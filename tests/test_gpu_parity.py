@@ -1955,6 +1955,17 @@ def test_decode_step_over_shared_units_in_two_launches(Hq, hidden, retrieved, us
     _chain_parity(case, fused=True, use_graph=use_graph)
 
 
+def test_decode_step_over_a_ragged_batch_that_shares_pages():
+    """Two users with a page in common: the step is the fused launch while their caches are nearly even, two launches where the longest unit
+    by instance is 400 tokens longer than the shared ones."""
+    def launches(lens):
+        case = Case("shared-step-ragged", n_layers=1, Hq=32, Hkv=8, D=128, hidden=4096, dtype="bf16", chunk_lens={0: 1500, **{1 + b: n for b, n in enumerate(lens)}},
+                    retrieved=[[0, 1 + b] for b in range(len(lens))], q_lens=[5] * len(lens), steps=1)
+        return _step_launches(case)
+
+    assert launches([8000, 8000]) == 1 and launches([12000, 3000]) == 1 and launches([16000, 500]) == 2
+
+
 @pytest.mark.parametrize("first", ["few", "many"])
 def test_recorded_step_replays_over_few_and_many_shared_pages(first):
     """A decode step recorded over a table with few shared pages (the fused launch) replays over one with many (two launches by itself), and the
