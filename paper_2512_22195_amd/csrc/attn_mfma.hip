@@ -249,7 +249,7 @@ __device__ __forceinline__ void merge_decode_step(const KernelArgs& a, const Ste
 // A projection wave of a fused decode step: one task = one rotary pair of K or of V of KV head
 // kvh for a group of FR instances; the pair is stored (bf16, agent scope) at the newest tail
 // row of each instance.  The n_waves projection waves of this KV head share the tasks round-robin.
-template <int FR>
+template <int FR, bool AHEAD>
 __device__ __forceinline__ void projection_tasks(const KernelArgs& a, const StepArgs& f, const InstanceInfo* __restrict__ insts,
                                                  int kvh, int wave_id, int n_waves, int lane) {
     typedef uint16_t T;
@@ -261,12 +261,12 @@ __device__ __forceinline__ void projection_tasks(const KernelArgs& a, const Step
         const T* w0 = w + ((size_t)kvh * D + j) * f.Hd;
         const T* w1 = w0 + (size_t)(D / 2) * f.Hd;
         const T* x = reinterpret_cast<const T*>(f.hidden) + (size_t)b0 * f.Hd;
-        // Several instances: where the pair goes and how far it is turned is asked for ahead of the weights instead of behind the sums (us per pass of eight
-        // layers, three 3B users of a few hundred tokens 1368 -> 1318, four 8B users of 3000 1189 -> 1161, two of 5000 compressed 906 -> 867).  For one these are
-        // scalar loads, which the weights would wait for (8B, 10 000 tokens 988 -> 1022); behind the weights it gives less (1372, 1182, 887; 989).
+        // AHEAD (several instances): where the pair goes and how far it is turned is asked for ahead of the weights instead of behind the sums (us per pass of eight
+        // layers, three 3B users of a few hundred tokens 1368 -> 1318, four 8B users of 3000 1189 -> 1161).  For one these are scalar loads, which the weights would wait
+        // for (8B, 10 000 tokens 988 -> 1022); behind the weights it gives less (1372, 1182; 989).  Which launches do, see launch_step_v.
         struct Place { int row; int64_t pos_base; RopeEntry turn; } at;
         auto look_up = [&](int b) { at.row = insts[b].tail_len - 1; at.pos_base = insts[b].pos_base; at.turn = f.rope[j]; };
-        if (FR > 1) look_up(min(b0 + lane % FR, f.batch - 1));
+        if (AHEAD) look_up(min(b0 + lane % FR, f.batch - 1));
         float acc0[FR], acc1[FR];
         if (f.Hd % 4096 == 0) gemv::pair_dots<FR, 8>(w0, w1, x, (size_t)f.Hd, f.batch - b0, f.Hd, lane, acc0, acc1);
         else                  gemv::pair_dots<FR, 6>(w0, w1, x, (size_t)f.Hd, f.batch - b0, f.Hd, lane, acc0, acc1);   // multiples of 3072
@@ -275,10 +275,10 @@ __device__ __forceinline__ void projection_tasks(const KernelArgs& a, const Step
 #pragma unroll
             for (int r = 0; r < FR; ++r) if (lane == r) { r0 = acc0[r]; r1 = acc1[r]; }
             const int b = b0 + lane;
-            const int row = FR > 1 ? at.row : insts[b].tail_len - 1;
+            const int row = AHEAD ? at.row : insts[b].tail_len - 1;
             if (row >= 0 && row < a.max_tail) {
                 if (kv == 0) {
-                    if (FR == 1) look_up(b);
+                    if (!AHEAD) look_up(b);
                     gemv::rotate_pair(at.turn, (float)(at.pos_base + row), r0, r1);
                 }
                 T* out = reinterpret_cast<T*>(const_cast<void*>(kv == 0 ? a.tail_k : a.tail_v)) +
@@ -340,10 +340,12 @@ __device__ __forceinline__ void merge_shared(const KernelArgs& a, const int4* us
 // its own partial, and the workgroup arrives at every user's counter: the last arrival at an
 // instance's counter folds that instance's partial slots.
 // NT: the cache's rows are not left in the last-level cache.
-template <int G, int NW, int MS, int PF, int FR, bool F8, bool SH = false, bool NT = false>
-__global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && PF <= 2)) ? 2 : 1) void attn_mfma_kernel(
+// STEP: instances per projection task of a fused step (0: attention alone); negative: the same, their places looked up behind the sums.
+template <int G, int NW, int MS, int PF, int STEP, bool F8, bool SH = false, bool NT = false>
+__global__ __launch_bounds__((STEP != 0 ? 2 : 1) * NW * 64, (STEP != 0 || (MS == 1 && PF <= 2)) ? 2 : 1) void attn_mfma_kernel(
         const Unit* __restrict__ units, const InstanceInfo* __restrict__ insts, const Item* __restrict__ items, int n_units,
         KernelArgs a, StepArgs f) {
+    constexpr int FR = STEP < 0 ? -STEP : STEP;
     constexpr int ROWS = 16 * MS;                       // (row, head) pairs per workgroup
     constexpr int NTH = (FR > 0 ? 2 : 1) * NW * 64;     // threads of the workgroup
     typedef uint16_t T;
@@ -416,7 +418,7 @@ __global__ __launch_bounds__((FR > 0 ? 2 : 1) * NW * 64, (FR > 0 || (MS == 1 && 
             // the waves of the projection-only workgroups come first: they have nothing else to do
             const int extra = (f.workgroups - n_units) * 2 * NW;
             const int id = walks ? extra + (int)blockIdx.x * NW + (wave - NW) : ((int)blockIdx.x - n_units) * 2 * NW + wave;
-            projection_tasks<FR>(a, f, insts, kvh, id, extra + n_units * NW, lane);
+            projection_tasks<FR, (STEP > 1)>(a, f, insts, kvh, id, extra + n_units * NW, lane);
         }
     } else {
     // Q in operand layout: lane (c16, g4) holds, for sub-tile j and chunk c of the head
@@ -748,8 +750,15 @@ hipError_t launch_step_v(const AttnArgs& a, const MaterializeArgs& m, hipStream_
     f.workgroups = a.n_units + extra;
     dim3 grid(f.workgroups, a.Hkv, 1), block(2 * NW * 64);
     const bool f8 = a.kv_fmt == MATKV_PAGE_E4M3;
+    // Several instances' places are looked up ahead over plain pages (298 seeded steps of two to four users take 1/1.025 of the time in the mean), and over compressed
+    // ones where a unit with a tail has been spared tokens.  302 such steps, against neither: both throughout 1/1.011 of the time and up to 1.05 (3B, four users of 3 x 158 tokens
+    // 10.4 -> 11.0 us a layer), spared with the places behind 1/1.004 and up to 1.10, ahead and not spared 1.002 and up to 1.06, both where spared and neither elsewhere 1/1.012
+    // and up to 1.045 (two 8B users of 5000 906 -> 867 a pass).
     auto kern = a.past_llc ? (f8 ? attn_mfma_kernel<G, NW, 1, 2, FR, true, false, true> : attn_mfma_kernel<G, NW, 1, 2, FR, false, false, true>)
                            : (f8 ? attn_mfma_kernel<G, NW, 1, 2, FR, true> : attn_mfma_kernel<G, NW, 1, 2, FR, false>);
+    if constexpr (FR > 1) {
+        if (f8 && !a.tail_spared) kern = a.past_llc ? attn_mfma_kernel<G, NW, 1, 2, -FR, true, false, true> : attn_mfma_kernel<G, NW, 1, 2, -FR, true>;
+    }
     hipLaunchKernelGGL(kern, grid, block, 0, s,
                        reinterpret_cast<const Unit*>(a.table + a.off_units), reinterpret_cast<const InstanceInfo*>(a.table + a.off_inst),
                        reinterpret_cast<const Item*>(a.table + a.off_items), a.n_units, k, f);

@@ -75,6 +75,7 @@ struct TableHost {
     int min_tail_len = 0;
     int n_decode_slots = 0;   // partial slots a decode launch writes (units, or (unit, user) pairs when shared)
     bool step_by_instance = false;      // a fused decode step reads every instance's cache for itself, beside a shared partition
+    bool tail_spared = false; // compressed pages: some unit by instance that has a tail has fewer page tokens than the others
     bool past_llc = false, step_past_llc = false;   // decode launches, fused steps leave the cache's rows out of the last-level cache (rows_pass_llc)
     std::vector<const void*> slots;   // distinct slots its pages point into
 };
@@ -1051,18 +1052,18 @@ bool step_by_instance(const matkv_config& cfg, size_t uses, size_t distinct, int
 // 1.15 times as fast.  (256 fewer: in the mean the same.  Plain pages, 32 or 64 fewer: 0.98 to 1.02.)
 // Nor where units are below 128 tokens, as they can be where the configuration fixes their number: several would come to lie behind the pages' end and
 // fall away, and a step recorded over one table would not fit the next.
-struct DecodeCut { int units, tail_tokens; };       // units; tokens that the tail counts for
+struct DecodeCut { int units, tail_tokens; bool spares; };      // units; tokens that the tail counts for
 DecodeCut decode_cut(const matkv_config& cfg, int batch, long page_tokens, int n_pages, int q_len, int kv_fmt) {
     const int tail = q_len + (cfg.max_tail_tokens - q_len) / 2, units = choose_decode_units(cfg, batch, page_tokens + tail);
     const bool spares = kv_fmt == MATKV_PAGE_E4M3 && (long)std::max(tail + 1, n_pages > 1 ? 192 : 128) * units <= page_tokens + tail;
-    return {units, tail + (spares ? 128 : 0)};
+    return {units, tail + (spares ? 128 : 0), spares && units > 1};
 }
 
 // Decode attention of a batch (insts: q_len is set): the units of every instance, and beside them the shared partition or
 // the even one where they apply.  sunits: the table's section of the shared partition; the even one's records follow dunits.
 struct DecodeLayout {
     int n_dunits = 0, n_sunits = 0;
-    bool even_built = false, even = false, past_llc = false;
+    bool even_built = false, even = false, past_llc = false, tail_spared = false;
     bool step_by_instance = false, step_past_llc = false;       // of a decode step in one launch
 };
 template <typename ScalesOff>
@@ -1074,6 +1075,7 @@ DecodeLayout lay_out_decode(const matkv_config& cfg, const TableLayout& tl, cons
         long inst_tokens = 0;
         for (int p = 0; p < n_pages[b]; ++p) inst_tokens += pg[p].n_tokens;
         const DecodeCut c = decode_cut(cfg, batch, inst_tokens, n_pages[b], insts[b].q_len, kv_fmt);
+        L.tail_spared |= c.spares;
         insts[b].dunit0 = L.n_dunits;
         insts[b].n_dunits = build_units(pg, n_pages[b], b, c.units, c.tail_tokens, cfg.max_tail_tokens, items, n_items, dunits, &L.n_dunits, scales_off);
     }
@@ -1842,7 +1844,7 @@ matkv_status matkv_assemble(matkv_ctx* c, const matkv_page* pages, const int32_t
     const DecodeLayout decode = lay_out_decode(cfg, c->tl, pages, n_pages, batch, kv_fmt, insts, items, &n_items, dunits,
                                                reinterpret_cast<SUnit*>(h + c->tl.off_sunits), scales_off);
     const int n_dunits = decode.n_dunits, n_sunits = decode.n_sunits;
-    th.even = decode.even; th.past_llc = decode.past_llc;
+    th.even = decode.even; th.past_llc = decode.past_llc; th.tail_spared = decode.tail_spared;
     th.step_by_instance = decode.step_by_instance; th.step_past_llc = decode.step_past_llc;
     // prefill: coarse partition (the question rows supply most of the parallelism)
     th.prefill = lay_out_prefill(cfg, pages, n_pages, q_len, batch, kv_fmt == MATKV_PAGE_E4M3, insts, items, &n_items, punits, scales_off);
@@ -2162,6 +2164,7 @@ static matkv_status attn_args(matkv_ctx* c, const char* name, int prefill, int32
     const bool even = !prefill && th->even;
     a.shared = !prefill && (th->n_sunits > 0 || even);
     a.past_llc = !prefill && th->past_llc;
+    a.tail_spared = !prefill && th->tail_spared;
     a.n_units = prefill ? th->prefill.n_units : (even ? 256 / c->cfg.n_kv_heads : a.shared ? th->n_sunits : th->n_dunits);
     a.max_units_inst = prefill ? th->prefill.max_units_inst : 0;
     a.batch = th->batch; a.total_q = th->total_q; a.kv_fmt = th->kv_fmt;

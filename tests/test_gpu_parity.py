@@ -1750,6 +1750,28 @@ def test_chain_with_compressed_blobs(batch, fused, files, tmp_path):
     chain.compare_attention(case, gpu["o_pre"], gpu["o_dec"], ref["pre"], ref["dec"])
 
 
+@pytest.mark.parametrize("Hq,hidden", [(2, 3072), (4, 4096), (6, 3072), (8, 4096)])
+@pytest.mark.parametrize("lens", [[450], [90, 60]], ids=["spared", "even"])
+def test_fused_step_of_several_users_over_compressed_pages(lens, Hq, hidden):
+    """Fused steps of two to four users over compressed pages with and without tokens spared for the tail, which look up where the new rows go ahead of
+    the projection or behind it, of every group size: tails and outputs against the oracle's chain."""
+    batch = 2 + Hq % 3
+    case = Case(f"f8-step-{Hq}-{len(lens)}", n_layers=1, Hq=Hq, Hkv=2, D=128, hidden=hidden, dtype="bf16", chunk_lens=dict(enumerate(lens * batch)),
+                retrieved=[list(range(len(lens) * b, len(lens) * (b + 1))) for b in range(batch)], q_lens=[5, 2, 9, 3][:batch],
+                steps=2, rope_base=500000.0, scale=1.0 / 8.0, q_scale=1.0, compressed=True)
+    from paper_2512_22195_amd import binding as mk
+    cfg = mk.make_config(1, Hq, 2, 128, hidden, "bf16", 500000.0, batch, len(lens), case.tail_cap)
+    assert (mk.plan_decode_units(cfg, lens, batch, 5, mk.PAGE_E4M3) != mk.plan_decode_units(cfg, lens, batch, 5)) == (len(lens) == 1)
+    assert _step_launches(case) == 1
+    inp = chain.make_chain_inputs(case)
+    gpu, ref = chain.run_gpu_chain(case, inp, fused=True), chain.run_oracle_chain(case, inp)
+    for (l, b), (Kt, Vt) in ref["tails"].items():
+        n = Kt.shape[1]
+        chain.compare_materialized(case, gpu["tail"][l, 0, b, :, :n], Kt, "tail K")
+        chain.compare_materialized(case, gpu["tail"][l, 1, b, :, :n], Vt, "tail V")
+    chain.compare_attention(case, gpu["o_pre"], gpu["o_dec"], ref["pre"], ref["dec"])
+
+
 def test_compressed_pages_argument_checks():
     from paper_2512_22195_amd import binding as mk
     case = Case("f8-args", n_layers=1, Hq=4, Hkv=2, D=128, hidden=128, dtype="bf16",
