@@ -147,7 +147,9 @@ const char* matkv_last_error(const matkv_ctx* ctx);
  * V[g][i][:] = Wv_g hidden[i].  k_out / v_out point at element [0][0][0] of a
  * [Hkv][token_stride][D] region (inside a blob, a slot or a private buffer); rows
  * 0..n_tokens-1 of each head are written.  A chunk uses pos0 = 0.  No bias, no norm:
- * hidden is whatever the layer would feed its K/V projections. */
+ * hidden is whatever the layer would feed its K/V projections.  The order of a row's sums follows
+ * from its place among the rows of the call: equal calls give equal bits, equal rows at different
+ * places agree to rounding (of matkv_materialize_tail too). */
 matkv_status matkv_materialize(matkv_ctx* ctx, const void* hidden, const void* w_k,
                                const void* w_v, int32_t n_tokens, int64_t pos0,
                                void* k_out, void* v_out, int64_t token_stride);

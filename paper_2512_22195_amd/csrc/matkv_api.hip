@@ -371,7 +371,10 @@ double prefill_form_time(int tile_rows, bool codes, long workgroups, long walk_t
 // of 2000 tables with 1 to 16 KV heads and 1 to 8 query heads to each 8 %, 1/1.11 and 1/1.08; six of those 158 were slower by 3 to 8 %, all of 12 to 23 us, when
 // 6 % were enough.  us a layer: 8B shape, two users of 145 rows over 631 tokens 22.4 -> 16.3, compressed, eleven of up to 83 rows over 10 800 345 -> 286;
 // 70B, eleven of 22 rows over 762 26.0 -> 19.3; 3B, compressed, nineteen of up to 42 rows over 27 000 501 -> 410.
-// Shorter caches would gain more and stay with the rules: 8B shape, 32 rows, in units -> uncut, sixteen users of 500 tokens 28.4 -> 17.5, one of 300 13.4 -> 11.8.
+// Shorter caches stay with the rules because their layouts are pinned as interface (tests hold matkv_plan_prefill's answers for them), not because the rules are
+// ahead there: 8B shape, 32 rows, in units -> uncut, sixteen users of 500 tokens 28.4 -> 17.5, one of 300 13.4 -> 11.8.
+// Of 6000 tables of those kinds and of 1 to 16 KV heads 268 are laid out another way than by the rules; 220 of them timed take 1/1.10 of the time in the mean, nine are more
+// than 2 % slower: 2 to 7 %, and one 22 % (fifteen users with 16 KV heads, compressed, 85 -> 104).
 struct PrefillShape {           // of an instance
     long rows, tokens, pieces;  // (question row, query head of one KV head) rows; cache and question; pages and tail
 };
@@ -569,6 +572,7 @@ PrefillLayout lay_out_prefill(const matkv_config& cfg, const matkv_page* pages, 
             for (int f = 0; f < 2; ++f) {
                 const long tiles_in_batch = tiles(f ? 256 : 128), one_round = 256 / std::max<long>(1, tiles_in_batch * cfg.n_kv_heads);
                 long before = 0;
+                // (up to 330 workgroups a KV head, which bounds the host's time: ten rounds at eight KV heads and little more than one at one, where more were not compared)
                 for (long u : {1l, 2l, 3l, 4l, 5l, 6l, 8l, 10l, 12l, 16l, 20l, 24l, 32l, std::min<long>(one_round, kMaxPrefillUnitsPerInstance)}) {
                     if (u < 1 || (u > 1 && u > most_tokens / 64) || u == before || tiles_in_batch * u > 330) continue;
                     before = u;
@@ -1126,7 +1130,9 @@ TableHost* find_table(matkv_ctx* c, const void* t) {
     return it == c->tables.end() ? nullptr : &it->second;
 }
 
-// Launch shapes and kernel choices are fixed when a call is recorded; they follow from these.
+// Launch shapes are fixed when a call is recorded; they follow from these.  Kernel choices are fixed too and need not: whether a step is the fused launch, whether rows
+// pass the last-level cache and whether places are looked up ahead may be other for a table that is assembled later, and each gives the right result over
+// every table of equal signature (the units by instance, the shared and the even ones are all there wherever they were).
 uint64_t fnv(std::initializer_list<int> f) {
     uint64_t h = 1469598103934665603ull;
     for (int v : f) { h ^= (uint64_t)(uint32_t)v; h *= 1099511628211ull; }
